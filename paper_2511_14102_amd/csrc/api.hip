@@ -429,11 +429,11 @@ int moe_draft_layer_int4_noalloc(moe_ctx *ctx, const moe_layer_desc *desc,
 
 // workspace of a prefill call: routing weights, sorted assignment indices and slots [T k], the
 // item count (one 256-byte line), the items, the operand tiles of x and of h (two planes) with
-// their tile row sums, and the per-slot outputs.
+// their group sums, a tile of zeros, and the per-slot outputs.
 // With shared experts: two plans (full chunk, ragged last chunk) and the buffers of one chunk of
 // `chunk` tokens through the bf16 kernels.
 struct PrefillLayout {
-    size_t w_all, sorted, slot_of, n_items, items, xt, x_sums, h_hi, h_lo, h_sums, obuf,
+    size_t w_all, sorted, slot_of, n_items, items, xt, x_sums, h_hi, h_lo, h_sums, zeros, obuf,
         plan_full, plan_tail, shared_ws, total;
     int max_items, chunk;
 };
@@ -455,6 +455,7 @@ static PrefillLayout prefill_layout(const moe_layer_desc &d, int T)
     L.h_hi = o;    o += align256(B.h_plane);
     L.h_lo = o;    o += align256(B.h_plane);
     L.h_sums = o;  o += align256(B.h_sums);
+    L.zeros = o;   o += align256(B.zeros);
     L.obuf = o;    o += align256(B.obuf);
     L.chunk = MOE_MAX_ASSIGN / d.top_k < MOE_MAX_TOKENS ? MOE_MAX_ASSIGN / d.top_k : MOE_MAX_TOKENS;
     L.plan_full = L.plan_tail = L.shared_ws = o;
@@ -512,8 +513,8 @@ int moe_draft_prefill_int4(moe_ctx *ctx, const moe_layer_desc *desc,
     p.items = (const PrefillItem *)(ws + L.items); p.n_items = (const int32_t *)(ws + L.n_items);
     p.sorted = (const int32_t *)(ws + L.sorted); p.slot_of = (const int32_t *)(ws + L.slot_of);
     p.w_all = (const float *)(ws + L.w_all);
-    p.xt = ws + L.xt; p.x_sums = (float *)(ws + L.x_sums);
-    p.h_hi = ws + L.h_hi; p.h_lo = ws + L.h_lo; p.h_sums = (float *)(ws + L.h_sums);
+    p.xt = ws + L.xt; p.x_sums = ws + L.x_sums;
+    p.h_hi = ws + L.h_hi; p.h_lo = ws + L.h_lo; p.h_sums = ws + L.h_sums; p.zeros = ws + L.zeros;
     p.obuf = (float *)(ws + L.obuf);
     p.y = y;
     { ProfScope t(ctx, MOE_KERNEL_ROUTE, st); launch_route(s, x, wr, bias, ids_out, (float *)(ws + L.w_all), conf_out, st); }

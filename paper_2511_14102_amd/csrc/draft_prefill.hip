@@ -5,26 +5,47 @@
 //
 //   prefill_plan_kernel    assignments sorted by expert, items, slot of every assignment
 //   prefill_stage_kernel   the items' tokens gathered into MFMA operand tiles (zero padded), and
-//                          the sum of each tile row (32 inputs), which the zero points need
-//   prefill_tile_kernel<gate/up>  one workgroup per (item, two slices of 32 intermediate rows):
+//                          each group's sum, in three bf16 pieces, for the zero points
+//   prefill_tile_kernel<gate/up>  one workgroup per (item, four slices of 32 intermediate rows):
 //                          per slice 64 pre-activations (32 gate, 32 up) x 64 tokens over all of
 //                          H, h = silu(gate) * up written as operand tiles of a bf16 value and
-//                          its bf16 remainder, plus the tile row sums of h
-//   prefill_tile_kernel<down>     one workgroup per (item, two tiles of 64 output rows): those
+//                          its bf16 remainder, plus the group sums of h
+//   prefill_tile_kernel<down>     one workgroup per (item, four tiles of 64 output rows): those
 //                          rows x 64 tokens over all of I, written to a per-slot fp32 buffer
 //   prefill_combine_kernel y[t] = sum over the token's k assignments of weight x slot output
 //
 // No kernel adds into memory another workgroup writes: every output element has one owner, so
 // the result does not depend on the order in which workgroups run.
 //
-// The tile kernel.  Its four waves each own one block of 16 weight rows in each of the
-// workgroup's 64-row weight tiles (the dword of that block in every lane's 16 bytes of a code
-// tile) and all four token blocks; the token operand tiles of a stage of k-steps are staged
-// through LDS once and read by all four waves (LDS double buffered, one barrier per stage; two
-// stages of global loads in flight).  Arithmetic as in the other draft kernels:
-// codes become the exact bf16 integers 128 + q, a group's products are summed by the matrix cores
-// (16x16x32 bf16, fp32 accumulate), and scale, zero point and the 128 offset are applied once per
-// group with the sum of the group's activations:  s * (acc - (z + 128) * sum).
+// The tile kernel.  Each of its four waves owns one 64-row weight tile per k-step of 32 inputs
+// (four row blocks of 16, one word of a lane's 16 bytes each) and all token blocks of the item.
+// A code is unpacked once per workgroup, straight into the MFMA operand registers of the only
+// wave that needs it; the token operand tiles are shared by the four waves and go from memory to
+// LDS without passing through registers.  An operand tile read from LDS feeds four MFMAs: with two
+// row blocks per wave the four SIMDs would ask LDS for 128 bytes a clock, all it delivers.
+//
+// Pipeline.  Operand tiles: stages of SK k-steps in four LDS buffers, requested three stages ahead,
+// one barrier per stage.  Codes: a rolling window of eight k-steps in registers, refilled as it is
+// consumed.  Every load is unconditional (past the end it repeats the last tile, and operand tiles
+// of k-steps past the end are zeros): a load inside a branch makes the compiler wait for ALL loads in
+// flight where the branch joins.  The four LDS buffers are four arrays on purpose: the compiler
+// then knows which transfer a read of LDS depends on and does not wait for the later ones.
+//
+// Arithmetic.  Codes become the exact bf16 integers 16 + q; a group's products are summed by the
+// matrix cores (16x16x32 bf16, fp32 accumulate) and enter the totals with one fused multiply-add by
+// the group's scale.  The zero points and the offset 16 are one more contraction, over groups
+// instead of inputs:  total = sum_G s_G acc_G + sum_G (-s_G (z_G + 16)) (sum of the group's x).
+// Both factors of the second sum are fp32 numbers cut into three bf16 pieces (exactly; of the nine
+// products of pieces all but the smallest are kept, 2^-32 of the result), eight k positions per
+// group, so that it runs on the matrix cores as well: a sixteenth of the k-steps (g = 128) instead of
+// a second multiply-add per group on the vector ALU, which the unpacking and the scales already load.
+//
+// Bound and figures (gate/up and down kernel; before: two row blocks per wave, operand tiles through
+// registers, offset 128, two multiply-adds per group).  Many tokens per expert: the matrix cores.
+// mixtral shape, 4096 tokens: 2028 and 1650 us, 951 and 1170 TFLOP/s counting both planes of h
+// (before: 3750 and 2933 us; a large library product reaches 1250 on this part).  phi shape, 512 tokens:
+// 181 and 165 us (406 and 261).  Few tokens per expert: the weight stream.  dsv2lite shape, 333 tokens
+// (31 per expert): 58 and 43 us for 197 and 98 MB (99 and 66).
 #include <hip/hip_runtime.h>
 #include "draft_common.h"
 
@@ -33,7 +54,8 @@ namespace moespeq {
 namespace {
 
 constexpr int kItemTokens = kPrefillChunk;        // 64 = four token blocks of 16
-constexpr int kTileThreads = 256;
+constexpr int kTileThreads = 256, kTileWaves = 4;
+constexpr int kXcds = 8;
 
 struct TileArgs {
     const char *q, *sz;              // int4 codes / scale(-zero) blobs of the routed experts
@@ -41,302 +63,402 @@ struct TileArgs {
     const PrefillItem *items;
     const int32_t *n_items;
     const char *act0, *act1;         // operand tiles [(item nk + u) 4 + tb] of 1 KiB: x, or h and its remainder
-    const float *sums;               // [(item nk + u)][64]: sum of each token's 32 values of tile u
-    char *h_hi, *h_lo;               // gate/up: out tiles [(item I/32 + slice) 4 + tb]
-    float *h_sums;                   // gate/up: out sums [(item I/32 + slice)][64]
+    const char *act_sums;            // group sums as operand tiles [(item nz + group / 4) 4 + tb]
+    const char *zeros;               // 4 KiB of zeros
+    char *h_hi, *h_lo, *h_sums;      // gate/up: out, the same layouts over I
     float *obuf;                     // down: out [item 64 + token][H]
-    int H, I, g;
+    int H, I;
 };
 
-// scale / zero entry of weight row (d, r) for group `grp` (gate/up: of slice `tile`; down: of row
-// tile `tile`), as the 32-bit {s, z} entry or the 16-bit scale of the symmetric format
-template <bool DOWN, bool SYM>
-__device__ inline uint32_t load_entry(const char *szb, int H, int I, int g, int tile, int grp, int r, int d)
-{
-    const size_t gu_entries = (size_t)(I / 32) * (H / g) * 64;
-    size_t e;
-    if constexpr (!SYM) {
-        e = DOWN ? gu_entries + (((size_t)grp * (H / 64) + tile) * 16 + r) * 4 + d
-                 : (((size_t)tile * (H / g) + grp) * 16 + r) * 4 + d;
-        return reinterpret_cast<const uint32_t *>(szb)[e];
-    } else {
-        e = DOWN ? gu_entries + ((((size_t)grp * (H / 128) + tile / 2) * 16 + r) * 2 + tile % 2) * 4 + d
-                 : ((((size_t)tile * (H / g / 2) + grp / 2) * 16 + r) * 2 + grp % 2) * 4 + d;
-        return reinterpret_cast<const uint16_t *>(szb)[e];
-    }
+// The 8 codes of one word as 8 bf16 values 16 + code: 0x4180 is bf16 16.0, and a code in mantissa
+// bits 3-6 adds itself (one unit there is 16 / 128).  The smaller offset costs one shift more than
+// 128 + code and leaves 1/8 of its rounding error in the sums.
+__device__ inline UnpackConsts unpack16_consts() {
+    UnpackConsts k = {0x00780078u, 0x41804180u};
+    asm volatile("" : "+s"(k.mask));
+    asm volatile("" : "+v"(k.magic));
+    return k;
+}
+__device__ inline bf16x8 unpack8_16(uint32_t w, UnpackConsts k) {
+    u32x4 r;
+    r.x = ((w << 3) & k.mask) | k.magic;
+    r.y = ((w >> 1) & k.mask) | k.magic;
+    r.z = ((w >> 5) & k.mask) | k.magic;
+    r.w = ((w >> 9) & k.mask) | k.magic;
+    return __builtin_bit_cast(bf16x8, r);
 }
 
-template <bool DOWN, bool SYM, int KPG, int RB>
-__global__ __launch_bounds__(kTileThreads, 2)
-void prefill_tile_kernel(TileArgs a, int max_items)
-{
-    constexpr int NP = DOWN ? 2 : 1;             // operand planes (h and its remainder)
-    constexpr int SK = DOWN ? 2 : 4;             // k-steps per stage
-    constexpr int NT = SK * NP * 4;              // operand tiles per stage (16 KiB)
-    constexpr int GS = KPG < SK ? KPG : SK;      // k-steps per row of sums
-    constexpr int NR = SK / GS;                  // rows of sums per stage
-    constexpr int kSumsOff = NT * 1024;          // then NR x 64 fp32 sums
-    constexpr int kStageBytes = kSumsOff + SK * 256;
-    __shared__ __align__(16) unsigned char s_stage[2][kStageBytes];
+// An fp32 value as three bf16 pieces (upper halves of p[0..2], exact), in the order in which the
+// two factors of the group-sum contraction pair up over eight k positions:
+//   factor:  a1 a1 a1 a2 a2 a3 a2 a3      sum:  b1 b2 b3 b1 b2 b1 b3 b2
+__device__ inline void three_pieces(float v, uint32_t p[3]) {
+    p[0] = __float_as_uint(v) & 0xffff0000u;
+    const float r1 = v - __uint_as_float(p[0]);
+    p[1] = __float_as_uint(r1) & 0xffff0000u;
+    p[2] = __float_as_uint(r1 - __uint_as_float(p[1])) & 0xffff0000u;
+}
+__device__ inline u32x4 factor_operand(float v) {
+    uint32_t p[3];
+    three_pieces(v, p);
+    const uint32_t a3a2 = p[2] | (p[1] >> 16);
+    return (u32x4){p[0] | (p[0] >> 16), p[1] | (p[0] >> 16), a3a2, a3a2};
+}
+__device__ inline u32x4 sum_operand(float v) {
+    uint32_t p[3];
+    three_pieces(v, p);
+    return (u32x4){p[1] | (p[0] >> 16), p[0] | (p[2] >> 16), p[0] | (p[1] >> 16), p[1] | (p[2] >> 16)};
+}
 
-    // RB weight tiles per workgroup (gate/up: slices; down: row tiles of 64), tile0 the first
-    const int item = blockIdx.x % max_items, tile0 = (blockIdx.x / max_items) * RB;
-    if (item >= *a.n_items) return;
+// scale / zero entries of the four row blocks of one lane row and group
+template <bool SYM> struct Entry;
+template <> struct Entry<false> {
+    u32x4 w;
+    __device__ static Entry load(const char *p) { return {*reinterpret_cast<const u32x4 *>(p)}; }
+    __device__ float scale(int d) const { return (float)__builtin_bit_cast(_Float16, (uint16_t)(w[d] & 0xffff)); }
+    __device__ float zero16(int d) const { return (float)__builtin_bit_cast(_Float16, (uint16_t)(w[d] >> 16)) + 16.f; }
+};
+template <> struct Entry<true> {
+    typedef __attribute__((ext_vector_type(2))) uint32_t u32x2;
+    u32x2 w;
+    __device__ static Entry load(const char *p) { return {*reinterpret_cast<const u32x2 *>(p)}; }
+    __device__ float scale(int d) const { return (float)__builtin_bit_cast(_Float16, (uint16_t)(w[d >> 1] >> (16 * (d & 1)))); }
+    __device__ float zero16(int) const { return 24.f; }
+};
+
+typedef __attribute__((address_space(3))) void *lvoid;
+
+template <bool DOWN, bool SYM, int KPG>            // KPG: k-steps per group (g / 32)
+__global__ __launch_bounds__(kTileThreads, 2)
+void prefill_tile_kernel(TileArgs a)
+{
+    constexpr int NP = DOWN ? 2 : 1;               // operand planes (h and its remainder)
+    constexpr int SK = DOWN ? 2 : 4;               // k-steps per stage
+    constexpr int kWin = 8;                        // k-steps of codes in flight
+    constexpr int EW = 8 / KPG < 4 ? 8 / KPG : 4;  // groups of entries in flight
+    constexpr int kBuf = SK * NP * 4 * 1024;       // one stage of operand tiles
+    __shared__ __align__(1024) unsigned char s_x0[kBuf];
+    __shared__ __align__(1024) unsigned char s_x1[kBuf];
+    __shared__ __align__(1024) unsigned char s_x2[kBuf];
+    __shared__ __align__(1024) unsigned char s_x3[kBuf];
+    __shared__ float s_hsum[kTileWaves][kItemTokens];
+
+    const int H = a.H, I = a.I;
+    const int nk = DOWN ? I / 32 : H / 32, G = nk / KPG, nz = (G + 3) / 4;
+    const int tiles = DOWN ? H / 64 : I / 32, cols = (tiles + kTileWaves - 1) / kTileWaves;
+    // Workgroups go to the XCDs in turn: XCD x takes the x-th contiguous eighth of the (column, item)
+    // pairs, items fastest, so that the items of one expert, neighbours in the list, read its
+    // weight tiles through the same L2.
+    const int n_items = *a.n_items, total = cols * n_items, per = (total + kXcds - 1) / kXcds;
+    const int pair = ((int)blockIdx.x % kXcds) * per + (int)blockIdx.x / kXcds;
+    if ((int)blockIdx.x / kXcds >= per || pair >= total) return;
+    const int col = pair / n_items, item = pair % n_items;
     const PrefillItem it = a.items[item];
     const int tid = threadIdx.x, lane = tid & 63, r = lane & 15, c = lane >> 4;
-    const int d = __builtin_amdgcn_readfirstlane(tid >> 6);           // this wave's row block in every tile
-    const int H = a.H, I = a.I, g = 32 * KPG;
-    const int nk = DOWN ? I / 32 : H / 32, nfull = nk / SK;
-    const int ntiles = DOWN ? H / 64 : I / 32;
-    const UnpackConsts uk = unpack_consts();
+    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const UnpackConsts uk = unpack16_consts();
+    const bool mine = col * kTileWaves + wave < tiles;               // a wave past the end repeats the last tile
+    const int tile = mine ? col * kTileWaves + wave : tiles - 1;
 
-    // a tile past the end repeats the last one (its results are dropped)
-    auto tile_of = [&](int rb) { return tile0 + rb < ntiles ? tile0 + rb : ntiles - 1; };
-    const char *wq = a.q + (size_t)it.expert * a.stride_q + (DOWN ? (size_t)(I / 32) * (H / 32) * 1024 : 0) +
-                     lane * 16 + 4 * d;
-    auto wstep = [&](int rb, int u) -> size_t {
-        return DOWN ? ((size_t)u * (H / 64) + tile_of(rb)) * 1024 : ((size_t)tile_of(rb) * (H / 32) + u) * 1024;
+    const char *wq = a.q + (size_t)it.expert * a.stride_q +
+                     (DOWN ? (size_t)(I / 32) * (H / 32) * 1024 + (size_t)tile * 1024 : (size_t)tile * (H / 32) * 1024);
+    const size_t wstep = DOWN ? (size_t)(H / 64) * 1024 : 1024;
+    auto load_codes = [&](int k) {
+        const char *p = wq + (size_t)(k < nk ? k : nk - 1) * wstep;
+        return *reinterpret_cast<const u32x4 *>(p + lane * 16);
     };
-    const char *szb = a.sz + (size_t)it.expert * a.stride_sz;
-    const size_t step0 = (size_t)item * nk;
-    f32x4 tot[RB][4];
-#pragma unroll
-    for (int rb = 0; rb < RB; ++rb)
-#pragma unroll
-        for (int tb = 0; tb < 4; ++tb) tot[rb][tb] = (f32x4){0.f, 0.f, 0.f, 0.f};
+    // symmetric format: 8-byte halves of the 16-byte units (two groups, or two row tiles)
+    const char *szb = a.sz + (size_t)it.expert * a.stride_sz +
+                      (DOWN ? (size_t)(I / 32) * (H / (32 * KPG)) * (SYM ? 128 : 256) : 0);
+    auto entry_at = [&](int grp) {
+        const int gi = grp < G ? grp : G - 1;
+        size_t off;
+        if constexpr (!SYM) off = (DOWN ? (size_t)gi * (H / 64) + tile : (size_t)tile * G + gi) * 256 + r * 16;
+        else if constexpr (DOWN) off = ((size_t)gi * (H / 128) + tile / 2) * 256 + r * 16 + (tile % 2) * 8;
+        else off = ((size_t)tile * (G / 2) + gi / 2) * 256 + r * 16 + (gi % 2) * 8;
+        return Entry<SYM>::load(szb + off);
+    };
+    auto buffer = [&](auto j) -> unsigned char * {
+        if constexpr (decltype(j)::value == 0) return s_x0;
+        else if constexpr (decltype(j)::value == 1) return s_x1;
+        else if constexpr (decltype(j)::value == 2) return s_x2;
+        else return s_x3;
+    };
+    const int my_k = DOWN ? wave >> 1 : wave;                        // the k-step (and plane) of a stage this wave requests
+    const char *act = (DOWN && (wave & 1)) ? a.act1 : a.act0;
 
-    // The whole K loop for an item with NTB token blocks (a compile-time count: no branch inside
-    // a stage, so the LDS reads of a stage are issued ahead of its MFMAs).
-    // kAct: this wave's token block exists (d < NTB), so it stages operand tiles and sums; the
-    // waves of absent blocks only take part in the weights.  Both are compile-time properties of
-    // the code a wave runs, and the loads of a stage are unconditional (past the end they repeat
-    // the last stage): a load inside a branch makes the compiler wait for ALL loads in flight
-    // where the branch joins, which would undo the two-stage pipeline.
-    auto run = [&](auto ntb_c, auto act_c) {
+    // the whole of an item with NTB token blocks (a compile-time count: no branch inside a stage)
+    auto run = [&](auto ntb_c) {
         constexpr int NTB = decltype(ntb_c)::value;
-        constexpr bool kAct = decltype(act_c)::value;
-        // What one thread moves per stage: its wave's token block of every operand tile, the code
-        // dword and the entry of its row block for every tile and k-step, and 16 bytes of one
-        // sums row (a row adds up the GS k-steps of a group that lie in the stage).  Two stages
-        // are in flight: set R[P] is loaded two stages ahead and written to LDS one stage ahead.
-        struct Stage { u32x4 act[SK * NP]; uint32_t w[RB][SK], e[RB][SK]; f32x4 sum[GS]; };
-        Stage R[2];
-        uint32_t cur_w[RB][SK], cur_e[RB][SK];
-        const int sum_row = (lane >> 2) & (NR - 1), sum_piece = lane & 3;   // this lane's 16 bytes of the sums
-        auto load_stage = [&](int n, Stage &S) {
+        auto request = [&](int n, auto j) {
+            const int k = n * SK + my_k;
+            // (chosen with a mask: a branch here would cut the stage into several scheduling regions)
+            const char *from = act + ((size_t)item * nk + k) * 4096;
+            const char *src = a.zeros + ((from - a.zeros) & (k < nk ? ~(ptrdiff_t)0 : (ptrdiff_t)0));
+            // Buffer loads, not global ones: after a FLAT-encoded load to LDS the compiler waits for ALL LDS
+            // reads in flight wherever it needs one.
+            const auto rsrc = __builtin_amdgcn_make_buffer_rsrc((void *)src, 0, 4096, 0x00027000);
+            unsigned char *dst = buffer(j) + wave * 4096;
 #pragma unroll
-            for (int s = 0; s < SK; ++s) {
-                const int u = n * SK + s < nk ? n * SK + s : nk - 1;
-                if constexpr (kAct) {
+            for (int tb = 0; tb < NTB; ++tb)
+                __builtin_amdgcn_raw_ptr_buffer_load_lds(rsrc, (lvoid)(dst + tb * 1024), 16, lane * 16, tb * 1024, 0, 0);
+        };
+        f32x4 tot[4][NTB], acc[4][NTB];
 #pragma unroll
-                    for (int p = 0; p < NP; ++p)
-                        S.act[s * NP + p] = *reinterpret_cast<const u32x4 *>(
-                            (p == 0 ? a.act0 : a.act1) + ((step0 + u) * 4 + d) * 1024 + lane * 16);
-                }
+        for (int d = 0; d < 4; ++d)
 #pragma unroll
-                for (int rb = 0; rb < RB; ++rb) {
-                    S.w[rb][s] = *reinterpret_cast<const uint32_t *>(wq + wstep(rb, u));
-                    S.e[rb][s] = load_entry<DOWN, SYM>(szb, H, I, g, tile_of(rb), u / KPG, r, d);
-                }
-            }
-            if constexpr (kAct) {
-                // sums of this wave's token block: rows lie inside [0, nk) or outside as a whole; added
-                // up when they go to LDS (adding here would make the wave wait for the loads)
-                const int u0 = n * SK + sum_row * GS < nk ? n * SK + sum_row * GS : nk - GS;
+            for (int tb = 0; tb < NTB; ++tb) tot[d][tb] = acc[d][tb] = (f32x4){0.f, 0.f, 0.f, 0.f};
+        u32x4 win[kWin];                           // codes of k-steps k .. k + 7, slot k % 8
+        bf16x8 wb[2][4];                           // operands of k-step k and, as it is unpacked, k + 1
+        Entry<SYM> ent[EW];
+        float sc[4] = {0.f, 0.f, 0.f, 0.f};        // scales of the group that ended last
+        auto add_scaled = [&](int tb) {
 #pragma unroll
-                for (int j = 0; j < GS; ++j)
-                    S.sum[j] = *reinterpret_cast<const f32x4 *>(a.sums + (step0 + u0 + j) * 64 + 16 * d + 4 * sum_piece);
+            for (int d = 0; d < 4; ++d) {
+#pragma unroll
+                for (int i = 0; i < 4; ++i) tot[d][tb][i] = fmaf(sc[d], acc[d][tb][i], tot[d][tb][i]);
+                asm volatile("" : "+v"(tot[d][tb]));   // here and not further down, or acc could not be used again
             }
         };
-        auto store_stage = [&](int b, const Stage &S) {
-            if constexpr (kAct) {
+
+        // One stage: its operand tiles are in buffer j once this wave's own transfers have landed and the
+        // workgroup has met; then the buffer that everybody has left takes the stage three further on.
+        // The stage is a row of blocks, one per operand tile: the LDS read three tiles ahead, a share of
+        // the next k-step's unpacking, the scaling of the token block before (its products are complete
+        // by then), and the tile's four MFMAs, so that the vector ALU and LDS work under the matrix
+        // cores.  The barriers between blocks keep the scheduler from gathering all reads of a stage in
+        // front, for which there are no registers.
+        auto stage = [&](int n, auto j) {
+            constexpr int J = decltype(j)::value;
+            constexpr int kFirst = J * SK;         // position in the four stages of a loop trip
+            constexpr int NB = NTB * NP, F = SK * NB, kA = 4;
+            // Issued behind this stage's transfers (vector memory operations complete in order): the
+            // codes of three stages and the transfers of two.
+            constexpr int kLater = 3 * SK + 2 * NTB;
+            static_assert(kLater < 64, "vmcnt");
+            __builtin_amdgcn_sched_barrier(0);
+            __builtin_amdgcn_s_waitcnt((kLater & 15) | ((kLater >> 4) << 14) | 0x0f70);
+            __builtin_amdgcn_s_barrier();
+            __builtin_amdgcn_sched_barrier(0);
+            const unsigned char *buf = buffer(j);
+            u32x4 xa[kA];
+            auto read = [&](int f) {               // tile f of the stage: k-step, token block, plane
+                const int s = f / NB, tb = f % NB / NP, p = f % NP;
+                xa[f % kA] = *reinterpret_cast<const u32x4 *>(&buf[((s * NP + p) * 4 + tb) * 1024 + lane * 16]);
+            };
 #pragma unroll
-                for (int j = 0; j < SK * NP; ++j)
-                    *reinterpret_cast<u32x4 *>(&s_stage[b][(j * 4 + d) * 1024 + lane * 16]) = S.act[j];
-                f32x4 v = S.sum[0];
+            for (int f = 0; f < kA - 1 && f < F; ++f) read(f);
+            request(n + 3, std::integral_constant<int, (J + 3) & 3>{});
 #pragma unroll
-                for (int j = 1; j < GS; ++j) v += S.sum[j];
-                if (lane < 4 * NR)
-                    *reinterpret_cast<f32x4 *>(&s_stage[b][kSumsOff + sum_row * 256 + (16 * d + 4 * sum_piece) * 4]) = v;
-            }
+            for (int f = 0; f < F; ++f) {
+                const int s = f / NB, t = f % NB, tb = t / NP, p = t % NP;
+                const int pos = kFirst + s;
+                const bool begins = pos % KPG == 0, ends = (pos + 1) % KPG == 0;      // of a group
+                __builtin_amdgcn_sched_barrier(0);
+                if (f + kA - 1 < F) read(f + kA - 1);
+                if (begins && t == 0) add_scaled(NTB - 1);                            // of the group before
+                if (ends && t == 0) {
+                    constexpr int kGroups = 4 * SK / KPG;
+                    static_assert(kGroups % EW == 0, "the slot of a group has to be the same in every loop trip");
+                    const int slot = (pos / KPG) % EW;
 #pragma unroll
-            for (int rb = 0; rb < RB; ++rb)
-#pragma unroll
-                for (int s = 0; s < SK; ++s) { cur_w[rb][s] = S.w[rb][s]; cur_e[rb][s] = S.e[rb][s]; }
-        };
-        f32x4 acc[RB][NTB], xs[NTB];
-#pragma unroll
-        for (int tb = 0; tb < NTB; ++tb) {
-            xs[tb] = (f32x4){0.f, 0.f, 0.f, 0.f};
-#pragma unroll
-            for (int rb = 0; rb < RB; ++rb) acc[rb][tb] = (f32x4){0.f, 0.f, 0.f, 0.f};
-        }
-        auto group_end = [&](int s) {                             // scale, zero point, offset
-#pragma unroll
-            for (int rb = 0; rb < RB; ++rb) {
-                const uint32_t ev = cur_e[rb][s];
-                const float sc = (float)__builtin_bit_cast(_Float16, (uint16_t)(ev & 0xffff));
-                const float zp = SYM ? 136.f : (float)__builtin_bit_cast(_Float16, (uint16_t)(ev >> 16)) + 128.f;
-                const float nsz = -sc * zp;
-#pragma unroll
-                for (int tb = 0; tb < NTB; ++tb) {
-#pragma unroll
-                    for (int i = 0; i < 4; ++i) {
-                        tot[rb][tb][i] = fmaf(sc, acc[rb][tb][i], tot[rb][tb][i]);
-                        tot[rb][tb][i] = fmaf(nsz, xs[tb][i], tot[rb][tb][i]);
-                    }
-                    acc[rb][tb] = (f32x4){0.f, 0.f, 0.f, 0.f};
+                    for (int d = 0; d < 4; ++d) sc[d] = ent[slot].scale(d);
+                    ent[slot] = entry_at((n * SK + s) / KPG + EW);
                 }
+                const int nx = (pos + 1) % kWin;
+#pragma unroll
+                for (int d = 0; d < 4; ++d)
+                    if (d * NB / 4 == t) wb[(s + 1) & 1][d] = unpack8_16(win[nx][d], uk);
+                if (t == NB - 1) win[nx] = load_codes(n * SK + s + 1 + kWin);
+#pragma unroll
+                for (int d = 0; d < 4; ++d)
+                    acc[d][tb] = mfma(xa[f % kA], wb[s & 1][d], begins && p == 0 ? (f32x4){0.f, 0.f, 0.f, 0.f} : acc[d][tb]);
+                if (ends && p == 0 && tb > 0) add_scaled(tb - 1);
             }
-#pragma unroll
-            for (int tb = 0; tb < NTB; ++tb) xs[tb] = (f32x4){0.f, 0.f, 0.f, 0.f};
-        };
-        // the k-steps of stage n from LDS buffer n & 1; full: all SK of them exist
-        auto compute_stage = [&](int n, auto full) {
-            constexpr bool kFull = decltype(full)::value;
-            const unsigned char *buf = s_stage[n & 1];
-#pragma unroll
-            for (int s = 0; s < SK; ++s) {
-                if (kFull || n * SK + s < nk) {
-                    bf16x8 wb[RB];
-#pragma unroll
-                    for (int rb = 0; rb < RB; ++rb) wb[rb] = unpack8(cur_w[rb][s], uk);
-#pragma unroll
-                    for (int tb = 0; tb < NTB; ++tb) {
-#pragma unroll
-                        for (int p = 0; p < NP; ++p) {
-                            const u32x4 xa = *reinterpret_cast<const u32x4 *>(&buf[((s * NP + p) * 4 + tb) * 1024 + lane * 16]);
-#pragma unroll
-                            for (int rb = 0; rb < RB; ++rb) acc[rb][tb] = mfma(xa, wb[rb], acc[rb][tb]);
-                        }
-                        if ((s + 1) % GS == 0)
-                            xs[tb] += *reinterpret_cast<const f32x4 *>(&buf[kSumsOff + (s / GS) * 256 + (16 * tb + 4 * c) * 4]);
-                    }
-                    if constexpr (KPG <= SK) {
-                        if ((s + 1) % KPG == 0) group_end(s);
-                    } else {
-                        if (s == SK - 1 && (n & (KPG / SK - 1)) == KPG / SK - 1) group_end(s);
-                    }
-                }
-            }
+            __builtin_amdgcn_sched_barrier(0);
         };
         const int ns = (nk + SK - 1) / SK;
-        auto iteration = [&](int n, auto parity) {
-            constexpr int P = decltype(parity)::value;
-            load_stage(n + 2 < ns ? n + 2 : ns - 1, R[P]);
-            if (n < nfull) compute_stage(n, std::true_type{});
-            else compute_stage(n, std::false_type{});
-            if (n + 1 < ns) store_stage((n + 1) & 1, R[P ^ 1]);
-            __syncthreads();
-        };
-
-        load_stage(0, R[0]);
-        load_stage(ns > 1 ? 1 : 0, R[1]);
-        store_stage(0, R[0]);
-        __syncthreads();
-        int n = 0;
-        for (; n + 1 < ns; n += 2) {
-            iteration(n, std::integral_constant<int, 0>{});
-            iteration(n + 1, std::integral_constant<int, 1>{});
+        request(0, std::integral_constant<int, 0>{});
+        request(1, std::integral_constant<int, 1>{});
+        request(2, std::integral_constant<int, 2>{});
+        __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+        for (int i = 0; i < kWin; ++i) win[i] = load_codes(i);
+#pragma unroll
+        for (int i = 0; i < EW; ++i) ent[i] = entry_at(i);
+        // the first stages' transfers have fewer operations behind them than the steady state counts on
+        __builtin_amdgcn_sched_barrier(0);
+        __builtin_amdgcn_s_waitcnt(0x0070);
+#pragma unroll
+        for (int d = 0; d < 4; ++d) wb[0][d] = unpack8_16(win[0][d], uk);
+        win[0] = load_codes(kWin);
+        for (int n = 0; n < ns; n += 4) {
+            stage(n, std::integral_constant<int, 0>{});
+            stage(n + 1, std::integral_constant<int, 1>{});
+            stage(n + 2, std::integral_constant<int, 2>{});
+            stage(n + 3, std::integral_constant<int, 3>{});
         }
-        if (n < ns) iteration(n, std::integral_constant<int, 0>{});
-    };
-    const int ntb = (it.cnt + 15) >> 4;
-    auto run_role = [&](auto ntb_c) {
-        if (d < decltype(ntb_c)::value) run(ntb_c, std::true_type{});
-        else run(ntb_c, std::false_type{});
-    };
-    if (ntb == 4) run(std::integral_constant<int, 4>{}, std::true_type{});
-    else if (ntb == 3) run_role(std::integral_constant<int, 3>{});
-    else if (ntb == 2) run_role(std::integral_constant<int, 2>{});
-    else run_role(std::integral_constant<int, 1>{});
+        // every last stage ends a group (k-steps past the end are zeros)
+        add_scaled(NTB - 1);
+        // the contraction over groups
+        {
+            const char *zs = a.act_sums + (size_t)item * nz * 4096 + lane * 16;
+            u32x4 zx[2][NTB];
+            Entry<SYM> ze[2];
+            auto load_sums = [&](int q, int b) {
+                const int qq = q < nz ? q : nz - 1;
+#pragma unroll
+                for (int tb = 0; tb < NTB; ++tb) zx[b][tb] = *reinterpret_cast<const u32x4 *>(zs + ((size_t)qq * 4 + tb) * 1024);
+                ze[b] = entry_at(4 * qq + c);
+            };
+            auto add_sums = [&](int b) {
+#pragma unroll
+                for (int d = 0; d < 4; ++d) {
+                    const bf16x8 f = __builtin_bit_cast(bf16x8, factor_operand(-ze[b].scale(d) * ze[b].zero16(d)));
+#pragma unroll
+                    for (int tb = 0; tb < NTB; ++tb) tot[d][tb] = mfma(zx[b][tb], f, tot[d][tb]);
+                }
+            };
+            load_sums(0, 0);
+            load_sums(1, 1);
+            int q = 0;
+            for (; q + 1 < nz; q += 2) {
+                add_sums(0);
+                load_sums(q + 2, 0);
+                add_sums(1);
+                load_sums(q + 3, 1);
+            }
+            if (q < nz) add_sums(0);
+        }
 
-    // lane (r, c) of wave d now holds, per tile and token block, rows d x 16 + r of tokens 4 c + i
-    if constexpr (DOWN) {
+        // lane (r, c) holds, per row block d and token block, row 16 d + r of tokens 4 c + i
+        if constexpr (DOWN) {
+            if (!mine) return;
 #pragma unroll
-        for (int rb = 0; rb < RB; ++rb) {
-            if (tile0 + rb >= ntiles) break;
-#pragma unroll
-            for (int tb = 0; tb < 4; ++tb) {
+            for (int tb = 0; tb < NTB; ++tb)
 #pragma unroll
                 for (int i = 0; i < 4; ++i) {
                     const int tok = 16 * tb + 4 * c + i;
-                    if (tok < it.cnt)
-                        a.obuf[((size_t)item * kItemTokens + tok) * H + 64 * (tile0 + rb) + 16 * d + r] = tot[rb][tb][i];
+                    if (tok < it.cnt) {
+                        float *o = a.obuf + ((size_t)item * kItemTokens + tok) * H + 64 * tile + r;
+#pragma unroll
+                        for (int d = 0; d < 4; ++d) o[16 * d] = tot[d][tb][i];
+                    }
                 }
-            }
-        }
-    } else {
-        // one slice at a time: pre-activations to LDS as [row block][token][r], then each wave
-        // turns one token block into its operand tile: lane (token, chunk) holds h of inputs
-        // 8 chunk .. 8 chunk + 7
-        float *s_out = reinterpret_cast<float *>(&s_stage[0][0]);       // 16 KiB
-#pragma unroll
-        for (int rb = 0; rb < RB; ++rb) {
-            if (tile0 + rb >= ntiles) break;                             // the same for the whole workgroup
-            if (rb > 0) __syncthreads();
-#pragma unroll
-            for (int tb = 0; tb < 4; ++tb) {
-                if (tb < ntb) {
-#pragma unroll
-                    for (int i = 0; i < 4; ++i) s_out[(d * 64 + 16 * tb + 4 * c + i) * 16 + r] = tot[rb][tb][i];
-                }
-            }
+        } else {
+            // h of 16 tokens x 32 columns through this wave's own LDS area: lane (token, chunk) then
+            // holds h of columns 8 chunk .. 8 chunk + 7, the operand layout
+            __builtin_amdgcn_s_waitcnt(0x0f70);                       // transfers requested past the end
             __syncthreads();
-            if (d < ntb) {
-                const int tok = 16 * d + r;
+            float *s_h = reinterpret_cast<float *>(wave == 0 ? s_x0 : wave == 1 ? s_x1 : wave == 2 ? s_x2 : s_x3);
+            constexpr int kRow = 36;                                  // 32 columns and 16 bytes against bank conflicts
+#pragma unroll
+            for (int tb = 0; tb < NTB; ++tb) {
+#pragma unroll
+                for (int dd = 0; dd < 2; ++dd)
+#pragma unroll
+                    for (int i = 0; i < 4; ++i) {
+                        const float gate = tot[dd][tb][i], up = tot[dd + 2][tb][i];
+                        s_h[(16 * tb + 4 * c + i) * kRow + 16 * dd + r] = gate / (1.f + expf(-gate)) * up;
+                    }
+            }
+            __builtin_amdgcn_wave_barrier();
+            const size_t slice = (size_t)item * (I / 32) + tile;
+#pragma unroll
+            for (int tb = 0; tb < NTB; ++tb) {
+                const f32x4 h0 = *reinterpret_cast<const f32x4 *>(&s_h[(16 * tb + r) * kRow + 8 * c]);
+                const f32x4 h1 = *reinterpret_cast<const f32x4 *>(&s_h[(16 * tb + r) * kRow + 8 * c + 4]);
                 uint32_t hi[4], lo[4];
                 float sum = 0.f;
 #pragma unroll
                 for (int j = 0; j < 8; ++j) {
-                    const int col = 8 * c + j, dd = col >> 4, rr = col & 15;
-                    const float gate = s_out[(dd * 64 + tok) * 16 + rr], up = s_out[((2 + dd) * 64 + tok) * 16 + rr];
-                    const float h = gate / (1.f + expf(-gate)) * up;
+                    const float h = j < 4 ? h0[j & 3] : h1[j & 3];
                     const uint32_t hb = f32_to_bf16_rne(h);
-                    const float rest = h - __uint_as_float(hb << 16);
-                    const uint32_t lb = f32_to_bf16_rne(rest);
+                    const uint32_t lb = f32_to_bf16_rne(h - __uint_as_float(hb << 16));
                     sum += __uint_as_float(hb << 16) + __uint_as_float(lb << 16);
                     if (j & 1) { hi[j >> 1] |= hb << 16; lo[j >> 1] |= lb << 16; }
                     else { hi[j >> 1] = hb; lo[j >> 1] = lb; }
                 }
-                const size_t slice = (size_t)item * (I / 32) + tile0 + rb;
-                const size_t t = (slice * 4 + d) * 1024 + lane * 16;
-                *reinterpret_cast<u32x4 *>(a.h_hi + t) = (u32x4){hi[0], hi[1], hi[2], hi[3]};
-                *reinterpret_cast<u32x4 *>(a.h_lo + t) = (u32x4){lo[0], lo[1], lo[2], lo[3]};
+                const size_t t = (slice * 4 + tb) * 1024 + lane * 16;
+                if (mine) {
+                    *reinterpret_cast<u32x4 *>(a.h_hi + t) = (u32x4){hi[0], hi[1], hi[2], hi[3]};
+                    *reinterpret_cast<u32x4 *>(a.h_lo + t) = (u32x4){lo[0], lo[1], lo[2], lo[3]};
+                }
                 sum += __shfl_xor(sum, 16);
                 sum += __shfl_xor(sum, 32);
-                if (c == 0) a.h_sums[slice * 64 + tok] = sum;
+                if (c == 0) s_hsum[wave][16 * tb + r] = sum;
+            }
+            __syncthreads();
+            // group sums of h: the workgroup's 128 columns hold 4 / KPG whole groups; the last column of
+            // workgroups also clears what is left of the last tile of four groups
+            const int tok = tid & 63, pos = tid >> 6;
+            const int GI = I / (32 * KPG), gi = col * (4 / KPG) + pos;
+            const bool real = pos < 4 / KPG && gi < GI;
+            const bool pad = gi >= GI && gi / 4 == (GI - 1) / 4 && col == cols - 1;
+            if (tok < 16 * NTB && (real || pad)) {
+                float v = 0.f;
+                if (real) {
+#pragma unroll
+                    for (int w = 0; w < KPG; ++w) v += s_hsum[(pos * KPG + w) & 3][tok];
+                }
+                const size_t t = (((size_t)item * ((GI + 3) / 4) + gi / 4) * 4 + (tok >> 4)) * 1024 +
+                                 ((gi & 3) * 16 + (tok & 15)) * 16;
+                *reinterpret_cast<u32x4 *>(a.h_sums + t) = sum_operand(v);
             }
         }
-    }
+    };
+    const int ntb = (it.cnt + 15) >> 4;
+    if (ntb == 4) run(std::integral_constant<int, 4>{});
+    else if (ntb == 3) run(std::integral_constant<int, 3>{});
+    else if (ntb == 2) run(std::integral_constant<int, 2>{});
+    else run(std::integral_constant<int, 1>{});
 }
 
 // Gathers the tokens of token block (item, tb) into operand tiles [(item nk + u) 4 + tb]: lane
 // (token, chunk) of tile u holds x[token][32 u + 8 chunk .. + 7]; positions past the item's count
-// hold zeros.  Also the sum of each token's 32 values of the tile.  One wave per (block, u).
+// hold zeros.  Also the group sums as operand tiles [(item nz + group / 4) 4 + tb].  One wave per
+// (block, four tiles): 128 inputs, whole groups.  The first workgroup also writes the tile of zeros.
+template <int KPG>
 __global__ __launch_bounds__(256)
 void prefill_stage_kernel(const uint16_t *__restrict__ x, const PrefillItem *__restrict__ items,
                           const int32_t *__restrict__ n_items, const int32_t *__restrict__ sorted,
-                          char *__restrict__ xt, float *__restrict__ sums, int H, int k)
+                          char *__restrict__ xt, char *__restrict__ sums, char *__restrict__ zeros, int H, int k)
 {
+    if (blockIdx.x == 0 && blockIdx.y == 0)
+        *reinterpret_cast<u32x4 *>(zeros + threadIdx.x * 16) = (u32x4){0u, 0u, 0u, 0u};
     const int item = blockIdx.x >> 2, tb = blockIdx.x & 3;
     if (item >= *n_items) return;
     const PrefillItem it = items[item];
     if (16 * tb >= it.cnt) return;
-    const int nk = H / 32, u = blockIdx.y * 4 + (threadIdx.x >> 6);
-    if (u >= nk) return;
+    const int nk = H / 32, u4 = blockIdx.y * 4 + (threadIdx.x >> 6);
+    if (u4 * 4 >= nk) return;
     const int lane = threadIdx.x & 63, tok16 = lane & 15, chunk = lane >> 4, pos = 16 * tb + tok16;
-    u32x4 v = {0u, 0u, 0u, 0u};
-    if (pos < it.cnt) {
-        const int token = sorted[it.first + pos] / k;
-        v = *reinterpret_cast<const u32x4 *>(x + (size_t)token * H + 32 * u + 8 * chunk);
+    const int token = pos < it.cnt ? sorted[it.first + pos] / k : 0;
+    float s[4];
+#pragma unroll
+    for (int j = 0; j < 4; ++j) {
+        const int u = u4 * 4 + j;
+        u32x4 v = {0u, 0u, 0u, 0u};
+        if (u < nk && pos < it.cnt) v = *reinterpret_cast<const u32x4 *>(x + (size_t)token * H + 32 * u + 8 * chunk);
+        if (u < nk) *reinterpret_cast<u32x4 *>(xt + (((size_t)item * nk + u) * 4 + tb) * 1024 + lane * 16) = v;
+        s[j] = ((bf16_lo(v.x) + bf16_hi(v.x)) + (bf16_lo(v.y) + bf16_hi(v.y))) +
+               ((bf16_lo(v.z) + bf16_hi(v.z)) + (bf16_lo(v.w) + bf16_hi(v.w)));
+        s[j] += __shfl_xor(s[j], 16);
+        s[j] += __shfl_xor(s[j], 32);
     }
-    *reinterpret_cast<u32x4 *>(xt + (((size_t)item * nk + u) * 4 + tb) * 1024 + lane * 16) = v;
-    float s = ((bf16_lo(v.x) + bf16_hi(v.x)) + (bf16_lo(v.y) + bf16_hi(v.y))) +
-              ((bf16_lo(v.z) + bf16_hi(v.z)) + (bf16_lo(v.w) + bf16_hi(v.w)));
-    s += __shfl_xor(s, 16);
-    s += __shfl_xor(s, 32);
-    if (chunk == 0) sums[((size_t)item * nk + u) * 64 + pos] = s;
+    // group `chunk` of this wave's 4 / KPG groups; the wave with the last inputs also clears what is left
+    // of the last tile of four groups
+    const int G = nk / KPG, gi = u4 * (4 / KPG) + chunk;
+    const bool real = chunk < 4 / KPG && gi < G, last = u4 * 4 + 4 >= nk;
+    if (real || (last && gi >= G && gi / 4 == (G - 1) / 4)) {
+        float v = 0.f;
+        if (real) {
+            if constexpr (KPG == 4) v = (s[0] + s[1]) + (s[2] + s[3]);
+            else if constexpr (KPG == 2) v = chunk == 0 ? s[0] + s[1] : s[2] + s[3];
+            else v = chunk == 0 ? s[0] : chunk == 1 ? s[1] : chunk == 2 ? s[2] : s[3];
+        }
+        *reinterpret_cast<u32x4 *>(sums + (((size_t)item * ((G + 3) / 4) + gi / 4) * 4 + tb) * 1024 +
+                                   ((gi & 3) * 16 + tok16) * 16) = sum_operand(v);
+    }
 }
 
 // Sorts the n = T k assignments by expert (the order inside an expert is arbitrary: no result
@@ -401,23 +523,21 @@ void prefill_combine_kernel(const float *__restrict__ obuf, const int32_t *__res
     *reinterpret_cast<f32x4 *>(y + (size_t)t * H + col) = acc;
 }
 
-constexpr int kRowBlocks = 2;                     // weight tiles per workgroup of the tile kernel
-
 template <bool DOWN, bool SYM>
-void launch_tile_g(const TileArgs &t, int tiles, int max_items, hipStream_t st)
+void launch_tile_g(const TileArgs &t, int g, int tiles, int max_items, hipStream_t st)
 {
-    const int cols = (tiles + kRowBlocks - 1) / kRowBlocks;
-    const dim3 grid((unsigned)((size_t)cols * max_items)), block(kTileThreads);
-    if (t.g == 32) launch(prefill_tile_kernel<DOWN, SYM, 1, kRowBlocks>, grid, block, 0, st, t, max_items);
-    else if (t.g == 64) launch(prefill_tile_kernel<DOWN, SYM, 2, kRowBlocks>, grid, block, 0, st, t, max_items);
-    else launch(prefill_tile_kernel<DOWN, SYM, 4, kRowBlocks>, grid, block, 0, st, t, max_items);
+    const size_t pairs = (size_t)((tiles + kTileWaves - 1) / kTileWaves) * max_items;
+    const dim3 grid((unsigned)((pairs + kXcds - 1) / kXcds * kXcds)), block(kTileThreads);
+    if (g == 32) launch(prefill_tile_kernel<DOWN, SYM, 1>, grid, block, 0, st, t);
+    else if (g == 64) launch(prefill_tile_kernel<DOWN, SYM, 2>, grid, block, 0, st, t);
+    else launch(prefill_tile_kernel<DOWN, SYM, 4>, grid, block, 0, st, t);
 }
 
 template <bool DOWN>
-void launch_tile(const TileArgs &t, bool sym, int tiles, int max_items, hipStream_t st)
+void launch_tile(const TileArgs &t, bool sym, int g, int tiles, int max_items, hipStream_t st)
 {
-    if (sym) launch_tile_g<DOWN, true>(t, tiles, max_items, st);
-    else launch_tile_g<DOWN, false>(t, tiles, max_items, st);
+    if (sym) launch_tile_g<DOWN, true>(t, g, tiles, max_items, st);
+    else launch_tile_g<DOWN, false>(t, g, tiles, max_items, st);
 }
 
 }  // namespace
@@ -427,9 +547,10 @@ PrefillBuffers prefill_buffers(const moe_layer_desc &d, int max_items)
     PrefillBuffers b;
     const size_t m = (size_t)max_items;
     b.xt = m * (d.hidden / 32) * 4096;
-    b.x_sums = m * (d.hidden / 32) * 256;
+    b.x_sums = m * ((d.hidden / d.group_size + 3) / 4) * 4096;
     b.h_plane = m * (d.inter / 32) * 4096;
-    b.h_sums = m * (d.inter / 32) * 256;
+    b.h_sums = m * ((d.inter / d.group_size + 3) / 4) * 4096;
+    b.zeros = 4096;
     b.obuf = m * kItemTokens * d.hidden * 4;
     return b;
 }
@@ -442,33 +563,38 @@ void launch_prefill_plan(const int32_t *ids, int n, int E, int32_t *sorted, int3
 
 void launch_prefill_stage(const Shape &s, const PrefillCall &p, int max_items, hipStream_t st)
 {
-    const int nk = s.H / 32;
-    launch(prefill_stage_kernel, dim3(max_items * 4, (nk + 3) / 4), dim3(256), 0, st,
-           (const uint16_t *)p.x, p.items, p.n_items, p.sorted, (char *)p.xt, p.x_sums, s.H, s.k);
+    const dim3 grid(max_items * 4, (s.H / 32 + 15) / 16), block(256);
+    auto go = [&](auto kernel) {
+        launch(kernel, grid, block, 0, st, (const uint16_t *)p.x, p.items, p.n_items, p.sorted, (char *)p.xt,
+               (char *)p.x_sums, (char *)p.zeros, s.H, s.k);
+    };
+    if (s.g == 32) go(prefill_stage_kernel<1>);
+    else if (s.g == 64) go(prefill_stage_kernel<2>);
+    else go(prefill_stage_kernel<4>);
 }
 
 static TileArgs tile_args(const Shape &s, const PrefillCall &p)
 {
     TileArgs t;
     t.q = (const char *)p.q; t.sz = (const char *)p.sz; t.stride_q = p.stride_q; t.stride_sz = p.stride_sz;
-    t.items = p.items; t.n_items = p.n_items;
-    t.h_hi = (char *)p.h_hi; t.h_lo = (char *)p.h_lo; t.h_sums = p.h_sums; t.obuf = p.obuf;
-    t.H = s.H; t.I = s.I; t.g = s.g;
+    t.items = p.items; t.n_items = p.n_items; t.zeros = (const char *)p.zeros;
+    t.h_hi = (char *)p.h_hi; t.h_lo = (char *)p.h_lo; t.h_sums = (char *)p.h_sums; t.obuf = p.obuf;
+    t.H = s.H; t.I = s.I;
     return t;
 }
 
 void launch_prefill_gateup(const Shape &s, const PrefillCall &p, int max_items, hipStream_t st)
 {
     TileArgs t = tile_args(s, p);
-    t.act0 = (const char *)p.xt; t.act1 = nullptr; t.sums = p.x_sums;
-    launch_tile<false>(t, p.symmetric != 0, s.I / 32, max_items, st);
+    t.act0 = (const char *)p.xt; t.act1 = nullptr; t.act_sums = (const char *)p.x_sums;
+    launch_tile<false>(t, p.symmetric != 0, s.g, s.I / 32, max_items, st);
 }
 
 void launch_prefill_down(const Shape &s, const PrefillCall &p, int max_items, hipStream_t st)
 {
     TileArgs t = tile_args(s, p);
-    t.act0 = (const char *)p.h_hi; t.act1 = (const char *)p.h_lo; t.sums = p.h_sums;
-    launch_tile<true>(t, p.symmetric != 0, s.H / 64, max_items, st);
+    t.act0 = (const char *)p.h_hi; t.act1 = (const char *)p.h_lo; t.act_sums = (const char *)p.h_sums;
+    launch_tile<true>(t, p.symmetric != 0, s.g, s.H / 64, max_items, st);
 }
 
 void launch_prefill_combine(const Shape &s, const PrefillCall &p, hipStream_t st)

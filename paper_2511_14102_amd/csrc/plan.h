@@ -136,14 +136,14 @@ void launch_stream_read(const void *src, size_t bytes, int workgroups, void *sin
 
 // draft_prefill.hip: a routed run of tokens.  Byte sizes of the buffers a call with at most
 // max_items work items needs (h_plane: each of the two planes of h), then the launches in order.
-struct PrefillBuffers { size_t xt, x_sums, h_plane, h_sums, obuf; };
+struct PrefillBuffers { size_t xt, x_sums, h_plane, h_sums, zeros, obuf; };
 PrefillBuffers prefill_buffers(const moe_layer_desc &d, int max_items);
 struct PrefillCall {
     const void *x;                     // [T,H] bf16
     const void *q, *sz; size_t stride_q, stride_sz; int symmetric;
     const PrefillItem *items; const int32_t *n_items; const int32_t *sorted; const int32_t *slot_of;
     const float *w_all;                // routing weight of every assignment [T k]
-    void *xt; float *x_sums; void *h_hi, *h_lo; float *h_sums; float *obuf;
+    void *xt, *x_sums, *h_hi, *h_lo, *h_sums, *zeros; float *obuf;
     float *y;                          // [T,H] fp32, written (not accumulated)
 };
 void launch_prefill_plan(const int32_t *ids, int n, int E, int32_t *sorted, int32_t *slot_of,

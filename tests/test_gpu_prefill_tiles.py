@@ -1,0 +1,47 @@
+"""The grouped contraction of the prefill call at the edges of its tiles: k-steps that do not fill a
+stage, group sums that do not fill a tile of four groups, slices and row tiles that do not fill a
+workgroup's four, and items of 1 to 64 tokens (whole and ragged token blocks, several items per
+expert), for every group size and both weight formats."""
+import numpy as np
+import pytest
+import torch
+
+import synth
+from synth.configs import LayerConfig
+from tests.common import oracle_arrays, oracle_draft, rel_err
+from tests.gpu_common import TOL_DRAFT, say, to_np, tokens_with_clear_routing
+
+pytestmark = pytest.mark.gpu
+
+from paper_2511_14102_amd import binding as B          # noqa: E402
+from paper_2511_14102_amd.harness import DeviceLayer   # noqa: E402
+
+SHAPES = [
+    #            idx  name    H    E   I   k   g  S  renorm
+    LayerConfig(61, "p64", 64, 3, 64, 1, 32, 0, 1),        # fewer k-steps than one stage, one row tile
+    LayerConfig(62, "p192", 192, 5, 320, 2, 64, 0, 1),     # 3 and 5 groups, 10 slices
+    LayerConfig(63, "p320", 320, 2, 192, 2, 32, 0, 0),     # 10 groups, every token in both experts
+    LayerConfig(64, "p640", 640, 4, 384, 2, 128, 0, 1),    # 5 and 3 groups, 12 slices
+    LayerConfig(65, "p256", 256, 40, 128, 3, 128, 0, 1),   # many experts with a token or two
+]
+
+
+@pytest.mark.parametrize("cfg", SHAPES, ids=[c.name for c in SHAPES])
+def test_prefill_tile_edges(cfg):
+    ctx = B.Context(0)
+    sizes = (1, 15, 33, 64, 150)
+    for symmetric in (False, True):
+        if symmetric and B.int4_expert_scale_bytes(B.LayerDesc.from_config(cfg)) == 0:
+            continue
+        L = synth.make_layer(cfg, 0, symmetric=symmetric)
+        A = oracle_arrays(L)
+        D = DeviceLayer(ctx, cfg, L, max_tokens=8, verify=False, symmetric=symmetric)
+        x = tokens_with_clear_routing(cfg, A, max(sizes), step=3, kind="iid")
+        ref = oracle_draft(A, x)
+        for T in sizes:
+            say("prefill", cfg.name, "symmetric" if symmetric else "", "T", T)
+            r = D.prefill(x[:T].cuda())
+            torch.cuda.synchronize()
+            assert np.array_equal(to_np(r["ids"]), ref["ids"][:T])
+            assert rel_err(to_np(r["y"]), ref["y"][:T]) <= TOL_DRAFT
+    ctx.close()
