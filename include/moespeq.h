@@ -283,13 +283,13 @@ int moe_draft_layer_int4_noalloc(moe_ctx *ctx, const moe_layer_desc *desc,
  * MOE_MAX_PREFILL_TOKENS tokens.  All tokens are routed first, the assignments are grouped by
  * expert and cut into work items of up to 64, and every expert's weights are streamed once per
  * item (a token-by-token loop streams them once per assignment): a gate/up contraction per
- * (item, 64 intermediate rows) leaves h in the workspace, a down contraction per (item, 128
+ * (item, 128 intermediate rows) leaves h in the workspace, a down contraction per (item, 256
  * output rows) leaves each assignment's output there, and a last kernel adds up a token's k
  * outputs in assignment order.  No kernel adds into memory that another workgroup writes, so
- * y does not depend on the order in which workgroups run.  Shared experts run over chunks of
- * up to 16 tokens and are added last.
+ * y does not depend on the order in which workgroups run.  A shared expert is one more expert
+ * that every token is assigned to; its outputs are added last.
  * ids_out [T,k] and conf_out [T,k] (or NULL) as in moe_draft_layer_int4; y_f32 [T,H] is written.
- * workspace: moe_prefill_workspace_bytes(desc, T) bytes (it grows with T k (3 H + 2 I) x 2 bytes
+ * workspace: moe_prefill_workspace_bytes(desc, T) bytes (it grows with T (k + S) (3 H + 2 I) x 2 bytes
  * for the operand tiles and outputs of the items), 256-byte aligned, no state is kept in it
  * between calls.
  */

@@ -430,19 +430,17 @@ int moe_draft_layer_int4_noalloc(moe_ctx *ctx, const moe_layer_desc *desc,
 // workspace of a prefill call: routing weights, sorted assignment indices and slots [T k], the
 // item count (one 256-byte line), the items, the operand tiles of x and of h (two planes) with
 // their group sums, a tile of zeros, and the per-slot outputs.
-// With shared experts: two plans (full chunk, ragged last chunk) and the buffers of one chunk of
-// `chunk` tokens through the bf16 kernels.
 struct PrefillLayout {
-    size_t w_all, sorted, slot_of, n_items, items, xt, x_sums, h_hi, h_lo, h_sums, zeros, obuf,
-        plan_full, plan_tail, shared_ws, total;
-    int max_items, chunk;
+    size_t w_all, sorted, slot_of, n_items, items, xt, x_sums, h_hi, h_lo, h_sums, zeros, obuf, total;
+    int max_items;
 };
 static PrefillLayout prefill_layout(const moe_layer_desc &d, int T)
 {
     PrefillLayout L;
     const size_t n = (size_t)T * d.top_k;
     // sum over experts of ceil(count / chunk) <= n / chunk + number of experts that occur
-    L.max_items = (int)(n / kPrefillChunk + ((size_t)d.n_experts < n ? (size_t)d.n_experts : n));
+    L.max_items = (int)(n / kPrefillChunk + ((size_t)d.n_experts < n ? (size_t)d.n_experts : n)) +
+                  d.n_shared * ((T + kPrefillChunk - 1) / kPrefillChunk);
     const PrefillBuffers B = prefill_buffers(d, L.max_items);
     size_t o = 0;
     L.w_all = o;   o += align256(n * 4);
@@ -457,13 +455,6 @@ static PrefillLayout prefill_layout(const moe_layer_desc &d, int T)
     L.h_sums = o;  o += align256(B.h_sums);
     L.zeros = o;   o += align256(B.zeros);
     L.obuf = o;    o += align256(B.obuf);
-    L.chunk = MOE_MAX_ASSIGN / d.top_k < MOE_MAX_TOKENS ? MOE_MAX_ASSIGN / d.top_k : MOE_MAX_TOKENS;
-    L.plan_full = L.plan_tail = L.shared_ws = o;
-    if (d.n_shared > 0) {
-        L.plan_full = o; o += align256(sizeof(Plan));
-        L.plan_tail = o; o += align256(sizeof(Plan));
-        L.shared_ws = o; o += ws_layout(d, L.chunk).total;
-    }
     L.total = o;
     return L;
 }
@@ -517,38 +508,15 @@ int moe_draft_prefill_int4(moe_ctx *ctx, const moe_layer_desc *desc,
     p.h_hi = ws + L.h_hi; p.h_lo = ws + L.h_lo; p.h_sums = ws + L.h_sums; p.zeros = ws + L.zeros;
     p.obuf = (float *)(ws + L.obuf);
     p.y = y;
+    p.shared = shared; p.shared_stride = moe_bf16_expert_bytes(desc);
     { ProfScope t(ctx, MOE_KERNEL_ROUTE, st); launch_route(s, x, wr, bias, ids_out, (float *)(ws + L.w_all), conf_out, st); }
     { ProfScope t(ctx, MOE_KERNEL_PLAN, st);
-      launch_prefill_plan(ids_out, T * s.k, s.E, (int32_t *)(ws + L.sorted), (int32_t *)(ws + L.slot_of),
+      launch_prefill_plan(s, ids_out, (int32_t *)(ws + L.sorted), (int32_t *)(ws + L.slot_of),
                           (PrefillItem *)(ws + L.items), (int32_t *)(ws + L.n_items), st); }
     { ProfScope t(ctx, MOE_KERNEL_PREFILL_STAGE, st); launch_prefill_stage(s, p, L.max_items, st); }
     { ProfScope t(ctx, MOE_KERNEL_PREFILL_GATEUP, st); launch_prefill_gateup(s, p, L.max_items, st); }
     { ProfScope t(ctx, MOE_KERNEL_PREFILL_DOWN, st); launch_prefill_down(s, p, L.max_items, st); }
     { ProfScope t(ctx, MOE_KERNEL_PREFILL_COMBINE, st); launch_prefill_combine(s, p, st); }
-    if (s.S > 0) {
-        // shared experts stay 16-bit (section 3.4.2): chunks of tokens through the bf16 kernels,
-        // added to y; the intermediate keeps a bf16 remainder as in the draft call
-        const size_t bf16_bytes = moe_bf16_expert_bytes(desc);
-        const WsLayout W = ws_layout(*desc, L.chunk);
-        char *sw = ws + L.shared_ws;
-        Shape sc = s;
-        sc.T = L.chunk;
-        Plan *full = (Plan *)(ws + L.plan_full), *tail = (Plan *)(ws + L.plan_tail);
-        if (T >= L.chunk) launch_shared_plan(sc, full, shared, bf16_bytes, st);
-        for (int t0 = 0; t0 < T; t0 += L.chunk) {
-            const int tc = T - t0 < L.chunk ? T - t0 : L.chunk;
-            sc.T = tc;
-            Plan *plan = full;
-            if (tc < L.chunk) { plan = tail; launch_shared_plan(sc, tail, shared, bf16_bytes, st); }
-            const char *xc = (const char *)x + (size_t)t0 * s.H * 2;
-            { ProfScope p(ctx, MOE_KERNEL_BF16_GATEUP, st);
-              launch_bf16_gateup(sc, plan, 0, s.S, xc, sw + W.hb, sw + W.hb_lo, st); }
-            { ProfScope p(ctx, MOE_KERNEL_BF16_DOWN, st);
-              launch_bf16_down(sc, plan, 0, s.S, sw + W.hb, sw + W.hb_lo, (float *)(sw + W.obuf), st); }
-            { ProfScope p(ctx, MOE_KERNEL_COMBINE, st);
-              launch_combine(sc, plan, nullptr, 0, (const float *)(sw + W.obuf), 1, 0, y + (size_t)t0 * s.H, st); }
-        }
-    }
     return hip_status(ctx, hipGetLastError());
 }
 
@@ -611,10 +579,9 @@ int moe_verify_layer_bf16(moe_ctx *ctx, const moe_layer_desc *desc,
     const int nexp = s.S + (s.E < s.T * s.k ? s.E : s.T * s.k);
     { ProfScope p(ctx, MOE_KERNEL_BF16_GATEUP, st); launch_bf16_gateup(s, plan, 0, nexp, x, ws + L.hb, nullptr, st); }
     { ProfScope p(ctx, MOE_KERNEL_BF16_DOWN, st);
-      launch_bf16_down(s, plan, 0, nexp, ws + L.hb, nullptr, (float *)(ws + L.obuf), st); }
+      launch_bf16_down(s, plan, 0, nexp, ws + L.hb, (float *)(ws + L.obuf), st); }
     { ProfScope p(ctx, MOE_KERNEL_COMBINE, st);
-      launch_combine(s, plan, (const float *)(ws + L.obuf), 1, (const float *)(ws + L.obuf),
-                     (flags & MOE_VERIFY_ACCUMULATE) ? 1 : 0, 1, y, st); }
+      launch_combine(s, plan, (const float *)(ws + L.obuf), (flags & MOE_VERIFY_ACCUMULATE) ? 1 : 0, y, st); }
     int rc = hip_status(ctx, hipGetLastError());
     if (rc != MOE_OK) return rc;
     if (flags & MOE_VERIFY_STRICT) {

@@ -3,7 +3,8 @@
 // of section 4.1.3).  The tokens are routed first; every expert's assignments are cut into work
 // items of up to 64, and each expert's weights are streamed once per item:
 //
-//   prefill_plan_kernel    assignments sorted by expert, items, slot of every assignment
+//   prefill_plan_kernel    assignments sorted by expert, items, slot of every assignment; a shared
+//                          expert's items are the tokens in order, in front of the others
 //   prefill_stage_kernel   the items' tokens gathered into MFMA operand tiles (zero padded), and
 //                          each group's sum, in three bf16 pieces, for the zero points
 //   prefill_tile_kernel<gate/up>  one workgroup per (item, four slices of 32 intermediate rows):
@@ -12,7 +13,8 @@
 //                          its bf16 remainder, plus the group sums of h
 //   prefill_tile_kernel<down>     one workgroup per (item, four tiles of 64 output rows): those
 //                          rows x 64 tokens over all of I, written to a per-slot fp32 buffer
-//   prefill_combine_kernel y[t] = sum over the token's k assignments of weight x slot output
+//   prefill_combine_kernel y[t] = sum over the token's k assignments of weight x slot output, and
+//                          over the shared experts of theirs
 //
 // No kernel adds into memory another workgroup writes: every output element has one owner, so
 // the result does not depend on the order in which workgroups run.
@@ -30,6 +32,12 @@
 // of k-steps past the end are zeros): a load inside a branch makes the compiler wait for ALL loads in
 // flight where the branch joins.  The four LDS buffers are four arrays on purpose: the compiler
 // then knows which transfer a read of LDS depends on and does not wait for the later ones.
+//
+// Shared experts stay bf16 (section 3.4.2).  Their items run in the same launches, through a loop
+// of the same form: a wave's 64 weight rows are four bf16 tiles per k-step instead of one tile of
+// codes, which need no unpacking and no scales.  (As chunks of 16 tokens through the verify
+// call's kernels, three launches each, they took 410 of the 605 us of a layer of the dsv2lite shape
+// with 333 tokens.)
 //
 // Arithmetic.  Codes become the exact bf16 integers 16 + q; a group's products are summed by the
 // matrix cores (16x16x32 bf16, fp32 accumulate) and enter the totals with one fused multiply-add by
@@ -67,7 +75,9 @@ struct TileArgs {
     const char *zeros;               // 4 KiB of zeros
     char *h_hi, *h_lo, *h_sums;      // gate/up: out, the same layouts over I
     float *obuf;                     // down: out [item 64 + token][H]
-    int H, I;
+    const char *shared;              // bf16 blobs of the shared experts (experts E, E + 1, ...)
+    size_t shared_stride;
+    int H, I, E;
 };
 
 // The 8 codes of one word as 8 bf16 values 16 + code: 0x4180 is bf16 16.0, and a code in mantissa
@@ -159,6 +169,7 @@ void prefill_tile_kernel(TileArgs a)
     const bool mine = col * kTileWaves + wave < tiles;               // a wave past the end repeats the last tile
     const int tile = mine ? col * kTileWaves + wave : tiles - 1;
 
+    const bool routed = it.expert < a.E;
     const char *wq = a.q + (size_t)it.expert * a.stride_q +
                      (DOWN ? (size_t)(I / 32) * (H / 32) * 1024 + (size_t)tile * 1024 : (size_t)tile * (H / 32) * 1024);
     const size_t wstep = DOWN ? (size_t)(H / 64) * 1024 : 1024;
@@ -184,153 +195,43 @@ void prefill_tile_kernel(TileArgs a)
         else return s_x3;
     };
     const int my_k = DOWN ? wave >> 1 : wave;                        // the k-step (and plane) of a stage this wave requests
-    const char *act = (DOWN && (wave & 1)) ? a.act1 : a.act0;
+    const char *act = ((DOWN && (wave & 1)) ? a.act1 : a.act0) + (size_t)(DOWN ? item : it.src) * nk * 4096;
 
-    // the whole of an item with NTB token blocks (a compile-time count: no branch inside a stage)
-    auto run = [&](auto ntb_c) {
+    // this wave's operand tiles of stage n into buffer j
+    auto request = [&](int n, auto j, auto ntb_c) {
+        const int k = n * SK + my_k;
+        // (chosen with a mask: a branch here would cut the stage into several scheduling regions)
+        const char *from = act + (size_t)k * 4096;
+        const char *src = a.zeros + ((from - a.zeros) & (k < nk ? ~(ptrdiff_t)0 : (ptrdiff_t)0));
+        // Buffer loads, not global ones: after a FLAT-encoded load to LDS the compiler waits for ALL LDS
+        // reads in flight wherever it needs one.
+        const auto rsrc = __builtin_amdgcn_make_buffer_rsrc((void *)src, 0, 4096, 0x00027000);
+        unsigned char *dst = buffer(j) + wave * 4096;
+#pragma unroll
+        for (int tb = 0; tb < decltype(ntb_c)::value; ++tb)
+            __builtin_amdgcn_raw_ptr_buffer_load_lds(rsrc, (lvoid)(dst + tb * 1024), 16, lane * 16, tb * 1024, 0, 0);
+    };
+    // The start of a stage: its operand tiles are in their buffer once this wave's own transfers have landed
+    // and the workgroup has met.  Issued behind those transfers (vector memory operations complete in
+    // order): the weights of three stages, and the transfers of two.
+    auto begin_stage = [&](auto ntb_c, auto stage_loads) {
+        constexpr int kLater = 3 * decltype(stage_loads)::value + 2 * decltype(ntb_c)::value;
+        static_assert(kLater < 64, "vmcnt");
+        __builtin_amdgcn_sched_barrier(0);
+        __builtin_amdgcn_s_waitcnt((kLater & 15) | ((kLater >> 4) << 14) | 0x0f70);
+        __builtin_amdgcn_s_barrier();
+        __builtin_amdgcn_sched_barrier(0);
+    };
+    const int ns = (nk + SK - 1) / SK;
+    constexpr std::integral_constant<int, 0> k0{};
+    constexpr std::integral_constant<int, 1> k1{};
+    constexpr std::integral_constant<int, 2> k2{};
+    constexpr std::integral_constant<int, 3> k3{};
+
+    // The results of an item: lane (r, c) holds, per row block d and token block, row 16 d + r of tokens
+    // 4 c + i.
+    auto finish = [&](auto ntb_c, auto &tot) {
         constexpr int NTB = decltype(ntb_c)::value;
-        auto request = [&](int n, auto j) {
-            const int k = n * SK + my_k;
-            // (chosen with a mask: a branch here would cut the stage into several scheduling regions)
-            const char *from = act + ((size_t)item * nk + k) * 4096;
-            const char *src = a.zeros + ((from - a.zeros) & (k < nk ? ~(ptrdiff_t)0 : (ptrdiff_t)0));
-            // Buffer loads, not global ones: after a FLAT-encoded load to LDS the compiler waits for ALL LDS
-            // reads in flight wherever it needs one.
-            const auto rsrc = __builtin_amdgcn_make_buffer_rsrc((void *)src, 0, 4096, 0x00027000);
-            unsigned char *dst = buffer(j) + wave * 4096;
-#pragma unroll
-            for (int tb = 0; tb < NTB; ++tb)
-                __builtin_amdgcn_raw_ptr_buffer_load_lds(rsrc, (lvoid)(dst + tb * 1024), 16, lane * 16, tb * 1024, 0, 0);
-        };
-        f32x4 tot[4][NTB], acc[4][NTB];
-#pragma unroll
-        for (int d = 0; d < 4; ++d)
-#pragma unroll
-            for (int tb = 0; tb < NTB; ++tb) tot[d][tb] = acc[d][tb] = (f32x4){0.f, 0.f, 0.f, 0.f};
-        u32x4 win[kWin];                           // codes of k-steps k .. k + 7, slot k % 8
-        bf16x8 wb[2][4];                           // operands of k-step k and, as it is unpacked, k + 1
-        Entry<SYM> ent[EW];
-        float sc[4] = {0.f, 0.f, 0.f, 0.f};        // scales of the group that ended last
-        auto add_scaled = [&](int tb) {
-#pragma unroll
-            for (int d = 0; d < 4; ++d) {
-#pragma unroll
-                for (int i = 0; i < 4; ++i) tot[d][tb][i] = fmaf(sc[d], acc[d][tb][i], tot[d][tb][i]);
-                asm volatile("" : "+v"(tot[d][tb]));   // here and not further down, or acc could not be used again
-            }
-        };
-
-        // One stage: its operand tiles are in buffer j once this wave's own transfers have landed and the
-        // workgroup has met; then the buffer that everybody has left takes the stage three further on.
-        // The stage is a row of blocks, one per operand tile: the LDS read three tiles ahead, a share of
-        // the next k-step's unpacking, the scaling of the token block before (its products are complete
-        // by then), and the tile's four MFMAs, so that the vector ALU and LDS work under the matrix
-        // cores.  The barriers between blocks keep the scheduler from gathering all reads of a stage in
-        // front, for which there are no registers.
-        auto stage = [&](int n, auto j) {
-            constexpr int J = decltype(j)::value;
-            constexpr int kFirst = J * SK;         // position in the four stages of a loop trip
-            constexpr int NB = NTB * NP, F = SK * NB, kA = 4;
-            // Issued behind this stage's transfers (vector memory operations complete in order): the
-            // codes of three stages and the transfers of two.
-            constexpr int kLater = 3 * SK + 2 * NTB;
-            static_assert(kLater < 64, "vmcnt");
-            __builtin_amdgcn_sched_barrier(0);
-            __builtin_amdgcn_s_waitcnt((kLater & 15) | ((kLater >> 4) << 14) | 0x0f70);
-            __builtin_amdgcn_s_barrier();
-            __builtin_amdgcn_sched_barrier(0);
-            const unsigned char *buf = buffer(j);
-            u32x4 xa[kA];
-            auto read = [&](int f) {               // tile f of the stage: k-step, token block, plane
-                const int s = f / NB, tb = f % NB / NP, p = f % NP;
-                xa[f % kA] = *reinterpret_cast<const u32x4 *>(&buf[((s * NP + p) * 4 + tb) * 1024 + lane * 16]);
-            };
-#pragma unroll
-            for (int f = 0; f < kA - 1 && f < F; ++f) read(f);
-            request(n + 3, std::integral_constant<int, (J + 3) & 3>{});
-#pragma unroll
-            for (int f = 0; f < F; ++f) {
-                const int s = f / NB, t = f % NB, tb = t / NP, p = t % NP;
-                const int pos = kFirst + s;
-                const bool begins = pos % KPG == 0, ends = (pos + 1) % KPG == 0;      // of a group
-                __builtin_amdgcn_sched_barrier(0);
-                if (f + kA - 1 < F) read(f + kA - 1);
-                if (begins && t == 0) add_scaled(NTB - 1);                            // of the group before
-                if (ends && t == 0) {
-                    constexpr int kGroups = 4 * SK / KPG;
-                    static_assert(kGroups % EW == 0, "the slot of a group has to be the same in every loop trip");
-                    const int slot = (pos / KPG) % EW;
-#pragma unroll
-                    for (int d = 0; d < 4; ++d) sc[d] = ent[slot].scale(d);
-                    ent[slot] = entry_at((n * SK + s) / KPG + EW);
-                }
-                const int nx = (pos + 1) % kWin;
-#pragma unroll
-                for (int d = 0; d < 4; ++d)
-                    if (d * NB / 4 == t) wb[(s + 1) & 1][d] = unpack8_16(win[nx][d], uk);
-                if (t == NB - 1) win[nx] = load_codes(n * SK + s + 1 + kWin);
-#pragma unroll
-                for (int d = 0; d < 4; ++d)
-                    acc[d][tb] = mfma(xa[f % kA], wb[s & 1][d], begins && p == 0 ? (f32x4){0.f, 0.f, 0.f, 0.f} : acc[d][tb]);
-                if (ends && p == 0 && tb > 0) add_scaled(tb - 1);
-            }
-            __builtin_amdgcn_sched_barrier(0);
-        };
-        const int ns = (nk + SK - 1) / SK;
-        request(0, std::integral_constant<int, 0>{});
-        request(1, std::integral_constant<int, 1>{});
-        request(2, std::integral_constant<int, 2>{});
-        __builtin_amdgcn_sched_barrier(0);
-#pragma unroll
-        for (int i = 0; i < kWin; ++i) win[i] = load_codes(i);
-#pragma unroll
-        for (int i = 0; i < EW; ++i) ent[i] = entry_at(i);
-        // the first stages' transfers have fewer operations behind them than the steady state counts on
-        __builtin_amdgcn_sched_barrier(0);
-        __builtin_amdgcn_s_waitcnt(0x0070);
-#pragma unroll
-        for (int d = 0; d < 4; ++d) wb[0][d] = unpack8_16(win[0][d], uk);
-        win[0] = load_codes(kWin);
-        for (int n = 0; n < ns; n += 4) {
-            stage(n, std::integral_constant<int, 0>{});
-            stage(n + 1, std::integral_constant<int, 1>{});
-            stage(n + 2, std::integral_constant<int, 2>{});
-            stage(n + 3, std::integral_constant<int, 3>{});
-        }
-        // every last stage ends a group (k-steps past the end are zeros)
-        add_scaled(NTB - 1);
-        // the contraction over groups
-        {
-            const char *zs = a.act_sums + (size_t)item * nz * 4096 + lane * 16;
-            u32x4 zx[2][NTB];
-            Entry<SYM> ze[2];
-            auto load_sums = [&](int q, int b) {
-                const int qq = q < nz ? q : nz - 1;
-#pragma unroll
-                for (int tb = 0; tb < NTB; ++tb) zx[b][tb] = *reinterpret_cast<const u32x4 *>(zs + ((size_t)qq * 4 + tb) * 1024);
-                ze[b] = entry_at(4 * qq + c);
-            };
-            auto add_sums = [&](int b) {
-#pragma unroll
-                for (int d = 0; d < 4; ++d) {
-                    const bf16x8 f = __builtin_bit_cast(bf16x8, factor_operand(-ze[b].scale(d) * ze[b].zero16(d)));
-#pragma unroll
-                    for (int tb = 0; tb < NTB; ++tb) tot[d][tb] = mfma(zx[b][tb], f, tot[d][tb]);
-                }
-            };
-            load_sums(0, 0);
-            load_sums(1, 1);
-            int q = 0;
-            for (; q + 1 < nz; q += 2) {
-                add_sums(0);
-                load_sums(q + 2, 0);
-                add_sums(1);
-                load_sums(q + 3, 1);
-            }
-            if (q < nz) add_sums(0);
-        }
-
-        // lane (r, c) holds, per row block d and token block, row 16 d + r of tokens 4 c + i
         if constexpr (DOWN) {
             if (!mine) return;
 #pragma unroll
@@ -388,6 +289,7 @@ void prefill_tile_kernel(TileArgs a)
                 if (c == 0) s_hsum[wave][16 * tb + r] = sum;
             }
             __syncthreads();
+            if (!routed) return;
             // group sums of h: the workgroup's 128 columns hold 4 / KPG whole groups; the last column of
             // workgroups also clears what is left of the last tile of four groups
             const int tok = tid & 63, pos = tid >> 6;
@@ -406,33 +308,232 @@ void prefill_tile_kernel(TileArgs a)
             }
         }
     };
+
+    // an item of a routed expert with NTB token blocks (a compile-time count: no branch inside a stage)
+    auto run = [&](auto ntb_c) {
+        constexpr int NTB = decltype(ntb_c)::value;
+        f32x4 tot[4][NTB], acc[4][NTB];
+#pragma unroll
+        for (int d = 0; d < 4; ++d)
+#pragma unroll
+            for (int tb = 0; tb < NTB; ++tb) tot[d][tb] = acc[d][tb] = (f32x4){0.f, 0.f, 0.f, 0.f};
+        u32x4 win[kWin];                           // codes of k-steps k .. k + 7, slot k % 8
+        bf16x8 wb[2][4];                           // operands of k-step k and, as it is unpacked, k + 1
+        Entry<SYM> ent[EW];
+        float sc[4] = {0.f, 0.f, 0.f, 0.f};        // scales of the group that ended last
+        auto add_scaled = [&](int tb) {
+#pragma unroll
+            for (int d = 0; d < 4; ++d) {
+#pragma unroll
+                for (int i = 0; i < 4; ++i) tot[d][tb][i] = fmaf(sc[d], acc[d][tb][i], tot[d][tb][i]);
+                asm volatile("" : "+v"(tot[d][tb]));   // here and not further down, or acc could not be used again
+            }
+        };
+
+        // One stage: the buffer that everybody has left takes the operand tiles three stages further on.
+        // The stage is a row of blocks, one per operand tile: the LDS read three tiles ahead, a share of
+        // the next k-step's unpacking, the scaling of the token block before (its products are complete
+        // by then), and the tile's four MFMAs, so that the vector ALU and LDS work under the matrix
+        // cores.  The barriers between blocks keep the scheduler from gathering all reads of a stage in
+        // front, for which there are no registers.
+        auto stage = [&](int n, auto j) {
+            constexpr int J = decltype(j)::value;
+            constexpr int kFirst = J * SK;         // position in the four stages of a loop trip
+            constexpr int NB = NTB * NP, F = SK * NB, kA = 4;
+            begin_stage(ntb_c, std::integral_constant<int, SK>{});
+            const unsigned char *buf = buffer(j);
+            u32x4 xa[kA];
+            auto read = [&](int f) {               // tile f of the stage: k-step, token block, plane
+                const int s = f / NB, tb = f % NB / NP, p = f % NP;
+                xa[f % kA] = *reinterpret_cast<const u32x4 *>(&buf[((s * NP + p) * 4 + tb) * 1024 + lane * 16]);
+            };
+#pragma unroll
+            for (int f = 0; f < kA - 1 && f < F; ++f) read(f);
+            request(n + 3, std::integral_constant<int, (J + 3) & 3>{}, ntb_c);
+#pragma unroll
+            for (int f = 0; f < F; ++f) {
+                const int s = f / NB, t = f % NB, tb = t / NP, p = t % NP;
+                const int pos = kFirst + s;
+                const bool begins = pos % KPG == 0, ends = (pos + 1) % KPG == 0;      // of a group
+                __builtin_amdgcn_sched_barrier(0);
+                if (f + kA - 1 < F) read(f + kA - 1);
+                if (begins && t == 0) add_scaled(NTB - 1);                            // of the group before
+                if (ends && t == 0) {
+                    constexpr int kGroups = 4 * SK / KPG;
+                    static_assert(kGroups % EW == 0, "the slot of a group has to be the same in every loop trip");
+                    const int slot = (pos / KPG) % EW;
+#pragma unroll
+                    for (int d = 0; d < 4; ++d) sc[d] = ent[slot].scale(d);
+                    ent[slot] = entry_at((n * SK + s) / KPG + EW);
+                }
+                const int nx = (pos + 1) % kWin;
+#pragma unroll
+                for (int d = 0; d < 4; ++d)
+                    if (d * NB / 4 == t) wb[(s + 1) & 1][d] = unpack8_16(win[nx][d], uk);
+                if (t == NB - 1) win[nx] = load_codes(n * SK + s + 1 + kWin);
+#pragma unroll
+                for (int d = 0; d < 4; ++d)
+                    acc[d][tb] = mfma(xa[f % kA], wb[s & 1][d], begins && p == 0 ? (f32x4){0.f, 0.f, 0.f, 0.f} : acc[d][tb]);
+                if (ends && p == 0 && tb > 0) add_scaled(tb - 1);
+            }
+            __builtin_amdgcn_sched_barrier(0);
+        };
+        request(0, k0, ntb_c);
+        request(1, k1, ntb_c);
+        request(2, k2, ntb_c);
+        __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+        for (int i = 0; i < kWin; ++i) win[i] = load_codes(i);
+#pragma unroll
+        for (int i = 0; i < EW; ++i) ent[i] = entry_at(i);
+        // the first stages' transfers have fewer operations behind them than the steady state counts on
+        __builtin_amdgcn_sched_barrier(0);
+        __builtin_amdgcn_s_waitcnt(0x0070);
+#pragma unroll
+        for (int d = 0; d < 4; ++d) wb[0][d] = unpack8_16(win[0][d], uk);
+        win[0] = load_codes(kWin);
+        for (int n = 0; n < ns; n += 4) {
+            stage(n, k0);
+            stage(n + 1, k1);
+            stage(n + 2, k2);
+            stage(n + 3, k3);
+        }
+        // every last stage ends a group (k-steps past the end are zeros)
+        add_scaled(NTB - 1);
+        // the contraction over groups
+        {
+            const char *zs = a.act_sums + (size_t)item * nz * 4096 + lane * 16;
+            u32x4 zx[2][NTB];
+            Entry<SYM> ze[2];
+            auto load_sums = [&](int q, int b) {
+                const int qq = q < nz ? q : nz - 1;
+#pragma unroll
+                for (int tb = 0; tb < NTB; ++tb) zx[b][tb] = *reinterpret_cast<const u32x4 *>(zs + ((size_t)qq * 4 + tb) * 1024);
+                ze[b] = entry_at(4 * qq + c);
+            };
+            auto add_sums = [&](int b) {
+#pragma unroll
+                for (int d = 0; d < 4; ++d) {
+                    const bf16x8 f = __builtin_bit_cast(bf16x8, factor_operand(-ze[b].scale(d) * ze[b].zero16(d)));
+#pragma unroll
+                    for (int tb = 0; tb < NTB; ++tb) tot[d][tb] = mfma(zx[b][tb], f, tot[d][tb]);
+                }
+            };
+            load_sums(0, 0);
+            load_sums(1, 1);
+            int q = 0;
+            for (; q + 1 < nz; q += 2) {
+                add_sums(0);
+                load_sums(q + 2, 0);
+                add_sums(1);
+                load_sums(q + 3, 1);
+            }
+            if (q < nz) add_sums(0);
+        }
+
+        finish(ntb_c, tot);
+    };
+
+    // an item of a shared expert: the same loop over bf16 weight tiles
+    auto run_shared = [&](auto ntb_c) {
+        constexpr int NTB = decltype(ntb_c)::value;
+        constexpr int kWinS = 4;                   // k-steps of weights in flight
+        // row block d: gate or up rows 32 tile + 16 (d % 2) .., or output rows 64 tile + 16 d ..
+        const char *blob = a.shared + (size_t)(it.expert - a.E) * a.shared_stride;
+        const char *rows[4];
+#pragma unroll
+        for (int d = 0; d < 4; ++d)
+            rows[d] = DOWN ? blob + (size_t)I * H * 4 + (size_t)(4 * tile + d) * nk * 1024
+                           : blob + (size_t)(d / 2) * I * H * 2 + (size_t)(2 * tile + d % 2) * nk * 1024;
+        auto load_weights = [&](int k, int d) {
+            return *reinterpret_cast<const u32x4 *>(rows[d] + (size_t)(k < nk ? k : nk - 1) * 1024 + lane * 16);
+        };
+        f32x4 acc[4][NTB];
+        u32x4 win[kWinS][4];
+#pragma unroll
+        for (int d = 0; d < 4; ++d)
+#pragma unroll
+            for (int tb = 0; tb < NTB; ++tb) acc[d][tb] = (f32x4){0.f, 0.f, 0.f, 0.f};
+        auto stage = [&](int n, auto j) {
+            constexpr int J = decltype(j)::value;
+            constexpr int kFirst = J * SK;
+            constexpr int NB = NTB * NP, F = SK * NB, kA = 4;
+            begin_stage(ntb_c, std::integral_constant<int, 4 * SK>{});
+            const unsigned char *buf = buffer(j);
+            u32x4 xa[kA];
+            auto read = [&](int f) {
+                const int s = f / NB, tb = f % NB / NP, p = f % NP;
+                xa[f % kA] = *reinterpret_cast<const u32x4 *>(&buf[((s * NP + p) * 4 + tb) * 1024 + lane * 16]);
+            };
+#pragma unroll
+            for (int f = 0; f < kA - 1 && f < F; ++f) read(f);
+            request(n + 3, std::integral_constant<int, (J + 3) & 3>{}, ntb_c);
+#pragma unroll
+            for (int f = 0; f < F; ++f) {
+                const int s = f / NB, t = f % NB, tb = t / NP;
+                const int slot = (kFirst + s) % kWinS;
+                __builtin_amdgcn_sched_barrier(0);
+                if (f + kA - 1 < F) read(f + kA - 1);
+#pragma unroll
+                for (int d = 0; d < 4; ++d)
+                    acc[d][tb] = mfma(xa[f % kA], __builtin_bit_cast(bf16x8, win[slot][d]), acc[d][tb]);
+                if (t == NB - 1) {
+#pragma unroll
+                    for (int d = 0; d < 4; ++d) win[slot][d] = load_weights(n * SK + s + kWinS, d);
+                }
+            }
+            __builtin_amdgcn_sched_barrier(0);
+        };
+        request(0, k0, ntb_c);
+        request(1, k1, ntb_c);
+        request(2, k2, ntb_c);
+        __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+        for (int i = 0; i < kWinS; ++i)
+#pragma unroll
+            for (int d = 0; d < 4; ++d) win[i][d] = load_weights(i, d);
+        __builtin_amdgcn_sched_barrier(0);
+        __builtin_amdgcn_s_waitcnt(0x0070);
+        for (int n = 0; n < ns; n += 4) {
+            stage(n, k0);
+            stage(n + 1, k1);
+            stage(n + 2, k2);
+            stage(n + 3, k3);
+        }
+        finish(ntb_c, acc);
+    };
     const int ntb = (it.cnt + 15) >> 4;
-    if (ntb == 4) run(std::integral_constant<int, 4>{});
-    else if (ntb == 3) run(std::integral_constant<int, 3>{});
-    else if (ntb == 2) run(std::integral_constant<int, 2>{});
-    else run(std::integral_constant<int, 1>{});
+    auto by_blocks = [&](auto &&go) {
+        if (ntb == 4) go(std::integral_constant<int, 4>{});
+        else if (ntb == 3) go(std::integral_constant<int, 3>{});
+        else if (ntb == 2) go(std::integral_constant<int, 2>{});
+        else go(std::integral_constant<int, 1>{});
+    };
+    if (routed) by_blocks(run);
+    else by_blocks(run_shared);
 }
 
 // Gathers the tokens of token block (item, tb) into operand tiles [(item nk + u) 4 + tb]: lane
 // (token, chunk) of tile u holds x[token][32 u + 8 chunk .. + 7]; positions past the item's count
-// hold zeros.  Also the group sums as operand tiles [(item nz + group / 4) 4 + tb].  One wave per
+// hold zeros.  (The shared experts read one copy.)  Also the group sums as operand tiles [(item nz + group / 4) 4 + tb].  One wave per
 // (block, four tiles): 128 inputs, whole groups.  The first workgroup also writes the tile of zeros.
 template <int KPG>
 __global__ __launch_bounds__(256)
 void prefill_stage_kernel(const uint16_t *__restrict__ x, const PrefillItem *__restrict__ items,
                           const int32_t *__restrict__ n_items, const int32_t *__restrict__ sorted,
-                          char *__restrict__ xt, char *__restrict__ sums, char *__restrict__ zeros, int H, int k)
+                          char *__restrict__ xt, char *__restrict__ sums, char *__restrict__ zeros, int H, int k, int E)
 {
     if (blockIdx.x == 0 && blockIdx.y == 0)
         *reinterpret_cast<u32x4 *>(zeros + threadIdx.x * 16) = (u32x4){0u, 0u, 0u, 0u};
     const int item = blockIdx.x >> 2, tb = blockIdx.x & 3;
     if (item >= *n_items) return;
     const PrefillItem it = items[item];
-    if (16 * tb >= it.cnt) return;
+    if (16 * tb >= it.cnt || it.src != item) return;
     const int nk = H / 32, u4 = blockIdx.y * 4 + (threadIdx.x >> 6);
     if (u4 * 4 >= nk) return;
     const int lane = threadIdx.x & 63, tok16 = lane & 15, chunk = lane >> 4, pos = 16 * tb + tok16;
-    const int token = pos < it.cnt ? sorted[it.first + pos] / k : 0;
+    const int at = it.first + (pos < it.cnt ? pos : 0);
+    const int token = it.expert < E ? sorted[at] / k : at;
     float s[4];
 #pragma unroll
     for (int j = 0; j < 4; ++j) {
@@ -464,20 +565,25 @@ void prefill_stage_kernel(const uint16_t *__restrict__ x, const PrefillItem *__r
 // Sorts the n = T k assignments by expert (the order inside an expert is arbitrary: no result
 // depends on it, a row's sums do not depend on the other rows of its item), cuts every expert's
 // run into items of at most 64 and records the slot (item x 64 + position) of every assignment.
-// One workgroup.
+// The first S ceil(T / 64) items are the shared experts', over the tokens in order.  One workgroup.
 __global__ __launch_bounds__(1024)
-void prefill_plan_kernel(const int32_t *__restrict__ ids, int n, int E,
+void prefill_plan_kernel(const int32_t *__restrict__ ids, int n, int E, int T, int S,
                          int32_t *__restrict__ sorted, int32_t *__restrict__ slot_of,
                          PrefillItem *__restrict__ items, int32_t *__restrict__ n_items)
 {
     __shared__ int32_t s_count[MOE_MAX_EXPERTS], s_off[MOE_MAX_EXPERTS], s_fill[MOE_MAX_EXPERTS],
         s_item0[MOE_MAX_EXPERTS];
+    const int chunks = (T + kItemTokens - 1) / kItemTokens;
+    for (int i = threadIdx.x; i < S * chunks; i += blockDim.x) {
+        const int j = i % chunks;
+        items[i] = PrefillItem{E + i / chunks, j * kItemTokens, T - j * kItemTokens < kItemTokens ? T - j * kItemTokens : kItemTokens, j};
+    }
     for (int e = threadIdx.x; e < E; e += blockDim.x) { s_count[e] = 0; s_fill[e] = 0; }
     __syncthreads();
     for (int i = threadIdx.x; i < n; i += blockDim.x) atomicAdd(&s_count[ids[i]], 1);
     __syncthreads();
     if (threadIdx.x == 0) {
-        int off = 0, item = 0;
+        int off = 0, item = S * chunks;
         for (int e = 0; e < E; ++e) {
             s_off[e] = off;
             s_item0[e] = item;
@@ -499,16 +605,16 @@ void prefill_plan_kernel(const int32_t *__restrict__ ids, int n, int E,
             PrefillItem it;
             it.expert = e; it.first = s_off[e] + j * kItemTokens;
             it.cnt = cnt - j * kItemTokens < kItemTokens ? cnt - j * kItemTokens : kItemTokens;
-            it.pad = 0;
+            it.src = s_item0[e] + j;
             items[s_item0[e] + j] = it;
         }
     }
 }
 
-// y[t][:] = sum_j w[t k + j] * obuf[slot_of[t k + j]][:], j ascending
+// y[t][:] = sum_j w[t k + j] * obuf[slot_of[t k + j]][:], j ascending, then the shared experts' rows
 __global__ __launch_bounds__(256)
 void prefill_combine_kernel(const float *__restrict__ obuf, const int32_t *__restrict__ slot_of,
-                            const float *__restrict__ w_all, float *__restrict__ y, int H, int k)
+                            const float *__restrict__ w_all, float *__restrict__ y, int H, int k, int S)
 {
     const int t = blockIdx.x, col = (blockIdx.y * 256 + threadIdx.x) * 4;
     if (col >= H) return;
@@ -520,6 +626,8 @@ void prefill_combine_kernel(const float *__restrict__ obuf, const int32_t *__res
 #pragma unroll
         for (int i = 0; i < 4; ++i) acc[i] = fmaf(w, v[i], acc[i]);
     }
+    const int slots = (int)(gridDim.x + kItemTokens - 1) / kItemTokens * kItemTokens;      // of one shared expert
+    for (int sh = 0; sh < S; ++sh) acc += *reinterpret_cast<const f32x4 *>(obuf + ((size_t)sh * slots + t) * H + col);
     *reinterpret_cast<f32x4 *>(y + (size_t)t * H + col) = acc;
 }
 
@@ -555,10 +663,10 @@ PrefillBuffers prefill_buffers(const moe_layer_desc &d, int max_items)
     return b;
 }
 
-void launch_prefill_plan(const int32_t *ids, int n, int E, int32_t *sorted, int32_t *slot_of,
+void launch_prefill_plan(const Shape &s, const int32_t *ids, int32_t *sorted, int32_t *slot_of,
                          PrefillItem *items, int32_t *n_items, hipStream_t st)
 {
-    launch(prefill_plan_kernel, dim3(1), dim3(1024), 0, st, ids, n, E, sorted, slot_of, items, n_items);
+    launch(prefill_plan_kernel, dim3(1), dim3(1024), 0, st, ids, s.T * s.k, s.E, s.T, s.S, sorted, slot_of, items, n_items);
 }
 
 void launch_prefill_stage(const Shape &s, const PrefillCall &p, int max_items, hipStream_t st)
@@ -566,7 +674,7 @@ void launch_prefill_stage(const Shape &s, const PrefillCall &p, int max_items, h
     const dim3 grid(max_items * 4, (s.H / 32 + 15) / 16), block(256);
     auto go = [&](auto kernel) {
         launch(kernel, grid, block, 0, st, (const uint16_t *)p.x, p.items, p.n_items, p.sorted, (char *)p.xt,
-               (char *)p.x_sums, (char *)p.zeros, s.H, s.k);
+               (char *)p.x_sums, (char *)p.zeros, s.H, s.k, s.E);
     };
     if (s.g == 32) go(prefill_stage_kernel<1>);
     else if (s.g == 64) go(prefill_stage_kernel<2>);
@@ -579,7 +687,8 @@ static TileArgs tile_args(const Shape &s, const PrefillCall &p)
     t.q = (const char *)p.q; t.sz = (const char *)p.sz; t.stride_q = p.stride_q; t.stride_sz = p.stride_sz;
     t.items = p.items; t.n_items = p.n_items; t.zeros = (const char *)p.zeros;
     t.h_hi = (char *)p.h_hi; t.h_lo = (char *)p.h_lo; t.h_sums = (char *)p.h_sums; t.obuf = p.obuf;
-    t.H = s.H; t.I = s.I;
+    t.shared = (const char *)p.shared; t.shared_stride = p.shared_stride;
+    t.H = s.H; t.I = s.I; t.E = s.E;
     return t;
 }
 
@@ -600,7 +709,7 @@ void launch_prefill_down(const Shape &s, const PrefillCall &p, int max_items, hi
 void launch_prefill_combine(const Shape &s, const PrefillCall &p, hipStream_t st)
 {
     launch(prefill_combine_kernel, dim3(s.T, (s.H / 4 + 255) / 256), dim3(256), 0, st,
-           (const float *)p.obuf, p.slot_of, p.w_all, p.y, s.H, s.k);
+           (const float *)p.obuf, p.slot_of, p.w_all, p.y, s.H, s.k, s.S);
 }
 
 }  // namespace moespeq

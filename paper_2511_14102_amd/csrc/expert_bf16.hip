@@ -113,10 +113,10 @@ void bf16_gateup_kernel(const Plan *__restrict__ plan, int first_active,
 
 // obuf[row, r] = row_w[row] * (Wd h[row])[r] for 16 values of r.
 // grid.x = H / 16, grid.y = experts; block = 4 waves splitting K = I.
-// kHiLo: the operand is hb + hb_lo (two MFMAs per tile).  kAddY: instead of writing obuf, add the
-// row's outputs to y[token] with fp32 atomics (the draft call's shared experts: y already holds
+// kShared (the draft call's shared experts): the operand is hb + hb_lo (two MFMAs per tile), and
+// instead of writing obuf the row's outputs are added to y[token] with fp32 atomics (y already holds
 // the routed experts' sum, itself made of such atomics, so no combine launch is needed).
-template <bool kHiLo, bool kAddY>
+template <bool kShared>
 __global__ __launch_bounds__(kWaves * 64)
 void bf16_down_kernel(const Plan *__restrict__ plan, int first_active,
                       const uint16_t *__restrict__ hb, const uint16_t *__restrict__ hb_lo,
@@ -136,7 +136,7 @@ void bf16_down_kernel(const Plan *__restrict__ plan, int first_active,
     const bool live = n < cnt;
     const size_t hoff = (size_t)(off + (live ? n : 0)) * I + c * 8;
     const uint16_t *hrow = hb + hoff;
-    const uint16_t *lrow = kHiLo ? hb_lo + hoff : nullptr;
+    const uint16_t *lrow = kShared ? hb_lo + hoff : nullptr;
     const int ku0 = (wave * U) / kWaves, ku1 = ((wave + 1) * U) / kWaves;
     const u32x4 zero = {0u, 0u, 0u, 0u};
 
@@ -148,19 +148,19 @@ void bf16_down_kernel(const Plan *__restrict__ plan, int first_active,
         for (int i = 0; i < kUnroll; ++i) {
             a[i] = __builtin_nontemporal_load(wd + (size_t)(ku + i) * 64);
             hv[i] = live ? *reinterpret_cast<const u32x4 *>(hrow + (ku + i) * 32) : zero;
-            if (kHiLo) lv[i] = live ? *reinterpret_cast<const u32x4 *>(lrow + (ku + i) * 32) : zero;
+            if (kShared) lv[i] = live ? *reinterpret_cast<const u32x4 *>(lrow + (ku + i) * 32) : zero;
         }
 #pragma unroll
         for (int i = 0; i < kUnroll; ++i) {
             acc = mfma16(a[i], hv[i], acc);
-            if (kHiLo) acc = mfma16(a[i], lv[i], acc);
+            if (kShared) acc = mfma16(a[i], lv[i], acc);
         }
     }
     for (; ku < ku1; ++ku) {
         u32x4 a = __builtin_nontemporal_load(wd + (size_t)ku * 64);
         u32x4 hv = live ? *reinterpret_cast<const u32x4 *>(hrow + ku * 32) : zero;
         acc = mfma16(a, hv, acc);
-        if (kHiLo) {
+        if (kShared) {
             u32x4 lv = live ? *reinterpret_cast<const u32x4 *>(lrow + ku * 32) : zero;
             acc = mfma16(a, lv, acc);
         }
@@ -181,7 +181,7 @@ void bf16_down_kernel(const Plan *__restrict__ plan, int first_active,
         for (int w = 0; w < kWaves; ++w) v += s_red[w][i][lane];
         op[i] = v * rw;
     }
-    if constexpr (kAddY) {
+    if constexpr (kShared) {
         float *yrow = obuf + (size_t)plan->row_tok[off + n] * H + blockIdx.x * 16 + c * 4;   // obuf is y here
 #pragma unroll
         for (int i = 0; i < 4; ++i)
@@ -191,13 +191,10 @@ void bf16_down_kernel(const Plan *__restrict__ plan, int first_active,
     }
 }
 
-// Final sum per token in a fixed order: routed rows by rank j (each summed over the K-splits),
-// then shared rows.  grid (ceil(H / 1024), T), 256 threads x 4 columns.
-template <bool kOutBf16>
+// Final sum per token in a fixed order: routed rows by rank j, then shared rows.  grid (ceil(H / 1024), T), 256 threads x 4 columns.
 __global__ __launch_bounds__(256)
-void combine_kernel(const Plan *__restrict__ plan, const float *__restrict__ routed, int nsplit,
-                    const float *__restrict__ obuf, int accumulate, void *__restrict__ y,
-                    int T, int H, int k, int S)
+void combine_kernel(const Plan *__restrict__ plan, const float *__restrict__ obuf, int accumulate,
+                    uint16_t *__restrict__ y, int T, int H, int k, int S)
 {
     __shared__ int32_t s_pos[MOE_MAX_TOPK];
     const int t = blockIdx.y;
@@ -212,23 +209,17 @@ void combine_kernel(const Plan *__restrict__ plan, const float *__restrict__ rou
     if (h >= H) return;
     float4 acc = make_float4(0.f, 0.f, 0.f, 0.f);
     if (accumulate) {
-        if (kOutBf16) {
-            uint2 old = *reinterpret_cast<const uint2 *>((const uint16_t *)y + (size_t)t * H + h);
-            acc.x = __uint_as_float(old.x << 16);
-            acc.y = __uint_as_float(old.x & 0xffff0000u);
-            acc.z = __uint_as_float(old.y << 16);
-            acc.w = __uint_as_float(old.y & 0xffff0000u);
-        } else {
-            acc = *reinterpret_cast<const float4 *>((const float *)y + (size_t)t * H + h);
-        }
+        uint2 old = *reinterpret_cast<const uint2 *>(y + (size_t)t * H + h);
+        acc.x = __uint_as_float(old.x << 16);
+        acc.y = __uint_as_float(old.x & 0xffff0000u);
+        acc.z = __uint_as_float(old.y << 16);
+        acc.w = __uint_as_float(old.y & 0xffff0000u);
     }
     for (int j = 0; j < k; ++j) {
         const int pos = s_pos[j];
         if (!plan->row_live[pos]) continue;
-        for (int sp = 0; sp < nsplit; ++sp) {
-            float4 v = *reinterpret_cast<const float4 *>(routed + ((size_t)sp * n + pos) * H + h);
-            acc.x += v.x; acc.y += v.y; acc.z += v.z; acc.w += v.w;
-        }
+        float4 v = *reinterpret_cast<const float4 *>(obuf + (size_t)pos * H + h);
+        acc.x += v.x; acc.y += v.y; acc.z += v.z; acc.w += v.w;
     }
     for (int s = 0; s < S; ++s) {
         const int pos = n + s * T + t;
@@ -236,13 +227,9 @@ void combine_kernel(const Plan *__restrict__ plan, const float *__restrict__ rou
         float4 v = *reinterpret_cast<const float4 *>(obuf + (size_t)pos * H + h);
         acc.x += v.x; acc.y += v.y; acc.z += v.z; acc.w += v.w;
     }
-    if (kOutBf16) {
-        uint2 pk = make_uint2((uint32_t)f32_to_bf16_rne(acc.x) | ((uint32_t)f32_to_bf16_rne(acc.y) << 16),
-                              (uint32_t)f32_to_bf16_rne(acc.z) | ((uint32_t)f32_to_bf16_rne(acc.w) << 16));
-        *reinterpret_cast<uint2 *>((uint16_t *)y + (size_t)t * H + h) = pk;
-    } else {
-        *reinterpret_cast<float4 *>((float *)y + (size_t)t * H + h) = acc;
-    }
+    *reinterpret_cast<uint2 *>(y + (size_t)t * H + h) =
+        make_uint2((uint32_t)f32_to_bf16_rne(acc.x) | ((uint32_t)f32_to_bf16_rne(acc.y) << 16),
+                   (uint32_t)f32_to_bf16_rne(acc.z) | ((uint32_t)f32_to_bf16_rne(acc.w) << 16));
 }
 
 }  // namespace
@@ -261,16 +248,12 @@ void launch_bf16_gateup(const Shape &s, const Plan *plan, int first_active, int 
 }
 
 void launch_bf16_down(const Shape &s, const Plan *plan, int first_active, int n_active_max,
-                      const void *hb, const void *hb_lo, float *obuf, hipStream_t st)
+                      const void *hb, float *obuf, hipStream_t st)
 {
     if (n_active_max <= 0) return;
     const dim3 grid(s.H / 16, n_active_max), block(kWaves * 64);
-    if (hb_lo)
-        launch(bf16_down_kernel<true, false>, grid, block, 0, st, plan, first_active,
-                           (const uint16_t *)hb, (const uint16_t *)hb_lo, obuf, s.H, s.I);
-    else
-        launch(bf16_down_kernel<false, false>, grid, block, 0, st, plan, first_active,
-                           (const uint16_t *)hb, (const uint16_t *)nullptr, obuf, s.H, s.I);
+    launch(bf16_down_kernel<false>, grid, block, 0, st, plan, first_active,
+                       (const uint16_t *)hb, (const uint16_t *)nullptr, obuf, s.H, s.I);
 }
 
 void launch_bf16_down_add(const Shape &s, const Plan *plan, int first_active, int n_active_max,
@@ -278,20 +261,14 @@ void launch_bf16_down_add(const Shape &s, const Plan *plan, int first_active, in
 {
     if (n_active_max <= 0) return;
     const dim3 grid(s.H / 16, n_active_max), block(kWaves * 64);
-    launch(bf16_down_kernel<true, true>, grid, block, 0, st, plan, first_active,
+    launch(bf16_down_kernel<true>, grid, block, 0, st, plan, first_active,
                        (const uint16_t *)hb, (const uint16_t *)hb_lo, y, s.H, s.I);
 }
 
-void launch_combine(const Shape &s, const Plan *plan, const float *routed, int nsplit,
-                    const float *obuf, int accumulate, int out_bf16, void *y, hipStream_t st)
+void launch_combine(const Shape &s, const Plan *plan, const float *obuf, int accumulate, void *y, hipStream_t st)
 {
-    dim3 grid((s.H + 1023) / 1024, s.T);
-    if (out_bf16)
-        launch(combine_kernel<true>, grid, dim3(256), 0, st, plan, routed, nsplit, obuf,
-                           accumulate, y, s.T, s.H, s.k, s.S);
-    else
-        launch(combine_kernel<false>, grid, dim3(256), 0, st, plan, routed, nsplit, obuf,
-                           accumulate, y, s.T, s.H, s.k, s.S);
+    launch(combine_kernel, dim3((s.H + 1023) / 1024, s.T), dim3(256), 0, st, plan, obuf, accumulate,
+           (uint16_t *)y, s.T, s.H, s.k, s.S);
 }
 
 }  // namespace moespeq

@@ -93,21 +93,19 @@ struct PlanArgs {
     int32_t *ids_out; float *conf_out;
     int32_t *missing; int32_t *n_missing;
 };
-void launch_plan(const Shape &s, const PlanArgs &a, hipStream_t st);
 // router + plan in one launch; logits: [T, E] fp64 scratch; token_arrivals [MOE_MAX_TOKENS] and
 // arrivals: counters in the workspace, zero between launches
 void launch_route_plan(const Shape &s, const void *x, const void *wr, const float *bias, const PlanArgs &a,
                        double *logits, uint32_t *token_arrivals, uint32_t *arrivals, hipStream_t st);
-// plan of the S shared experts alone over s.T tokens
-void launch_shared_plan(const Shape &s, Plan *plan, const void *shared, size_t shared_stride, hipStream_t st);
 void launch_union(const int32_t *ids, int n_ids, int E, const int32_t *slot,
                   uint64_t *mask, int32_t *list, int32_t *n_list,
                   int32_t *missing, int32_t *n_missing, hipStream_t st);
 
 // Work item of the draft call over a long run of tokens: up to kPrefillChunk assignments of one
-// expert, sorted[first .. first + cnt).  Item i owns slots [64 i, 64 i + cnt).
+// expert, sorted[first .. first + cnt), or (expert >= E: shared expert) tokens [first, first + cnt).
+// Item i owns slots [64 i, 64 i + cnt); src: the item whose operand tiles of x it reads.
 constexpr int kPrefillChunk = 64;
-struct PrefillItem { int32_t expert, first, cnt, pad; };
+struct PrefillItem { int32_t expert, first, cnt, src; };
 
 // draft_int4.hip (a call of 2 to 8 tokens) and draft_slice.hip (a call of one token)
 struct DraftFusedArgs {
@@ -145,8 +143,9 @@ struct PrefillCall {
     const float *w_all;                // routing weight of every assignment [T k]
     void *xt, *x_sums, *h_hi, *h_lo, *h_sums, *zeros; float *obuf;
     float *y;                          // [T,H] fp32, written (not accumulated)
+    const void *shared; size_t shared_stride;                          // bf16 blobs of the shared experts
 };
-void launch_prefill_plan(const int32_t *ids, int n, int E, int32_t *sorted, int32_t *slot_of,
+void launch_prefill_plan(const Shape &s, const int32_t *ids, int32_t *sorted, int32_t *slot_of,
                          PrefillItem *items, int32_t *n_items, hipStream_t st);
 void launch_prefill_stage(const Shape &s, const PrefillCall &p, int max_items, hipStream_t st);
 void launch_prefill_gateup(const Shape &s, const PrefillCall &p, int max_items, hipStream_t st);
@@ -158,15 +157,12 @@ void launch_prefill_combine(const Shape &s, const PrefillCall &p, hipStream_t st
 void launch_bf16_gateup(const Shape &s, const Plan *plan, int first_active, int n_active_max,
                         const void *x, void *hb, void *hb_lo, hipStream_t st);
 void launch_bf16_down(const Shape &s, const Plan *plan, int first_active, int n_active_max,
-                      const void *hb, const void *hb_lo, float *obuf, hipStream_t st);
+                      const void *hb, float *obuf, hipStream_t st);
 // the same product, each row's outputs added to y[row_tok[row]] (fp32, [T,H]) with atomics; the
 // intermediate is the bf16 hi + lo pair
 void launch_bf16_down_add(const Shape &s, const Plan *plan, int first_active, int n_active_max,
                           const void *hb, const void *hb_lo, float *y, hipStream_t st);
-// y[t] = (accumulate ? y[t] : 0) + sum over the token's live routed rows of
-// sum_{split < nsplit} routed[split][row] + sum over its live shared rows of obuf[row];
-// routed is [nsplit][T*k][H] fp32, obuf is [rows][H] fp32 indexed by row number.
-void launch_combine(const Shape &s, const Plan *plan, const float *routed, int nsplit,
-                    const float *obuf, int accumulate, int out_bf16, void *y, hipStream_t st);
+// y[t] (bf16) = (accumulate ? y[t] : 0) + the token's live rows of obuf ([rows][H] fp32)
+void launch_combine(const Shape &s, const Plan *plan, const float *obuf, int accumulate, void *y, hipStream_t st);
 
 }  // namespace moespeq

@@ -189,29 +189,6 @@ void perm_kernel(const int32_t *__restrict__ ids, int n, int E, int32_t *count, 
     histogram_perm(s_ids, n, E, count, off, perm, s_count);
 }
 
-// Plan that runs only the S shared experts over T tokens (rows n .. n + S T, n = T k routed rows
-// that stay dead): what the draft kernel leaves for the shared-expert kernels, for callers that
-// route elsewhere.
-__global__ __launch_bounds__(256)
-void shared_plan_kernel(Plan *__restrict__ p, int T, int k, int S, int E, const char *shared, size_t shared_stride)
-{
-    const int n = T * k, tid = threadIdx.x;
-    for (int i = tid; i < n; i += 256) { p->perm[i] = i; p->row_live[i] = 0; }
-    for (int i = tid; i < S * T; i += 256) {
-        p->row_tok[n + i] = i % T;
-        p->row_w[n + i] = 1.f;
-        p->row_live[n + i] = 1;
-    }
-    if (tid < S) {
-        p->act_expert[tid] = E + tid;
-        p->act_off[tid] = n + tid * T;
-        p->act_cnt[tid] = T;
-        p->act_w0[tid] = (uint64_t)(shared + (size_t)tid * shared_stride);
-        p->act_w1[tid] = 0;
-    }
-    if (tid == 0) { p->n_active = S; p->n_routed_active = 0; p->n_rows = n + S * T; p->n_missing = 0; }
-}
-
 // Builds the execution plan: histogram / permutation, the list of experts to run (shared
 // experts at active indices [0, S), then present routed experts ascending), their weight
 // pointers and row ranges, the per-row token / weight / live flags, and the missing list.
@@ -318,13 +295,6 @@ struct PlanKernelArgs {
     const int32_t *slot_of_expert; const char *shared; size_t shared_stride; int flags;
     int32_t *ids_out; float *conf_out; int32_t *missing; int32_t *n_missing;
 };
-
-__global__ __launch_bounds__(256)
-void plan_kernel(const PlanKernelArgs a)
-{
-    plan_body<false>(a.plan, a.T, a.E, a.k, a.S, a.mode, a.w0, a.stride0, a.w1, a.stride1, a.slot_of_expert,
-                     a.shared, a.shared_stride, a.flags, a.ids_out, a.conf_out, a.missing, a.n_missing);
-}
 
 // Router and plan in one launch (the verify call).  Workgroup (b, t) reduces the router rows of
 // experts 16 b .. 16 b + 15 for token t, one row per wave, and stores the fp64 logits at agent
@@ -502,22 +472,12 @@ static PlanKernelArgs plan_kernel_args(const Shape &s, const PlanArgs &a)
     return k;
 }
 
-void launch_plan(const Shape &s, const PlanArgs &a, hipStream_t st)
-{
-    launch(plan_kernel, dim3(1), dim3(256), 0, st, plan_kernel_args(s, a));
-}
-
 void launch_route_plan(const Shape &s, const void *x, const void *wr, const float *bias, const PlanArgs &a,
                        double *logits, uint32_t *token_arrivals, uint32_t *arrivals, hipStream_t st)
 {
     const dim3 grid((s.E + kRouteBlock - 1) / kRouteBlock, s.T);
     launch(route_plan_kernel, grid, dim3(kRouteThreads), 0, st, (const uint16_t *)x, (const uint16_t *)wr,
            bias, s.H, s.renorm, plan_kernel_args(s, a), logits, token_arrivals, arrivals);
-}
-
-void launch_shared_plan(const Shape &s, Plan *plan, const void *shared, size_t shared_stride, hipStream_t st)
-{
-    launch(shared_plan_kernel, dim3(1), dim3(256), 0, st, plan, s.T, s.k, s.S, s.E, (const char *)shared, shared_stride);
 }
 
 void launch_union(const int32_t *ids, int n_ids, int E, const int32_t *slot,

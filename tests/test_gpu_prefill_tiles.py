@@ -19,7 +19,7 @@ from paper_2511_14102_amd.harness import DeviceLayer   # noqa: E402
 SHAPES = [
     #            idx  name    H    E   I   k   g  S  renorm
     LayerConfig(61, "p64", 64, 3, 64, 1, 32, 0, 1),        # fewer k-steps than one stage, one row tile
-    LayerConfig(62, "p192", 192, 5, 320, 2, 64, 0, 1),     # 3 and 5 groups, 10 slices
+    LayerConfig(62, "p192", 192, 5, 320, 2, 64, 2, 1),     # 3 and 5 groups, 10 slices, two shared experts
     LayerConfig(63, "p320", 320, 2, 192, 2, 32, 0, 0),     # 10 groups, every token in both experts
     LayerConfig(64, "p640", 640, 4, 384, 2, 128, 0, 1),    # 5 and 3 groups, 12 slices
     LayerConfig(65, "p256", 256, 40, 128, 3, 128, 0, 1),   # many experts with a token or two
