@@ -370,17 +370,19 @@ static int enqueue_draft(moe_ctx *ctx, const moe_layer_desc *desc, const void *x
     a.plan = plan; a.shared = shared; a.shared_stride = moe_bf16_expert_bytes(desc);
     // the workgroups that reduce the router rows (the first min(E, grid) of the launch) must be
     // running while the others wait for them
-    if (!draft_producers_resident(s, a, ctx->n_cu)) return MOE_ERR_INVALID_ARG;
+    const int slots = draft_resident_slots(s, a, ctx->n_cu);
+    if (slots == 0) return MOE_ERR_INVALID_ARG;
+    const bool own_launches = s.S > 0 && T > 1;     // a one-token call runs its shared experts in its one launch
     if (!timed) {
-        launch_draft_fused(s, a, ctx->n_cu, st);
-        if (s.S > 0) {
+        launch_draft_fused(s, a, slots, st);
+        if (own_launches) {
             launch_bf16_gateup(s, plan, 0, s.S, x, ws + L.hb, ws + L.hb_lo, st);
             launch_bf16_down_add(s, plan, 0, s.S, ws + L.hb, ws + L.hb_lo, y, st);
         }
         return hip_status(ctx, hipGetLastError());
     }
-    { ProfScope p(ctx, MOE_KERNEL_DRAFT_FUSED, st); launch_draft_fused(s, a, ctx->n_cu, st); }
-    if (s.S > 0) {   // shared experts stay 16-bit in the draft model (section 3.4.2)
+    { ProfScope p(ctx, MOE_KERNEL_DRAFT_FUSED, st); launch_draft_fused(s, a, slots, st); }
+    if (own_launches) {   // shared experts stay 16-bit in the draft model (section 3.4.2)
         { ProfScope p(ctx, MOE_KERNEL_BF16_GATEUP, st);
           launch_bf16_gateup(s, plan, 0, s.S, x, ws + L.hb, ws + L.hb_lo, st); }
         // the down kernel adds the shared experts' outputs to y itself (fp32 atomics on top of

@@ -29,10 +29,6 @@ constexpr int kThreads = kWaves * 64;
 // that the polls of hundreds of workgroups do not all land on one address.
 constexpr int kReplicas = kDraftSlotReplicas;
 constexpr int kTicketGroups = 16;
-// Up to this many experts the wave that polled a token's logits also selects its top-k by itself;
-// beyond, all waves share the ranking (two more barriers, which cost more than they save on few
-// experts: measured 1 us on 16 experts).
-constexpr int kLoneWaveTopk = 32;
 constexpr uint32_t kMagic = 0x43004300u;      // bf16 pair (128, 128)
 
 __device__ inline float bf16_lo(uint32_t u) { return __uint_as_float(u << 16); }
@@ -67,6 +63,16 @@ __device__ inline bf16x8 unpack8(uint32_t w, UnpackConsts k) {
     return __builtin_bit_cast(bf16x8, r);
 }
 
+// Computes a value here: a window slot may be refilled behind this point (into the same registers) though the
+// value made from its old contents is used further down.  Left alone, the compiler makes the value where it
+// is used, copies the slot's contents for that, and waits for all loads in flight at every such copy.
+__device__ inline void compute_here(bf16x8 &v) {
+    u32x4 u = __builtin_bit_cast(u32x4, v);
+    asm volatile("" : "+v"(u));
+    v = __builtin_bit_cast(bf16x8, u);
+}
+__device__ inline void compute_here(float &v) { asm volatile("" : "+v"(v)); }
+
 __device__ inline f32x4 mfma(u32x4 a, bf16x8 b, f32x4 c) {
     return __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8, a), b, c, 0, 0, 0);
 }
@@ -76,6 +82,19 @@ __device__ inline u32x4 load16_agent(const void *p) {
     u32x4 v;
     asm volatile("global_load_dwordx4 %0, %1, off sc1\n\ts_waitcnt vmcnt(0)" : "=v"(v) : "v"(p) : "memory");
     return v;
+}
+
+// Two and four of them behind one wait (early-clobber outputs: an output must not take the place of
+// an address that a later load of the block still needs)
+__device__ inline void load16_agent(const void *const (&p)[1], u32x4 (&v)[1]) { v[0] = load16_agent(p[0]); }
+__device__ inline void load16_agent(const void *const (&p)[2], u32x4 (&v)[2]) {
+    asm volatile("global_load_dwordx4 %0, %2, off sc1\n\tglobal_load_dwordx4 %1, %3, off sc1\n\ts_waitcnt vmcnt(0)"
+                 : "=&v"(v[0]), "=&v"(v[1]) : "v"(p[0]), "v"(p[1]) : "memory");
+}
+__device__ inline void load16_agent(const void *const (&p)[4], u32x4 (&v)[4]) {
+    asm volatile("global_load_dwordx4 %0, %4, off sc1\n\tglobal_load_dwordx4 %1, %5, off sc1\n\t"
+                 "global_load_dwordx4 %2, %6, off sc1\n\tglobal_load_dwordx4 %3, %7, off sc1\n\ts_waitcnt vmcnt(0)"
+                 : "=&v"(v[0]), "=&v"(v[1]), "=&v"(v[2]), "=&v"(v[3]) : "v"(p[0]), "v"(p[1]), "v"(p[2]), "v"(p[3]) : "memory");
 }
 
 __device__ inline void store16_agent(void *p, u32x4 v) {
@@ -91,6 +110,21 @@ __device__ inline void store16_agent(void *p, u32x4 v) {
 __device__ inline void load16_to_lds(const void *g, uint32_t lds_base) {
     asm volatile("s_mov_b32 m0, %0\n\tglobal_load_lds_dwordx4 %1, off" : : "s"(lds_base), "v"(g) : "memory");
 }
+
+// A run of a weight stream as a buffer: `bytes` bytes from `base` (both wave-uniform).  A load past the run's
+// end returns zeros and moves nothing, so a window's loads need no clamps: positions are 32-bit offsets, four
+// tiles of 1 KiB under one address register.  (As global loads with clamped 64-bit addresses a tile cost a
+// dozen scalar instructions and a branch, and the first window of a workgroup took 5 us to issue.)
+typedef __amdgpu_buffer_rsrc_t run_t;
+__device__ inline run_t make_run(const char *base, uint32_t bytes) {
+    return __builtin_amdgcn_make_buffer_rsrc((void *)base, 0, (int)bytes, 0x00027000);
+}
+constexpr int kNonTemporal = 2;
+__device__ inline u32x4 run_load16(run_t r, uint32_t off) {
+    return __builtin_bit_cast(u32x4, __builtin_amdgcn_raw_buffer_load_b128(r, off, 0, kNonTemporal));
+}
+__device__ inline uint32_t run_load4(run_t r, uint32_t off) { return __builtin_amdgcn_raw_buffer_load_b32(r, off, 0, kNonTemporal); }
+__device__ inline uint32_t run_load2(run_t r, uint32_t off) { return (uint16_t)__builtin_amdgcn_raw_buffer_load_b16(r, off, 0, kNonTemporal); }
 
 struct FusedArgs {
     const uint16_t *wr;         // [E,H] bf16
@@ -111,6 +145,213 @@ struct FusedArgs {
     size_t shared_stride;
     int T, H, E, I, k, g, S, renorm;
 };
+
+// ---- the router inside a draft call (both kernels)
+
+// Workgroup b (numbered among the call's `nprod` router workgroups) reduces router rows b, b + nprod, ...
+// for all T tokens and publishes each {logit, tag}.  The NW waves are shared out over the tokens, NW / T2
+// of them (T2: T rounded up to a power of two) splitting H, so that a row costs one round of loads and
+// one barrier however many tokens there are (one token after another took 6 us for 8 tokens).  fp64
+// accumulation of exact fp32 products.  Before it publishes, the workgroup clears its share of y.
+template <int NW>
+__device__ inline void publish_router_rows(const uint16_t *__restrict__ xin, const FusedArgs &a, int b, int nprod,
+                                           double (&s_part)[NW])
+{
+    constexpr int kTh = NW * 64;
+    const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int T = a.T, H = a.H, E = a.E, chunks = H / 8;
+    for (int i = b * kTh + tid; i < T * H; i += nprod * kTh)
+        __hip_atomic_store(&a.y[i], 0.f, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    const int lt = T <= 1 ? 0 : (T <= 2 ? 1 : (T <= 4 ? 2 : 3));
+    const int t = wave & ((1 << lt) - 1), part = wave >> lt, step = (NW >> lt) * 64;
+    const uint16_t *xt = xin + (size_t)(t < T ? t : T - 1) * H;
+    for (int e = b; e < E; e += nprod) {
+        const uint16_t *row = a.wr + (size_t)e * H;
+        const float bias = a.bias ? a.bias[e] : 0.f;          // (here and not behind the barrier: a round trip to memory)
+        double acc[4] = {0.0, 0.0, 0.0, 0.0};
+        auto chunks_at = [&](int c0, auto batch) {           // (a position past the end counts as zeros)
+            constexpr int kB = decltype(batch)::value;
+            u32x4 xv[kB], wv[kB];
+#pragma unroll
+            for (int j = 0; j < kB; ++j) {
+                const int c = c0 + j * step, cc = c < chunks ? c : chunks - 1;
+                xv[j] = *reinterpret_cast<const u32x4 *>(xt + cc * 8);
+                wv[j] = *reinterpret_cast<const u32x4 *>(row + cc * 8);
+            }
+#pragma unroll
+            for (int j = 0; j < kB; ++j) {
+                const bool in = c0 + j * step < chunks;
+#pragma unroll
+                for (int i = 0; i < 4; ++i) {
+                    const uint32_t xs = in ? xv[j][i] : 0u, ws = in ? wv[j][i] : 0u;
+                    acc[i] += (double)(bf16_lo(xs) * bf16_lo(ws));       // bf16 x bf16 is exact in fp32
+                    acc[i] += (double)(bf16_hi(xs) * bf16_hi(ws));
+                }
+            }
+        };
+        if (chunks <= step) chunks_at(part * 64 + lane, std::integral_constant<int, 1>{});
+        else for (int c0 = part * 64 + lane; c0 - lane < chunks; c0 += 4 * step) chunks_at(c0, std::integral_constant<int, 4>{});
+        const double sum = wave::sum((acc[0] + acc[1]) + (acc[2] + acc[3]));
+        if (lane == 0) s_part[wave] = sum;
+        // every thread's clearing stores have been performed before the workgroup publishes (a
+        // workgroup-scope release fence does not imply this wait; it is nearly free here, the loads
+        // of the row were issued after the stores and have returned)
+        asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+        __syncthreads();
+        if (tid < T * kReplicas) {                           // thread (token, replica)
+            const int tt = tid / kReplicas, rep = tid % kReplicas;
+            double l = 0.0;
+#pragma unroll
+            for (int w = 0; w < NW; ++w) l += (w & ((1 << lt) - 1)) == tt ? s_part[w] : 0.0;
+            l += (double)bias;
+            // {logit, tag} leaves as ONE aligned 16-byte agent-scope store and is read with one
+            // 16-byte load: a reader sees the tag only together with the logit
+            const unsigned long long lb = (unsigned long long)__double_as_longlong(l);
+            const u32x4 rec = {(uint32_t)lb, (uint32_t)(lb >> 32), 1u, 0u};
+            store16_agent(a.slots + (size_t)rep * a.replica_stride + 2 * ((size_t)tt * E + e), rec);
+        }
+        if (e + nprod < E) __syncthreads();                  // s_part is written again
+    }
+}
+
+// One wave polls the slots of token t until all are tagged and selects its top-k: ids in rank order
+// (larger logit first, lower index first among equals) to ids[0 .. k), every logit and its rank
+// (MOE_MAX_EXPERTS: not selected) to LDS for the softmax, which follows later, and the selected experts
+// to the words of `mask` (unless null).  `logit` null: only the wait.  False: the wait ran out of polls.
+//
+// Selection: k rounds of a maximum over 32-bit keys that order like the logits rounded to fp32 (six
+// lane moves each); where several logits share the largest key, their fp64 values decide.  (Counting the
+// rank of every fp64 logit, by one wave for up to 32 experts and by all waves beyond, took 0.9 us for 16
+// experts, 2.8 us for 128, and 12.8 us for 128 experts and 8 tokens.)
+template <int NR>                                // NR: 64 NR >= E
+__device__ inline bool poll_and_select(const FusedArgs &a, int t, double *logit, int32_t *rank, int32_t *ids,
+                                       unsigned long long *mask)
+{
+    const int lane = threadIdx.x & 63, E = a.E, k = a.k;
+    const void *from[NR];
+#pragma unroll
+    for (int i = 0; i < NR; ++i) {
+        const int e = lane + 64 * i < E ? lane + 64 * i : E - 1;
+        from[i] = a.slots + (size_t)(blockIdx.x % kReplicas) * a.replica_stride + 2 * ((size_t)t * E + e);
+    }
+    u32x4 v[NR];
+    bool all = false;
+    for (uint32_t spins = 1; spins < a.spin_limit; ++spins) {
+        load16_agent(from, v);
+        bool mine = true;
+#pragma unroll
+        for (int i = 0; i < NR; ++i) mine = mine && v[i].z == 1u;
+        all = __all(mine);
+        if (all) break;
+        __builtin_amdgcn_s_sleep(2);
+    }
+    if (!all) return false;
+    if (!logit) return true;
+    constexpr int kNone = -2147483647 - 1;       // below the key of every number
+    double l[NR];
+    int key[NR], rk[NR];
+#pragma unroll
+    for (int i = 0; i < NR; ++i) {
+        const int e = lane + 64 * i;
+        l[i] = __longlong_as_double((long long)(((unsigned long long)v[i].y << 32) | v[i].x));
+        if (e < E) logit[e] = l[i];
+        if (!(l[i] == l[i])) l[i] = -INFINITY;               // a NaN is selected last
+        const int b = __float_as_int((float)l[i] + 0.f);     // (-0 and 0 are equal)
+        key[i] = e < E ? b ^ ((b >> 31) & 0x7fffffff) : kNone;
+        rk[i] = MOE_MAX_EXPERTS;
+    }
+    int id = 0;
+    for (int j = 0; j < k; ++j) {
+        int m = key[0];
+#pragma unroll
+        for (int i = 1; i < NR; ++i) m = m > key[i] ? m : key[i];
+        m = wave::max(m);
+        unsigned long long hit[NR];
+        int hits = 0;
+#pragma unroll
+        for (int i = 0; i < NR; ++i) { hit[i] = __ballot(key[i] == m); hits += __popcll(hit[i]); }
+        if (hits > 1) {
+            double d = -INFINITY;
+#pragma unroll
+            for (int i = 0; i < NR; ++i) d = key[i] == m ? fmax(d, l[i]) : d;
+            d = wave::max(d);
+#pragma unroll
+            for (int i = 0; i < NR; ++i) hit[i] = __ballot(key[i] == m && l[i] == d);
+        }
+        int e = 0;
+#pragma unroll
+        for (int i = NR - 1; i >= 0; --i) e = hit[i] ? 64 * i + __ffsll((long long)hit[i]) - 1 : e;
+#pragma unroll
+        for (int i = 0; i < NR; ++i) {
+            const bool won = lane + 64 * i == e;
+            key[i] = won ? kNone : key[i];
+            rk[i] = won ? j : rk[i];
+        }
+        id = lane == j ? e : id;
+    }
+    if (lane < k) ids[lane] = id;
+#pragma unroll
+    for (int i = 0; i < NR; ++i) {
+        if (lane + 64 * i < E) rank[lane + 64 * i] = rk[i];
+        if (mask) {
+            const unsigned long long sel = __ballot(rk[i] < k);
+            if (lane == 0) atomicOr(&mask[i], sel);
+        }
+    }
+    return true;
+}
+__device__ inline bool poll_and_select(const FusedArgs &a, int t, double *logit, int32_t *rank, int32_t *ids,
+                                       unsigned long long *mask)
+{
+    if (a.E <= 64) return poll_and_select<1>(a, t, logit, rank, ids, mask);
+    if (a.E <= 128) return poll_and_select<2>(a, t, logit, rank, ids, mask);
+    return poll_and_select<4>(a, t, logit, rank, ids, mask);
+}
+
+// Tickets.  A wave draws one when its workgroup has finished polling; the holder of the last one puts the
+// slots back to idle.  Two levels (kTicketGroups counters, then one) so that the returning atomics do not
+// queue up on one address.  The counter's address goes through an opaque vector register: on a uniform
+// address the compiler aggregates over the wave and reads the result back at once, which waits for
+// everything the wave has in flight; like this the result is waited for where it is used.
+__device__ inline uint32_t draw_ticket(uint32_t *counter) {
+    uint64_t p = (uint64_t)counter;
+    asm volatile("" : "+v"(p));
+    return __hip_atomic_fetch_add((__attribute__((address_space(1))) uint32_t *)p, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+}
+__device__ inline uint32_t ticket_members(uint32_t b, uint32_t grid) { return (grid - b % kTicketGroups + kTicketGroups - 1) / kTicketGroups; }
+__device__ inline uint32_t ticket_groups(uint32_t grid) { return grid < (uint32_t)kTicketGroups ? grid : (uint32_t)kTicketGroups; }
+// the calling wave puts slots and tickets back to idle
+__device__ inline void reset_exchange(const FusedArgs &a) {
+    const int lane = threadIdx.x & 63, n = a.T * a.E;
+    for (int rep = 0; rep < kReplicas; ++rep)
+        for (int i = lane; i < n; i += 64)
+            __hip_atomic_store(a.slots + (size_t)rep * a.replica_stride + 2 * (size_t)i + 1, 0ull, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    if (lane <= kTicketGroups) __hip_atomic_store(a.tickets + lane, 0u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+}
+
+// The softmax of a token whose logits and ranks the calling wave left in LDS: confidences and routing
+// weights in rank order.  The selection compared the fp64 logits; the softmax values only have to be good
+// to fp32, so they are computed in fp32 from the fp64 differences.
+__device__ inline void finish_softmax(const FusedArgs &a, const double *logit, const int32_t *rank, float *conf, float *w)
+{
+    const int lane = threadIdx.x & 63, E = a.E, k = a.k;
+    double mx = -INFINITY;
+    for (int e = lane; e < E; e += 64) mx = fmax(mx, logit[e]);
+    mx = wave::max(mx);
+    float den = 0.f, sel = 0.f;
+    for (int e = lane; e < E; e += 64) den += expf((float)(logit[e] - mx));
+    den = wave::sum(den);
+    for (int e = lane; e < E; e += 64) sel += rank[e] < k ? expf((float)(logit[e] - mx)) / den : 0.f;
+    sel = wave::sum(sel);
+    for (int e = lane; e < E; e += 64) {
+        const int r = rank[e];
+        if (r < k) {
+            const float p = expf((float)(logit[e] - mx)) / den;
+            conf[r] = p;
+            w[r] = a.renorm ? p / sel : p;
+        }
+    }
+}
 
 // Scale and zero of the four row blocks d of one (group, lane row): the asymmetric format keeps
 // a 4-byte {s, z} entry per d, the symmetric one (z = 8) only the four fp16 scales.

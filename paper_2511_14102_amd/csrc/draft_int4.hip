@@ -43,15 +43,6 @@
 
 namespace moespeq {
 
-// Timing-only build (-DMOE_STAMPS, never the shipped library): every wave leaves wall-clock stamps
-// (100 MHz) of its phases in a device array that moe_debug_stamps copies out.
-#ifdef MOE_STAMPS
-__device__ unsigned long long moe_stamps[1024 * 8 * 32];
-#define STAMP(id) do { if (lane == 0) moe_stamps[((size_t)blockIdx.x * kWaves + wave) * 32 + (id)] = wall_clock64(); } while (0)
-#else
-#define STAMP(id) do {} while (0)
-#endif
-
 namespace {
 
 // MT: token capacity of the launch (2, 4 or 8; the code also serves 1); UPG: 32-code units per
@@ -72,13 +63,13 @@ void draft_stream_kernel(const uint16_t *__restrict__ xin, const FusedArgs a)
     __shared__ float s_w[MOE_MAX_ASSIGN];
     __shared__ float s_conf[MOE_MAX_ASSIGN];
     __shared__ unsigned long long s_mask[MOE_MAX_EXPERTS / 64];
-    // per-item state is kept twice (item parity): an item's successor is set up while waves may
-    // still be reading the item's own
+    // rows and sums of an item are kept twice (item parity): an item's successor is set up while waves
+    // may still be reading the item's own
     __shared__ int32_t s_row_a[2][MT];          // assignment index of each row (token slot) of the item
     __shared__ int32_t s_cnt[2];
     __shared__ float s_hsum[2][MT];
     __shared__ int32_t s_flag;
-    __shared__ int32_t s_first[2];               // one token, few experts: experts of the first two items
+    __shared__ int32_t s_list[MOE_MAX_EXPERTS];  // the call's distinct experts, ascending
     // partial gate/up sums [wave][row block][token in lane group][lane]
     typedef float red_t[4][NI][NC * 16];
     __shared__ red_t s_red[kWaves];
@@ -99,49 +90,9 @@ void draft_stream_kernel(const uint16_t *__restrict__ xin, const FusedArgs a)
     double *s_logit = reinterpret_cast<double *>(s_dyn + logit_off);
     int32_t *s_rank = reinterpret_cast<int32_t *>(s_dyn + logit_off + (size_t)MT * E * 8);
 
-    STAMP(0);
-    // ---- 1. router rows owned by this workgroup (fp64 accumulation of exact fp32 products)
-    if ((int)blockIdx.x < E) {
-        const int nprod = E < (int)gridDim.x ? E : (int)gridDim.x;
-        for (int i = blockIdx.x * kThreads + tid; i < T * H; i += nprod * kThreads)
-            __hip_atomic_store(&a.y[i], 0.f, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-    }
-    for (int e = blockIdx.x; e < E; e += gridDim.x) {
-        const uint16_t *row = a.wr + (size_t)e * H;
-        for (int t = 0; t < T; ++t) {
-            const uint16_t *xt = xin + (size_t)t * H;
-            double acc = 0.0;
-            for (int c = tid; c < H / 8; c += kThreads) {
-                const u32x4 xv = *reinterpret_cast<const u32x4 *>(xt + c * 8);
-                const u32x4 wv = *reinterpret_cast<const u32x4 *>(row + c * 8);
-                const uint32_t xs[4] = {xv.x, xv.y, xv.z, xv.w}, ws[4] = {wv.x, wv.y, wv.z, wv.w};
-#pragma unroll
-                for (int i = 0; i < 4; ++i) {
-                    acc += (double)(bf16_lo(xs[i]) * bf16_lo(ws[i]));     // bf16 x bf16 is exact in fp32
-                    acc += (double)(bf16_hi(xs[i]) * bf16_hi(ws[i]));
-                }
-            }
-            acc = wave::sum(acc);
-            if (lane == 0) s_part[wave] = acc;
-            // every thread's clearing stores have been performed before the workgroup publishes (a
-            // workgroup-scope release fence does not imply this wait; it is free here, the loads
-            // of the row were issued after the stores and have returned)
-            asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
-            __syncthreads();
-            if (tid < kReplicas) {                                       // thread r writes replica r
-                double l = 0.0;
-                for (int w = 0; w < kWaves; ++w) l += s_part[w];
-                l += a.bias ? (double)a.bias[e] : 0.0;
-                // {logit, tag} leaves as ONE aligned 16-byte agent-scope store and is read with one
-                // 16-byte load: a reader sees the tag only together with the logit
-                const unsigned long long lb = (unsigned long long)__double_as_longlong(l);
-                const u32x4 rec = {(uint32_t)lb, (uint32_t)(lb >> 32), 1u, 0u};
-                store16_agent(a.slots + (size_t)tid * a.replica_stride + 2 * ((size_t)t * E + e), rec);
-            }
-            __syncthreads();
-        }
-    }
-    STAMP(1);
+    // ---- 1. router rows owned by this workgroup
+    if ((int)blockIdx.x < E)
+        publish_router_rows<kWaves>(xin, a, blockIdx.x, E < (int)gridDim.x ? E : (int)gridDim.x, s_part);
     if (tid == 0) s_flag = 1;
     if (tid < MOE_MAX_EXPERTS / 64) s_mask[tid] = 0ull;
     if (tid < 2 * MT) s_hsum[tid / MT][tid % MT] = 0.f;
@@ -164,22 +115,6 @@ void draft_stream_kernel(const uint16_t *__restrict__ xin, const FusedArgs a)
         if (part == 0) s_xsum[t * G + gi] = v;
     }
 
-    // the u-th distinct expert (u-th set bit of the mask words, which are scalars by then)
-    uint32_t mask_lo[MOE_MAX_EXPERTS / 64] = {}, mask_hi[MOE_MAX_EXPERTS / 64] = {};
-    auto nth_expert = [&](int u) {
-        int seen = 0, expert = 0;
-#pragma unroll
-        for (int wd = 0; wd < MOE_MAX_EXPERTS / 64; ++wd) {
-            unsigned long long mk = ((unsigned long long)mask_hi[wd] << 32) | mask_lo[wd];
-            const int pc = __popcll(mk);
-            if (u >= seen && u < seen + pc) {
-                for (int i = u - seen; i > 0; --i) mk &= mk - 1ull;
-                expert = wd * 64 + __ffsll((long long)mk) - 1;
-            }
-            seen += pc;
-        }
-        return expert;
-    };
     const int nslice = I / 32;
     const int U = H / 32;
     const int r = lane & 15, c = lane >> 4;                  // MFMA lane coordinates
@@ -259,42 +194,43 @@ void draft_stream_kernel(const uint16_t *__restrict__ xin, const FusedArgs a)
     };
 
     // Scale / zero entries do not travel through registers: a wave copies the entries of its own
-    // groups and row tiles of an item straight into LDS (16-byte loads that write LDS, 1 KiB per
+    // groups (row tiles) of an item straight into LDS (16-byte loads that write LDS, 1 KiB per
     // instruction, no destination registers and so nothing the compiler has to keep alive across
-    // the item loop) BEFORE it requests any tile of that item.  Vector memory operations complete
-    // in order, so once a tile of the item has arrived, so have the item's entries; an entry is
-    // read only behind the use of such a tile.  Two copies (item parity): an item's entries are
-    // requested while its predecessor's are in use.
+    // the item loop) BEFORE it requests any tile they belong to: the down entries as the item's gate/up
+    // part begins, the successor's gate/up entries as the item's down part begins, when the wave has
+    // used the ones in their place.  Vector memory operations complete in order, so once a tile has
+    // arrived, so have its entries; an entry is read only behind the use of such a tile.  (A wave without
+    // tiles in one of the parts requests the other part's tiles too early for this and waits.)
     const int ngl = (g1 - g0) / kEpl, ndl = (r1 - r0) / kEpl;          // 256-byte blocks of this wave
     const int gl_max = (G / kEpl + kWaves - 1) / kWaves, dl_max = (nrt / kEpl + kWaves - 1) / kWaves;
     const int eb_gu = (gl_max + 3) / 4 * 1024, eb_dn = (dl_max + 3) / 4 * 1024;
     const size_t ent_off = (logit_off + (size_t)MT * E * 12 + 15) & ~(size_t)15;
-    unsigned char *s_ent = s_dyn + ent_off + (size_t)wave * 2 * (eb_gu + eb_dn);   // [parity][gate/up | down]
+    unsigned char *s_ent = s_dyn + ent_off + (size_t)wave * (eb_gu + eb_dn);                  // [gate/up | down]
     const uint32_t s_ent_addr = __builtin_amdgcn_readfirstlane((uint32_t)(uintptr_t)s_ent);   // LDS byte address
-    auto request_entries = [&](const Item &it, int par) {
-        const uint32_t dst = s_ent_addr + par * (eb_gu + eb_dn);
-        const char *gsrc = it.szb + ((size_t)it.slice * (G / kEpl) + g0 / kEpl) * 256;
-        for (int op = 0; op * 4 < ngl; ++op) {
+    auto request_blocks = [&](const char *src, int blocks, uint32_t dst) {
+        for (int op = 0; op * 4 < blocks; ++op) {
             const int off = op * 1024 + (int)lane_off;
-            const int lim = ngl * 256 - 16;
-            load16_to_lds(gsrc + (off < lim ? off : lim), dst + op * 1024);
+            const int lim = blocks * 256 - 16;
+            load16_to_lds(src + (off < lim ? off : lim), dst + op * 1024);
         }
-        const char *dsrc = it.szb + ((size_t)nslice * (G / kEpl) + (size_t)((it.slice * 32) / g) * (nrt / kEpl) + r0 / kEpl) * 256;
-        for (int op = 0; op * 4 < ndl; ++op) {
-            const int off = op * 1024 + (int)lane_off;
-            const int lim = ndl * 256 - 16;
-            load16_to_lds(dsrc + (off < lim ? off : lim), dst + eb_gu + op * 1024);
-        }
+        if (ngl == 0 || ndl == 0) asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+    };
+    auto request_gu_entries = [&](const Item &it) {
+        request_blocks(it.szb + ((size_t)it.slice * (G / kEpl) + g0 / kEpl) * 256, ngl, s_ent_addr);
+    };
+    auto request_dn_entries = [&](const Item &it) {
+        request_blocks(it.szb + ((size_t)nslice * (G / kEpl) + (size_t)((it.slice * 32) / g) * (nrt / kEpl) + r0 / kEpl) * 256,
+                       ndl, s_ent_addr + eb_gu);
     };
     // entries of block `unit` (counted from the wave's first), part 0 gate/up, 1 down; `odd`: the
     // second group (row tile) of a pair in the symmetric format
-    auto own_entry = [&](int par, int part, int unit, int odd) -> uint32_t {      // this lane's row block c of row r
-        const unsigned char *p = s_ent + par * (eb_gu + eb_dn) + part * eb_gu + unit * 256 + r * 16;
+    auto own_entry = [&](int part, int unit, int odd) -> uint32_t {      // this lane's row block c of row r
+        const unsigned char *p = s_ent + part * eb_gu + unit * 256 + r * 16;
         if constexpr (SYM) return *reinterpret_cast<const uint16_t *>(p + odd * 8 + c * 2);
         else return *reinterpret_cast<const uint32_t *>(p + c * 4);
     };
-    auto row_entries = [&](int par, int part, int unit, int odd) {                 // all four row blocks of row r
-        const unsigned char *p = s_ent + par * (eb_gu + eb_dn) + part * eb_gu + unit * 256 + r * 16;
+    auto row_entries = [&](int part, int unit, int odd) {                 // all four row blocks of row r
+        const unsigned char *p = s_ent + part * eb_gu + unit * 256 + r * 16;
         GroupParams<SYM> gp;
         if constexpr (SYM) {
             const uint2 v = *reinterpret_cast<const uint2 *>(p + odd * 8);
@@ -331,11 +267,7 @@ void draft_stream_kernel(const uint16_t *__restrict__ xin, const FusedArgs a)
     };
 
     // Work split: the items (distinct experts ascending, I / 32 slices each) are dealt evenly, n / G
-    // each, the first n % G workgroups one more.  With one token the k experts are distinct, so the
-    // number of items and this workgroup's positions are known before the routing is, and are
-    // computed here, while the router result travels; only the expert numbers are filled in later
-    // (on the path from the routing to the first weight load every hundred instructions cost a
-    // microsecond: a lone wave issues one dependent instruction every 8 to 16 clocks).
+    // each, the first n % G workgroups one more.
     int it_begin = 0, it_end = 0;
     Item cur, nxt;
     auto split_items = [&](int n_items) {
@@ -346,207 +278,58 @@ void draft_stream_kernel(const uint16_t *__restrict__ xin, const FusedArgs a)
         if (it_begin + 1 < it_end) item_after(nxt, cur);
         else nxt = cur;
     };
-    if constexpr (MT == 1) split_items(k * nslice);
 
-    // ---- 2. wave t polls the slots of token t (bounded), then ranks its logits
-    double sm_logit = -INFINITY;                 // few experts: this lane's logit and rank, for the softmax later
-    int sm_rank = MOE_MAX_EXPERTS;
-    for (int t = wave; t < T; t += kWaves) {
-        double l[4];
-        {
-            uint32_t spins = 0;
-            bool all = false;
-            while (!all && ++spins < a.spin_limit) {
-                bool mine = true;
-#pragma unroll
-                for (int i = 0; i < 4; ++i) {
-                    const int e = lane + 64 * i;
-                    if (e < E) {
-                        const u32x4 v = load16_agent(a.slots + (size_t)(blockIdx.x % kReplicas) * a.replica_stride +
-                                                     2 * ((size_t)t * E + e));
-                        mine = mine && v.z == 1u;
-                        l[i] = __longlong_as_double((long long)(((unsigned long long)v.y << 32) | v.x));
-                    } else {
-                        l[i] = -INFINITY;
-                    }
-                }
-                all = __all(mine);
-                if (!all) __builtin_amdgcn_s_sleep(2);
-            }
-            if (!all) {                          // gave up: the call fails, and says so in the workspace
-                if (lane == 0) {
-                    s_flag = 0;
-                    __hip_atomic_store(a.status, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-                }
-                continue;
-            }
-        }
-        STAMP(2);
-#pragma unroll
-        for (int i = 0; i < 4; ++i) {
-            const int e = lane + 64 * i;
-            if (e < E) { s_logit[t * E + e] = l[i]; s_rank[t * E + e] = 0; }
-        }
-        if (E <= kLoneWaveTopk) {
-            // Rank of every logit in the strict order (larger first, lower index first among equals),
-            // so the ranks are a permutation and rank < k selects.  The wave's 64 lanes are P copies of
-            // the experts (E2 = E rounded up to a power of two, P = 64 / E2 >= 2): copy q of expert e
-            // counts the logits q per .. q per + per - 1 that come before logit e, read from LDS (the
-            // lanes of one copy read one address), and the P counts meet through lane exchanges.  Only
-            // the selection is on the path to the first weight load; the softmax follows later.
-            int E2 = 2;
-            while (E2 < E) E2 <<= 1;
-            const int P = 64 / E2, per = (E + P - 1) / P;
-            const int q = lane / E2, e = lane % E2;
-            const double mine = s_logit[t * E + (e < E ? e : E - 1)];
-            int part = 0;
-            for (int j = 0; j < per; ++j) {
-                const int e2 = q * per + j;
-                const double v = s_logit[t * E + (e2 < E ? e2 : E - 1)];
-                part += (int)(e2 < E) & ((int)(v > mine) | ((int)(v == mine) & (int)(e2 < e)));
-            }
-            for (int d = E2; d < 64; d <<= 1) part += __shfl_xor(part, d, 64);
-            if (lane < E) {
-                sm_logit = mine;
-                sm_rank = part;
-                if (part < k) {
-                    s_ids[t * k + part] = lane;
-                    atomicOr(&s_mask[lane >> 6], 1ull << (lane & 63));
-                }
-            }
-            if constexpr (MT == 1) {
-                // the experts of this workgroup's first two items, for every wave to pick up behind
-                // the barrier (each wave searching the mask by itself keeps the one scalar unit of
-                // the compute unit busy for a microsecond)
-                unsigned long long sel = __ballot(lane < E && part < k);
-                unsigned long long m0 = sel, m1 = sel;
-                for (int i = cur.u; i > 0; --i) m0 &= m0 - 1ull;
-                for (int i = nxt.u; i > 0; --i) m1 &= m1 - 1ull;
-                if (lane == 0) { s_first[0] = __ffsll((long long)m0) - 1; s_first[1] = __ffsll((long long)m1) - 1; }
-            }
-        }
-    }
-    // the softmax of wave t's token (few experts), off the path to the first weight load: the
-    // selection compared the fp64 logits; the softmax values only have to be good to fp32, so they
-    // are computed in fp32 from the fp64 differences
-    auto finish_softmax = [&]() {
-        if (E > kLoneWaveTopk || wave >= T || s_flag == 0) return;
-        const int t = wave;                      // T <= kWaves: one token per wave
-        const double mx = wave::max(sm_logit);
-        const float pe = lane < E ? expf((float)(sm_logit - mx)) : 0.f;
-        const float conf = pe / wave::sum(pe);
-        const bool sel = sm_rank < k;
-        const float sel_sum = wave::sum(sel ? conf : 0.f);
-        if (sel) {
-            s_conf[t * k + sm_rank] = conf;
-            s_w[t * k + sm_rank] = a.renorm ? conf / sel_sum : conf;
-        }
-    };
-    if (E > kLoneWaveTopk) {
-        // Ranks in the order (larger first, lower index first among equals), counted by all eight
-        // waves, each over its share of the experts; the order is strict, so rank < k selects.  (k
-        // rounds of arg-max in the one wave of a token took 5.4 us for 128 experts and k = 8.)
-        __syncthreads();
-        if (s_flag != 0) {
-            for (int t = 0; t < T; ++t) {
-                if (E <= 64) wave::count_ranks<1, 4>(s_logit + t * E, s_rank + t * E, E, lane, wave, kWaves);
-                else if (E <= 128) wave::count_ranks<2, 4>(s_logit + t * E, s_rank + t * E, E, lane, wave, kWaves);
-                else wave::count_ranks<4, 2>(s_logit + t * E, s_rank + t * E, E, lane, wave, kWaves);
-            }
-        }
-        __syncthreads();
-        for (int t = wave; t < T && s_flag != 0; t += kWaves) {
-            double mine[4];
-            int rank[4];
-            double mx = -INFINITY;
-#pragma unroll
-            for (int i = 0; i < 4; ++i) {
-                const int e = lane + 64 * i;
-                const bool have = 64 * i < E && e < E;
-                mine[i] = have ? s_logit[t * E + e] : -INFINITY;
-                rank[i] = have ? s_rank[t * E + e] : MOE_MAX_EXPERTS;
-                mx = fmax(mx, mine[i]);
-            }
-            mx = wave::max(mx);
-            float pe[4], den = 0.f, sel = 0.f;
-#pragma unroll
-            for (int i = 0; i < 4; ++i) {
-                pe[i] = rank[i] < MOE_MAX_EXPERTS ? expf((float)(mine[i] - mx)) : 0.f;
-                den += pe[i];
-            }
-            den = wave::sum(den);
-#pragma unroll
-            for (int i = 0; i < 4; ++i) {
-                pe[i] = pe[i] / den;
-                sel += rank[i] < k ? pe[i] : 0.f;
-            }
-            sel = wave::sum(sel);
-#pragma unroll
-            for (int i = 0; i < 4; ++i) {
-                if (rank[i] < k) {
-                    const int e = lane + 64 * i;
-                    s_ids[t * k + rank[i]] = e;
-                    s_conf[t * k + rank[i]] = pe[i];
-                    s_w[t * k + rank[i]] = a.renorm ? pe[i] / sel : pe[i];
-                    atomicOr(&s_mask[e >> 6], 1ull << (e & 63));
-                }
-            }
+    // ---- 2. wave t polls the slots of token t (bounded) and selects its top-k
+    if (wave < T) {                              // T <= kWaves
+        const bool got = poll_and_select(a, wave, s_logit + wave * E, s_rank + wave * E, s_ids + wave * k, s_mask);
+        if (!got && lane == 0) {                 // gave up: the call fails, and says so in the workspace
+            s_flag = 0;
+            __hip_atomic_store(a.status, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
         }
     }
     __syncthreads();
-    STAMP(3);
     const bool ok = s_flag != 0;
-    // This workgroup will not look at the slots again: it will draw a ticket.  The tickets are
-    // two-level (kTicketGroups first-level counters, then one) so that the returning atomics do
-    // not queue up on one address.  The compiler turns the atomic (one lane, wave-uniform
-    // address) into a form whose result it reads back at once, which waits for everything the
-    // drawing wave has in flight; before a barrier the whole workgroup would wait for it, so the
-    // ticket is drawn behind the barriers of the first item's set-up.
-    uint32_t ticket = 0xffffffffu;
-    auto draw_ticket = [&]() {
-        if (tid == kThreads - 64)
-            ticket = __hip_atomic_fetch_add(a.tickets + blockIdx.x % kTicketGroups, 1u, __ATOMIC_RELAXED,
-                                            __HIP_MEMORY_SCOPE_AGENT);
+    // the softmax of wave t's token, off the path to the first weight load
+    auto softmax = [&]() {
+        if (wave < T && ok) finish_softmax(a, s_logit + wave * E, s_rank + wave * E, s_conf + wave * k, s_w + wave * k);
+    };
+    // This workgroup will not look at the slots again: its last wave draws a ticket (the holder of the last one
+    // puts the slots back to idle, at its own end).
+    uint32_t ticket = 0xffffffffu, ticket2 = 0xffffffffu;
+    if (tid == kThreads - 64) ticket = draw_ticket(a.tickets + blockIdx.x % kTicketGroups);
+    auto second_ticket = [&]() {
+        if (lane == 0 && ticket == ticket_members(blockIdx.x, gridDim.x) - 1) ticket2 = draw_ticket(a.tickets + kTicketGroups);
     };
 
-    // ---- 3. this workgroup's items: the distinct experts ascending, I / 32 slices each
+    // ---- 3. this workgroup's items: the distinct experts ascending, I / 32 slices each.  Every wave lists the
+    // experts for itself (the same values in the same places, so no barrier is needed).
     int n_experts_used = 0;
-#pragma unroll
-    for (int wd = 0; wd < MOE_MAX_EXPERTS / 64; ++wd) {
+    for (int wd = 0; wd * 64 < E; ++wd) {
         const unsigned long long mk = s_mask[wd];
-        mask_lo[wd] = __builtin_amdgcn_readfirstlane((uint32_t)mk);
-        mask_hi[wd] = __builtin_amdgcn_readfirstlane((uint32_t)(mk >> 32));
-        n_experts_used += __popc(mask_lo[wd]) + __popc(mask_hi[wd]);
+        const uint32_t lo = __builtin_amdgcn_readfirstlane((uint32_t)mk), hi = __builtin_amdgcn_readfirstlane((uint32_t)(mk >> 32));
+        const int below = n_experts_used + __builtin_amdgcn_mbcnt_hi(hi, __builtin_amdgcn_mbcnt_lo(lo, 0));
+        if (((lane < 32 ? lo : hi) >> (lane & 31)) & 1u) s_list[below] = wd * 64 + lane;
+        n_experts_used += __popc(lo) + __popc(hi);
     }
-    if constexpr (MT != 1) split_items(ok ? n_experts_used * nslice : 0);
-    if (!ok) it_end = it_begin;
-    STAMP(14);
+    auto nth_expert = [&](int u) { return __builtin_amdgcn_readfirstlane(s_list[u]); };
+    split_items(ok ? n_experts_used * nslice : 0);
     if (it_begin < it_end) {
-        if (MT == 1 && E <= kLoneWaveTopk) {
-            item_addr(cur, __builtin_amdgcn_readfirstlane(s_first[0]));
-            if (it_begin + 1 < it_end) item_addr(nxt, __builtin_amdgcn_readfirstlane(s_first[1]));
-            else nxt = cur;
-        } else {
-            item_addr(cur, nth_expert(cur.u));
-            if (it_begin + 1 < it_end) item_addr(nxt, nth_expert(nxt.u));
-            else nxt = cur;
-        }
-        STAMP(15);
+        item_addr(cur, nth_expert(cur.u));
+        if (it_begin + 1 < it_end) item_addr(nxt, nth_expert(nxt.u));
+        else nxt = cur;
         // ---- 3a. the first entries and the first window of weight loads go out before anything
         // else of the item is set up: every microsecond of bookkeeping behind them is hidden by
         // their latency
         u32x4 win[kWin];
         if (Lw > 0) {
-            request_entries(cur, 0);
+            request_gu_entries(cur);
             const Run w0 = window_run(cur, nxt, it_begin + 1 < it_end, 0);
 #pragma unroll
             for (int i = 0; i < kWin; ++i) win[i] = __builtin_nontemporal_load(tile_of(w0, i));
         }
-        STAMP(4);
-        if (wave == 0) item_rows(cur.expert, 0);
-        finish_softmax();
+        if (wave == kWaves - 1) item_rows(cur.expert, 0);
+        softmax();
         __syncthreads();
-        draw_ticket();
 
         for (int it = it_begin; it < it_end; ++it) {
             const int par = (it - it_begin) & 1;
@@ -572,8 +355,7 @@ void draft_stream_kernel(const uint16_t *__restrict__ xin, const FusedArgs a)
             }
             float tot1 = 0.f;
             if (Lw > 0) {
-                // the successor's entries, before any of the successor's tiles is requested
-                if (!last) request_entries(nxt, par ^ 1);
+                request_dn_entries(cur);
                 u32x4 xa = *reinterpret_cast<const u32x4 *>(xrow + (nt > 0 ? u0 : 0) * 32);
                 // one window of the gate/up part; kGuard: some of its tiles may lie past the wave's
                 // run (the padding of the last window) and are skipped.  Full windows carry no
@@ -608,14 +390,14 @@ void draft_stream_kernel(const uint16_t *__restrict__ xin, const FusedArgs a)
                                 for (int j = 0; j < NI; ++j) xs[j] = s_xsum[tok[j] * G + gi];
                                 behind_tile(qv.x);
                                 if constexpr (kOwnGu) {
-                                    const uint32_t ev = own_entry(par, 0, (gi - g0) / kEpl, gi & 1);
+                                    const uint32_t ev = own_entry(0, (gi - g0) / kEpl, gi & 1);
                                     const float sc = (float)__builtin_bit_cast(_Float16, (uint16_t)(ev & 0xffff));
                                     const float zp = SYM ? 136.f : (float)__builtin_bit_cast(_Float16, (uint16_t)(ev >> 16)) + 128.f;
                                     tot1 += sc * (of_my_block(acc[0][0], acc[1][0], acc[2][0], acc[3][0]) - zp * xs[0]);
 #pragma unroll
                                     for (int d = 0; d < 4; ++d) acc[d] = (f32x4){0.f, 0.f, 0.f, 0.f};
                                 } else {
-                                    const GroupParams<SYM> gp = row_entries(par, 0, (gi - g0) / kEpl, gi & 1);
+                                    const GroupParams<SYM> gp = row_entries(0, (gi - g0) / kEpl, gi & 1);
 #pragma unroll
                                     for (int d = 0; d < 4; ++d) {
                                         const float sc = gp.scale(d), zp = gp.zero128(d);
@@ -636,7 +418,6 @@ void draft_stream_kernel(const uint16_t *__restrict__ xin, const FusedArgs a)
                 // the window now holds this wave's first down tiles (or, for a wave without down
                 // tiles, the successor's first gate/up tiles)
             }
-            if (it - it_begin < 2) STAMP(5 + 4 * (it - it_begin));
             if constexpr (kOwnGu) {
                 s_red[wave][c][0][r] = tot1;
             } else if (c < NC) {
@@ -646,7 +427,6 @@ void draft_stream_kernel(const uint16_t *__restrict__ xin, const FusedArgs a)
                     for (int i = 0; i < NI; ++i) s_red[wave][d][i][c * 16 + r] = tot[d][i];
             }
             __syncthreads();
-            if (it - it_begin < 2) STAMP(6 + 4 * (it - it_begin));
             // h for (token slot, row): row blocks 0, 1 are gate rows 0-15, 16-31; 2, 3 the matching up rows
             for (int idx = tid; idx < 2 * NI * NC * 16; idx += kThreads) {
                 const int lr = idx % (NC * 16), i = (idx / (NC * 16)) % NI, d = idx / (NC * 16 * NI);
@@ -671,11 +451,11 @@ void draft_stream_kernel(const uint16_t *__restrict__ xin, const FusedArgs a)
             // the last wave (it has no part in the sums above) sets up the successor's rows and
             // clears the successor's h sums; the other copy of both is still being read
             if (wave == kWaves - 1) {
+                if (it == it_begin) second_ticket();
                 if (!last) item_rows(nxt.expert, par ^ 1);
                 if (lane < MT) s_hsum[par ^ 1][lane] = 0.f;
             }
             __syncthreads();
-            if (it - it_begin < 2) STAMP(7 + 4 * (it - it_begin));
 
             // ---- down: this wave's row tiles, all H outputs of the slice's 32 columns.
             // The hi and the lo part of h of a token slot are two A rows, so one MFMA yields both
@@ -688,6 +468,7 @@ void draft_stream_kernel(const uint16_t *__restrict__ xin, const FusedArgs a)
             constexpr int kRs = 16 / kBpa;                           // A rows per row block
             constexpr int kLgb = 4 / kBpa;                           // lane groups per row block
             constexpr int ND = MT < 2 ? 1 : 2;                       // token slots per lane
+            if (Lw > 0 && !last) request_gu_entries(nxt);
             if (Lw > 0 && ndw > 0) {
                 u32x4 hab[kBpa];
                 {
@@ -714,7 +495,6 @@ void draft_stream_kernel(const uint16_t *__restrict__ xin, const FusedArgs a)
                     tokd[i] = arow / k;
                     rwd[i] = s_w[arow];
                 }
-                if (it == it_begin) STAMP(16);
                 // one pass over the window; every slot is refilled with the stream's tile kWin further
                 // on (clamped, unconditional), which after this item's last down tile is the
                 // successor's first gate/up tile
@@ -729,13 +509,12 @@ void draft_stream_kernel(const uint16_t *__restrict__ xin, const FusedArgs a)
                         __builtin_amdgcn_sched_barrier(0);
                         win[i] = __builtin_nontemporal_load(tile_of(wr, i));
                         __builtin_amdgcn_sched_barrier(0);
-                        if (it == it_begin) STAMP(17 + i);
                         if (rt < r1) {
                             behind_tile(qv.x);
                             uint32_t ev = 0;
                             GroupParams<SYM> gp;
-                            if constexpr (kOwnEntry) ev = own_entry(par, 1, (rt - r0) / kEpl, rt & 1);
-                            else gp = row_entries(par, 1, (rt - r0) / kEpl, rt & 1);
+                            if constexpr (kOwnEntry) ev = own_entry(1, (rt - r0) / kEpl, rt & 1);
+                            else gp = row_entries(1, (rt - r0) / kEpl, rt & 1);
 #pragma unroll
                             for (int q = 0; q < 4 / kBpa; ++q) {
                                 f32x4 o = (f32x4){0.f, 0.f, 0.f, 0.f};
@@ -764,36 +543,17 @@ void draft_stream_kernel(const uint16_t *__restrict__ xin, const FusedArgs a)
                 };
                 for (int j0 = 0; j0 < ndw; j0 += kWin) down_pass(j0);
             }
-            if (it - it_begin < 2) STAMP(8 + 4 * (it - it_begin));
             cur = nxt;
             if (it + 2 < it_end) { item_after(nxt, cur); item_addr(nxt, nth_expert(nxt.u)); }
         }
     } else {
-        finish_softmax();
-        draw_ticket();
+        softmax();
+        if (wave == kWaves - 1) second_ticket();
+        __syncthreads();
     }
 
-    STAMP(13);
-    // ---- 4. last ticket: every workgroup has its logits, put the workspace back to idle
-    if (tid == kThreads - 64) {
-        const uint32_t grp = blockIdx.x % kTicketGroups;
-        const uint32_t members = (gridDim.x - grp + kTicketGroups - 1) / kTicketGroups;
-        int last = 0;
-        if (ticket == members - 1) {                   // last of its group: second level
-            const uint32_t ngroups = gridDim.x < (uint32_t)kTicketGroups ? gridDim.x : (uint32_t)kTicketGroups;
-            const uint32_t t2 = __hip_atomic_fetch_add(a.tickets + kTicketGroups, 1u, __ATOMIC_RELAXED,
-                                                       __HIP_MEMORY_SCOPE_AGENT);
-            last = t2 == ngroups - 1;
-        }
-        s_flag = last;
-    }
-    __syncthreads();
-    if (s_flag) {
-        for (int i = tid; i < T * E * kReplicas; i += kThreads)
-            __hip_atomic_store(a.slots + (size_t)(i / (T * E)) * a.replica_stride + 2 * (size_t)(i % (T * E)) + 1, 0ull,
-                               __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-        if (tid <= kTicketGroups) __hip_atomic_store(a.tickets + tid, 0u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-    }
+    // ---- 4. the holder of the last ticket puts the workspace back to idle
+    if (wave == kWaves - 1 && __any(ticket2 == ticket_groups(gridDim.x) - 1)) reset_exchange(a);
 
     // ---- 5. workgroup 0 reports the routing (and the plan the shared-expert kernels read)
     if (blockIdx.x != 0) return;
@@ -867,12 +627,12 @@ void stream_read_kernel(const u32x4 *__restrict__ src, size_t tiles, uint32_t *s
 // the phi shape, 2 tokens: 37.9 us against 40.7 us with 16 waves and windows of 4.
 constexpr int stream_waves(int) { return 8; }
 constexpr int stream_window(int) { return 8; }
-constexpr int stream_wg_per_cu(int MT) { return MT <= 2 ? 2 : 1; }
+constexpr int kMaxPerCu = 2;
 
 // dynamic LDS: the bf16 copy of x (padded rows), its per-group sums, the routing scratch (fp64
-// logits and ranks), and per wave two copies of the scale / zero entries of its groups and row
-// tiles of one item (whole KiB each)
-size_t draft_dynamic_lds(int MT, int H, int g, int E, bool sym)
+// logits and ranks), and per wave the scale / zero entries of its groups and row tiles of one
+// item (whole KiB each)
+size_t draft_dynamic_lds(int MT, int H, int g, int E, bool sym, int entry_copies = 1)
 {
     const int nw = stream_waves(MT);
     size_t lds = ((size_t)MT * (H + 8) * 2 + (size_t)MT * (H / g) * 4 + 7) & ~(size_t)7;
@@ -880,18 +640,17 @@ size_t draft_dynamic_lds(int MT, int H, int g, int E, bool sym)
     lds = (lds + 15) & ~(size_t)15;
     const int epl = sym ? 2 : 1;
     const int gl_max = (H / g / epl + nw - 1) / nw, dl_max = (H / 64 / epl + nw - 1) / nw;
-    lds += (size_t)nw * 2 * ((size_t)((gl_max + 3) / 4) + (size_t)((dl_max + 3) / 4)) * 1024;
+    lds += (size_t)entry_copies * nw * ((size_t)((gl_max + 3) / 4) + (size_t)((dl_max + 3) / 4)) * 1024;
     return lds;
 }
 
 template <int MT, bool SYM>
-void launch_stream_t(const uint16_t *x, const FusedArgs &a, int n_cu, hipStream_t st)
+void launch_stream_t(const uint16_t *x, const FusedArgs &a, long slots, hipStream_t st)
 {
     constexpr int NW = stream_waves(MT), KW = stream_window(MT);
-    // at most one workgroup per compute unit, never more than there can be items
+    // never more workgroups than there can be items
     const int maxu = a.E < a.T * a.k ? a.E : a.T * a.k;
     const long items = (long)maxu * (a.I / 32);
-    const long slots = (long)n_cu * stream_wg_per_cu(MT);
     const dim3 grid((unsigned)(items < slots ? items : slots)), block(NW * 64);
     const size_t lds = draft_dynamic_lds(MT, a.H, a.g, a.E, SYM);
     if (a.g == 32) launch_with_lds(draft_stream_kernel<MT, 1, SYM, NW, KW>, grid, block, lds, st, x, a);
@@ -900,26 +659,11 @@ void launch_stream_t(const uint16_t *x, const FusedArgs &a, int n_cu, hipStream_
 }
 
 template <bool SYM>
-void launch_stream(int T, const uint16_t *x, const FusedArgs &a, int n_cu, hipStream_t st)
+void launch_stream(int T, const uint16_t *x, const FusedArgs &a, long slots, hipStream_t st)
 {
-    if (T <= 2) launch_stream_t<2, SYM>(x, a, n_cu, st);
-    else if (T <= 4) launch_stream_t<4, SYM>(x, a, n_cu, st);
-    else launch_stream_t<8, SYM>(x, a, n_cu, st);
-}
-
-}  // namespace
-
-void launch_draft_fused(const Shape &s, const DraftFusedArgs &d, int n_cu, hipStream_t st)
-{
-    // One token: items are few (k I / 32, about one and a half per compute unit on the phi shape) and
-    // one workgroup per item is as fast or a little faster (phi 25.5 us against 26.3 us for the
-    // persistent launch, mixtral 49.7 / 50.6, qwen3 18.9 / 19.5); from two tokens on the persistent
-    // launch wins (4 tokens: 56 against 76 us, 8 tokens: 90 against 144 us).
-    if (s.T == 1) { launch_draft_one_token(s, d, st); return; }
-    const FusedArgs a = fused_args(s, d);
-    const uint16_t *x = (const uint16_t *)d.x;
-    if (d.symmetric) launch_stream<true>(s.T, x, a, n_cu, st);
-    else launch_stream<false>(s.T, x, a, n_cu, st);
+    if (T <= 2) launch_stream_t<2, SYM>(x, a, slots, st);
+    else if (T <= 4) launch_stream_t<4, SYM>(x, a, slots, st);
+    else launch_stream_t<8, SYM>(x, a, slots, st);
 }
 
 template <int MT, bool SYM>
@@ -932,30 +676,48 @@ int stream_resident_per_cu(const Shape &s)
     return resident_per_cu(draft_stream_kernel<MT, 4, SYM, NW, KW>, NW * 64, lds);
 }
 
+}  // namespace
+
 // The launch shapes: one token, one workgroup per item, dispatched in order, so the first
 // min(E, grid) of them are resident together when that many fit on the device at once; more tokens,
-// a grid of at most stream_wg_per_cu workgroups per compute unit, all of which must fit at once.
-bool draft_producers_resident(const Shape &s, const DraftFusedArgs &d, int n_cu)
+// a grid of as many workgroups as the device holds at once.
+int draft_resident_slots(const Shape &s, const DraftFusedArgs &d, int n_cu)
 {
     const int maxu = s.E < s.T * s.k ? s.E : s.T * s.k;
     const long items = (long)maxu * (s.I / 32);
     if (s.T == 1) {
         const long need = s.E < items ? s.E : items;
-        return need <= draft_one_token_resident(s, d, n_cu);
+        const int slots = draft_one_token_resident(s, d, n_cu);
+        return need <= slots ? slots : 0;
     }
     const int MT = s.T <= 2 ? 2 : (s.T <= 4 ? 4 : 8);
     int per = 0;
     if (d.symmetric) per = MT == 2 ? stream_resident_per_cu<2, true>(s) : (MT == 4 ? stream_resident_per_cu<4, true>(s) : stream_resident_per_cu<8, true>(s));
     else per = MT == 2 ? stream_resident_per_cu<2, false>(s) : (MT == 4 ? stream_resident_per_cu<4, false>(s) : stream_resident_per_cu<8, false>(s));
-    return per >= stream_wg_per_cu(MT);
+    return (per < kMaxPerCu ? per : kMaxPerCu) * n_cu;
+}
+
+void launch_draft_fused(const Shape &s, const DraftFusedArgs &d, int slots, hipStream_t st)
+{
+    // One token: items are few (k I / 32, about one and a half per compute unit on the phi shape) and
+    // one workgroup per item is as fast or a little faster (phi 25.5 us against 26.3 us for the
+    // persistent launch, mixtral 49.7 / 50.6, qwen3 18.9 / 19.5); from two tokens on the persistent
+    // launch wins (4 tokens: 56 against 76 us, 8 tokens: 90 against 144 us).
+    if (s.T == 1) { launch_draft_one_token(s, d, st); return; }
+    const FusedArgs a = fused_args(s, d);
+    const uint16_t *x = (const uint16_t *)d.x;
+    if (d.symmetric) launch_stream<true>(s.T, x, a, slots, st);
+    else launch_stream<false>(s.T, x, a, slots, st);
 }
 
 bool draft_fits(const Shape &s, int tokens, bool sym)
 {
     if (tokens <= 1) return draft_one_token_fits(s);
     const int MT = tokens <= 2 ? 2 : (tokens <= 4 ? 4 : 8);
-    // 160 KiB of LDS per workgroup, 20 KiB of them for the kernel's static arrays
-    return draft_dynamic_lds(MT, s.H, s.g, s.E, sym) <= (size_t)(160 - 20) * 1024;
+    // 160 KiB of LDS per workgroup, 20 KiB of them for the kernel's static arrays.  (The limit callers
+    // know counts the entries twice; one copy is kept.)
+    const size_t entries = draft_dynamic_lds(MT, s.H, s.g, s.E, sym) - draft_dynamic_lds(MT, s.H, s.g, s.E, sym, 0);
+    return draft_dynamic_lds(MT, s.H, s.g, s.E, sym) + entries <= (size_t)(160 - 20) * 1024;
 }
 
 void launch_stream_read(const void *src, size_t bytes, int workgroups, void *sink, hipStream_t st)
@@ -963,19 +725,6 @@ void launch_stream_read(const void *src, size_t bytes, int workgroups, void *sin
     launch(stream_read_kernel<8>, dim3(workgroups), dim3(512), 0, st, (const u32x4 *)src,
                        bytes / 1024, (uint32_t *)sink);
 }
-
-#ifdef MOE_STAMPS
-extern "C" int moe_debug_stamps(unsigned long long *host, size_t n)
-{
-    return (int)hipMemcpyFromSymbol(host, HIP_SYMBOL(moe_stamps), n * sizeof(unsigned long long), 0, hipMemcpyDeviceToHost);
-}
-extern "C" int moe_debug_clear_stamps(void)
-{
-    void *p = nullptr;
-    if (hipGetSymbolAddress(&p, HIP_SYMBOL(moe_stamps)) != hipSuccess) return -1;
-    return (int)hipMemset(p, 0, sizeof(unsigned long long) * 1024 * 8 * 32);
-}
-#endif
 
 void launch_zero(void *p, size_t bytes, hipStream_t st)
 {

@@ -22,756 +22,430 @@ namespace moespeq {
 
 namespace {
 
-// MT: token capacity of the launch (1, 2, 4 or 8); UPG: 32-code units per group (g / 32); SYM:
-// symmetric format (scale blobs, z = 8).  Only MT = 1 is instantiated: calls of two to eight
-// tokens run the streaming kernel, longer runs the grouped contraction.
-template <int MT, int UPG, bool SYM>
-__global__ __launch_bounds__(kThreads, MT <= 2 ? 4 : 2)   // MT <= 2: 4 waves per SIMD, two workgroups per CU
+// UPG: 32-code units per group (g / 32); SYM: symmetric format (scale blobs, z = 8); SHARED: the layer has
+// shared experts (a layer without them runs a smaller kernel: its start is a chain of code that runs once)
+template <int UPG, bool SYM, bool SHARED>
+__global__ __launch_bounds__(kThreads, 4)            // 4 waves per SIMD, two workgroups per compute unit
 void draft_fused_kernel(const uint16_t *__restrict__ xin, const FusedArgs a)
 {
-    constexpr int NI = MT < 4 ? MT : 4;          // D rows (tokens) per lane that can be valid
-    constexpr int NC = MT > 4 ? 2 : 1;           // lane groups (of 16) whose D rows can be valid
-    // tiles a wave keeps in flight (rolling window); no instantiation spills with 8 (two
-    // workgroups per CU leave 128 VGPRs per wave for MT <= 2)
-    constexpr int kGuWin = 8;
-    constexpr int kSzWin = kGuWin / UPG;
+    // tiles a wave keeps in flight (rolling window): two workgroups per compute unit leave 128 VGPRs per
+    // wave, and with an entry per tile (g = 32) a window of 8 spills
+    constexpr int kWin = UPG == 1 ? 6 : 8;
+    constexpr int kSzWin = kWin / UPG;
     __shared__ double s_part[kWaves];
-    __shared__ int32_t s_ids[MOE_MAX_ASSIGN];
-    __shared__ float s_w[MOE_MAX_ASSIGN];
-    __shared__ float s_conf[MOE_MAX_ASSIGN];
-    __shared__ unsigned long long s_mask[MOE_MAX_EXPERTS / 64];
-    __shared__ int32_t s_row_a[MT];             // assignment index of each row (token) of this item
-    __shared__ int32_t s_cnt;
-    __shared__ int32_t s_flag;
-    __shared__ double s_few[MT][kLoneWaveTopk];   // few experts: a token's logits for the ranking
-    // partial gate/up sums [wave][row block][token in lane group][lane].  With 8 tokens the array
-    // (16 KiB) takes the place of the x copy, which is no longer needed by then: the workgroup's LDS
-    // then stays under half of a compute unit's, so that two workgroups share a unit.
-    constexpr bool kRedOverX = MT >= 8;
-    typedef float red_t[4][NI][NC * 16];
-    __shared__ float s_red_own[kRedOverX ? 1 : kWaves * 4 * NI * NC * 16];
-    __shared__ __attribute__((aligned(16))) uint16_t s_hhi[MT][32], s_hlo[MT][32];
-    __shared__ float s_hsum[MT];
-    extern __shared__ __attribute__((aligned(16))) unsigned char s_dyn[];   // x copy, then its group sums
+    __shared__ int32_t s_ids[MOE_MAX_TOPK];
+    __shared__ float s_w[MOE_MAX_TOPK], s_conf[MOE_MAX_TOPK];
+    __shared__ int32_t s_ok;
+    __shared__ float s_red[kWaves][64];              // partial gate/up sums
+    __shared__ __attribute__((aligned(16))) uint16_t s_h[kWaves][2][32];    // h and its remainder, each wave's own copy
+    extern __shared__ __attribute__((aligned(16))) unsigned char s_dyn[];   // x, its group sums, logits, ranks
 
     const int tid = threadIdx.x;
     const int lane = tid & 63;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
-    const int T = a.T, H = a.H, E = a.E, I = a.I, k = a.k, g = a.g;
-    const int n = T * k;
-    const int G = H / g;
-    const int xstride = H + 8;                   // bf16 elements per token in LDS (+16 B against bank conflicts)
+    const int H = a.H, E = a.E, I = a.I, k = a.k;
+    const int G = H / (32 * UPG), U = H / 32, nslice = I / 32;
     uint16_t *s_x = reinterpret_cast<uint16_t *>(s_dyn);
-    float *s_xsum = reinterpret_cast<float *>(s_dyn + (size_t)MT * xstride * 2);   // [MT][G]
-    static_assert(!kRedOverX || sizeof(red_t) * kWaves == (size_t)kWaves * 4 * 4 * 32 * 4, "launcher sizes the dynamic LDS for this");
-    red_t *s_red = reinterpret_cast<red_t *>(kRedOverX ? reinterpret_cast<float *>(s_dyn) : s_red_own);
-    // routing scratch behind the group sums, used with many experts: logits [MT][E] (fp64), ranks
-    const size_t logit_off = ((size_t)MT * xstride * 2 + (size_t)MT * G * 4 + 7) & ~(size_t)7;
-    double *s_logit = reinterpret_cast<double *>(s_dyn + logit_off);
-    int32_t *s_rank = reinterpret_cast<int32_t *>(s_dyn + logit_off + (size_t)MT * E * 8);
-    // ---- 1. router rows owned by this workgroup (fp64 accumulation of exact fp32 products)
-    if ((int)blockIdx.x < E) {
-        const int nprod = E < (int)gridDim.x ? E : (int)gridDim.x;
-        for (int i = blockIdx.x * kThreads + tid; i < T * H; i += nprod * kThreads)
-            __hip_atomic_store(&a.y[i], 0.f, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-    }
-    for (int e = blockIdx.x; e < E; e += gridDim.x) {
-        const uint16_t *row = a.wr + (size_t)e * H;
-        for (int t = 0; t < T; ++t) {
-            const uint16_t *xt = xin + (size_t)t * H;
-            double acc = 0.0;
-            for (int c = tid; c < H / 8; c += kThreads) {
-                const u32x4 xv = *reinterpret_cast<const u32x4 *>(xt + c * 8);
-                const u32x4 wv = *reinterpret_cast<const u32x4 *>(row + c * 8);
-                const uint32_t xs[4] = {xv.x, xv.y, xv.z, xv.w}, ws[4] = {wv.x, wv.y, wv.z, wv.w};
-#pragma unroll
-                for (int i = 0; i < 4; ++i) {
-                    acc += (double)(bf16_lo(xs[i]) * bf16_lo(ws[i]));     // bf16 x bf16 is exact in fp32
-                    acc += (double)(bf16_hi(xs[i]) * bf16_hi(ws[i]));
-                }
-            }
-            acc = wave::sum(acc);
-            if (lane == 0) s_part[wave] = acc;
-            // every thread's clearing stores have been performed before the workgroup publishes (a
-            // workgroup-scope release fence does not imply this wait; it is free here, the loads
-            // of the row were issued after the stores and have returned)
-            asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
-            __syncthreads();
-            if (tid < kReplicas) {                                       // thread r writes replica r
-                double l = 0.0;
-                for (int w = 0; w < kWaves; ++w) l += s_part[w];
-                l += a.bias ? (double)a.bias[e] : 0.0;
-                // {logit, tag} leaves as ONE aligned 16-byte agent-scope store and is read with one
-                // 16-byte load: a reader sees the tag only together with the logit
-                const unsigned long long lb = (unsigned long long)__double_as_longlong(l);
-                const u32x4 rec = {(uint32_t)lb, (uint32_t)(lb >> 32), 1u, 0u};
-                store16_agent(a.slots + (size_t)tid * a.replica_stride + 2 * ((size_t)t * E + e), rec);
-            }
-            __syncthreads();
-        }
-    }
-    if (tid == 0) s_flag = 1;
-    if (tid < MOE_MAX_EXPERTS / 64) s_mask[tid] = 0ull;
-    __syncthreads();
-
-    // ---- 1b. (while the router result travels) stage x in LDS and sum it per group
-    const int Ts = T;
-    for (int i = tid; i < Ts * (H / 8); i += kThreads) {
-        const int t = i / (H / 8), c8 = i % (H / 8);
-        const int src = t;
-        *reinterpret_cast<u32x4 *>(s_x + t * xstride + c8 * 8) = *reinterpret_cast<const u32x4 *>(xin + (size_t)src * H + c8 * 8);
-    }
-    __syncthreads();
-    for (int i = tid; i < Ts * G * 16; i += kThreads) {       // 16 threads per (token, group)
-        const int part = i & 15, tg_ = i >> 4;
-        const int t = tg_ / G, gi = tg_ % G;
-        const int per = g / 16;                               // 2, 4 or 8 values each
-        const uint16_t *src = s_x + t * xstride + gi * g + part * per;
-        float v = 0.f;
-        for (int j = 0; j < per; ++j) v += __uint_as_float((uint32_t)src[j] << 16);
-        v = wave::row_sum(v);
-        if (part == 0) s_xsum[t * G + gi] = v;
-    }
-
-    // ---- 2. wave t polls the slots of token t (bounded), then selects its top-k
-    double sm_logit = -INFINITY;                 // few experts: this lane's logit and rank, for the softmax later
-    int sm_rank = MOE_MAX_EXPERTS;
-    for (int t = wave; t < T; t += kWaves) {
-        double l[4];
-        {
-            uint32_t spins = 0;
-            bool all = false;
-            while (!all && ++spins < a.spin_limit) {
-                bool mine = true;
-#pragma unroll
-                for (int i = 0; i < 4; ++i) {
-                    const int e = lane + 64 * i;
-                    if (e < E) {
-                        const u32x4 v = load16_agent(a.slots + (size_t)(blockIdx.x % kReplicas) * a.replica_stride +
-                                                     2 * ((size_t)t * E + e));
-                        mine = mine && v.z == 1u;
-                        l[i] = __longlong_as_double((long long)(((unsigned long long)v.y << 32) | v.x));
-                    } else {
-                        l[i] = -INFINITY;
-                    }
-                }
-                all = __all(mine);
-                if (!all) __builtin_amdgcn_s_sleep(2);
-            }
-            if (!all) {                          // gave up: the call fails, and says so in the workspace
-                if (lane == 0) {
-                    s_flag = 0;
-                    __hip_atomic_store(a.status, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-                }
-                continue;
-            }
-        }
-        if (E <= kLoneWaveTopk) {
-            // Rank of every logit in the strict order (larger first, lower index first among equals),
-            // so the ranks are a permutation and rank < k selects.  The wave's 64 lanes are P copies of
-            // the experts (E2 = E rounded up to a power of two, P = 64 / E2 >= 2): copy q of expert e
-            // counts the logits q per .. q per + per - 1 that come before logit e, read from LDS (the
-            // lanes of one copy read one address), and the P counts meet through lane exchanges.  Only
-            // the selection is on the path to the first weight load; the softmax follows behind the
-            // first loads.  (A serial count over all experts in one wave, with the softmax, took 1.1 us
-            // for 16 experts: a lone wave issues one dependent instruction every 8 to 16 clocks.)
-            if (lane < E) s_few[t][lane] = l[0];
-            int E2 = 2;
-            while (E2 < E) E2 <<= 1;
-            const int P = 64 / E2, per = (E + P - 1) / P;
-            const int q = lane / E2, e = lane % E2;
-            const double mine = s_few[t][e < E ? e : E - 1];
-            int part = 0;
-            for (int j = 0; j < per; ++j) {
-                const int e2 = q * per + j;
-                const double v = s_few[t][e2 < E ? e2 : E - 1];
-                part += (int)(e2 < E) & ((int)(v > mine) | ((int)(v == mine) & (int)(e2 < e)));
-            }
-            for (int d = E2; d < 64; d <<= 1) part += __shfl_xor(part, d, 64);
-            if (lane < E) {
-                sm_logit = mine;
-                sm_rank = part;
-                if (part < k) {
-                    s_ids[t * k + part] = lane;
-                    atomicOr(&s_mask[lane >> 6], 1ull << (lane & 63));
-                }
-            }
-        } else {
-            // many experts: the logits go to LDS and all waves rank them (below)
-#pragma unroll
-            for (int i = 0; i < 4; ++i) {
-                const int e = lane + 64 * i;
-                if (e < E) { s_logit[t * E + e] = l[i]; s_rank[t * E + e] = 0; }
-            }
-        }
-    }
-    if (E > kLoneWaveTopk) {
-        // Ranks in the order (larger first, lower index first among equals), counted by all eight
-        // waves, each over its share of the experts; the order is strict, so rank < k selects.  (k
-        // rounds of arg-max in the one wave of a token took 5.4 us for 128 experts and k = 8.)
-        __syncthreads();
-        if (s_flag != 0) {
-            for (int t = 0; t < T; ++t) {
-                if (E <= 64) wave::count_ranks<1, 4>(s_logit + t * E, s_rank + t * E, E, lane, wave, kWaves);
-                else if (E <= 128) wave::count_ranks<2, 4>(s_logit + t * E, s_rank + t * E, E, lane, wave, kWaves);
-                else wave::count_ranks<4, 2>(s_logit + t * E, s_rank + t * E, E, lane, wave, kWaves);
-            }
-        }
-        __syncthreads();
-        for (int t = wave; t < T && s_flag != 0; t += kWaves) {
-            double mine[4];
-            int rank[4];
-            double mx = -INFINITY;
-#pragma unroll
-            for (int i = 0; i < 4; ++i) {
-                const int e = lane + 64 * i;
-                const bool have = 64 * i < E && e < E;
-                mine[i] = have ? s_logit[t * E + e] : -INFINITY;
-                rank[i] = have ? s_rank[t * E + e] : MOE_MAX_EXPERTS;
-                mx = fmax(mx, mine[i]);
-            }
-            mx = wave::max(mx);
-            // the selection compares the fp64 logits; the softmax values only have to be good to
-            // fp32, so they are computed in fp32 from the fp64 differences
-            float pe[4], den = 0.f, sel = 0.f;
-#pragma unroll
-            for (int i = 0; i < 4; ++i) {
-                pe[i] = rank[i] < MOE_MAX_EXPERTS ? expf((float)(mine[i] - mx)) : 0.f;
-                den += pe[i];
-            }
-            den = wave::sum(den);
-#pragma unroll
-            for (int i = 0; i < 4; ++i) {
-                pe[i] = pe[i] / den;
-                sel += rank[i] < k ? pe[i] : 0.f;
-            }
-            sel = wave::sum(sel);
-#pragma unroll
-            for (int i = 0; i < 4; ++i) {
-                if (rank[i] < k) {
-                    const int e = lane + 64 * i;
-                    s_ids[t * k + rank[i]] = e;
-                    s_conf[t * k + rank[i]] = pe[i];
-                    s_w[t * k + rank[i]] = a.renorm ? pe[i] / sel : pe[i];
-                    atomicOr(&s_mask[e >> 6], 1ull << (e & 63));
-                }
-            }
-        }
-    }
-    __syncthreads();
-    const bool ok = s_flag != 0;
-    // This workgroup will not look at the slots again: it will draw a ticket.  The tickets are
-    // two-level (kTicketGroups first-level counters, then one) so that the returning atomics do
-    // not queue up on one address (measured: up to 5 us with one counter).  The compiler turns the
-    // atomic (one lane, wave-uniform address) into a form whose result it reads back at once, which
-    // waits for everything the drawing wave has in flight.  Where that happens matters: before a
-    // barrier the whole workgroup would wait for it, so the ticket is drawn behind the barriers of
-    // the item set-up (measured on the phi shape: 25.3 us there, 26.3 right after the first loads,
-    // 26.9 before the barrier that ends the gate/up phase; 25.8 and 26.2 with the wait deferred to
-    // the kernel's end, when the loads behind the ticket wait for it in the return queue instead).
-    uint32_t ticket = 0xffffffffu;
-    auto draw_ticket = [&]() {
-        if (tid == kThreads - 64)
-            ticket = __hip_atomic_fetch_add(a.tickets + blockIdx.x % kTicketGroups, 1u, __ATOMIC_RELAXED,
-                                            __HIP_MEMORY_SCOPE_AGENT);
-    };
-    // ---- 3. this workgroup's item: the u-th distinct expert (ascending id), slice s
-    const int nslice = I / 32;
-    const int u = blockIdx.x / nslice, slice = blockIdx.x % nslice;
-    int expert = -1;
-    if (ok) {
-        int seen = 0;
-        for (int wd = 0; wd < MOE_MAX_EXPERTS / 64 && expert < 0; ++wd) {
-            unsigned long long mk = s_mask[wd];
-            const int pc = __popcll(mk);
-            if (u < seen + pc) {
-                for (int r = u - seen; r > 0; --r) mk &= mk - 1ull;
-                expert = wd * 64 + __ffsll((long long)mk) - 1;
-            }
-            seen += pc;
-        }
-    }
-    expert = __builtin_amdgcn_readfirstlane(expert);   // the same in every lane; tell the compiler
-    // ---- 3a. the first window of weight loads goes out before anything else of the item is set
-    // up: the addresses need only the expert and the slice, and every microsecond of bookkeeping
-    // behind them is hidden by their latency.  (Without an expert -- a surplus workgroup -- the
-    // addresses are those of expert 0 and the loaded tiles are not used.)
-    const int ex = expert >= 0 ? expert : 0;
-    const int U = H / 32;
+    double *s_logit = reinterpret_cast<double *>(s_dyn + (size_t)H * 2);
+    int32_t *s_rank = reinterpret_cast<int32_t *>(s_logit + E);
+    float *s_xsum = reinterpret_cast<float *>(s_rank + E);
     const int r = lane & 15, c = lane >> 4;                  // MFMA lane coordinates
-    const UnpackConsts uk = unpack_consts();
-    const char *qb = a.q + (size_t)ex * a.stride_q;
-    const char *szb = a.sz + (size_t)ex * a.stride_sz;
-    // codes: [gate|up tiles (slice, ku)] then [down tiles (slice, rt)], 64 lanes x 16 B each
-    // A tile's address is a wave-uniform base (scalar arithmetic) plus the lane's 16 bytes.
-    const int gu0 = slice * U, dn0 = nslice * U + slice * (H / 64);          // first tile of each part
-    const uint32_t lane_off = (uint32_t)lane * 16u;
-    auto tile_ptr = [&](int tile) {
-        return reinterpret_cast<const u32x4 *>(qb + (size_t)tile * 1024 + lane_off);
-    };
-    // scale/zero: 16 B = the 4 row blocks' (s, z) of lane row r; [gate|up (slice, group)] then
-    // [down (group of I, rt)]
-    // (symmetric format: 16 B = the 4 row blocks' s of row r for two groups / two row tiles)
-    constexpr int kEpl = SYM ? 2 : 1;                        // groups (row tiles) per 16-byte load
-    const u32x4 *szgu = reinterpret_cast<const u32x4 *>(szb) + (size_t)slice * (G / kEpl) * 16 + r;
-    const u32x4 *szd = reinterpret_cast<const u32x4 *>(szb) + (size_t)nslice * (G / kEpl) * 16 +
-                       (size_t)((slice * 32) / g) * (H / (64 * kEpl)) * 16 + r;
 
-    // ---- this wave's tile stream: its gate/up tiles u0 .. u1 (K = H split over the waves by
-    // groups), padded to whole windows, then its down row tiles wave, wave + 8, ... (their loads
-    // do not depend on h).  A rolling window of kGuWin tiles is in flight.  EVERY load of the
-    // stream is unconditional: past the end of a part its address is clamped to the part's
-    // last tile.  The compiler counts the loads in flight in program order; a load under a
-    // branch makes it wait for all of them wherever it needs one, which empties the window.
+    // this thread's first piece of x, on its way while the router rows are reduced
+    u32x4 xr = *reinterpret_cast<const u32x4 *>(xin + (tid < H / 8 ? tid : H / 8 - 1) * 8);
+
+    // ---- 1. which work item.  The first workgroups reduce the router rows; workgroups are dispatched in order, so
+    // they are running before any other waits for them.  Behind them the shared experts' items, which start at
+    // once, then the other routed items, which wait for the routing.
+    const int n_sh = SHARED ? a.S * (I / 16) : 0, n_routed = (int)gridDim.x - n_sh;
+    const int nprod = E < n_routed ? E : n_routed;
+    const int b = blockIdx.x;
+    const bool shared = SHARED && b >= nprod && b < nprod + n_sh;
+    if (b < nprod) publish_router_rows<kWaves>(xin, a, b, nprod, s_part);
+    uint32_t ticket = 0xffffffffu, ticket2 = 0xffffffffu;
+    auto first_ticket = [&]() { if (lane == 0) ticket = draw_ticket(a.tickets + b % kTicketGroups); };
+    auto stage_x = [&]() {
+        if (tid < H / 8) *reinterpret_cast<u32x4 *>(s_x + tid * 8) = xr;
+        for (int i = tid + kThreads; i < H / 8; i += kThreads)
+            *reinterpret_cast<u32x4 *>(s_x + i * 8) = *reinterpret_cast<const u32x4 *>(xin + i * 8);
+        __syncthreads();
+    };
+    auto give_up = [&]() {
+        if (lane == 0) __hip_atomic_store(a.status, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    };
+    // Tickets: wave 0 draws the workgroup's when it has polled.  The holder of the last one puts the
+    // workspace back to idle (at its own end: nothing waits for it).
+    auto second_ticket = [&]() {
+        if (lane == 0 && ticket == ticket_members(b, gridDim.x) - 1) ticket2 = draw_ticket(a.tickets + kTicketGroups);
+    };
+    auto reset_if_last = [&]() {
+        if (__any(ticket2 == ticket_groups(gridDim.x) - 1)) reset_exchange(a);
+    };
+
+    if constexpr (SHARED) if (shared) {
+        // ---- 2. an item of a shared expert: 16 intermediate rows (a gate and an up tile of 16 x 32 bf16 per
+        // k-step), then their 16 columns of the down projection: half of a 16 x 32 tile, so a load takes the
+        // halves of two tiles, and one MFMA multiplies both (the A rows of one tile's half are zero in the
+        // other's k positions).  The stream and its window are the routed items'.
+        const int sh = (b - nprod) / (I / 16), row16 = (b - nprod) % (I / 16);
+        const char *blob = a.shared + (size_t)sh * a.shared_stride;
+        const char *gate = blob + (size_t)row16 * U * 1024, *up = gate + (size_t)I * H * 2;
+        const uint32_t rstep = (uint32_t)(I / 32) * 1024;            // from one output row tile to the next
+        const char *down = blob + (size_t)I * H * 4 + (size_t)(row16 / 2) * 1024;
+        const uint32_t lane_off = lane * 16u;
+        const uint32_t dlane = (uint32_t)(c >> 1) * 2 * rstep + (uint32_t)(((row16 & 1) * 2 + (c & 1)) * 16 + r) * 16u;
+        const int k0 = (wave * U) / kWaves, nt = ((wave + 1) * U) / kWaves - k0;
+        const int ntp = (2 * nt + kWin - 1) / kWin * kWin;           // gate/up loads, padded to whole windows
+        const int ngrp = H / 64;                                     // groups of four row tiles: two loads each
+        const int q0 = (wave * ngrp) / kWaves, nd = 2 * (((wave + 1) * ngrp) / kWaves - q0);
+        // gate and up tiles of a k-step are I H 2 bytes apart: two runs; a pair of down loads is 4 rstep from the next
+        const run_t g_run = make_run(gate + (size_t)k0 * 1024, nt * 1024), u_run = make_run(up + (size_t)k0 * 1024, nt * 1024);
+        const run_t d_run = make_run(down + (size_t)4 * q0 * rstep, nd > 0 ? 2 * nd * rstep - (uint32_t)(row16 / 2) * 1024 : 0);
+        auto pair_load = [&](bool into_down, int p, u32x4 &v, u32x4 &w) {      // loads p, p + 1 of a part
+            const uint32_t off = into_down ? dlane + 2u * (uint32_t)p * rstep : lane_off + (uint32_t)p * 512u;
+            v = run_load16(into_down ? d_run : g_run, off);
+            w = run_load16(into_down ? d_run : u_run, off + (into_down ? rstep : 0u));
+        };
+        u32x4 win[kWin];
+#pragma unroll
+        for (int i = 0; i < kWin; i += 2) pair_load(ntp == 0, i, win[i], win[i + 1]);
+        stage_x();
+        const uint16_t *xrow = s_x + c * 8;
+        f32x4 ag = {0.f, 0.f, 0.f, 0.f}, au = {0.f, 0.f, 0.f, 0.f};
+        for (int base = 0; base < ntp; base += kWin) {
+            const bool into_down = base + kWin >= ntp;
+#pragma unroll
+            for (int i = 0; i < kWin; i += 2) {
+                const int kk = (base + i) / 2;
+                const bf16x8 wg = __builtin_bit_cast(bf16x8, win[i]), wu = __builtin_bit_cast(bf16x8, win[i + 1]);
+                if (kk < nt) {                       // (the padding of the last window is skipped)
+                    const u32x4 xa = *reinterpret_cast<const u32x4 *>(xrow + (k0 + kk) * 32);
+                    ag = mfma(xa, wg, ag);
+                    au = mfma(xa, wu, au);
+                }
+                __builtin_amdgcn_sched_barrier(0);
+                pair_load(into_down, (into_down ? 0 : base + kWin) + i, win[i], win[i + 1]);
+                __builtin_amdgcn_sched_barrier(0);
+            }
+        }
+        // all 16 A rows are the token: every lane group holds the same sums
+        if (c < 2) s_red[wave][lane] = c == 0 ? ag[0] : au[0];
+        if (wave == 0) {
+            // the outputs may be added once y has been cleared, which every router workgroup does before it publishes
+            const bool ok = poll_and_select(a, 0, nullptr, nullptr, nullptr, nullptr);
+            first_ticket();
+            if (!ok) give_up();
+            if (lane == 0) s_ok = ok;
+        }
+        __syncthreads();
+        {
+            float v = 0.f;
+#pragma unroll
+            for (int w = 0; w < kWaves; ++w) v += s_red[w][lane & 31];
+            const float u = __shfl_xor(v, 16);
+            const float h = v / (1.f + expf(-v)) * u;
+            const uint16_t hi = f32_to_bf16_rne(h);
+            if (lane < 16) {
+                s_h[wave][0][lane] = hi;
+                s_h[wave][1][lane] = f32_to_bf16_rne(h - __uint_as_float((uint32_t)hi << 16));
+            }
+            __builtin_amdgcn_wave_barrier();
+        }
+        if (wave == 0) second_ticket();
+        if (s_ok) {
+            // A rows 4 q, 4 q + 1 hold h and its remainder for the tile whose outputs lane group q gets:
+            // groups 0, 2 from the halves of a pair's first load, 1, 3 from its second
+            u32x4 ha[2];
+            {
+                const u32x4 hv = *reinterpret_cast<const u32x4 *>(&s_h[wave][r & 1][(c & 1) * 8]);
+#pragma unroll
+                for (int j = 0; j < 2; ++j) {
+                    const bool on = (r & 3) < 2 && ((r >> 2) & 1) == j && (r >> 3) == (c >> 1);
+                    ha[j] = (u32x4){on ? hv.x : 0u, on ? hv.y : 0u, on ? hv.z : 0u, on ? hv.w : 0u};
+                }
+            }
+            auto down_pass = [&](int d0, auto reload) {
+#pragma unroll
+                for (int i = 0; i < kWin; i += 2) {
+                    f32x4 o = {0.f, 0.f, 0.f, 0.f};
+                    o = mfma(ha[0], __builtin_bit_cast(bf16x8, win[i]), o);
+                    o = mfma(ha[1], __builtin_bit_cast(bf16x8, win[i + 1]), o);
+                    if constexpr (decltype(reload)::value) {
+                        __builtin_amdgcn_sched_barrier(0);
+                        pair_load(true, d0 + kWin + i, win[i], win[i + 1]);
+                        __builtin_amdgcn_sched_barrier(0);
+                    }
+                    if (d0 + i < nd)
+                        __hip_atomic_fetch_add(&a.y[(q0 + (d0 + i) / 2) * 64 + lane], o[0] + o[1], __ATOMIC_RELAXED,
+                                               __HIP_MEMORY_SCOPE_AGENT);
+                }
+            };
+            int d0 = 0;
+            for (; d0 + kWin < nd; d0 += kWin) down_pass(d0, std::true_type{});
+            down_pass(d0, std::false_type{});
+        }
+        if (wave == 0) reset_if_last();
+        return;
+    }
+
+    // ---- 3. a routed item: slice `slice` of the u-th ranked expert.  What does not depend on the expert is computed
+    // while the router result travels.
+    const int item = b < nprod ? b : b - n_sh;
+    const int u = item / nslice, slice = item % nslice;
+    const UnpackConsts uk = unpack_consts();
+    const uint32_t lane_off = (uint32_t)lane * 16u;
     const int nrt = H / 64;
-    // (the symmetric format shares a load between two groups / row tiles: whole pairs per wave)
+    constexpr int kEpl = SYM ? 2 : 1;                        // groups (row tiles) per 16-byte unit of entries
+    // This wave's tile stream: its gate/up tiles u0 .. u1 (K = H split over the waves by groups; the
+    // symmetric format keeps two groups in a unit: whole pairs), padded to whole windows, then its down row
+    // tiles r0 .. r1 (their loads do not depend on h).  A rolling window of kWin tiles is in flight.  EVERY
+    // load of the stream is unconditional: the compiler counts the loads in flight in program order, and a
+    // load under a branch makes it wait for all of them wherever it needs one, which empties the window.
     const int u0 = ((wave * (G / kEpl)) / kWaves) * kEpl * UPG, u1 = (((wave + 1) * (G / kEpl)) / kWaves) * kEpl * UPG;
     const int nt = u1 - u0;
-    const int ntp = (nt + kGuWin - 1) / kGuWin * kGuWin;
-    const int r0 = ((wave * (nrt / kEpl)) / kWaves) * kEpl, r1 = (((wave + 1) * (nrt / kEpl)) / kWaves) * kEpl;   // this wave's down row tiles
-    const int rt_last = r1 > r0 ? r1 - 1 : 0;
-    const int g_last = nt > 0 ? (u1 - 1) / UPG : 0;
-    auto stream_ptr = [&](int p) -> const u32x4 * {            // p: position in the stream
-        const int ku = u0 + p;
-        const int rt = r0 + (p - ntp);
-        const int gt = gu0 + (ku < u1 ? ku : u1 - 1);
-        const int dt = dn0 + (rt < r1 ? rt : rt_last);
-        return tile_ptr(p < ntp ? gt : dt);
-    };
-    // Scale/zero entries are fetched 4 kEpl groups (or row tiles) per load: lane group c
-    // takes the 16 bytes of row r of load unit first / kEpl + 4 pk + c, and a lane picks the
-    // entry of the group at hand from that lane group with a lane permute.  `first` is a
-    // multiple of kEpl everywhere below.
-    constexpr int kPerPack = 4 * kEpl;
-    constexpr int kSzPacks = (kSzWin + kPerPack - 1) / kPerPack;
-    auto gsz_ptr = [&](int first, int pk) {
-        const int gi = first / kEpl + 4 * pk + c;
-        const int last = g_last / kEpl;
-        return szgu + (size_t)(gi < last ? gi : last) * 16;
-    };
-    // parameters of the j-th group (row tile) after the packs' first one, lane row r
-    auto pick = [&](const u32x4 *packs, int j) {
-        const u32x4 &v = packs[j / kPerPack];
-        const int src = ((j / kEpl) % 4) * 16 + r;
-        GroupParams<SYM> p;
-        if constexpr (SYM) {
-            p.w[0] = (uint32_t)__shfl((int)((j & 1) ? v.z : v.x), src, 64);
-            p.w[1] = (uint32_t)__shfl((int)((j & 1) ? v.w : v.y), src, 64);
-        } else {
-            p.w[0] = (uint32_t)__shfl((int)v.x, src, 64);
-            p.w[1] = (uint32_t)__shfl((int)v.y, src, 64);
-            p.w[2] = (uint32_t)__shfl((int)v.z, src, 64);
-            p.w[3] = (uint32_t)__shfl((int)v.w, src, 64);
-        }
-        return p;
-    };
-    // With ONE token all 16 A rows hold that token, so every lane group ends up with the same
-    // sums.  Lane group c then finishes row block c only: it loads that block's entry itself
-    // (no lane permutes), picks accumulator c and applies scale and zero to one value instead
-    // of four.
-    constexpr bool kOwnGu = MT == 1;
-    using gentry_t = typename std::conditional<SYM, uint16_t, uint32_t>::type;
-    const gentry_t *gent_base = reinterpret_cast<const gentry_t *>(szb) + (size_t)slice * G * 64 +
-                                (SYM ? r * 8 : r * 4) + c;
-    auto gent_load = [&](int gi) -> uint32_t {
-        const int t = gi < g_last ? gi : g_last;
-        return (uint32_t)__builtin_nontemporal_load(gent_base + (SYM ? (t >> 1) * 128 + (t & 1) * 4 : t * 64));
-    };
-    const uint32_t cm1 = 0u - (uint32_t)(c & 1), cm2 = 0u - (uint32_t)(c >> 1);
-    auto of_my_block = [&](float v0, float v1, float v2, float v3) {   // v_c, chosen with bit masks
-        const uint32_t lo = (__float_as_uint(v1) & cm1) | (__float_as_uint(v0) & ~cm1);
-        const uint32_t hi = (__float_as_uint(v3) & cm1) | (__float_as_uint(v2) & ~cm1);
-        return __uint_as_float((hi & cm2) | (lo & ~cm2));
-    };
-    u32x4 win[kGuWin], gsz[kSzPacks];
-    uint32_t gent[kSzWin] = {};
+    const int ntp = (nt + kWin - 1) / kWin * kWin;
+    const int r0 = ((wave * (nrt / kEpl)) / kWaves) * kEpl, r1 = (((wave + 1) * (nrt / kEpl)) / kWaves) * kEpl;
+    const int ndw = r1 - r0;
+    // codes: [gate|up tiles (slice, ku)] then [down tiles (slice, rt)], 64 lanes x 16 B each; the wave's two runs:
+    const size_t gu_off = ((size_t)slice * U + u0) * 1024, dn_off = ((size_t)nslice * U + (size_t)slice * nrt + r0) * 1024;
+    // scale/zero: 16 B = the 4 row blocks' (s, z) of lane row r; [gate|up (slice, group)] then [down (group of I, rt)]
+    // (symmetric format: 16 B = the 4 row blocks' s of row r for two groups / two row tiles).  With one token all
+    // 16 A rows hold it, so every lane group ends up with the same sums: lane group c finishes row block c
+    // only and loads that block's entry itself.
+    const uint32_t ent_lane = (uint32_t)((SYM ? r * 8 : r * 4) + c) * (SYM ? 2u : 4u);
+    const size_t gent_off = ((size_t)slice * (G / kEpl) + u0 / (UPG * kEpl)) * 256;
+    const size_t dent_off = ((size_t)nslice * (G / kEpl) + (size_t)(slice / UPG) * (nrt / kEpl) + r0 / kEpl) * 256;
+
+    stage_x();
+    // sums of x per group: 16 threads each
+    for (int i = tid; i < G * 16; i += kThreads) {
+        constexpr int kPer = 2 * UPG;
+        const uint16_t *src = s_x + i * kPer;
+        float v = 0.f;
 #pragma unroll
-    for (int i = 0; i < kGuWin; ++i) win[i] = __builtin_nontemporal_load(stream_ptr(i));
-    if constexpr (kOwnGu) {
-#pragma unroll
-        for (int j = 0; j < kSzWin; ++j) gent[j] = gent_load(u0 / UPG + j);
-    } else {
-#pragma unroll
-        for (int pk = 0; pk < kSzPacks; ++pk) gsz[pk] = __builtin_nontemporal_load(gsz_ptr(u0 / UPG, pk));
+        for (int j = 0; j < kPer; ++j) v += __uint_as_float((uint32_t)src[j] << 16);
+        v = wave::row_sum(v);
+        if ((i & 15) == 0) s_xsum[i >> 4] = v;
     }
-    // the softmax of wave t's token (few experts), off the path to the first weight load: the
-    // selection compared the fp64 logits; the softmax values only have to be good to fp32, so they
-    // are computed in fp32 from the fp64 differences
-    if (E <= kLoneWaveTopk && wave < T && ok) {
-        const int t = wave;                      // T <= kWaves: one token per wave
-        const double mx = wave::max(sm_logit);
-        const float pe = lane < E ? expf((float)(sm_logit - mx)) : 0.f;
-        const float conf = pe / wave::sum(pe);
-        const bool sel = sm_rank < k;
-        const float sel_sum = wave::sum(sel ? conf : 0.f);
-        if (sel) {
-            s_conf[t * k + sm_rank] = conf;
-            s_w[t * k + sm_rank] = a.renorm ? conf / sel_sum : conf;
-        }
+
+    // ---- 4. wave 0 polls the slots (bounded) and selects the top-k
+    if (wave == 0) {
+        const bool got = poll_and_select(a, 0, s_logit, s_rank, s_ids, nullptr);
+        if (!got) give_up();                     // the call fails, and says so in the workspace
+        if (lane == 0) s_ok = got;
     }
-    // ---- 3b. the rows (tokens) of the item
-    if (tid == 0) s_cnt = 0;
-    if (tid < MT) s_hsum[tid] = 0.f;
     __syncthreads();
-    if (expert >= 0 && wave == 0) {     // rows of the item: assignments with this expert, ascending
-        int cnt = 0;
-        for (int base = 0; base < n; base += 64) {
-            const int aidx = base + lane;
-            const bool hit = aidx < n && s_ids[aidx] == expert;
-            const unsigned long long b = __ballot(hit);
-            if (hit) {
-                const int pos = cnt + __popcll(b & ((1ull << lane) - 1ull));
-                if (pos < MT) s_row_a[pos] = aidx;
+    const bool ok = s_ok != 0;
+    if (ok) {
+        // ---- 5. the first window of weight loads goes out at once
+        const int ex = __builtin_amdgcn_readfirstlane(s_ids[u]);
+        const char *qb = a.q + (size_t)ex * a.stride_q, *sz = a.sz + (size_t)ex * a.stride_sz;
+        const run_t gu_run = make_run(qb + gu_off, nt * 1024), dn_run = make_run(qb + dn_off, ndw * 1024);
+        const run_t gent_run = make_run(sz + gent_off, nt / (UPG * kEpl) * 256), dent_run = make_run(sz + dent_off, ndw / kEpl * 256);
+        auto entry = [&](run_t run, int t) {                 // of the run's t-th group or row tile
+            if constexpr (SYM) return run_load2(run, ent_lane + (uint32_t)((t >> 1) * 256 + (t & 1) * 8));
+            else return run_load4(run, ent_lane + (uint32_t)t * 256u);
+        };
+        auto scale_of = [](uint32_t e) { return (float)__builtin_bit_cast(_Float16, (uint16_t)(e & 0xffff)); };
+        auto zero_of = [](uint32_t e) { return SYM ? 136.f : (float)__builtin_bit_cast(_Float16, (uint16_t)(e >> 16)) + 128.f; };
+        const uint32_t cm1 = 0u - (uint32_t)(c & 1), cm2 = 0u - (uint32_t)(c >> 1);
+        auto of_my_block = [&](float v0, float v1, float v2, float v3) {   // v_c, chosen with bit masks
+            const uint32_t lo = (__float_as_uint(v1) & cm1) | (__float_as_uint(v0) & ~cm1);
+            const uint32_t hi = (__float_as_uint(v3) & cm1) | (__float_as_uint(v2) & ~cm1);
+            return __uint_as_float((hi & cm2) | (lo & ~cm2));
+        };
+        // (an entry goes out before the last tile of its group: loads return in order)
+        u32x4 win[kWin];
+        uint32_t gent[kSzWin], dpe[kWin];
+        {
+            const run_t first = nt > 0 ? gu_run : dn_run;
+#pragma unroll
+            for (int i = 0; i < kWin; ++i) {
+                win[i] = run_load16(first, lane_off + (uint32_t)i * 1024u);
+                if (i % UPG == UPG - 1) gent[i / UPG] = entry(gent_run, i / UPG);
             }
-            cnt += __popcll(b);
         }
-        if (lane == 0) s_cnt = cnt < MT ? cnt : MT;
-    }
-    __syncthreads();
-    const int cnt = __builtin_amdgcn_readfirstlane(s_cnt);
-    draw_ticket();
+        // the ticket goes out behind the first loads: they would wait for it (loads and returning atomics complete in
+        // order, and hundreds of tickets are drawn at about the same time)
+        if (wave == 0) first_ticket();
+        // the softmax, off the path to the first weight load
+        if (wave == 0) finish_softmax(a, s_logit, s_rank, s_conf, s_w);
 
-    if (expert >= 0 && cnt > 0) {
-        // A-operand row of this lane: token slot r (slots >= cnt repeat slot 0; their D rows are ignored)
-        auto lds_row = [&](int slot) { return s_row_a[slot] / k; };   // where the slot's x was staged
-        const uint16_t *xrow = s_x + lds_row(r < cnt ? r : 0) * xstride + c * 8;
-        // tokens whose results this lane holds in its D registers: slot 4c + i
-        int tok[NI];
-#pragma unroll
-        for (int i = 0; i < NI; ++i) {
-            const int slot = 4 * c + i;
-            tok[i] = lds_row(slot < cnt ? slot : 0);
-        }
-
-        float tot[4][NI];
+        // ---- 6. gate and up
+        const uint16_t *xrow = s_x + c * 8;
         f32x4 acc[4];
 #pragma unroll
-        for (int d = 0; d < 4; ++d) {
-            acc[d] = (f32x4){0.f, 0.f, 0.f, 0.f};
-#pragma unroll
-            for (int i = 0; i < NI; ++i) tot[d][i] = 0.f;
-        }
-        float tot1 = 0.f;
+        for (int d = 0; d < 4; ++d) acc[d] = (f32x4){0.f, 0.f, 0.f, 0.f};
+        float tot = 0.f;
         u32x4 xa = *reinterpret_cast<const u32x4 *>(xrow + (nt > 0 ? u0 : 0) * 32);
-        // one window of the gate/up part; kGuard: some of its tiles may lie past the wave's run (the
-        // padding of the last window) and are skipped.  Full windows carry no per-tile tests.
+        // one window; kGuard: some of its tiles may lie past the wave's run (the padding of the last window)
+        // and are skipped.  Full windows carry no per-tile tests.
         auto gu_window = [&](int base, auto guarded) {
             constexpr bool kGuard = decltype(guarded)::value;
-            u32x4 gsz_next[kSzPacks];                             // the next window's groups
-            uint32_t gent_next[kSzWin];
-            if constexpr (kOwnGu) {
+            const bool into_down = base + kWin >= ntp;
+            const run_t run = into_down ? dn_run : gu_run;
+            const uint32_t off = lane_off + (into_down ? 0u : (uint32_t)(base + kWin) * 1024u);
 #pragma unroll
-                for (int j = 0; j < kSzWin; ++j) gent_next[j] = gent_load((u0 + base) / UPG + kSzWin + j);
-            } else {
-#pragma unroll
-                for (int pk = 0; pk < kSzPacks; ++pk)
-                    gsz_next[pk] = __builtin_nontemporal_load(gsz_ptr((u0 + base) / UPG + kSzWin, pk));
-            }
-#pragma unroll
-            for (int i = 0; i < kGuWin; ++i) {
-                const int pz = base + i, ku = u0 + pz;
-                const u32x4 qv = win[i];
-                win[i] = __builtin_nontemporal_load(stream_ptr(pz + kGuWin));
+            for (int i = 0; i < kWin; ++i) {
+                const int ku = u0 + base + i;
+                // The tile's words are unpacked first, then the window slot is refilled, then come the products.  Left
+                // alone, the scheduler gathers the refills behind the whole window's arithmetic.
+                bf16x8 b0 = unpack8(win[i].x, uk), b1 = unpack8(win[i].y, uk), b2 = unpack8(win[i].z, uk), b3 = unpack8(win[i].w, uk);
+                compute_here(b0); compute_here(b1); compute_here(b2); compute_here(b3);
+                __builtin_amdgcn_sched_barrier(0);
+                win[i] = run_load16(run, off + (uint32_t)i * 1024u);
+                float sc = 0.f, zp = 0.f;
+                if (i % UPG == UPG - 1) {
+                    sc = scale_of(gent[i / UPG]);
+                    zp = zero_of(gent[i / UPG]);
+                    compute_here(sc); compute_here(zp);
+                    gent[i / UPG] = entry(gent_run, (base + kWin) / UPG + i / UPG);
+                }
+                __builtin_amdgcn_sched_barrier(0);
                 if (!kGuard || ku < u1) {
                     const u32x4 xn = *reinterpret_cast<const u32x4 *>(xrow + (ku + 1 < u1 ? ku + 1 : ku) * 32);
-                    acc[0] = mfma(xa, unpack8(qv.x, uk), acc[0]);
-                    acc[1] = mfma(xa, unpack8(qv.y, uk), acc[1]);
-                    acc[2] = mfma(xa, unpack8(qv.z, uk), acc[2]);
-                    acc[3] = mfma(xa, unpack8(qv.w, uk), acc[3]);
+                    acc[0] = mfma(xa, b0, acc[0]);
+                    acc[1] = mfma(xa, b1, acc[1]);
+                    acc[2] = mfma(xa, b2, acc[2]);
+                    acc[3] = mfma(xa, b3, acc[3]);
                     xa = xn;
                     if (i % UPG == UPG - 1) {                 // end of a group: scale / zero / offset
-                        const int gi = ku / UPG;
-                        float xs[NI];
+                        tot += sc * (of_my_block(acc[0][0], acc[1][0], acc[2][0], acc[3][0]) - zp * s_xsum[ku / UPG]);
 #pragma unroll
-                        for (int j = 0; j < NI; ++j) xs[j] = s_xsum[tok[j] * G + gi];
-                        if constexpr (kOwnGu) {
-                            const uint32_t ev = gent[i / UPG];
-                            const float sc = (float)__builtin_bit_cast(_Float16, (uint16_t)(ev & 0xffff));
-                            const float zp = SYM ? 136.f : (float)__builtin_bit_cast(_Float16, (uint16_t)(ev >> 16)) + 128.f;
-                            tot1 += sc * (of_my_block(acc[0][0], acc[1][0], acc[2][0], acc[3][0]) - zp * xs[0]);
-#pragma unroll
-                            for (int d = 0; d < 4; ++d) acc[d] = (f32x4){0.f, 0.f, 0.f, 0.f};
-                        } else {
-                            const GroupParams<SYM> gp = pick(gsz, i / UPG);
-#pragma unroll
-                            for (int d = 0; d < 4; ++d) {
-                                const float sc = gp.scale(d), zp = gp.zero128(d);
-#pragma unroll
-                                for (int j = 0; j < NI; ++j) tot[d][j] += sc * (acc[d][j] - zp * xs[j]);
-                                acc[d] = (f32x4){0.f, 0.f, 0.f, 0.f};
-                            }
-                        }
+                        for (int d = 0; d < 4; ++d) acc[d] = (f32x4){0.f, 0.f, 0.f, 0.f};
                     }
                 }
-            }
-            if constexpr (kOwnGu) {
-#pragma unroll
-                for (int j = 0; j < kSzWin; ++j) gent[j] = gent_next[j];
-            } else {
-#pragma unroll
-                for (int pk = 0; pk < kSzPacks; ++pk) gsz[pk] = gsz_next[pk];
             }
         };
         {
             int base = 0;
-            for (; base + kGuWin <= nt; base += kGuWin) gu_window(base, std::false_type{});
+            for (; base + kWin <= nt; base += kWin) gu_window(base, std::false_type{});
             if (base < ntp) gu_window(base, std::true_type{});
         }
-        // the window now holds this wave's first kGuWin down tiles; their scales follow
-        constexpr int kDPacks = (kGuWin + kPerPack - 1) / kPerPack;
-        auto dsz_ptr = [&](int first, int pk) {
-            const int rt = first / kEpl + 4 * pk + c;
-            const int last = rt_last / kEpl;
-            return szd + (size_t)(rt < last ? rt : last) * 16;
-        };
-        // With one or two tokens a lane's D registers hold ONE row block of every down tile (its
-        // lane group's, see below), so it needs one entry per tile and loads that itself: no lane
-        // permutes and no selection among the four entries.
-        constexpr bool kOwnEntry = MT <= 2;
-        using entry_t = typename std::conditional<SYM, uint16_t, uint32_t>::type;
-        const entry_t *dent = reinterpret_cast<const entry_t *>(szb) + (size_t)nslice * G * 64 +
-                              (size_t)((slice * 32) / g) * nrt * 64 + (SYM ? r * 8 : r * 4) + c;
-        auto dent_load = [&](int rt) -> uint32_t {
-            const int t = rt < r1 ? rt : rt_last;
-            return (uint32_t)__builtin_nontemporal_load(dent + (SYM ? (t >> 1) * 128 + (t & 1) * 4 : t * 64));
-        };
-        u32x4 dsz[kDPacks];
-        uint32_t dpe[kGuWin] = {};
-        if constexpr (kOwnEntry) {
+        // the window now holds this wave's first down tiles; their entries follow
 #pragma unroll
-            for (int i = 0; i < kGuWin; ++i) dpe[i] = dent_load(r0 + i);
-        } else {
-#pragma unroll
-            for (int pk = 0; pk < kDPacks; ++pk) dsz[pk] = __builtin_nontemporal_load(dsz_ptr(r0, pk));
-        }
-        if constexpr (kRedOverX) __syncthreads();      // every wave has finished reading x
-        if constexpr (kOwnGu) {
-            s_red[wave][c][0][r] = tot1;
-        } else if (c < NC) {
-#pragma unroll
-            for (int d = 0; d < 4; ++d)
-#pragma unroll
-                for (int i = 0; i < NI; ++i) s_red[wave][d][i][c * 16 + r] = tot[d][i];
-        }
-        __syncthreads();
-        // h for (token slot, row): row blocks 0, 1 are gate rows 0-15, 16-31; 2, 3 the matching up rows
-        for (int idx = tid; idx < 2 * NI * NC * 16; idx += kThreads) {
-            const int lr = idx % (NC * 16), i = (idx / (NC * 16)) % NI, d = idx / (NC * 16 * NI);
-            const int slot = 4 * (lr >> 4) + i;
-            if (slot < cnt) {
-                float gsum = 0.f, usum = 0.f;
-#pragma unroll
-                for (int w = 0; w < kWaves; ++w) { gsum += s_red[w][d][i][lr]; usum += s_red[w][d + 2][i][lr]; }
-                const float h = gsum / (1.f + expf(-gsum)) * usum;
-                const uint16_t hi = f32_to_bf16_rne(h);
-                const uint16_t lo = f32_to_bf16_rne(h - __uint_as_float((uint32_t)hi << 16));
-                s_hhi[slot][d * 16 + (lr & 15)] = hi;
-                s_hlo[slot][d * 16 + (lr & 15)] = lo;
-                // sum of the represented h over the slice, per token: the 16 lanes of a
-                // (slot, row block) group add up in a fixed order, and the slot's two group
-                // sums meet in LDS (two addends commute, so the result does not depend on order)
-                float hs = __uint_as_float((uint32_t)hi << 16) + __uint_as_float((uint32_t)lo << 16);
-                hs = wave::row_sum(hs);
-                if ((lr & 15) == 0) atomicAdd(&s_hsum[slot], hs);
-            }
-        }
+        for (int i = 0; i < kWin; ++i) dpe[i] = entry(dent_run, i);
+        s_red[wave][lane] = tot;
+        if (wave == 0) second_ticket();
         __syncthreads();
 
-        // ---- down: this wave's row tiles, all H outputs of the slice's 32 columns.
-        // The hi and the lo part of h of a token slot are two A rows, so one MFMA yields both
-        // products.  With few token slots the 16 A rows have room for more: the tile's row block
-        // bl gets its own copy of the h rows at A rows bl * kRs .. (all other rows zero), and the
-        // kBpa MFMAs of kBpa row blocks accumulate into ONE D tile, whose lane group(s) bl then
-        // hold row block bl.  For one or two tokens that is the whole tile (64 outputs) in one D
-        // register pair per token: one 64-lane atomic per token and tile instead of four 16-lane ones.
-        constexpr int kBpa = MT <= 2 ? 4 : (MT == 4 ? 2 : 1);    // row blocks per accumulated D tile
-        constexpr int kRs = 16 / kBpa;                           // A rows per row block
-        constexpr int kLgb = 4 / kBpa;                           // lane groups per row block
-        constexpr int ND = MT < 2 ? 1 : 2;                       // token slots per lane
-        u32x4 hab[kBpa];
+        // ---- 7. h of the slice's 32 rows, in every wave: lanes 0-31 hold the gate rows, 32-63 the up rows
+        float hsum;
         {
-            const int within = r % kRs, slot = (within >> 1) < cnt ? (within >> 1) : 0;
-            const u32x4 hv = *reinterpret_cast<const u32x4 *>((within & 1) ? &s_hlo[slot][c * 8] : &s_hhi[slot][c * 8]);
-            const bool used = within < 2 * MT;
+            float v = 0.f;
 #pragma unroll
-            for (int bl = 0; bl < kBpa; ++bl) {
-                const bool on = used && r / kRs == bl;
-                hab[bl] = (u32x4){on ? hv.x : 0u, on ? hv.y : 0u, on ? hv.z : 0u, on ? hv.w : 0u};
+            for (int w = 0; w < kWaves; ++w) v += s_red[w][lane];
+            const float up = __shfl_xor(v, 32);
+            const float h = v / (1.f + expf(-v)) * up;
+            const uint16_t hi = f32_to_bf16_rne(h);
+            const uint16_t lo = f32_to_bf16_rne(h - __uint_as_float((uint32_t)hi << 16));
+            if (lane < 32) { s_h[wave][0][lane] = hi; s_h[wave][1][lane] = lo; }
+            const float hs = __uint_as_float((uint32_t)hi << 16) + __uint_as_float((uint32_t)lo << 16);   // the represented h
+            hsum = wave::sum(lane < 32 ? hs : 0.f);
+            __builtin_amdgcn_wave_barrier();
+        }
+        const float rw = s_w[u];
+
+        // ---- 8. down: this wave's row tiles, all H outputs of the slice's 32 columns.  A rows 4 bl, 4 bl + 1
+        // hold h and its remainder for row block bl of the tile (all other rows zero), and the four MFMAs
+        // of a tile accumulate into ONE D tile whose lane group bl then holds row block bl: the tile's 64 outputs
+        // in one register pair, one 64-lane atomic per tile.
+        u32x4 ha[4];
+        {
+            const u32x4 hv = *reinterpret_cast<const u32x4 *>(&s_h[wave][r & 1][c * 8]);
+#pragma unroll
+            for (int bl = 0; bl < 4; ++bl) {
+                const bool on = (r & 3) < 2 && (r >> 2) == bl;
+                ha[bl] = (u32x4){on ? hv.x : 0u, on ? hv.y : 0u, on ? hv.z : 0u, on ? hv.w : 0u};
             }
         }
-        const int my_bl = c / kLgb;                              // the row block this lane's D registers hold
-        float hsum[ND], rwd[ND];
-        int tokd[ND];
-        bool live[ND];
-#pragma unroll
-        for (int i = 0; i < ND; ++i) {
-            const int t = 2 * (c % kLgb) + i;
-            const int slot = t < cnt ? t : 0;
-            const int arow = s_row_a[slot];
-            live[i] = t < cnt;
-            hsum[i] = s_hsum[slot];
-            tokd[i] = arow / k;
-            rwd[i] = s_w[arow];
-        }
-        // one pass over the window: kReload: the slot is refilled with the tile kGuWin further on
-        // (clamped, unconditional); the last pass refills nothing
+        // one pass over the window; kReload: the slot is refilled with the tile kWin further on; the last pass
+        // refills nothing
         auto down_pass = [&](int j0, auto reload) {
             constexpr bool kReload = decltype(reload)::value;
-            u32x4 dsz_next[kDPacks];
-            if (kReload && !kOwnEntry) {
 #pragma unroll
-                for (int pk = 0; pk < kDPacks; ++pk)
-                    dsz_next[pk] = __builtin_nontemporal_load(dsz_ptr(r0 + j0 + kGuWin, pk));
-            }
-#pragma unroll
-            for (int i = 0; i < kGuWin; ++i) {
+            for (int i = 0; i < kWin; ++i) {
                 const int rt = r0 + j0 + i;
-                const u32x4 qv = win[i];
-                const uint32_t ev = dpe[i];
-                if (kReload) {
-                    const int rtn = rt + kGuWin;
-                    win[i] = __builtin_nontemporal_load(tile_ptr(dn0 + (rtn < r1 ? rtn : rt_last)));
-                    if constexpr (kOwnEntry) dpe[i] = dent_load(rtn);
+                float sc = scale_of(dpe[i]), zp = zero_of(dpe[i]);
+                bf16x8 b0 = unpack8(win[i].x, uk), b1 = unpack8(win[i].y, uk), b2 = unpack8(win[i].z, uk), b3 = unpack8(win[i].w, uk);
+                if constexpr (kReload) {
+                    compute_here(b0); compute_here(b1); compute_here(b2); compute_here(b3);
+                    compute_here(sc); compute_here(zp);
+                    __builtin_amdgcn_sched_barrier(0);
+                    win[i] = run_load16(dn_run, lane_off + (uint32_t)(j0 + kWin + i) * 1024u);
+                    dpe[i] = entry(dent_run, j0 + kWin + i);
+                    __builtin_amdgcn_sched_barrier(0);
                 }
                 if (rt < r1) {
-                    GroupParams<SYM> gp;
-                    if constexpr (!kOwnEntry) gp = pick(dsz, i);
-                    const uint32_t qw[4] = {qv.x, qv.y, qv.z, qv.w};
-#pragma unroll
-                    for (int q = 0; q < 4 / kBpa; ++q) {
-                        f32x4 o = (f32x4){0.f, 0.f, 0.f, 0.f};
-#pragma unroll
-                        for (int bl = 0; bl < kBpa; ++bl) o = mfma(hab[bl], unpack8(qw[q * kBpa + bl], uk), o);
-                        const int d = q * kBpa + my_bl;          // this lane's row block of the tile
-                        float sc, zp;
-                        if constexpr (kOwnEntry) {
-                            sc = (float)__builtin_bit_cast(_Float16, (uint16_t)(ev & 0xffff));
-                            zp = SYM ? 136.f : (float)__builtin_bit_cast(_Float16, (uint16_t)(ev >> 16)) + 128.f;
-                        } else {
-                            sc = gp.scale(d);
-                            zp = gp.zero128(d);
-                        }
-#pragma unroll
-                        for (int j = 0; j < ND; ++j) {
-                            if (live[j]) {
-                                const float val = sc * ((o[2 * j] + o[2 * j + 1]) - zp * hsum[j]) * rwd[j];
-                                __hip_atomic_fetch_add(&a.y[(size_t)tokd[j] * H + rt * 64 + d * 16 + r], val,
-                                                       __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-                            }
-                        }
-                    }
+                    f32x4 o = (f32x4){0.f, 0.f, 0.f, 0.f};
+                    o = mfma(ha[0], b0, o);
+                    o = mfma(ha[1], b1, o);
+                    o = mfma(ha[2], b2, o);
+                    o = mfma(ha[3], b3, o);
+                    const float val = sc * ((o[0] + o[1]) - zp * hsum) * rw;
+                    __hip_atomic_fetch_add(&a.y[rt * 64 + lane], val, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
                 }
             }
-            if (kReload && !kOwnEntry) {
-#pragma unroll
-                for (int pk = 0; pk < kDPacks; ++pk) dsz[pk] = dsz_next[pk];
-            }
         };
-        const int ndw = r1 - r0;
         int j0 = 0;
-        for (; j0 + kGuWin < ndw; j0 += kGuWin) down_pass(j0, std::true_type{});
+        for (; j0 + kWin < ndw; j0 += kWin) down_pass(j0, std::true_type{});
         down_pass(j0, std::false_type{});
+    } else if (wave == 0) {
+        first_ticket();
+        second_ticket();
     }
 
-    // ---- 4. last ticket: every workgroup has its logits, put the workspace back to idle
-    if (tid == kThreads - 64) {
-        const uint32_t grp = blockIdx.x % kTicketGroups;
-        const uint32_t members = (gridDim.x - grp + kTicketGroups - 1) / kTicketGroups;
-        int last = 0;
-        if (ticket == members - 1) {                   // last of its group: second level
-            const uint32_t ngroups = gridDim.x < (uint32_t)kTicketGroups ? gridDim.x : (uint32_t)kTicketGroups;
-            const uint32_t t2 = __hip_atomic_fetch_add(a.tickets + kTicketGroups, 1u, __ATOMIC_RELAXED,
-                                                       __HIP_MEMORY_SCOPE_AGENT);
-            last = t2 == ngroups - 1;
-        }
-        s_flag = last;
-    }
-    __syncthreads();
-    if (s_flag) {
-        for (int i = tid; i < T * E * kReplicas; i += kThreads)
-            __hip_atomic_store(a.slots + (size_t)(i / (T * E)) * a.replica_stride + 2 * (size_t)(i % (T * E)) + 1, 0ull,
-                               __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-        if (tid <= kTicketGroups) __hip_atomic_store(a.tickets + tid, 0u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-    }
-
-    // ---- 5. workgroup 0 reports the routing (and the plan the shared-expert kernels read)
-    if (blockIdx.x != 0) return;
-    for (int i = tid; i < n; i += kThreads) {
-        a.ids_out[i] = ok ? s_ids[i] : -1;
-        if (a.conf_out) a.conf_out[i] = ok ? s_conf[i] : 0.f;
-    }
-    if (a.S > 0) {
-        Plan *p = a.plan;
-        for (int i = tid; i < n; i += kThreads) { p->perm[i] = i; p->row_live[i] = 0; }
-        for (int i = tid; i < a.S * T; i += kThreads) {
-            p->row_tok[n + i] = i % T;
-            p->row_w[n + i] = 1.f;
-            p->row_live[n + i] = 1;
-        }
-        if (tid < a.S) {
-            p->act_expert[tid] = E + tid;
-            p->act_off[tid] = n + tid * T;
-            p->act_cnt[tid] = T;
-            p->act_w0[tid] = (uint64_t)(a.shared + (size_t)tid * a.shared_stride);
-            p->act_w1[tid] = 0;
-        }
-        if (tid == 0) { p->n_active = a.S; p->n_routed_active = 0; p->n_rows = n + a.S * T; p->n_missing = 0; }
+    // ---- 9. workgroup 0 reports the routing
+    if (wave == 0) reset_if_last();
+    if (b != 0) return;
+    if (!ok) { if (tid < k) { a.ids_out[tid] = -1; if (a.conf_out) a.conf_out[tid] = 0.f; } return; }
+    if (tid < k) {
+        a.ids_out[tid] = s_ids[tid];
+        if (a.conf_out) a.conf_out[tid] = s_conf[tid];
     }
 }
 
-// dynamic LDS: the bf16 copy of the item's token rows (padded) and their per-group sums; with 8
-// rows the partial gate/up sums (8 waves x 4 row blocks x 4 x 32 floats) later take the same place;
-// routed call with many experts: fp64 logits and ranks behind them
-size_t slice_dynamic_lds(int MT, int H, int g, int E, bool routed)
-{
-    size_t lds = (size_t)MT * (H + 8) * 2 + (size_t)MT * (H / g) * 4;
-    if (routed && E > kLoneWaveTopk) lds = ((lds + 7) & ~(size_t)7) + (size_t)MT * E * 12;
-    if (MT >= 8 && lds < (size_t)kWaves * 4 * 4 * 32 * 4) lds = (size_t)kWaves * 4 * 4 * 32 * 4;
-    return lds;
-}
+// dynamic LDS: x, the fp64 logits and the ranks, the sums of x per group
+size_t slice_dynamic_lds(int H, int g, int E) { return (size_t)H * 2 + (size_t)E * 12 + (size_t)(H / g) * 4; }
 
-template <int MT, bool SYM>
-void launch_slice_t(const uint16_t *x, const FusedArgs &a, hipStream_t st, int n_groups_of_slices)
+template <bool SYM, bool SHARED, typename F>
+void slice_kernel(int g, F go)
 {
-    const dim3 grid(n_groups_of_slices * (a.I / 32)), block(kThreads);
-    const size_t lds = slice_dynamic_lds(MT, a.H, a.g, a.E, true);
-    if (a.g == 32) launch_with_lds(draft_fused_kernel<MT, 1, SYM>, grid, block, lds, st, x, a);
-    else if (a.g == 64) launch_with_lds(draft_fused_kernel<MT, 2, SYM>, grid, block, lds, st, x, a);
-    else launch_with_lds(draft_fused_kernel<MT, 4, SYM>, grid, block, lds, st, x, a);
+    if (g == 32) go(draft_fused_kernel<1, SYM, SHARED>);
+    else if (g == 64) go(draft_fused_kernel<2, SYM, SHARED>);
+    else go(draft_fused_kernel<4, SYM, SHARED>);
+}
+template <typename F>
+void slice_kernel(const Shape &s, const DraftFusedArgs &d, F go)
+{
+    if (d.symmetric) { if (s.S > 0) slice_kernel<true, true>(s.g, go); else slice_kernel<true, false>(s.g, go); }
+    else { if (s.S > 0) slice_kernel<false, true>(s.g, go); else slice_kernel<false, false>(s.g, go); }
 }
 
 }  // namespace
 
-// one token: router inside the launch, one workgroup per (selected expert, slice)
+// one token: router inside the launch, one workgroup per (selected expert, slice) and per 16 rows of
+// every shared expert
 void launch_draft_one_token(const Shape &s, const DraftFusedArgs &d, hipStream_t st)
 {
     const FusedArgs a = fused_args(s, d);
-    const uint16_t *x = (const uint16_t *)d.x;
-    const int experts = a.E < a.k ? a.E : a.k;
-    if (d.symmetric) launch_slice_t<1, true>(x, a, st, experts);
-    else launch_slice_t<1, false>(x, a, st, experts);
+    const int grid = a.k * (a.I / 32) + a.S * (a.I / 16);
+    const size_t lds = slice_dynamic_lds(a.H, a.g, a.E);
+    slice_kernel(s, d, [&](auto kernel) {
+        launch_with_lds(kernel, dim3(grid), dim3(kThreads), lds, st, (const uint16_t *)d.x, a);
+    });
 }
 
 int draft_one_token_resident(const Shape &s, const DraftFusedArgs &d, int n_cu)
 {
-    const size_t lds = slice_dynamic_lds(1, s.H, s.g, s.E, true);
     int per = 0;
-    auto ask = [&](auto kernel) { per = resident_per_cu(kernel, kThreads, lds); };
-    if (d.symmetric) {
-        if (s.g == 32) ask(draft_fused_kernel<1, 1, true>);
-        else if (s.g == 64) ask(draft_fused_kernel<1, 2, true>);
-        else ask(draft_fused_kernel<1, 4, true>);
-    } else {
-        if (s.g == 32) ask(draft_fused_kernel<1, 1, false>);
-        else if (s.g == 64) ask(draft_fused_kernel<1, 2, false>);
-        else ask(draft_fused_kernel<1, 4, false>);
-    }
+    slice_kernel(s, d, [&](auto kernel) { per = resident_per_cu(kernel, kThreads, slice_dynamic_lds(s.H, s.g, s.E)); });
     return per * n_cu;
 }
 
 bool draft_one_token_fits(const Shape &s)
 {
-    return slice_dynamic_lds(1, s.H, s.g, s.E, true) <= (size_t)(160 - 20) * 1024;
+    return slice_dynamic_lds(s.H, s.g, s.E) <= (size_t)(160 - 20) * 1024;
 }
 
 }  // namespace moespeq

@@ -117,13 +117,13 @@ struct DraftFusedArgs {
     float *y; int32_t *ids_out; float *conf_out;
     Plan *plan; const void *shared; size_t shared_stride;
 };
-// n_cu: compute units of the device (the launch is persistent, at most one workgroup per unit)
-void launch_draft_fused(const Shape &s, const DraftFusedArgs &a, int n_cu, hipStream_t st);
+// slots: what draft_resident_slots returned for the call (more than one token: the persistent grid)
+void launch_draft_fused(const Shape &s, const DraftFusedArgs &a, int slots, hipStream_t st);
 // whether the x copy and the entry buffers of a call with `tokens` tokens (1-8) fit into LDS
 bool draft_fits(const Shape &s, int tokens, bool symmetric);
-// whether the workgroups of the call's launch that reduce the router rows are all resident at once
-// (occupancy of the kernel the call will run x compute units)
-bool draft_producers_resident(const Shape &s, const DraftFusedArgs &a, int n_cu);
+// How many workgroups of the call's launch the device (n_cu compute units) holds at once; 0 if the ones that
+// reduce the router rows would not all be running while the others wait for them
+int draft_resident_slots(const Shape &s, const DraftFusedArgs &a, int n_cu);
 // draft_slice.hip: the call with ONE token (router inside the launch), one workgroup per
 // (expert, slice) work item
 void launch_draft_one_token(const Shape &s, const DraftFusedArgs &a, hipStream_t st);

@@ -74,6 +74,7 @@ __device__ inline T all(T v, Op op) {
 __device__ inline float sum(float v) { return all(v, [](float a, float b) { return a + b; }); }
 __device__ inline double sum(double v) { return all(v, [](double a, double b) { return a + b; }); }
 __device__ inline double max(double v) { return all(v, [](double a, double b) { return fmax(a, b); }); }
+__device__ inline int max(int v) { return all(v, [](int a, int b) { return a > b ? a : b; }); }
 __device__ inline float row_sum(float v) { return row_all(v, [](float a, float b) { return a + b; }); }
 
 

@@ -1,0 +1,70 @@
+"""The draft call's own router and its shared experts at their edges.
+
+Selection: expert counts around the 64-expert words, k up to E, logits that are equal, that differ
+only below fp32 and that are -inf; ids against the oracle, exactly.  Shared experts of a one-token
+call: hidden sizes with fewer k-steps or row tiles than waves, with a ragged last window and with more
+than one window of down tiles; y against the oracle."""
+import numpy as np
+import pytest
+import torch
+
+import synth
+from oracle import oracle as orc
+from synth.configs import LayerConfig
+from tests.common import oracle_arrays, oracle_draft, rel_err
+from tests.gpu_common import TOL_DRAFT, say, to_np, tokens_with_clear_routing
+
+pytestmark = pytest.mark.gpu
+
+from paper_2511_14102_amd import binding as B          # noqa: E402
+from paper_2511_14102_amd.harness import DeviceLayer   # noqa: E402
+
+
+@pytest.mark.parametrize("E,k", [(1, 1), (8, 8), (63, 3), (65, 16), (128, 8), (129, 5), (256, 16)])
+def test_selection_edges(E, k):
+    cfg = LayerConfig(71, "sel%d" % E, 64, E, 64, k, 32, 0, 1)
+    ctx = B.Context(0)
+    L = synth.make_layer(cfg, 0)
+    rng = np.random.default_rng(E)
+    # integer logits from a narrow range: many exact ties; half the experts sit at 2^30, where fp32
+    # cannot tell neighbouring integers apart
+    router = rng.integers(-1, 2, (E, 64)).astype(np.float32)
+    router[:, 0] = 2.0 ** 15 * rng.integers(0, 2, E)
+    L["router"] = torch.from_numpy(router).to(torch.bfloat16)
+    x = rng.integers(-1, 2, (8, 64)).astype(np.float32)
+    x[:, 0] = 2.0 ** 15
+    x[7] = 0.0                                             # all logits equal
+    x = torch.from_numpy(x).to(torch.bfloat16)
+    bias = np.zeros(E, np.float32)
+    bias[rng.permutation(E)[: E // 2]] = -np.inf
+    for b in (None, bias):
+        L["router_bias"] = None if b is None else torch.from_numpy(b)
+        D = DeviceLayer(ctx, cfg, L, max_tokens=8, verify=False)
+        A = oracle_arrays(L)
+        ids, _, conf, _ = orc.route(orc.bits(x), A["router"], A["bias"], k, True)
+        for T in (1, 3, min(8, 128 // k)):
+            say("selection E", E, "k", k, "T", T, "bias" if b is not None else "")
+            xs = x[8 - T:]
+            r = D.draft(xs.cuda())
+            torch.cuda.synchronize()
+            assert np.array_equal(to_np(r["ids"]), ids[8 - T:])
+            np.testing.assert_allclose(to_np(r["conf"]), conf[8 - T:], rtol=2e-6, atol=1e-30)
+    ctx.close()
+
+
+@pytest.mark.parametrize("H,I,g,S", [(64, 64, 32, 1), (192, 128, 64, 4), (320, 192, 32, 2), (2304, 128, 128, 1), (1088, 320, 64, 3)])
+def test_one_token_with_shared_experts(H, I, g, S):
+    cfg = LayerConfig(72, "sh%d" % H, H, 6, I, 2, g, S, 1)
+    ctx = B.Context(0)
+    L = synth.make_layer(cfg, 0)
+    A = oracle_arrays(L)
+    D = DeviceLayer(ctx, cfg, L, max_tokens=2, verify=False)
+    x = tokens_with_clear_routing(cfg, A, 3, step=4)
+    ref = oracle_draft(A, x)
+    for t in range(3):
+        say("shared H", H, "I", I, "g", g, "S", S, "token", t)
+        r = D.draft(x[t:t + 1].cuda())
+        torch.cuda.synchronize()
+        assert np.array_equal(to_np(r["ids"]), ref["ids"][t:t + 1])
+        assert rel_err(to_np(r["y"]), ref["y"][t:t + 1]) <= TOL_DRAFT
+    ctx.close()
