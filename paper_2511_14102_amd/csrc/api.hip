@@ -361,6 +361,7 @@ static int enqueue_draft(moe_ctx *ctx, const moe_layer_desc *desc, const void *x
     a.q = routed->q; a.sz = routed->sz;
     a.stride_q = routed->expert_stride_q; a.stride_sz = routed->expert_stride_sz;
     a.symmetric = routed->symmetric ? 1 : 0;
+    a.shared_inside = draft_shared_inside(s, ctx->n_cu) ? 1 : 0;
     a.slots = (unsigned long long *)(ws + L.slots);
     a.replica_stride = L.slot_replica_bytes / 8;
     a.tickets = (uint32_t *)(ws + L.tickets);
@@ -372,16 +373,16 @@ static int enqueue_draft(moe_ctx *ctx, const moe_layer_desc *desc, const void *x
     // running while the others wait for them
     const int slots = draft_resident_slots(s, a, ctx->n_cu);
     if (slots == 0) return MOE_ERR_INVALID_ARG;
-    const bool own_launches = s.S > 0 && T > 1;     // a one-token call runs its shared experts in its one launch
+    const bool own_launches = s.S > 0 && !a.shared_inside;
     if (!timed) {
-        launch_draft_fused(s, a, slots, st);
+        launch_draft_fused(s, a, ctx->n_cu, slots, st);
         if (own_launches) {
             launch_bf16_gateup(s, plan, 0, s.S, x, ws + L.hb, ws + L.hb_lo, st);
             launch_bf16_down_add(s, plan, 0, s.S, ws + L.hb, ws + L.hb_lo, y, st);
         }
         return hip_status(ctx, hipGetLastError());
     }
-    { ProfScope p(ctx, MOE_KERNEL_DRAFT_FUSED, st); launch_draft_fused(s, a, slots, st); }
+    { ProfScope p(ctx, MOE_KERNEL_DRAFT_FUSED, st); launch_draft_fused(s, a, ctx->n_cu, slots, st); }
     if (own_launches) {   // shared experts stay 16-bit in the draft model (section 3.4.2)
         { ProfScope p(ctx, MOE_KERNEL_BF16_GATEUP, st);
           launch_bf16_gateup(s, plan, 0, s.S, x, ws + L.hb, ws + L.hb_lo, st); }

@@ -353,33 +353,26 @@ __device__ inline void finish_softmax(const FusedArgs &a, const double *logit, c
     }
 }
 
-// Scale and zero of the four row blocks d of one (group, lane row): the asymmetric format keeps
-// a 4-byte {s, z} entry per d, the symmetric one (z = 8) only the four fp16 scales.
-template <bool SYM> struct GroupParams;
-template <> struct GroupParams<false> {
-    uint32_t w[4];
-    // entry d; d may differ from lane to lane, so the choice is made with bit masks (a chain of
-    // conditional expressions on a lane-varying d was compiled into divergent branches)
-    __device__ uint32_t entry(int d) const {
-        const uint32_t m1 = 0u - (uint32_t)(d & 1), m2 = 0u - (uint32_t)((d >> 1) & 1);
-        const uint32_t lo = (w[1] & m1) | (w[0] & ~m1), hi = (w[3] & m1) | (w[2] & ~m1);
-        return (hi & m2) | (lo & ~m2);
+// The plan that the shared experts' own kernels read (one workgroup writes it)
+__device__ inline void write_shared_plan(const FusedArgs &a)
+{
+    Plan *p = a.plan;
+    const int tid = threadIdx.x, n = a.T * a.k;
+    for (int i = tid; i < n; i += blockDim.x) { p->perm[i] = i; p->row_live[i] = 0; }
+    for (int i = tid; i < a.S * a.T; i += blockDim.x) {
+        p->row_tok[n + i] = i % a.T;
+        p->row_w[n + i] = 1.f;
+        p->row_live[n + i] = 1;
     }
-    __device__ float scale(int d) const { return (float)__builtin_bit_cast(_Float16, (uint16_t)(entry(d) & 0xffff)); }
-    __device__ float zero128(int d) const {                   // z + 128
-        return (float)__builtin_bit_cast(_Float16, (uint16_t)(entry(d) >> 16)) + 128.f;
+    if (tid < a.S) {
+        p->act_expert[tid] = a.E + tid;
+        p->act_off[tid] = n + tid * a.T;
+        p->act_cnt[tid] = a.T;
+        p->act_w0[tid] = (uint64_t)(a.shared + (size_t)tid * a.shared_stride);
+        p->act_w1[tid] = 0;
     }
-};
-template <> struct GroupParams<true> {
-    uint32_t w[2];
-    __device__ float scale(int d) const {
-        const uint32_t m2 = 0u - (uint32_t)((d >> 1) & 1);
-        const uint32_t e = (w[1] & m2) | (w[0] & ~m2);
-        return (float)__builtin_bit_cast(_Float16, (uint16_t)(e >> (16 * (d & 1))));
-    }
-    __device__ float zero128(int) const { return 136.f; }
-};
-
+    if (tid == 0) { p->n_active = a.S; p->n_routed_active = 0; p->n_rows = n + a.S * a.T; p->n_missing = 0; }
+}
 
 // Launch with `lds` bytes of dynamic LDS; beyond 48 KiB the limit has to be raised once per kernel.
 template <typename K>

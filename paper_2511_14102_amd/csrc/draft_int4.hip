@@ -1,6 +1,6 @@
-// Draft-pass kernel for calls of two to eight tokens: router, top-k and the SwiGLU FFN of the
+// Draft-pass kernel for calls of two to eight tokens, and of one token with many work items: router, top-k and the SwiGLU FFN of the
 // selected experts on group-wise int4 weights, dequantisation fused into the matrix products, ONE
-// launch per call (gfx950).  (A call with one token runs the kernel of draft_slice.hip.)
+// launch per call (gfx950).  (Other calls with one token run the kernel of draft_slice.hip.)
 //
 // Paper section 3.4.3: the draft pass has to avoid the launch and utilisation losses of
 // per-expert small GEMMs (one monolithic expert-fused kernel); section 4.1.3: 4-bit weights in
@@ -18,11 +18,14 @@
 // that is read through a rolling window of tiles in flight, so the loads of an item's successor
 // are under way while the item's own sums are reduced, h is formed and its down tiles are
 // multiplied.  With several tokens a call has many items (every distinct expert of the call,
-// I / 32 slices each) and this wins clearly over one workgroup per item (phi shape, 4 tokens:
-// 56 against 76 us, 8 tokens: 90 against 144 us; qwen3 shape, 8 tokens: 60 against 103 us).
-// With one token there are about one and a half items per compute unit on the phi shape, a
-// workgroup's stream is one or two items long, and there is nothing for it to overlap: 26.3 us
-// against 25.5 us for one workgroup per item, the same to 3 % on the other shapes.
+// I / 32 slices each) and this wins clearly over one workgroup per item.
+//
+// Bound: the weight stream at one workgroup per compute unit (phi shape, 4 tokens: 202 MB in 52.7 us, of which
+// the start takes about 5 us), and with few tokens per expert also the vector work per tile.  What the stream
+// needs is that its loads stay in flight: a window slot is unpacked and refilled at once, addresses are
+// buffer offsets without clamps, and nothing under a branch counts on the vector memory counter (an empty slot's
+// atomics go out of range instead).  us per call before these: phi 4 tokens 57.5, mixtral 3 tokens, symmetric
+// 87 (now 83), qwen3 8 tokens 60.6 (now 40).
 //
 // Cross-workgroup protocol (one bounded wait, no cache flushes):
 //   1. router row e is reduced by workgroup e (mod grid), which first clears its share of y
@@ -45,19 +48,14 @@ namespace moespeq {
 
 namespace {
 
-// MT: token capacity of the launch (2, 4 or 8; the code also serves 1); UPG: 32-code units per
+// MT: token capacity of the launch (2, 4 or 8); UPG: 32-code units per
 // group (g / 32); SYM: symmetric format (scale blobs, z = 8); NW: waves of the workgroup; kWin:
-// tiles a wave keeps in flight.  (Measured: a tile costs about 70 instructions, most of them in
-// dependent chains, and one wave issues such an instruction every 8 to 16 clocks, the scalar ones
-// through the one scalar unit all waves of a compute unit share; 16 waves with windows of 4 tiles
-// were no faster than 8 waves with windows of 8.)
+// tiles a wave keeps in flight.
 template <int MT, int UPG, bool SYM, int NW, int kWin>
-__global__ __launch_bounds__(NW * 64, (NW / 4) * (MT <= 2 ? 2 : 1))
+__global__ __launch_bounds__(NW * 64, NW / 4)
 void draft_stream_kernel(const uint16_t *__restrict__ xin, const FusedArgs a)
 {
     constexpr int kWaves = NW, kThreads = NW * 64;   // (these names shadow the 8-wave constants of the prefill kernel)
-    constexpr int NI = MT < 4 ? MT : 4;          // D rows (tokens) per lane that can be valid
-    constexpr int NC = MT > 4 ? 2 : 1;           // lane groups (of 16) whose D rows can be valid
     __shared__ double s_part[kWaves];
     __shared__ int32_t s_ids[MOE_MAX_ASSIGN];
     __shared__ float s_w[MOE_MAX_ASSIGN];
@@ -70,9 +68,7 @@ void draft_stream_kernel(const uint16_t *__restrict__ xin, const FusedArgs a)
     __shared__ float s_hsum[2][MT];
     __shared__ int32_t s_flag;
     __shared__ int32_t s_list[MOE_MAX_EXPERTS];  // the call's distinct experts, ascending
-    // partial gate/up sums [wave][row block][token in lane group][lane]
-    typedef float red_t[4][NI][NC * 16];
-    __shared__ red_t s_red[kWaves];
+    __shared__ float s_red[kWaves][MT][64];      // partial gate/up sums [wave][token slot][row]
     __shared__ __attribute__((aligned(16))) uint16_t s_hhi[MT][32], s_hlo[MT][32];
     extern __shared__ __attribute__((aligned(16))) unsigned char s_dyn[];   // x copy, its group sums, routing scratch
 
@@ -160,37 +156,21 @@ void draft_stream_kernel(const uint16_t *__restrict__ xin, const FusedArgs a)
         it.gu_run = qb + ((size_t)it.slice * U + u0) * 1024;
         it.dn_run = qb + ((size_t)nslice * U + (size_t)it.slice * nrt + r0) * 1024;
     };
-    constexpr bool kOwnGu = MT == 1;       // one token: lane group c finishes row block c only and needs its entry only
-    constexpr bool kOwnEntry = MT <= 2;    // down: a lane's D registers hold one row block of every tile
-
-    // Addresses of one window of this wave's stream: kWin positions from q0 (a multiple of kWin,
-    // counted from the start of item `cur`; positions from Lw on belong to `nxt`).  Parts are
-    // padded to whole windows, so a window lies inside one part: `base` is its first tile and
-    // `room` the number of tiles up to the part's end; tile i of the window is tile min(i, room - 1)
-    // from base.  EVERY load of the stream is unconditional: past the end of a part it repeats the
-    // part's last tile, and past the last item (`more` false) the item's last tile (the compiler
-    // counts the loads in flight in program order; a load under a branch makes it wait for more of
-    // them than it needs, and a second copy of a loop body without the loads costs a full wait
-    // where the copies meet).  One address computation per window, not per tile: the scalar unit
-    // is shared by all waves of the compute unit.
-    struct Run { const char *base; int room; };
+    // One window of this wave's stream: kWin positions from q0 (a multiple of kWin, counted from the start of
+    // item `cur`; positions from Lw on belong to `nxt`).  Parts are padded to whole windows, so a window
+    // lies inside one part and is a run that ends with the part.  EVERY load of the stream is
+    // unconditional: past the end of a part, and past the last item (`more` false), it returns zeros and
+    // moves nothing (the compiler counts the loads in flight in program order; a load under a branch
+    // makes it wait for more of them than it needs, and a second copy of a loop body without the loads
+    // costs a full wait where the copies meet).
     auto window_run = [&](const Item &cur, const Item &nxt, bool more, int q0) {
         const bool wrap = q0 >= Lw;
         const int qq = wrap ? q0 - Lw : q0;
         const char *gu = wrap ? nxt.gu_run : cur.gu_run, *dn = wrap ? nxt.dn_run : cur.dn_run;
         const int j = qq - ntp;
-        Run w;
-        w.base = qq < ntp ? gu + (size_t)qq * 1024 : dn + (size_t)j * 1024;
-        w.room = qq < ntp ? nt - qq : ndw - j;
-        if (wrap && !more) {                                     // nothing follows: repeat the very last tile
-            w.base = ndw > 0 ? cur.dn_run + (size_t)(ndw - 1) * 1024 : cur.gu_run + (size_t)(nt > 0 ? nt - 1 : 0) * 1024;
-            w.room = 1;
-        }
-        return w;
-    };
-    auto tile_of = [&](const Run &w, int i) {
-        const int t = i < w.room ? i : w.room - 1;
-        return reinterpret_cast<const u32x4 *>(w.base + (size_t)t * 1024 + lane_off);
+        const char *base = qq < ntp ? gu + (size_t)qq * 1024 : dn + (size_t)j * 1024;
+        const int room = qq < ntp ? nt - qq : ndw - j;
+        return make_run(base, room > 0 && (!wrap || more) ? (uint32_t)room * 1024u : 0u);
     };
 
     // Scale / zero entries do not travel through registers: a wave copies the entries of its own
@@ -222,34 +202,24 @@ void draft_stream_kernel(const uint16_t *__restrict__ xin, const FusedArgs a)
         request_blocks(it.szb + ((size_t)nslice * (G / kEpl) + (size_t)((it.slice * 32) / g) * (nrt / kEpl) + r0 / kEpl) * 256,
                        ndl, s_ent_addr + eb_gu);
     };
-    // entries of block `unit` (counted from the wave's first), part 0 gate/up, 1 down; `odd`: the
-    // second group (row tile) of a pair in the symmetric format
-    auto own_entry = [&](int part, int unit, int odd) -> uint32_t {      // this lane's row block c of row r
+    // entry of row block d, row r in block `unit` (counted from the wave's first) of part 0 gate/up, 1 down;
+    // `odd`: the second group (row tile) of a pair in the symmetric format
+    auto entry = [&](int part, int unit, int odd, int d) -> uint32_t {
         const unsigned char *p = s_ent + part * eb_gu + unit * 256 + r * 16;
-        if constexpr (SYM) return *reinterpret_cast<const uint16_t *>(p + odd * 8 + c * 2);
-        else return *reinterpret_cast<const uint32_t *>(p + c * 4);
+        if constexpr (SYM) return *reinterpret_cast<const uint16_t *>(p + odd * 8 + d * 2);
+        else return *reinterpret_cast<const uint32_t *>(p + d * 4);
     };
-    auto row_entries = [&](int part, int unit, int odd) {                 // all four row blocks of row r
-        const unsigned char *p = s_ent + part * eb_gu + unit * 256 + r * 16;
-        GroupParams<SYM> gp;
-        if constexpr (SYM) {
-            const uint2 v = *reinterpret_cast<const uint2 *>(p + odd * 8);
-            gp.w[0] = v.x; gp.w[1] = v.y;
-        } else {
-            const u32x4 v = *reinterpret_cast<const u32x4 *>(p);
-            gp.w[0] = v.x; gp.w[1] = v.y; gp.w[2] = v.z; gp.w[3] = v.w;
-        }
-        return gp;
-    };
-    // Orders what follows behind the arrival of a tile: `word` comes from the tile's registers, so
-    // the wait for the tile's load precedes this point, and no memory access is moved across it.
-    auto behind_tile = [](uint32_t word) { asm volatile("" : : "v"(word) : "memory"); };
+    auto scale_of = [](uint32_t e) { return (float)__builtin_bit_cast(_Float16, (uint16_t)(e & 0xffff)); };
+    auto zero_of = [](uint32_t e) { return SYM ? 136.f : (float)__builtin_bit_cast(_Float16, (uint16_t)(e >> 16)) + 128.f; };
+    // Orders what follows behind the arrival of a tile: `b` is made from the tile's words, so the wait for the
+    // tile's load precedes this point, and no memory access is moved across it.
+    auto behind_tile = [](const bf16x8 &b) { asm volatile("" : : "v"(__builtin_bit_cast(u32x4, b)) : "memory"); };
     const uint32_t cm1 = 0u - (uint32_t)(c & 1), cm2 = 0u - (uint32_t)(c >> 1);
-    auto of_my_block = [&](float v0, float v1, float v2, float v3) {   // v_c, chosen with bit masks
-        const uint32_t lo = (__float_as_uint(v1) & cm1) | (__float_as_uint(v0) & ~cm1);
-        const uint32_t hi = (__float_as_uint(v3) & cm1) | (__float_as_uint(v2) & ~cm1);
-        return __uint_as_float((hi & cm2) | (lo & ~cm2));
-    };
+    auto mix = [](float a, float b, uint32_t m) { return __uint_as_float((__float_as_uint(b) & m) | (__float_as_uint(a) & ~m)); };
+    auto pick4 = [&](float v0, float v1, float v2, float v3) { return mix(mix(v0, v1, cm1), mix(v2, v3, cm1), cm2); };   // v_c
+    auto pick2 = [&](float v0, float v1) { return mix(v0, v1, cm2); };                                                // v_(c / 2)
+    constexpr uint32_t kPastY = 0x80000000u;     // beyond any y, also with a tile's offset added
+    const run_t y_run = make_run((const char *)a.y, (uint32_t)(T * H) * 4u);
     // rows (token slots) of an item: the assignments with its expert, ascending; one wave
     auto item_rows = [&](int expert, int par) {
         int cnt = 0;
@@ -323,9 +293,9 @@ void draft_stream_kernel(const uint16_t *__restrict__ xin, const FusedArgs a)
         u32x4 win[kWin];
         if (Lw > 0) {
             request_gu_entries(cur);
-            const Run w0 = window_run(cur, nxt, it_begin + 1 < it_end, 0);
+            const run_t w0 = window_run(cur, nxt, it_begin + 1 < it_end, 0);
 #pragma unroll
-            for (int i = 0; i < kWin; ++i) win[i] = __builtin_nontemporal_load(tile_of(w0, i));
+            for (int i = 0; i < kWin; ++i) win[i] = run_load16(w0, lane_off + (uint32_t)i * 1024u);
         }
         if (wave == kWaves - 1) item_rows(cur.expert, 0);
         softmax();
@@ -335,46 +305,44 @@ void draft_stream_kernel(const uint16_t *__restrict__ xin, const FusedArgs a)
             const int par = (it - it_begin) & 1;
             const bool last = it + 1 == it_end;
             const int cnt = __builtin_amdgcn_readfirstlane(s_cnt[par]);
-            // A-operand row of this lane: token slot r (slots >= cnt repeat slot 0; their D rows are ignored)
-            auto lds_row = [&](int slot) { return s_row_a[par][slot] / k; };   // where the slot's x was staged
-            const uint16_t *xrow = s_x + lds_row(r < cnt ? r : 0) * xstride + c * 8;
-            // tokens whose results this lane holds in its D registers: slot 4c + i
-            int tok[NI];
+            auto token_of = [&](int slot) { return s_row_a[par][slot < cnt ? slot : 0] / k; };   // (slots >= cnt repeat slot 0)
+            if (Lw > 0) request_dn_entries(cur);
+            {
+                // A row m is token slot m % MT, so lane group c holds, for each of its slots, the sums of all four row
+                // blocks, and finishes only some of them: with up to four slots block c of every slot, with eight
+                // slots blocks 2 (c / 2), 2 (c / 2) + 1 of slots 4 (c % 2) ...  (Every lane group finishing all four blocks
+                // of its own slots, most of them empty, was twice the vector work.)
+                constexpr int NI = MT < 4 ? MT : 4;                  // slots per lane
+                constexpr int NB = MT > 4 ? 2 : 1;                   // row blocks per lane
+                const int slot0 = MT > 4 ? 4 * (c & 1) : 0, block0 = MT > 4 ? 2 * (c >> 1) : c;
+                const uint16_t *xrow = s_x + token_of(r % MT) * xstride + c * 8;
+                const float *xs_of[NI];
 #pragma unroll
-            for (int i = 0; i < NI; ++i) {
-                const int slot = 4 * c + i;
-                tok[i] = lds_row(slot < cnt ? slot : 0);
-            }
-            float tot[4][NI];
-            f32x4 acc[4];
+                for (int i = 0; i < NI; ++i) xs_of[i] = s_xsum + token_of(slot0 + i) * G;
+                float tot[NB][NI];
+                f32x4 acc[4];
 #pragma unroll
-            for (int d = 0; d < 4; ++d) {
-                acc[d] = (f32x4){0.f, 0.f, 0.f, 0.f};
+                for (int d = 0; d < 4; ++d) acc[d] = (f32x4){0.f, 0.f, 0.f, 0.f};
 #pragma unroll
-                for (int i = 0; i < NI; ++i) tot[d][i] = 0.f;
-            }
-            float tot1 = 0.f;
-            if (Lw > 0) {
-                request_dn_entries(cur);
+                for (int bb = 0; bb < NB; ++bb)
+#pragma unroll
+                    for (int i = 0; i < NI; ++i) tot[bb][i] = 0.f;
                 u32x4 xa = *reinterpret_cast<const u32x4 *>(xrow + (nt > 0 ? u0 : 0) * 32);
-                // one window of the gate/up part; kGuard: some of its tiles may lie past the wave's
-                // run (the padding of the last window) and are skipped.  Full windows carry no
-                // per-tile tests.
+                // one window; kGuard: some of its tiles may lie past the wave's run (the padding of the last window)
+                // and are skipped.  Full windows carry no per-tile tests.
                 auto gu_window = [&](int base, auto guarded) {
                     constexpr bool kGuard = decltype(guarded)::value;
-                    const Run wr = window_run(cur, nxt, !last, base + kWin);
+                    const run_t wr = window_run(cur, nxt, !last, base + kWin);
 #pragma unroll
                     for (int i = 0; i < kWin; ++i) {
-                        const int pz = base + i, ku = u0 + pz;
-                        const u32x4 qv = win[i];
-                        // The tile's four words are unpacked first, then the window slot is refilled
-                        // (into the registers the words just left: a refill issued earlier would need
-                        // other registers and a copy of them, with a full wait, at the loop's head),
-                        // then the products.  Left alone, the scheduler gathers the eight refills
-                        // behind the whole window's arithmetic.
-                        const bf16x8 b0 = unpack8(qv.x, uk), b1 = unpack8(qv.y, uk), b2 = unpack8(qv.z, uk), b3 = unpack8(qv.w, uk);
+                        const int ku = u0 + base + i;
+                        // The tile's four words are unpacked first, then the window slot is refilled (into the
+                        // registers the words just left), then come the products.  Left alone, the scheduler gathers
+                        // the refills behind the whole window's arithmetic.
+                        bf16x8 b0 = unpack8(win[i].x, uk), b1 = unpack8(win[i].y, uk), b2 = unpack8(win[i].z, uk), b3 = unpack8(win[i].w, uk);
+                        compute_here(b0); compute_here(b1); compute_here(b2); compute_here(b3);
                         __builtin_amdgcn_sched_barrier(0);
-                        win[i] = __builtin_nontemporal_load(tile_of(wr, i));
+                        win[i] = run_load16(wr, lane_off + (uint32_t)i * 1024u);
                         __builtin_amdgcn_sched_barrier(0);
                         if (!kGuard || ku < u1) {
                             const u32x4 xn = *reinterpret_cast<const u32x4 *>(xrow + (ku + 1 < u1 ? ku + 1 : ku) * 32);
@@ -385,70 +353,52 @@ void draft_stream_kernel(const uint16_t *__restrict__ xin, const FusedArgs a)
                             xa = xn;
                             if (i % UPG == UPG - 1) {                 // end of a group: scale / zero / offset
                                 const int gi = ku / UPG;
-                                float xs[NI];
+                                behind_tile(b0);
 #pragma unroll
-                                for (int j = 0; j < NI; ++j) xs[j] = s_xsum[tok[j] * G + gi];
-                                behind_tile(qv.x);
-                                if constexpr (kOwnGu) {
-                                    const uint32_t ev = own_entry(0, (gi - g0) / kEpl, gi & 1);
-                                    const float sc = (float)__builtin_bit_cast(_Float16, (uint16_t)(ev & 0xffff));
-                                    const float zp = SYM ? 136.f : (float)__builtin_bit_cast(_Float16, (uint16_t)(ev >> 16)) + 128.f;
-                                    tot1 += sc * (of_my_block(acc[0][0], acc[1][0], acc[2][0], acc[3][0]) - zp * xs[0]);
+                                for (int bb = 0; bb < NB; ++bb) {
+                                    const uint32_t ev = entry(0, (gi - g0) / kEpl, gi & 1, block0 + bb);
+                                    const float sc = scale_of(ev), zp = zero_of(ev);
 #pragma unroll
-                                    for (int d = 0; d < 4; ++d) acc[d] = (f32x4){0.f, 0.f, 0.f, 0.f};
-                                } else {
-                                    const GroupParams<SYM> gp = row_entries(0, (gi - g0) / kEpl, gi & 1);
-#pragma unroll
-                                    for (int d = 0; d < 4; ++d) {
-                                        const float sc = gp.scale(d), zp = gp.zero128(d);
-#pragma unroll
-                                        for (int j = 0; j < NI; ++j) tot[d][j] += sc * (acc[d][j] - zp * xs[j]);
-                                        acc[d] = (f32x4){0.f, 0.f, 0.f, 0.f};
+                                    for (int j = 0; j < NI; ++j) {
+                                        const float v = MT > 4 ? pick2(acc[bb][j], acc[bb + 2][j]) : pick4(acc[0][j], acc[1][j], acc[2][j], acc[3][j]);
+                                        tot[bb][j] += sc * (v - zp * xs_of[j][gi]);
                                     }
                                 }
+#pragma unroll
+                                for (int d = 0; d < 4; ++d) acc[d] = (f32x4){0.f, 0.f, 0.f, 0.f};
                             }
                         }
                     }
                 };
-                {
-                    int base = 0;
-                    for (; base + kWin <= nt; base += kWin) gu_window(base, std::false_type{});
-                    if (base < ntp) gu_window(base, std::true_type{});
-                }
-                // the window now holds this wave's first down tiles (or, for a wave without down
-                // tiles, the successor's first gate/up tiles)
-            }
-            if constexpr (kOwnGu) {
-                s_red[wave][c][0][r] = tot1;
-            } else if (c < NC) {
+                int base = 0;
+                for (; base + kWin <= nt; base += kWin) gu_window(base, std::false_type{});
+                if (base < ntp) gu_window(base, std::true_type{});
+                // the window now holds this wave's first down tiles (or, for a wave without down tiles, the
+                // successor's first gate/up tiles)
 #pragma unroll
-                for (int d = 0; d < 4; ++d)
+                for (int bb = 0; bb < NB; ++bb)
 #pragma unroll
-                    for (int i = 0; i < NI; ++i) s_red[wave][d][i][c * 16 + r] = tot[d][i];
+                    for (int i = 0; i < NI; ++i) s_red[wave][slot0 + i][(block0 + bb) * 16 + r] = tot[bb][i];
             }
             __syncthreads();
-            // h for (token slot, row): row blocks 0, 1 are gate rows 0-15, 16-31; 2, 3 the matching up rows
-            for (int idx = tid; idx < 2 * NI * NC * 16; idx += kThreads) {
-                const int lr = idx % (NC * 16), i = (idx / (NC * 16)) % NI, d = idx / (NC * 16 * NI);
-                const int slot = 4 * (lr >> 4) + i;
-                if (slot < cnt) {
-                    float gsum = 0.f, usum = 0.f;
+            // h for (token slot, row): rows 0-31 of the sums are gate rows, 32-63 the matching up rows
+            if (tid < 32 * cnt) {
+                const int slot = tid >> 5, row = tid & 31;
+                float gsum = 0.f, usum = 0.f;
 #pragma unroll
-                    for (int w = 0; w < kWaves; ++w) { gsum += s_red[w][d][i][lr]; usum += s_red[w][d + 2][i][lr]; }
-                    const float h = gsum / (1.f + expf(-gsum)) * usum;
-                    const uint16_t hi = f32_to_bf16_rne(h);
-                    const uint16_t lo = f32_to_bf16_rne(h - __uint_as_float((uint32_t)hi << 16));
-                    s_hhi[slot][d * 16 + (lr & 15)] = hi;
-                    s_hlo[slot][d * 16 + (lr & 15)] = lo;
-                    // sum of the represented h over the slice, per token: the 16 lanes of a
-                    // (slot, row block) group add up in a fixed order, and the slot's two group
-                    // sums meet in LDS (two addends commute, so the result does not depend on order)
-                    float hs = __uint_as_float((uint32_t)hi << 16) + __uint_as_float((uint32_t)lo << 16);
-                    hs = wave::row_sum(hs);
-                    if ((lr & 15) == 0) atomicAdd(&s_hsum[par][slot], hs);
-                }
+                for (int w = 0; w < kWaves; ++w) { gsum += s_red[w][slot][row]; usum += s_red[w][slot][row + 32]; }
+                const float h = gsum / (1.f + expf(-gsum)) * usum;
+                const uint16_t hi = f32_to_bf16_rne(h);
+                const uint16_t lo = f32_to_bf16_rne(h - __uint_as_float((uint32_t)hi << 16));
+                s_hhi[slot][row] = hi;
+                s_hlo[slot][row] = lo;
+                // sum of the represented h over the slice, per token: 16 lanes add up in a fixed order, and the
+                // slot's two sums meet in LDS (two addends commute, so the result does not depend on order)
+                float hs = __uint_as_float((uint32_t)hi << 16) + __uint_as_float((uint32_t)lo << 16);
+                hs = wave::row_sum(hs);
+                if ((row & 15) == 0) atomicAdd(&s_hsum[par][slot], hs);
             }
-            // the last wave (it has no part in the sums above) sets up the successor's rows and
+            // the last wave (it has the smallest part, if any, in the sums above) sets up the successor's rows and
             // clears the successor's h sums; the other copy of both is still being read
             if (wave == kWaves - 1) {
                 if (it == it_begin) second_ticket();
@@ -458,90 +408,85 @@ void draft_stream_kernel(const uint16_t *__restrict__ xin, const FusedArgs a)
             __syncthreads();
 
             // ---- down: this wave's row tiles, all H outputs of the slice's 32 columns.
-            // The hi and the lo part of h of a token slot are two A rows, so one MFMA yields both
-            // products.  With few token slots the 16 A rows have room for more: the tile's row block
-            // bl gets its own copy of the h rows at A rows bl * kRs .. (all other rows zero), and the
-            // kBpa MFMAs of kBpa row blocks accumulate into ONE D tile, whose lane group(s) bl then
-            // hold row block bl.  For one or two tokens that is the whole tile (64 outputs) in one D
-            // register pair per token: one 64-lane atomic per token and tile instead of four 16-lane ones.
-            constexpr int kBpa = MT <= 2 ? 4 : (MT == 4 ? 2 : 1);    // row blocks per accumulated D tile
-            constexpr int kRs = 16 / kBpa;                           // A rows per row block
-            constexpr int kLgb = 4 / kBpa;                           // lane groups per row block
-            constexpr int ND = MT < 2 ? 1 : 2;                       // token slots per lane
+            // The hi and the lo part of h of a token slot are two A rows, so one MFMA yields both products.  The 16 A
+            // rows have room for more: the tile's row block bl gets its own copy of the h rows at A rows
+            // bl * kRs .. (all other rows zero), and the kBpa MFMAs of kBpa row blocks accumulate into ONE D
+            // tile, whose lane group(s) bl then hold row block bl.  Two slots take four row blocks: the whole
+            // tile (64 outputs) in one D register pair per slot, one 64-lane atomic per slot and tile.  Most items
+            // have one or two tokens: those are always done, slots 2-3 and 4-7 (two row blocks at a time) only
+            // where the item has them.
             if (Lw > 0 && !last) request_gu_entries(nxt);
             if (Lw > 0 && ndw > 0) {
-                u32x4 hab[kBpa];
-                {
-                    const int within = r % kRs, slot = (within >> 1) < cnt ? (within >> 1) : 0;
-                    const u32x4 hv = *reinterpret_cast<const u32x4 *>((within & 1) ? &s_hlo[slot][c * 8] : &s_hhi[slot][c * 8]);
-                    const bool used = within < 2 * MT;
+                auto h_rows = [&](int first, auto bpa_c, u32x4 *hab) {
+                    constexpr int kBpa = decltype(bpa_c)::value, kRs = 16 / kBpa;
+                    const int within = r % kRs, slot = first + (within >> 1);
+                    const bool used = kBpa == 4 ? within < 4 : true;
+                    const u32x4 hv = *reinterpret_cast<const u32x4 *>((within & 1) ? &s_hlo[slot & (MT - 1)][c * 8] : &s_hhi[slot & (MT - 1)][c * 8]);
 #pragma unroll
                     for (int bl = 0; bl < kBpa; ++bl) {
-                        const bool on = used && r / kRs == bl;
+                        const bool on = used && slot < cnt && r / kRs == bl;
                         hab[bl] = (u32x4){on ? hv.x : 0u, on ? hv.y : 0u, on ? hv.z : 0u, on ? hv.w : 0u};
                     }
-                }
-                const int my_bl = c / kLgb;                              // the row block this lane's D registers hold
-                float hsum[ND], rwd[ND];
-                int tokd[ND];
-                bool live[ND];
+                };
+                // what the lane's two slots need: their sums of h, weights, and offsets in y.  An empty slot's outputs go
+                // past the end of y, where an addition is dropped: no branch, so that the compiler can count
+                // the atomics between the loads (it counts none under a branch, and each wait for a tile then also
+                // waits for tiles requested behind it).
+                struct Out { float hsum[2], w[2]; uint32_t off[2]; };
+                auto outs = [&](int slot0, int block) {
+                    Out o;
 #pragma unroll
-                for (int i = 0; i < ND; ++i) {
-                    const int t = 2 * (c % kLgb) + i;
-                    const int slot = t < cnt ? t : 0;
-                    const int arow = s_row_a[par][slot];
-                    live[i] = t < cnt;
-                    hsum[i] = s_hsum[par][slot];
-                    tokd[i] = arow / k;
-                    rwd[i] = s_w[arow];
-                }
-                // one pass over the window; every slot is refilled with the stream's tile kWin further
-                // on (clamped, unconditional), which after this item's last down tile is the
-                // successor's first gate/up tile
-                auto down_pass = [&](int j0) {
-                    const Run wr = window_run(cur, nxt, !last, ntp + j0 + kWin);
+                    for (int i = 0; i < 2; ++i) {
+                        const int t = slot0 + i, slot = t < cnt ? t : 0;
+                        const int arow = s_row_a[par][slot];
+                        o.hsum[i] = s_hsum[par][slot];
+                        o.w[i] = s_w[arow];
+                        o.off[i] = t < cnt ? (uint32_t)((arow / k) * H + block * 16 + r) * 4u : kPastY;
+                    }
+                    return o;
+                };
+                constexpr std::integral_constant<int, 4> four{};
+                constexpr std::integral_constant<int, 2> two{};
+                u32x4 ha[4], hb[MT > 2 ? 4 : 1], hc[MT > 4 ? 2 : 1];
+                const Out oa = outs(0, c);
+                Out ob, oc;
+                h_rows(0, four, ha);
+                if constexpr (MT > 2) { h_rows(2, four, hb); ob = outs(2, c); }
+                if constexpr (MT > 4) { h_rows(4, two, hc); oc = outs(4 + 2 * (c & 1), c >> 1); }
+                auto add = [&](const Out &o, f32x4 d, uint32_t ev, uint32_t toff) {
+                    const float sc = scale_of(ev), zp = zero_of(ev);
+#pragma unroll
+                    for (int j = 0; j < 2; ++j)
+                        __builtin_amdgcn_raw_ptr_buffer_atomic_fadd_f32(sc * ((d[2 * j] + d[2 * j + 1]) - zp * o.hsum[j]) * o.w[j],
+                                                                        y_run, (int)(o.off[j] + toff), 0, 0);
+                };
+                for (int j0 = 0; j0 < ndw; j0 += kWin) {
+                    const run_t wr = window_run(cur, nxt, !last, ntp + j0 + kWin);
 #pragma unroll
                     for (int i = 0; i < kWin; ++i) {
-                        const int rt = r0 + j0 + i;
-                        const u32x4 qv = win[i];
-                        bf16x8 b[4];
-                        b[0] = unpack8(qv.x, uk); b[1] = unpack8(qv.y, uk); b[2] = unpack8(qv.z, uk); b[3] = unpack8(qv.w, uk);
+                        const int rt = r0 + j0 + i, rt_in = rt < r1 ? rt : r1 - 1;
+                        bf16x8 b[4] = {unpack8(win[i].x, uk), unpack8(win[i].y, uk), unpack8(win[i].z, uk), unpack8(win[i].w, uk)};
+                        compute_here(b[0]); compute_here(b[1]); compute_here(b[2]); compute_here(b[3]);
                         __builtin_amdgcn_sched_barrier(0);
-                        win[i] = __builtin_nontemporal_load(tile_of(wr, i));
+                        win[i] = run_load16(wr, lane_off + (uint32_t)i * 1024u);
                         __builtin_amdgcn_sched_barrier(0);
-                        if (rt < r1) {
-                            behind_tile(qv.x);
-                            uint32_t ev = 0;
-                            GroupParams<SYM> gp;
-                            if constexpr (kOwnEntry) ev = own_entry(1, (rt - r0) / kEpl, rt & 1);
-                            else gp = row_entries(1, (rt - r0) / kEpl, rt & 1);
+                        behind_tile(b[0]);
+                        const uint32_t toff = rt < r1 ? (uint32_t)rt * 256u : kPastY / 2;    // (padding: dropped as well)
+                        const f32x4 zero = {0.f, 0.f, 0.f, 0.f};
+                        const uint32_t ev = entry(1, (rt_in - r0) / kEpl, rt_in & 1, c);
+                        add(oa, mfma(ha[3], b[3], mfma(ha[2], b[2], mfma(ha[1], b[1], mfma(ha[0], b[0], zero)))), ev, toff);
+                        if (MT > 2 && cnt > 2)
+                            add(ob, mfma(hb[3], b[3], mfma(hb[2], b[2], mfma(hb[1], b[1], mfma(hb[0], b[0], zero)))), ev, toff);
+                        if constexpr (MT > 4) {
+                            if (cnt > 4) {
 #pragma unroll
-                            for (int q = 0; q < 4 / kBpa; ++q) {
-                                f32x4 o = (f32x4){0.f, 0.f, 0.f, 0.f};
-#pragma unroll
-                                for (int bl = 0; bl < kBpa; ++bl) o = mfma(hab[bl], b[q * kBpa + bl], o);
-                                const int d = q * kBpa + my_bl;          // this lane's row block of the tile
-                                float sc, zp;
-                                if constexpr (kOwnEntry) {
-                                    sc = (float)__builtin_bit_cast(_Float16, (uint16_t)(ev & 0xffff));
-                                    zp = SYM ? 136.f : (float)__builtin_bit_cast(_Float16, (uint16_t)(ev >> 16)) + 128.f;
-                                } else {
-                                    sc = gp.scale(d);
-                                    zp = gp.zero128(d);
-                                }
-#pragma unroll
-                                for (int j = 0; j < ND; ++j) {
-                                    if (live[j]) {
-                                        const float val = sc * ((o[2 * j] + o[2 * j + 1]) - zp * hsum[j]) * rwd[j];
-                                        __hip_atomic_fetch_add(&a.y[(size_t)tokd[j] * H + rt * 64 + d * 16 + r], val,
-                                                               __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-                                    }
-                                }
+                                for (int q = 0; q < 2; ++q)
+                                    add(oc, mfma(hc[1], b[2 * q + 1], mfma(hc[0], b[2 * q], zero)),
+                                        entry(1, (rt_in - r0) / kEpl, rt_in & 1, 2 * q + (c >> 1)), toff + q * 128u);
                             }
                         }
                     }
-                };
-                for (int j0 = 0; j0 < ndw; j0 += kWin) down_pass(j0);
+                }
             }
             cur = nxt;
             if (it + 2 < it_end) { item_after(nxt, cur); item_addr(nxt, nth_expert(nxt.u)); }
@@ -561,23 +506,7 @@ void draft_stream_kernel(const uint16_t *__restrict__ xin, const FusedArgs a)
         a.ids_out[i] = ok ? s_ids[i] : -1;
         if (a.conf_out) a.conf_out[i] = ok ? s_conf[i] : 0.f;
     }
-    if (a.S > 0) {
-        Plan *p = a.plan;
-        for (int i = tid; i < n; i += kThreads) { p->perm[i] = i; p->row_live[i] = 0; }
-        for (int i = tid; i < a.S * T; i += kThreads) {
-            p->row_tok[n + i] = i % T;
-            p->row_w[n + i] = 1.f;
-            p->row_live[n + i] = 1;
-        }
-        if (tid < a.S) {
-            p->act_expert[tid] = E + tid;
-            p->act_off[tid] = n + tid * T;
-            p->act_cnt[tid] = T;
-            p->act_w0[tid] = (uint64_t)(a.shared + (size_t)tid * a.shared_stride);
-            p->act_w1[tid] = 0;
-        }
-        if (tid == 0) { p->n_active = a.S; p->n_routed_active = 0; p->n_rows = n + a.S * T; p->n_missing = 0; }
-    }
+    if (a.S > 0) write_shared_plan(a);
 }
 
 __global__ __launch_bounds__(256)
@@ -621,20 +550,31 @@ void stream_read_kernel(const u32x4 *__restrict__ src, size_t tiles, uint32_t *s
     if (fold == 0x9E3779B9u) sink[0] = fold;
 }
 
-// waves per workgroup and window depth for a token capacity
-// Launch shape for a token capacity (two tokens: two workgroups may share a compute unit, which
-// needs 128 registers per wave; more tokens need more registers and own the unit).  Measured on
-// the phi shape, 2 tokens: 37.9 us against 40.7 us with 16 waves and windows of 4.
-constexpr int stream_waves(int) { return 8; }
-constexpr int stream_window(int) { return 8; }
-constexpr int kMaxPerCu = 2;
+constexpr int kStreamWaves = 8;
+
+// One workgroup per compute unit: two that share a unit are slower, also where they fit its registers (phi
+// shape, 2 tokens: 37.6 us against 41.6 with two, qwen3 19.2 / 20.6; 4 tokens, held to 128 registers: 52.7 / 60.4).
+constexpr int kMaxPerCu = 1;
+
+// Tiles a wave keeps in flight: eight, or four where padding the two parts of an item to whole windows of eight
+// would add more than a fifth to the stream's positions (an empty position is a load that is not in
+// flight).  8 against 4: phi shape (16 and 8 tiles per part and wave), 4 tokens 52.7 / 58.4 us; qwen3 shape (8
+// and 4), 8 tokens 44.7 / 39.9 us.  Windows of 12 and 16 only add padding (58.3 and 59.4 us on the phi shape).
+int stream_window(const Shape &s, bool sym)
+{
+    const int epl = sym ? 2 : 1;
+    const int nt = (s.H / s.g / epl + kStreamWaves - 1) / kStreamWaves * epl * (s.g / 32);
+    const int nd = (s.H / 64 / epl + kStreamWaves - 1) / kStreamWaves * epl;
+    auto positions = [&](int w) { return (nt + w - 1) / w * w + (nd + w - 1) / w * w; };
+    return positions(8) * 5 > positions(4) * 6 ? 4 : 8;
+}
 
 // dynamic LDS: the bf16 copy of x (padded rows), its per-group sums, the routing scratch (fp64
 // logits and ranks), and per wave the scale / zero entries of its groups and row tiles of one
 // item (whole KiB each)
 size_t draft_dynamic_lds(int MT, int H, int g, int E, bool sym, int entry_copies = 1)
 {
-    const int nw = stream_waves(MT);
+    const int nw = kStreamWaves;
     size_t lds = ((size_t)MT * (H + 8) * 2 + (size_t)MT * (H / g) * 4 + 7) & ~(size_t)7;
     lds += (size_t)MT * E * 12;
     lds = (lds + 15) & ~(size_t)15;
@@ -644,36 +584,36 @@ size_t draft_dynamic_lds(int MT, int H, int g, int E, bool sym, int entry_copies
     return lds;
 }
 
-template <int MT, bool SYM>
-void launch_stream_t(const uint16_t *x, const FusedArgs &a, long slots, hipStream_t st)
+// go(kernel, MT) with the instantiation for a call
+template <int MT, bool SYM, int KW, typename F>
+void stream_kernel_g(int g, F go)
 {
-    constexpr int NW = stream_waves(MT), KW = stream_window(MT);
-    // never more workgroups than there can be items
-    const int maxu = a.E < a.T * a.k ? a.E : a.T * a.k;
-    const long items = (long)maxu * (a.I / 32);
-    const dim3 grid((unsigned)(items < slots ? items : slots)), block(NW * 64);
-    const size_t lds = draft_dynamic_lds(MT, a.H, a.g, a.E, SYM);
-    if (a.g == 32) launch_with_lds(draft_stream_kernel<MT, 1, SYM, NW, KW>, grid, block, lds, st, x, a);
-    else if (a.g == 64) launch_with_lds(draft_stream_kernel<MT, 2, SYM, NW, KW>, grid, block, lds, st, x, a);
-    else launch_with_lds(draft_stream_kernel<MT, 4, SYM, NW, KW>, grid, block, lds, st, x, a);
+    if (g == 32) go(draft_stream_kernel<MT, 1, SYM, kStreamWaves, KW>, MT);
+    else if (g == 64) go(draft_stream_kernel<MT, 2, SYM, kStreamWaves, KW>, MT);
+    else go(draft_stream_kernel<MT, 4, SYM, kStreamWaves, KW>, MT);
+}
+template <bool SYM, int KW, typename F>
+void stream_kernel_t(const Shape &s, F go)
+{
+    if (s.T <= 2) stream_kernel_g<2, SYM, KW>(s.g, go);
+    else if (s.T <= 4) stream_kernel_g<4, SYM, KW>(s.g, go);
+    else stream_kernel_g<8, SYM, KW>(s.g, go);
+}
+template <typename F>
+void stream_kernel(const Shape &s, bool sym, F go)
+{
+    const bool deep = stream_window(s, sym) == 8;
+    if (sym) { if (deep) stream_kernel_t<true, 8>(s, go); else stream_kernel_t<true, 4>(s, go); }
+    else { if (deep) stream_kernel_t<false, 8>(s, go); else stream_kernel_t<false, 4>(s, go); }
 }
 
-template <bool SYM>
-void launch_stream(int T, const uint16_t *x, const FusedArgs &a, long slots, hipStream_t st)
+// One token through the persistent kernel: from two items per compute unit on, where the launch carries no shared
+// experts and the kernel's two copies of x fit LDS.  us per call, persistent / one workgroup per item: mixtral
+// (896 items) 43.9 / 46.5, the same with I = 9600 (600 items) 34.7 / 37.5, qwen3 with H = 1024, I = 2048 (512
+// items) 23.1 / 24.2; phi (400 items) 26.6 / 24.7.
+bool one_token_streams(const Shape &s, const DraftFusedArgs &d, int n_cu)
 {
-    if (T <= 2) launch_stream_t<2, SYM>(x, a, slots, st);
-    else if (T <= 4) launch_stream_t<4, SYM>(x, a, slots, st);
-    else launch_stream_t<8, SYM>(x, a, slots, st);
-}
-
-template <int MT, bool SYM>
-int stream_resident_per_cu(const Shape &s)
-{
-    constexpr int NW = stream_waves(MT), KW = stream_window(MT);
-    const size_t lds = draft_dynamic_lds(MT, s.H, s.g, s.E, SYM);
-    if (s.g == 32) return resident_per_cu(draft_stream_kernel<MT, 1, SYM, NW, KW>, NW * 64, lds);
-    if (s.g == 64) return resident_per_cu(draft_stream_kernel<MT, 2, SYM, NW, KW>, NW * 64, lds);
-    return resident_per_cu(draft_stream_kernel<MT, 4, SYM, NW, KW>, NW * 64, lds);
+    return s.k * (s.I / 32) >= 2 * n_cu && !d.shared_inside && draft_fits(s, 2, d.symmetric != 0);
 }
 
 }  // namespace
@@ -685,29 +625,29 @@ int draft_resident_slots(const Shape &s, const DraftFusedArgs &d, int n_cu)
 {
     const int maxu = s.E < s.T * s.k ? s.E : s.T * s.k;
     const long items = (long)maxu * (s.I / 32);
-    if (s.T == 1) {
+    if (s.T == 1 && !one_token_streams(s, d, n_cu)) {
         const long need = s.E < items ? s.E : items;
         const int slots = draft_one_token_resident(s, d, n_cu);
         return need <= slots ? slots : 0;
     }
-    const int MT = s.T <= 2 ? 2 : (s.T <= 4 ? 4 : 8);
     int per = 0;
-    if (d.symmetric) per = MT == 2 ? stream_resident_per_cu<2, true>(s) : (MT == 4 ? stream_resident_per_cu<4, true>(s) : stream_resident_per_cu<8, true>(s));
-    else per = MT == 2 ? stream_resident_per_cu<2, false>(s) : (MT == 4 ? stream_resident_per_cu<4, false>(s) : stream_resident_per_cu<8, false>(s));
+    stream_kernel(s, d.symmetric != 0, [&](auto kernel, int MT) {
+        per = resident_per_cu(kernel, kStreamWaves * 64, draft_dynamic_lds(MT, s.H, s.g, s.E, d.symmetric != 0));
+    });
     return (per < kMaxPerCu ? per : kMaxPerCu) * n_cu;
 }
 
-void launch_draft_fused(const Shape &s, const DraftFusedArgs &d, int slots, hipStream_t st)
+void launch_draft_fused(const Shape &s, const DraftFusedArgs &d, int n_cu, int slots, hipStream_t st)
 {
-    // One token: items are few (k I / 32, about one and a half per compute unit on the phi shape) and
-    // one workgroup per item is as fast or a little faster (phi 25.5 us against 26.3 us for the
-    // persistent launch, mixtral 49.7 / 50.6, qwen3 18.9 / 19.5); from two tokens on the persistent
-    // launch wins (4 tokens: 56 against 76 us, 8 tokens: 90 against 144 us).
-    if (s.T == 1) { launch_draft_one_token(s, d, st); return; }
+    if (s.T == 1 && !one_token_streams(s, d, n_cu)) { launch_draft_one_token(s, d, st); return; }
     const FusedArgs a = fused_args(s, d);
-    const uint16_t *x = (const uint16_t *)d.x;
-    if (d.symmetric) launch_stream<true>(s.T, x, a, slots, st);
-    else launch_stream<false>(s.T, x, a, slots, st);
+    // never more workgroups than there can be items
+    const int maxu = s.E < s.T * s.k ? s.E : s.T * s.k;
+    const long items = (long)maxu * (s.I / 32);
+    const dim3 grid((unsigned)(items < slots ? items : slots)), block(kStreamWaves * 64);
+    stream_kernel(s, d.symmetric != 0, [&](auto kernel, int MT) {
+        launch_with_lds(kernel, grid, block, draft_dynamic_lds(MT, s.H, s.g, s.E, d.symmetric != 0), st, (const uint16_t *)d.x, a);
+    });
 }
 
 bool draft_fits(const Shape &s, int tokens, bool sym)

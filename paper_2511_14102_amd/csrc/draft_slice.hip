@@ -1,7 +1,7 @@
 // Draft-pass kernel for a call with ONE token: router, top-k and the SwiGLU FFN of the selected
 // experts on group-wise int4 weights in one launch, one workgroup per work item (gfx950).
-// (Calls of two to eight tokens run the persistent kernel of draft_int4.hip, longer runs of
-// tokens the grouped contraction of draft_prefill.hip.)
+// (Calls with two or more items per compute unit, or two to eight tokens, run the persistent kernel of
+// draft_int4.hip, longer runs of tokens the grouped contraction of draft_prefill.hip.)
 //
 // Paper section 3.4.3 (one expert-fused kernel instead of per-expert small GEMMs), section 4.1.3
 // (4-bit weights in groups along the input dimension), section 3.3.1 (expert id and confidence
@@ -12,18 +12,21 @@
 // rows): its workgroup computes the 32 gate and 32 up pre-activations (K = H split over the 8
 // waves by groups), h = silu(gate) * up, and immediately multiplies h into the 32 matching
 // columns of the down projection for all H outputs, adding the partial outputs into y with
-// fp32 atomics.  With one token a call has k I / 32 items (400 on the phi shape), about one
-// and a half per compute unit: one workgroup per item, two resident per unit, was measured
-// as fast or a little faster here than a persistent launch (25.5 against 26.3 us), whose
-// continuous stream has nothing to overlap when it is only one or two items long.
+// fp32 atomics.  With one token a call has k I / 32 items (400 on the phi shape, about one and a half per
+// compute unit): up to two workgroups share a unit.  Below two items per unit a persistent launch, whose
+// stream would be one or two items long, has nothing to overlap (phi 24.4 us here, 26.6 persistent; qwen3 14.7 /
+// 16.2); from there on it is the faster one.
+//
+// Bound: a chain of round trips to memory up to the first weight load (x and router rows, exchange, selection:
+// about 3 us), then the weight stream (84 MB in 17 us on the phi shape) with one or two items per unit.
 #include "draft_common.h"
 
 namespace moespeq {
 
 namespace {
 
-// UPG: 32-code units per group (g / 32); SYM: symmetric format (scale blobs, z = 8); SHARED: the layer has
-// shared experts (a layer without them runs a smaller kernel: its start is a chain of code that runs once)
+// UPG: 32-code units per group (g / 32); SYM: symmetric format (scale blobs, z = 8); SHARED: the shared
+// experts run in this launch (without them the kernel is smaller: its start is a chain of code that runs once)
 template <int UPG, bool SYM, bool SHARED>
 __global__ __launch_bounds__(kThreads, 4)            // 4 waves per SIMD, two workgroups per compute unit
 void draft_fused_kernel(const uint16_t *__restrict__ xin, const FusedArgs a)
@@ -398,6 +401,7 @@ void draft_fused_kernel(const uint16_t *__restrict__ xin, const FusedArgs a)
     // ---- 9. workgroup 0 reports the routing
     if (wave == 0) reset_if_last();
     if (b != 0) return;
+    if (!SHARED && a.S > 0) write_shared_plan(a);
     if (!ok) { if (tid < k) { a.ids_out[tid] = -1; if (a.conf_out) a.conf_out[tid] = 0.f; } return; }
     if (tid < k) {
         a.ids_out[tid] = s_ids[tid];
@@ -418,18 +422,28 @@ void slice_kernel(int g, F go)
 template <typename F>
 void slice_kernel(const Shape &s, const DraftFusedArgs &d, F go)
 {
-    if (d.symmetric) { if (s.S > 0) slice_kernel<true, true>(s.g, go); else slice_kernel<true, false>(s.g, go); }
-    else { if (s.S > 0) slice_kernel<false, true>(s.g, go); else slice_kernel<false, false>(s.g, go); }
+    if (d.symmetric) { if (d.shared_inside) slice_kernel<true, true>(s.g, go); else slice_kernel<true, false>(s.g, go); }
+    else { if (d.shared_inside) slice_kernel<false, true>(s.g, go); else slice_kernel<false, false>(s.g, go); }
 }
 
 }  // namespace
+
+// Whether a one-token call runs its shared experts in its own launch: up to three 16-row items per compute unit, fewer
+// than one per 256 of H where that is more.  Beyond, items are many and short, a workgroup's start costs more
+// than two launches, and the bf16 kernels take them (S = 4, us per call inside / in their own launches: H = 640,
+// I = 2816 37.5 / 47.7, I = 8192 97.7 / 83; H = 2048, I = 1408 30.3 / 42.4, I = 8192 115 / 126).
+bool draft_shared_inside(const Shape &s, int n_cu)
+{
+    const long items = (long)s.S * (s.I / 16);
+    return s.T == 1 && s.S > 0 && (items <= 3L * n_cu || items < (long)n_cu * s.H / 256);
+}
 
 // one token: router inside the launch, one workgroup per (selected expert, slice) and per 16 rows of
 // every shared expert
 void launch_draft_one_token(const Shape &s, const DraftFusedArgs &d, hipStream_t st)
 {
     const FusedArgs a = fused_args(s, d);
-    const int grid = a.k * (a.I / 32) + a.S * (a.I / 16);
+    const int grid = a.k * (a.I / 32) + (d.shared_inside ? a.S * (a.I / 16) : 0);
     const size_t lds = slice_dynamic_lds(a.H, a.g, a.E);
     slice_kernel(s, d, [&](auto kernel) {
         launch_with_lds(kernel, dim3(grid), dim3(kThreads), lds, st, (const uint16_t *)d.x, a);

@@ -112,13 +112,14 @@ struct DraftFusedArgs {
     const void *x, *wr; const float *bias;
     const void *q, *sz; size_t stride_q, stride_sz;
     int symmetric;                     // sz holds scale blobs (z = 8)
+    int shared_inside;                 // the shared experts run in the call's launch
     unsigned long long *slots; size_t replica_stride; uint32_t *tickets;
     uint32_t *status; uint32_t spin_limit;
     float *y; int32_t *ids_out; float *conf_out;
     Plan *plan; const void *shared; size_t shared_stride;
 };
 // slots: what draft_resident_slots returned for the call (more than one token: the persistent grid)
-void launch_draft_fused(const Shape &s, const DraftFusedArgs &a, int slots, hipStream_t st);
+void launch_draft_fused(const Shape &s, const DraftFusedArgs &a, int n_cu, int slots, hipStream_t st);
 // whether the x copy and the entry buffers of a call with `tokens` tokens (1-8) fit into LDS
 bool draft_fits(const Shape &s, int tokens, bool symmetric);
 // How many workgroups of the call's launch the device (n_cu compute units) holds at once; 0 if the ones that
@@ -128,6 +129,7 @@ int draft_resident_slots(const Shape &s, const DraftFusedArgs &a, int n_cu);
 // (expert, slice) work item
 void launch_draft_one_token(const Shape &s, const DraftFusedArgs &a, hipStream_t st);
 bool draft_one_token_fits(const Shape &s);
+bool draft_shared_inside(const Shape &s, int n_cu);      // whether the call's launch runs the shared experts too
 int draft_one_token_resident(const Shape &s, const DraftFusedArgs &a, int n_cu);   // workgroups resident at once
 void launch_zero(void *p, size_t bytes, hipStream_t st);
 void launch_stream_read(const void *src, size_t bytes, int workgroups, void *sink, hipStream_t st);

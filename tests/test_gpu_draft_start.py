@@ -68,3 +68,26 @@ def test_one_token_with_shared_experts(H, I, g, S):
         assert np.array_equal(to_np(r["ids"]), ref["ids"][t:t + 1])
         assert rel_err(to_np(r["y"]), ref["y"][t:t + 1]) <= TOL_DRAFT
     ctx.close()
+
+
+@pytest.mark.parametrize("H,k,g,S", [(128, 2, 32, 0), (576, 2, 64, 0), (128, 2, 32, 2), (128, 1, 32, 4)])
+def test_one_token_with_many_items(H, k, g, S):
+    """I = 8192: 256 work items per selected expert (two experts: the persistent kernel runs the call), and
+    with two or more shared experts more 16-row items than the call's own launch takes."""
+    cfg = LayerConfig(73, "many%d" % H, H, 4, 8192, k, g, S, 1)
+    ctx = B.Context(0)
+    for symmetric in (False, True):
+        if symmetric and B.int4_expert_scale_bytes(B.LayerDesc.from_config(cfg)) == 0:
+            continue
+        L = synth.make_layer(cfg, 0, symmetric=symmetric)
+        A = oracle_arrays(L)
+        D = DeviceLayer(ctx, cfg, L, max_tokens=3, verify=False, symmetric=symmetric)
+        x = tokens_with_clear_routing(cfg, A, 3, step=6)
+        ref = oracle_draft(A, x)
+        for t0, t1 in ((0, 1), (1, 2), (0, 3)):
+            say("many items H", H, "S", S, "symmetric" if symmetric else "", "tokens", t0, t1)
+            r = D.draft(x[t0:t1].cuda())
+            torch.cuda.synchronize()
+            assert np.array_equal(to_np(r["ids"]), ref["ids"][t0:t1])
+            assert rel_err(to_np(r["y"]), ref["y"][t0:t1]) <= TOL_DRAFT
+    ctx.close()
