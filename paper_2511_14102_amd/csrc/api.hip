@@ -430,11 +430,11 @@ int moe_draft_layer_int4_noalloc(moe_ctx *ctx, const moe_layer_desc *desc,
     return enqueue_draft(ctx, desc, x, wr, bias, routed, shared, T, y, ids_out, conf_out, ws, L, st, false);
 }
 
-// workspace of a prefill call: routing weights, sorted assignment indices and slots [T k], the
-// item count (one 256-byte line), the items, the operand tiles of x and of h (two planes) with
+// workspace of a prefill call: routing weights and slots [T k], the experts' counts and lists, the
+// partial logits, the item count (one 256-byte line), the items, the operand tiles of x and of h (two planes) with
 // their group sums, a tile of zeros, and the per-slot outputs.
 struct PrefillLayout {
-    size_t w_all, sorted, slot_of, n_items, items, xt, x_sums, h_hi, h_lo, h_sums, zeros, obuf, total;
+    size_t w_all, count, list, parts, slot_of, n_items, items, xt, x_sums, h_hi, h_lo, h_sums, zeros, obuf, total;
     int max_items;
 };
 static PrefillLayout prefill_layout(const moe_layer_desc &d, int T)
@@ -447,7 +447,9 @@ static PrefillLayout prefill_layout(const moe_layer_desc &d, int T)
     const PrefillBuffers B = prefill_buffers(d, L.max_items);
     size_t o = 0;
     L.w_all = o;   o += align256(n * 4);
-    L.sorted = o;  o += align256(n * 4);
+    L.count = o;   o += align256((size_t)d.n_experts * 4);
+    L.list = o;    o += align256((size_t)d.n_experts * T * 4);
+    L.parts = o;   o += align256((size_t)prefill_logit_parts(make_shape(&d, T)) * T * d.n_experts * 8);
     L.slot_of = o; o += align256(n * 4);
     L.n_items = o; o += 256;
     L.items = o;   o += align256((size_t)L.max_items * sizeof(PrefillItem));
@@ -504,18 +506,23 @@ int moe_draft_prefill_int4(moe_ctx *ctx, const moe_layer_desc *desc,
     p.x = x; p.q = routed->q; p.sz = routed->sz;
     p.stride_q = routed->expert_stride_q; p.stride_sz = routed->expert_stride_sz;
     p.symmetric = routed->symmetric ? 1 : 0;
-    p.items = (const PrefillItem *)(ws + L.items); p.n_items = (const int32_t *)(ws + L.n_items);
-    p.sorted = (const int32_t *)(ws + L.sorted); p.slot_of = (const int32_t *)(ws + L.slot_of);
+    p.items = (PrefillItem *)(ws + L.items); p.n_items = (int32_t *)(ws + L.n_items);
+    p.count = (const int32_t *)(ws + L.count); p.list = (const int32_t *)(ws + L.list); p.slot_of = (int32_t *)(ws + L.slot_of);
     p.w_all = (const float *)(ws + L.w_all);
     p.xt = ws + L.xt; p.x_sums = ws + L.x_sums;
     p.h_hi = ws + L.h_hi; p.h_lo = ws + L.h_lo; p.h_sums = ws + L.h_sums; p.zeros = ws + L.zeros;
     p.obuf = (float *)(ws + L.obuf);
     p.y = y;
     p.shared = shared; p.shared_stride = moe_bf16_expert_bytes(desc);
-    { ProfScope t(ctx, MOE_KERNEL_ROUTE, st); launch_route(s, x, wr, bias, ids_out, (float *)(ws + L.w_all), conf_out, st); }
-    { ProfScope t(ctx, MOE_KERNEL_PLAN, st);
-      launch_prefill_plan(s, ids_out, (int32_t *)(ws + L.sorted), (int32_t *)(ws + L.slot_of),
-                          (PrefillItem *)(ws + L.items), (int32_t *)(ws + L.n_items), st); }
+    if (prefill_small(s)) {
+        { ProfScope t(ctx, MOE_KERNEL_ROUTE, st); launch_route(s, x, wr, bias, ids_out, (float *)(ws + L.w_all), conf_out, st); }
+        { ProfScope t(ctx, MOE_KERNEL_PLAN, st); launch_prefill_plan(s, ids_out, p, st); }
+    } else {
+        { ProfScope t(ctx, MOE_KERNEL_ROUTE, st); launch_prefill_logits(s, x, wr, (double *)(ws + L.parts), (int32_t *)(ws + L.count), st); }
+        { ProfScope t(ctx, MOE_KERNEL_PLAN, st);
+          launch_prefill_topk(s, (const double *)(ws + L.parts), bias, ids_out, (float *)(ws + L.w_all), conf_out,
+                              (int32_t *)(ws + L.count), (int32_t *)(ws + L.list), st); }
+    }
     { ProfScope t(ctx, MOE_KERNEL_PREFILL_STAGE, st); launch_prefill_stage(s, p, L.max_items, st); }
     { ProfScope t(ctx, MOE_KERNEL_PREFILL_GATEUP, st); launch_prefill_gateup(s, p, L.max_items, st); }
     { ProfScope t(ctx, MOE_KERNEL_PREFILL_DOWN, st); launch_prefill_down(s, p, L.max_items, st); }

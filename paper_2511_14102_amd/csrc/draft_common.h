@@ -218,11 +218,6 @@ __device__ inline void publish_router_rows(const uint16_t *__restrict__ xin, con
 // (larger logit first, lower index first among equals) to ids[0 .. k), every logit and its rank
 // (MOE_MAX_EXPERTS: not selected) to LDS for the softmax, which follows later, and the selected experts
 // to the words of `mask` (unless null).  `logit` null: only the wait.  False: the wait ran out of polls.
-//
-// Selection: k rounds of a maximum over 32-bit keys that order like the logits rounded to fp32 (six
-// lane moves each); where several logits share the largest key, their fp64 values decide.  (Counting the
-// rank of every fp64 logit, by one wave for up to 32 experts and by all waves beyond, took 0.9 us for 16
-// experts, 2.8 us for 128, and 12.8 us for 128 experts and 8 tokens.)
 template <int NR>                                // NR: 64 NR >= E
 __device__ inline bool poll_and_select(const FusedArgs &a, int t, double *logit, int32_t *rank, int32_t *ids,
                                        unsigned long long *mask)
@@ -247,48 +242,15 @@ __device__ inline bool poll_and_select(const FusedArgs &a, int t, double *logit,
     }
     if (!all) return false;
     if (!logit) return true;
-    constexpr int kNone = -2147483647 - 1;       // below the key of every number
     double l[NR];
-    int key[NR], rk[NR];
+    int rk[NR];
 #pragma unroll
     for (int i = 0; i < NR; ++i) {
         const int e = lane + 64 * i;
         l[i] = __longlong_as_double((long long)(((unsigned long long)v[i].y << 32) | v[i].x));
         if (e < E) logit[e] = l[i];
-        if (!(l[i] == l[i])) l[i] = -INFINITY;               // a NaN is selected last
-        const int b = __float_as_int((float)l[i] + 0.f);     // (-0 and 0 are equal)
-        key[i] = e < E ? b ^ ((b >> 31) & 0x7fffffff) : kNone;
-        rk[i] = MOE_MAX_EXPERTS;
     }
-    int id = 0;
-    for (int j = 0; j < k; ++j) {
-        int m = key[0];
-#pragma unroll
-        for (int i = 1; i < NR; ++i) m = m > key[i] ? m : key[i];
-        m = wave::max(m);
-        unsigned long long hit[NR];
-        int hits = 0;
-#pragma unroll
-        for (int i = 0; i < NR; ++i) { hit[i] = __ballot(key[i] == m); hits += __popcll(hit[i]); }
-        if (hits > 1) {
-            double d = -INFINITY;
-#pragma unroll
-            for (int i = 0; i < NR; ++i) d = key[i] == m ? fmax(d, l[i]) : d;
-            d = wave::max(d);
-#pragma unroll
-            for (int i = 0; i < NR; ++i) hit[i] = __ballot(key[i] == m && l[i] == d);
-        }
-        int e = 0;
-#pragma unroll
-        for (int i = NR - 1; i >= 0; --i) e = hit[i] ? 64 * i + __ffsll((long long)hit[i]) - 1 : e;
-#pragma unroll
-        for (int i = 0; i < NR; ++i) {
-            const bool won = lane + 64 * i == e;
-            key[i] = won ? kNone : key[i];
-            rk[i] = won ? j : rk[i];
-        }
-        id = lane == j ? e : id;
-    }
+    const int id = wave::select_topk(l, E, k, lane, rk);
     if (lane < k) ids[lane] = id;
 #pragma unroll
     for (int i = 0; i < NR; ++i) {

@@ -3,9 +3,10 @@
 // of section 4.1.3).  The tokens are routed first; every expert's assignments are cut into work
 // items of up to 64, and each expert's weights are streamed once per item:
 //
-//   prefill_plan_kernel    assignments sorted by expert, items, slot of every assignment; a shared
-//                          expert's items are the tokens in order, in front of the others
-//   prefill_stage_kernel   the items' tokens gathered into MFMA operand tiles (zero padded), and
+//   prefill_logits_kernel, prefill_topk_kernel (route.hip)  the routing, and every expert's assignments;
+//                          small calls: route_kernel and prefill_plan_kernel
+//   prefill_stage_kernel   the items (a shared expert's are the tokens in order, in front of the
+//                          others), their tokens gathered into MFMA operand tiles (zero padded), and
 //                          each group's sum, in three bf16 pieces, for the zero points
 //   prefill_tile_kernel<gate/up>  one workgroup per (item, four slices of 32 intermediate rows):
 //                          per slice 64 pre-activations (32 gate, 32 up) x 64 tokens over all of
@@ -311,6 +312,9 @@ void prefill_tile_kernel(TileArgs a)
 
     // an item of a routed expert with NTB token blocks (a compile-time count: no branch inside a stage)
     auto run = [&](auto ntb_c) {
+        // exits between the stages of a trip, for few k-steps (H = 256: gate/up 9.1 -> 7.6 us); not where a group spans
+        // two stages: with them those loops spill
+        constexpr bool kExits = SK >= KPG;
         constexpr int NTB = decltype(ntb_c)::value;
         f32x4 tot[4][NTB], acc[4][NTB];
 #pragma unroll
@@ -392,11 +396,24 @@ void prefill_tile_kernel(TileArgs a)
 #pragma unroll
         for (int d = 0; d < 4; ++d) wb[0][d] = unpack8_16(win[0][d], uk);
         win[0] = load_codes(kWin);
-        for (int n = 0; n < ns; n += 4) {
-            stage(n, k0);
-            stage(n + 1, k1);
-            stage(n + 2, k2);
-            stage(n + 3, k3);
+        if constexpr (kExits) {
+            for (int n = 0; ; n += 4) {
+                stage(n, k0);
+                if (n + 1 >= ns) break;
+                stage(n + 1, k1);
+                if (n + 2 >= ns) break;
+                stage(n + 2, k2);
+                if (n + 3 >= ns) break;
+                stage(n + 3, k3);
+                if (n + 4 >= ns) break;
+            }
+        } else {
+            for (int n = 0; n < ns; n += 4) {
+                stage(n, k0);
+                stage(n + 1, k1);
+                stage(n + 2, k2);
+                stage(n + 3, k3);
+            }
         }
         // every last stage ends a group (k-steps past the end are zeros)
         add_scaled(NTB - 1);
@@ -516,24 +533,71 @@ void prefill_tile_kernel(TileArgs a)
 // Gathers the tokens of token block (item, tb) into operand tiles [(item nk + u) 4 + tb]: lane
 // (token, chunk) of tile u holds x[token][32 u + 8 chunk .. + 7]; positions past the item's count
 // hold zeros.  (The shared experts read one copy.)  Also the group sums as operand tiles [(item nz + group / 4) 4 + tb].  One wave per
-// (block, four tiles): 128 inputs, whole groups.  The first workgroup also writes the tile of zeros.
-template <int KPG>
+// (block, four tiles): 128 inputs, whole groups.
+// Which item that is: kPlanned: prefill_plan_kernel has written the items; else it follows from the experts'
+// counts (the shared experts' S ceil(T / 64) items come first, then every expert's, in chunks of 64; expert
+// e's assignments are list[e T ..]); each workgroup sums the counts up for itself, the first one also writes the items,
+// and a block's first workgroup the slots of its assignments.  The first workgroup also writes the tile of zeros.
+template <int KPG, bool kPlanned>
 __global__ __launch_bounds__(256)
-void prefill_stage_kernel(const uint16_t *__restrict__ x, const PrefillItem *__restrict__ items,
-                          const int32_t *__restrict__ n_items, const int32_t *__restrict__ sorted,
-                          char *__restrict__ xt, char *__restrict__ sums, char *__restrict__ zeros, int H, int k, int E)
+void prefill_stage_kernel(const uint16_t *__restrict__ x, const int32_t *__restrict__ count, const int32_t *__restrict__ list,
+                          PrefillItem *__restrict__ items, int32_t *__restrict__ n_items, int32_t *__restrict__ slot_of,
+                          char *__restrict__ xt, char *__restrict__ sums, char *__restrict__ zeros, int T, int H, int k, int E, int S)
 {
-    if (blockIdx.x == 0 && blockIdx.y == 0)
-        *reinterpret_cast<u32x4 *>(zeros + threadIdx.x * 16) = (u32x4){0u, 0u, 0u, 0u};
-    const int item = blockIdx.x >> 2, tb = blockIdx.x & 3;
-    if (item >= *n_items) return;
-    const PrefillItem it = items[item];
+    const int item = blockIdx.x >> 2, tb = blockIdx.x & 3, tid = threadIdx.x;
+    const bool first = blockIdx.x == 0 && blockIdx.y == 0;
+    if (first) *reinterpret_cast<u32x4 *>(zeros + tid * 16) = (u32x4){0u, 0u, 0u, 0u};
+    PrefillItem it;
+    if constexpr (kPlanned) {
+        const int n = *n_items;                      // (both loads at once: items past the last are inside the buffer)
+        it = items[item];
+        if ((item >= n) | (16 * tb >= it.cnt) | (it.src != item)) return;
+    } else {
+        __shared__ int32_t s_end[4];                     // per wave: items of its 64 experts
+        __shared__ PrefillItem s_item;
+        const int chunks = (T + kItemTokens - 1) / kItemTokens;
+        if (tid == 0) s_item = PrefillItem{0, 0, 0, -1};
+        // thread e: expert e's items are [begin, begin + mine)
+        const int cnt = tid < E ? count[tid] : 0, mine = (cnt + kItemTokens - 1) / kItemTokens;
+        int incl = mine;
+#pragma unroll
+        for (int d = 1; d < 64; d <<= 1) {
+            const int v = __shfl_up(incl, d, 64);
+            if ((tid & 63) >= d) incl += v;
+        }
+        if ((tid & 63) == 63) s_end[tid >> 6] = incl;
+        __syncthreads();
+        int begin = S * chunks + incl - mine, total = S * chunks;
+        for (int w = 0; w < 4; ++w) {
+            begin += w < (tid >> 6) ? s_end[w] : 0;
+            total += s_end[w];
+        }
+        auto chunk_of = [&](int j) {                     // of this thread's expert
+            return PrefillItem{tid, tid * T + j * kItemTokens, cnt - j * kItemTokens < kItemTokens ? cnt - j * kItemTokens : kItemTokens, begin + j};
+        };
+        auto shared_item = [&](int i) {
+            const int j = i % chunks;
+            return PrefillItem{E + i / chunks, j * kItemTokens, T - j * kItemTokens < kItemTokens ? T - j * kItemTokens : kItemTokens, j};
+        };
+        if (item >= begin && item < begin + mine) s_item = chunk_of(item - begin);
+        if (tid == 0 && item < S * chunks) s_item = shared_item(item);
+        if (first) {
+            for (int i = tid; i < S * chunks; i += 256) items[i] = shared_item(i);
+            for (int j = 0; j < mine; ++j) items[begin + j] = chunk_of(j);
+            if (tid == 0) *n_items = total;
+        }
+        __syncthreads();
+        if (item >= total) return;
+        it = s_item;
+        if (blockIdx.y == 0 && tid < 16 && it.expert < E && 16 * tb + tid < it.cnt)
+            slot_of[list[it.first + 16 * tb + tid]] = item * kItemTokens + 16 * tb + tid;
+    }
     if (16 * tb >= it.cnt || it.src != item) return;
     const int nk = H / 32, u4 = blockIdx.y * 4 + (threadIdx.x >> 6);
     if (u4 * 4 >= nk) return;
     const int lane = threadIdx.x & 63, tok16 = lane & 15, chunk = lane >> 4, pos = 16 * tb + tok16;
     const int at = it.first + (pos < it.cnt ? pos : 0);
-    const int token = it.expert < E ? sorted[at] / k : at;
+    const int token = it.expert < E ? list[at] / k : at;
     float s[4];
 #pragma unroll
     for (int j = 0; j < 4; ++j) {
@@ -568,7 +632,7 @@ void prefill_stage_kernel(const uint16_t *__restrict__ x, const PrefillItem *__r
 // The first S ceil(T / 64) items are the shared experts', over the tokens in order.  One workgroup.
 __global__ __launch_bounds__(1024)
 void prefill_plan_kernel(const int32_t *__restrict__ ids, int n, int E, int T, int S,
-                         int32_t *__restrict__ sorted, int32_t *__restrict__ slot_of,
+                         int32_t *__restrict__ list, int32_t *__restrict__ slot_of,
                          PrefillItem *__restrict__ items, int32_t *__restrict__ n_items)
 {
     __shared__ int32_t s_count[MOE_MAX_EXPERTS], s_off[MOE_MAX_EXPERTS], s_fill[MOE_MAX_EXPERTS],
@@ -596,7 +660,7 @@ void prefill_plan_kernel(const int32_t *__restrict__ ids, int n, int E, int T, i
     for (int i = threadIdx.x; i < n; i += blockDim.x) {
         const int e = ids[i];
         const int idx = atomicAdd(&s_fill[e], 1);
-        sorted[s_off[e] + idx] = i;
+        list[s_off[e] + idx] = i;
         slot_of[i] = (s_item0[e] + idx / kItemTokens) * kItemTokens + idx % kItemTokens;
     }
     for (int e = threadIdx.x; e < E; e += blockDim.x) {
@@ -663,22 +727,32 @@ PrefillBuffers prefill_buffers(const moe_layer_desc &d, int max_items)
     return b;
 }
 
-void launch_prefill_plan(const Shape &s, const int32_t *ids, int32_t *sorted, int32_t *slot_of,
-                         PrefillItem *items, int32_t *n_items, hipStream_t st)
+// Small calls: one workgroup per token routes (route_kernel) and one workgroup sorts (prefill_plan_kernel); larger
+// ones: the two launches of route.hip, and the stage launch finds the items.  us of the three launches, small
+// form / large form: 421 tokens of the tiny shape (H = 256, E = 8, k = 2; 1.7 million here) 11 / 14, 1703
+// tokens (7 million) 18 / 15, phi shape, 512 tokens (34 million) 28 / 20, dsv2lite, 333 (46 million) 40 / 22.
+bool prefill_small(const Shape &s) { return (long)s.T * ((long)s.E * s.H + 1024L * s.k) < (4L << 20); }
+
+void launch_prefill_plan(const Shape &s, const int32_t *ids, const PrefillCall &p, hipStream_t st)
 {
-    launch(prefill_plan_kernel, dim3(1), dim3(1024), 0, st, ids, s.T * s.k, s.E, s.T, s.S, sorted, slot_of, items, n_items);
+    launch(prefill_plan_kernel, dim3(1), dim3(1024), 0, st, ids, s.T * s.k, s.E, s.T, s.S, (int32_t *)p.list, p.slot_of, p.items, p.n_items);
 }
 
 void launch_prefill_stage(const Shape &s, const PrefillCall &p, int max_items, hipStream_t st)
 {
     const dim3 grid(max_items * 4, (s.H / 32 + 15) / 16), block(256);
     auto go = [&](auto kernel) {
-        launch(kernel, grid, block, 0, st, (const uint16_t *)p.x, p.items, p.n_items, p.sorted, (char *)p.xt,
-               (char *)p.x_sums, (char *)p.zeros, s.H, s.k, s.E);
+        launch(kernel, grid, block, 0, st, (const uint16_t *)p.x, p.count, p.list, p.items, p.n_items, p.slot_of, (char *)p.xt,
+               (char *)p.x_sums, (char *)p.zeros, s.T, s.H, s.k, s.E, s.S);
     };
-    if (s.g == 32) go(prefill_stage_kernel<1>);
-    else if (s.g == 64) go(prefill_stage_kernel<2>);
-    else go(prefill_stage_kernel<4>);
+    auto of_group = [&](auto planned) {
+        constexpr bool kPlanned = decltype(planned)::value;
+        if (s.g == 32) go(prefill_stage_kernel<1, kPlanned>);
+        else if (s.g == 64) go(prefill_stage_kernel<2, kPlanned>);
+        else go(prefill_stage_kernel<4, kPlanned>);
+    };
+    if (prefill_small(s)) of_group(std::true_type{});
+    else of_group(std::false_type{});
 }
 
 static TileArgs tile_args(const Shape &s, const PrefillCall &p)

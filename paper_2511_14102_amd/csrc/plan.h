@@ -82,6 +82,12 @@ void launch_route(const Shape &s, const void *x, const void *wr, const float *bi
                   int32_t *ids, float *w, float *conf, hipStream_t st);
 void launch_perm(const Shape &s, const int32_t *ids, int32_t *count, int32_t *off,
                  int32_t *perm, hipStream_t st);
+// a long run of tokens: partial logits [prefill_logit_parts][T][E] (and the expert counts cleared), then ids, weights,
+// confidences, the experts' counts and their assignments list[expert T + place]
+int prefill_logit_parts(const Shape &s);
+void launch_prefill_logits(const Shape &s, const void *x, const void *wr, double *parts, int32_t *count, hipStream_t st);
+void launch_prefill_topk(const Shape &s, const double *parts, const float *bias, int32_t *ids, float *w, float *conf,
+                         int32_t *count, int32_t *list, hipStream_t st);
 struct PlanArgs {
     Plan *plan;
     int mode;                          // 0 draft (int4 routed, all present), 1 verify (slot table)
@@ -102,7 +108,7 @@ void launch_union(const int32_t *ids, int n_ids, int E, const int32_t *slot,
                   int32_t *missing, int32_t *n_missing, hipStream_t st);
 
 // Work item of the draft call over a long run of tokens: up to kPrefillChunk assignments of one
-// expert, sorted[first .. first + cnt), or (expert >= E: shared expert) tokens [first, first + cnt).
+// expert, list[first .. first + cnt), or (expert >= E: shared expert) tokens [first, first + cnt).
 // Item i owns slots [64 i, 64 i + cnt); src: the item whose operand tiles of x it reads.
 constexpr int kPrefillChunk = 64;
 struct PrefillItem { int32_t expert, first, cnt, src; };
@@ -141,14 +147,15 @@ PrefillBuffers prefill_buffers(const moe_layer_desc &d, int max_items);
 struct PrefillCall {
     const void *x;                     // [T,H] bf16
     const void *q, *sz; size_t stride_q, stride_sz; int symmetric;
-    const PrefillItem *items; const int32_t *n_items; const int32_t *sorted; const int32_t *slot_of;
+    PrefillItem *items; int32_t *n_items;                          // written by the plan or the stage launch
+    const int32_t *count, *list; int32_t *slot_of;
     const float *w_all;                // routing weight of every assignment [T k]
     void *xt, *x_sums, *h_hi, *h_lo, *h_sums, *zeros; float *obuf;
     float *y;                          // [T,H] fp32, written (not accumulated)
     const void *shared; size_t shared_stride;                          // bf16 blobs of the shared experts
 };
-void launch_prefill_plan(const Shape &s, const int32_t *ids, int32_t *sorted, int32_t *slot_of,
-                         PrefillItem *items, int32_t *n_items, hipStream_t st);
+bool prefill_small(const Shape &s);        // the small form of the routing: launch_route, then
+void launch_prefill_plan(const Shape &s, const int32_t *ids, const PrefillCall &p, hipStream_t st);
 void launch_prefill_stage(const Shape &s, const PrefillCall &p, int max_items, hipStream_t st);
 void launch_prefill_gateup(const Shape &s, const PrefillCall &p, int max_items, hipStream_t st);
 void launch_prefill_down(const Shape &s, const PrefillCall &p, int max_items, hipStream_t st);

@@ -413,6 +413,142 @@ void route_plan_kernel(const uint16_t *__restrict__ x, const uint16_t *__restric
                     a.shared, a.shared_stride, a.flags, a.ids_out, a.conf_out, a.missing, a.n_missing);
 }
 
+// Router of a long run of tokens, first launch: partial logits [part][T][E] in fp64 over a share of H.  A
+// workgroup takes 16 tokens, 16 experts and one of gridDim.z shares of the k-steps of 32 inputs, its four
+// waves a quarter of that each, on the fp64 matrix cores (16x16x4): a lane loads 8 inputs of one token and of
+// one expert row and feeds eight products.  Bound: those matrix instructions (64 cycles each) and the round
+// trip in front of them; the shares are there to spread few tokens over the chip.  (One workgroup per token,
+// re-reading all router rows for each, took 24.5 us for 333 tokens x 64 experts x 2048 inputs and 92 us for
+// 4096 x 8 x 4096; now 12 and 26 us with the second launch.)
+typedef __attribute__((ext_vector_type(4))) double f64x4;
+constexpr int kLogitWaves = 4, kMaxParts = 8;
+
+__global__ __launch_bounds__(kLogitWaves * 64)
+void prefill_logits_kernel(const uint16_t *__restrict__ x, const uint16_t *__restrict__ wr, int T, int H, int E,
+                           double *__restrict__ parts, int32_t *__restrict__ count)
+{
+    __shared__ double s_part[kLogitWaves][256];
+    const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int r = lane & 15, c = lane >> 4;
+    if (blockIdx.x == 0 && blockIdx.y == 0 && blockIdx.z == 0)           // the expert counts of the second launch
+        for (int e = tid; e < E; e += kLogitWaves * 64) count[e] = 0;
+    const int t = blockIdx.x * 16 + r, e = blockIdx.y * 16 + r;
+    const uint16_t *xt = x + (size_t)(t < T ? t : T - 1) * H + c * 8;
+    const uint16_t *row = wr + (size_t)(e < E ? e : E - 1) * H + c * 8;
+    const int nk = H / 32, shares = gridDim.z * kLogitWaves, share = blockIdx.z * kLogitWaves + wave;
+    const int k0 = (int)((long)nk * share / shares), k1 = (int)((long)nk * (share + 1) / shares);
+    f64x4 acc = {0.0, 0.0, 0.0, 0.0};
+    constexpr int kAhead = 4;                    // k-steps in flight; past the end the last one is loaded again
+    uint4 xv[kAhead], wv[kAhead];
+    auto load = [&](int slot, int k) {
+        const int kk = k < nk ? k : nk - 1;
+        xv[slot] = *reinterpret_cast<const uint4 *>(xt + kk * 32);
+        wv[slot] = *reinterpret_cast<const uint4 *>(row + kk * 32);
+    };
+#pragma unroll
+    for (int i = 0; i < kAhead; ++i) load(i, k0 + i);
+    for (int k = k0; k < k1; k += kAhead) {
+#pragma unroll
+        for (int i = 0; i < kAhead; ++i) {
+            const uint32_t xs[4] = {xv[i].x, xv[i].y, xv[i].z, xv[i].w}, ws[4] = {wv[i].x, wv[i].y, wv[i].z, wv[i].w};
+            if (k + i < k1) {
+#pragma unroll
+                for (int j = 0; j < 4; ++j) {
+                    acc = __builtin_amdgcn_mfma_f64_16x16x4f64((double)__uint_as_float(xs[j] << 16), (double)__uint_as_float(ws[j] << 16), acc, 0, 0, 0);
+                    acc = __builtin_amdgcn_mfma_f64_16x16x4f64((double)__uint_as_float(xs[j] & 0xffff0000u), (double)__uint_as_float(ws[j] & 0xffff0000u), acc, 0, 0, 0);
+                }
+            }
+            load(i, k + i + kAhead);
+        }
+    }
+    // fp64 results: lane (r, c) holds column r (expert) of rows (tokens) c, c + 4, c + 8, c + 12
+#pragma unroll
+    for (int i = 0; i < 4; ++i) s_part[wave][(4 * i + c) * 16 + r] = acc[i];
+    __syncthreads();
+    const int to = blockIdx.x * 16 + (tid >> 4), eo = blockIdx.y * 16 + (tid & 15);
+    if (to < T && eo < E)
+        parts[((size_t)blockIdx.z * T + to) * E + eo] = (s_part[0][tid] + s_part[1][tid]) + (s_part[2][tid] + s_part[3][tid]);
+}
+
+// Second launch: one wave per token adds the shares, selects the top-k, and forms the softmax; the workgroup
+// then gives every assignment a place in its expert's list (list[expert T + place]; the order inside an expert is
+// arbitrary: no result depends on it), with one addition to the expert's count for all its tokens.
+template <int NR>
+__device__ inline void prefill_topk(const double *__restrict__ parts, int nparts, const float *__restrict__ bias, int T, int E,
+                                    int k, int renorm, int t, int lane, int32_t *ids, float *w, float *conf, int &id)
+{
+    double l[NR], v[NR][kMaxParts];
+    int rank[NR];
+#pragma unroll
+    for (int i = 0; i < NR; ++i) {
+        const int e = lane + 64 * i < E ? lane + 64 * i : E - 1;
+        l[i] = bias ? (double)bias[e] : 0.0;
+        v[i][0] = parts[(size_t)t * E + e];
+        if (nparts > 1) {                        // (all loads before the first sum; past the end the last share again)
+#pragma unroll
+            for (int p = 1; p < kMaxParts; ++p) v[i][p] = parts[((size_t)(p < nparts ? p : nparts - 1) * T + t) * E + e];
+        }
+    }
+#pragma unroll
+    for (int i = 0; i < NR; ++i) {
+        double sum = v[i][0];
+#pragma unroll
+        for (int p = 1; p < kMaxParts; ++p) sum += p < nparts ? v[i][p] : 0.0;
+        l[i] += sum;
+    }
+    id = wave::select_topk(l, E, k, lane, rank);
+    double mx = -INFINITY, den = 0.0, sel = 0.0, pe[NR];
+#pragma unroll
+    for (int i = 0; i < NR; ++i) mx = lane + 64 * i < E ? fmax(mx, l[i]) : mx;
+    mx = wave::max(mx);
+#pragma unroll
+    for (int i = 0; i < NR; ++i) {
+        pe[i] = lane + 64 * i < E ? exp(l[i] - mx) : 0.0;
+        den += pe[i];
+    }
+    den = wave::sum(den);
+#pragma unroll
+    for (int i = 0; i < NR; ++i) {
+        pe[i] = pe[i] / den;
+        sel += rank[i] < k ? pe[i] : 0.0;
+    }
+    sel = wave::sum(sel);
+    if (lane < k) ids[(size_t)t * k + lane] = id;
+#pragma unroll
+    for (int i = 0; i < NR; ++i) {
+        if (rank[i] < k) {
+            const size_t o = (size_t)t * k + rank[i];
+            if (conf) conf[o] = (float)pe[i];
+            w[o] = renorm ? (float)(pe[i] / sel) : (float)pe[i];
+        }
+    }
+}
+
+constexpr int kTopkTokens = 16;
+
+__global__ __launch_bounds__(kTopkTokens * 64)
+void prefill_topk_kernel(const double *__restrict__ parts, int nparts, const float *__restrict__ bias, int T, int E, int k,
+                         int renorm, int32_t *__restrict__ ids, float *__restrict__ w, float *__restrict__ conf,
+                         int32_t *__restrict__ count, int32_t *__restrict__ list)
+{
+    __shared__ int32_t s_count[MOE_MAX_EXPERTS], s_base[MOE_MAX_EXPERTS];
+    const int tid = threadIdx.x, lane = tid & 63, t = blockIdx.x * kTopkTokens + (tid >> 6);
+    for (int e = tid; e < E; e += kTopkTokens * 64) s_count[e] = 0;
+    __syncthreads();
+    int id = 0, place = 0;
+    const bool mine = t < T && lane < k;
+    if (t < T) {
+        if (E <= 64) prefill_topk<1>(parts, nparts, bias, T, E, k, renorm, t, lane, ids, w, conf, id);
+        else if (E <= 128) prefill_topk<2>(parts, nparts, bias, T, E, k, renorm, t, lane, ids, w, conf, id);
+        else prefill_topk<4>(parts, nparts, bias, T, E, k, renorm, t, lane, ids, w, conf, id);
+        if (mine) place = atomicAdd(&s_count[id], 1);
+    }
+    __syncthreads();
+    for (int e = tid; e < E; e += kTopkTokens * 64) s_base[e] = s_count[e] > 0 ? atomicAdd(&count[e], s_count[e]) : 0;
+    __syncthreads();
+    if (mine) list[(size_t)id * T + s_base[id] + place] = t * k + lane;
+}
+
 // Union of expert ids: bitmask in shared memory, then ordered compaction by one wave.
 __global__ __launch_bounds__(256)
 void union_kernel(const int32_t *__restrict__ ids, int n_ids, int E,
@@ -454,6 +590,28 @@ void launch_route(const Shape &s, const void *x, const void *wr, const float *bi
     launch(route_kernel, dim3(s.T), dim3(kRouteThreads), 0, st,
                        (const uint16_t *)x, (const uint16_t *)wr, bias, s.H, s.E, s.k, s.renorm,
                        ids, w, conf);
+}
+
+// shares of H: enough workgroups to fill the chip twice, at least four k-steps per wave
+int prefill_logit_parts(const Shape &s)
+{
+    const int blocks = ((s.T + 15) / 16) * ((s.E + 15) / 16), most = s.H / 32 / (4 * kLogitWaves);
+    const int want = 512 / blocks;
+    const int parts = want < most ? want : most;
+    return parts < 1 ? 1 : (parts < kMaxParts ? parts : kMaxParts);
+}
+
+void launch_prefill_logits(const Shape &s, const void *x, const void *wr, double *parts, int32_t *count, hipStream_t st)
+{
+    launch(prefill_logits_kernel, dim3((s.T + 15) / 16, (s.E + 15) / 16, prefill_logit_parts(s)), dim3(kLogitWaves * 64), 0, st,
+           (const uint16_t *)x, (const uint16_t *)wr, s.T, s.H, s.E, parts, count);
+}
+
+void launch_prefill_topk(const Shape &s, const double *parts, const float *bias, int32_t *ids, float *w, float *conf,
+                         int32_t *count, int32_t *list, hipStream_t st)
+{
+    launch(prefill_topk_kernel, dim3((s.T + kTopkTokens - 1) / kTopkTokens), dim3(kTopkTokens * 64), 0, st, parts, prefill_logit_parts(s),
+           bias, s.T, s.E, s.k, s.renorm, ids, w, conf, count, list);
 }
 
 void launch_perm(const Shape &s, const int32_t *ids, int32_t *count, int32_t *off,

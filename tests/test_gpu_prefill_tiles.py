@@ -45,3 +45,29 @@ def test_prefill_tile_edges(cfg):
             assert np.array_equal(to_np(r["ids"]), ref["ids"][:T])
             assert rel_err(to_np(r["y"]), ref["y"][:T]) <= TOL_DRAFT
     ctx.close()
+
+
+ROUTED = [
+    #            idx  name    H    E   I   k   g  S  renorm     (large enough for the two-launch routing)
+    LayerConfig(66, "r70", 320, 70, 64, 3, 32, 0, 1),      # ragged token and expert blocks, k-steps that do not fill a share
+    LayerConfig(67, "r130", 192, 130, 64, 4, 64, 1, 0),    # more than 128 experts, a shared expert
+    LayerConfig(68, "r5", 2112, 5, 64, 5, 64, 2, 1),       # few experts, shares of H, every token in every expert
+]
+
+
+@pytest.mark.parametrize("cfg", ROUTED, ids=[c.name for c in ROUTED])
+def test_prefill_routing_edges(cfg):
+    ctx = B.Context(0)
+    L = synth.make_layer(cfg, 0)
+    A = oracle_arrays(L)
+    D = DeviceLayer(ctx, cfg, L, max_tokens=8, verify=False)
+    x = tokens_with_clear_routing(cfg, A, 421, step=5, kind="iid")
+    ref = oracle_draft(A, x)
+    for T in (257, 421):
+        say("prefill routing", cfg.name, "T", T)
+        r = D.prefill(x[:T].cuda())
+        torch.cuda.synchronize()
+        assert np.array_equal(to_np(r["ids"]), ref["ids"][:T])
+        np.testing.assert_allclose(to_np(r["conf"]), ref["conf"][:T], rtol=2e-6)
+        assert rel_err(to_np(r["y"]), ref["y"][:T]) <= TOL_DRAFT
+    ctx.close()
