@@ -106,9 +106,10 @@ __device__ inline void store16_agent(void *p, u32x4 v) {
 // does not know of the transfer and adds no waits of its own for it (it would wait for ALL vector
 // memory operations before every barrier and every LDS read that follows); the caller orders the
 // use of the data behind the arrival of a later load of the same wave (vector memory operations
-// complete in order).
+// complete in order).  A load to LDS reads M0, and needs a wait state behind the scalar write of it: the
+// compiler puts one there for its own loads, but does not look into assembly.
 __device__ inline void load16_to_lds(const void *g, uint32_t lds_base) {
-    asm volatile("s_mov_b32 m0, %0\n\tglobal_load_lds_dwordx4 %1, off" : : "s"(lds_base), "v"(g) : "memory");
+    asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, off" : : "s"(lds_base), "v"(g) : "memory");
 }
 
 // A run of a weight stream as a buffer: `bytes` bytes from `base` (both wave-uniform).  A load past the run's

@@ -7,14 +7,18 @@ instead of 29.6 us per call on the phi shape with 12 spilled registers).
 The streaming kernel copies scale / zero entries into LDS with loads issued from inline assembly
 that set the M0 register themselves; the compiler is not told, so nothing else in those kernels
 may depend on M0."""
+import functools
 import os
 import re
 import subprocess
 import tempfile
 
+import pytest
+
 ROOT = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
 
 
+@functools.lru_cache(maxsize=None)
 def _assembly(name):
     from paper_2511_14102_amd import build as B
     src = os.path.join(B.CSRC, name)
@@ -55,3 +59,14 @@ def test_streaming_kernel_uses_m0_only_for_its_loads_to_lds():
     for l in uses:
         assert l.startswith("s_mov_b32 m0,"), l
     assert "global_load_lds_dwordx4" in body
+
+
+@pytest.mark.parametrize("src", ["draft_int4.hip", "draft_prefill.hip"])
+def test_loads_to_lds_do_not_follow_the_write_of_m0_directly(src):
+    """A load to LDS needs a wait state between the scalar write of M0 and itself."""
+    code = [l.strip() for l in _assembly(src).splitlines()]
+    code = [l for l in code if re.match(r"[a-z]\w*( |$)", l)]            # instructions: no comments, labels, directives
+    loads = [(a, b) for a, b in zip(code, code[1:]) if re.match(r"(global_load_lds_|buffer_load_\w+ .*\blds\b)", b)]
+    assert loads, "the loads to LDS are gone?"
+    for before, load in loads:
+        assert not re.search(r"\bm0\b", before), (before, load)
