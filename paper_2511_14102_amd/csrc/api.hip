@@ -449,7 +449,7 @@ static PrefillLayout prefill_layout(const moe_layer_desc &d, int T)
     L.w_all = o;   o += align256(n * 4);
     L.count = o;   o += align256((size_t)d.n_experts * 4);
     L.list = o;    o += align256((size_t)d.n_experts * T * 4);
-    L.parts = o;   o += align256((size_t)prefill_logit_parts(make_shape(&d, T)) * T * d.n_experts * 8);
+    L.parts = o;   o += align256(prefill_logit_rows(make_shape(&d, T)) * d.n_experts * 8);
     L.slot_of = o; o += align256(n * 4);
     L.n_items = o; o += 256;
     L.items = o;   o += align256((size_t)L.max_items * sizeof(PrefillItem));

@@ -85,6 +85,7 @@ void launch_perm(const Shape &s, const int32_t *ids, int32_t *count, int32_t *of
 // a long run of tokens: partial logits [prefill_logit_parts][T][E] (and the expert counts cleared), then ids, weights,
 // confidences, the experts' counts and their assignments list[expert T + place]
 int prefill_logit_parts(const Shape &s);
+size_t prefill_logit_rows(const Shape &s);       // rows of E logits the workspace holds for them: at least parts x T
 void launch_prefill_logits(const Shape &s, const void *x, const void *wr, double *parts, int32_t *count, hipStream_t st);
 void launch_prefill_topk(const Shape &s, const double *parts, const float *bias, int32_t *ids, float *w, float *conf,
                          int32_t *count, int32_t *list, hipStream_t st);

@@ -593,12 +593,27 @@ void launch_route(const Shape &s, const void *x, const void *wr, const float *bi
 }
 
 // shares of H: enough workgroups to fill the chip twice, at least four k-steps per wave
+constexpr int kLogitBlocks = 512;
+static int most_parts(const Shape &s)
+{
+    const int most = s.H / 32 / (4 * kLogitWaves);
+    return most < 1 ? 1 : (most < kMaxParts ? most : kMaxParts);
+}
 int prefill_logit_parts(const Shape &s)
 {
-    const int blocks = ((s.T + 15) / 16) * ((s.E + 15) / 16), most = s.H / 32 / (4 * kLogitWaves);
-    const int want = 512 / blocks;
-    const int parts = want < most ? want : most;
-    return parts < 1 ? 1 : (parts < kMaxParts ? parts : kMaxParts);
+    const int blocks = ((s.T + 15) / 16) * ((s.E + 15) / 16);
+    const int want = kLogitBlocks / blocks, most = most_parts(s);
+    return want < 1 ? 1 : (want < most ? want : most);
+}
+
+// The largest parts x T of any call with up to s.T tokens: the shares get fewer as the tokens get more, and a
+// workspace made for many tokens has to hold a call with fewer.  With two or more shares parts x ceil(T / 16) x
+// ceil(E / 16) is at most kLogitBlocks.
+size_t prefill_logit_rows(const Shape &s)
+{
+    const size_t all = (size_t)s.T * most_parts(s), spread = (size_t)kLogitBlocks * 16 / ((s.E + 15) / 16);
+    const size_t split = all < spread ? all : spread;
+    return split > (size_t)s.T ? split : (size_t)s.T;
 }
 
 void launch_prefill_logits(const Shape &s, const void *x, const void *wr, double *parts, int32_t *count, hipStream_t st)

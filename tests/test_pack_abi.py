@@ -216,6 +216,14 @@ def test_host_only_entry_points():
     for bad_T in (0, 4097):
         with pytest.raises(B.MoeError):
             B.prefill_workspace_bytes(d, bad_T)
+    # a workspace made for a long prompt holds every shorter one (the phi shape's share of partial logits gets
+    # smaller from 2720 to 2721 tokens)
+    for cfg in synth.CONFIGS:
+        dc = B.LayerDesc.from_config(cfg)
+        sizes = [B.prefill_workspace_bytes(dc, T) for T in range(1, 4097)]
+        assert all(a <= b for a, b in zip(sizes, sizes[1:])), cfg.name
+        sizes = [B.workspace_bytes(dc, T) for T in range(1, min(16, 128 // cfg.top_k) + 1)]
+        assert all(a <= b for a, b in zip(sizes, sizes[1:])), cfg.name
     ds = B.LayerDesc.from_config(synth.config_by_name("dsv2lite"))     # shared experts: room for one chunk
     assert B.prefill_workspace_bytes(ds, 16) > B.workspace_bytes(ds, 16)
     lib = B.load_library()
