@@ -7,7 +7,7 @@
 //                          small calls: route_kernel and prefill_plan_kernel
 //   prefill_stage_kernel   the items (a shared expert's are the tokens in order, in front of the
 //                          others), their tokens gathered into MFMA operand tiles (zero padded), and
-//                          each group's sum, in three bf16 pieces, for the zero points
+//                          each group's sum for the zero points
 //   prefill_tile_kernel<gate/up>  one workgroup per (item, four slices of 32 intermediate rows):
 //                          per slice 64 pre-activations (32 gate, 32 up) x 64 tokens over all of
 //                          H, h = silu(gate) * up written as operand tiles of a bf16 value and
@@ -41,13 +41,19 @@
 // with 333 tokens.)
 //
 // Arithmetic.  Codes become the exact bf16 integers 16 + q; a group's products are summed by the
-// matrix cores (16x16x32 bf16, fp32 accumulate) and enter the totals with one fused multiply-add by
-// the group's scale.  The zero points and the offset 16 are one more contraction, over groups
-// instead of inputs:  total = sum_G s_G acc_G + sum_G (-s_G (z_G + 16)) (sum of the group's x).
+// matrix cores (16x16x32 bf16, fp32 accumulate), starting at -24 (sum of the group's x), so that the sum
+// is that of (q - 8) x, and enter the totals with one fused multiply-add by the group's scale.  What the
+// zero points differ from 8 is one more contraction, over groups instead of inputs:
+//   total = sum_G s_G acc_G + sum_G s_G (z_G - 8) / 24 (-24 x the sum of the group's x).
 // Both factors of the second sum are fp32 numbers cut into three bf16 pieces (exactly; of the nine
-// products of pieces all but the smallest are kept, 2^-32 of the result), eight k positions per
+// products of pieces all but the smallest are kept, 2^-30 of the term), eight k positions per
 // group, so that it runs on the matrix cores as well: a sixteenth of the k-steps (g = 128) instead of
 // a second multiply-add per group on the vector ALU, which the unpacking and the scales already load.
+// It is added every four groups, so that the totals never hold more than four groups' share of it: added up
+// behind the loop, and without the start at -24 sums, the totals of activations with a mean grew to 23.5 s
+// times the sum of all x before they cancelled (x of mean 0.3 sigma, H = 4096, g = 32: error of y 4.0e-5; now
+// 2.5e-6; h >= 0 over I = 8192: 1.1e-4, now 2.8e-6).  The start costs one LDS read per group and token block
+// (mixtral shape, 4096 tokens: 2 % of the call).
 //
 // Bound and figures (gate/up and down kernel; before: two row blocks per wave, operand tiles through
 // registers, offset 128, two multiply-adds per group).  Many tokens per expert: the matrix cores.
@@ -65,6 +71,7 @@ namespace {
 constexpr int kItemTokens = kPrefillChunk;        // 64 = four token blocks of 16
 constexpr int kTileThreads = 256, kTileWaves = 4;
 constexpr int kXcds = 8;
+constexpr float kOffset = -24.f;                  // factor of a stored group sum: takes 16 + q to q - 8
 
 struct TileArgs {
     const char *q, *sz;              // int4 codes / scale(-zero) blobs of the routed experts
@@ -72,7 +79,7 @@ struct TileArgs {
     const PrefillItem *items;
     const int32_t *n_items;
     const char *act0, *act1;         // operand tiles [(item nk + u) 4 + tb] of 1 KiB: x, or h and its remainder
-    const char *act_sums;            // group sums as operand tiles [(item nz + group / 4) 4 + tb]
+    const char *act_sums;            // -24 x group sums, fp32 [(item 4 nz + group) 64 + token]; nz = ceil(groups / 4)
     const char *zeros;               // 4 KiB of zeros
     char *h_hi, *h_lo, *h_sums;      // gate/up: out, the same layouts over I
     float *obuf;                     // down: out [item 64 + token][H]
@@ -126,14 +133,13 @@ template <> struct Entry<false> {
     u32x4 w;
     __device__ static Entry load(const char *p) { return {*reinterpret_cast<const u32x4 *>(p)}; }
     __device__ float scale(int d) const { return (float)__builtin_bit_cast(_Float16, (uint16_t)(w[d] & 0xffff)); }
-    __device__ float zero16(int d) const { return (float)__builtin_bit_cast(_Float16, (uint16_t)(w[d] >> 16)) + 16.f; }
+    __device__ float zero(int d) const { return (float)__builtin_bit_cast(_Float16, (uint16_t)(w[d] >> 16)); }
 };
 template <> struct Entry<true> {
     typedef __attribute__((ext_vector_type(2))) uint32_t u32x2;
     u32x2 w;
     __device__ static Entry load(const char *p) { return {*reinterpret_cast<const u32x2 *>(p)}; }
     __device__ float scale(int d) const { return (float)__builtin_bit_cast(_Float16, (uint16_t)(w[d >> 1] >> (16 * (d & 1)))); }
-    __device__ float zero16(int) const { return 24.f; }
 };
 
 typedef __attribute__((address_space(3))) void *lvoid;
@@ -145,13 +151,13 @@ void prefill_tile_kernel(TileArgs a)
     constexpr int NP = DOWN ? 2 : 1;               // operand planes (h and its remainder)
     constexpr int SK = DOWN ? 2 : 4;               // k-steps per stage
     constexpr int kWin = 8;                        // k-steps of codes in flight
-    constexpr int EW = 8 / KPG < 4 ? 8 / KPG : 4;  // groups of entries in flight
-    constexpr int kBuf = SK * NP * 4 * 1024;       // one stage of operand tiles
+    constexpr int kZeroStages = 4 * KPG / SK;      // stages per four groups
+    constexpr int kSums = SK * NP * 4 * 1024;      // one stage of operand tiles, then the sums of the groups that begin in it
+    constexpr int kBuf = kSums + 1024;
     __shared__ __align__(1024) unsigned char s_x0[kBuf];
     __shared__ __align__(1024) unsigned char s_x1[kBuf];
     __shared__ __align__(1024) unsigned char s_x2[kBuf];
     __shared__ __align__(1024) unsigned char s_x3[kBuf];
-    __shared__ float s_hsum[kTileWaves][kItemTokens];
 
     const int H = a.H, I = a.I;
     const int nk = DOWN ? I / 32 : H / 32, G = nk / KPG, nz = (G + 3) / 4;
@@ -212,9 +218,17 @@ void prefill_tile_kernel(TileArgs a)
         for (int tb = 0; tb < decltype(ntb_c)::value; ++tb)
             __builtin_amdgcn_raw_ptr_buffer_load_lds(rsrc, (lvoid)(dst + tb * 1024), 16, lane * 16, tb * 1024, 0, 0);
     };
+    // the sums of the groups that begin in stage n into buffer j (the waves share them out, or repeat them)
+    constexpr int kBegin = SK > KPG ? SK / KPG : 1;
+    auto request_sums = [&](int n, auto j) {
+        const int grp = n * SK / KPG + wave % kBegin;
+        const char *src = a.act_sums + ((size_t)item * nz * 4 + (grp < 4 * nz ? grp : 4 * nz - 1)) * 256;
+        const auto rsrc = __builtin_amdgcn_make_buffer_rsrc((void *)src, 0, 256, 0x00027000);
+        __builtin_amdgcn_raw_ptr_buffer_load_lds(rsrc, (lvoid)(buffer(j) + kSums + wave % kBegin * 256), 4, lane * 4, 0, 0, 0);
+    };
     // The start of a stage: its operand tiles are in their buffer once this wave's own transfers have landed
     // and the workgroup has met.  Issued behind those transfers (vector memory operations complete in
-    // order): the weights of three stages, and the transfers of two.
+    // order): the weights of three stages, and the transfers of two (and some entries and sums, not counted).
     auto begin_stage = [&](auto ntb_c, auto stage_loads) {
         constexpr int kLater = 3 * decltype(stage_loads)::value + 2 * decltype(ntb_c)::value;
         static_assert(kLater < 64, "vmcnt");
@@ -251,6 +265,7 @@ void prefill_tile_kernel(TileArgs a)
             // holds h of columns 8 chunk .. 8 chunk + 7, the operand layout
             __builtin_amdgcn_s_waitcnt(0x0f70);                       // transfers requested past the end
             __syncthreads();
+            float (*s_hsum)[kItemTokens] = reinterpret_cast<float (*)[kItemTokens]>(s_x0 + kSums);
             float *s_h = reinterpret_cast<float *>(wave == 0 ? s_x0 : wave == 1 ? s_x1 : wave == 2 ? s_x2 : s_x3);
             constexpr int kRow = 36;                                  // 32 columns and 16 bytes against bank conflicts
 #pragma unroll
@@ -303,9 +318,7 @@ void prefill_tile_kernel(TileArgs a)
 #pragma unroll
                     for (int w = 0; w < KPG; ++w) v += s_hsum[(pos * KPG + w) & 3][tok];
                 }
-                const size_t t = (((size_t)item * ((GI + 3) / 4) + gi / 4) * 4 + (tok >> 4)) * 1024 +
-                                 ((gi & 3) * 16 + (tok & 15)) * 16;
-                *reinterpret_cast<u32x4 *>(a.h_sums + t) = sum_operand(v);
+                reinterpret_cast<float *>(a.h_sums)[((size_t)item * ((GI + 3) / 4) * 4 + gi) * kItemTokens + tok] = kOffset * v;
             }
         }
     };
@@ -316,6 +329,7 @@ void prefill_tile_kernel(TileArgs a)
         // two stages: with them those loops spill
         constexpr bool kExits = SK >= KPG;
         constexpr int NTB = decltype(ntb_c)::value;
+        constexpr int EW = KPG == 1 || (KPG == 2 && NTB < 4) ? 4 : 2;     // groups of entries in flight (four more spill)
         f32x4 tot[4][NTB], acc[4][NTB];
 #pragma unroll
         for (int d = 0; d < 4; ++d)
@@ -325,6 +339,36 @@ void prefill_tile_kernel(TileArgs a)
         bf16x8 wb[2][4];                           // operands of k-step k and, as it is unpacked, k + 1
         Entry<SYM> ent[EW];
         float sc[4] = {0.f, 0.f, 0.f, 0.f};        // scales of the group that ended last
+        // The zero points of four groups: lane group c keeps the entries and the sums of the c-th.
+        // (past the tile's last group its entries are read again: the sums there are zeros)
+        Entry<SYM> ze;
+        float zs[NTB];
+        const uint32_t zstep = DOWN ? (uint32_t)(H / 64) * 256 : 256;
+        const char *z_run = szb + (size_t)tile * (DOWN ? 1 : G) * 256, *s_run = a.act_sums + (size_t)item * nz * 1024;
+        auto load_zeros = [&](int q) {
+            if constexpr (!SYM) {
+                const uint32_t grp = 4 * q + c, off = (grp < (uint32_t)G ? grp : G - 1) * zstep + r * 16;
+                ze.w = *reinterpret_cast<const u32x4 *>(z_run + off);
+                const char *sums = s_run + (size_t)(q < nz ? q : nz - 1) * 1024;
+#pragma unroll
+                for (int tb = 0; tb < NTB; ++tb)
+                    zs[tb] = *reinterpret_cast<const float *>(sums + (uint32_t)((c * kItemTokens + r) * 4) + tb * 64);
+            }
+        };
+        auto add_zeros = [&]() {
+            if constexpr (!SYM) {
+                bf16x8 zx[NTB];
+#pragma unroll
+                for (int tb = 0; tb < NTB; ++tb) zx[tb] = __builtin_bit_cast(bf16x8, sum_operand(zs[tb]));
+#pragma unroll
+                for (int d = 0; d < 4; ++d) {
+                    const bf16x8 f = __builtin_bit_cast(bf16x8, factor_operand(ze.scale(d) * ((ze.zero(d) - 8.f) * (-1.f / kOffset))));
+#pragma unroll
+                    for (int tb = NTB - 1; tb >= 0; --tb)
+                        tot[d][tb] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(zx[tb], f, tot[d][tb], 0, 0, 0);
+                }
+            }
+        };
         auto add_scaled = [&](int tb) {
 #pragma unroll
             for (int d = 0; d < 4; ++d) {
@@ -347,13 +391,28 @@ void prefill_tile_kernel(TileArgs a)
             begin_stage(ntb_c, std::integral_constant<int, SK>{});
             const unsigned char *buf = buffer(j);
             u32x4 xa[kA];
+            constexpr int kF = 2;                  // (three spill with g = 64)
+            f32x4 from[kF];                        // where the products of a group start
             auto read = [&](int f) {               // tile f of the stage: k-step, token block, plane
                 const int s = f / NB, tb = f % NB / NP, p = f % NP;
                 xa[f % kA] = *reinterpret_cast<const u32x4 *>(&buf[((s * NP + p) * 4 + tb) * 1024 + lane * 16]);
             };
+            auto read_sums = [&](int f) {
+                const int s = f / NB, tb = f % NB / NP, p = f % NP;
+                if ((kFirst + s) % KPG == 0 && p == 0)
+                    from[f % kF] = *reinterpret_cast<const f32x4 *>(&buf[kSums + (s / KPG) * 256 + (16 * tb + 4 * c) * 4]);
+            };
 #pragma unroll
-            for (int f = 0; f < kA - 1 && f < F; ++f) read(f);
+            for (int f = 0; f < kA - 1 && f < F; ++f) {
+                read(f);
+                if (f < kF - 1) read_sums(f);
+            }
             request(n + 3, std::integral_constant<int, (J + 3) & 3>{}, ntb_c);
+            if constexpr ((J + 3) * SK % KPG == 0) request_sums(n + 3, std::integral_constant<int, (J + 3) & 3>{});
+            if constexpr (J % kZeroStages == 0) {
+                if (kZeroStages <= 4 || n % kZeroStages == 0) add_zeros();
+            }
+            if constexpr (J % kZeroStages == 0) load_zeros(n / kZeroStages + 1);
 #pragma unroll
             for (int f = 0; f < F; ++f) {
                 const int s = f / NB, t = f % NB, tb = t / NP, p = t % NP;
@@ -361,6 +420,7 @@ void prefill_tile_kernel(TileArgs a)
                 const bool begins = pos % KPG == 0, ends = (pos + 1) % KPG == 0;      // of a group
                 __builtin_amdgcn_sched_barrier(0);
                 if (f + kA - 1 < F) read(f + kA - 1);
+                if (f + kF - 1 < F) read_sums(f + kF - 1);
                 if (begins && t == 0) add_scaled(NTB - 1);                            // of the group before
                 if (ends && t == 0) {
                     constexpr int kGroups = 4 * SK / KPG;
@@ -377,19 +437,23 @@ void prefill_tile_kernel(TileArgs a)
                 if (t == NB - 1) win[nx] = load_codes(n * SK + s + 1 + kWin);
 #pragma unroll
                 for (int d = 0; d < 4; ++d)
-                    acc[d][tb] = mfma(xa[f % kA], wb[s & 1][d], begins && p == 0 ? (f32x4){0.f, 0.f, 0.f, 0.f} : acc[d][tb]);
+                    acc[d][tb] = mfma(xa[f % kA], wb[s & 1][d], begins && p == 0 ? from[f % kF] : acc[d][tb]);
                 if (ends && p == 0 && tb > 0) add_scaled(tb - 1);
             }
             __builtin_amdgcn_sched_barrier(0);
         };
         request(0, k0, ntb_c);
+        request_sums(0, k0);
         request(1, k1, ntb_c);
+        if constexpr (SK % KPG == 0) request_sums(1, k1);
         request(2, k2, ntb_c);
+        request_sums(2, k2);
         __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
         for (int i = 0; i < kWin; ++i) win[i] = load_codes(i);
 #pragma unroll
         for (int i = 0; i < EW; ++i) ent[i] = entry_at(i);
+        load_zeros(0);
         // the first stages' transfers have fewer operations behind them than the steady state counts on
         __builtin_amdgcn_sched_barrier(0);
         __builtin_amdgcn_s_waitcnt(0x0070);
@@ -417,37 +481,6 @@ void prefill_tile_kernel(TileArgs a)
         }
         // every last stage ends a group (k-steps past the end are zeros)
         add_scaled(NTB - 1);
-        // the contraction over groups
-        {
-            const char *zs = a.act_sums + (size_t)item * nz * 4096 + lane * 16;
-            u32x4 zx[2][NTB];
-            Entry<SYM> ze[2];
-            auto load_sums = [&](int q, int b) {
-                const int qq = q < nz ? q : nz - 1;
-#pragma unroll
-                for (int tb = 0; tb < NTB; ++tb) zx[b][tb] = *reinterpret_cast<const u32x4 *>(zs + ((size_t)qq * 4 + tb) * 1024);
-                ze[b] = entry_at(4 * qq + c);
-            };
-            auto add_sums = [&](int b) {
-#pragma unroll
-                for (int d = 0; d < 4; ++d) {
-                    const bf16x8 f = __builtin_bit_cast(bf16x8, factor_operand(-ze[b].scale(d) * ze[b].zero16(d)));
-#pragma unroll
-                    for (int tb = 0; tb < NTB; ++tb) tot[d][tb] = mfma(zx[b][tb], f, tot[d][tb]);
-                }
-            };
-            load_sums(0, 0);
-            load_sums(1, 1);
-            int q = 0;
-            for (; q + 1 < nz; q += 2) {
-                add_sums(0);
-                load_sums(q + 2, 0);
-                add_sums(1);
-                load_sums(q + 3, 1);
-            }
-            if (q < nz) add_sums(0);
-        }
-
         finish(ntb_c, tot);
     };
 
@@ -532,7 +565,7 @@ void prefill_tile_kernel(TileArgs a)
 
 // Gathers the tokens of token block (item, tb) into operand tiles [(item nk + u) 4 + tb]: lane
 // (token, chunk) of tile u holds x[token][32 u + 8 chunk .. + 7]; positions past the item's count
-// hold zeros.  (The shared experts read one copy.)  Also the group sums as operand tiles [(item nz + group / 4) 4 + tb].  One wave per
+// hold zeros.  (The shared experts read one copy.)  Also the group sums x -24, [(item 4 nz + group) 64 + token].  One wave per
 // (block, four tiles): 128 inputs, whole groups.
 // Which item that is: kPlanned: prefill_plan_kernel has written the items; else it follows from the experts'
 // counts (the shared experts' S ceil(T / 64) items come first, then every expert's, in chunks of 64; expert
@@ -621,8 +654,7 @@ void prefill_stage_kernel(const uint16_t *__restrict__ x, const int32_t *__restr
             else if constexpr (KPG == 2) v = chunk == 0 ? s[0] + s[1] : s[2] + s[3];
             else v = chunk == 0 ? s[0] : chunk == 1 ? s[1] : chunk == 2 ? s[2] : s[3];
         }
-        *reinterpret_cast<u32x4 *>(sums + (((size_t)item * ((G + 3) / 4) + gi / 4) * 4 + tb) * 1024 +
-                                   ((gi & 3) * 16 + tok16) * 16) = sum_operand(v);
+        reinterpret_cast<float *>(sums)[((size_t)item * ((G + 3) / 4) * 4 + gi) * kItemTokens + 16 * tb + tok16] = kOffset * v;
     }
 }
 
@@ -719,9 +751,9 @@ PrefillBuffers prefill_buffers(const moe_layer_desc &d, int max_items)
     PrefillBuffers b;
     const size_t m = (size_t)max_items;
     b.xt = m * (d.hidden / 32) * 4096;
-    b.x_sums = m * ((d.hidden / d.group_size + 3) / 4) * 4096;
+    b.x_sums = m * ((d.hidden / d.group_size + 3) / 4) * 1024;
     b.h_plane = m * (d.inter / 32) * 4096;
-    b.h_sums = m * ((d.inter / d.group_size + 3) / 4) * 4096;
+    b.h_sums = m * ((d.inter / d.group_size + 3) / 4) * 1024;
     b.zeros = 4096;
     b.obuf = m * kItemTokens * d.hidden * 4;
     return b;
