@@ -281,7 +281,7 @@ int moe_draft_layer_int4_noalloc(moe_ctx *ctx, const moe_layer_desc *desc,
  * int4 layer and choose its backend for the prefill stage as well as the decode stage (the
  * figure comparing backends there).  Same mathematics, arguments and outputs as moe_draft_layer_int4 for 1 <= T <=
  * MOE_MAX_PREFILL_TOKENS tokens.  All tokens are routed first, the assignments are grouped by
- * expert and cut into work items of up to 64, and every expert's weights are streamed once per
+ * expert and cut into work items of up to 64 (small calls 32), and every expert's weights are streamed once per
  * item (a token-by-token loop streams them once per assignment): a gate/up contraction per
  * (item, 128 intermediate rows) leaves h in the workspace, a down contraction per (item, 256
  * output rows) leaves each assignment's output there, and a last kernel adds up a token's k

@@ -441,18 +441,18 @@ static PrefillLayout prefill_layout(const moe_layer_desc &d, int T)
 {
     PrefillLayout L;
     const size_t n = (size_t)T * d.top_k;
-    // sum over experts of ceil(count / chunk) <= n / chunk + number of experts that occur
-    L.max_items = (int)(n / kPrefillChunk + ((size_t)d.n_experts < n ? (size_t)d.n_experts : n)) +
-                  d.n_shared * ((T + kPrefillChunk - 1) / kPrefillChunk);
-    const PrefillBuffers B = prefill_buffers(d, L.max_items);
+    const Shape s = make_shape(&d, T);
+    L.max_items = prefill_max_items(s);
+    const size_t room = prefill_item_room(s);
+    const PrefillBuffers B = prefill_buffers(d, room);
     size_t o = 0;
     L.w_all = o;   o += align256(n * 4);
     L.count = o;   o += align256((size_t)d.n_experts * 4);
     L.list = o;    o += align256((size_t)d.n_experts * T * 4);
-    L.parts = o;   o += align256(prefill_logit_rows(make_shape(&d, T)) * d.n_experts * 8);
+    L.parts = o;   o += align256(prefill_logit_rows(s) * d.n_experts * 8);
     L.slot_of = o; o += align256(n * 4);
     L.n_items = o; o += 256;
-    L.items = o;   o += align256((size_t)L.max_items * sizeof(PrefillItem));
+    L.items = o;   o += align256(room * sizeof(PrefillItem));
     L.xt = o;      o += align256(B.xt);
     L.x_sums = o;  o += align256(B.x_sums);
     L.h_hi = o;    o += align256(B.h_plane);

@@ -68,7 +68,7 @@ namespace moespeq {
 
 namespace {
 
-constexpr int kItemTokens = kPrefillChunk;        // 64 = four token blocks of 16
+constexpr int kItemTokens = 64;                   // slots of an item: four token blocks of 16
 constexpr int kTileThreads = 256, kTileWaves = 4;
 constexpr int kXcds = 8;
 constexpr float kOffset = -24.f;                  // factor of a stored group sum: takes 16 + q to q - 8
@@ -568,16 +568,16 @@ void prefill_tile_kernel(TileArgs a)
 // hold zeros.  (The shared experts read one copy.)  Also the group sums x -24, [(item 4 nz + group) 64 + token].  One wave per
 // (block, four tiles): 128 inputs, whole groups.
 // Which item that is: kPlanned: prefill_plan_kernel has written the items; else it follows from the experts'
-// counts (the shared experts' S ceil(T / 64) items come first, then every expert's, in chunks of 64; expert
+// counts (the shared experts' S ceil(T / chunk) items come first, then every expert's; expert
 // e's assignments are list[e T ..]); each workgroup sums the counts up for itself, the first one also writes the items,
 // and a block's first workgroup the slots of its assignments.  The first workgroup also writes the tile of zeros.
 template <int KPG, bool kPlanned>
 __global__ __launch_bounds__(256)
 void prefill_stage_kernel(const uint16_t *__restrict__ x, const int32_t *__restrict__ count, const int32_t *__restrict__ list,
                           PrefillItem *__restrict__ items, int32_t *__restrict__ n_items, int32_t *__restrict__ slot_of,
-                          char *__restrict__ xt, char *__restrict__ sums, char *__restrict__ zeros, int T, int H, int k, int E, int S)
+                          char *__restrict__ xt, char *__restrict__ sums, char *__restrict__ zeros, int T, int H, int k, int E, int S, int chunk)
 {
-    const int item = blockIdx.x >> 2, tb = blockIdx.x & 3, tid = threadIdx.x;
+    const int blocks = chunk >> 4, item = blockIdx.x / blocks, tb = blockIdx.x % blocks, tid = threadIdx.x;
     const bool first = blockIdx.x == 0 && blockIdx.y == 0;
     if (first) *reinterpret_cast<u32x4 *>(zeros + tid * 16) = (u32x4){0u, 0u, 0u, 0u};
     PrefillItem it;
@@ -588,10 +588,10 @@ void prefill_stage_kernel(const uint16_t *__restrict__ x, const int32_t *__restr
     } else {
         __shared__ int32_t s_end[4];                     // per wave: items of its 64 experts
         __shared__ PrefillItem s_item;
-        const int chunks = (T + kItemTokens - 1) / kItemTokens;
+        const int chunks = (T + chunk - 1) / chunk;
         if (tid == 0) s_item = PrefillItem{0, 0, 0, -1};
         // thread e: expert e's items are [begin, begin + mine)
-        const int cnt = tid < E ? count[tid] : 0, mine = (cnt + kItemTokens - 1) / kItemTokens;
+        const int cnt = tid < E ? count[tid] : 0, mine = (cnt + chunk - 1) / chunk;
         int incl = mine;
 #pragma unroll
         for (int d = 1; d < 64; d <<= 1) {
@@ -606,11 +606,11 @@ void prefill_stage_kernel(const uint16_t *__restrict__ x, const int32_t *__restr
             total += s_end[w];
         }
         auto chunk_of = [&](int j) {                     // of this thread's expert
-            return PrefillItem{tid, tid * T + j * kItemTokens, cnt - j * kItemTokens < kItemTokens ? cnt - j * kItemTokens : kItemTokens, begin + j};
+            return PrefillItem{tid, tid * T + j * chunk, cnt - j * chunk < chunk ? cnt - j * chunk : chunk, begin + j};
         };
         auto shared_item = [&](int i) {
             const int j = i % chunks;
-            return PrefillItem{E + i / chunks, j * kItemTokens, T - j * kItemTokens < kItemTokens ? T - j * kItemTokens : kItemTokens, j};
+            return PrefillItem{E + i / chunks, j * chunk, T - j * chunk < chunk ? T - j * chunk : chunk, j};
         };
         if (item >= begin && item < begin + mine) s_item = chunk_of(item - begin);
         if (tid == 0 && item < S * chunks) s_item = shared_item(item);
@@ -628,7 +628,7 @@ void prefill_stage_kernel(const uint16_t *__restrict__ x, const int32_t *__restr
     if (16 * tb >= it.cnt || it.src != item) return;
     const int nk = H / 32, u4 = blockIdx.y * 4 + (threadIdx.x >> 6);
     if (u4 * 4 >= nk) return;
-    const int lane = threadIdx.x & 63, tok16 = lane & 15, chunk = lane >> 4, pos = 16 * tb + tok16;
+    const int lane = threadIdx.x & 63, tok16 = lane & 15, part = lane >> 4, pos = 16 * tb + tok16;
     const int at = it.first + (pos < it.cnt ? pos : 0);
     const int token = it.expert < E ? list[at] / k : at;
     float s[4];
@@ -636,23 +636,23 @@ void prefill_stage_kernel(const uint16_t *__restrict__ x, const int32_t *__restr
     for (int j = 0; j < 4; ++j) {
         const int u = u4 * 4 + j;
         u32x4 v = {0u, 0u, 0u, 0u};
-        if (u < nk && pos < it.cnt) v = *reinterpret_cast<const u32x4 *>(x + (size_t)token * H + 32 * u + 8 * chunk);
+        if (u < nk && pos < it.cnt) v = *reinterpret_cast<const u32x4 *>(x + (size_t)token * H + 32 * u + 8 * part);
         if (u < nk) *reinterpret_cast<u32x4 *>(xt + (((size_t)item * nk + u) * 4 + tb) * 1024 + lane * 16) = v;
         s[j] = ((bf16_lo(v.x) + bf16_hi(v.x)) + (bf16_lo(v.y) + bf16_hi(v.y))) +
                ((bf16_lo(v.z) + bf16_hi(v.z)) + (bf16_lo(v.w) + bf16_hi(v.w)));
         s[j] += __shfl_xor(s[j], 16);
         s[j] += __shfl_xor(s[j], 32);
     }
-    // group `chunk` of this wave's 4 / KPG groups; the wave with the last inputs also clears what is left
+    // group `part` of this wave's 4 / KPG groups; the wave with the last inputs also clears what is left
     // of the last tile of four groups
-    const int G = nk / KPG, gi = u4 * (4 / KPG) + chunk;
-    const bool real = chunk < 4 / KPG && gi < G, last = u4 * 4 + 4 >= nk;
+    const int G = nk / KPG, gi = u4 * (4 / KPG) + part;
+    const bool real = part < 4 / KPG && gi < G, last = u4 * 4 + 4 >= nk;
     if (real || (last && gi >= G && gi / 4 == (G - 1) / 4)) {
         float v = 0.f;
         if (real) {
             if constexpr (KPG == 4) v = (s[0] + s[1]) + (s[2] + s[3]);
-            else if constexpr (KPG == 2) v = chunk == 0 ? s[0] + s[1] : s[2] + s[3];
-            else v = chunk == 0 ? s[0] : chunk == 1 ? s[1] : chunk == 2 ? s[2] : s[3];
+            else if constexpr (KPG == 2) v = part == 0 ? s[0] + s[1] : s[2] + s[3];
+            else v = part == 0 ? s[0] : part == 1 ? s[1] : part == 2 ? s[2] : s[3];
         }
         reinterpret_cast<float *>(sums)[((size_t)item * ((G + 3) / 4) * 4 + gi) * kItemTokens + 16 * tb + tok16] = kOffset * v;
     }
@@ -660,19 +660,19 @@ void prefill_stage_kernel(const uint16_t *__restrict__ x, const int32_t *__restr
 
 // Sorts the n = T k assignments by expert (the order inside an expert is arbitrary: no result
 // depends on it, a row's sums do not depend on the other rows of its item), cuts every expert's
-// run into items of at most 64 and records the slot (item x 64 + position) of every assignment.
-// The first S ceil(T / 64) items are the shared experts', over the tokens in order.  One workgroup.
+// run into items of at most `chunk` and records the slot (item x 64 + position) of every assignment.
+// The first S ceil(T / chunk) items are the shared experts', over the tokens in order.  One workgroup.
 __global__ __launch_bounds__(1024)
-void prefill_plan_kernel(const int32_t *__restrict__ ids, int n, int E, int T, int S,
+void prefill_plan_kernel(const int32_t *__restrict__ ids, int n, int E, int T, int S, int chunk,
                          int32_t *__restrict__ list, int32_t *__restrict__ slot_of,
                          PrefillItem *__restrict__ items, int32_t *__restrict__ n_items)
 {
     __shared__ int32_t s_count[MOE_MAX_EXPERTS], s_off[MOE_MAX_EXPERTS], s_fill[MOE_MAX_EXPERTS],
         s_item0[MOE_MAX_EXPERTS];
-    const int chunks = (T + kItemTokens - 1) / kItemTokens;
+    const int chunks = (T + chunk - 1) / chunk;
     for (int i = threadIdx.x; i < S * chunks; i += blockDim.x) {
         const int j = i % chunks;
-        items[i] = PrefillItem{E + i / chunks, j * kItemTokens, T - j * kItemTokens < kItemTokens ? T - j * kItemTokens : kItemTokens, j};
+        items[i] = PrefillItem{E + i / chunks, j * chunk, T - j * chunk < chunk ? T - j * chunk : chunk, j};
     }
     for (int e = threadIdx.x; e < E; e += blockDim.x) { s_count[e] = 0; s_fill[e] = 0; }
     __syncthreads();
@@ -684,7 +684,7 @@ void prefill_plan_kernel(const int32_t *__restrict__ ids, int n, int E, int T, i
             s_off[e] = off;
             s_item0[e] = item;
             off += s_count[e];
-            item += (s_count[e] + kItemTokens - 1) / kItemTokens;
+            item += (s_count[e] + chunk - 1) / chunk;
         }
         *n_items = item;
     }
@@ -693,14 +693,14 @@ void prefill_plan_kernel(const int32_t *__restrict__ ids, int n, int E, int T, i
         const int e = ids[i];
         const int idx = atomicAdd(&s_fill[e], 1);
         list[s_off[e] + idx] = i;
-        slot_of[i] = (s_item0[e] + idx / kItemTokens) * kItemTokens + idx % kItemTokens;
+        slot_of[i] = (s_item0[e] + idx / chunk) * kItemTokens + idx % chunk;
     }
     for (int e = threadIdx.x; e < E; e += blockDim.x) {
         const int cnt = s_count[e];
-        for (int j = 0; j * kItemTokens < cnt; ++j) {
+        for (int j = 0; j * chunk < cnt; ++j) {
             PrefillItem it;
-            it.expert = e; it.first = s_off[e] + j * kItemTokens;
-            it.cnt = cnt - j * kItemTokens < kItemTokens ? cnt - j * kItemTokens : kItemTokens;
+            it.expert = e; it.first = s_off[e] + j * chunk;
+            it.cnt = cnt - j * chunk < chunk ? cnt - j * chunk : chunk;
             it.src = s_item0[e] + j;
             items[s_item0[e] + j] = it;
         }
@@ -710,7 +710,7 @@ void prefill_plan_kernel(const int32_t *__restrict__ ids, int n, int E, int T, i
 // y[t][:] = sum_j w[t k + j] * obuf[slot_of[t k + j]][:], j ascending, then the shared experts' rows
 __global__ __launch_bounds__(256)
 void prefill_combine_kernel(const float *__restrict__ obuf, const int32_t *__restrict__ slot_of,
-                            const float *__restrict__ w_all, float *__restrict__ y, int H, int k, int S)
+                            const float *__restrict__ w_all, float *__restrict__ y, int H, int k, int S, int chunk)
 {
     const int t = blockIdx.x, col = (blockIdx.y * 256 + threadIdx.x) * 4;
     if (col >= H) return;
@@ -722,8 +722,9 @@ void prefill_combine_kernel(const float *__restrict__ obuf, const int32_t *__res
 #pragma unroll
         for (int i = 0; i < 4; ++i) acc[i] = fmaf(w, v[i], acc[i]);
     }
-    const int slots = (int)(gridDim.x + kItemTokens - 1) / kItemTokens * kItemTokens;      // of one shared expert
-    for (int sh = 0; sh < S; ++sh) acc += *reinterpret_cast<const f32x4 *>(obuf + ((size_t)sh * slots + t) * H + col);
+    const int chunks = ((int)gridDim.x + chunk - 1) / chunk;                               // items of one shared expert
+    for (int sh = 0; sh < S; ++sh)
+        acc += *reinterpret_cast<const f32x4 *>(obuf + ((size_t)(sh * chunks + t / chunk) * kItemTokens + t % chunk) * H + col);
     *reinterpret_cast<f32x4 *>(y + (size_t)t * H + col) = acc;
 }
 
@@ -746,10 +747,37 @@ void launch_tile(const TileArgs &t, bool sym, int g, int tiles, int max_items, h
 
 }  // namespace
 
-PrefillBuffers prefill_buffers(const moe_layer_desc &d, int max_items)
+// workgroups of a tile launch per item, the larger of the two
+static int prefill_columns(const Shape &s)
+{
+    const int gate = (s.I / 32 + kTileWaves - 1) / kTileWaves, down = (s.H / 64 + kTileWaves - 1) / kTileWaves;
+    return gate > down ? gate : down;
+}
+
+// sum over experts of ceil(count / chunk) <= n / chunk + number of experts that occur
+static int items_of(const Shape &s, int chunk)
+{
+    const int n = s.T * s.k;
+    return n / chunk + (s.E < n ? s.E : n) + s.S * ((s.T + chunk - 1) / chunk);
+}
+
+// A launch that leaves compute units empty gets items of 32 tokens: as long as those are at most one workgroup per
+// unit.  us per call, items of 64 / of 32 (workgroups of 32, upper bound): H = 256, I = 512, E = 8, k = 2, 421 tokens
+// (136) 38.5 / 32.7; H = 384, I = 384, k = 5, 274 tokens (150) 39.2 / 34.4; H = 2048, I = 1408, E = 4, a shared
+// expert, 200 tokens (253) 72.5 / 60.2, 400 tokens (462) 78.7 / 85.2.  With more columns 32 still wins beyond the line
+// (H = 1024, I = 2048, 300 tokens, 416: 65.8 / 55.9), the more evenly the 64s fill the units the less.
+constexpr int kSmallGrid = 256;
+int prefill_chunk(const Shape &s) { return (long)prefill_columns(s) * items_of(s, 32) <= kSmallGrid ? 32 : 64; }
+int prefill_max_items(const Shape &s) { return items_of(s, prefill_chunk(s)); }
+size_t prefill_item_room(const Shape &s)
+{
+    const int items = prefill_max_items(s), small = kSmallGrid / prefill_columns(s);
+    return prefill_chunk(s) == 32 || items > small ? items : small;
+}
+
+PrefillBuffers prefill_buffers(const moe_layer_desc &d, size_t m)
 {
     PrefillBuffers b;
-    const size_t m = (size_t)max_items;
     b.xt = m * (d.hidden / 32) * 4096;
     b.x_sums = m * ((d.hidden / d.group_size + 3) / 4) * 1024;
     b.h_plane = m * (d.inter / 32) * 4096;
@@ -767,15 +795,16 @@ bool prefill_small(const Shape &s) { return (long)s.T * ((long)s.E * s.H + 1024L
 
 void launch_prefill_plan(const Shape &s, const int32_t *ids, const PrefillCall &p, hipStream_t st)
 {
-    launch(prefill_plan_kernel, dim3(1), dim3(1024), 0, st, ids, s.T * s.k, s.E, s.T, s.S, (int32_t *)p.list, p.slot_of, p.items, p.n_items);
+    launch(prefill_plan_kernel, dim3(1), dim3(1024), 0, st, ids, s.T * s.k, s.E, s.T, s.S, prefill_chunk(s), (int32_t *)p.list, p.slot_of, p.items, p.n_items);
 }
 
 void launch_prefill_stage(const Shape &s, const PrefillCall &p, int max_items, hipStream_t st)
 {
-    const dim3 grid(max_items * 4, (s.H / 32 + 15) / 16), block(256);
+    const int chunk = prefill_chunk(s);
+    const dim3 grid(max_items * (chunk / 16), (s.H / 32 + 15) / 16), block(256);
     auto go = [&](auto kernel) {
         launch(kernel, grid, block, 0, st, (const uint16_t *)p.x, p.count, p.list, p.items, p.n_items, p.slot_of, (char *)p.xt,
-               (char *)p.x_sums, (char *)p.zeros, s.T, s.H, s.k, s.E, s.S);
+               (char *)p.x_sums, (char *)p.zeros, s.T, s.H, s.k, s.E, s.S, chunk);
     };
     auto of_group = [&](auto planned) {
         constexpr bool kPlanned = decltype(planned)::value;
@@ -815,7 +844,7 @@ void launch_prefill_down(const Shape &s, const PrefillCall &p, int max_items, hi
 void launch_prefill_combine(const Shape &s, const PrefillCall &p, hipStream_t st)
 {
     launch(prefill_combine_kernel, dim3(s.T, (s.H / 4 + 255) / 256), dim3(256), 0, st,
-           (const float *)p.obuf, p.slot_of, p.w_all, p.y, s.H, s.k, s.S);
+           (const float *)p.obuf, p.slot_of, p.w_all, p.y, s.H, s.k, s.S, prefill_chunk(s));
 }
 
 }  // namespace moespeq

@@ -108,11 +108,13 @@ void launch_union(const int32_t *ids, int n_ids, int E, const int32_t *slot,
                   uint64_t *mask, int32_t *list, int32_t *n_list,
                   int32_t *missing, int32_t *n_missing, hipStream_t st);
 
-// Work item of the draft call over a long run of tokens: up to kPrefillChunk assignments of one
+// Work item of the draft call over a long run of tokens: up to prefill_chunk(s) assignments of one
 // expert, list[first .. first + cnt), or (expert >= E: shared expert) tokens [first, first + cnt).
 // Item i owns slots [64 i, 64 i + cnt); src: the item whose operand tiles of x it reads.
-constexpr int kPrefillChunk = 64;
 struct PrefillItem { int32_t expert, first, cnt, src; };
+int prefill_chunk(const Shape &s);         // tokens of a full item: 64, or 32 for small calls
+int prefill_max_items(const Shape &s);     // at most that many items
+size_t prefill_item_room(const Shape &s);  // items the workspace has room for: no fewer than any call with fewer tokens needs
 
 // draft_int4.hip (a call of 2 to 8 tokens) and draft_slice.hip (a call of one token)
 struct DraftFusedArgs {
@@ -142,9 +144,9 @@ void launch_zero(void *p, size_t bytes, hipStream_t st);
 void launch_stream_read(const void *src, size_t bytes, int workgroups, void *sink, hipStream_t st);
 
 // draft_prefill.hip: a routed run of tokens.  Byte sizes of the buffers a call with at most
-// max_items work items needs (h_plane: each of the two planes of h), then the launches in order.
+// `items` work items needs (h_plane: each of the two planes of h), then the launches in order.
 struct PrefillBuffers { size_t xt, x_sums, h_plane, h_sums, zeros, obuf; };
-PrefillBuffers prefill_buffers(const moe_layer_desc &d, int max_items);
+PrefillBuffers prefill_buffers(const moe_layer_desc &d, size_t items);
 struct PrefillCall {
     const void *x;                     // [T,H] bf16
     const void *q, *sz; size_t stride_q, stride_sz; int symmetric;

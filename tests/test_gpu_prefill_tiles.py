@@ -1,7 +1,7 @@
 """The grouped contraction of the prefill call at the edges of its tiles: k-steps that do not fill a
 stage, group sums that do not fill a tile of four groups, slices and row tiles that do not fill a
-workgroup's four, and items of 1 to 64 tokens (whole and ragged token blocks, several items per
-expert), for every group size and both weight formats."""
+workgroup's four, and items of 1 to 32 (small calls) or 64 tokens (whole and ragged token blocks,
+several items per expert), for every group size and both weight formats."""
 import numpy as np
 import pytest
 import torch
@@ -44,6 +44,39 @@ def test_prefill_tile_edges(cfg):
             torch.cuda.synchronize()
             assert np.array_equal(to_np(r["ids"]), ref["ids"][:T])
             assert rel_err(to_np(r["y"]), ref["y"][:T]) <= TOL_DRAFT
+    ctx.close()
+
+
+WIDE = [
+    #            idx  name    H    E   I    k   g  S  renorm    (enough weight columns for items of 64 tokens)
+    LayerConfig(76, "w32", 384, 5, 1280, 2, 32, 0, 1),     # 12 and 40 groups, 6 row tiles
+    LayerConfig(77, "w64", 256, 5, 1344, 2, 64, 1, 1),     # 4 and 21 groups, 42 slices, a shared expert
+    LayerConfig(78, "w128", 640, 5, 1152, 2, 128, 0, 1),   # 5 and 9 groups, 36 slices, 10 row tiles
+    LayerConfig(79, "v128", 256, 5, 1280, 2, 128, 2, 0),   # 2 and 10 groups, both formats
+]
+
+
+@pytest.mark.parametrize("cfg", WIDE, ids=[c.name for c in WIDE])
+def test_prefill_long_items(cfg):
+    """Items of up to 64 tokens: the experts' counts leave items of one to four token blocks."""
+    ctx = B.Context(0)
+    blocks = set()
+    for symmetric in (False, True):
+        if symmetric and B.int4_expert_scale_bytes(B.LayerDesc.from_config(cfg)) == 0:
+            continue
+        L = synth.make_layer(cfg, 0, symmetric=symmetric)
+        A = oracle_arrays(L)
+        D = DeviceLayer(ctx, cfg, L, max_tokens=8, verify=False, symmetric=symmetric)
+        x = tokens_with_clear_routing(cfg, A, 477, step=9, kind="iid")
+        ref = oracle_draft(A, x)
+        for T in (400, 431, 477):
+            say("prefill", cfg.name, "symmetric" if symmetric else "", "T", T)
+            r = D.prefill(x[:T].cuda())
+            torch.cuda.synchronize()
+            assert np.array_equal(to_np(r["ids"]), ref["ids"][:T])
+            assert rel_err(to_np(r["y"]), ref["y"][:T]) <= TOL_DRAFT
+            blocks |= {(c % 64 + 15) // 16 for c in np.bincount(ref["ids"][:T].ravel(), minlength=5)}
+    assert blocks >= {1, 2, 3, 4}
     ctx.close()
 
 
