@@ -428,14 +428,21 @@ void slice_kernel(const Shape &s, const DraftFusedArgs &d, F go)
 
 }  // namespace
 
-// Whether a one-token call runs its shared experts in its own launch: up to three 16-row items per compute unit, fewer
-// than one per 256 of H where that is more.  Beyond, items are many and short, a workgroup's start costs more
-// than two launches, and the bf16 kernels take them (S = 4, us per call inside / in their own launches: H = 640,
-// I = 2816 37.5 / 47.7, I = 8192 97.7 / 83; H = 2048, I = 1408 30.3 / 42.4, I = 8192 115 / 126).
+// Whether a one-token call runs its shared experts in its own launch: up to three 16-row items per compute unit, or
+// one per 256 of H where that is more.  Beyond, items are many and short, a workgroup's start costs more
+// than two launches, and the bf16 kernels take them.  us per call inside / in their own launches (16 experts, k = 4,
+// 256 units; H of 256 to 4096, one, two and four shared experts were measured):
+//   items per unit  H = 256      H = 1024     H = 2048      H = 4096
+//   1.4 (S = 4)     19.4 / 21.4  22.8 / 25.6  28.8 / 32.9   37.4 / 47.0
+//   2.8 (S = 2)     40.0 / 44.0  45.6 / 50.0  54.0 / 61.9   76.8 / 89.4
+//   2.8 (S = 4)     31.3 / 31.3  37.0 / 38.5  45.2 / 50.8   64.8 / 75.5
+//   4   (S = 2)     56.3 / 52.4  62.0 / 61.2  73.9 / 77.7   103.8 / 120.5
+//   5.5 (S = 4)     57.5 / 46.7  66.0 / 58.2  77.4 / 81.2   122.1 / 131.6
+//   8   (S = 4)     81.7 / 56.0  87.7 / 74.1  102.7 / 107.5 166.0 / 183.6
 bool draft_shared_inside(const Shape &s, int n_cu)
 {
     const long items = (long)s.S * (s.I / 16);
-    return s.T == 1 && s.S > 0 && (items <= 3L * n_cu || items < (long)n_cu * s.H / 256);
+    return s.T == 1 && s.S > 0 && (items <= 3L * n_cu || items * 256 <= (long)n_cu * s.H);
 }
 
 // one token: router inside the launch, one workgroup per (selected expert, slice) and per 16 rows of

@@ -12,7 +12,7 @@ import synth
 from oracle import oracle as orc
 from synth.configs import LayerConfig
 from tests.common import oracle_arrays, oracle_draft, rel_err
-from tests.gpu_common import TOL_DRAFT, say, to_np, tokens_with_clear_routing
+from tests.gpu_common import TOL_DRAFT, build_layer, say, to_np, tokens_with_clear_routing
 
 pytestmark = pytest.mark.gpu
 
@@ -90,4 +90,27 @@ def test_one_token_with_many_items(H, k, g, S):
             torch.cuda.synchronize()
             assert np.array_equal(to_np(r["ids"]), ref["ids"][t0:t1])
             assert rel_err(to_np(r["y"]), ref["y"][t0:t1]) <= TOL_DRAFT
+    ctx.close()
+
+
+def test_shared_experts_on_the_line_run_inside():
+    """As many 16-row items per compute unit as H has 256s (1024 on 256 units): the call's own launch runs the
+    shared experts, no launch of the bf16 kernels is made."""
+    cfg = LayerConfig(74, "line", 1024, 2, 8192, 1, 128, 2, 1)
+    if torch.cuda.get_device_properties(0).multi_processor_count != 256:
+        pytest.skip("the line is stated for 256 compute units")
+    ctx = B.Context(0)
+    L = build_layer(cfg)
+    A = oracle_arrays(L)
+    D = DeviceLayer(ctx, cfg, L, max_tokens=1, verify=False)
+    x = tokens_with_clear_routing(cfg, A, 1, step=2)
+    ref = oracle_draft(A, x)
+    ctx.profile_enable(True)
+    r = D.draft(x.cuda())
+    torch.cuda.synchronize()
+    launches = {name: n for name, (_, n) in ctx.profile_read().items()}
+    ctx.profile_enable(False)
+    assert np.array_equal(to_np(r["ids"]), ref["ids"])
+    assert rel_err(to_np(r["y"]), ref["y"]) <= TOL_DRAFT
+    assert launches["draft_fused_kernel"] == 1 and launches["bf16_gateup_kernel"] == 0
     ctx.close()
