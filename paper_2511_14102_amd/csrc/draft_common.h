@@ -283,13 +283,13 @@ __device__ inline uint32_t draw_ticket(uint32_t *counter) {
 }
 __device__ inline uint32_t ticket_members(uint32_t b, uint32_t grid) { return (grid - b % kTicketGroups + kTicketGroups - 1) / kTicketGroups; }
 __device__ inline uint32_t ticket_groups(uint32_t grid) { return grid < (uint32_t)kTicketGroups ? grid : (uint32_t)kTicketGroups; }
-// the calling wave puts slots and tickets back to idle
-__device__ inline void reset_exchange(const FusedArgs &a) {
-    const int lane = threadIdx.x & 63, n = a.T * a.E;
+// `threads` threads, of which the calling one is number `me`, put slots and tickets back to idle
+__device__ inline void reset_exchange(const FusedArgs &a, int me, int threads) {
+    const int n = a.T * a.E;
     for (int rep = 0; rep < kReplicas; ++rep)
-        for (int i = lane; i < n; i += 64)
+        for (int i = me; i < n; i += threads)
             __hip_atomic_store(a.slots + (size_t)rep * a.replica_stride + 2 * (size_t)i + 1, 0ull, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-    if (lane <= kTicketGroups) __hip_atomic_store(a.tickets + lane, 0u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    if (me <= kTicketGroups) __hip_atomic_store(a.tickets + me, 0u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
 }
 
 // The softmax of a token whose logits and ranks the calling wave left in LDS: confidences and routing

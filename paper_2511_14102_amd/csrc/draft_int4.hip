@@ -66,7 +66,7 @@ void draft_stream_kernel(const uint16_t *__restrict__ xin, const FusedArgs a)
     __shared__ int32_t s_row_a[2][MT];          // assignment index of each row (token slot) of the item
     __shared__ int32_t s_cnt[2];
     __shared__ float s_hsum[2][MT];
-    __shared__ int32_t s_flag;
+    __shared__ int32_t s_flag, s_last;
     __shared__ int32_t s_list[MOE_MAX_EXPERTS];  // the call's distinct experts, ascending
     __shared__ float s_red[kWaves][MT][64];      // partial gate/up sums [wave][token slot][row]
     __shared__ __attribute__((aligned(16))) uint16_t s_hhi[MT][32], s_hlo[MT][32];
@@ -497,8 +497,11 @@ void draft_stream_kernel(const uint16_t *__restrict__ xin, const FusedArgs a)
         __syncthreads();
     }
 
-    // ---- 4. the holder of the last ticket puts the workspace back to idle
-    if (wave == kWaves - 1 && __any(ticket2 == ticket_groups(gridDim.x) - 1)) reset_exchange(a);
+    // ---- 4. the workgroup that holds the last ticket puts the workspace back to idle, all waves together (8 tokens x
+    // 128 experts are 16384 stores: 256 rounds of one wave)
+    if (tid == kThreads - 64) s_last = ticket2 == ticket_groups(gridDim.x) - 1;
+    __syncthreads();
+    if (s_last) reset_exchange(a, tid, kThreads);
 
     // ---- 5. workgroup 0 reports the routing (and the plan the shared-expert kernels read)
     if (blockIdx.x != 0) return;

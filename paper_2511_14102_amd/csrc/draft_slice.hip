@@ -82,7 +82,7 @@ void draft_fused_kernel(const uint16_t *__restrict__ xin, const FusedArgs a)
         if (lane == 0 && ticket == ticket_members(b, gridDim.x) - 1) ticket2 = draw_ticket(a.tickets + kTicketGroups);
     };
     auto reset_if_last = [&]() {
-        if (__any(ticket2 == ticket_groups(gridDim.x) - 1)) reset_exchange(a);
+        if (__any(ticket2 == ticket_groups(gridDim.x) - 1)) reset_exchange(a, lane, 64);
     };
 
     if constexpr (SHARED) if (shared) {
