@@ -574,8 +574,8 @@ int moe_verify_layer_bf16(moe_ctx *ctx, const moe_layer_desc *desc,
     Plan *plan = (Plan *)(ws + L.plan);
     PlanArgs a;
     memset(&a, 0, sizeof a);
-    a.plan = plan; a.mode = 1;
-    a.w0 = slot_pool; a.stride0 = slot_stride;
+    a.plan = plan;
+    a.pool = slot_pool; a.slot_stride = slot_stride;
     a.slot_of_expert = slot_of_expert;
     a.shared = shared; a.shared_stride = moe_bf16_expert_bytes(desc);
     a.flags = flags;

@@ -332,7 +332,6 @@ __device__ inline void write_shared_plan(const FusedArgs &a)
         p->act_off[tid] = n + tid * a.T;
         p->act_cnt[tid] = a.T;
         p->act_w0[tid] = (uint64_t)(a.shared + (size_t)tid * a.shared_stride);
-        p->act_w1[tid] = 0;
     }
     if (tid == 0) { p->n_active = a.S; p->n_routed_active = 0; p->n_rows = n + a.S * a.T; p->n_missing = 0; }
 }

@@ -49,13 +49,12 @@ namespace moespeq {
 namespace {
 
 // MT: token capacity of the launch (2, 4 or 8); UPG: 32-code units per
-// group (g / 32); SYM: symmetric format (scale blobs, z = 8); NW: waves of the workgroup; kWin:
+// group (g / 32); SYM: symmetric format (scale blobs, z = 8); kWin:
 // tiles a wave keeps in flight.
-template <int MT, int UPG, bool SYM, int NW, int kWin>
-__global__ __launch_bounds__(NW * 64, NW / 4)
+template <int MT, int UPG, bool SYM, int kWin>
+__global__ __launch_bounds__(kThreads, kWaves / 4)
 void draft_stream_kernel(const uint16_t *__restrict__ xin, const FusedArgs a)
 {
-    constexpr int kWaves = NW, kThreads = NW * 64;   // (these names shadow the 8-wave constants of the prefill kernel)
     __shared__ double s_part[kWaves];
     __shared__ int32_t s_ids[MOE_MAX_ASSIGN];
     __shared__ float s_w[MOE_MAX_ASSIGN];
@@ -553,8 +552,6 @@ void stream_read_kernel(const u32x4 *__restrict__ src, size_t tiles, uint32_t *s
     if (fold == 0x9E3779B9u) sink[0] = fold;
 }
 
-constexpr int kStreamWaves = 8;
-
 // One workgroup per compute unit: two that share a unit are slower, also where they fit its registers (phi
 // shape, 2 tokens: 37.6 us against 41.6 with two, qwen3 19.2 / 20.6; 4 tokens, held to 128 registers: 52.7 / 60.4).
 constexpr int kMaxPerCu = 1;
@@ -566,8 +563,8 @@ constexpr int kMaxPerCu = 1;
 int stream_window(const Shape &s, bool sym)
 {
     const int epl = sym ? 2 : 1;
-    const int nt = (s.H / s.g / epl + kStreamWaves - 1) / kStreamWaves * epl * (s.g / 32);
-    const int nd = (s.H / 64 / epl + kStreamWaves - 1) / kStreamWaves * epl;
+    const int nt = (s.H / s.g / epl + kWaves - 1) / kWaves * epl * (s.g / 32);
+    const int nd = (s.H / 64 / epl + kWaves - 1) / kWaves * epl;
     auto positions = [&](int w) { return (nt + w - 1) / w * w + (nd + w - 1) / w * w; };
     return positions(8) * 5 > positions(4) * 6 ? 4 : 8;
 }
@@ -577,7 +574,7 @@ int stream_window(const Shape &s, bool sym)
 // item (whole KiB each)
 size_t draft_dynamic_lds(int MT, int H, int g, int E, bool sym, int entry_copies = 1)
 {
-    const int nw = kStreamWaves;
+    const int nw = kWaves;
     size_t lds = ((size_t)MT * (H + 8) * 2 + (size_t)MT * (H / g) * 4 + 7) & ~(size_t)7;
     lds += (size_t)MT * E * 12;
     lds = (lds + 15) & ~(size_t)15;
@@ -591,9 +588,9 @@ size_t draft_dynamic_lds(int MT, int H, int g, int E, bool sym, int entry_copies
 template <int MT, bool SYM, int KW, typename F>
 void stream_kernel_g(int g, F go)
 {
-    if (g == 32) go(draft_stream_kernel<MT, 1, SYM, kStreamWaves, KW>, MT);
-    else if (g == 64) go(draft_stream_kernel<MT, 2, SYM, kStreamWaves, KW>, MT);
-    else go(draft_stream_kernel<MT, 4, SYM, kStreamWaves, KW>, MT);
+    if (g == 32) go(draft_stream_kernel<MT, 1, SYM, KW>, MT);
+    else if (g == 64) go(draft_stream_kernel<MT, 2, SYM, KW>, MT);
+    else go(draft_stream_kernel<MT, 4, SYM, KW>, MT);
 }
 template <bool SYM, int KW, typename F>
 void stream_kernel_t(const Shape &s, F go)
@@ -635,7 +632,7 @@ int draft_resident_slots(const Shape &s, const DraftFusedArgs &d, int n_cu)
     }
     int per = 0;
     stream_kernel(s, d.symmetric != 0, [&](auto kernel, int MT) {
-        per = resident_per_cu(kernel, kStreamWaves * 64, draft_dynamic_lds(MT, s.H, s.g, s.E, d.symmetric != 0));
+        per = resident_per_cu(kernel, kThreads, draft_dynamic_lds(MT, s.H, s.g, s.E, d.symmetric != 0));
     });
     return (per < kMaxPerCu ? per : kMaxPerCu) * n_cu;
 }
@@ -647,7 +644,7 @@ void launch_draft_fused(const Shape &s, const DraftFusedArgs &d, int n_cu, int s
     // never more workgroups than there can be items
     const int maxu = s.E < s.T * s.k ? s.E : s.T * s.k;
     const long items = (long)maxu * (s.I / 32);
-    const dim3 grid((unsigned)(items < slots ? items : slots)), block(kStreamWaves * 64);
+    const dim3 grid((unsigned)(items < slots ? items : slots)), block(kThreads);
     stream_kernel(s, d.symmetric != 0, [&](auto kernel, int MT) {
         launch_with_lds(kernel, grid, block, draft_dynamic_lds(MT, s.H, s.g, s.E, d.symmetric != 0), st, (const uint16_t *)d.x, a);
     });

@@ -40,15 +40,13 @@ struct Plan {
     int32_t n_missing;
     int32_t ids[MOE_MAX_ASSIGN];      // [T,k]
     float   w[MOE_MAX_ASSIGN];
-    float   conf[MOE_MAX_ASSIGN];
     int32_t count[MOE_MAX_EXPERTS];
     int32_t off[MOE_MAX_EXPERTS + 1];
     int32_t perm[MOE_MAX_ASSIGN];
     int32_t act_expert[kMaxActive];   // expert id (>= E: shared expert id - E)
     int32_t act_off[kMaxActive];      // first row
     int32_t act_cnt[kMaxActive];      // number of rows (tokens of that expert)
-    uint64_t act_w0[kMaxActive];      // weights: bf16 blob / int4 codes blob
-    uint64_t act_w1[kMaxActive];      // int4 scale-zero blob
+    uint64_t act_w0[kMaxActive];      // weights: bf16 blob
     int32_t row_tok[kMaxRows];        // token of a row
     float   row_w[kMaxRows];          // routing weight of a row (1 for shared)
     int32_t row_live[kMaxRows];       // 0: expert absent, the row's output must be skipped
@@ -91,13 +89,11 @@ void launch_prefill_topk(const Shape &s, const double *parts, const float *bias,
                          int32_t *count, int32_t *list, hipStream_t st);
 struct PlanArgs {
     Plan *plan;
-    int mode;                          // 0 draft (int4 routed, all present), 1 verify (slot table)
-    const void *w0; size_t stride0;    // draft: codes base / stride; verify: slot pool / stride
-    const void *w1; size_t stride1;    // draft: scale-zero base / stride
+    const void *pool; size_t slot_stride;
     const int32_t *slot_of_expert;
     const void *shared; size_t shared_stride;
     int flags;
-    int32_t *ids_out; float *conf_out;
+    int32_t *ids_out;
     int32_t *missing; int32_t *n_missing;
 };
 // router + plan in one launch; logits: [T, E] fp64 scratch; token_arrivals [MOE_MAX_TOKENS] and

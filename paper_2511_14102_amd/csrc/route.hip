@@ -20,21 +20,10 @@ constexpr int kRouteThreads = 1024;
 // One workgroup per token: logits of all experts (one wave per expert row at a time), ranks of
 // the logits counted by all waves, then wave 0 writes the k selected experts in rank order with
 // their softmax weights.
-// kAgent: the results are stored at agent scope (another workgroup of the same launch reads them).
-template <bool kAgent, typename V>
-__device__ inline void put(V *p, V v) {
-    if (kAgent) __hip_atomic_store(p, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-    else *p = v;
-}
-template <bool kAgent, typename V>
-__device__ inline V get(const V *p) {
-    return kAgent ? __hip_atomic_load(p, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) : *p;
-}
-
-template <bool kAgent>
-__device__ inline void route_token(const uint16_t *__restrict__ x, const uint16_t *__restrict__ wr,
-                                   const float *__restrict__ bias, int H, int E, int k, int renorm,
-                                   int32_t *__restrict__ ids, float *__restrict__ w, float *__restrict__ conf)
+__global__ __launch_bounds__(kRouteThreads)
+void route_kernel(const uint16_t *__restrict__ x, const uint16_t *__restrict__ wr,
+                  const float *__restrict__ bias, int H, int E, int k, int renorm,
+                  int32_t *__restrict__ ids, float *__restrict__ w, float *__restrict__ conf)
 {
     __shared__ double s_logit[MOE_MAX_EXPERTS];
     __shared__ int32_t s_rank[MOE_MAX_EXPERTS];
@@ -73,7 +62,7 @@ __device__ inline void route_token(const uint16_t *__restrict__ x, const uint16_
     // strict, so the ranks are a permutation and rank < k is the selection.
     wave::count_ranks(s_logit, s_rank, E, lane, wave, nwave);
     __syncthreads();
-    if (wave != 0) return;                 // (the caller's next barrier is reached by all waves)
+    if (wave != 0) return;
     double mine[4], pe[4];
     int rank[4];
     double mx = -INFINITY;
@@ -103,20 +92,12 @@ __device__ inline void route_token(const uint16_t *__restrict__ x, const uint16_
     for (int i = 0; i < 4; ++i) {
         if (rank[i] < k) {
             const size_t o = (size_t)t * k + rank[i];
-            put<kAgent>(&ids[o], (int32_t)(lane + 64 * i));
+            ids[o] = lane + 64 * i;
             const float c = (float)pe[i];
-            if (conf) put<kAgent>(&conf[o], c);
-            put<kAgent>(&w[o], renorm ? (float)(pe[i] / sel) : c);
+            if (conf) conf[o] = c;
+            w[o] = renorm ? (float)(pe[i] / sel) : c;
         }
     }
-}
-
-__global__ __launch_bounds__(kRouteThreads)
-void route_kernel(const uint16_t *__restrict__ x, const uint16_t *__restrict__ wr,
-                  const float *__restrict__ bias, int H, int E, int k, int renorm,
-                  int32_t *__restrict__ ids, float *__restrict__ w, float *__restrict__ conf)
-{
-    route_token<false>(x, wr, bias, H, E, k, renorm, ids, w, conf);
 }
 
 // count / off / perm for n <= MOE_MAX_ASSIGN assignments over E experts; one workgroup of at least
@@ -191,13 +172,18 @@ void perm_kernel(const int32_t *__restrict__ ids, int n, int E, int32_t *count, 
 
 // Builds the execution plan: histogram / permutation, the list of experts to run (shared
 // experts at active indices [0, S), then present routed experts ascending), their weight
-// pointers and row ranges, the per-row token / weight / live flags, and the missing list.
-template <bool kAgent>
-__device__ inline void plan_body(Plan *__restrict__ plan, int T, int E, int k, int S, int mode,
-                 const char *w0, size_t stride0, const char *w1, size_t stride1,
+// pointers and row ranges, the per-row token / weight / live flags, and the missing list.  The ids and weights
+// come from other workgroups of the launch: stored and loaded at agent scope.
+template <typename V>
+__device__ inline void put(V *p, V v) { __hip_atomic_store(p, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT); }
+template <typename V>
+__device__ inline V get(const V *p) { return __hip_atomic_load(p, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT); }
+
+__device__ inline void plan_body(Plan *__restrict__ plan, int T, int E, int k, int S,
+                 const char *pool, size_t slot_stride,
                  const int32_t *__restrict__ slot_of_expert,
                  const char *shared, size_t shared_stride, int flags,
-                 int32_t *ids_out, float *conf_out, int32_t *missing, int32_t *n_missing)
+                 int32_t *ids_out, int32_t *missing, int32_t *n_missing)
 {
     __shared__ int32_t s_ids[MOE_MAX_ASSIGN];
     __shared__ int32_t s_count[MOE_MAX_EXPERTS];
@@ -210,13 +196,12 @@ __device__ inline void plan_body(Plan *__restrict__ plan, int T, int E, int k, i
     const bool only_listed = (flags & MOE_VERIFY_ONLY_LISTED) != 0;
 
     for (int a = threadIdx.x; a < n; a += blockDim.x) {
-        int id = get<kAgent>(&plan->ids[a]);
+        int id = get(&plan->ids[a]);
         s_ids[a] = id;
         if (ids_out) ids_out[a] = id;
-        if (conf_out) conf_out[a] = get<kAgent>(&plan->conf[a]);
     }
     for (int e = threadIdx.x; e < E; e += blockDim.x) {
-        s_slot[e] = mode == 0 ? e : slot_of_expert[e];
+        s_slot[e] = slot_of_expert[e];
         s_listed[e] = only_listed ? 0 : 1;
     }
     __syncthreads();
@@ -245,7 +230,6 @@ __device__ inline void plan_body(Plan *__restrict__ plan, int T, int E, int k, i
         plan->act_off[s] = n + s * T;
         plan->act_cnt[s] = only_listed ? 0 : T;
         plan->act_w0[s] = (uint64_t)(shared + (size_t)s * shared_stride);
-        plan->act_w1[s] = 0;
     }
     // routed experts: ordered compaction, 64 experts per step, by wave 0
     if (threadIdx.x < 64) {
@@ -263,8 +247,7 @@ __device__ inline void plan_body(Plan *__restrict__ plan, int T, int E, int k, i
                 plan->act_expert[u] = e;
                 plan->act_off[u] = s_off[e];
                 plan->act_cnt[u] = s_count[e];
-                plan->act_w0[u] = (uint64_t)(w0 + (size_t)slot * stride0);
-                plan->act_w1[u] = w1 ? (uint64_t)(w1 + (size_t)slot * stride1) : 0;
+                plan->act_w0[u] = (uint64_t)(pool + (size_t)slot * slot_stride);
             }
             if (absent) missing[nmiss + __popcll(ba & below)] = e;
             nact += __popcll(bp);
@@ -277,7 +260,7 @@ __device__ inline void plan_body(Plan *__restrict__ plan, int T, int E, int k, i
         int a = s_perm[pos];
         int e = s_ids[a];
         plan->row_tok[pos] = a / k;
-        plan->row_w[pos] = get<kAgent>(&plan->w[a]);
+        plan->row_w[pos] = get(&plan->w[a]);
         plan->row_live[pos] = (s_listed[e] && s_slot[e] >= 0) ? 1 : 0;
     }
     if (threadIdx.x == 0) {
@@ -290,10 +273,10 @@ __device__ inline void plan_body(Plan *__restrict__ plan, int T, int E, int k, i
 }
 
 struct PlanKernelArgs {
-    Plan *plan; int T, E, k, S, mode;
-    const char *w0; size_t stride0; const char *w1; size_t stride1;
+    Plan *plan; int T, E, k, S;
+    const char *pool; size_t slot_stride;
     const int32_t *slot_of_expert; const char *shared; size_t shared_stride; int flags;
-    int32_t *ids_out; float *conf_out; int32_t *missing; int32_t *n_missing;
+    int32_t *ids_out; int32_t *missing; int32_t *n_missing;
 };
 
 // Router and plan in one launch (the verify call).  Workgroup (b, t) reduces the router rows of
@@ -393,10 +376,8 @@ void route_plan_kernel(const uint16_t *__restrict__ x, const uint16_t *__restric
         for (int i = 0; i < 4; ++i) {
             if (rank[i] < k) {
                 const size_t o = (size_t)t * k + rank[i];
-                put<true>(&a.plan->ids[o], (int32_t)(lane + 64 * i));
-                const float c = (float)pe[i];
-                put<true>(&a.plan->conf[o], c);
-                put<true>(&a.plan->w[o], renorm ? (float)(pe[i] / sel) : c);
+                put(&a.plan->ids[o], (int32_t)(lane + 64 * i));
+                put(&a.plan->w[o], renorm ? (float)(pe[i] / sel) : (float)pe[i]);
             }
         }
     }
@@ -409,8 +390,8 @@ void route_plan_kernel(const uint16_t *__restrict__ x, const uint16_t *__restric
     }
     __syncthreads();
     if (!s_last) return;
-    plan_body<true>(a.plan, a.T, a.E, a.k, a.S, a.mode, a.w0, a.stride0, a.w1, a.stride1, a.slot_of_expert,
-                    a.shared, a.shared_stride, a.flags, a.ids_out, a.conf_out, a.missing, a.n_missing);
+    plan_body(a.plan, a.T, a.E, a.k, a.S, a.pool, a.slot_stride, a.slot_of_expert,
+              a.shared, a.shared_stride, a.flags, a.ids_out, a.missing, a.n_missing);
 }
 
 // Router of a long run of tokens, first launch: partial logits [part][T][E] in fp64 over a share of H.  A
@@ -638,10 +619,10 @@ void launch_perm(const Shape &s, const int32_t *ids, int32_t *count, int32_t *of
 static PlanKernelArgs plan_kernel_args(const Shape &s, const PlanArgs &a)
 {
     PlanKernelArgs k;
-    k.plan = a.plan; k.T = s.T; k.E = s.E; k.k = s.k; k.S = s.S; k.mode = a.mode;
-    k.w0 = (const char *)a.w0; k.stride0 = a.stride0; k.w1 = (const char *)a.w1; k.stride1 = a.stride1;
+    k.plan = a.plan; k.T = s.T; k.E = s.E; k.k = s.k; k.S = s.S;
+    k.pool = (const char *)a.pool; k.slot_stride = a.slot_stride;
     k.slot_of_expert = a.slot_of_expert; k.shared = (const char *)a.shared; k.shared_stride = a.shared_stride;
-    k.flags = a.flags; k.ids_out = a.ids_out; k.conf_out = a.conf_out; k.missing = a.missing; k.n_missing = a.n_missing;
+    k.flags = a.flags; k.ids_out = a.ids_out; k.missing = a.missing; k.n_missing = a.n_missing;
     return k;
 }
 
