@@ -79,6 +79,10 @@ __device__ inline int max(int v) { return all(v, [](int a, int b) { return a > b
 __device__ inline float row_sum(float v) { return row_all(v, [](float a, float b) { return a + b; }); }
 
 
+// A logit as the selections compare it: NaN comes last (unordered, several would share a rank, and ranks below k
+// would be left without an expert)
+__device__ inline double ordered(double l) { return l == l ? l : -INFINITY; }
+
 // Top-k selection by one wave: lane l holds logits l, l + 64, ... (NR of them, 64 NR >= E).  rank[i] becomes
 // the position of logit lane + 64 i in the order (larger first, lower index first among equals) where that is
 // below k, else MOE_MAX_EXPERTS; returns, in lane j < k, the index of rank j.
@@ -95,7 +99,7 @@ __device__ inline int select_topk(const double (&logit)[NR], int E, int k, int l
     int key[NR];
 #pragma unroll
     for (int i = 0; i < NR; ++i) {
-        l[i] = logit[i] == logit[i] ? logit[i] : -INFINITY;  // a NaN is selected last
+        l[i] = ordered(logit[i]);
         const int b = __float_as_int((float)l[i] + 0.f);     // (-0 and 0 are equal)
         key[i] = lane + 64 * i < E ? b ^ ((b >> 31) & 0x7fffffff) : kNone;
         rank[i] = MOE_MAX_EXPERTS;
@@ -147,7 +151,7 @@ __device__ inline void count_ranks(const double *logit, int32_t *rank, int E, in
 #pragma unroll
     for (int i = 0; i < NR; ++i) {
         const int e = lane + 64 * i;
-        mine[i] = logit[e < E ? e : E - 1];
+        mine[i] = ordered(logit[e < E ? e : E - 1]);
         part[i] = 0;
     }
     for (int e2 = first; e2 < E; e2 += kBatch * stride) {
@@ -155,7 +159,7 @@ __device__ inline void count_ranks(const double *logit, int32_t *rank, int E, in
 #pragma unroll
         for (int j = 0; j < kBatch; ++j) {
             const int idx = e2 + j * stride;
-            v[j] = logit[idx < E ? idx : E - 1];
+            v[j] = ordered(logit[idx < E ? idx : E - 1]);
         }
 #pragma unroll
         for (int j = 0; j < kBatch; ++j) {
