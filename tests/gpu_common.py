@@ -41,3 +41,18 @@ def tokens_with_clear_routing(cfg, A, T, layer=0, step=0, kind=None):
 def to_np(t):
     return t.detach().float().cpu().numpy().astype(np.float64) if t.is_floating_point() \
         else t.detach().cpu().numpy()
+
+
+class Guarded:
+    """A device buffer with canary bytes before and after the part handed to the library."""
+    PAD = 4096
+
+    def __init__(self, nbytes, dtype=torch.uint8, shape=None):
+        self.raw = torch.full((nbytes + 2 * self.PAD,), 0xA5, dtype=torch.uint8, device="cuda")
+        self.view = self.raw[self.PAD:self.PAD + nbytes].view(dtype)
+        if shape is not None:
+            self.view = self.view.reshape(shape)
+
+    def intact(self):
+        n = self.raw.numel()
+        return bool((self.raw[:self.PAD] == 0xA5).all()) and bool((self.raw[n - self.PAD:] == 0xA5).all())

@@ -93,6 +93,28 @@ def test_one_token_with_many_items(H, k, g, S):
     ctx.close()
 
 
+
+@pytest.mark.parametrize("g", [32, 64, 128])
+def test_stream_windows_of_eight(g):
+    """H = 2304: 9 to 12 gate/up and 4 to 6 down tiles per wave, ragged parts under the window of eight (the other
+    small shapes of these group sizes run the window of four)."""
+    cfg = LayerConfig(79, "win%d" % g, 2304, 5, 128, 2, g, 0, 1)
+    ctx = B.Context(0)
+    for symmetric in (False, True):
+        L = synth.make_layer(cfg, 0, symmetric=symmetric)
+        A = oracle_arrays(L)
+        D = DeviceLayer(ctx, cfg, L, max_tokens=8, verify=False, symmetric=symmetric)
+        x = tokens_with_clear_routing(cfg, A, 8, step=3)
+        ref = oracle_draft(A, x)
+        for T in (2, 3, 8):
+            say("window of eight g", g, "symmetric" if symmetric else "", "T", T)
+            r = D.draft(x[:T].cuda())
+            torch.cuda.synchronize()
+            assert np.array_equal(to_np(r["ids"]), ref["ids"][:T])
+            assert rel_err(to_np(r["y"]), ref["y"][:T]) <= TOL_DRAFT
+    ctx.close()
+
+
 def test_shared_experts_on_the_line_run_inside():
     """As many 16-row items per compute unit as H has 256s (1024 on 256 units): the call's own launch runs the
     shared experts, no launch of the bf16 kernels is made."""

@@ -11,7 +11,7 @@ import torch
 import synth
 from oracle import oracle as orc
 from tests.common import oracle_arrays, oracle_draft, oracle_verify, rel_err, bf16_exact
-from tests.gpu_common import (TOL_DRAFT, TOL_VERIFY, build_layer, say, to_np,
+from tests.gpu_common import (Guarded, TOL_DRAFT, TOL_VERIFY, build_layer, say, to_np,
                               tokens_with_clear_routing)
 
 pytestmark = pytest.mark.gpu
@@ -560,21 +560,6 @@ def test_draft_wait_that_runs_out_is_reported(ctx, name):
         ctx.set_draft_spin_limit(1 << 22)
     with pytest.raises(B.MoeError):
         ctx.set_draft_spin_limit(0)
-
-
-class Guarded:
-    """A device buffer with canary bytes before and after the part handed to the library."""
-    PAD = 4096
-
-    def __init__(self, nbytes, dtype=torch.uint8, shape=None):
-        self.raw = torch.full((nbytes + 2 * self.PAD,), 0xA5, dtype=torch.uint8, device="cuda")
-        self.view = self.raw[self.PAD:self.PAD + nbytes].view(dtype)
-        if shape is not None:
-            self.view = self.view.reshape(shape)
-
-    def intact(self):
-        n = self.raw.numel()
-        return bool((self.raw[:self.PAD] == 0xA5).all()) and bool((self.raw[n - self.PAD:] == 0xA5).all())
 
 
 @pytest.mark.parametrize("name", ["tiny", "s192"])

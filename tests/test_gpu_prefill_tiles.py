@@ -9,7 +9,7 @@ import torch
 import synth
 from synth.configs import LayerConfig
 from tests.common import oracle_arrays, oracle_draft, rel_err
-from tests.gpu_common import TOL_DRAFT, say, to_np, tokens_with_clear_routing
+from tests.gpu_common import TOL_DRAFT, Guarded, say, to_np, tokens_with_clear_routing
 
 pytestmark = pytest.mark.gpu
 
@@ -85,6 +85,7 @@ ROUTED = [
     LayerConfig(66, "r70", 320, 70, 64, 3, 32, 0, 1),      # ragged token and expert blocks, k-steps that do not fill a share
     LayerConfig(67, "r130", 192, 130, 64, 4, 64, 1, 0),    # more than 128 experts, a shared expert
     LayerConfig(68, "r5", 2112, 5, 64, 5, 64, 2, 1),       # few experts, shares of H, every token in every expert
+    LayerConfig(70, "r4160", 4160, 4, 64, 2, 64, 0, 1),    # the most shares of H (8 x 4 waves), 130 k-steps over them
 ]
 
 
@@ -96,10 +97,14 @@ def test_prefill_routing_edges(cfg):
     D = DeviceLayer(ctx, cfg, L, max_tokens=8, verify=False)
     x = tokens_with_clear_routing(cfg, A, 421, step=5, kind="iid")
     ref = oracle_draft(A, x)
-    for T in (257, 421):
+    ws = Guarded(max(B.prefill_workspace_bytes(D.desc, T) for T in (257, 420, 421)))
+    D._prefill_ws = ws.view                                # (one workspace for all of them)
+    for T in (257, 420, 421):
         say("prefill routing", cfg.name, "T", T)
+        assert B.prefill_workspace_bytes(D.desc, T) <= B.prefill_workspace_bytes(D.desc, 421)
         r = D.prefill(x[:T].cuda())
         torch.cuda.synchronize()
+        assert ws.intact() and D._prefill_ws is ws.view
         assert np.array_equal(to_np(r["ids"]), ref["ids"][:T])
         np.testing.assert_allclose(to_np(r["conf"]), ref["conf"][:T], rtol=2e-6)
         assert rel_err(to_np(r["y"]), ref["y"][:T]) <= TOL_DRAFT
