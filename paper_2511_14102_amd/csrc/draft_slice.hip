@@ -257,7 +257,7 @@ void draft_fused_kernel(const uint16_t *__restrict__ xin, const FusedArgs a)
             const uint32_t hi = (__float_as_uint(v3) & cm1) | (__float_as_uint(v2) & ~cm1);
             return __uint_as_float((hi & cm2) | (lo & ~cm2));
         };
-        // (an entry goes out before the last tile of its group: loads return in order)
+        // (an entry follows the last tile of its group)
         u32x4 win[kWin];
         uint32_t gent[kSzWin], dpe[kWin];
         {
