@@ -55,12 +55,13 @@
 // 2.5e-6; h >= 0 over I = 8192: 1.1e-4, now 2.8e-6).  The start costs one LDS read per group and token block
 // (mixtral shape, 4096 tokens: 2 % of the call).
 //
-// Bound and figures (gate/up and down kernel; before: two row blocks per wave, operand tiles through
+// Bound and figures (gate/up and down kernel; first form: two row blocks per wave, operand tiles through
 // registers, offset 128, two multiply-adds per group).  Many tokens per expert: the matrix cores.
-// mixtral shape, 4096 tokens: 2028 and 1650 us, 951 and 1170 TFLOP/s counting both planes of h
-// (before: 3750 and 2933 us; a large library product reaches 1250 on this part).  phi shape, 512 tokens:
-// 181 and 165 us (406 and 261).  Few tokens per expert: the weight stream.  dsv2lite shape, 333 tokens
-// (31 per expert): 58 and 43 us for 197 and 98 MB (99 and 66).
+// mixtral shape, 4096 tokens: 2213 and 1790 us, 870 and 1075 TFLOP/s counting both planes of h
+// (first form: 3750 and 2933 us; a large library product reaches 1250 on this part).  phi shape, 512 tokens:
+// 207 and 193 us (406 and 261).  Few tokens per expert: the weight stream.  dsv2lite shape, 333 tokens
+// (31 per expert), with its shared experts in the same launches: 75 and 60 us for 219 and 110 MB (routed experts
+// alone, first form: 99 and 66).
 #include <hip/hip_runtime.h>
 #include "draft_common.h"
 
