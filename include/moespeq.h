@@ -160,8 +160,8 @@ int moe_workspace_bytes(const moe_layer_desc *desc, int max_tokens, size_t *byte
  * multiple of 4).  Required once after allocation, before the first moe_draft_layer_int4 OR
  * moe_verify_layer_bf16 call on it, and again after a draft call that timed out (below).  The first
  * 512 bytes and the slot area behind them hold what the kernels exchange between their workgroups:
- * the draft kernels' ticket counters and tagged router-result slots, the verify call's arrival
- * counters, and the draft status word.  Both calls expect the counters and tags zero on entry and
+ * the draft kernels' ticket counters and tagged router-result slots (the verify call counts arrivals in
+ * the same tags), the verify call's arrival counter, and the draft status word.  Both calls expect the counters and tags zero on entry and
  * leave them zero on exit (also when the call is replayed from a HIP graph); nothing else is
  * carried from call to call. */
 int moe_workspace_init(moe_ctx *ctx, void *workspace, size_t workspace_bytes, void *stream);
@@ -344,8 +344,8 @@ int moe_expert_union(moe_ctx *ctx, const int32_t *ids, int n_ids, int n_experts,
  *
  * 1 <= T <= MOE_MAX_TOKENS.  y_bf16 [T,H]; ids_out [T,k] int32 or NULL; missing [E] int32 and
  * n_missing [1] int32 device memory, required.  `workspace` must have been put into its idle
- * state once (moe_workspace_init): the launch that routes counts its arriving workgroups there
- * and leaves the counter zero again.
+ * state once (moe_workspace_init): the launch that routes counts its arriving workgroups there, the
+ * launch of the down products counts its own in the exchange slots' tags, and both leave zeros again.
  */
 int moe_verify_layer_bf16(moe_ctx *ctx, const moe_layer_desc *desc,
                           const void *x_bf16, const void *w_router_bf16,
@@ -372,13 +372,13 @@ int moe_expert_copy_async(moe_ctx *ctx, void *dst_slot_dev, const void *src_pinn
 
 /* ---- measurement aid (not part of the method) ---------------------------------------------- */
 
-#define MOE_KERNEL_ROUTE         0   /* router logits + softmax + top-k; in the verify call the same launch also builds the plan (route_plan_kernel); prefill call: route_kernel or prefill_logits_kernel */
+#define MOE_KERNEL_ROUTE         0   /* router logits + softmax + top-k; verify call: router logits, top-k and plan (verify_route_kernel); prefill call: route_kernel or prefill_logits_kernel */
 #define MOE_KERNEL_PLAN          1   /* histogram / permutation of moe_route_topk (perm_kernel); prefill call: prefill_topk_kernel or prefill_plan_kernel */
 #define MOE_KERNEL_DRAFT_FUSED   2   /* router + top-k + int4 SwiGLU experts, one launch     */
 #define MOE_KERNEL_STREAM_READ   3   /* plain streaming read (moe_stream_read_probe)         */
-#define MOE_KERNEL_BF16_GATEUP   4   /* bf16 gate+up small-M contraction, SwiGLU             */
-#define MOE_KERNEL_BF16_DOWN     5   /* bf16 down small-M contraction                        */
-#define MOE_KERNEL_COMBINE       6   /* weighted sum over a token's experts                  */
+#define MOE_KERNEL_BF16_GATEUP   4   /* bf16 gate+up small-M contraction, SwiGLU; verify call: also the softmax weights */
+#define MOE_KERNEL_BF16_DOWN     5   /* bf16 down small-M contraction; verify call: also the sum over a token's experts */
+#define MOE_KERNEL_COMBINE       6   /* no launch of its own any more (0 launches): part of MOE_KERNEL_BF16_DOWN */
 #define MOE_KERNEL_UNION         7   /* expert union                                         */
 #define MOE_KERNEL_PREFILL_STAGE   8  /* moe_draft_prefill_int4: tokens gathered into operand tiles  */
 #define MOE_KERNEL_PREFILL_GATEUP  9  /* ... int4 gate+up grouped small-M contraction, SwiGLU         */

@@ -377,19 +377,19 @@ static int enqueue_draft(moe_ctx *ctx, const moe_layer_desc *desc, const void *x
     if (!timed) {
         launch_draft_fused(s, a, ctx->n_cu, slots, st);
         if (own_launches) {
-            launch_bf16_gateup(s, plan, 0, s.S, x, ws + L.hb, ws + L.hb_lo, st);
-            launch_bf16_down_add(s, plan, 0, s.S, ws + L.hb, ws + L.hb_lo, y, st);
+            launch_shared_gateup(s, plan, x, ws + L.hb, ws + L.hb_lo, st);
+            launch_shared_down_add(s, plan, ws + L.hb, ws + L.hb_lo, y, st);
         }
         return hip_status(ctx, hipGetLastError());
     }
     { ProfScope p(ctx, MOE_KERNEL_DRAFT_FUSED, st); launch_draft_fused(s, a, ctx->n_cu, slots, st); }
     if (own_launches) {   // shared experts stay 16-bit in the draft model (section 3.4.2)
         { ProfScope p(ctx, MOE_KERNEL_BF16_GATEUP, st);
-          launch_bf16_gateup(s, plan, 0, s.S, x, ws + L.hb, ws + L.hb_lo, st); }
+          launch_shared_gateup(s, plan, x, ws + L.hb, ws + L.hb_lo, st); }
         // the down kernel adds the shared experts' outputs to y itself (fp32 atomics on top of
         // the routed experts' sum): no combine launch
         { ProfScope p(ctx, MOE_KERNEL_BF16_DOWN, st);
-          launch_bf16_down_add(s, plan, 0, s.S, ws + L.hb, ws + L.hb_lo, y, st); }
+          launch_shared_down_add(s, plan, ws + L.hb, ws + L.hb_lo, y, st); }
     }
     return hip_status(ctx, hipGetLastError());
 }
@@ -581,17 +581,15 @@ int moe_verify_layer_bf16(moe_ctx *ctx, const moe_layer_desc *desc,
     a.flags = flags;
     a.ids_out = ids_out;
     a.missing = missing; a.n_missing = n_missing;
+    double *logits = (double *)(ws + L.vlogits);
     // router and plan in one launch; its arrival counter sits behind the draft kernel's tickets
     { ProfScope p(ctx, MOE_KERNEL_ROUTE, st);
-      launch_route_plan(s, x, wr, bias, a, (double *)(ws + L.vlogits),
-                        (uint32_t *)(ws + L.tickets + kWsTokenArrivalsOffset),
-                        (uint32_t *)(ws + L.tickets + kWsArrivalsOffset), st); }
-    const int nexp = s.S + (s.E < s.T * s.k ? s.E : s.T * s.k);
-    { ProfScope p(ctx, MOE_KERNEL_BF16_GATEUP, st); launch_bf16_gateup(s, plan, 0, nexp, x, ws + L.hb, nullptr, st); }
+      launch_verify_route(s, x, wr, bias, a, logits, (uint32_t *)(ws + L.tickets + kWsArrivalsOffset), st); }
+    { ProfScope p(ctx, MOE_KERNEL_BF16_GATEUP, st);
+      launch_verify_gateup(s, plan, x, logits, plan->ids, plan->row_w, ws + L.hb, st); }
     { ProfScope p(ctx, MOE_KERNEL_BF16_DOWN, st);
-      launch_bf16_down(s, plan, 0, nexp, ws + L.hb, (float *)(ws + L.obuf), st); }
-    { ProfScope p(ctx, MOE_KERNEL_COMBINE, st);
-      launch_combine(s, plan, (const float *)(ws + L.obuf), (flags & MOE_VERIFY_ACCUMULATE) ? 1 : 0, y, st); }
+      launch_verify_down(s, plan, ws + L.hb, (float *)(ws + L.obuf), (unsigned long long *)(ws + L.slots), kDraftSlotReplicas * L.slot_replica_bytes,
+                         (flags & MOE_VERIFY_ACCUMULATE) ? 1 : 0, y, st); }
     int rc = hip_status(ctx, hipGetLastError());
     if (rc != MOE_OK) return rc;
     if (flags & MOE_VERIFY_STRICT) {

@@ -13,15 +13,12 @@
 #pragma once
 #include <type_traits>
 #include "plan.h"
+#include "stream.h"
 #include "wave.h"
 
 namespace moespeq {
 
 namespace {
-
-typedef __attribute__((ext_vector_type(8))) __bf16 bf16x8;
-typedef __attribute__((ext_vector_type(4))) float f32x4;
-typedef __attribute__((ext_vector_type(4))) uint32_t u32x4;
 
 constexpr int kWaves = 8;
 constexpr int kThreads = kWaves * 64;
@@ -33,12 +30,6 @@ constexpr uint32_t kMagic = 0x43004300u;      // bf16 pair (128, 128)
 
 __device__ inline float bf16_lo(uint32_t u) { return __uint_as_float(u << 16); }
 __device__ inline float bf16_hi(uint32_t u) { return __uint_as_float(u & 0xffff0000u); }
-
-__device__ inline uint16_t f32_to_bf16_rne(float f) {
-    uint32_t u = __float_as_uint(f);
-    u += 0x7fffu + ((u >> 16) & 1u);
-    return (uint16_t)(u >> 16);
-}
 
 // Unpack constants.  Both are made opaque to the compiler (one in a scalar, one in a vector
 // register) so that (a & mask) | magic has no literal operand and is selected as the single
@@ -111,21 +102,6 @@ __device__ inline void store16_agent(void *p, u32x4 v) {
 __device__ inline void load16_to_lds(const void *g, uint32_t lds_base) {
     asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, off" : : "s"(lds_base), "v"(g) : "memory");
 }
-
-// A run of a weight stream as a buffer: `bytes` bytes from `base` (both wave-uniform).  A load past the run's
-// end returns zeros and moves nothing, so a window's loads need no clamps: positions are 32-bit offsets, four
-// tiles of 1 KiB under one address register.  (As global loads with clamped 64-bit addresses a tile cost a
-// dozen scalar instructions and a branch, and the first window of a workgroup took 5 us to issue.)
-typedef __amdgpu_buffer_rsrc_t run_t;
-__device__ inline run_t make_run(const char *base, uint32_t bytes) {
-    return __builtin_amdgcn_make_buffer_rsrc((void *)base, 0, (int)bytes, 0x00027000);
-}
-constexpr int kNonTemporal = 2;
-__device__ inline u32x4 run_load16(run_t r, uint32_t off) {
-    return __builtin_bit_cast(u32x4, __builtin_amdgcn_raw_buffer_load_b128(r, off, 0, kNonTemporal));
-}
-__device__ inline uint32_t run_load4(run_t r, uint32_t off) { return __builtin_amdgcn_raw_buffer_load_b32(r, off, 0, kNonTemporal); }
-__device__ inline uint32_t run_load2(run_t r, uint32_t off) { return (uint16_t)__builtin_amdgcn_raw_buffer_load_b16(r, off, 0, kNonTemporal); }
 
 struct FusedArgs {
     const uint16_t *wr;         // [E,H] bf16
@@ -321,19 +297,12 @@ __device__ inline void write_shared_plan(const FusedArgs &a)
 {
     Plan *p = a.plan;
     const int tid = threadIdx.x, n = a.T * a.k;
-    for (int i = tid; i < n; i += blockDim.x) { p->perm[i] = i; p->row_live[i] = 0; }
-    for (int i = tid; i < a.S * a.T; i += blockDim.x) {
-        p->row_tok[n + i] = i % a.T;
-        p->row_w[n + i] = 1.f;
-        p->row_live[n + i] = 1;
+    if (tid < a.S * 16) {
+        const int s = tid / 16, t = tid % 16;
+        p->act_row[s][t] = t < a.T ? (uint8_t)(n + s * a.T + t) : kNoRow;
     }
-    if (tid < a.S) {
-        p->act_expert[tid] = a.E + tid;
-        p->act_off[tid] = n + tid * a.T;
-        p->act_cnt[tid] = a.T;
-        p->act_w0[tid] = (uint64_t)(a.shared + (size_t)tid * a.shared_stride);
-    }
-    if (tid == 0) { p->n_active = a.S; p->n_routed_active = 0; p->n_rows = n + a.S * a.T; p->n_missing = 0; }
+    if (tid < a.S) p->act_w0[tid] = (uint64_t)(a.shared + (size_t)tid * a.shared_stride);
+    if (tid == 0) p->n_active = a.S;
 }
 
 // Launch with `lds` bytes of dynamic LDS; beyond 48 KiB the limit has to be raised once per kernel.

@@ -30,24 +30,17 @@ inline void launch(K kernel, dim3 grid, dim3 block, size_t lds, hipStream_t st, 
 constexpr int kMaxRows = MOE_MAX_ASSIGN + MOE_MAX_TOKENS * MOE_MAX_SHARED;   // routed + shared rows
 constexpr int kMaxActive = MOE_MAX_ASSIGN + MOE_MAX_SHARED;                   // distinct experts per call
 
-// A "row" is one (token, expert) pair the expert kernels work on.  Rows of one expert are
-// contiguous: routed rows are the stable permutation of the assignments (section 3.4.4),
-// shared-expert rows follow, one per token and shared expert.
+// A "row" is one (token, expert) pair the bf16 expert kernels work on: assignment a = t k + j is row a, token t of
+// shared expert s is row T k + s T + t.  Column t of an expert's matrix products is token t (T <= 16 columns of
+// the MFMA), so the tokens of one expert run together (section 3.4.4) without being moved next to each other.
+constexpr uint8_t kNoRow = 255;
+static_assert(kMaxRows < kNoRow && MOE_MAX_TOKENS <= 16, "rows are bytes, tokens are MFMA columns");
 struct Plan {
-    int32_t n_active;                 // experts the expert kernels run (routed present + shared)
-    int32_t n_routed_active;
-    int32_t n_rows;                   // T*k + T*S
-    int32_t n_missing;
+    int32_t n_active;                 // experts of the down launch: the shared ones, then the present routed ones, ascending
+    int32_t n_live;                   // those of them that have tokens
     int32_t ids[MOE_MAX_ASSIGN];      // [T,k]
-    float   w[MOE_MAX_ASSIGN];
-    int32_t count[MOE_MAX_EXPERTS];
-    int32_t off[MOE_MAX_EXPERTS + 1];
-    int32_t perm[MOE_MAX_ASSIGN];
-    int32_t act_expert[kMaxActive];   // expert id (>= E: shared expert id - E)
-    int32_t act_off[kMaxActive];      // first row
-    int32_t act_cnt[kMaxActive];      // number of rows (tokens of that expert)
     uint64_t act_w0[kMaxActive];      // weights: bf16 blob
-    int32_t row_tok[kMaxRows];        // token of a row
+    alignas(16) uint8_t act_row[kMaxActive][16];     // row of token t, kNoRow: the token did not choose this expert
     float   row_w[kMaxRows];          // routing weight of a row (1 for shared)
     int32_t row_live[kMaxRows];       // 0: expert absent, the row's output must be skipped
 };
@@ -63,7 +56,6 @@ constexpr int kDraftSlotReplicas = 16;   // copies of the draft kernel's router-
 // inside the first block (the `tickets` block, kWsHeadBytes): the verify call's arrival counter and the
 // draft calls' status word (0: fine, 1: a wait for the router result ran out of polls)
 constexpr size_t kWsArrivalsOffset = 128, kWsStatusOffset = 192;
-constexpr size_t kWsTokenArrivalsOffset = 256;           // MOE_MAX_TOKENS counters of the verify call's router
 constexpr size_t kWsHeadBytes = 512;                     // size of that first block
 constexpr uint32_t kDefaultSpinLimit = 1u << 22;
 
@@ -87,6 +79,8 @@ size_t prefill_logit_rows(const Shape &s);       // rows of E logits the workspa
 void launch_prefill_logits(const Shape &s, const void *x, const void *wr, double *parts, int32_t *count, hipStream_t st);
 void launch_prefill_topk(const Shape &s, const double *parts, const float *bias, int32_t *ids, float *w, float *conf,
                          int32_t *count, int32_t *list, hipStream_t st);
+// the verify call's router and plan: fp64 logits [T, E], the plan but its row weights, the ids (plan->ids and ids_out) and
+// the missing list; arrivals: a counter in the workspace, zero between launches
 struct PlanArgs {
     Plan *plan;
     const void *pool; size_t slot_stride;
@@ -96,10 +90,8 @@ struct PlanArgs {
     int32_t *ids_out;
     int32_t *missing; int32_t *n_missing;
 };
-// router + plan in one launch; logits: [T, E] fp64 scratch; token_arrivals [MOE_MAX_TOKENS] and
-// arrivals: counters in the workspace, zero between launches
-void launch_route_plan(const Shape &s, const void *x, const void *wr, const float *bias, const PlanArgs &a,
-                       double *logits, uint32_t *token_arrivals, uint32_t *arrivals, hipStream_t st);
+void launch_verify_route(const Shape &s, const void *x, const void *wr, const float *bias, const PlanArgs &a,
+                         double *logits, uint32_t *arrivals, hipStream_t st);
 void launch_union(const int32_t *ids, int n_ids, int E, const int32_t *slot,
                   uint64_t *mask, int32_t *list, int32_t *n_list,
                   int32_t *missing, int32_t *n_missing, hipStream_t st);
@@ -161,16 +153,17 @@ void launch_prefill_down(const Shape &s, const PrefillCall &p, int max_items, hi
 void launch_prefill_combine(const Shape &s, const PrefillCall &p, hipStream_t st);
 
 // expert_bf16.hip
-// hb_lo != nullptr: the intermediate is kept as a bf16 hi + lo pair (draft-pass precision)
-void launch_bf16_gateup(const Shape &s, const Plan *plan, int first_active, int n_active_max,
-                        const void *x, void *hb, void *hb_lo, hipStream_t st);
-void launch_bf16_down(const Shape &s, const Plan *plan, int first_active, int n_active_max,
-                      const void *hb, float *obuf, hipStream_t st);
-// the same product, each row's outputs added to y[row_tok[row]] (fp32, [T,H]) with atomics; the
-// intermediate is the bf16 hi + lo pair
-void launch_bf16_down_add(const Shape &s, const Plan *plan, int first_active, int n_active_max,
-                          const void *hb, const void *hb_lo, float *y, hipStream_t st);
-// y[t] (bf16) = (accumulate ? y[t] : 0) + the token's live rows of obuf ([rows][H] fp32)
-void launch_combine(const Shape &s, const Plan *plan, const float *obuf, int accumulate, void *y, hipStream_t st);
+// The verify call's gate/up launch on the plan, which also writes the rows' routing weights
+void launch_verify_gateup(const Shape &s, const Plan *plan, const void *x, const double *logits, const int32_t *ids, float *row_w,
+                          void *hb, hipStream_t st);
+// the down products of the plan's experts into obuf ([rows][H] fp32); the last workgroup of every 32 output columns to
+// arrive (counted in the tags of the exchange slots, zero before and after) writes y[t] (bf16) = (accumulate ? y[t] : 0) +
+// the token's live rows
+void launch_verify_down(const Shape &s, const Plan *plan, const void *hb, float *obuf, unsigned long long *slots, size_t slot_bytes,
+                        int accumulate, void *y, hipStream_t st);
+// The draft call's shared experts on the plan of its launch: the intermediate is kept as a bf16 hi + lo pair, and each
+// row's outputs are added to y[token] (fp32, [T,H]) with atomics
+void launch_shared_gateup(const Shape &s, const Plan *plan, const void *x, void *hb, void *hb_lo, hipStream_t st);
+void launch_shared_down_add(const Shape &s, const Plan *plan, const void *hb, const void *hb_lo, float *y, hipStream_t st);
 
 }  // namespace moespeq

@@ -9,6 +9,7 @@
 // Section 3.4.4: assignments are regrouped per expert.  Section 2.3 / 3.2.2: union of the
 // experts of a window and the part of it that is not resident.
 #include "plan.h"
+#include "stream.h"
 #include "wave.h"
 
 namespace moespeq {
@@ -170,228 +171,153 @@ void perm_kernel(const int32_t *__restrict__ ids, int n, int E, int32_t *count, 
     histogram_perm(s_ids, n, E, count, off, perm, s_count);
 }
 
-// Builds the execution plan: histogram / permutation, the list of experts to run (shared
-// experts at active indices [0, S), then present routed experts ascending), their weight
-// pointers and row ranges, the per-row token / weight / live flags, and the missing list.  The ids and weights
-// come from other workgroups of the launch: stored and loaded at agent scope.
 template <typename V>
 __device__ inline void put(V *p, V v) { __hip_atomic_store(p, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT); }
 template <typename V>
 __device__ inline V get(const V *p) { return __hip_atomic_load(p, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT); }
 
-__device__ inline void plan_body(Plan *__restrict__ plan, int T, int E, int k, int S,
-                 const char *pool, size_t slot_stride,
-                 const int32_t *__restrict__ slot_of_expert,
-                 const char *shared, size_t shared_stride, int flags,
-                 int32_t *ids_out, int32_t *missing, int32_t *n_missing)
-{
-    __shared__ int32_t s_ids[MOE_MAX_ASSIGN];
-    __shared__ int32_t s_count[MOE_MAX_EXPERTS];
-    __shared__ int32_t s_slot[MOE_MAX_EXPERTS];
-    __shared__ unsigned char s_listed[MOE_MAX_EXPERTS];
-    __shared__ int32_t s_off[MOE_MAX_EXPERTS + 1];     // offsets and permutation stay in LDS for the
-    __shared__ int32_t s_perm[MOE_MAX_ASSIGN];         // steps below; the plan gets a copy
-    __shared__ int32_t s_nact, s_nmiss;
-    const int n = T * k;
-    const bool only_listed = (flags & MOE_VERIFY_ONLY_LISTED) != 0;
+// Router and plan of the verify call.  One workgroup per expert row and up to eight tokens: its eight waves are shared out
+// over the tokens, the waves of a token splitting H, and a wave keeps its loads of a batch in flight.  The workgroup
+// that arrives last (a counter in the workspace, put back to zero) has all logits in reach: one wave per token selects,
+// then the present experts are listed in ascending order behind the shared ones.  The softmax is not on this path: the
+// gate/up launch computes the rows' weights on the side.  Ids and logits travel at agent scope.
+// Bound: the launch and a chain of four round trips to memory (rows, stores, counter, logits).
+// (A counter per token and another over all, the softmax and a permutation of the rows in the chain: 12.6 us for 8 tokens
+// x 128 experts x 2048 inputs, now 9.0; 5 x 16 x 4096: 10.6 / 6.7.  Logits alone, each workgroup of the next launch
+// finding its own expert's tokens in them: 4.8 us here, but 6 us more there, for the workgroups of experts nobody chose.)
+constexpr int kVerifyWaves = 8;
 
-    for (int a = threadIdx.x; a < n; a += blockDim.x) {
-        int id = get(&plan->ids[a]);
-        s_ids[a] = id;
-        if (ids_out) ids_out[a] = id;
-    }
-    for (int e = threadIdx.x; e < E; e += blockDim.x) {
-        s_slot[e] = slot_of_expert[e];
-        s_listed[e] = only_listed ? 0 : 1;
-    }
-    __syncthreads();
-    if (only_listed) {
-        int nin = *n_missing;
-        nin = nin < 0 ? 0 : (nin > E ? E : nin);
-        for (int i = threadIdx.x; i < nin; i += blockDim.x) {
-            int e = missing[i];
-            if (e >= 0 && e < E) s_listed[e] = 1;
-        }
-    }
-    __syncthreads();
-    histogram_perm(s_ids, n, E, plan->count, s_off, s_perm, s_count);
-    for (int e = threadIdx.x; e <= E; e += blockDim.x) plan->off[e] = s_off[e];
-    for (int i = threadIdx.x; i < n; i += blockDim.x) plan->perm[i] = s_perm[i];
-
-    // shared experts: active slots [0, S), rows T*k + s*T + t
-    for (int i = threadIdx.x; i < S * T; i += blockDim.x) {
-        plan->row_tok[n + i] = i % T;
-        plan->row_w[n + i] = 1.f;
-        plan->row_live[n + i] = only_listed ? 0 : 1;
-    }
-    if ((int)threadIdx.x < S) {
-        int s = threadIdx.x;
-        plan->act_expert[s] = E + s;
-        plan->act_off[s] = n + s * T;
-        plan->act_cnt[s] = only_listed ? 0 : T;
-        plan->act_w0[s] = (uint64_t)(shared + (size_t)s * shared_stride);
-    }
-    // routed experts: ordered compaction, 64 experts per step, by wave 0
-    if (threadIdx.x < 64) {
-        int nact = S, nmiss = 0;
-        for (int base = 0; base < E; base += 64) {
-            int e = base + threadIdx.x;
-            bool used = e < E && s_count[e] > 0 && s_listed[e];
-            bool present = used && s_slot[e] >= 0;
-            bool absent = used && s_slot[e] < 0;
-            unsigned long long bp = __ballot(present), ba = __ballot(absent);
-            unsigned long long below = (1ull << threadIdx.x) - 1ull;
-            if (present) {
-                int u = nact + __popcll(bp & below);
-                int slot = s_slot[e];
-                plan->act_expert[u] = e;
-                plan->act_off[u] = s_off[e];
-                plan->act_cnt[u] = s_count[e];
-                plan->act_w0[u] = (uint64_t)(pool + (size_t)slot * slot_stride);
-            }
-            if (absent) missing[nmiss + __popcll(ba & below)] = e;
-            nact += __popcll(bp);
-            nmiss += __popcll(ba);
-        }
-        if (threadIdx.x == 0) { s_nact = nact; s_nmiss = nmiss; }
-    }
-    __syncthreads();
-    for (int pos = threadIdx.x; pos < n; pos += blockDim.x) {
-        int a = s_perm[pos];
-        int e = s_ids[a];
-        plan->row_tok[pos] = a / k;
-        plan->row_w[pos] = get(&plan->w[a]);
-        plan->row_live[pos] = (s_listed[e] && s_slot[e] >= 0) ? 1 : 0;
-    }
-    if (threadIdx.x == 0) {
-        plan->n_active = s_nact;
-        plan->n_routed_active = s_nact - S;
-        plan->n_rows = n + S * T;
-        plan->n_missing = s_nmiss;
-        if (n_missing) *n_missing = s_nmiss;
-    }
-}
-
-struct PlanKernelArgs {
-    Plan *plan; int T, E, k, S;
+struct VerifyRouteArgs {
+    Plan *plan; int T, H, E, k, S;
     const char *pool; size_t slot_stride;
-    const int32_t *slot_of_expert; const char *shared; size_t shared_stride; int flags;
+    const int32_t *slot_of_expert; const char *shared; size_t shared_stride; int only_listed;
     int32_t *ids_out; int32_t *missing; int32_t *n_missing;
+    double *logits; uint32_t *arrivals;
 };
 
-// Router and plan in one launch (the verify call).  Workgroup (b, t) reduces the router rows of
-// experts 16 b .. 16 b + 15 for token t, one row per wave, and stores the fp64 logits at agent
-// scope; the workgroup that arrives last for its token (a counter per token) has all of the
-// token's logits in reach, ranks them, forms the softmax weights and stores ids / weights /
-// confidences; the workgroup that arrives last of all builds the plan.  All counters live in the
-// workspace, are zero between launches and are put back to zero by the last arrival.  (One
-// workgroup per token computing all E rows took 25 us for 128 experts: the instruction rate of
-// the one compute unit a token ran on.)
-constexpr int kRouteBlock = kRouteThreads / 64;          // experts per workgroup: one per wave
-
-__global__ __launch_bounds__(kRouteThreads)
-void route_plan_kernel(const uint16_t *__restrict__ x, const uint16_t *__restrict__ wr,
-                       const float *__restrict__ bias, int H, int renorm, const PlanKernelArgs a,
-                       double *logits, uint32_t *token_arrivals, uint32_t *arrivals)
+template <int NR>                            // NR: 64 NR >= E
+__device__ inline int select_of_token(const VerifyRouteArgs &a, int t, int lane)
 {
-    __shared__ double s_logit[MOE_MAX_EXPERTS];
-    __shared__ int32_t s_rank[MOE_MAX_EXPERTS];
+    double l[NR];
+    int rank[NR];
+#pragma unroll
+    for (int i = 0; i < NR; ++i) l[i] = get(&a.logits[(size_t)t * a.E + (lane + 64 * i < a.E ? lane + 64 * i : a.E - 1)]);
+    return wave::select_topk(l, a.E, a.k, lane, rank);
+}
+
+__global__ __launch_bounds__(kVerifyWaves * 64)
+void verify_route_kernel(const uint16_t *__restrict__ x, const uint16_t *__restrict__ wr, const float *__restrict__ bias,
+                         const VerifyRouteArgs a)
+{
+    __shared__ double s_part[kVerifyWaves];
+    __shared__ __attribute__((aligned(16))) uint8_t s_row[MOE_MAX_EXPERTS][16];      // row of (expert, token)
+    __shared__ uint32_t s_chosen[MOE_MAX_EXPERTS / 32], s_listed[MOE_MAX_EXPERTS / 32];
     __shared__ int s_last;
-    const int t = blockIdx.y, E = a.E, k = a.k;
-    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-    const int nblk = gridDim.x;
-    const int e = blockIdx.x * kRouteBlock + wave;
-    if (e < E) {
-        const uint16_t *xt = x + (size_t)t * H, *row = wr + (size_t)e * H;
-        // eight independent partial sums instead of one chain of dependent fp64 additions; the
-        // products are exact in fp32 (bf16 x bf16)
-        double part[8] = {0.0, 0.0, 0.0, 0.0, 0.0, 0.0, 0.0, 0.0};
-        for (int c = lane; c < H / 8; c += 64) {
-            uint4 xv = *reinterpret_cast<const uint4 *>(xt + c * 8);
-            uint4 wv = *reinterpret_cast<const uint4 *>(row + c * 8);
-            const uint32_t xs[4] = {xv.x, xv.y, xv.z, xv.w};
-            const uint32_t ws[4] = {wv.x, wv.y, wv.z, wv.w};
+    const int T = a.T, H = a.H, E = a.E, k = a.k, S = a.S;
+    const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int e = blockIdx.x, t0 = blockIdx.y * kVerifyWaves, n = T - t0 < kVerifyWaves ? T - t0 : kVerifyWaves;
+    const int lt = n <= 1 ? 0 : (n <= 2 ? 1 : (n <= 4 ? 2 : 3));
+    const int t = wave & ((1 << lt) - 1), part = wave >> lt, step = (kVerifyWaves >> lt) * 64;
+    const uint16_t *xt = x + (size_t)(t0 + (t < n ? t : n - 1)) * H, *row = wr + (size_t)e * H;
+    const int chunks = H / 8;
+    const float b = bias ? bias[e] : 0.f;
+    double acc[4] = {0.0, 0.0, 0.0, 0.0};
+    constexpr int kB = 4;
+    for (int c0 = part * 64 + lane; c0 - lane < chunks; c0 += kB * step) {
+        uint4 xv[kB], wv[kB];
+#pragma unroll
+        for (int j = 0; j < kB; ++j) {
+            const int c = c0 + j * step, cc = c < chunks ? c : chunks - 1;
+            xv[j] = *reinterpret_cast<const uint4 *>(xt + cc * 8);
+            wv[j] = *reinterpret_cast<const uint4 *>(row + cc * 8);
+        }
+#pragma unroll
+        for (int j = 0; j < kB; ++j) {
+            const bool in = c0 + j * step < chunks;              // (a position past the end counts as zeros)
+            const uint32_t xs[4] = {xv[j].x, xv[j].y, xv[j].z, xv[j].w}, ws[4] = {wv[j].x, wv[j].y, wv[j].z, wv[j].w};
 #pragma unroll
             for (int i = 0; i < 4; ++i) {
-                part[2 * i] += (double)(__uint_as_float(xs[i] << 16) * __uint_as_float(ws[i] << 16));
-                part[2 * i + 1] += (double)(__uint_as_float(xs[i] & 0xffff0000u) * __uint_as_float(ws[i] & 0xffff0000u));
+                const uint32_t xi = in ? xs[i] : 0u, wi = in ? ws[i] : 0u;
+                acc[i] += (double)(__uint_as_float(xi << 16) * __uint_as_float(wi << 16));      // bf16 x bf16 is exact in fp32
+                acc[i] += (double)(__uint_as_float(xi & 0xffff0000u) * __uint_as_float(wi & 0xffff0000u));
             }
         }
-        double acc = ((part[0] + part[1]) + (part[2] + part[3])) + ((part[4] + part[5]) + (part[6] + part[7]));
-        acc = wave::sum(acc);
-        if (lane == 0) {
-            acc += bias ? (double)bias[e] : 0.0;
-            if (nblk > 1) __hip_atomic_store(&logits[(size_t)t * E + e], acc, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-            else { s_logit[e] = acc; s_rank[e] = 0; }
-        }
     }
-    if (nblk > 1) {
-        asm volatile("s_waitcnt vmcnt(0)" ::: "memory");          // this thread's stores have been performed
-        __syncthreads();
-        if (threadIdx.x == 0) {
-            const uint32_t n = __hip_atomic_fetch_add(&token_arrivals[t], 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-            s_last = n == (uint32_t)nblk - 1;
-            if (s_last) __hip_atomic_store(&token_arrivals[t], 0u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-        }
-        __syncthreads();
-        if (!s_last) return;
-        for (int i = threadIdx.x; i < E; i += kRouteThreads) {
-            s_logit[i] = __hip_atomic_load(&logits[(size_t)t * E + i], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-            s_rank[i] = 0;
-        }
-    }
-    __syncthreads();
-    // Rank of every logit under (larger first, lower index first among equals), counted by all
-    // sixteen waves, each over its share of the experts; the order is strict, so the ranks are a
-    // permutation and rank < k is the selection.
-    wave::count_ranks(s_logit, s_rank, E, lane, wave, kRouteThreads / 64);
+    const double sum = wave::sum((acc[0] + acc[1]) + (acc[2] + acc[3]));
+    if (lane == 0) s_part[wave] = sum;
     __syncthreads();
     if (wave == 0) {
-        double mine[4], pe[4];
-        int rank[4];
-        double mx = -INFINITY;
+        if (lane < n) {
+            double l = 0.0;
 #pragma unroll
-        for (int i = 0; i < 4; ++i) {
-            const int ei = lane + 64 * i;
-            const bool have = 64 * i < E && ei < E;
-            mine[i] = have ? s_logit[ei] : -INFINITY;
-            rank[i] = have ? s_rank[ei] : MOE_MAX_EXPERTS;
-            mx = fmax(mx, mine[i]);
+            for (int w = 0; w < kVerifyWaves; ++w) l += (w & ((1 << lt) - 1)) == lane ? s_part[w] : 0.0;
+            put(&a.logits[(size_t)(t0 + lane) * E + e], l + (double)b);
         }
-        mx = wave::max(mx);
-        double den = 0.0, sel = 0.0;
-#pragma unroll
-        for (int i = 0; i < 4; ++i) {
-            pe[i] = rank[i] < MOE_MAX_EXPERTS ? exp(mine[i] - mx) : 0.0;
-            den += pe[i];
-        }
-        den = wave::sum(den);
-#pragma unroll
-        for (int i = 0; i < 4; ++i) {
-            pe[i] = pe[i] / den;
-            sel += rank[i] < k ? pe[i] : 0.0;
-        }
-        sel = wave::sum(sel);
-#pragma unroll
-        for (int i = 0; i < 4; ++i) {
-            if (rank[i] < k) {
-                const size_t o = (size_t)t * k + rank[i];
-                put(&a.plan->ids[o], (int32_t)(lane + 64 * i));
-                put(&a.plan->w[o], renorm ? (float)(pe[i] / sel) : (float)pe[i]);
-            }
+        asm volatile("s_waitcnt vmcnt(0)" ::: "memory");          // the stores have been performed
+        if (lane == 0) {
+            const uint32_t before = __hip_atomic_fetch_add(a.arrivals, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+            s_last = before == gridDim.x * gridDim.y - 1;
         }
     }
-    asm volatile("s_waitcnt vmcnt(0)" ::: "memory");          // this thread's stores have been performed
-    __syncthreads();
-    if (threadIdx.x == 0) {
-        const uint32_t n = __hip_atomic_fetch_add(arrivals, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-        s_last = n == gridDim.y - 1;
-        if (s_last) __hip_atomic_store(arrivals, 0u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-    }
+    for (int i = tid; i < E * 4; i += kVerifyWaves * 64) reinterpret_cast<uint32_t *>(s_row)[i] = kNoRow * 0x01010101u;
+    if (tid < MOE_MAX_EXPERTS / 32) { s_chosen[tid] = 0u; s_listed[tid] = a.only_listed ? 0u : ~0u; }
     __syncthreads();
     if (!s_last) return;
-    plan_body(a.plan, a.T, a.E, a.k, a.S, a.pool, a.slot_stride, a.slot_of_expert,
-              a.shared, a.shared_stride, a.flags, a.ids_out, a.missing, a.n_missing);
+    if (tid == 0) put(a.arrivals, 0u);
+    for (int tt = wave; tt < T; tt += kVerifyWaves) {
+        const int id = E <= 64 ? select_of_token<1>(a, tt, lane) : E <= 128 ? select_of_token<2>(a, tt, lane) : select_of_token<4>(a, tt, lane);
+        if (lane < k) {
+            s_row[id][tt] = (uint8_t)(tt * k + lane);
+            atomicOr(&s_chosen[id >> 5], 1u << (id & 31));
+            a.plan->ids[tt * k + lane] = id;
+            if (a.ids_out) a.ids_out[tt * k + lane] = id;
+        }
+    }
+    if (a.only_listed) {
+        int nin = *a.n_missing;
+        nin = nin < 0 ? 0 : (nin > E ? E : nin);
+        for (int i = tid; i < nin; i += kVerifyWaves * 64) {
+            const int m = a.missing[i];
+            if (m >= 0 && m < E) atomicOr(&s_listed[m >> 5], 1u << (m & 31));
+        }
+    }
+    // shared experts: active indices [0, S), rows T k + s T + t; left out by a call for listed experts
+    Plan *plan = a.plan;
+    if (tid < S * 16) plan->act_row[tid / 16][tid % 16] = tid % 16 < T && !a.only_listed ? (uint8_t)(T * k + tid / 16 * T + tid % 16) : kNoRow;
+    if (tid < S) plan->act_w0[tid] = (uint64_t)(a.shared + (size_t)tid * a.shared_stride);
+    if (tid < S * T) plan->row_live[T * k + tid] = a.only_listed ? 0 : 1;
+    __syncthreads();
+    // routed experts: ordered compaction, 64 experts per step
+    if (wave != 0) return;
+    int nact = S, nmiss = 0;
+    for (int base = 0; base < E; base += 64) {
+        const int o = base + lane;
+        const bool used = o < E && ((s_chosen[o >> 5] >> (o & 31)) & 1u);
+        const bool listed = used && ((s_listed[o >> 5] >> (o & 31)) & 1u);
+        const int slot = used ? a.slot_of_expert[o] : -1;
+        const unsigned long long bp = __ballot(listed && slot >= 0), ba = __ballot(listed && slot < 0);
+        const unsigned long long below = (1ull << lane) - 1ull;
+        if (used) {
+            const u32x4 rows = *reinterpret_cast<const u32x4 *>(s_row[o]);
+            if (listed && slot >= 0) {
+                const int u = nact + __popcll(bp & below);
+                plan->act_w0[u] = (uint64_t)(a.pool + (size_t)slot * a.slot_stride);
+                *reinterpret_cast<u32x4 *>(plan->act_row[u]) = rows;
+            }
+            for (int tt = 0; tt < T; ++tt) {
+                const uint32_t row = s_row[o][tt];
+                if (row != kNoRow) plan->row_live[row] = listed && slot >= 0 ? 1 : 0;
+            }
+        }
+        if (listed && slot < 0) a.missing[nmiss + __popcll(ba & below)] = o;
+        nact += __popcll(bp);
+        nmiss += __popcll(ba);
+    }
+    if (lane == 0) {
+        plan->n_active = nact;
+        plan->n_live = a.only_listed ? nact - S : nact;
+        *a.n_missing = nmiss;
+    }
 }
 
 // Router of a long run of tokens, first launch: partial logits [part][T][E] in fp64 over a share of H.  A
@@ -616,22 +542,18 @@ void launch_perm(const Shape &s, const int32_t *ids, int32_t *count, int32_t *of
     launch(perm_kernel, dim3(1), dim3(256), 0, st, ids, s.T * s.k, s.E, count, off, perm);
 }
 
-static PlanKernelArgs plan_kernel_args(const Shape &s, const PlanArgs &a)
+void launch_verify_route(const Shape &s, const void *x, const void *wr, const float *bias, const PlanArgs &p,
+                         double *logits, uint32_t *arrivals, hipStream_t st)
 {
-    PlanKernelArgs k;
-    k.plan = a.plan; k.T = s.T; k.E = s.E; k.k = s.k; k.S = s.S;
-    k.pool = (const char *)a.pool; k.slot_stride = a.slot_stride;
-    k.slot_of_expert = a.slot_of_expert; k.shared = (const char *)a.shared; k.shared_stride = a.shared_stride;
-    k.flags = a.flags; k.ids_out = a.ids_out; k.missing = a.missing; k.n_missing = a.n_missing;
-    return k;
-}
-
-void launch_route_plan(const Shape &s, const void *x, const void *wr, const float *bias, const PlanArgs &a,
-                       double *logits, uint32_t *token_arrivals, uint32_t *arrivals, hipStream_t st)
-{
-    const dim3 grid((s.E + kRouteBlock - 1) / kRouteBlock, s.T);
-    launch(route_plan_kernel, grid, dim3(kRouteThreads), 0, st, (const uint16_t *)x, (const uint16_t *)wr,
-           bias, s.H, s.renorm, plan_kernel_args(s, a), logits, token_arrivals, arrivals);
+    VerifyRouteArgs a;
+    a.plan = p.plan; a.T = s.T; a.H = s.H; a.E = s.E; a.k = s.k; a.S = s.S;
+    a.pool = (const char *)p.pool; a.slot_stride = p.slot_stride;
+    a.slot_of_expert = p.slot_of_expert; a.shared = (const char *)p.shared; a.shared_stride = p.shared_stride;
+    a.only_listed = (p.flags & MOE_VERIFY_ONLY_LISTED) ? 1 : 0;
+    a.ids_out = p.ids_out; a.missing = p.missing; a.n_missing = p.n_missing;
+    a.logits = logits; a.arrivals = arrivals;
+    launch(verify_route_kernel, dim3(s.E, (s.T + kVerifyWaves - 1) / kVerifyWaves), dim3(kVerifyWaves * 64), 0, st,
+           (const uint16_t *)x, (const uint16_t *)wr, bias, a);
 }
 
 void launch_union(const int32_t *ids, int n_ids, int E, const int32_t *slot,
