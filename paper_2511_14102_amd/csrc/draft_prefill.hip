@@ -72,13 +72,19 @@ namespace {
 constexpr int kItemTokens = 64;                   // slots of an item: four token blocks of 16
 constexpr int kTileThreads = 256, kTileWaves = 4;
 constexpr int kXcds = 8;
+// The items: shared experts' and full ones, then what is left of every expert's run, four, three, two and one token blocks of 16.
+// n_items: their count, then each segment's.  A launch is only one and a half to three rounds of workgroups (two a compute
+// unit) where a prompt is of ordinary length, so that its end counts: largest first, it ends with the short ones.  us per
+// call, expert by expert / largest first: phi shape, 512 tokens (24 items, 50 and 16 columns) 350 / 314, dsv2lite, 333
+// tokens (76 items, 11 and 8 columns) 157 / 150; mixtral, 4096 tokens (30 and 4 rounds) the same.
+constexpr int kSegments = 5;
 constexpr float kOffset = -24.f;                  // factor of a stored group sum: takes 16 + q to q - 8
 
 struct TileArgs {
     const char *q, *sz;              // int4 codes / scale(-zero) blobs of the routed experts
     size_t stride_q, stride_sz;
     const PrefillItem *items;
-    const int32_t *n_items;
+    const int32_t *n_items;          // [1 + kSegments]
     const char *act0, *act1;         // operand tiles [(item nk + u) 4 + tb] of 1 KiB: x, or h and its remainder
     const char *act_sums;            // -24 x group sums, fp32 [(item 4 nz + group) 64 + token]; nz = ceil(groups / 4)
     const char *zeros;               // 4 KiB of zeros
@@ -163,13 +169,23 @@ void prefill_tile_kernel(TileArgs a)
     const int H = a.H, I = a.I;
     const int nk = DOWN ? I / 32 : H / 32, G = nk / KPG, nz = (G + 3) / 4;
     const int tiles = DOWN ? H / 64 : I / 32, cols = (tiles + kTileWaves - 1) / kTileWaves;
-    // Workgroups go to the XCDs in turn: XCD x takes the x-th contiguous eighth of the (column, item)
-    // pairs, items fastest, so that the items of one expert, neighbours in the list, read its
-    // weight tiles through the same L2.
-    const int n_items = *a.n_items, total = cols * n_items, per = (total + kXcds - 1) / kXcds;
-    const int pair = ((int)blockIdx.x % kXcds) * per + (int)blockIdx.x / kXcds;
-    if ((int)blockIdx.x / kXcds >= per || pair >= total) return;
-    const int col = pair / n_items, item = pair % n_items;
+    // Workgroups go to the XCDs in turn.  The item list is in segments of falling size; of each segment XCD x takes the
+    // x-th contiguous eighth of the (column, item) pairs, items fastest, so that the items of one expert,
+    // neighbours in the list, read its weight tiles through the same L2, and the smallest workgroups come last.
+    int pair = -1, seg_items = 1, first_item = 0;
+    for (int seg = 0, at = (int)blockIdx.x / kXcds; seg < kSegments; ++seg) {
+        const int n = a.n_items[1 + seg], total = cols * n, per = (total + kXcds - 1) / kXcds;
+        if (at < per) {
+            pair = ((int)blockIdx.x % kXcds) * per + at;
+            pair = pair < total ? pair : -1;
+            seg_items = n;
+            break;
+        }
+        at -= per;
+        first_item += n;
+    }
+    if (pair < 0) return;
+    const int col = pair / seg_items, item = first_item + pair % seg_items;
     const PrefillItem it = a.items[item];
     const int tid = threadIdx.x, lane = tid & 63, r = lane & 15, c = lane >> 4;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
@@ -569,7 +585,7 @@ void prefill_tile_kernel(TileArgs a)
 // hold zeros.  (The shared experts read one copy.)  Also the group sums x -24, [(item 4 nz + group) 64 + token].  One wave per
 // (block, four tiles): 128 inputs, whole groups.
 // Which item that is: kPlanned: prefill_plan_kernel has written the items; else it follows from the experts'
-// counts (the shared experts' S ceil(T / chunk) items come first, then every expert's; expert
+// counts (the shared experts' S ceil(T / chunk) items come first, then the routed ones in their segments; expert
 // e's assignments are list[e T ..]); each workgroup sums the counts up for itself, the first one also writes the items,
 // and a block's first workgroup the slots of its assignments.  The first workgroup also writes the tile of zeros.
 template <int KPG, bool kPlanned>
@@ -587,38 +603,60 @@ void prefill_stage_kernel(const uint16_t *__restrict__ x, const int32_t *__restr
         it = items[item];
         if ((item >= n) | (16 * tb >= it.cnt) | (it.src != item)) return;
     } else {
-        __shared__ int32_t s_end[4];                     // per wave: items of its 64 experts
+        __shared__ int32_t s_count[kSegments][4];        // per segment and wave of 64 experts: items
         __shared__ PrefillItem s_item;
-        const int chunks = (T + chunk - 1) / chunk;
+        const int chunks = (T + chunk - 1) / chunk, wave = tid >> 6, lane = tid & 63;
         if (tid == 0) s_item = PrefillItem{0, 0, 0, -1};
-        // thread e: expert e's items are [begin, begin + mine)
-        const int cnt = tid < E ? count[tid] : 0, mine = (cnt + chunk - 1) / chunk;
-        int incl = mine;
+        // thread e: expert e's full items are [begin, begin + full), its last one is item `rest`
+        const int cnt = tid < E ? count[tid] : 0, full = cnt / chunk;
+        const int blocks_left = (cnt - full * chunk + 15) >> 4, seg = blocks_left ? kSegments - blocks_left : 0;
+        int incl = full;
 #pragma unroll
         for (int d = 1; d < 64; d <<= 1) {
             const int v = __shfl_up(incl, d, 64);
-            if ((tid & 63) >= d) incl += v;
+            if (lane >= d) incl += v;
         }
-        if ((tid & 63) == 63) s_end[tid >> 6] = incl;
+        if (lane == 63) s_count[0][wave] = incl;
+        int rest = 0;
+#pragma unroll
+        for (int g = 1; g < kSegments; ++g) {
+            const unsigned long long in = __ballot(seg == g);
+            if (lane == 0) s_count[g][wave] = __popcll(in);
+            if (seg == g) rest = __popcll(in & ((1ull << lane) - 1ull));
+        }
         __syncthreads();
-        int begin = S * chunks + incl - mine, total = S * chunks;
-        for (int w = 0; w < 4; ++w) {
-            begin += w < (tid >> 6) ? s_end[w] : 0;
-            total += s_end[w];
+        int begin = S * chunks + incl - full, total = S * chunks, n_seg[kSegments];
+#pragma unroll
+        for (int g = 0; g < kSegments; ++g) {
+            n_seg[g] = g == 0 ? S * chunks : 0;
+            rest += seg == g ? total : 0;
+            for (int w = 0; w < 4; ++w) {
+                const int n = s_count[g][w];
+                begin += g == 0 && w < wave ? n : 0;
+                rest += seg == g && w < wave ? n : 0;
+                n_seg[g] += n;
+                total += n;
+            }
         }
-        auto chunk_of = [&](int j) {                     // of this thread's expert
-            return PrefillItem{tid, tid * T + j * chunk, cnt - j * chunk < chunk ? cnt - j * chunk : chunk, begin + j};
+        auto chunk_of = [&](int j, int at) {             // of this thread's expert
+            return PrefillItem{tid, tid * T + j * chunk, cnt - j * chunk < chunk ? cnt - j * chunk : chunk, at};
         };
         auto shared_item = [&](int i) {
             const int j = i % chunks;
             return PrefillItem{E + i / chunks, j * chunk, T - j * chunk < chunk ? T - j * chunk : chunk, j};
         };
-        if (item >= begin && item < begin + mine) s_item = chunk_of(item - begin);
+        if (item >= begin && item < begin + full) s_item = chunk_of(item - begin, item);
+        if (seg != 0 && item == rest) s_item = chunk_of(full, item);
         if (tid == 0 && item < S * chunks) s_item = shared_item(item);
         if (first) {
             for (int i = tid; i < S * chunks; i += 256) items[i] = shared_item(i);
-            for (int j = 0; j < mine; ++j) items[begin + j] = chunk_of(j);
-            if (tid == 0) *n_items = total;
+            for (int j = 0; j < full; ++j) items[begin + j] = chunk_of(j, begin + j);
+            if (seg != 0) items[rest] = chunk_of(full, rest);
+            if (tid == 0) {
+                n_items[0] = total;
+#pragma unroll
+                for (int g = 0; g < kSegments; ++g) n_items[1 + g] = n_seg[g];
+            }
         }
         __syncthreads();
         if (item >= total) return;
@@ -669,7 +707,7 @@ void prefill_plan_kernel(const int32_t *__restrict__ ids, int n, int E, int T, i
                          PrefillItem *__restrict__ items, int32_t *__restrict__ n_items)
 {
     __shared__ int32_t s_count[MOE_MAX_EXPERTS], s_off[MOE_MAX_EXPERTS], s_fill[MOE_MAX_EXPERTS],
-        s_item0[MOE_MAX_EXPERTS];
+        s_full0[MOE_MAX_EXPERTS], s_rest[MOE_MAX_EXPERTS];           // first full item, item of the rest
     const int chunks = (T + chunk - 1) / chunk;
     for (int i = threadIdx.x; i < S * chunks; i += blockDim.x) {
         const int j = i % chunks;
@@ -679,22 +717,42 @@ void prefill_plan_kernel(const int32_t *__restrict__ ids, int n, int E, int T, i
     __syncthreads();
     for (int i = threadIdx.x; i < n; i += blockDim.x) atomicAdd(&s_count[ids[i]], 1);
     __syncthreads();
-    if (threadIdx.x == 0) {
+    if (threadIdx.x < 64) {
+        const int lane = threadIdx.x;
         int off = 0, item = S * chunks;
-        for (int e = 0; e < E; ++e) {
-            s_off[e] = off;
-            s_item0[e] = item;
-            off += s_count[e];
-            item += (s_count[e] + chunk - 1) / chunk;
+        for (int base = 0; base < E; base += 64) {
+            const int cnt = base + lane < E ? s_count[base + lane] : 0, full = cnt / chunk;
+            int a = cnt, f = full;
+#pragma unroll
+            for (int d = 1; d < 64; d <<= 1) {
+                const int av = __shfl_up(a, d, 64), fv = __shfl_up(f, d, 64);
+                if (lane >= d) { a += av; f += fv; }
+            }
+            if (base + lane < E) { s_off[base + lane] = off + a - cnt; s_full0[base + lane] = item + f - full; }
+            off += __shfl(a, 63);
+            item += __shfl(f, 63);
         }
-        *n_items = item;
+        if (lane == 0) n_items[1] = item;
+        for (int g = 1; g < kSegments; ++g) {
+            const int first = item;
+            for (int base = 0; base < E; base += 64) {
+                const int cnt = base + lane < E ? s_count[base + lane] : 0;
+                const bool in = (cnt % chunk + 15) / 16 == kSegments - g;
+                const unsigned long long b = __ballot(in);
+                if (in) s_rest[base + lane] = item + __popcll(b & ((1ull << lane) - 1ull));
+                item += __popcll(b);
+            }
+            if (lane == 0) n_items[1 + g] = item - first;
+        }
+        if (lane == 0) n_items[0] = item;
     }
     __syncthreads();
+    auto item_of = [&](int e, int j) { return j < s_count[e] / chunk ? s_full0[e] + j : s_rest[e]; };
     for (int i = threadIdx.x; i < n; i += blockDim.x) {
         const int e = ids[i];
         const int idx = atomicAdd(&s_fill[e], 1);
         list[s_off[e] + idx] = i;
-        slot_of[i] = (s_item0[e] + idx / chunk) * kItemTokens + idx % chunk;
+        slot_of[i] = item_of(e, idx / chunk) * kItemTokens + idx % chunk;
     }
     for (int e = threadIdx.x; e < E; e += blockDim.x) {
         const int cnt = s_count[e];
@@ -702,8 +760,8 @@ void prefill_plan_kernel(const int32_t *__restrict__ ids, int n, int E, int T, i
             PrefillItem it;
             it.expert = e; it.first = s_off[e] + j * chunk;
             it.cnt = cnt - j * chunk < chunk ? cnt - j * chunk : chunk;
-            it.src = s_item0[e] + j;
-            items[s_item0[e] + j] = it;
+            it.src = item_of(e, j);
+            items[it.src] = it;
         }
     }
 }
@@ -733,7 +791,7 @@ template <bool DOWN, bool SYM>
 void launch_tile_g(const TileArgs &t, int g, int tiles, int max_items, hipStream_t st)
 {
     const size_t pairs = (size_t)((tiles + kTileWaves - 1) / kTileWaves) * max_items;
-    const dim3 grid((unsigned)((pairs + kXcds - 1) / kXcds * kXcds)), block(kTileThreads);
+    const dim3 grid((unsigned)(((pairs + kXcds - 1) / kXcds + kSegments - 1) * kXcds)), block(kTileThreads);   // (each segment is rounded up)
     if (g == 32) launch(prefill_tile_kernel<DOWN, SYM, 1>, grid, block, 0, st, t);
     else if (g == 64) launch(prefill_tile_kernel<DOWN, SYM, 2>, grid, block, 0, st, t);
     else launch(prefill_tile_kernel<DOWN, SYM, 4>, grid, block, 0, st, t);

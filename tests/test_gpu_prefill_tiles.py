@@ -85,6 +85,7 @@ ROUTED = [
     LayerConfig(66, "r70", 320, 70, 64, 3, 32, 0, 1),      # ragged token and expert blocks, k-steps that do not fill a share
     LayerConfig(67, "r130", 192, 130, 64, 4, 64, 1, 0),    # more than 128 experts, a shared expert
     LayerConfig(68, "r5", 2112, 5, 64, 5, 64, 2, 1),       # few experts, shares of H, every token in every expert
+    LayerConfig(80, "r72", 512, 72, 1024, 6, 128, 1, 1),   # more than 64 experts with one to four token blocks left (items by size)
     LayerConfig(70, "r4160", 4160, 4, 64, 2, 64, 0, 1),    # the most shares of H (8 x 4 waves), 130 k-steps over them
 ]
 
