@@ -72,12 +72,15 @@ namespace {
 constexpr int kItemTokens = 64;                   // slots of an item: four token blocks of 16
 constexpr int kTileThreads = 256, kTileWaves = 4;
 constexpr int kXcds = 8;
-// The items: shared experts' and full ones, then what is left of every expert's run, four, three, two and one token blocks of 16.
+// The items: shared experts' and full ones, then what is left of every expert's run: four, three, and two or one token blocks of 16.
 // n_items: their count, then each segment's.  A launch is only one and a half to three rounds of workgroups (two a compute
 // unit) where a prompt is of ordinary length, so that its end counts: largest first, it ends with the short ones.  us per
 // call, expert by expert / largest first: phi shape, 512 tokens (24 items, 50 and 16 columns) 350 / 314, dsv2lite, 333
 // tokens (76 items, 11 and 8 columns) 157 / 150; mixtral, 4096 tokens (30 and 4 rounds) the same.
-constexpr int kSegments = 5;
+constexpr int kSegments = 4;
+constexpr int kSmallItem = 32;                    // items of small calls, whose launches are one round: all in the first segment
+// segment of the `left` (1 .. 63) last assignments of an expert
+__device__ inline int segment_of(int left) { return left > 48 ? 1 : left > 32 ? 2 : 3; }
 constexpr float kOffset = -24.f;                  // factor of a stored group sum: takes 16 + q to q - 8
 
 struct TileArgs {
@@ -172,20 +175,22 @@ void prefill_tile_kernel(TileArgs a)
     // Workgroups go to the XCDs in turn.  The item list is in segments of falling size; of each segment XCD x takes the
     // x-th contiguous eighth of the (column, item) pairs, items fastest, so that the items of one expert,
     // neighbours in the list, read its weight tiles through the same L2, and the smallest workgroups come last.
-    int pair = -1, seg_items = 1, first_item = 0;
-    for (int seg = 0, at = (int)blockIdx.x / kXcds; seg < kSegments; ++seg) {
-        const int n = a.n_items[1 + seg], total = cols * n, per = (total + kXcds - 1) / kXcds;
-        if (at < per) {
-            pair = ((int)blockIdx.x % kXcds) * per + at;
-            pair = pair < total ? pair : -1;
-            seg_items = n;
-            break;
+    int pair = 0, seg_items = 0, first_item = 0;
+    {
+        int at = (int)blockIdx.x / kXcds, first = 0;
+#pragma unroll
+        for (int seg = 0; seg < kSegments; ++seg) {                      // (all counts by one load, no branches)
+            const int n = a.n_items[1 + seg], per = (cols * n + kXcds - 1) / kXcds;
+            const bool here = at >= 0 && at < per;
+            pair = here ? ((int)blockIdx.x % kXcds) * per + at : pair;
+            seg_items = here ? n : seg_items;
+            first_item = here ? first : first_item;
+            at -= per;
+            first += n;
         }
-        at -= per;
-        first_item += n;
     }
-    if (pair < 0) return;
-    const int col = pair / seg_items, item = first_item + pair % seg_items;
+    if (pair >= cols * seg_items) return;
+    const int col = pair / seg_items, item = first_item + pair - col * seg_items;
     const PrefillItem it = a.items[item];
     const int tid = threadIdx.x, lane = tid & 63, r = lane & 15, c = lane >> 4;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
@@ -603,40 +608,42 @@ void prefill_stage_kernel(const uint16_t *__restrict__ x, const int32_t *__restr
         it = items[item];
         if ((item >= n) | (16 * tb >= it.cnt) | (it.src != item)) return;
     } else {
-        __shared__ int32_t s_count[kSegments][4];        // per segment and wave of 64 experts: items
+        __shared__ __align__(16) int32_t s_count[kSegments][4];        // per segment and wave of 64 experts: items
         __shared__ PrefillItem s_item;
         const int chunks = (T + chunk - 1) / chunk, wave = tid >> 6, lane = tid & 63;
+        const bool by_size = chunk > kSmallItem;
         if (tid == 0) s_item = PrefillItem{0, 0, 0, -1};
         // thread e: expert e's full items are [begin, begin + full), its last one is item `rest`
-        const int cnt = tid < E ? count[tid] : 0, full = cnt / chunk;
-        const int blocks_left = (cnt - full * chunk + 15) >> 4, seg = blocks_left ? kSegments - blocks_left : 0;
+        const int cnt = tid < E ? count[tid] : 0, shift = chunk > kSmallItem ? 6 : 5, full = (cnt + (by_size ? 0 : chunk - 1)) >> shift;
+        const int left = cnt - (full << shift), seg = left > 0 ? segment_of(left) : 0;
         int incl = full;
 #pragma unroll
         for (int d = 1; d < 64; d <<= 1) {
             const int v = __shfl_up(incl, d, 64);
             if (lane >= d) incl += v;
         }
-        if (lane == 63) s_count[0][wave] = incl;
-        int rest = 0;
+        int rest = 0, counts[kSegments];
 #pragma unroll
         for (int g = 1; g < kSegments; ++g) {
             const unsigned long long in = __ballot(seg == g);
-            if (lane == 0) s_count[g][wave] = __popcll(in);
-            if (seg == g) rest = __popcll(in & ((1ull << lane) - 1ull));
+            counts[g] = __popcll(in);
+            rest = seg == g ? __popcll(in & ((1ull << lane) - 1ull)) : rest;
+        }
+        if (lane == 63) {
+            counts[0] = incl;
+#pragma unroll
+            for (int g = 0; g < kSegments; ++g) s_count[g][wave] = counts[g];
         }
         __syncthreads();
         int begin = S * chunks + incl - full, total = S * chunks, n_seg[kSegments];
 #pragma unroll
         for (int g = 0; g < kSegments; ++g) {
-            n_seg[g] = g == 0 ? S * chunks : 0;
-            rest += seg == g ? total : 0;
-            for (int w = 0; w < 4; ++w) {
-                const int n = s_count[g][w];
-                begin += g == 0 && w < wave ? n : 0;
-                rest += seg == g && w < wave ? n : 0;
-                n_seg[g] += n;
-                total += n;
-            }
+            const int4 n = *reinterpret_cast<const int4 *>(s_count[g]);
+            const int before = (wave > 0 ? n.x : 0) + (wave > 1 ? n.y : 0) + (wave > 2 ? n.z : 0), sum = n.x + n.y + n.z + n.w;
+            begin += g == 0 ? before : 0;
+            rest += seg == g ? total + before : 0;
+            n_seg[g] = sum + (g == 0 ? S * chunks : 0);
+            total += sum;
         }
         auto chunk_of = [&](int j, int at) {             // of this thread's expert
             return PrefillItem{tid, tid * T + j * chunk, cnt - j * chunk < chunk ? cnt - j * chunk : chunk, at};
@@ -708,6 +715,7 @@ void prefill_plan_kernel(const int32_t *__restrict__ ids, int n, int E, int T, i
 {
     __shared__ int32_t s_count[MOE_MAX_EXPERTS], s_off[MOE_MAX_EXPERTS], s_fill[MOE_MAX_EXPERTS],
         s_full0[MOE_MAX_EXPERTS], s_rest[MOE_MAX_EXPERTS];           // first full item, item of the rest
+    const bool by_size = chunk > kSmallItem;
     const int chunks = (T + chunk - 1) / chunk;
     for (int i = threadIdx.x; i < S * chunks; i += blockDim.x) {
         const int j = i % chunks;
@@ -721,23 +729,24 @@ void prefill_plan_kernel(const int32_t *__restrict__ ids, int n, int E, int T, i
         const int lane = threadIdx.x;
         int off = 0, item = S * chunks;
         for (int base = 0; base < E; base += 64) {
-            const int cnt = base + lane < E ? s_count[base + lane] : 0, full = cnt / chunk;
-            int a = cnt, f = full;
+            const int cnt = base + lane < E ? s_count[base + lane] : 0, full = (cnt + (by_size ? 0 : chunk - 1)) / chunk;
+            int incl = cnt | full << 18;                 // (assignments: at most 2^16, full items: at most 2^11)
 #pragma unroll
             for (int d = 1; d < 64; d <<= 1) {
-                const int av = __shfl_up(a, d, 64), fv = __shfl_up(f, d, 64);
-                if (lane >= d) { a += av; f += fv; }
+                const int v = __shfl_up(incl, d, 64);
+                if (lane >= d) incl += v;
             }
-            if (base + lane < E) { s_off[base + lane] = off + a - cnt; s_full0[base + lane] = item + f - full; }
-            off += __shfl(a, 63);
-            item += __shfl(f, 63);
+            if (base + lane < E) { s_off[base + lane] = off + (incl & 0x3ffff) - cnt; s_full0[base + lane] = item + (incl >> 18) - full; }
+            const int all = __builtin_amdgcn_readlane(incl, 63);
+            off += all & 0x3ffff;
+            item += all >> 18;
         }
-        if (lane == 0) n_items[1] = item;
-        for (int g = 1; g < kSegments; ++g) {
+        if (lane < kSegments) n_items[1 + lane] = lane == 0 ? item : 0;
+        for (int g = 1; by_size && g < kSegments; ++g) {
             const int first = item;
             for (int base = 0; base < E; base += 64) {
-                const int cnt = base + lane < E ? s_count[base + lane] : 0;
-                const bool in = (cnt % chunk + 15) / 16 == kSegments - g;
+                const int left = (base + lane < E ? s_count[base + lane] : 0) % chunk;
+                const bool in = left > 0 && segment_of(left) == g;
                 const unsigned long long b = __ballot(in);
                 if (in) s_rest[base + lane] = item + __popcll(b & ((1ull << lane) - 1ull));
                 item += __popcll(b);
@@ -747,7 +756,7 @@ void prefill_plan_kernel(const int32_t *__restrict__ ids, int n, int E, int T, i
         if (lane == 0) n_items[0] = item;
     }
     __syncthreads();
-    auto item_of = [&](int e, int j) { return j < s_count[e] / chunk ? s_full0[e] + j : s_rest[e]; };
+    auto item_of = [&](int e, int j) { return !by_size || j < s_count[e] / chunk ? s_full0[e] + j : s_rest[e]; };
     for (int i = threadIdx.x; i < n; i += blockDim.x) {
         const int e = ids[i];
         const int idx = atomicAdd(&s_fill[e], 1);
