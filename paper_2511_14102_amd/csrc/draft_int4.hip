@@ -20,7 +20,7 @@
 // multiplied.  With several tokens a call has many items (every distinct expert of the call,
 // I / 32 slices each) and this wins clearly over one workgroup per item.
 //
-// Bound: the weight stream at one workgroup per compute unit (phi shape, 4 tokens: 202 MB in 52.7 us, of which
+// Bound: the weight stream at one workgroup per compute unit (phi shape, 4 tokens: 202 MB in 46.4 us, of which
 // the start takes about 5 us), and with few tokens per expert also the vector work per tile.  What the stream
 // needs is that its loads stay in flight: a window slot is unpacked and refilled at once, addresses are
 // buffer offsets without clamps, and nothing under a branch counts on the vector memory counter (an empty slot's
@@ -33,7 +33,7 @@
 //      slot {logit, tag = 1} of every token as one 16-byte store (in kReplicas copies);
 //   2. every workgroup polls the slots with single 16-byte agent-scope loads until all are
 //      tagged, then selects the top-k itself (identical in all workgroups) and draws a ticket;
-//   3. y contributions are agent-scope atomics, which land after the clearing stores because
+//   3. y contributions (of an item, or of a workgroup's items of one expert) are agent-scope atomics, which land after the clearing stores because
 //      the clearing completed before the slots were published;
 //   4. the workgroup holding the last ticket (everybody has finished polling by then) clears
 //      the tags and the ticket counters at its end, so the workspace is back in its idle state
@@ -51,9 +51,11 @@ namespace {
 // MT: token capacity of the launch (2, 4 or 8); UPG: 32-code units per
 // group (g / 32); SYM: symmetric format (scale blobs, z = 8); kWin:
 // tiles a wave keeps in flight.
-template <int MT, int UPG, bool SYM, int kWin>
-__global__ __launch_bounds__(kThreads, kWaves / 4)
-void draft_stream_kernel(const uint16_t *__restrict__ xin, const FusedArgs a)
+// SUMS: y is summed in LDS over a workgroup's items of one expert, that many token slots of it
+constexpr int sum_slots(int MT) { return MT == 4 ? 4 : 2; }
+
+template <int MT, int UPG, bool SYM, int kWin, bool SUMS>
+__device__ __forceinline__ void draft_stream(const uint16_t *__restrict__ xin, const FusedArgs &a)
 {
     __shared__ double s_part[kWaves];
     __shared__ int32_t s_ids[MOE_MAX_ASSIGN];
@@ -185,6 +187,8 @@ void draft_stream_kernel(const uint16_t *__restrict__ xin, const FusedArgs a)
     const int eb_gu = (gl_max + 3) / 4 * 1024, eb_dn = (dl_max + 3) / 4 * 1024;
     const size_t ent_off = (logit_off + (size_t)MT * E * 12 + 15) & ~(size_t)15;
     unsigned char *s_ent = s_dyn + ent_off + (size_t)wave * (eb_gu + eb_dn);                  // [gate/up | down]
+    // Sums of y over this workgroup's items of one expert: kAcc token slots of H outputs, each wave's own columns
+    float *s_y = reinterpret_cast<float *>(s_dyn + ent_off + (size_t)kWaves * (eb_gu + eb_dn));
     const uint32_t s_ent_addr = __builtin_amdgcn_readfirstlane((uint32_t)(uintptr_t)s_ent);   // LDS byte address
     auto request_blocks = [&](const char *src, int blocks, uint32_t dst) {
         for (int op = 0; op * 4 < blocks; ++op) {
@@ -298,6 +302,12 @@ void draft_stream_kernel(const uint16_t *__restrict__ xin, const FusedArgs a)
         }
         if (wave == kWaves - 1) item_rows(cur.expert, 0);
         softmax();
+        constexpr int kAcc = sum_slots(MT);
+        if constexpr (SUMS) {
+#pragma unroll
+            for (int sl = 0; sl < kAcc; ++sl)
+                for (int rt = r0; rt < r1; ++rt) s_y[sl * H + rt * 64 + lane] = 0.f;
+        }
         __syncthreads();
 
         for (int it = it_begin; it < it_end; ++it) {
@@ -438,8 +448,8 @@ void draft_stream_kernel(const uint16_t *__restrict__ xin, const FusedArgs a)
                     for (int i = 0; i < 2; ++i) {
                         const int t = slot0 + i, slot = t < cnt ? t : 0;
                         const int arow = s_row_a[par][slot];
-                        o.hsum[i] = s_hsum[par][slot];
-                        o.w[i] = s_w[arow];
+                        o.hsum[i] = t < cnt ? s_hsum[par][slot] : 0.f;
+                        o.w[i] = t < cnt ? s_w[arow] : 0.f;
                         o.off[i] = t < cnt ? (uint32_t)((arow / k) * H + block * 16 + r) * 4u : kPastY;
                     }
                     return o;
@@ -459,6 +469,17 @@ void draft_stream_kernel(const uint16_t *__restrict__ xin, const FusedArgs a)
                         __builtin_amdgcn_raw_ptr_buffer_atomic_fadd_f32(sc * ((d[2 * j] + d[2 * j + 1]) - zp * o.hsum[j]) * o.w[j],
                                                                         y_run, (int)(o.off[j] + toff), 0, 0);
                 };
+                // slots sl, sl + 1 (block c of the row tile: lane = output): onto `old` in LDS, or added to y at once.  (The
+                // sums are each wave's own, so they are read and written: an atomic addition in LDS takes 160 clocks.)
+                auto add_slots = [&](int sl, const Out &o, f32x4 d, uint32_t ev, uint32_t toff, int rt, const float *old) {
+                    if constexpr (!SUMS) add(o, d, ev, toff);
+                    else if (rt < r1) {
+                        const float sc = scale_of(ev), zp = zero_of(ev);
+#pragma unroll
+                        for (int j = 0; j < 2; ++j)
+                            s_y[(sl + j) * H + rt * 64 + lane] = old[j] + sc * ((d[2 * j] + d[2 * j + 1]) - zp * o.hsum[j]) * o.w[j];
+                    }
+                };
                 for (int j0 = 0; j0 < ndw; j0 += kWin) {
                     const run_t wr = window_run(cur, nxt, !last, ntp + j0 + kWin);
 #pragma unroll
@@ -473,9 +494,15 @@ void draft_stream_kernel(const uint16_t *__restrict__ xin, const FusedArgs a)
                         const uint32_t toff = rt < r1 ? (uint32_t)rt * 256u : kPastY / 2;    // (padding: dropped as well)
                         const f32x4 zero = {0.f, 0.f, 0.f, 0.f};
                         const uint32_t ev = entry(1, (rt_in - r0) / kEpl, rt_in & 1, c);
-                        add(oa, mfma(ha[3], b[3], mfma(ha[2], b[2], mfma(ha[1], b[1], mfma(ha[0], b[0], zero)))), ev, toff);
-                        if (MT > 2 && cnt > 2)
-                            add(ob, mfma(hb[3], b[3], mfma(hb[2], b[2], mfma(hb[1], b[1], mfma(hb[0], b[0], zero)))), ev, toff);
+                        float old[4] = {0.f, 0.f, 0.f, 0.f};
+                        if constexpr (SUMS) { old[0] = s_y[rt_in * 64 + lane]; old[1] = s_y[H + rt_in * 64 + lane]; }
+                        add_slots(0, oa, mfma(ha[3], b[3], mfma(ha[2], b[2], mfma(ha[1], b[1], mfma(ha[0], b[0], zero)))), ev, toff, rt, old);
+                        if (MT > 2 && cnt > 2) {
+                            if constexpr (SUMS && kAcc > 2) { old[2] = s_y[2 * H + rt_in * 64 + lane]; old[3] = s_y[3 * H + rt_in * 64 + lane]; }
+                            const f32x4 d = mfma(hb[3], b[3], mfma(hb[2], b[2], mfma(hb[1], b[1], mfma(hb[0], b[0], zero))));
+                            if constexpr (!SUMS || kAcc > 2) add_slots(2, ob, d, ev, toff, rt, old + 2);
+                            else add(ob, d, ev, toff);
+                        }
                         if constexpr (MT > 4) {
                             if (cnt > 4) {
 #pragma unroll
@@ -484,6 +511,17 @@ void draft_stream_kernel(const uint16_t *__restrict__ xin, const FusedArgs a)
                                         entry(1, (rt_in - r0) / kEpl, rt_in & 1, 2 * q + (c >> 1)), toff + q * 128u);
                             }
                         }
+                    }
+                }
+            }
+            // the last item of this expert: its sums leave
+            if (SUMS && (last || nxt.expert != cur.expert)) {
+                for (int sl = 0; sl < (cnt < kAcc ? cnt : kAcc); ++sl) {
+                    const uint32_t off = (uint32_t)((s_row_a[par][sl] / k) * H + lane) * 4u;
+                    for (int rt = r0; rt < r1; ++rt) {
+                        float *p = &s_y[sl * H + rt * 64 + lane];
+                        __builtin_amdgcn_raw_ptr_buffer_atomic_fadd_f32(*p, y_run, (int)(off + (uint32_t)rt * 256u), 0, 0);
+                        *p = 0.f;
                     }
                 }
             }
@@ -510,6 +548,18 @@ void draft_stream_kernel(const uint16_t *__restrict__ xin, const FusedArgs a)
     }
     if (a.S > 0) write_shared_plan(a);
 }
+
+template <int MT, int UPG, bool SYM, int kWin>
+__global__ __launch_bounds__(kThreads, kWaves / 4)
+void draft_stream_kernel(const uint16_t *__restrict__ xin, const FusedArgs a) { draft_stream<MT, UPG, SYM, kWin, false>(xin, a); }
+
+// Many items per workgroup: y summed in LDS.  Added to y item by item, the atomics sit between the weight loads, which
+// complete in order behind them.  us per call, added at once / summed: phi shape, 4 tokens 50.8 / 46.4, 8 tokens 76.2 / 67.4,
+// mixtral, 3 tokens, symmetric 84 / 72, 1 token 43.8 / 39.6.  With one or two short items per workgroup the sums only cost
+// (24 experts, H = 3072, I = 640, 7 tokens: 44.8 / 46.0), and so they do with the window of four (qwen3 shape, 8 tokens: 38.2 / 40.1).
+template <int MT, int UPG, bool SYM>
+__global__ __launch_bounds__(kThreads, kWaves / 4)
+void draft_stream_sums_kernel(const uint16_t *__restrict__ xin, const FusedArgs a) { draft_stream<MT, UPG, SYM, 8, true>(xin, a); }
 
 __global__ __launch_bounds__(256)
 void zero_kernel(uint32_t *p, size_t n)
@@ -584,27 +634,43 @@ size_t draft_dynamic_lds(int MT, int H, int g, int E, bool sym, int entry_copies
     return lds;
 }
 
-// go(kernel, MT) with the instantiation for a call
-template <int MT, bool SYM, int KW, typename F>
-void stream_kernel_g(int g, F go)
+// and behind it the sums of y: from two items per workgroup on, in calls with the window of eight, where they fit (0: no sums)
+size_t sum_lds(const Shape &s, int MT, bool sym, int n_cu)
 {
-    if (g == 32) go(draft_stream_kernel<MT, 1, SYM, KW>, MT);
-    else if (g == 64) go(draft_stream_kernel<MT, 2, SYM, KW>, MT);
-    else go(draft_stream_kernel<MT, 4, SYM, KW>, MT);
+    const int maxu = s.E < s.T * s.k ? s.E : s.T * s.k;
+    const size_t sums = (size_t)sum_slots(MT) * s.H * 4;
+    if ((long)maxu * (s.I / 32) < 2L * n_cu || stream_window(s, sym) != 8) return 0;
+    return draft_dynamic_lds(MT, s.H, s.g, s.E, sym) + sums <= (size_t)(160 - 20) * 1024 ? sums : 0;
 }
-template <bool SYM, int KW, typename F>
-void stream_kernel_t(const Shape &s, F go)
+
+// go(kernel, bytes of dynamic LDS) with the instantiation for a call
+template <int MT, int UPG, bool SYM, typename F>
+void stream_kernel_m(const Shape &s, int n_cu, F go)
 {
-    if (s.T <= 2) stream_kernel_g<2, SYM, KW>(s.g, go);
-    else if (s.T <= 4) stream_kernel_g<4, SYM, KW>(s.g, go);
-    else stream_kernel_g<8, SYM, KW>(s.g, go);
+    const size_t lds = draft_dynamic_lds(MT, s.H, s.g, s.E, SYM), sums = sum_lds(s, MT, SYM, n_cu);
+    if (sums) go(draft_stream_sums_kernel<MT, UPG, SYM>, lds + sums);
+    else if (stream_window(s, SYM) == 8) go(draft_stream_kernel<MT, UPG, SYM, 8>, lds);
+    else go(draft_stream_kernel<MT, UPG, SYM, 4>, lds);
+}
+template <int UPG, bool SYM, typename F>
+void stream_kernel_g(const Shape &s, int n_cu, F go)
+{
+    if (s.T <= 2) stream_kernel_m<2, UPG, SYM>(s, n_cu, go);
+    else if (s.T <= 4) stream_kernel_m<4, UPG, SYM>(s, n_cu, go);
+    else stream_kernel_m<8, UPG, SYM>(s, n_cu, go);
+}
+template <bool SYM, typename F>
+void stream_kernel_t(const Shape &s, int n_cu, F go)
+{
+    if (s.g == 32) stream_kernel_g<1, SYM>(s, n_cu, go);
+    else if (s.g == 64) stream_kernel_g<2, SYM>(s, n_cu, go);
+    else stream_kernel_g<4, SYM>(s, n_cu, go);
 }
 template <typename F>
-void stream_kernel(const Shape &s, bool sym, F go)
+void stream_kernel(const Shape &s, bool sym, int n_cu, F go)
 {
-    const bool deep = stream_window(s, sym) == 8;
-    if (sym) { if (deep) stream_kernel_t<true, 8>(s, go); else stream_kernel_t<true, 4>(s, go); }
-    else { if (deep) stream_kernel_t<false, 8>(s, go); else stream_kernel_t<false, 4>(s, go); }
+    if (sym) stream_kernel_t<true>(s, n_cu, go);
+    else stream_kernel_t<false>(s, n_cu, go);
 }
 
 // One token through the persistent kernel: from two items per compute unit on, where the launch carries no shared
@@ -631,9 +697,7 @@ int draft_resident_slots(const Shape &s, const DraftFusedArgs &d, int n_cu)
         return need <= slots ? slots : 0;
     }
     int per = 0;
-    stream_kernel(s, d.symmetric != 0, [&](auto kernel, int MT) {
-        per = resident_per_cu(kernel, kThreads, draft_dynamic_lds(MT, s.H, s.g, s.E, d.symmetric != 0));
-    });
+    stream_kernel(s, d.symmetric != 0, n_cu, [&](auto kernel, size_t lds) { per = resident_per_cu(kernel, kThreads, lds); });
     return (per < kMaxPerCu ? per : kMaxPerCu) * n_cu;
 }
 
@@ -645,8 +709,8 @@ void launch_draft_fused(const Shape &s, const DraftFusedArgs &d, int n_cu, int s
     const int maxu = s.E < s.T * s.k ? s.E : s.T * s.k;
     const long items = (long)maxu * (s.I / 32);
     const dim3 grid((unsigned)(items < slots ? items : slots)), block(kThreads);
-    stream_kernel(s, d.symmetric != 0, [&](auto kernel, int MT) {
-        launch_with_lds(kernel, grid, block, draft_dynamic_lds(MT, s.H, s.g, s.E, d.symmetric != 0), st, (const uint16_t *)d.x, a);
+    stream_kernel(s, d.symmetric != 0, n_cu, [&](auto kernel, size_t lds) {
+        launch_with_lds(kernel, grid, block, lds, st, (const uint16_t *)d.x, a);
     });
 }
 
