@@ -72,16 +72,29 @@ namespace {
 constexpr int kItemTokens = 64;                   // slots of an item: four token blocks of 16
 constexpr int kTileThreads = 256, kTileWaves = 4;
 constexpr int kXcds = 8;
-// The items: shared experts' and full ones, then what is left of every expert's run: four, three, and two or one token blocks of 16.
-// n_items: their count, then each segment's.  A launch is only one and a half to three rounds of workgroups (two a compute
-// unit) where a prompt is of ordinary length, so that its end counts: largest first, it ends with the short ones.  us per
-// call, expert by expert / largest first: phi shape, 512 tokens (24 items, 50 and 16 columns) 350 / 314, dsv2lite, 333
-// tokens (76 items, 11 and 8 columns) 157 / 150; mixtral, 4096 tokens (30 and 4 rounds) the same.
+// The items, in segments: the shared experts' and full ones; then what is left of the experts' runs, by its token blocks of 16:
+// four, three, two or one.  n_items: their count, then each segment's.  A launch is only one and a half to three rounds of
+// workgroups (two a compute unit) where a prompt is of ordinary length, so that its end counts: largest first, it ends with
+// the short ones.  But the rest of a long run reads its weights a second time there, from the memory-side cache as
+// long as what lies between stays inside it; beyond kRestBytes a long run stays in one piece, in the first segment.
+// us per call, expert by expert / largest first / largest first, long runs in one piece:
+//   phi shape, 512 tokens (24 items, 50 and 16 columns; 131 MB in long runs)  343 / 317 / 329
+//   dsv2lite, 333 tokens (76 items, 11 and 8 columns; nearly no long runs)    155 / 147 / 146
+//   mixtral, 283 tokens (16 items, 112 and 16 columns; 470 MB in long runs)   409 / 433 / 412
+//   128 experts, 109 tokens (128 items of one or two blocks)                  109 / 111 / 111
 constexpr int kSegments = 4;
+constexpr long kRestBytes = 192L << 20;             // of the 256 MiB cache
 constexpr int kSmallItem = 32;                    // items of small calls, whose launches are one round: all in the first segment
-// segment of the `left` (1 .. 63) last assignments of an expert
-__device__ inline int segment_of(int left) { return left > 48 ? 1 : left > 32 ? 2 : 3; }
 constexpr float kOffset = -24.f;                  // factor of a stored group sum: takes 16 + q to q - 8
+
+// Items of an expert in the first segment, and the segment of its last item (0: it has none elsewhere)
+__device__ inline int head_items(int assignments, int chunk, bool in_pieces) {
+    return (assignments + (chunk == kSmallItem || (assignments > chunk && !in_pieces) ? chunk - 1 : 0)) / chunk;
+}
+__device__ inline int rest_segment(int assignments, int head, int chunk) {
+    const int left = assignments - head * chunk;
+    return left <= 0 ? 0 : left > 48 ? 1 : left > 32 ? 2 : 3;
+}
 
 struct TileArgs {
     const char *q, *sz;              // int4 codes / scale(-zero) blobs of the routed experts
@@ -597,7 +610,7 @@ template <int KPG, bool kPlanned>
 __global__ __launch_bounds__(256)
 void prefill_stage_kernel(const uint16_t *__restrict__ x, const int32_t *__restrict__ count, const int32_t *__restrict__ list,
                           PrefillItem *__restrict__ items, int32_t *__restrict__ n_items, int32_t *__restrict__ slot_of,
-                          char *__restrict__ xt, char *__restrict__ sums, char *__restrict__ zeros, int T, int H, int k, int E, int S, int chunk)
+                          char *__restrict__ xt, char *__restrict__ sums, char *__restrict__ zeros, int T, int H, int I, int k, int E, int S, int chunk)
 {
     const int blocks = chunk >> 4, item = blockIdx.x / blocks, tb = blockIdx.x % blocks, tid = threadIdx.x;
     const bool first = blockIdx.x == 0 && blockIdx.y == 0;
@@ -611,18 +624,18 @@ void prefill_stage_kernel(const uint16_t *__restrict__ x, const int32_t *__restr
         __shared__ __align__(16) int32_t s_count[kSegments][4];        // per segment and wave of 64 experts: items
         __shared__ PrefillItem s_item;
         const int chunks = (T + chunk - 1) / chunk, wave = tid >> 6, lane = tid & 63;
-        const bool by_size = chunk > kSmallItem;
         if (tid == 0) s_item = PrefillItem{0, 0, 0, -1};
-        // thread e: expert e's full items are [begin, begin + full), its last one is item `rest`
-        const int cnt = tid < E ? count[tid] : 0, shift = chunk > kSmallItem ? 6 : 5, full = (cnt + (by_size ? 0 : chunk - 1)) >> shift;
-        const int left = cnt - (full << shift), seg = left > 0 ? segment_of(left) : 0;
-        int incl = full;
+        // thread e: expert e's items are [begin, begin + head) and, in segment `seg`, item `rest`
+        const int cnt = tid < E ? count[tid] : 0;
+        const bool in_pieces = (long)__syncthreads_count(cnt > chunk) * H * I <= kRestBytes;
+        const int head = head_items(cnt, chunk, in_pieces), seg = rest_segment(cnt, head, chunk);
+        int incl = head;
 #pragma unroll
         for (int d = 1; d < 64; d <<= 1) {
             const int v = __shfl_up(incl, d, 64);
             if (lane >= d) incl += v;
         }
-        int rest = 0, counts[kSegments];
+        int begin = S * chunks + incl - head, rest = 0, counts[kSegments];
 #pragma unroll
         for (int g = 1; g < kSegments; ++g) {
             const unsigned long long in = __ballot(seg == g);
@@ -635,7 +648,7 @@ void prefill_stage_kernel(const uint16_t *__restrict__ x, const int32_t *__restr
             for (int g = 0; g < kSegments; ++g) s_count[g][wave] = counts[g];
         }
         __syncthreads();
-        int begin = S * chunks + incl - full, total = S * chunks, n_seg[kSegments];
+        int total = S * chunks, n_seg[kSegments];
 #pragma unroll
         for (int g = 0; g < kSegments; ++g) {
             const int4 n = *reinterpret_cast<const int4 *>(s_count[g]);
@@ -652,13 +665,13 @@ void prefill_stage_kernel(const uint16_t *__restrict__ x, const int32_t *__restr
             const int j = i % chunks;
             return PrefillItem{E + i / chunks, j * chunk, T - j * chunk < chunk ? T - j * chunk : chunk, j};
         };
-        if (item >= begin && item < begin + full) s_item = chunk_of(item - begin, item);
-        if (seg != 0 && item == rest) s_item = chunk_of(full, item);
+        if (item >= begin && item < begin + head) s_item = chunk_of(item - begin, item);
+        if (seg != 0 && item == rest) s_item = chunk_of(head, item);
         if (tid == 0 && item < S * chunks) s_item = shared_item(item);
         if (first) {
             for (int i = tid; i < S * chunks; i += 256) items[i] = shared_item(i);
-            for (int j = 0; j < full; ++j) items[begin + j] = chunk_of(j, begin + j);
-            if (seg != 0) items[rest] = chunk_of(full, rest);
+            for (int j = 0; j < head; ++j) items[begin + j] = chunk_of(j, begin + j);
+            if (seg != 0) items[rest] = chunk_of(head, rest);
             if (tid == 0) {
                 n_items[0] = total;
 #pragma unroll
@@ -704,77 +717,6 @@ void prefill_stage_kernel(const uint16_t *__restrict__ x, const int32_t *__restr
     }
 }
 
-// Sorts the n = T k assignments by expert (the order inside an expert is arbitrary: no result
-// depends on it, a row's sums do not depend on the other rows of its item), cuts every expert's
-// run into items of at most `chunk` and records the slot (item x 64 + position) of every assignment.
-// The first S ceil(T / chunk) items are the shared experts', over the tokens in order.  One workgroup.
-__global__ __launch_bounds__(1024)
-void prefill_plan_kernel(const int32_t *__restrict__ ids, int n, int E, int T, int S, int chunk,
-                         int32_t *__restrict__ list, int32_t *__restrict__ slot_of,
-                         PrefillItem *__restrict__ items, int32_t *__restrict__ n_items)
-{
-    __shared__ int32_t s_count[MOE_MAX_EXPERTS], s_off[MOE_MAX_EXPERTS], s_fill[MOE_MAX_EXPERTS],
-        s_full0[MOE_MAX_EXPERTS], s_rest[MOE_MAX_EXPERTS];           // first full item, item of the rest
-    const bool by_size = chunk > kSmallItem;
-    const int chunks = (T + chunk - 1) / chunk;
-    for (int i = threadIdx.x; i < S * chunks; i += blockDim.x) {
-        const int j = i % chunks;
-        items[i] = PrefillItem{E + i / chunks, j * chunk, T - j * chunk < chunk ? T - j * chunk : chunk, j};
-    }
-    for (int e = threadIdx.x; e < E; e += blockDim.x) { s_count[e] = 0; s_fill[e] = 0; }
-    __syncthreads();
-    for (int i = threadIdx.x; i < n; i += blockDim.x) atomicAdd(&s_count[ids[i]], 1);
-    __syncthreads();
-    if (threadIdx.x < 64) {
-        const int lane = threadIdx.x;
-        int off = 0, item = S * chunks;
-        for (int base = 0; base < E; base += 64) {
-            const int cnt = base + lane < E ? s_count[base + lane] : 0, full = (cnt + (by_size ? 0 : chunk - 1)) / chunk;
-            int incl = cnt | full << 18;                 // (assignments: at most 2^16, full items: at most 2^11)
-#pragma unroll
-            for (int d = 1; d < 64; d <<= 1) {
-                const int v = __shfl_up(incl, d, 64);
-                if (lane >= d) incl += v;
-            }
-            if (base + lane < E) { s_off[base + lane] = off + (incl & 0x3ffff) - cnt; s_full0[base + lane] = item + (incl >> 18) - full; }
-            const int all = __builtin_amdgcn_readlane(incl, 63);
-            off += all & 0x3ffff;
-            item += all >> 18;
-        }
-        if (lane < kSegments) n_items[1 + lane] = lane == 0 ? item : 0;
-        for (int g = 1; by_size && g < kSegments; ++g) {
-            const int first = item;
-            for (int base = 0; base < E; base += 64) {
-                const int left = (base + lane < E ? s_count[base + lane] : 0) % chunk;
-                const bool in = left > 0 && segment_of(left) == g;
-                const unsigned long long b = __ballot(in);
-                if (in) s_rest[base + lane] = item + __popcll(b & ((1ull << lane) - 1ull));
-                item += __popcll(b);
-            }
-            if (lane == 0) n_items[1 + g] = item - first;
-        }
-        if (lane == 0) n_items[0] = item;
-    }
-    __syncthreads();
-    auto item_of = [&](int e, int j) { return !by_size || j < s_count[e] / chunk ? s_full0[e] + j : s_rest[e]; };
-    for (int i = threadIdx.x; i < n; i += blockDim.x) {
-        const int e = ids[i];
-        const int idx = atomicAdd(&s_fill[e], 1);
-        list[s_off[e] + idx] = i;
-        slot_of[i] = item_of(e, idx / chunk) * kItemTokens + idx % chunk;
-    }
-    for (int e = threadIdx.x; e < E; e += blockDim.x) {
-        const int cnt = s_count[e];
-        for (int j = 0; j * chunk < cnt; ++j) {
-            PrefillItem it;
-            it.expert = e; it.first = s_off[e] + j * chunk;
-            it.cnt = cnt - j * chunk < chunk ? cnt - j * chunk : chunk;
-            it.src = item_of(e, j);
-            items[it.src] = it;
-        }
-    }
-}
-
 // y[t][:] = sum_j w[t k + j] * obuf[slot_of[t k + j]][:], j ascending, then the shared experts' rows
 __global__ __launch_bounds__(256)
 void prefill_combine_kernel(const float *__restrict__ obuf, const int32_t *__restrict__ slot_of,
@@ -794,6 +736,80 @@ void prefill_combine_kernel(const float *__restrict__ obuf, const int32_t *__res
     for (int sh = 0; sh < S; ++sh)
         acc += *reinterpret_cast<const f32x4 *>(obuf + ((size_t)(sh * chunks + t / chunk) * kItemTokens + t % chunk) * H + col);
     *reinterpret_cast<f32x4 *>(y + (size_t)t * H + col) = acc;
+}
+
+// Sorts the n = T k assignments by expert (the order inside an expert is arbitrary: no result
+// depends on it, a row's sums do not depend on the other rows of its item), cuts every expert's
+// run into items of at most `chunk` and records the slot (item x 64 + position) of every assignment.
+// The first S ceil(T / chunk) items are the shared experts', over the tokens in order.  One workgroup.
+__global__ __launch_bounds__(1024)
+void prefill_plan_kernel(const int32_t *__restrict__ ids, int n, int E, int T, int S, int chunk, long weights,
+                         int32_t *__restrict__ list, int32_t *__restrict__ slot_of,
+                         PrefillItem *__restrict__ items, int32_t *__restrict__ n_items)
+{
+    __shared__ int32_t s_count[MOE_MAX_EXPERTS], s_off[MOE_MAX_EXPERTS], s_fill[MOE_MAX_EXPERTS],
+        s_item0[MOE_MAX_EXPERTS], s_rest[MOE_MAX_EXPERTS];
+    const int chunks = (T + chunk - 1) / chunk;
+    for (int i = threadIdx.x; i < S * chunks; i += blockDim.x) {
+        const int j = i % chunks;
+        items[i] = PrefillItem{E + i / chunks, j * chunk, T - j * chunk < chunk ? T - j * chunk : chunk, j};
+    }
+    for (int e = threadIdx.x; e < E; e += blockDim.x) { s_count[e] = 0; s_fill[e] = 0; }
+    __syncthreads();
+    for (int i = threadIdx.x; i < n; i += blockDim.x) atomicAdd(&s_count[ids[i]], 1);
+    __syncthreads();
+    int n_long = 0;
+    for (int base = 0; chunk > kSmallItem && base < E; base += 64) {
+        const int e = base + (threadIdx.x & 63);
+        n_long += __popcll(__ballot(e < E && s_count[e < E ? e : 0] > chunk));
+    }
+    const bool in_pieces = n_long * weights <= kRestBytes;
+    if (threadIdx.x < 64) {
+        const int lane = threadIdx.x;
+        int off = 0, item = S * chunks;
+        for (int g = 0; g < (chunk > kSmallItem ? kSegments : 1); ++g) {
+            const int first = g == 0 ? 0 : item;
+            for (int base = 0; base < E; base += 64) {
+                const int cnt = base + lane < E ? s_count[base + lane] : 0;
+                const int head = head_items(cnt, chunk, in_pieces), mine = g == 0 ? head : rest_segment(cnt, head, chunk) == g ? 1 : 0;
+                // (assignments of all experts, in the first round: at most 2^16; items: at most 2^11 + 2^8)
+                int incl = (g == 0 ? cnt : 0) | mine << 18;
+#pragma unroll
+                for (int d = 1; d < 64; d <<= 1) {
+                    const int v = __shfl_up(incl, d, 64);
+                    if (lane >= d) incl += v;
+                }
+                if (g == 0 && base + lane < E) s_off[base + lane] = off + (incl & 0x3ffff) - cnt;
+                if (mine > 0) (g == 0 ? s_item0 : s_rest)[base + lane] = item + (incl >> 18) - mine;
+                const int all = __builtin_amdgcn_readlane(incl, 63);
+                off += all & 0x3ffff;
+                item += all >> 18;
+            }
+            if (lane == 0) n_items[1 + g] = item - first;
+        }
+        if (lane == 0) {
+            n_items[0] = item;
+            for (int g = 1; chunk <= kSmallItem && g < kSegments; ++g) n_items[1 + g] = 0;
+        }
+    }
+    __syncthreads();
+    auto item_of = [&](int e, int j) { return j < head_items(s_count[e], chunk, in_pieces) ? s_item0[e] + j : s_rest[e]; };
+    for (int i = threadIdx.x; i < n; i += blockDim.x) {
+        const int e = ids[i];
+        const int idx = atomicAdd(&s_fill[e], 1);
+        list[s_off[e] + idx] = i;
+        slot_of[i] = item_of(e, idx / chunk) * kItemTokens + idx % chunk;
+    }
+    for (int e = threadIdx.x; e < E; e += blockDim.x) {
+        const int cnt = s_count[e];
+        for (int j = 0; j * chunk < cnt; ++j) {
+            PrefillItem it;
+            it.expert = e; it.first = s_off[e] + j * chunk;
+            it.cnt = cnt - j * chunk < chunk ? cnt - j * chunk : chunk;
+            it.src = item_of(e, j);
+            items[it.src] = it;
+        }
+    }
 }
 
 template <bool DOWN, bool SYM>
@@ -863,7 +879,7 @@ bool prefill_small(const Shape &s) { return (long)s.T * ((long)s.E * s.H + 1024L
 
 void launch_prefill_plan(const Shape &s, const int32_t *ids, const PrefillCall &p, hipStream_t st)
 {
-    launch(prefill_plan_kernel, dim3(1), dim3(1024), 0, st, ids, s.T * s.k, s.E, s.T, s.S, prefill_chunk(s), (int32_t *)p.list, p.slot_of, p.items, p.n_items);
+    launch(prefill_plan_kernel, dim3(1), dim3(1024), 0, st, ids, s.T * s.k, s.E, s.T, s.S, prefill_chunk(s), (long)s.H * s.I, (int32_t *)p.list, p.slot_of, p.items, p.n_items);
 }
 
 void launch_prefill_stage(const Shape &s, const PrefillCall &p, int max_items, hipStream_t st)
@@ -872,7 +888,7 @@ void launch_prefill_stage(const Shape &s, const PrefillCall &p, int max_items, h
     const dim3 grid(max_items * (chunk / 16), (s.H / 32 + 15) / 16), block(256);
     auto go = [&](auto kernel) {
         launch(kernel, grid, block, 0, st, (const uint16_t *)p.x, p.count, p.list, p.items, p.n_items, p.slot_of, (char *)p.xt,
-               (char *)p.x_sums, (char *)p.zeros, s.T, s.H, s.k, s.E, s.S, chunk);
+               (char *)p.x_sums, (char *)p.zeros, s.T, s.H, s.I, s.k, s.E, s.S, chunk);
     };
     auto of_group = [&](auto planned) {
         constexpr bool kPlanned = decltype(planned)::value;
