@@ -514,13 +514,14 @@ __device__ __forceinline__ void draft_stream(const uint16_t *__restrict__ xin, c
                     }
                 }
             }
-            // the last item of this expert: its sums leave
+            // the last item of this expert: its sums leave, and all slots start again (an empty slot's products are zeros, but
+            // not times an infinite scale)
             if (SUMS && (last || nxt.expert != cur.expert)) {
-                for (int sl = 0; sl < (cnt < kAcc ? cnt : kAcc); ++sl) {
-                    const uint32_t off = (uint32_t)((s_row_a[par][sl] / k) * H + lane) * 4u;
+                for (int sl = 0; sl < kAcc; ++sl) {
+                    const uint32_t off = (uint32_t)((s_row_a[par][sl < cnt ? sl : 0] / k) * H + lane) * 4u;
                     for (int rt = r0; rt < r1; ++rt) {
                         float *p = &s_y[sl * H + rt * 64 + lane];
-                        __builtin_amdgcn_raw_ptr_buffer_atomic_fadd_f32(*p, y_run, (int)(off + (uint32_t)rt * 256u), 0, 0);
+                        if (sl < cnt) __builtin_amdgcn_raw_ptr_buffer_atomic_fadd_f32(*p, y_run, (int)(off + (uint32_t)rt * 256u), 0, 0);
                         *p = 0.f;
                     }
                 }
