@@ -84,12 +84,12 @@ constexpr int kXcds = 8;
 //   128 experts, 109 tokens (128 items of one or two blocks)                  109 / 111 / 111
 constexpr int kSegments = 4;
 constexpr long kRestBytes = 192L << 20;             // of the 256 MiB cache
-constexpr int kSmallItem = 32;                    // items of small calls, whose launches are one round: all in the first segment
+// Where a launch is one round (items of 32 tokens) or many (prefill_by_size), all items are in the first segment, expert by expert.
 constexpr float kOffset = -24.f;                  // factor of a stored group sum: takes 16 + q to q - 8
 
 // Items of an expert in the first segment, and the segment of its last item (0: it has none elsewhere)
-__device__ inline int head_items(int assignments, int chunk, bool in_pieces) {
-    return (assignments + (chunk == kSmallItem || (assignments > chunk && !in_pieces) ? chunk - 1 : 0)) / chunk;
+__device__ inline int head_items(int assignments, int chunk, bool by_size, bool in_pieces) {
+    return (assignments + (!by_size || (assignments > chunk && !in_pieces) ? chunk - 1 : 0)) / chunk;
 }
 __device__ inline int rest_segment(int assignments, int head, int chunk) {
     const int left = assignments - head * chunk;
@@ -610,7 +610,7 @@ template <int KPG, bool kPlanned>
 __global__ __launch_bounds__(256)
 void prefill_stage_kernel(const uint16_t *__restrict__ x, const int32_t *__restrict__ count, const int32_t *__restrict__ list,
                           PrefillItem *__restrict__ items, int32_t *__restrict__ n_items, int32_t *__restrict__ slot_of,
-                          char *__restrict__ xt, char *__restrict__ sums, char *__restrict__ zeros, int T, int H, int I, int k, int E, int S, int chunk)
+                          char *__restrict__ xt, char *__restrict__ sums, char *__restrict__ zeros, int T, int H, int I, int k, int E, int S, int chunk, bool by_size)
 {
     const int blocks = chunk >> 4, item = blockIdx.x / blocks, tb = blockIdx.x % blocks, tid = threadIdx.x;
     const bool first = blockIdx.x == 0 && blockIdx.y == 0;
@@ -628,7 +628,7 @@ void prefill_stage_kernel(const uint16_t *__restrict__ x, const int32_t *__restr
         // thread e: expert e's items are [begin, begin + head) and, in segment `seg`, item `rest`
         const int cnt = tid < E ? count[tid] : 0;
         const bool in_pieces = (long)__syncthreads_count(cnt > chunk) * H * I <= kRestBytes;
-        const int head = head_items(cnt, chunk, in_pieces), seg = rest_segment(cnt, head, chunk);
+        const int head = head_items(cnt, chunk, by_size, in_pieces), seg = rest_segment(cnt, head, chunk);
         int incl = head;
 #pragma unroll
         for (int d = 1; d < 64; d <<= 1) {
@@ -743,7 +743,7 @@ void prefill_combine_kernel(const float *__restrict__ obuf, const int32_t *__res
 // run into items of at most `chunk` and records the slot (item x 64 + position) of every assignment.
 // The first S ceil(T / chunk) items are the shared experts', over the tokens in order.  One workgroup.
 __global__ __launch_bounds__(1024)
-void prefill_plan_kernel(const int32_t *__restrict__ ids, int n, int E, int T, int S, int chunk, long weights,
+void prefill_plan_kernel(const int32_t *__restrict__ ids, int n, int E, int T, int S, int chunk, bool by_size, long weights,
                          int32_t *__restrict__ list, int32_t *__restrict__ slot_of,
                          PrefillItem *__restrict__ items, int32_t *__restrict__ n_items)
 {
@@ -759,7 +759,7 @@ void prefill_plan_kernel(const int32_t *__restrict__ ids, int n, int E, int T, i
     for (int i = threadIdx.x; i < n; i += blockDim.x) atomicAdd(&s_count[ids[i]], 1);
     __syncthreads();
     int n_long = 0;
-    for (int base = 0; chunk > kSmallItem && base < E; base += 64) {
+    for (int base = 0; by_size && base < E; base += 64) {
         const int e = base + (threadIdx.x & 63);
         n_long += __popcll(__ballot(e < E && s_count[e < E ? e : 0] > chunk));
     }
@@ -767,11 +767,11 @@ void prefill_plan_kernel(const int32_t *__restrict__ ids, int n, int E, int T, i
     if (threadIdx.x < 64) {
         const int lane = threadIdx.x;
         int off = 0, item = S * chunks;
-        for (int g = 0; g < (chunk > kSmallItem ? kSegments : 1); ++g) {
+        for (int g = 0; g < (by_size ? kSegments : 1); ++g) {
             const int first = g == 0 ? 0 : item;
             for (int base = 0; base < E; base += 64) {
                 const int cnt = base + lane < E ? s_count[base + lane] : 0;
-                const int head = head_items(cnt, chunk, in_pieces), mine = g == 0 ? head : rest_segment(cnt, head, chunk) == g ? 1 : 0;
+                const int head = head_items(cnt, chunk, by_size, in_pieces), mine = g == 0 ? head : rest_segment(cnt, head, chunk) == g ? 1 : 0;
                 // (assignments of all experts, in the first round: at most 2^16; items: at most 2^11 + 2^8)
                 int incl = (g == 0 ? cnt : 0) | mine << 18;
 #pragma unroll
@@ -789,11 +789,11 @@ void prefill_plan_kernel(const int32_t *__restrict__ ids, int n, int E, int T, i
         }
         if (lane == 0) {
             n_items[0] = item;
-            for (int g = 1; chunk <= kSmallItem && g < kSegments; ++g) n_items[1 + g] = 0;
+            for (int g = 1; !by_size && g < kSegments; ++g) n_items[1 + g] = 0;
         }
     }
     __syncthreads();
-    auto item_of = [&](int e, int j) { return j < head_items(s_count[e], chunk, in_pieces) ? s_item0[e] + j : s_rest[e]; };
+    auto item_of = [&](int e, int j) { return j < head_items(s_count[e], chunk, by_size, in_pieces) ? s_item0[e] + j : s_rest[e]; };
     for (int i = threadIdx.x; i < n; i += blockDim.x) {
         const int e = ids[i];
         const int idx = atomicAdd(&s_fill[e], 1);
@@ -852,6 +852,13 @@ static int items_of(const Shape &s, int chunk)
 // (H = 1024, I = 2048, 300 tokens, 416: 65.8 / 55.9), the more evenly the 64s fill the units the less.
 constexpr int kSmallGrid = 256;
 int prefill_chunk(const Shape &s) { return (long)prefill_columns(s) * items_of(s, 32) <= kSmallGrid ? 32 : 64; }
+// Largest items first, up to three and a half rounds of 512 workgroups (upper bound): the end of a longer launch is a smaller part
+// of it, and the order costs neighbours in the cache.  us per pass, without segments / largest first (workgroups), and in
+// brackets the experts' order with the segments' arithmetic, which costs what is left: phi shape, 512 tokens (1600) 712 / 648;
+// dsv2lite, 333 tokens (1177) 628 / 603; H = 1408, E = 41, I = 4864, k = 3, 298 tokens (2052) 365 / 369 (1.2 % as well);
+// H = 512, E = 112, I = 1856, k = 8, 4 shared, 201 tokens (2295) 425 / 434 (0.7 %); H = 448, E = 81, I = 9024, k = 7,
+// 618 tokens (10508) 368 / 377 (0.7 %).
+static bool prefill_by_size(const Shape &s) { return prefill_chunk(s) == kItemTokens && (long)prefill_columns(s) * items_of(s, kItemTokens) < 7 * 256; }
 int prefill_max_items(const Shape &s) { return items_of(s, prefill_chunk(s)); }
 size_t prefill_item_room(const Shape &s)
 {
@@ -879,7 +886,7 @@ bool prefill_small(const Shape &s) { return (long)s.T * ((long)s.E * s.H + 1024L
 
 void launch_prefill_plan(const Shape &s, const int32_t *ids, const PrefillCall &p, hipStream_t st)
 {
-    launch(prefill_plan_kernel, dim3(1), dim3(1024), 0, st, ids, s.T * s.k, s.E, s.T, s.S, prefill_chunk(s), (long)s.H * s.I, (int32_t *)p.list, p.slot_of, p.items, p.n_items);
+    launch(prefill_plan_kernel, dim3(1), dim3(1024), 0, st, ids, s.T * s.k, s.E, s.T, s.S, prefill_chunk(s), prefill_by_size(s), (long)s.H * s.I, (int32_t *)p.list, p.slot_of, p.items, p.n_items);
 }
 
 void launch_prefill_stage(const Shape &s, const PrefillCall &p, int max_items, hipStream_t st)
@@ -888,7 +895,7 @@ void launch_prefill_stage(const Shape &s, const PrefillCall &p, int max_items, h
     const dim3 grid(max_items * (chunk / 16), (s.H / 32 + 15) / 16), block(256);
     auto go = [&](auto kernel) {
         launch(kernel, grid, block, 0, st, (const uint16_t *)p.x, p.count, p.list, p.items, p.n_items, p.slot_of, (char *)p.xt,
-               (char *)p.x_sums, (char *)p.zeros, s.T, s.H, s.I, s.k, s.E, s.S, chunk);
+               (char *)p.x_sums, (char *)p.zeros, s.T, s.H, s.I, s.k, s.E, s.S, chunk, prefill_by_size(s));
     };
     auto of_group = [&](auto planned) {
         constexpr bool kPlanned = decltype(planned)::value;
