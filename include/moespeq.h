@@ -161,9 +161,11 @@ int moe_workspace_bytes(const moe_layer_desc *desc, int max_tokens, size_t *byte
  * moe_verify_layer_bf16 call on it, and again after a draft call that timed out (below).  The first
  * 512 bytes and the slot area behind them hold what the kernels exchange between their workgroups:
  * the draft kernels' ticket counters and tagged router-result slots (the verify call counts arrivals in
- * the same tags), the verify call's arrival counter, and the draft status word.  Both calls expect the counters and tags zero on entry and
- * leave them zero on exit (also when the call is replayed from a HIP graph); nothing else is
- * carried from call to call. */
+ * the same tags), the verify call's arrival counter, and the draft status word.  Draft calls expect the
+ * counters and tags zero on entry; verify calls only their counter in the first 512 bytes.  Both leave
+ * counters and tags zero on exit (also when the call is replayed from a HIP graph); nothing else is
+ * carried from call to call.  (The size of the slot area depends on n_experts alone: layers of different
+ * expert counts can share a workspace for verify calls; a draft call there needs it idle again.) */
 int moe_workspace_init(moe_ctx *ctx, void *workspace, size_t workspace_bytes, void *stream);
 
 /* Size of the leading part of a workspace that holds the "idle state": 512 bytes of counters and
@@ -344,8 +346,9 @@ int moe_expert_union(moe_ctx *ctx, const int32_t *ids, int n_ids, int n_experts,
  *
  * 1 <= T <= MOE_MAX_TOKENS.  y_bf16 [T,H]; ids_out [T,k] int32 or NULL; missing [E] int32 and
  * n_missing [1] int32 device memory, required.  `workspace` must have been put into its idle
- * state once (moe_workspace_init): the launch that routes counts its arriving workgroups there, the
- * launch of the down products counts its own in the exchange slots' tags, and both leave zeros again.
+ * state once (moe_workspace_init): the launch that routes counts its arriving workgroups there and
+ * leaves zeros again, and so does the launch of the down products in the exchange slots' tags, which
+ * the launch before it clears.
  */
 int moe_verify_layer_bf16(moe_ctx *ctx, const moe_layer_desc *desc,
                           const void *x_bf16, const void *w_router_bf16,

@@ -585,11 +585,10 @@ int moe_verify_layer_bf16(moe_ctx *ctx, const moe_layer_desc *desc,
     // router and plan in one launch; its arrival counter sits behind the draft kernel's tickets
     { ProfScope p(ctx, MOE_KERNEL_ROUTE, st);
       launch_verify_route(s, x, wr, bias, a, logits, (uint32_t *)(ws + L.tickets + kWsArrivalsOffset), st); }
-    { ProfScope p(ctx, MOE_KERNEL_BF16_GATEUP, st);
-      launch_verify_gateup(s, plan, x, logits, plan->ids, plan->row_w, ws + L.hb, st); }
-    { ProfScope p(ctx, MOE_KERNEL_BF16_DOWN, st);
-      launch_verify_down(s, plan, ws + L.hb, (float *)(ws + L.obuf), (unsigned long long *)(ws + L.slots), kDraftSlotReplicas * L.slot_replica_bytes,
-                         (flags & MOE_VERIFY_ACCUMULATE) ? 1 : 0, y, st); }
+    const VerifyCall v = {plan, x, logits, ws + L.hb, (float *)(ws + L.obuf), (unsigned long long *)(ws + L.slots),
+                          kDraftSlotReplicas * L.slot_replica_bytes, (flags & MOE_VERIFY_ACCUMULATE) ? 1 : 0, y};
+    { ProfScope p(ctx, MOE_KERNEL_BF16_GATEUP, st); launch_verify_gateup(s, v, st); }
+    { ProfScope p(ctx, MOE_KERNEL_BF16_DOWN, st); launch_verify_down(s, v, st); }
     int rc = hip_status(ctx, hipGetLastError());
     if (rc != MOE_OK) return rc;
     if (flags & MOE_VERIFY_STRICT) {

@@ -107,17 +107,42 @@ __device__ inline void routing_weights(const WeightArgs &a)
     if (tid < a.S * a.T) a.row_w[a.T * a.k + tid] = 1.f;
 }
 
+// The verify call's down launch counts its arrivals (two row tiles of every live expert) per 32 output columns in the tags of
+// the draft kernels' exchange slots (16 bytes each, the tag in the last 8): counter i in the tag of slot i `spread`, as far
+// apart as there is room, since atomics on one line are served one after another; the smallest workspace (8 KiB of slots) has
+// room for the 2048 counters of the largest H at four to a tag (16 bits each; spread 0).  The gate/up launch clears the
+// counters, whatever the workspace holds there (another layer's rows, where layers of different expert counts share it), and the
+// last arrival leaves zeros, as the draft calls need them.
+struct CombineArgs { unsigned long long *slots; uint16_t *y; int spread, T, k, S, accumulate; };
+struct Counter { uint32_t *word; uint32_t shift; };
+__device__ inline Counter counter_of(const CombineArgs &c, uint32_t i)
+{
+    const uint32_t slot = c.spread ? i * c.spread : i / 4, field = c.spread ? 0 : i % 4;
+    return {reinterpret_cast<uint32_t *>(c.slots + 2 * slot + 1) + field / 2, 16 * (field % 2)};
+}
+
+// All counters to zero, by `workgroups` workgroups
+__device__ inline void clear_counters(const CombineArgs &c, int n, int workgroup, int workgroups)
+{
+    for (int i = workgroup * kWaves * 64 + threadIdx.x; i < n; i += workgroups * kWaves * 64) *counter_of(c, i).word = 0u;
+}
+
 // grid.x = I / 16, grid.y = experts of the plan.  kHiLo: the shared experts of a draft call.  Otherwise the verify call;
-// its grid has a row more, in front, whose first workgroup computes the routing weights (which only the down launch needs).
+// its grid has a row more, in front, for what only the down launch needs: the first workgroup computes the routing weights, the
+// others clear the arrival counters.
 template <bool kHiLo>
 __global__ __launch_bounds__(kWaves * 64)
 void bf16_gateup_kernel(const Plan *__restrict__ plan, const uint16_t *__restrict__ x, uint16_t *__restrict__ hb,
-                        uint16_t *__restrict__ hb_lo, int H, int I, const WeightArgs w)
+                        uint16_t *__restrict__ hb_lo, int H, int I, const WeightArgs w, const CombineArgs comb)
 {
     __shared__ GateUpSums s_red;
     const int u = kHiLo ? blockIdx.y : (int)blockIdx.y - 1;
     if constexpr (!kHiLo) {
-        if (u < 0) { if (blockIdx.x == 0) routing_weights(w); return; }
+        if (u < 0) {
+            if (blockIdx.x == 0) routing_weights(w);
+            else clear_counters(comb, H / 32, blockIdx.x - 1, gridDim.x - 1);          // (I >= 64: at least four workgroups)
+            return;
+        }
     }
     const int row = plan->act_row[u][threadIdx.x & 15];              // (entries past the last are inside the plan)
     const char *gate = (const char *)plan->act_w0[u];
@@ -136,17 +161,6 @@ __device__ inline void load16_agent(const float *p, f32x4 &v)      // two 8-byte
 
 // What the last workgroup of 32 output columns does for them: y[t] (bf16) = the token's live rows in a fixed order, routed ones
 // by rank, then shared ones.  One wave: lane (token, column quad) takes 4 columns of each half.
-// Arrivals are counted in the tags of the draft kernels' exchange slots (16 bytes each, the tag in the last 8), which are
-// zero between calls: counter i in the tag of slot i `spread`, as far apart as there is room, since atomics on one line
-// are served one after another; the smallest workspace (8 KiB of slots) has room for the 2048 counters of the largest H
-// at four to a tag (16 bits each, two arrivals per expert; spread 0).
-struct CombineArgs { unsigned long long *slots; uint16_t *y; int spread, T, k, S, accumulate; };
-struct Counter { uint32_t *word; uint32_t shift; };
-__device__ inline Counter counter_of(const CombineArgs &c, uint32_t i)
-{
-    const uint32_t slot = c.spread ? i * c.spread : i / 4, field = c.spread ? 0 : i % 4;
-    return {reinterpret_cast<uint32_t *>(c.slots + 2 * slot + 1) + field / 2, 16 * (field % 2)};
-}
 __device__ inline void combine_columns(const Plan *__restrict__ plan, const float *obuf, const CombineArgs &c, int H, int col0)
 {
     const int lane = threadIdx.x & 63, t = lane & 15, T = c.T, k = c.k, rows = k + c.S;
@@ -186,10 +200,9 @@ __device__ inline void combine_columns(const Plan *__restrict__ plan, const floa
 // kShared (the draft call's shared experts): the operand is hb + hb_lo (two MFMAs per tile), and
 // instead of writing obuf the row's outputs are added to y[token] with fp32 atomics (y already holds
 // the routed experts' sum, itself made of such atomics, so no combine launch is needed).
-// Verify call: the rows leave at agent scope, and the last workgroup of 32 columns to arrive (two row tiles of every live
-// expert) adds them up: 0.5 to 2.3 us of this launch instead of 4.7 to 5.2 us and a gap for one of its own.  That holds a
-// workgroup about a round trip longer, which the loads pay for: a wave's tiles past its last whole batch come in
-// one batch too (one by one, 768 inputs: 28.5 us for 8 tokens x 128 experts x 2048 outputs, now 25.0).
+// Verify call: the rows leave at agent scope, and the last workgroup of 32 columns to arrive adds them up: 0.5 to 2.3 us of
+// this launch instead of 4.7 to 5.2 us and a gap for one of its own.  That holds a workgroup about a round trip
+// longer, which the loads pay for: a wave's tiles past its last whole batch come in one batch too (one by one, 768 inputs: 28.5 us for 8 tokens x 128 experts x 2048 outputs, now 25.0).
 template <bool kShared>
 __global__ __launch_bounds__(kWaves * 64)
 void bf16_down_kernel(const Plan *__restrict__ plan, const uint16_t *__restrict__ hb, const uint16_t *__restrict__ hb_lo,
@@ -272,28 +285,31 @@ void bf16_down_kernel(const Plan *__restrict__ plan, const uint16_t *__restrict_
     }
 }
 
-}  // namespace
-
-void launch_verify_gateup(const Shape &s, const Plan *plan, const void *x, const double *logits, const int32_t *ids, float *row_w,
-                          void *hb, hipStream_t st)
+CombineArgs combine_args(const Shape &s, const VerifyCall &v)
 {
-    const WeightArgs w = {logits, ids, row_w, s.T, s.E, s.k, s.S, s.renorm};
-    launch(bf16_gateup_kernel<false>, dim3(s.I / 16, 1 + s.S + (s.E < s.T * s.k ? s.E : s.T * s.k)), dim3(kWaves * 64), 0, st, plan,
-           (const uint16_t *)x, (uint16_t *)hb, (uint16_t *)nullptr, s.H, s.I, w);
+    return {v.slots, (uint16_t *)v.y, (int)(v.slot_bytes / 16 / (s.H / 32)), s.T, s.k, s.S, v.accumulate};
 }
 
-void launch_verify_down(const Shape &s, const Plan *plan, const void *hb, float *obuf, unsigned long long *slots, size_t slot_bytes,
-                        int accumulate, void *y, hipStream_t st)
+}  // namespace
+
+void launch_verify_gateup(const Shape &s, const VerifyCall &v, hipStream_t st)
+{
+    const WeightArgs w = {v.logits, v.plan->ids, v.plan->row_w, s.T, s.E, s.k, s.S, s.renorm};
+    launch(bf16_gateup_kernel<false>, dim3(s.I / 16, 1 + s.S + (s.E < s.T * s.k ? s.E : s.T * s.k)), dim3(kWaves * 64), 0, st, v.plan,
+           (const uint16_t *)v.x, (uint16_t *)v.hb, (uint16_t *)nullptr, s.H, s.I, w, combine_args(s, v));
+}
+
+void launch_verify_down(const Shape &s, const VerifyCall &v, hipStream_t st)
 {
     const dim3 grid(s.H / 16, s.S + (s.E < s.T * s.k ? s.E : s.T * s.k)), block(kWaves * 64);
-    launch(bf16_down_kernel<false>, grid, block, 0, st, plan, (const uint16_t *)hb, (const uint16_t *)nullptr, obuf, s.H, s.I,
-           CombineArgs{slots, (uint16_t *)y, (int)(slot_bytes / 16 / (s.H / 32)), s.T, s.k, s.S, accumulate});
+    launch(bf16_down_kernel<false>, grid, block, 0, st, v.plan, (const uint16_t *)v.hb, (const uint16_t *)nullptr, v.obuf, s.H, s.I,
+           combine_args(s, v));
 }
 
 void launch_shared_gateup(const Shape &s, const Plan *plan, const void *x, void *hb, void *hb_lo, hipStream_t st)
 {
     launch(bf16_gateup_kernel<true>, dim3(s.I / 16, s.S), dim3(kWaves * 64), 0, st, plan, (const uint16_t *)x, (uint16_t *)hb,
-           (uint16_t *)hb_lo, s.H, s.I, WeightArgs{});
+           (uint16_t *)hb_lo, s.H, s.I, WeightArgs{}, CombineArgs{});
 }
 
 void launch_shared_down_add(const Shape &s, const Plan *plan, const void *hb, const void *hb_lo, float *y, hipStream_t st)

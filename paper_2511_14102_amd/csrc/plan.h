@@ -153,14 +153,18 @@ void launch_prefill_down(const Shape &s, const PrefillCall &p, int max_items, hi
 void launch_prefill_combine(const Shape &s, const PrefillCall &p, hipStream_t st);
 
 // expert_bf16.hip
-// The verify call's gate/up launch on the plan, which also writes the rows' routing weights
-void launch_verify_gateup(const Shape &s, const Plan *plan, const void *x, const double *logits, const int32_t *ids, float *row_w,
-                          void *hb, hipStream_t st);
-// the down products of the plan's experts into obuf ([rows][H] fp32); the last workgroup of every 32 output columns to
-// arrive (counted in the tags of the exchange slots, zero before and after) writes y[t] (bf16) = (accumulate ? y[t] : 0) +
-// the token's live rows
-void launch_verify_down(const Shape &s, const Plan *plan, const void *hb, float *obuf, unsigned long long *slots, size_t slot_bytes,
-                        int accumulate, void *y, hipStream_t st);
+// The verify call's launches on the plan.  Gate/up also writes the rows' routing weights and clears the arrival counters of
+// the next one; down: the products into obuf ([rows][H] fp32), and the last workgroup of every 32 output columns to arrive
+// (counted in the tags of the exchange slots, zero after) writes y[t] (bf16) = (accumulate ? y[t] : 0) + the token's live rows
+struct VerifyCall {
+    Plan *plan;
+    const void *x; const double *logits;
+    void *hb; float *obuf;
+    unsigned long long *slots; size_t slot_bytes;
+    int accumulate; void *y;
+};
+void launch_verify_gateup(const Shape &s, const VerifyCall &v, hipStream_t st);
+void launch_verify_down(const Shape &s, const VerifyCall &v, hipStream_t st);
 // The draft call's shared experts on the plan of its launch: the intermediate is kept as a bf16 hi + lo pair, and each
 // row's outputs are added to y[token] (fp32, [T,H]) with atomics
 void launch_shared_gateup(const Shape &s, const Plan *plan, const void *x, void *hb, void *hb_lo, hipStream_t st);

@@ -76,3 +76,24 @@ def test_verify_rows(ctx, cfg, tokens):
         torch.cuda.synchronize()
         assert int(D.n_missing.item()) == 0 and idle(D)
         assert rel_err(to_np(r0["y"]), ref["y"]) <= TOL_VERIFY
+
+
+def test_verify_layers_of_different_expert_counts_share_a_workspace(ctx):
+    """The rows of the layer of few experts lie where the other layer's exchange slots, and the arrival counters in their
+    tags, are."""
+    cfgs = (LayerConfig(85, "v2", 448, 2, 384, 1, 64, 0, 1), LayerConfig(63, "v448", 448, 20, 384, 3, 64, 4, 0))
+    layers = []
+    for cfg in cfgs:
+        L = synth.make_layer(cfg, 0, quantize=False)
+        A = oracle_arrays(L)
+        x = tokens_with_clear_routing(cfg, A, 9, step=5)
+        layers.append((DeviceLayer(ctx, cfg, L, max_tokens=9, draft=False), x.cuda(), oracle_verify(A, x)))
+    ws = max((D.workspace for D, _, _ in layers), key=lambda w: w.numel())
+    assert B.workspace_idle_bytes(layers[0][0].desc) < B.workspace_idle_bytes(layers[1][0].desc)
+    ctx.workspace_init(ws)
+    for D, x, ref in layers * 3:
+        say("verify", D.cfg.name)
+        D.workspace = ws
+        r = D.verify(x, y=torch.full((9, 448), 7.0, dtype=torch.bfloat16, device="cuda"))
+        torch.cuda.synchronize()
+        assert np.array_equal(to_np(r["ids"]), ref["ids"]) and rel_err(to_np(r["y"]), ref["y"]) <= TOL_VERIFY
