@@ -390,6 +390,17 @@ void prefill_tile_kernel(TileArgs a)
                     zs[tb] = *reinterpret_cast<const float *>(sums + (uint32_t)((c * kItemTokens + r) * 4) + tb * 64);
             }
         };
+        auto add_scaled_rows = [&](int d, int tb) {
+#pragma unroll
+            for (int i = 0; i < 4; ++i) tot[d][tb][i] = fmaf(sc[d], acc[d][tb][i], tot[d][tb][i]);
+            asm volatile("" : "+v"(tot[d][tb]));       // here and not further down, or acc could not be used again
+        };
+        auto add_scaled = [&](int tb) {
+#pragma unroll
+            for (int d = 0; d < 4; ++d) add_scaled_rows(d, tb);
+        };
+        // The last token block's share of the group before is added here, in front of its zero points, as the other blocks'
+        // was: a token's sums are the same bits in every block of an item.
         auto add_zeros = [&]() {
             if constexpr (!SYM) {
                 bf16x8 zx[NTB];
@@ -398,18 +409,11 @@ void prefill_tile_kernel(TileArgs a)
 #pragma unroll
                 for (int d = 0; d < 4; ++d) {
                     const bf16x8 f = __builtin_bit_cast(bf16x8, factor_operand(ze.scale(d) * ((ze.zero(d) - 8.f) * (-1.f / kOffset))));
+                    add_scaled_rows(d, NTB - 1);
 #pragma unroll
-                    for (int tb = NTB - 1; tb >= 0; --tb)
+                    for (int tb = 0; tb < NTB; ++tb)
                         tot[d][tb] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(zx[tb], f, tot[d][tb], 0, 0, 0);
                 }
-            }
-        };
-        auto add_scaled = [&](int tb) {
-#pragma unroll
-            for (int d = 0; d < 4; ++d) {
-#pragma unroll
-                for (int i = 0; i < 4; ++i) tot[d][tb][i] = fmaf(sc[d], acc[d][tb][i], tot[d][tb][i]);
-                asm volatile("" : "+v"(tot[d][tb]));   // here and not further down, or acc could not be used again
             }
         };
 
@@ -444,10 +448,12 @@ void prefill_tile_kernel(TileArgs a)
             }
             request(n + 3, std::integral_constant<int, (J + 3) & 3>{}, ntb_c);
             if constexpr ((J + 3) * SK % KPG == 0) request_sums(n + 3, std::integral_constant<int, (J + 3) & 3>{});
-            if constexpr (J % kZeroStages == 0) {
+            constexpr bool kZeros = !SYM && J % kZeroStages == 0;
+            if constexpr (kZeros) {
                 if (kZeroStages <= 4 || n % kZeroStages == 0) add_zeros();
+                else add_scaled(NTB - 1);
+                load_zeros(n / kZeroStages + 1);
             }
-            if constexpr (J % kZeroStages == 0) load_zeros(n / kZeroStages + 1);
 #pragma unroll
             for (int f = 0; f < F; ++f) {
                 const int s = f / NB, t = f % NB, tb = t / NP, p = t % NP;
@@ -456,7 +462,7 @@ void prefill_tile_kernel(TileArgs a)
                 __builtin_amdgcn_sched_barrier(0);
                 if (f + kA - 1 < F) read(f + kA - 1);
                 if (f + kF - 1 < F) read_sums(f + kF - 1);
-                if (begins && t == 0) add_scaled(NTB - 1);                            // of the group before
+                if (begins && t == 0 && !(kZeros && s == 0)) add_scaled(NTB - 1);     // of the group before
                 if (ends && t == 0) {
                     constexpr int kGroups = 4 * SK / KPG;
                     static_assert(kGroups % EW == 0, "the slot of a group has to be the same in every loop trip");

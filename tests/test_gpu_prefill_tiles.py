@@ -135,3 +135,32 @@ def test_prefill_sums_of_tokens_with_a_mean(H, I, g, symmetric):
     say("prefill %.3e draft %.3e" % (long_run, short))
     assert long_run <= 1.125 * short
     ctx.close()
+
+
+PLACES = [
+    #            idx  name     H    E   I   k  g    S  renorm
+    (LayerConfig(86, "q32", 384, 3, 384, 2, 32, 0, 1), 150),       # items of 32 tokens, 12 groups
+    (LayerConfig(87, "q64", 640, 5, 1344, 2, 64, 1, 1), 431),      # items of 64, 10 and 21 groups, a shared expert
+    (LayerConfig(88, "q128", 1152, 5, 1280, 2, 128, 0, 1), 400),   # 9 and 10 groups
+]
+
+
+@pytest.mark.parametrize("cfg,T", PLACES, ids=[c[0].name for c in PLACES])
+def test_prefill_does_not_depend_on_a_tokens_place(cfg, T):
+    """A token's y, ids and confidences are the same bits wherever it stands in the prompt, and so in its experts' items
+    (the place there is drawn from a counter, so that calls on the same prompt differ in it)."""
+    ctx = B.Context(0)
+    for symmetric in (False, True):
+        if symmetric and B.int4_expert_scale_bytes(B.LayerDesc.from_config(cfg)) == 0:
+            continue
+        D = DeviceLayer(ctx, cfg, synth.make_layer(cfg, 0, symmetric=symmetric), max_tokens=8, verify=False, symmetric=symmetric)
+        x = synth.make_tokens(cfg, T, step=13, kind="iid").cuda()
+        first = D.prefill(x)
+        for seed in range(3):
+            perm = torch.randperm(T, generator=torch.Generator().manual_seed(seed)).cuda()
+            say("prefill", cfg.name, "symmetric" if symmetric else "", "order", seed)
+            r = D.prefill(x[perm].contiguous())
+            torch.cuda.synchronize()
+            for n in ("ids", "conf", "y"):
+                assert torch.equal(r[n], first[n][perm]), n
+    ctx.close()
