@@ -73,23 +73,14 @@ constexpr int kItemTokens = 64;                   // slots of an item: four toke
 constexpr int kTileThreads = 256, kTileWaves = 4;
 constexpr int kXcds = 8;
 // The items, in segments: the shared experts' and full ones; then what is left of the experts' runs, by its token blocks of 16:
-// four, three, two or one.  n_items: their count, then each segment's.  A launch is only one and a half to three rounds of
-// workgroups (two a compute unit) where a prompt is of ordinary length, so that its end counts: largest first, it ends with
-// the short ones.  But the rest of a long run reads its weights a second time there, from the memory-side cache as
-// long as what lies between stays inside it; beyond kRestBytes a long run stays in one piece, in the first segment.
-// us per call, expert by expert / largest first / largest first, long runs in one piece:
-//   phi shape, 512 tokens (24 items, 50 and 16 columns; 131 MB in long runs)  343 / 317 / 329
-//   dsv2lite, 333 tokens (76 items, 11 and 8 columns; nearly no long runs)    155 / 147 / 146
-//   mixtral, 283 tokens (16 items, 112 and 16 columns; 470 MB in long runs)   409 / 433 / 412
-//   128 experts, 109 tokens (128 items of one or two blocks)                  109 / 111 / 111
+// four, three, two or one.  n_items: their count, then each segment's.  Where prefill_by_size does not choose this order, all
+// items are in the first segment, expert by expert.
 constexpr int kSegments = 4;
-constexpr long kRestBytes = 192L << 20;             // of the 256 MiB cache
-// Where a launch is one round (items of 32 tokens) or many (prefill_by_size), all items are in the first segment, expert by expert.
 constexpr float kOffset = -24.f;                  // factor of a stored group sum: takes 16 + q to q - 8
 
 // Items of an expert in the first segment, and the segment of its last item (0: it has none elsewhere)
-__device__ inline int head_items(int assignments, int chunk, bool by_size, bool in_pieces) {
-    return (assignments + (!by_size || (assignments > chunk && !in_pieces) ? chunk - 1 : 0)) / chunk;
+__device__ inline int head_items(int assignments, int chunk, bool by_size) {
+    return (assignments + (by_size ? 0 : chunk - 1)) / chunk;
 }
 __device__ inline int rest_segment(int assignments, int head, int chunk) {
     const int left = assignments - head * chunk;
@@ -616,7 +607,7 @@ template <int KPG, bool kPlanned>
 __global__ __launch_bounds__(256)
 void prefill_stage_kernel(const uint16_t *__restrict__ x, const int32_t *__restrict__ count, const int32_t *__restrict__ list,
                           PrefillItem *__restrict__ items, int32_t *__restrict__ n_items, int32_t *__restrict__ slot_of,
-                          char *__restrict__ xt, char *__restrict__ sums, char *__restrict__ zeros, int T, int H, int I, int k, int E, int S, int chunk, bool by_size)
+                          char *__restrict__ xt, char *__restrict__ sums, char *__restrict__ zeros, int T, int H, int k, int E, int S, int chunk, bool by_size)
 {
     const int blocks = chunk >> 4, item = blockIdx.x / blocks, tb = blockIdx.x % blocks, tid = threadIdx.x;
     const bool first = blockIdx.x == 0 && blockIdx.y == 0;
@@ -633,8 +624,7 @@ void prefill_stage_kernel(const uint16_t *__restrict__ x, const int32_t *__restr
         if (tid == 0) s_item = PrefillItem{0, 0, 0, -1};
         // thread e: expert e's items are [begin, begin + head) and, in segment `seg`, item `rest`
         const int cnt = tid < E ? count[tid] : 0;
-        const bool in_pieces = (long)__syncthreads_count(cnt > chunk) * H * I <= kRestBytes;
-        const int head = head_items(cnt, chunk, by_size, in_pieces), seg = rest_segment(cnt, head, chunk);
+        const int head = head_items(cnt, chunk, by_size), seg = rest_segment(cnt, head, chunk);
         int incl = head;
 #pragma unroll
         for (int d = 1; d < 64; d <<= 1) {
@@ -749,7 +739,7 @@ void prefill_combine_kernel(const float *__restrict__ obuf, const int32_t *__res
 // run into items of at most `chunk` and records the slot (item x 64 + position) of every assignment.
 // The first S ceil(T / chunk) items are the shared experts', over the tokens in order.  One workgroup.
 __global__ __launch_bounds__(1024)
-void prefill_plan_kernel(const int32_t *__restrict__ ids, int n, int E, int T, int S, int chunk, bool by_size, long weights,
+void prefill_plan_kernel(const int32_t *__restrict__ ids, int n, int E, int T, int S, int chunk, bool by_size,
                          int32_t *__restrict__ list, int32_t *__restrict__ slot_of,
                          PrefillItem *__restrict__ items, int32_t *__restrict__ n_items)
 {
@@ -764,12 +754,6 @@ void prefill_plan_kernel(const int32_t *__restrict__ ids, int n, int E, int T, i
     __syncthreads();
     for (int i = threadIdx.x; i < n; i += blockDim.x) atomicAdd(&s_count[ids[i]], 1);
     __syncthreads();
-    int n_long = 0;
-    for (int base = 0; by_size && base < E; base += 64) {
-        const int e = base + (threadIdx.x & 63);
-        n_long += __popcll(__ballot(e < E && s_count[e < E ? e : 0] > chunk));
-    }
-    const bool in_pieces = n_long * weights <= kRestBytes;
     if (threadIdx.x < 64) {
         const int lane = threadIdx.x;
         int off = 0, item = S * chunks;
@@ -777,7 +761,7 @@ void prefill_plan_kernel(const int32_t *__restrict__ ids, int n, int E, int T, i
             const int first = g == 0 ? 0 : item;
             for (int base = 0; base < E; base += 64) {
                 const int cnt = base + lane < E ? s_count[base + lane] : 0;
-                const int head = head_items(cnt, chunk, by_size, in_pieces), mine = g == 0 ? head : rest_segment(cnt, head, chunk) == g ? 1 : 0;
+                const int head = head_items(cnt, chunk, by_size), mine = g == 0 ? head : rest_segment(cnt, head, chunk) == g ? 1 : 0;
                 // (assignments of all experts, in the first round: at most 2^16; items: at most 2^11 + 2^8)
                 int incl = (g == 0 ? cnt : 0) | mine << 18;
 #pragma unroll
@@ -799,7 +783,7 @@ void prefill_plan_kernel(const int32_t *__restrict__ ids, int n, int E, int T, i
         }
     }
     __syncthreads();
-    auto item_of = [&](int e, int j) { return j < head_items(s_count[e], chunk, by_size, in_pieces) ? s_item0[e] + j : s_rest[e]; };
+    auto item_of = [&](int e, int j) { return j < head_items(s_count[e], chunk, by_size) ? s_item0[e] + j : s_rest[e]; };
     for (int i = threadIdx.x; i < n; i += blockDim.x) {
         const int e = ids[i];
         const int idx = atomicAdd(&s_fill[e], 1);
@@ -837,10 +821,11 @@ void launch_tile(const TileArgs &t, bool sym, int g, int tiles, int max_items, h
 
 }  // namespace
 
-// workgroups of a tile launch per item, the larger of the two
+// workgroups of the tile launches per item: the down launch's, and the larger of the two
+static int down_columns(const Shape &s) { return (s.H / 64 + kTileWaves - 1) / kTileWaves; }
 static int prefill_columns(const Shape &s)
 {
-    const int gate = (s.I / 32 + kTileWaves - 1) / kTileWaves, down = (s.H / 64 + kTileWaves - 1) / kTileWaves;
+    const int gate = (s.I / 32 + kTileWaves - 1) / kTileWaves, down = down_columns(s);
     return gate > down ? gate : down;
 }
 
@@ -858,13 +843,25 @@ static int items_of(const Shape &s, int chunk)
 // (H = 1024, I = 2048, 300 tokens, 416: 65.8 / 55.9), the more evenly the 64s fill the units the less.
 constexpr int kSmallGrid = 256;
 int prefill_chunk(const Shape &s) { return (long)prefill_columns(s) * items_of(s, 32) <= kSmallGrid ? 32 : 64; }
-// Largest items first, up to three and a half rounds of 512 workgroups (upper bound): the end of a longer launch is a smaller part
-// of it, and the order costs neighbours in the cache.  us per pass, without segments / largest first (workgroups), and in
-// brackets the experts' order with the segments' arithmetic, which costs what is left: phi shape, 512 tokens (1600) 712 / 648;
-// dsv2lite, 333 tokens (1177) 628 / 603; H = 1408, E = 41, I = 4864, k = 3, 298 tokens (2052) 365 / 369 (1.2 % as well);
-// H = 512, E = 112, I = 1856, k = 8, 4 shared, 201 tokens (2295) 425 / 434 (0.7 %); H = 448, E = 81, I = 9024, k = 7,
-// 618 tokens (10508) 368 / 377 (0.7 %).
-static bool prefill_by_size(const Shape &s) { return prefill_chunk(s) == kItemTokens && (long)prefill_columns(s) * items_of(s, kItemTokens) < 7 * 256; }
+// Largest items first, where a launch has few rounds of workgroups (two a compute unit), so that it ends with short ones and a unit
+// that takes two workgroups takes a long and a short one.  Not where that counts little: beyond three and a half rounds
+// (upper bound of either launch), where the parting of an expert's items, which read the same weights, counts more; where the down
+// launch leaves units empty; and where all items are alike: runs of less than a token block and no shared experts.
+// us per call, expert by expert / largest first (gate/up and down workgroups, upper bound):
+//   phi shape, 512 tokens (1600, 512)       348 / 324       dsv2lite, 333 tokens (1177, 856)        156 / 147
+//   phi shape, 600 tokens (1700, 544)       374 / 354       ..., 700 tokens (1661, 1208)            229 / 224
+//   even popularity, 600 tokens             397 / 375       H = 1472, E = 20, k = 6, 2 shared, 294 (342, 342)   82.4 / 72.0
+//   mixtral, 200 tokens (1568, 224)         368 / 360       H = 4096, E = 4, I = 12288, k = 4, 200 (1536, 256)  393 / 385
+// and outside: mixtral, 283 tokens (1792, 256) 405 / 425; dsv2lite, 1200 (2354, 1712) 322 / 335; qwen3, 1500 (1890, 2520) 298 / 314;
+// H = 1280, E = 7, I = 7296, k = 1, 4 shared, 27 tokens (627, 55) 149 / 152; H = 256, E = 109, I = 1920, k = 6, 40 tokens
+// (1680, 112) 57.0 / 58.8.  Inside it can lose (H = 2112, I = 512, E = 15, k = 1, 2 shared, 2024 tokens (440, 990) 122.9 / 125.7),
+// above the line it can win (zipf popularity, H = 1088, E = 96, 378 tokens (3562, 685) 196 / 173).
+static bool prefill_by_size(const Shape &s)
+{
+    const long items = items_of(s, kItemTokens);
+    const bool alike = s.S == 0 && s.T * s.k < 16 * s.E;
+    return prefill_chunk(s) == kItemTokens && prefill_columns(s) * items < 7 * 256 && down_columns(s) * items > 200 && !alike;
+}
 int prefill_max_items(const Shape &s) { return items_of(s, prefill_chunk(s)); }
 size_t prefill_item_room(const Shape &s)
 {
@@ -892,7 +889,7 @@ bool prefill_small(const Shape &s) { return (long)s.T * ((long)s.E * s.H + 1024L
 
 void launch_prefill_plan(const Shape &s, const int32_t *ids, const PrefillCall &p, hipStream_t st)
 {
-    launch(prefill_plan_kernel, dim3(1), dim3(1024), 0, st, ids, s.T * s.k, s.E, s.T, s.S, prefill_chunk(s), prefill_by_size(s), (long)s.H * s.I, (int32_t *)p.list, p.slot_of, p.items, p.n_items);
+    launch(prefill_plan_kernel, dim3(1), dim3(1024), 0, st, ids, s.T * s.k, s.E, s.T, s.S, prefill_chunk(s), prefill_by_size(s), (int32_t *)p.list, p.slot_of, p.items, p.n_items);
 }
 
 void launch_prefill_stage(const Shape &s, const PrefillCall &p, int max_items, hipStream_t st)
@@ -901,7 +898,7 @@ void launch_prefill_stage(const Shape &s, const PrefillCall &p, int max_items, h
     const dim3 grid(max_items * (chunk / 16), (s.H / 32 + 15) / 16), block(256);
     auto go = [&](auto kernel) {
         launch(kernel, grid, block, 0, st, (const uint16_t *)p.x, p.count, p.list, p.items, p.n_items, p.slot_of, (char *)p.xt,
-               (char *)p.x_sums, (char *)p.zeros, s.T, s.H, s.I, s.k, s.E, s.S, chunk, prefill_by_size(s));
+               (char *)p.x_sums, (char *)p.zeros, s.T, s.H, s.k, s.E, s.S, chunk, prefill_by_size(s));
     };
     auto of_group = [&](auto planned) {
         constexpr bool kPlanned = decltype(planned)::value;

@@ -9,7 +9,7 @@ import torch
 import synth
 from synth.configs import LayerConfig
 from tests.common import oracle_arrays, oracle_draft, rel_err
-from tests.gpu_common import TOL_DRAFT, Guarded, say, to_np, tokens_with_clear_routing
+from tests.gpu_common import TOL_DRAFT, Guarded, build_layer, say, to_np, tokens_with_clear_routing
 
 pytestmark = pytest.mark.gpu
 
@@ -85,7 +85,7 @@ ROUTED = [
     LayerConfig(66, "r70", 320, 70, 64, 3, 32, 0, 1),      # ragged token and expert blocks, k-steps that do not fill a share
     LayerConfig(67, "r130", 192, 130, 64, 4, 64, 1, 0),    # more than 128 experts, a shared expert
     LayerConfig(68, "r5", 2112, 5, 64, 5, 64, 2, 1),       # few experts, shares of H, every token in every expert
-    LayerConfig(80, "r72", 512, 72, 1024, 6, 128, 1, 1),   # more than 64 experts with one to four token blocks left (items by size)
+    LayerConfig(80, "r72", 512, 72, 1024, 6, 128, 1, 1),   # more than 64 experts with one to four token blocks left
     LayerConfig(70, "r4160", 4160, 4, 64, 2, 64, 0, 1),    # the most shares of H (8 x 4 waves), 130 k-steps over them
 ]
 
@@ -163,4 +163,44 @@ def test_prefill_does_not_depend_on_a_tokens_place(cfg, T):
             torch.cuda.synchronize()
             for n in ("ids", "conf", "y"):
                 assert torch.equal(r[n], first[n][perm]), n
+    ctx.close()
+
+
+ORDERS = [
+    #            idx  name      H    E   I    k  g   S  renorm     tokens, largest items first, items by the sorting kernel
+    (LayerConfig(89, "o768", 768, 72, 1024, 6, 128, 1, 1), 421, True, False),     # every kind of rest, a shared expert
+    (LayerConfig(90, "o4096s", 4096, 8, 128, 2, 64, 4, 1), 120, True, True),
+    (LayerConfig(91, "o4096", 4096, 16, 64, 2, 32, 0, 1), 300, True, False),      # no shared experts
+    (LayerConfig(92, "o128", 128, 48, 4096, 8, 32, 0, 1), 300, False, False),     # more than three and a half rounds
+    (LayerConfig(93, "o192", 192, 20, 8192, 2, 64, 1, 1), 280, False, True),
+]
+
+
+@pytest.mark.parametrize("cfg,T,by_size,sorted_by_kernel", ORDERS, ids=[c[0].name for c in ORDERS])
+def test_prefill_orders_of_the_items(cfg, T, by_size, sorted_by_kernel):
+    """Items of 64 tokens in both orders, from the stage kernel and from the sorting kernel, with runs of no and of several
+    whole items and rests of one to four token blocks (experts of falling popularity)."""
+    cols = max(-(-cfg.inter // 128), -(-cfg.hidden // 256))
+    items = lambda n: T * cfg.top_k // n + min(cfg.n_experts, T * cfg.top_k) + cfg.n_shared * -(-T // n)
+    assert cols * items(32) > 256                          # items of 64
+    assert (cols * items(64) < 1792 and -(-cfg.hidden // 256) * items(64) > 200
+            and (cfg.n_shared > 0 or T * cfg.top_k >= 16 * cfg.n_experts)) == by_size
+    assert (T * (cfg.n_experts * cfg.hidden + 1024 * cfg.top_k) < 4 << 20) == sorted_by_kernel
+    ctx = B.Context(0)
+    L = build_layer(cfg, bias="zipf")
+    A = oracle_arrays(L)
+    D = DeviceLayer(ctx, cfg, L, max_tokens=8, verify=False)
+    x = tokens_with_clear_routing(cfg, A, T, step=17, kind="iid")
+    ref = oracle_draft(A, x)
+    counts = np.bincount(ref["ids"].ravel(), minlength=cfg.n_experts)
+    say("prefill", cfg.name, "T", T, "counts", counts.tolist())
+    assert counts.max() > 64 and counts.min() < 16 and len({(c % 64 + 15) // 16 for c in counts} - {0}) >= 3
+    ws = Guarded(B.prefill_workspace_bytes(D.desc, T))
+    D._prefill_ws = ws.view
+    for _ in range(2):
+        ws.view.fill_(0xff)
+        r = D.prefill(x.cuda())
+        torch.cuda.synchronize()
+        assert ws.intact() and np.array_equal(to_np(r["ids"]), ref["ids"])
+        assert rel_err(to_np(r["y"]), ref["y"]) <= TOL_DRAFT
     ctx.close()
