@@ -78,12 +78,12 @@ constexpr int kXcds = 8;
 constexpr int kSegments = 4;
 constexpr float kOffset = -24.f;                  // factor of a stored group sum: takes 16 + q to q - 8
 
-// Items of an expert in the first segment, and the segment of its last item (0: it has none elsewhere)
-__device__ inline int head_items(int assignments, int chunk, bool by_size) {
-    return (assignments + (by_size ? 0 : chunk - 1)) / chunk;
+// Items of an expert in the first segment (lg: log2 of an item's tokens), and the segment of its last item (0: it has none elsewhere)
+__device__ inline int head_items(int assignments, int lg, bool by_size) {
+    return (assignments + (by_size ? 0 : (1 << lg) - 1)) >> lg;
 }
-__device__ inline int rest_segment(int assignments, int head, int chunk) {
-    const int left = assignments - head * chunk;
+__device__ inline int rest_segment(int assignments, int head, int lg) {
+    const int left = assignments - (head << lg);
     return left <= 0 ? 0 : left > 48 ? 1 : left > 32 ? 2 : 3;
 }
 
@@ -91,7 +91,7 @@ struct TileArgs {
     const char *q, *sz;              // int4 codes / scale(-zero) blobs of the routed experts
     size_t stride_q, stride_sz;
     const PrefillItem *items;
-    const int32_t *n_items;          // [1 + kSegments]
+    const int32_t *n_items;          // [1 + segments]
     const char *act0, *act1;         // operand tiles [(item nk + u) 4 + tb] of 1 KiB: x, or h and its remainder
     const char *act_sums;            // -24 x group sums, fp32 [(item 4 nz + group) 64 + token]; nz = ceil(groups / 4)
     const char *zeros;               // 4 KiB of zeros
@@ -99,7 +99,7 @@ struct TileArgs {
     float *obuf;                     // down: out [item 64 + token][H]
     const char *shared;              // bf16 blobs of the shared experts (experts E, E + 1, ...)
     size_t shared_stride;
-    int H, I, E;
+    int H, I, E, segments;
 };
 
 // The 8 codes of one word as 8 bf16 values 16 + code: 0x4180 is bf16 16.0, and a code in mantissa
@@ -179,21 +179,22 @@ void prefill_tile_kernel(TileArgs a)
     // Workgroups go to the XCDs in turn.  The item list is in segments of falling size; of each segment XCD x takes the
     // x-th contiguous eighth of the (column, item) pairs, items fastest, so that the items of one expert,
     // neighbours in the list, read its weight tiles through the same L2, and the smallest workgroups come last.
-    int pair = 0, seg_items = 0, first_item = 0;
-    {
-        int at = (int)blockIdx.x / kXcds, first = 0;
+    int n[kSegments];                                                    // (all counts by one load)
 #pragma unroll
-        for (int seg = 0; seg < kSegments; ++seg) {                      // (all counts by one load, no branches)
-            const int n = a.n_items[1 + seg], per = (cols * n + kXcds - 1) / kXcds;
-            const bool here = at >= 0 && at < per;
-            pair = here ? ((int)blockIdx.x % kXcds) * per + at : pair;
-            seg_items = here ? n : seg_items;
-            first_item = here ? first : first_item;
-            at -= per;
-            first += n;
+    for (int seg = 0; seg < kSegments; ++seg) n[seg] = a.n_items[1 + seg];
+    int at = (int)blockIdx.x / kXcds, seg_items = n[0], first_item = 0, per = (cols * seg_items + kXcds - 1) / kXcds;
+    if (a.segments > 1) {                                                // (without: H = 512, 201 tokens 50.7 / 50.0 us)
+#pragma unroll
+        for (int seg = 1; seg < kSegments; ++seg) {
+            const bool past = at >= per;
+            at -= past ? per : 0;
+            first_item += past ? seg_items : 0;
+            seg_items = past ? n[seg] : seg_items;
+            per = (cols * seg_items + kXcds - 1) / kXcds;
         }
     }
-    if (pair >= cols * seg_items) return;
+    const int pair = ((int)blockIdx.x % kXcds) * per + at;
+    if (at >= per || pair >= cols * seg_items) return;
     const int col = pair / seg_items, item = first_item + pair - col * seg_items;
     const PrefillItem it = a.items[item];
     const int tid = threadIdx.x, lane = tid & 63, r = lane & 15, c = lane >> 4;
@@ -603,13 +604,16 @@ void prefill_tile_kernel(TileArgs a)
 // counts (the shared experts' S ceil(T / chunk) items come first, then the routed ones in their segments; expert
 // e's assignments are list[e T ..]); each workgroup sums the counts up for itself, the first one also writes the items,
 // and a block's first workgroup the slots of its assignments.  The first workgroup also writes the tile of zeros.
-template <int KPG, bool kPlanned>
+// kBySize: in segments by size; else all in the first one, without the work for the others.  Every workgroup finds its item
+// first, so that counts: sums over the experts by lane moves, two words a wave (lane permutes, ballots and a word per
+// segment, in every call: this launch for dsv2lite, 333 tokens 8.9 / 7.8 us; qwen3, 333 tokens 11.1 / 9.6; H = 448, 618 tokens 6.1 / 5.2).
+template <int KPG, bool kPlanned, bool kBySize>
 __global__ __launch_bounds__(256)
 void prefill_stage_kernel(const uint16_t *__restrict__ x, const int32_t *__restrict__ count, const int32_t *__restrict__ list,
                           PrefillItem *__restrict__ items, int32_t *__restrict__ n_items, int32_t *__restrict__ slot_of,
-                          char *__restrict__ xt, char *__restrict__ sums, char *__restrict__ zeros, int T, int H, int k, int E, int S, int chunk, bool by_size)
+                          char *__restrict__ xt, char *__restrict__ sums, char *__restrict__ zeros, int T, int H, int k, int E, int S, int lg)
 {
-    const int blocks = chunk >> 4, item = blockIdx.x / blocks, tb = blockIdx.x % blocks, tid = threadIdx.x;
+    const int chunk = 1 << lg, item = blockIdx.x >> (lg - 4), tb = blockIdx.x & ((chunk >> 4) - 1), tid = threadIdx.x;
     const bool first = blockIdx.x == 0 && blockIdx.y == 0;
     if (first) *reinterpret_cast<u32x4 *>(zeros + tid * 16) = (u32x4){0u, 0u, 0u, 0u};
     PrefillItem it;
@@ -618,41 +622,40 @@ void prefill_stage_kernel(const uint16_t *__restrict__ x, const int32_t *__restr
         it = items[item];
         if ((item >= n) | (16 * tb >= it.cnt) | (it.src != item)) return;
     } else {
-        __shared__ __align__(16) int32_t s_count[kSegments][4];        // per segment and wave of 64 experts: items
+        __shared__ __align__(16) int32_t s_head[4], s_rest[4];         // per wave of 64 experts: items in the first and in the other segments
         __shared__ PrefillItem s_item;
-        const int chunks = (T + chunk - 1) / chunk, wave = tid >> 6, lane = tid & 63;
+        const int chunks = (T + chunk - 1) >> lg, wave = tid >> 6, lane = tid & 63;
         if (tid == 0) s_item = PrefillItem{0, 0, 0, -1};
-        // thread e: expert e's items are [begin, begin + head) and, in segment `seg`, item `rest`
+        // thread e: expert e's items are [begin, begin + head) and, in segment `seg`, item `rest`.  (The counts of the
+        // other segments travel as three fields of ten bits.)
         const int cnt = tid < E ? count[tid] : 0;
-        const int head = head_items(cnt, chunk, by_size), seg = rest_segment(cnt, head, chunk);
-        int incl = head;
-#pragma unroll
-        for (int d = 1; d < 64; d <<= 1) {
-            const int v = __shfl_up(incl, d, 64);
-            if (lane >= d) incl += v;
-        }
-        int begin = S * chunks + incl - head, rest = 0, counts[kSegments];
-#pragma unroll
-        for (int g = 1; g < kSegments; ++g) {
-            const unsigned long long in = __ballot(seg == g);
-            counts[g] = __popcll(in);
-            rest = seg == g ? __popcll(in & ((1ull << lane) - 1ull)) : rest;
-        }
+        const int head = head_items(cnt, lg, kBySize), seg = kBySize ? rest_segment(cnt, head, lg) : 0;
+        const int field = 10 * (seg - 1), incl = wave::prefix_sum(head, lane), rests = kBySize ? wave::prefix_sum(seg ? 1 << field : 0, lane) : 0;
         if (lane == 63) {
-            counts[0] = incl;
-#pragma unroll
-            for (int g = 0; g < kSegments; ++g) s_count[g][wave] = counts[g];
+            s_head[wave] = incl;
+            if constexpr (kBySize) s_rest[wave] = rests;
         }
         __syncthreads();
-        int total = S * chunks, n_seg[kSegments];
+        auto of_waves = [&](const int32_t *p, int &below, int &all) {
+            const int4 n = *reinterpret_cast<const int4 *>(p);
+            below = (wave > 0 ? n.x : 0) + (wave > 1 ? n.y : 0) + (wave > 2 ? n.z : 0);
+            all = n.x + n.y + n.z + n.w;
+        };
+        int begin, total, rest = 0, n_seg[kSegments] = {0, 0, 0, 0};
+        of_waves(s_head, begin, total);
+        begin += S * chunks + incl - head;
+        total += S * chunks;
+        n_seg[0] = total;
+        if constexpr (kBySize) {
+            int below, all;
+            of_waves(s_rest, below, all);
+            if (seg) rest = total + ((below + rests) >> field & 1023) - 1;
 #pragma unroll
-        for (int g = 0; g < kSegments; ++g) {
-            const int4 n = *reinterpret_cast<const int4 *>(s_count[g]);
-            const int before = (wave > 0 ? n.x : 0) + (wave > 1 ? n.y : 0) + (wave > 2 ? n.z : 0), sum = n.x + n.y + n.z + n.w;
-            begin += g == 0 ? before : 0;
-            rest += seg == g ? total + before : 0;
-            n_seg[g] = sum + (g == 0 ? S * chunks : 0);
-            total += sum;
+            for (int g = 1; g < kSegments; ++g) {
+                n_seg[g] = all >> 10 * (g - 1) & 1023;
+                total += n_seg[g];
+                rest += seg > g ? n_seg[g] : 0;
+            }
         }
         auto chunk_of = [&](int j, int at) {             // of this thread's expert
             return PrefillItem{tid, tid * T + j * chunk, cnt - j * chunk < chunk ? cnt - j * chunk : chunk, at};
@@ -671,7 +674,7 @@ void prefill_stage_kernel(const uint16_t *__restrict__ x, const int32_t *__restr
             if (tid == 0) {
                 n_items[0] = total;
 #pragma unroll
-                for (int g = 0; g < kSegments; ++g) n_items[1 + g] = n_seg[g];
+                for (int g = 0; g < (kBySize ? kSegments : 1); ++g) n_items[1 + g] = n_seg[g];
             }
         }
         __syncthreads();
@@ -739,13 +742,13 @@ void prefill_combine_kernel(const float *__restrict__ obuf, const int32_t *__res
 // run into items of at most `chunk` and records the slot (item x 64 + position) of every assignment.
 // The first S ceil(T / chunk) items are the shared experts', over the tokens in order.  One workgroup.
 __global__ __launch_bounds__(1024)
-void prefill_plan_kernel(const int32_t *__restrict__ ids, int n, int E, int T, int S, int chunk, bool by_size,
+void prefill_plan_kernel(const int32_t *__restrict__ ids, int n, int E, int T, int S, int lg, bool by_size,
                          int32_t *__restrict__ list, int32_t *__restrict__ slot_of,
                          PrefillItem *__restrict__ items, int32_t *__restrict__ n_items)
 {
     __shared__ int32_t s_count[MOE_MAX_EXPERTS], s_off[MOE_MAX_EXPERTS], s_fill[MOE_MAX_EXPERTS],
         s_item0[MOE_MAX_EXPERTS], s_rest[MOE_MAX_EXPERTS];
-    const int chunks = (T + chunk - 1) / chunk;
+    const int chunk = 1 << lg, chunks = (T + chunk - 1) >> lg;
     for (int i = threadIdx.x; i < S * chunks; i += blockDim.x) {
         const int j = i % chunks;
         items[i] = PrefillItem{E + i / chunks, j * chunk, T - j * chunk < chunk ? T - j * chunk : chunk, j};
@@ -761,14 +764,9 @@ void prefill_plan_kernel(const int32_t *__restrict__ ids, int n, int E, int T, i
             const int first = g == 0 ? 0 : item;
             for (int base = 0; base < E; base += 64) {
                 const int cnt = base + lane < E ? s_count[base + lane] : 0;
-                const int head = head_items(cnt, chunk, by_size), mine = g == 0 ? head : rest_segment(cnt, head, chunk) == g ? 1 : 0;
+                const int head = head_items(cnt, lg, by_size), mine = g == 0 ? head : rest_segment(cnt, head, lg) == g ? 1 : 0;
                 // (assignments of all experts, in the first round: at most 2^16; items: at most 2^11 + 2^8)
-                int incl = (g == 0 ? cnt : 0) | mine << 18;
-#pragma unroll
-                for (int d = 1; d < 64; d <<= 1) {
-                    const int v = __shfl_up(incl, d, 64);
-                    if (lane >= d) incl += v;
-                }
+                const int incl = wave::prefix_sum((g == 0 ? cnt : 0) | mine << 18, lane);
                 if (g == 0 && base + lane < E) s_off[base + lane] = off + (incl & 0x3ffff) - cnt;
                 if (mine > 0) (g == 0 ? s_item0 : s_rest)[base + lane] = item + (incl >> 18) - mine;
                 const int all = __builtin_amdgcn_readlane(incl, 63);
@@ -777,18 +775,15 @@ void prefill_plan_kernel(const int32_t *__restrict__ ids, int n, int E, int T, i
             }
             if (lane == 0) n_items[1 + g] = item - first;
         }
-        if (lane == 0) {
-            n_items[0] = item;
-            for (int g = 1; !by_size && g < kSegments; ++g) n_items[1 + g] = 0;
-        }
+        if (lane == 0) n_items[0] = item;
     }
     __syncthreads();
-    auto item_of = [&](int e, int j) { return j < head_items(s_count[e], chunk, by_size) ? s_item0[e] + j : s_rest[e]; };
+    auto item_of = [&](int e, int j) { return j < head_items(s_count[e], lg, by_size) ? s_item0[e] + j : s_rest[e]; };
     for (int i = threadIdx.x; i < n; i += blockDim.x) {
         const int e = ids[i];
         const int idx = atomicAdd(&s_fill[e], 1);
         list[s_off[e] + idx] = i;
-        slot_of[i] = item_of(e, idx / chunk) * kItemTokens + idx % chunk;
+        slot_of[i] = item_of(e, idx >> lg) * kItemTokens + (idx & (chunk - 1));
     }
     for (int e = threadIdx.x; e < E; e += blockDim.x) {
         const int cnt = s_count[e];
@@ -806,7 +801,7 @@ template <bool DOWN, bool SYM>
 void launch_tile_g(const TileArgs &t, int g, int tiles, int max_items, hipStream_t st)
 {
     const size_t pairs = (size_t)((tiles + kTileWaves - 1) / kTileWaves) * max_items;
-    const dim3 grid((unsigned)(((pairs + kXcds - 1) / kXcds + kSegments - 1) * kXcds)), block(kTileThreads);   // (each segment is rounded up)
+    const dim3 grid((unsigned)(((pairs + kXcds - 1) / kXcds + t.segments - 1) * kXcds)), block(kTileThreads);   // (each segment is rounded up)
     if (g == 32) launch(prefill_tile_kernel<DOWN, SYM, 1>, grid, block, 0, st, t);
     else if (g == 64) launch(prefill_tile_kernel<DOWN, SYM, 2>, grid, block, 0, st, t);
     else launch(prefill_tile_kernel<DOWN, SYM, 4>, grid, block, 0, st, t);
@@ -862,6 +857,7 @@ static bool prefill_by_size(const Shape &s)
     const bool alike = s.S == 0 && s.T * s.k < 16 * s.E;
     return prefill_chunk(s) == kItemTokens && prefill_columns(s) * items < 7 * 256 && down_columns(s) * items > 200 && !alike;
 }
+static int prefill_lg(const Shape &s) { return prefill_chunk(s) == 32 ? 5 : 6; }
 int prefill_max_items(const Shape &s) { return items_of(s, prefill_chunk(s)); }
 size_t prefill_item_room(const Shape &s)
 {
@@ -889,25 +885,26 @@ bool prefill_small(const Shape &s) { return (long)s.T * ((long)s.E * s.H + 1024L
 
 void launch_prefill_plan(const Shape &s, const int32_t *ids, const PrefillCall &p, hipStream_t st)
 {
-    launch(prefill_plan_kernel, dim3(1), dim3(1024), 0, st, ids, s.T * s.k, s.E, s.T, s.S, prefill_chunk(s), prefill_by_size(s), (int32_t *)p.list, p.slot_of, p.items, p.n_items);
+    launch(prefill_plan_kernel, dim3(1), dim3(1024), 0, st, ids, s.T * s.k, s.E, s.T, s.S, prefill_lg(s), prefill_by_size(s), (int32_t *)p.list, p.slot_of, p.items, p.n_items);
 }
 
 void launch_prefill_stage(const Shape &s, const PrefillCall &p, int max_items, hipStream_t st)
 {
-    const int chunk = prefill_chunk(s);
-    const dim3 grid(max_items * (chunk / 16), (s.H / 32 + 15) / 16), block(256);
+    const int lg = prefill_lg(s);
+    const dim3 grid(max_items << (lg - 4), (s.H / 32 + 15) / 16), block(256);
     auto go = [&](auto kernel) {
         launch(kernel, grid, block, 0, st, (const uint16_t *)p.x, p.count, p.list, p.items, p.n_items, p.slot_of, (char *)p.xt,
-               (char *)p.x_sums, (char *)p.zeros, s.T, s.H, s.k, s.E, s.S, chunk, prefill_by_size(s));
+               (char *)p.x_sums, (char *)p.zeros, s.T, s.H, s.k, s.E, s.S, lg);
     };
-    auto of_group = [&](auto planned) {
-        constexpr bool kPlanned = decltype(planned)::value;
-        if (s.g == 32) go(prefill_stage_kernel<1, kPlanned>);
-        else if (s.g == 64) go(prefill_stage_kernel<2, kPlanned>);
-        else go(prefill_stage_kernel<4, kPlanned>);
+    auto of_group = [&](auto planned, auto by_size) {
+        constexpr bool kPlanned = decltype(planned)::value, kBySize = decltype(by_size)::value;
+        if (s.g == 32) go(prefill_stage_kernel<1, kPlanned, kBySize>);
+        else if (s.g == 64) go(prefill_stage_kernel<2, kPlanned, kBySize>);
+        else go(prefill_stage_kernel<4, kPlanned, kBySize>);
     };
-    if (prefill_small(s)) of_group(std::true_type{});
-    else of_group(std::false_type{});
+    if (prefill_small(s)) of_group(std::true_type{}, std::false_type{});
+    else if (prefill_by_size(s)) of_group(std::false_type{}, std::true_type{});
+    else of_group(std::false_type{}, std::false_type{});
 }
 
 static TileArgs tile_args(const Shape &s, const PrefillCall &p)
@@ -917,7 +914,7 @@ static TileArgs tile_args(const Shape &s, const PrefillCall &p)
     t.items = p.items; t.n_items = p.n_items; t.zeros = (const char *)p.zeros;
     t.h_hi = (char *)p.h_hi; t.h_lo = (char *)p.h_lo; t.h_sums = (char *)p.h_sums; t.obuf = p.obuf;
     t.shared = (const char *)p.shared; t.shared_stride = p.shared_stride;
-    t.H = s.H; t.I = s.I; t.E = s.E;
+    t.H = s.H; t.I = s.I; t.E = s.E; t.segments = prefill_by_size(s) ? kSegments : 1;
     return t;
 }
 

@@ -78,6 +78,15 @@ __device__ inline double max(double v) { return all(v, [](double a, double b) { 
 __device__ inline int max(int v) { return all(v, [](int a, int b) { return a > b ? a : b; }); }
 __device__ inline float row_sum(float v) { return row_all(v, [](float a, float b) { return a + b; }); }
 
+// Sum of the values of this lane and of the lanes below it: shifts inside the rows of 16 lanes, then the row totals
+__device__ inline int prefix_sum(int v, int lane) {
+    v += move<0x111>(v);                // row_shr 1, 2, 4, 8: lanes that have no partner get 0
+    v += move<0x112>(v);
+    v += move<0x114>(v);
+    v += move<0x118>(v);
+    const int r0 = from_lane<15>(v), r1 = r0 + from_lane<31>(v), r2 = r1 + from_lane<47>(v);
+    return v + (lane < 16 ? 0 : lane < 32 ? r0 : lane < 48 ? r1 : r2);
+}
 
 // A logit as the selections compare it: NaN comes last (unordered, several would share a rank, and ranks below k
 // would be left without an expert)
