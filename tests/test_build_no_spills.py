@@ -37,6 +37,7 @@ def _kernel_blocks(text, kernel):
 
 def test_draft_kernel_instantiations_do_not_spill():
     for src, kernel, count in (("draft_int4.hip", "draft_stream_kernel", 36),     # 2 windows x 3 token capacities x 3 group sizes x 2 formats
+                               ("draft_int4.hip", "draft_stream_sums_kernel", 18),    # 3 token capacities x 3 group sizes x 2 formats
                                ("draft_slice.hip", "draft_fused_kernel", 12),     # with and without shared experts x 3 group sizes x 2 formats
                                ("draft_prefill.hip", "prefill_tile_kernel", 12)): # (gate/up, down) x 3 group sizes x 2 formats
         blocks = _kernel_blocks(_assembly(src), kernel)
@@ -48,8 +49,7 @@ def test_draft_kernel_instantiations_do_not_spill():
 
 
 def test_streaming_kernel_uses_m0_only_for_its_loads_to_lds():
-    text = _assembly("draft_int4.hip")
-    body = text.split("draft_stream_kernel", 1)[1]
+    body = _assembly("draft_int4.hip")
     uses = [l.strip() for l in body.splitlines() if re.search(r"\bm0\b", l) and not l.strip().startswith(";")]
     assert uses, "the loads to LDS are gone?"
     for l in uses:
