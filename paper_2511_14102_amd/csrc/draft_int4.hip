@@ -555,8 +555,8 @@ __global__ __launch_bounds__(kThreads, kWaves / 4)
 void draft_stream_kernel(const uint16_t *__restrict__ xin, const FusedArgs a) { draft_stream<MT, UPG, SYM, kWin, false>(xin, a); }
 
 // Many items per workgroup: y summed in LDS.  Added to y item by item, the atomics sit between the weight loads, which
-// complete in order behind them.  us per call, added at once / summed: phi shape, 4 tokens 50.8 / 46.4, 8 tokens 76.2 / 67.4,
-// mixtral, 3 tokens, symmetric 84 / 72, 1 token 43.8 / 39.6.  With one or two short items per workgroup the sums only cost
+// complete in order behind them.  us per call, added at once / summed: phi shape, 4 tokens 48.7 / 43.3, 8 tokens 74.3 / 67.4,
+// mixtral, 3 tokens, symmetric 88.0 / 76.7, 1 token 43.8 / 39.6.  With one or two short items per workgroup the sums only cost
 // (24 experts, H = 3072, I = 640, 7 tokens: 44.8 / 46.0), and so they do with the window of four (qwen3 shape, 8 tokens: 38.2 / 40.1).
 template <int MT, int UPG, bool SYM>
 __global__ __launch_bounds__(kThreads, kWaves / 4)
@@ -604,13 +604,15 @@ void stream_read_kernel(const u32x4 *__restrict__ src, size_t tiles, uint32_t *s
 }
 
 // One workgroup per compute unit: two that share a unit are slower, also where they fit its registers (phi
-// shape, 2 tokens: 37.6 us against 41.6 with two, qwen3 19.2 / 20.6; 4 tokens, held to 128 registers: 52.7 / 60.4).
+// shape, 2 tokens: 37.6 us against 41.6 with two, qwen3 19.2 / 20.6; 4 tokens, held to 128 registers: 52.7 / 60.4; all on the
+// form without sums of y in LDS).
 constexpr int kMaxPerCu = 1;
 
 // Tiles a wave keeps in flight: eight, or four where padding the two parts of an item to whole windows of eight
 // would add more than a fifth to the stream's positions (an empty position is a load that is not in
-// flight).  8 against 4: phi shape (16 and 8 tiles per part and wave), 4 tokens 52.7 / 58.4 us; qwen3 shape (8
-// and 4), 8 tokens 44.7 / 39.9 us.  Windows of 12 and 16 only add padding (58.3 and 59.4 us on the phi shape).
+// flight).  8 against 4: phi shape (16 and 8 tiles per part and wave), 4 tokens 43.3 / 50.4 us (without the sums of y, which the
+// window of four does not have, 48.7 / 50.4), 2 tokens 36.7 / 38.4; qwen3 shape (8 and 4), 8 tokens 41.5 / 37.4, 2 tokens 20.8 /
+// 19.1.  Windows of 12 and 16 only add padding (phi, 4 tokens, when 8 took 52.7 us: 58.3 and 59.4).
 int stream_window(const Shape &s, bool sym)
 {
     const int epl = sym ? 2 : 1;
@@ -676,8 +678,10 @@ void stream_kernel(const Shape &s, bool sym, int n_cu, F go)
 
 // One token through the persistent kernel: from two items per compute unit on, where the launch carries no shared
 // experts and the kernel's two copies of x fit LDS.  us per call, persistent / one workgroup per item: mixtral
-// (896 items) 43.9 / 46.5, the same with I = 9600 (600 items) 34.7 / 37.5, qwen3 with H = 1024, I = 2048 (512
-// items) 23.1 / 24.2; phi (400 items) 26.6 / 24.7.
+// (896 items) 39.8 / 46.4, the same with I = 9600 (600 items) 31.3 / 37.5, I = 8192 (512 items) 27.5 / 31.5, qwen3 with H = 1024,
+// I = 2048 (512 items, no sums of y in LDS) 22.8 / 24.2; phi (400 items, no sums) 26.7 / 24.4.  The sums begin at the same line: with
+// them below it as well, phi 24.1 / 24.4, the same with I = 7168 (448 items) 25.1 / 27.3, dsv2lite without its shared experts
+// (264 items) 19.1 / 18.4.
 bool one_token_streams(const Shape &s, const DraftFusedArgs &d, int n_cu)
 {
     return s.k * (s.I / 32) >= 2 * n_cu && !d.shared_inside && draft_fits(s, 2, d.symmetric != 0);

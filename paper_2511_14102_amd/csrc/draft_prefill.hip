@@ -57,11 +57,12 @@
 //
 // Bound and figures (gate/up and down kernel; first form: two row blocks per wave, operand tiles through
 // registers, offset 128, two multiply-adds per group).  Many tokens per expert: the matrix cores.
-// mixtral shape, 4096 tokens: 2213 and 1790 us, 870 and 1075 TFLOP/s counting both planes of h
+// mixtral shape, 4096 tokens: 2122 and 1672 us, 907 and 1150 TFLOP/s counting both planes of h
 // (first form: 3750 and 2933 us; a large library product reaches 1250 on this part).  phi shape, 512 tokens:
-// 207 and 193 us (406 and 261).  Few tokens per expert: the weight stream.  dsv2lite shape, 333 tokens
-// (31 per expert), with its shared experts in the same launches: 75 and 60 us for 219 and 110 MB (routed experts
-// alone, first form: 99 and 66).
+// 182 and 135 us (406 and 261), the matrix cores busy 29 and 40 % of it and the vector ALU 44 and 34 %: between the two bounds, a
+// wave waits for its turn at an instruction 38 % of its time and for data 19 %.  Few tokens per expert: the weight stream.
+// dsv2lite shape, 333 tokens (31 per expert), with its shared experts in the same launches: 65 and 55 us for 219 and 110 MB (routed
+// experts alone, first form: 99 and 66); matrix cores 23 and 29 %, waiting for data 23 and 28 %.
 #include <hip/hip_runtime.h>
 #include "draft_common.h"
 

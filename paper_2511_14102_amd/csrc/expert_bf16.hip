@@ -200,9 +200,11 @@ __device__ inline void combine_columns(const Plan *__restrict__ plan, const floa
 // kShared (the draft call's shared experts): the operand is hb + hb_lo (two MFMAs per tile), and
 // instead of writing obuf the row's outputs are added to y[token] with fp32 atomics (y already holds
 // the routed experts' sum, itself made of such atomics, so no combine launch is needed).
-// Verify call: the rows leave at agent scope, and the last workgroup of 32 columns to arrive adds them up: 0.5 to 2.3 us of
-// this launch instead of 4.7 to 5.2 us and a gap for one of its own.  That holds a workgroup about a round trip
-// longer, which the loads pay for: a wave's tiles past its last whole batch come in one batch too (one by one, 768 inputs: 28.5 us for 8 tokens x 128 experts x 2048 outputs, now 25.0).
+// Verify call: the rows leave at agent scope, and the last workgroup of 32 columns to arrive adds them up.  That costs this
+// launch 1.8 us (phi shape, 5 tokens: 40.5 / 42.3; 8 tokens x 128 experts 23.3 / 25.0), 3.4 with two shared experts (dsv2lite, 6
+// tokens: 29.6 / 33.0), and saves a launch of 4.0 to 4.8 us and the gap before it.  That holds a workgroup about a round trip
+// longer, which the loads pay for: a wave's tiles past its last whole batch come in one batch too (one by one, 768
+// inputs: 28.5 us for 8 tokens x 128 experts x 2048 outputs, now 25.0).
 template <bool kShared>
 __global__ __launch_bounds__(kWaves * 64)
 void bf16_down_kernel(const Plan *__restrict__ plan, const uint16_t *__restrict__ hb, const uint16_t *__restrict__ hb_lo,
