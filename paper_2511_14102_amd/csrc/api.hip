@@ -369,7 +369,7 @@ static int enqueue_draft(moe_ctx *ctx, const moe_layer_desc *desc, const void *x
     a.spin_limit = ctx->spin_limit;
     a.y = y; a.ids_out = ids_out; a.conf_out = conf_out;
     a.plan = plan; a.shared = shared; a.shared_stride = moe_bf16_expert_bytes(desc);
-    // the workgroups that reduce the router rows (the first min(E, grid) of the launch) must be
+    // the workgroups that reduce the router rows (the first ones of the launch, router_workgroups) must be
     // running while the others wait for them
     const int slots = draft_resident_slots(s, a, ctx->n_cu);
     if (slots == 0) return MOE_ERR_INVALID_ARG;

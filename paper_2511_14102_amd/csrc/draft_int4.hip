@@ -28,7 +28,7 @@
 // 87 (now 83), qwen3 8 tokens 60.6 (now 40).
 //
 // Cross-workgroup protocol (one bounded wait, no cache flushes):
-//   1. router row e is reduced by workgroup e (mod grid), which first clears its share of y
+//   1. router row e is reduced, for a share of the tokens (router_tokens_log2), by one of the first workgroups, which first clears its share of y
 //      with agent-scope stores, waits for their completion, and then publishes the 16-byte
 //      slot {logit, tag = 1} of every token as one 16-byte store (in kReplicas copies);
 //   2. every workgroup polls the slots with single 16-byte agent-scope loads until all are
@@ -38,7 +38,7 @@
 //   4. the workgroup holding the last ticket (everybody has finished polling by then) clears
 //      the tags and the ticket counters at its end, so the workspace is back in its idle state
 //      when the kernel ends.  This also holds when the same launch is replayed from a HIP graph.
-// The wait of step 2 needs the producing workgroups (the first min(E, grid) ones) to be running
+// The wait of step 2 needs the producing workgroups (the first router_workgroups ones; of one token min(E, grid)) to be running
 // while the others poll: the grid never exceeds the number of compute units, and a workgroup
 // fits a compute unit by itself, so on an otherwise idle device all are resident.  If the wait
 // runs out (spin limit), the workgroup skips its items and workgroup 0 reports ids = -1.
@@ -88,31 +88,43 @@ __device__ __forceinline__ void draft_stream(const uint16_t *__restrict__ xin, c
     int32_t *s_rank = reinterpret_cast<int32_t *>(s_dyn + logit_off + (size_t)MT * E * 8);
 
     // ---- 1. router rows owned by this workgroup
-    if ((int)blockIdx.x < E)
-        publish_router_rows<kWaves>(xin, a, blockIdx.x, E < (int)gridDim.x ? E : (int)gridDim.x, s_part);
+    const int lt = router_tokens_log2(T, E, gridDim.x), nprod = router_workgroups(T, E, gridDim.x);
+    if ((int)blockIdx.x < nprod) publish_router_rows<kWaves>(xin, a, blockIdx.x, nprod, lt, s_part);
     if (tid == 0) s_flag = 1;
     if (tid < MOE_MAX_EXPERTS / 64) s_mask[tid] = 0ull;
     if (tid < 2 * MT) s_hsum[tid / MT][tid % MT] = 0.f;
-    __syncthreads();
 
-    // ---- 1b. (while the router result travels) stage x in LDS and sum it per group
-    for (int i = tid; i < T * (H / 8); i += kThreads) {
-        const int t = i / (H / 8), c8 = i % (H / 8);
-        *reinterpret_cast<u32x4 *>(s_x + t * xstride + c8 * 8) = *reinterpret_cast<const u32x4 *>(xin + (size_t)t * H + c8 * 8);
+    // ---- 1b. (while the router result travels) x goes to LDS, and its sum per group: 4 UPG neighbouring threads hold a group.
+    // (Summed from LDS, by threads that found their token and group with divisions, this was 2.4 us of the start of a call with 4 tokens
+    // of the phi shape and 3.5 us with 8 of the qwen3 shape, where the routing's result is there after 3 us.)
+    const int nx = T * (H / 8);                  // pieces of eight values
+    // (whole quotients below 2^19: i + 1/2 over a divisor is further from a whole number than the reciprocal's error)
+    const float per_token = 8.f * __builtin_amdgcn_rcpf((float)H);
+    auto keep = [&](int i, u32x4 v) {
+        float s = ((bf16_lo(v.x) + bf16_hi(v.x)) + (bf16_lo(v.y) + bf16_hi(v.y))) +
+                  ((bf16_lo(v.z) + bf16_hi(v.z)) + (bf16_lo(v.w) + bf16_hi(v.w)));
+        s += wave::move<wave::kSwap1>(s);
+        s += wave::move<wave::kSwap2>(s);
+        if constexpr (UPG > 1) s += wave::move<wave::kHalfMirror>(s);
+        if constexpr (UPG > 2) s += wave::move<wave::kMirror>(s);
+        if (i < nx) {
+            *reinterpret_cast<u32x4 *>(s_x + (i + (int)(((float)i + 0.5f) * per_token)) * 8) = v;      // (rows are 8 elements longer than H)
+            if (i % (4 * UPG) == 0) s_xsum[i / (4 * UPG)] = s;
+        }
+    };
+    constexpr int kBatch = MT < 4 ? MT : 4;
+    for (int i0 = tid; i0 - tid < nx; i0 += kBatch * kThreads) {
+        u32x4 v[kBatch];
+#pragma unroll
+        for (int j = 0; j < kBatch; ++j) v[j] = *reinterpret_cast<const u32x4 *>(xin + (size_t)(i0 + j * kThreads < nx ? i0 + j * kThreads : nx - 1) * 8);
+#pragma unroll
+        for (int j = 0; j < kBatch; ++j)
+            if (i0 - tid + j * kThreads < nx) keep(i0 + j * kThreads, v[j]);
     }
     __syncthreads();
-    for (int i = tid; i < T * G * 16; i += kThreads) {       // 16 threads per (token, group)
-        const int part = i & 15, tg_ = i >> 4;
-        const int t = tg_ / G, gi = tg_ % G;
-        const int per = g / 16;                               // 2, 4 or 8 values each
-        const uint16_t *src = s_x + t * xstride + gi * g + part * per;
-        float v = 0.f;
-        for (int j = 0; j < per; ++j) v += __uint_as_float((uint32_t)src[j] << 16);
-        v = wave::row_sum(v);
-        if (part == 0) s_xsum[t * G + gi] = v;
-    }
 
     const int nslice = I / 32;
+    const float per_slice = __builtin_amdgcn_rcpf((float)nslice), per_workgroup = __builtin_amdgcn_rcpf((float)gridDim.x);     // (while the router result travels; exact as above)
     const int U = H / 32;
     const int r = lane & 15, c = lane >> 4;                  // MFMA lane coordinates
     const UnpackConsts uk = unpack_consts();
@@ -141,7 +153,7 @@ __device__ __forceinline__ void draft_stream(const uint16_t *__restrict__ xin, c
     };
     // where item idx sits (no routing needed) ...
     auto item_pos = [&](Item &it, int idx) {
-        it.u = idx / nslice;
+        it.u = __builtin_amdgcn_readfirstlane((int)(((float)idx + 0.5f) * per_slice));
         it.slice = idx - it.u * nslice;
     };
     auto item_after = [&](Item &it, const Item &prev) {     // ... and its successor, without a division
@@ -240,13 +252,15 @@ __device__ __forceinline__ void draft_stream(const uint16_t *__restrict__ xin, c
     };
 
     // Work split: the items (distinct experts ascending, I / 32 slices each) are dealt evenly, n / G
-    // each, the first n % G workgroups one more.
+    // each, the last n % G workgroups one more (the first ones, which reduce the router rows, begin later: phi, 4 tokens
+    // 45.7 / 45.3 us; H = 384, E = 5, I = 3200, 2 tokens 16.9 / 16.5).
     int it_begin = 0, it_end = 0;
     Item cur, nxt;
     auto split_items = [&](int n_items) {
-        const uint32_t it_q = (uint32_t)n_items / gridDim.x, it_r = (uint32_t)n_items - it_q * gridDim.x;
-        it_begin = (int)(blockIdx.x * it_q + (blockIdx.x < it_r ? blockIdx.x : it_r));
-        it_end = it_begin + (int)it_q + (blockIdx.x < it_r ? 1 : 0);
+        const uint32_t it_q = (uint32_t)__builtin_amdgcn_readfirstlane((int)(((float)n_items + 0.5f) * per_workgroup)), it_r = (uint32_t)n_items - it_q * gridDim.x;
+        const uint32_t fewer = gridDim.x - it_r;              // workgroups without one more
+        it_begin = (int)(blockIdx.x * it_q + (blockIdx.x > fewer ? blockIdx.x - fewer : 0u));
+        it_end = it_begin + (int)it_q + (blockIdx.x >= fewer ? 1 : 0);
         item_pos(cur, it_begin);
         if (it_begin + 1 < it_end) item_after(nxt, cur);
         else nxt = cur;

@@ -64,7 +64,7 @@ void draft_fused_kernel(const uint16_t *__restrict__ xin, const FusedArgs a)
     const int nprod = E < n_routed ? E : n_routed;
     const int b = blockIdx.x;
     const bool shared = SHARED && b >= nprod && b < nprod + n_sh;
-    if (b < nprod) publish_router_rows<kWaves>(xin, a, b, nprod, s_part);
+    if (b < nprod) publish_router_rows<kWaves>(xin, a, b, nprod, 0, s_part);
     uint32_t ticket = 0xffffffffu, ticket2 = 0xffffffffu;
     auto first_ticket = [&]() { if (lane == 0) ticket = draw_ticket(a.tickets + b % kTicketGroups); };
     auto stage_x = [&]() {

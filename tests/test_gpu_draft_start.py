@@ -115,6 +115,26 @@ def test_stream_windows_of_eight(g):
     ctx.close()
 
 
+@pytest.mark.parametrize("H,E,T,g", [(192, 16, 8, 32), (3136, 60, 7, 64), (2176, 100, 5, 128), (1088, 200, 3, 32), (64, 256, 8, 32), (4224, 5, 2, 128)])
+def test_router_rows_shared_out_by_tokens(H, E, T, g):
+    """A router row's tokens in one workgroup (E = 256), in two with a ragged last one (100 and 5 tokens), in four and in one
+    each; x in one round of a workgroup's loads and in several, the last one ragged."""
+    cfg = LayerConfig(80, "rows%d" % E, H, E, 256, min(8, E), g, 0, 1)
+    ctx = B.Context(0)
+    L = build_layer(cfg)
+    A = oracle_arrays(L)
+    D = DeviceLayer(ctx, cfg, L, max_tokens=T, verify=False)
+    x = tokens_with_clear_routing(cfg, A, T, step=5)
+    ref = oracle_draft(A, x)
+    say("router rows H", H, "E", E, "T", T)
+    for again in range(2):                                 # (the second call finds the exchange slots as the first left them)
+        r = D.draft(x.cuda())
+        torch.cuda.synchronize()
+        assert np.array_equal(to_np(r["ids"]), ref["ids"])
+        assert rel_err(to_np(r["y"]), ref["y"]) <= TOL_DRAFT
+    ctx.close()
+
+
 def test_shared_experts_on_the_line_run_inside():
     """As many 16-row items per compute unit as H has 256s (1024 on 256 units): the call's own launch runs the
     shared experts, no launch of the bf16 kernels is made."""
