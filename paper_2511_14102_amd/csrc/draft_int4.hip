@@ -691,14 +691,15 @@ void stream_kernel(const Shape &s, bool sym, int n_cu, F go)
 }
 
 // One token through the persistent kernel: from two items per compute unit on, where the launch carries no shared
-// experts and the kernel's two copies of x fit LDS.  us per call, persistent / one workgroup per item: mixtral
-// (896 items) 39.8 / 46.4, the same with I = 9600 (600 items) 31.3 / 37.5, I = 8192 (512 items) 27.5 / 31.5, qwen3 with H = 1024,
-// I = 2048 (512 items, no sums of y in LDS) 22.8 / 24.2; phi (400 items, no sums) 26.7 / 24.4.  The sums begin at the same line: with
-// them below it as well, phi 24.1 / 24.4, the same with I = 7168 (448 items) 25.1 / 27.3, dsv2lite without its shared experts
-// (264 items) 19.1 / 18.4.
+// experts and the kernel's two copies of x fit LDS, if it sums y in LDS (long rows); without the sums only where pairs of items
+// (draft_slice.hip) make between one and one and a half rounds of long workgroups.  us per call, persistent / pairs (items):
+// H = 4096 (with the sums): 512 27.4 / 27.8, 600 30.9 / 40.9; H = 2304, 576 27.4 / 33.0; H = 2048: 512 23.9 / 20.1, 640 27.7 / 29.5,
+// 768 30.2 / 30.1, 1024 37.2 / 33.4; H = 1024: 512 21.9 / 17.2, 640 25.7 / 25.2, 1024 34.6 / 28.0; H = 320, 1870 56.2 / 39.9.
 bool one_token_streams(const Shape &s, const DraftFusedArgs &d, int n_cu)
 {
-    return s.k * (s.I / 32) >= 2 * n_cu && !d.shared_inside && draft_fits(s, 2, d.symmetric != 0);
+    const int items = s.k * (s.I / 32);
+    if (items < 2 * n_cu || d.shared_inside || !draft_fits(s, 2, d.symmetric != 0)) return false;
+    return s.H > 2048 || sum_lds(s, 2, d.symmetric != 0, n_cu) > 0 || (s.H > 1024 && items > 2 * n_cu && items < 3 * n_cu);
 }
 
 }  // namespace
@@ -708,11 +709,10 @@ bool one_token_streams(const Shape &s, const DraftFusedArgs &d, int n_cu)
 // a grid of as many workgroups as the device holds at once.
 int draft_resident_slots(const Shape &s, const DraftFusedArgs &d, int n_cu)
 {
-    const int maxu = s.E < s.T * s.k ? s.E : s.T * s.k;
-    const long items = (long)maxu * (s.I / 32);
     if (s.T == 1 && !one_token_streams(s, d, n_cu)) {
-        const long need = s.E < items ? s.E : items;
-        const int slots = draft_one_token_resident(s, d, n_cu);
+        long routed = 0;
+        const int slots = draft_one_token_resident(s, d, n_cu, &routed);
+        const long need = s.E < routed ? s.E : routed;
         return need <= slots ? slots : 0;
     }
     int per = 0;
@@ -722,7 +722,7 @@ int draft_resident_slots(const Shape &s, const DraftFusedArgs &d, int n_cu)
 
 void launch_draft_fused(const Shape &s, const DraftFusedArgs &d, int n_cu, int slots, hipStream_t st)
 {
-    if (s.T == 1 && !one_token_streams(s, d, n_cu)) { launch_draft_one_token(s, d, st); return; }
+    if (s.T == 1 && !one_token_streams(s, d, n_cu)) { launch_draft_one_token(s, d, n_cu, st); return; }
     const FusedArgs a = fused_args(s, d);
     // never more workgroups than there can be items
     const int maxu = s.E < s.T * s.k ? s.E : s.T * s.k;

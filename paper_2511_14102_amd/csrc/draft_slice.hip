@@ -9,13 +9,11 @@
 // cross-workgroup protocol of the router exchange in draft_int4.hip (the same here).
 //
 // Work decomposition ("slice fusion").  A work item is (expert, slice of 32 intermediate
-// rows): its workgroup computes the 32 gate and 32 up pre-activations (K = H split over the 8
-// waves by groups), h = silu(gate) * up, and immediately multiplies h into the 32 matching
-// columns of the down projection for all H outputs, adding the partial outputs into y with
-// fp32 atomics.  With one token a call has k I / 32 items (400 on the phi shape, about one and a half per
-// compute unit): up to two workgroups share a unit.  Below two items per unit a persistent launch, whose
-// stream would be one or two items long, has nothing to overlap (phi 24.4 us here, 26.6 persistent; qwen3 14.7 /
-// 16.2); from there on it is the faster one.
+// rows): eight waves compute the 32 gate and 32 up pre-activations (K = H split over them
+// by groups), h = silu(gate) * up, and immediately multiply h into the 32 matching
+// columns of the down projection for all H outputs, which are added into y with
+// fp32 atomics.  With one token a call has k I / 32 items (400 on the phi shape); a workgroup has one of them, or two
+// (slice_pairs).  Long rows and two items per unit and more run the persistent kernel (one_token_streams).
 //
 // Bound: a chain of round trips to memory up to the first weight load (x and router rows, exchange, selection:
 // about 3 us), then the weight stream (84 MB in 17 us on the phi shape) with one or two items per unit.
@@ -26,32 +24,36 @@ namespace moespeq {
 namespace {
 
 // UPG: 32-code units per group (g / 32); SYM: symmetric format (scale blobs, z = 8); SHARED: the shared
-// experts run in this launch (without them the kernel is smaller: its start is a chain of code that runs once)
-template <int UPG, bool SYM, bool SHARED>
-__global__ __launch_bounds__(kThreads, 4)            // 4 waves per SIMD, two workgroups per compute unit
-void draft_fused_kernel(const uint16_t *__restrict__ xin, const FusedArgs a)
+// experts run in this launch (without them the kernel is smaller: its start is a chain of code that runs once); ITEMS: one item
+// per workgroup, or two neighbours (of one expert), eight waves each, whose outputs are added up in LDS
+template <int UPG, bool SYM, bool SHARED, int ITEMS>
+__device__ __forceinline__ void draft_one_token(const uint16_t *__restrict__ xin, const FusedArgs &a)
 {
     // tiles a wave keeps in flight (rolling window): two workgroups per compute unit leave 128 VGPRs per
     // wave, and with an entry per tile (g = 32) a window of 8 spills
     constexpr int kWin = UPG == 1 ? 6 : 8;
     constexpr int kSzWin = kWin / UPG;
-    __shared__ double s_part[kWaves];
+    constexpr int kAll = kThreads * ITEMS;
+    __shared__ double s_part[kWaves * ITEMS];
     __shared__ int32_t s_ids[MOE_MAX_TOPK];
     __shared__ float s_w[MOE_MAX_TOPK], s_conf[MOE_MAX_TOPK];
     __shared__ int32_t s_ok;
-    __shared__ float s_red[kWaves][64];              // partial gate/up sums
-    __shared__ __attribute__((aligned(16))) uint16_t s_h[kWaves][2][32];    // h and its remainder, each wave's own copy
-    extern __shared__ __attribute__((aligned(16))) unsigned char s_dyn[];   // x, its group sums, logits, ranks
+    __shared__ float s_red[ITEMS][kWaves][64];       // partial gate/up sums
+    __shared__ __attribute__((aligned(16))) uint16_t s_h[ITEMS][kWaves][2][32];    // h and its remainder, each wave's own copy
+    extern __shared__ __attribute__((aligned(16))) unsigned char s_dyn[];   // x, its group sums, logits, ranks, two items' outputs
 
     const int tid = threadIdx.x;
     const int lane = tid & 63;
-    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    // eight waves to an item: `wave` of them, `half`: which item
+    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6) % kWaves, half = ITEMS > 1 ? __builtin_amdgcn_readfirstlane(tid >> 9) : 0;
+    const bool wave0 = __builtin_amdgcn_readfirstlane(tid >> 6) == 0;
     const int H = a.H, E = a.E, I = a.I, k = a.k;
     const int G = H / (32 * UPG), U = H / 32, nslice = I / 32;
     uint16_t *s_x = reinterpret_cast<uint16_t *>(s_dyn);
     double *s_logit = reinterpret_cast<double *>(s_dyn + (size_t)H * 2);
     int32_t *s_rank = reinterpret_cast<int32_t *>(s_logit + E);
     float *s_xsum = reinterpret_cast<float *>(s_rank + E);
+    float *s_y = s_xsum + G;                                 // [ITEMS][H], two items only
     const int r = lane & 15, c = lane >> 4;                  // MFMA lane coordinates
 
     // this thread's first piece of x, on its way while the router rows are reduced
@@ -60,16 +62,16 @@ void draft_fused_kernel(const uint16_t *__restrict__ xin, const FusedArgs a)
     // ---- 1. which work item.  The first workgroups reduce the router rows; workgroups are dispatched in order, so
     // they are running before any other waits for them.  Behind them the shared experts' items, which start at
     // once, then the other routed items, which wait for the routing.
-    const int n_sh = SHARED ? a.S * (I / 16) : 0, n_routed = (int)gridDim.x - n_sh;
+    const int n_sh = SHARED ? a.S * (I / 16) / ITEMS : 0, n_routed = (int)gridDim.x - n_sh;
     const int nprod = E < n_routed ? E : n_routed;
     const int b = blockIdx.x;
     const bool shared = SHARED && b >= nprod && b < nprod + n_sh;
-    if (b < nprod) publish_router_rows<kWaves>(xin, a, b, nprod, 0, s_part);
+    if (b < nprod) publish_router_rows<kWaves * ITEMS>(xin, a, b, nprod, 0, s_part);
     uint32_t ticket = 0xffffffffu, ticket2 = 0xffffffffu;
     auto first_ticket = [&]() { if (lane == 0) ticket = draw_ticket(a.tickets + b % kTicketGroups); };
     auto stage_x = [&]() {
         if (tid < H / 8) *reinterpret_cast<u32x4 *>(s_x + tid * 8) = xr;
-        for (int i = tid + kThreads; i < H / 8; i += kThreads)
+        for (int i = tid + kAll; i < H / 8; i += kAll)
             *reinterpret_cast<u32x4 *>(s_x + i * 8) = *reinterpret_cast<const u32x4 *>(xin + i * 8);
         __syncthreads();
     };
@@ -85,12 +87,24 @@ void draft_fused_kernel(const uint16_t *__restrict__ xin, const FusedArgs a)
         if (__any(ticket2 == ticket_groups(gridDim.x) - 1)) reset_exchange(a, lane, 64);
     };
 
+    // An output of an item: added to y, or kept until both items of the workgroup have theirs
+    auto add_output = [&](int at, float v) {
+        if constexpr (ITEMS > 1) s_y[half * H + at] = v;
+        else __hip_atomic_fetch_add(&a.y[at], v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    };
+    auto add_both = [&]() {
+        if constexpr (ITEMS > 1) {
+            __syncthreads();
+            for (int i = tid; i < H; i += kAll) __hip_atomic_fetch_add(&a.y[i], s_y[i] + s_y[H + i], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        }
+    };
+
     if constexpr (SHARED) if (shared) {
         // ---- 2. an item of a shared expert: 16 intermediate rows (a gate and an up tile of 16 x 32 bf16 per
         // k-step), then their 16 columns of the down projection: half of a 16 x 32 tile, so a load takes the
         // halves of two tiles, and one MFMA multiplies both (the A rows of one tile's half are zero in the
         // other's k positions).  The stream and its window are the routed items'.
-        const int sh = (b - nprod) / (I / 16), row16 = (b - nprod) % (I / 16);
+        const int nth = (b - nprod) * ITEMS + half, sh = nth / (I / 16), row16 = nth % (I / 16);
         const char *blob = a.shared + (size_t)sh * a.shared_stride;
         const char *gate = blob + (size_t)row16 * U * 1024, *up = gate + (size_t)I * H * 2;
         const uint32_t rstep = (uint32_t)(I / 32) * 1024;            // from one output row tile to the next
@@ -132,8 +146,8 @@ void draft_fused_kernel(const uint16_t *__restrict__ xin, const FusedArgs a)
             }
         }
         // all 16 A rows are the token: every lane group holds the same sums
-        if (c < 2) s_red[wave][lane] = c == 0 ? ag[0] : au[0];
-        if (wave == 0) {
+        if (c < 2) s_red[half][wave][lane] = c == 0 ? ag[0] : au[0];
+        if (wave0) {
             // the outputs may be added once y has been cleared, which every router workgroup does before it publishes
             const bool ok = poll_and_select(a, 0, nullptr, nullptr, nullptr, nullptr);
             first_ticket();
@@ -144,23 +158,23 @@ void draft_fused_kernel(const uint16_t *__restrict__ xin, const FusedArgs a)
         {
             float v = 0.f;
 #pragma unroll
-            for (int w = 0; w < kWaves; ++w) v += s_red[w][lane & 31];
+            for (int w = 0; w < kWaves; ++w) v += s_red[half][w][lane & 31];
             const float u = __shfl_xor(v, 16);
             const float h = v / (1.f + expf(-v)) * u;
             const uint16_t hi = f32_to_bf16_rne(h);
             if (lane < 16) {
-                s_h[wave][0][lane] = hi;
-                s_h[wave][1][lane] = f32_to_bf16_rne(h - __uint_as_float((uint32_t)hi << 16));
+                s_h[half][wave][0][lane] = hi;
+                s_h[half][wave][1][lane] = f32_to_bf16_rne(h - __uint_as_float((uint32_t)hi << 16));
             }
             __builtin_amdgcn_wave_barrier();
         }
-        if (wave == 0) second_ticket();
+        if (wave0) second_ticket();
         if (s_ok) {
             // A rows 4 q, 4 q + 1 hold h and its remainder for the tile whose outputs lane group q gets:
             // groups 0, 2 from the halves of a pair's first load, 1, 3 from its second
             u32x4 ha[2];
             {
-                const u32x4 hv = *reinterpret_cast<const u32x4 *>(&s_h[wave][r & 1][(c & 1) * 8]);
+                const u32x4 hv = *reinterpret_cast<const u32x4 *>(&s_h[half][wave][r & 1][(c & 1) * 8]);
 #pragma unroll
                 for (int j = 0; j < 2; ++j) {
                     const bool on = (r & 3) < 2 && ((r >> 2) & 1) == j && (r >> 3) == (c >> 1);
@@ -179,21 +193,21 @@ void draft_fused_kernel(const uint16_t *__restrict__ xin, const FusedArgs a)
                         __builtin_amdgcn_sched_barrier(0);
                     }
                     if (d0 + i < nd)
-                        __hip_atomic_fetch_add(&a.y[(q0 + (d0 + i) / 2) * 64 + lane], o[0] + o[1], __ATOMIC_RELAXED,
-                                               __HIP_MEMORY_SCOPE_AGENT);
+                        add_output((q0 + (d0 + i) / 2) * 64 + lane, o[0] + o[1]);
                 }
             };
             int d0 = 0;
             for (; d0 + kWin < nd; d0 += kWin) down_pass(d0, std::true_type{});
             down_pass(d0, std::false_type{});
+            add_both();
         }
-        if (wave == 0) reset_if_last();
+        if (wave0) reset_if_last();
         return;
     }
 
     // ---- 3. a routed item: slice `slice` of the u-th ranked expert.  What does not depend on the expert is computed
     // while the router result travels.
-    const int item = b < nprod ? b : b - n_sh;
+    const int item = (b < nprod ? b : b - n_sh) * ITEMS + half;
     const int u = item / nslice, slice = item % nslice;
     const UnpackConsts uk = unpack_consts();
     const uint32_t lane_off = (uint32_t)lane * 16u;
@@ -221,7 +235,7 @@ void draft_fused_kernel(const uint16_t *__restrict__ xin, const FusedArgs a)
 
     stage_x();
     // sums of x per group: 16 threads each
-    for (int i = tid; i < G * 16; i += kThreads) {
+    for (int i = tid; i < G * 16; i += kAll) {
         constexpr int kPer = 2 * UPG;
         const uint16_t *src = s_x + i * kPer;
         float v = 0.f;
@@ -232,7 +246,7 @@ void draft_fused_kernel(const uint16_t *__restrict__ xin, const FusedArgs a)
     }
 
     // ---- 4. wave 0 polls the slots (bounded) and selects the top-k
-    if (wave == 0) {
+    if (wave0) {
         const bool got = poll_and_select(a, 0, s_logit, s_rank, s_ids, nullptr);
         if (!got) give_up();                     // the call fails, and says so in the workspace
         if (lane == 0) s_ok = got;
@@ -270,9 +284,9 @@ void draft_fused_kernel(const uint16_t *__restrict__ xin, const FusedArgs a)
         }
         // the ticket goes out behind the first loads: they would wait for it (loads and returning atomics complete in
         // order, and hundreds of tickets are drawn at about the same time)
-        if (wave == 0) first_ticket();
+        if (wave0) first_ticket();
         // the softmax, off the path to the first weight load
-        if (wave == 0) finish_softmax(a, s_logit, s_rank, s_conf, s_w);
+        if (wave0) finish_softmax(a, s_logit, s_rank, s_conf, s_w);
 
         // ---- 6. gate and up
         const uint16_t *xrow = s_x + c * 8;
@@ -328,8 +342,8 @@ void draft_fused_kernel(const uint16_t *__restrict__ xin, const FusedArgs a)
         // the window now holds this wave's first down tiles; their entries follow
 #pragma unroll
         for (int i = 0; i < kWin; ++i) dpe[i] = entry(dent_run, i);
-        s_red[wave][lane] = tot;
-        if (wave == 0) second_ticket();
+        s_red[half][wave][lane] = tot;
+        if (wave0) second_ticket();
         __syncthreads();
 
         // ---- 7. h of the slice's 32 rows, in every wave: lanes 0-31 hold the gate rows, 32-63 the up rows
@@ -337,12 +351,12 @@ void draft_fused_kernel(const uint16_t *__restrict__ xin, const FusedArgs a)
         {
             float v = 0.f;
 #pragma unroll
-            for (int w = 0; w < kWaves; ++w) v += s_red[w][lane];
+            for (int w = 0; w < kWaves; ++w) v += s_red[half][w][lane];
             const float up = __shfl_xor(v, 32);
             const float h = v / (1.f + expf(-v)) * up;
             const uint16_t hi = f32_to_bf16_rne(h);
             const uint16_t lo = f32_to_bf16_rne(h - __uint_as_float((uint32_t)hi << 16));
-            if (lane < 32) { s_h[wave][0][lane] = hi; s_h[wave][1][lane] = lo; }
+            if (lane < 32) { s_h[half][wave][0][lane] = hi; s_h[half][wave][1][lane] = lo; }
             const float hs = __uint_as_float((uint32_t)hi << 16) + __uint_as_float((uint32_t)lo << 16);   // the represented h
             hsum = wave::sum(lane < 32 ? hs : 0.f);
             __builtin_amdgcn_wave_barrier();
@@ -355,7 +369,7 @@ void draft_fused_kernel(const uint16_t *__restrict__ xin, const FusedArgs a)
         // in one register pair, one 64-lane atomic per tile.
         u32x4 ha[4];
         {
-            const u32x4 hv = *reinterpret_cast<const u32x4 *>(&s_h[wave][r & 1][c * 8]);
+            const u32x4 hv = *reinterpret_cast<const u32x4 *>(&s_h[half][wave][r & 1][c * 8]);
 #pragma unroll
             for (int bl = 0; bl < 4; ++bl) {
                 const bool on = (r & 3) < 2 && (r >> 2) == bl;
@@ -386,20 +400,21 @@ void draft_fused_kernel(const uint16_t *__restrict__ xin, const FusedArgs a)
                     o = mfma(ha[2], b2, o);
                     o = mfma(ha[3], b3, o);
                     const float val = sc * ((o[0] + o[1]) - zp * hsum) * rw;
-                    __hip_atomic_fetch_add(&a.y[rt * 64 + lane], val, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+                    add_output(rt * 64 + lane, val);
                 }
             }
         };
         int j0 = 0;
         for (; j0 + kWin < ndw; j0 += kWin) down_pass(j0, std::true_type{});
         down_pass(j0, std::false_type{});
-    } else if (wave == 0) {
+        add_both();
+    } else if (wave0) {
         first_ticket();
         second_ticket();
     }
 
     // ---- 9. workgroup 0 reports the routing
-    if (wave == 0) reset_if_last();
+    if (wave0) reset_if_last();
     if (b != 0) return;
     if (!SHARED && a.S > 0) write_shared_plan(a);
     if (!ok) { if (tid < k) { a.ids_out[tid] = -1; if (a.conf_out) a.conf_out[tid] = 0.f; } return; }
@@ -409,21 +424,47 @@ void draft_fused_kernel(const uint16_t *__restrict__ xin, const FusedArgs a)
     }
 }
 
-// dynamic LDS: x, the fp64 logits and the ranks, the sums of x per group
-size_t slice_dynamic_lds(int H, int g, int E) { return (size_t)H * 2 + (size_t)E * 12 + (size_t)(H / g) * 4; }
+// 4 waves per SIMD: two workgroups of one item per compute unit, or one of two
+template <int UPG, bool SYM, bool SHARED>
+__global__ __launch_bounds__(kThreads, 4)
+void draft_fused_kernel(const uint16_t *__restrict__ xin, const FusedArgs a) { draft_one_token<UPG, SYM, SHARED, 1>(xin, a); }
+template <int UPG, bool SYM, bool SHARED>
+__global__ __launch_bounds__(2 * kThreads, 4)
+void draft_pair_kernel(const uint16_t *__restrict__ xin, const FusedArgs a) { draft_one_token<UPG, SYM, SHARED, 2>(xin, a); }
+
+// dynamic LDS: x, the fp64 logits and the ranks, the sums of x per group, the outputs of two items
+size_t slice_dynamic_lds(int H, int g, int E, int items) { return (size_t)H * 2 + (size_t)E * 12 + (size_t)(H / g) * 4 + (items > 1 ? (size_t)H * 8 : 0); }
+
+// Items per workgroup.  Every item adds to all of y, and fp32 additions to one address follow each other at 25 ns (400 workgroups
+// adding to the same 4096 floats take 13.8 us, to four copies of them 7.9, without adding 3.8), so that n items cannot
+// end less than n x 25 ns after the first one, and beyond 256 items some units have two, whose second one also starts late: its
+// loads wait until the first one's have returned.  Two items in one workgroup halve the chain and give every unit the same.
+// Not below one item per unit, where pairs leave units empty, and with long items not beyond two per unit, where a second
+// round of workgroups costs more than the chain.  us per call, single / paired (items):
+//   H = 4096: 224 18.5 / 19.6, 256 20.0 / 20.0, 320 23.7 / 21.5, 384 25.7 / 24.7, 576 38.9 / 47.0, 768 44.4 / 49.8
+//   H = 2048: 192 14.6 / 17.1, 224 14.3 / 15.1, 240 15.0 / 15.2, 320 18.8 / 16.4, 504 24.4 / 20.6, 624 30.9 / 28.7, 768 35.6 / 28.9
+//   H = 512: 240 13.0 / 12.6, 504 21.1 / 15.8, 768 26.0 / 17.9
+bool slice_pairs(const Shape &s, const DraftFusedArgs &d, int n_cu)
+{
+    const int items = s.k * (s.I / 32) + (d.shared_inside ? s.S * (s.I / 16) : 0), routed = s.k * (s.I / 32) / 2;
+    // (a unit holds one workgroup of two items: those that reduce the router rows have to be running together)
+    return items >= n_cu && (items <= 2 * n_cu || s.H <= 2048) && (s.E <= n_cu || routed <= n_cu) &&
+           slice_dynamic_lds(s.H, s.g, s.E, 2) <= (size_t)(160 - 20) * 1024;
+}
 
 template <bool SYM, bool SHARED, typename F>
-void slice_kernel(int g, F go)
+void slice_kernel(int g, bool pairs, F go)           // go(kernel, items per workgroup)
 {
-    if (g == 32) go(draft_fused_kernel<1, SYM, SHARED>);
-    else if (g == 64) go(draft_fused_kernel<2, SYM, SHARED>);
-    else go(draft_fused_kernel<4, SYM, SHARED>);
+    if (g == 32) pairs ? go(draft_pair_kernel<1, SYM, SHARED>, 2) : go(draft_fused_kernel<1, SYM, SHARED>, 1);
+    else if (g == 64) pairs ? go(draft_pair_kernel<2, SYM, SHARED>, 2) : go(draft_fused_kernel<2, SYM, SHARED>, 1);
+    else pairs ? go(draft_pair_kernel<4, SYM, SHARED>, 2) : go(draft_fused_kernel<4, SYM, SHARED>, 1);
 }
 template <typename F>
-void slice_kernel(const Shape &s, const DraftFusedArgs &d, F go)
+void slice_kernel(const Shape &s, const DraftFusedArgs &d, int n_cu, F go)
 {
-    if (d.symmetric) { if (d.shared_inside) slice_kernel<true, true>(s.g, go); else slice_kernel<true, false>(s.g, go); }
-    else { if (d.shared_inside) slice_kernel<false, true>(s.g, go); else slice_kernel<false, false>(s.g, go); }
+    const bool pairs = slice_pairs(s, d, n_cu);
+    if (d.symmetric) { if (d.shared_inside) slice_kernel<true, true>(s.g, pairs, go); else slice_kernel<true, false>(s.g, pairs, go); }
+    else { if (d.shared_inside) slice_kernel<false, true>(s.g, pairs, go); else slice_kernel<false, false>(s.g, pairs, go); }
 }
 
 }  // namespace
@@ -445,28 +486,31 @@ bool draft_shared_inside(const Shape &s, int n_cu)
     return s.T == 1 && s.S > 0 && (items <= 3L * n_cu || items * 256 <= (long)n_cu * s.H);
 }
 
-// one token: router inside the launch, one workgroup per (selected expert, slice) and per 16 rows of
+// one token: router inside the launch, a work item per (selected expert, slice) and per 16 rows of
 // every shared expert
-void launch_draft_one_token(const Shape &s, const DraftFusedArgs &d, hipStream_t st)
+void launch_draft_one_token(const Shape &s, const DraftFusedArgs &d, int n_cu, hipStream_t st)
 {
     const FusedArgs a = fused_args(s, d);
-    const int grid = a.k * (a.I / 32) + (d.shared_inside ? a.S * (a.I / 16) : 0);
-    const size_t lds = slice_dynamic_lds(a.H, a.g, a.E);
-    slice_kernel(s, d, [&](auto kernel) {
-        launch_with_lds(kernel, dim3(grid), dim3(kThreads), lds, st, (const uint16_t *)d.x, a);
+    slice_kernel(s, d, n_cu, [&](auto kernel, int items) {
+        const int grid = (a.k * (a.I / 32) + (d.shared_inside ? a.S * (a.I / 16) : 0)) / items;      // (I is a multiple of 64: even counts)
+        launch_with_lds(kernel, dim3(grid), dim3(kThreads * items), slice_dynamic_lds(a.H, a.g, a.E, items), st, (const uint16_t *)d.x, a);
     });
 }
 
-int draft_one_token_resident(const Shape &s, const DraftFusedArgs &d, int n_cu)
+// workgroups the device holds at once, and how many of them the call's routed items make
+int draft_one_token_resident(const Shape &s, const DraftFusedArgs &d, int n_cu, long *routed)
 {
     int per = 0;
-    slice_kernel(s, d, [&](auto kernel) { per = resident_per_cu(kernel, kThreads, slice_dynamic_lds(s.H, s.g, s.E)); });
+    slice_kernel(s, d, n_cu, [&](auto kernel, int items) {
+        per = resident_per_cu(kernel, kThreads * items, slice_dynamic_lds(s.H, s.g, s.E, items));
+        *routed = (long)s.k * (s.I / 32) / items;
+    });
     return per * n_cu;
 }
 
 bool draft_one_token_fits(const Shape &s)
 {
-    return slice_dynamic_lds(s.H, s.g, s.E) <= (size_t)(160 - 20) * 1024;
+    return slice_dynamic_lds(s.H, s.g, s.E, 1) <= (size_t)(160 - 20) * 1024;
 }
 
 }  // namespace moespeq

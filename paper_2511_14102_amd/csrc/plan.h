@@ -124,10 +124,10 @@ bool draft_fits(const Shape &s, int tokens, bool symmetric);
 int draft_resident_slots(const Shape &s, const DraftFusedArgs &a, int n_cu);
 // draft_slice.hip: the call with ONE token (router inside the launch), one workgroup per
 // (expert, slice) work item
-void launch_draft_one_token(const Shape &s, const DraftFusedArgs &a, hipStream_t st);
+void launch_draft_one_token(const Shape &s, const DraftFusedArgs &a, int n_cu, hipStream_t st);
 bool draft_one_token_fits(const Shape &s);
 bool draft_shared_inside(const Shape &s, int n_cu);      // whether the call's launch runs the shared experts too
-int draft_one_token_resident(const Shape &s, const DraftFusedArgs &a, int n_cu);   // workgroups resident at once
+int draft_one_token_resident(const Shape &s, const DraftFusedArgs &a, int n_cu, long *routed);   // workgroups resident at once; its routed ones
 void launch_zero(void *p, size_t bytes, hipStream_t st);
 void launch_stream_read(const void *src, size_t bytes, int workgroups, void *sink, hipStream_t st);
 

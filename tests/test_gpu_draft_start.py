@@ -115,6 +115,30 @@ def test_stream_windows_of_eight(g):
     ctx.close()
 
 
+@pytest.mark.parametrize("H,I,E,k,g,S", [(64, 4096, 3, 2, 32, 0), (320, 2048, 4, 4, 64, 0), (2112, 2752, 5, 3, 64, 0), (1088, 4160, 6, 4, 32, 0),
+                                         (512, 2048, 4, 1, 64, 2), (2304, 1024, 8, 8, 128, 2), (192, 8192, 3, 2, 64, 2)])
+def test_one_token_with_pairs_of_items(H, I, E, k, g, S):
+    """Calls of one token with 256 work items and more, which run two items per workgroup: fewer row tiles or groups than waves, ragged
+    shares of both, exactly 256 and 512 items, more than two per unit with short rows, and shared experts beside the routed ones."""
+    cfg = LayerConfig(81, "pair%d" % H, H, E, I, k, g, S, 1)
+    ctx = B.Context(0)
+    for symmetric in (False, True):
+        if symmetric and B.int4_expert_scale_bytes(B.LayerDesc.from_config(cfg)) == 0:
+            continue
+        L = synth.make_layer(cfg, 0, symmetric=symmetric)
+        A = oracle_arrays(L)
+        D = DeviceLayer(ctx, cfg, L, max_tokens=1, verify=False, symmetric=symmetric)
+        x = tokens_with_clear_routing(cfg, A, 2, step=6)
+        ref = oracle_draft(A, x)
+        for t in (0, 1, 0):
+            say("pairs H", H, "I", I, "S", S, "symmetric" if symmetric else "", "token", t)
+            r = D.draft(x[t:t + 1].cuda())
+            torch.cuda.synchronize()
+            assert np.array_equal(to_np(r["ids"]), ref["ids"][t:t + 1])
+            assert rel_err(to_np(r["y"]), ref["y"][t:t + 1]) <= TOL_DRAFT
+    ctx.close()
+
+
 @pytest.mark.parametrize("H,E,T,g", [(192, 16, 8, 32), (3136, 60, 7, 64), (2176, 100, 5, 128), (1088, 200, 3, 32), (64, 256, 8, 32), (4224, 5, 2, 128)])
 def test_router_rows_shared_out_by_tokens(H, E, T, g):
     """A router row's tokens in one workgroup (E = 256), in two with a ragged last one (100 and 5 tokens), in four and in one
