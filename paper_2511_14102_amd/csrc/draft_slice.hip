@@ -469,21 +469,21 @@ void slice_kernel(const Shape &s, const DraftFusedArgs &d, int n_cu, F go)
 
 }  // namespace
 
-// Whether a one-token call runs its shared experts in its own launch: up to three 16-row items per compute unit, or
-// one per 256 of H where that is more.  Beyond, items are many and short, a workgroup's start costs more
-// than two launches, and the bf16 kernels take them.  us per call inside / in their own launches (16 experts, k = 4,
-// 256 units; H of 256 to 4096, one, two and four shared experts were measured):
-//   items per unit  H = 256      H = 1024     H = 2048      H = 4096
-//   1.4 (S = 4)     19.4 / 21.4  22.8 / 25.6  28.8 / 32.9   37.4 / 47.0
-//   2.8 (S = 2)     40.0 / 44.0  45.6 / 50.0  54.0 / 61.9   76.8 / 89.4
-//   2.8 (S = 4)     31.3 / 31.3  37.0 / 38.5  45.2 / 50.8   64.8 / 75.5
-//   4   (S = 2)     56.3 / 52.4  62.0 / 61.2  73.9 / 77.7   103.8 / 120.5
-//   5.5 (S = 4)     57.5 / 46.7  66.0 / 58.2  77.4 / 81.2   122.1 / 131.6
-//   8   (S = 4)     81.7 / 56.0  87.7 / 74.1  102.7 / 107.5 166.0 / 183.6
+// Whether a one-token call runs its shared experts in its own launch: up to seven 16-row items per compute unit, or
+// one per 128 of H where that is more.  Beyond, items are many and short, a workgroup's start costs more
+// than two launches, and the bf16 kernels take them.  us per call inside / in their own launches (256 units; with pairs of
+// items inside, slice_pairs; with single ones, whose chain of additions is twice as long, the line lay at three per unit, or one per 256):
+//   items per unit   H = 256       H = 512       H = 1024      H = 1536      H = 2048
+//   4   (S = 4)      28.1 / 29.8                 35.1 / 35.1
+//   5.5 (S = 4)      37.7 / 41.5   40.1 / 44.9   48.5 / 53.5
+//   7   (S = 2)      39.8 / 50.7                 49.0 / 58.4
+//   8   (S = 4)      48.8 / 47.7                 50.9 / 54.9
+//   12  (S = 4)                                                99.5 / 106.0
+//   14  (S = 4)                    71.7 / 67.2   78.8 / 77.5                 142.2 / 147.5
 bool draft_shared_inside(const Shape &s, int n_cu)
 {
     const long items = (long)s.S * (s.I / 16);
-    return s.T == 1 && s.S > 0 && (items <= 3L * n_cu || items * 256 <= (long)n_cu * s.H);
+    return s.T == 1 && s.S > 0 && (items <= 7L * n_cu || items * 128 <= (long)n_cu * s.H);
 }
 
 // one token: router inside the launch, a work item per (selected expert, slice) and per 16 rows of
