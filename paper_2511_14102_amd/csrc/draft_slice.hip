@@ -1,6 +1,6 @@
 // Draft-pass kernel for a call with ONE token: router, top-k and the SwiGLU FFN of the selected
-// experts on group-wise int4 weights in one launch, one workgroup per work item (gfx950).
-// (Calls with two or more items per compute unit, or two to eight tokens, run the persistent kernel of
+// experts on group-wise int4 weights in one launch, one or two work items per workgroup (gfx950).
+// (Calls of two to eight tokens, and of one with many long items, run the persistent kernel of
 // draft_int4.hip, longer runs of tokens the grouped contraction of draft_prefill.hip.)
 //
 // Paper section 3.4.3 (one expert-fused kernel instead of per-expert small GEMMs), section 4.1.3
@@ -16,7 +16,7 @@
 // (slice_pairs).  Long rows and two items per unit and more run the persistent kernel (one_token_streams).
 //
 // Bound: a chain of round trips to memory up to the first weight load (x and router rows, exchange, selection:
-// about 3 us), then the weight stream (84 MB in 17 us on the phi shape) with one or two items per unit.
+// about 3 us), then the weight stream (84 MB in about 14 us on the phi shape), then the chain of additions to y (slice_pairs).
 #include "draft_common.h"
 
 namespace moespeq {
