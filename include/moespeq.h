@@ -183,7 +183,11 @@ int moe_workspace_idle_bytes(const moe_layer_desc *desc, size_t *bytes);
  * seconds).  The wait ends only if the producing workgroups run while the others poll.  The
  * library checks on the host that the launch fits the device at once (else the call returns
  * MOE_ERR_INVALID_ARG), which is enough on a device that runs nothing else; kernels of other
- * streams or processes that hold compute units can delay the producers.  If a workgroup runs out of
+ * streams or processes that hold compute units can delay the producers.  Draft calls that run at the same
+ * time on n streams, each with its own workspace, always go on if n * n_experts is no more than the
+ * device's compute units (at most n_experts workgroups of a call are producers, and one of the n calls
+ * holds 1/n of the units); with more, each may hold units that the others' producers need, and all
+ * wait until their polls run out.  If a workgroup runs out of
  * polls it skips its work: the call still returns MOE_OK (the launch was enqueued), ids_out holds
  * -1 (conf_out 0), y is unspecified, the status word in the workspace is set and stays set, and the
  * counters may be left non-zero.  moe_draft_status waits for `stream`, reads the word and writes

@@ -12,6 +12,7 @@
 // A operand.  Scale, zero and the 128 offset are applied once per group on the accumulators.
 #pragma once
 #include <type_traits>
+#include "draft_rules.h"
 #include "plan.h"
 #include "stream.h"
 #include "wave.h"
@@ -125,27 +126,13 @@ struct FusedArgs {
 
 // ---- the router inside a draft call (both kernels)
 
-// Tokens per router workgroup, as a power of two: the fewest with which every (row, share of the tokens) has a workgroup of its own,
-// so that a workgroup's part of the start, which everybody waits for, is short.  us per call, all tokens of a row in one
-// workgroup / shared out: phi shape, 4 tokens (16 / 64 router workgroups) 46.7 / 46.1; qwen3, 8 tokens (128 / 256) 37.5 / 36.5;
-// H = 1024, E = 10, I = 1984, k = 7, 5 tokens (10 / 50) 28.6 / 28.0.
-__host__ __device__ inline int router_tokens_log2(int T, int E, int grid) {
-    int lt = 0;
-    while ((1 << lt) < T && E * ((T + (1 << lt) - 1) >> lt) > grid) ++lt;
-    return lt;
-}
-__host__ __device__ inline int router_workgroups(int T, int E, int grid) {
-    const int lt = router_tokens_log2(T, E, grid), n = E * ((T + (1 << lt) - 1) >> lt);
-    return n < grid ? n : grid;
-}
-
-// Workgroup b (numbered among the call's `nprod` router workgroups) takes the (router row, 2^lt tokens) pairs b, b + nprod, ...
-// and publishes each {logit, tag}.  The NW waves are shared out over the tokens, NW / 2^lt
-// of them splitting H, so that a row costs one round of loads and
+// Workgroup b (numbered among the call's `nprod` router workgroups) reduces router rows b, b + nprod, ...
+// for all T tokens and publishes each {logit, tag}.  The NW waves are shared out over the tokens, NW / T2
+// of them (T2: T rounded up to a power of two) splitting H, so that a row costs one round of loads and
 // one barrier however many tokens there are (one token after another took 6 us for 8 tokens).  fp64
 // accumulation of exact fp32 products.  Before it publishes, the workgroup clears its share of y.
 template <int NW>
-__device__ inline void publish_router_rows(const uint16_t *__restrict__ xin, const FusedArgs &a, int b, int nprod, int lt,
+__device__ inline void publish_router_rows(const uint16_t *__restrict__ xin, const FusedArgs &a, int b, int nprod,
                                            double (&s_part)[NW])
 {
     constexpr int kTh = NW * 64;
@@ -153,12 +140,10 @@ __device__ inline void publish_router_rows(const uint16_t *__restrict__ xin, con
     const int T = a.T, H = a.H, E = a.E, chunks = H / 8;
     for (int i = b * kTh + tid; i < T * H; i += nprod * kTh)
         __hip_atomic_store(&a.y[i], 0.f, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-    const int shares = (T + (1 << lt) - 1) >> lt, part = wave >> lt, step = (NW >> lt) * 64;
-    for (int p = b; p < E * shares; p += nprod) {
-        int e = p, t0 = 0;
-        for (; e >= E; e -= E) t0 += 1 << lt;
-        const int t = t0 + (wave & ((1 << lt) - 1));
-        const uint16_t *xt = xin + (size_t)(t < T ? t : T - 1) * H;
+    const int lt = T <= 1 ? 0 : (T <= 2 ? 1 : (T <= 4 ? 2 : 3));
+    const int t = wave & ((1 << lt) - 1), part = wave >> lt, step = (NW >> lt) * 64;
+    const uint16_t *xt = xin + (size_t)(t < T ? t : T - 1) * H;
+    for (int e = b; e < E; e += nprod) {
         const uint16_t *row = a.wr + (size_t)e * H;
         const float bias = a.bias ? a.bias[e] : 0.f;          // (here and not behind the barrier: a round trip to memory)
         double acc[4] = {0.0, 0.0, 0.0, 0.0};
@@ -191,7 +176,7 @@ __device__ inline void publish_router_rows(const uint16_t *__restrict__ xin, con
         // of the row were issued after the stores and have returned)
         asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
         __syncthreads();
-        if (tid < kReplicas << lt && t0 + tid / kReplicas < T) {                           // thread (token, replica)
+        if (tid < T * kReplicas) {                           // thread (token, replica)
             const int tt = tid / kReplicas, rep = tid % kReplicas;
             double l = 0.0;
 #pragma unroll
@@ -201,9 +186,9 @@ __device__ inline void publish_router_rows(const uint16_t *__restrict__ xin, con
             // 16-byte load: a reader sees the tag only together with the logit
             const unsigned long long lb = (unsigned long long)__double_as_longlong(l);
             const u32x4 rec = {(uint32_t)lb, (uint32_t)(lb >> 32), 1u, 0u};
-            store16_agent(a.slots + (size_t)rep * a.replica_stride + 2 * ((size_t)(t0 + tt) * E + e), rec);
+            store16_agent(a.slots + (size_t)rep * a.replica_stride + 2 * ((size_t)tt * E + e), rec);
         }
-        if (p + nprod < E * shares) __syncthreads();                  // s_part is written again
+        if (e + nprod < E) __syncthreads();                  // s_part is written again
     }
 }
 

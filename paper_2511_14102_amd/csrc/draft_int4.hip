@@ -28,7 +28,7 @@
 // 87 (now 83), qwen3 8 tokens 60.6 (now 40).
 //
 // Cross-workgroup protocol (one bounded wait, no cache flushes):
-//   1. router row e is reduced, for a share of the tokens (router_tokens_log2), by one of the first workgroups, which first clears its share of y
+//   1. router row e is reduced by workgroup e (mod router_workgroups), which first clears its share of y
 //      with agent-scope stores, waits for their completion, and then publishes the 16-byte
 //      slot {logit, tag = 1} of every token as one 16-byte store (in kReplicas copies);
 //   2. every workgroup polls the slots with single 16-byte agent-scope loads until all are
@@ -38,7 +38,7 @@
 //   4. the workgroup holding the last ticket (everybody has finished polling by then) clears
 //      the tags and the ticket counters at its end, so the workspace is back in its idle state
 //      when the kernel ends.  This also holds when the same launch is replayed from a HIP graph.
-// The wait of step 2 needs the producing workgroups (the first router_workgroups ones; of one token min(E, grid)) to be running
+// The wait of step 2 needs the producing workgroups (the first min(E, grid) ones) to be running
 // while the others poll: the grid never exceeds the number of compute units, and a workgroup
 // fits a compute unit by itself, so on an otherwise idle device all are resident.  If the wait
 // runs out (spin limit), the workgroup skips its items and workgroup 0 reports ids = -1.
@@ -88,8 +88,8 @@ __device__ __forceinline__ void draft_stream(const uint16_t *__restrict__ xin, c
     int32_t *s_rank = reinterpret_cast<int32_t *>(s_dyn + logit_off + (size_t)MT * E * 8);
 
     // ---- 1. router rows owned by this workgroup
-    const int lt = router_tokens_log2(T, E, gridDim.x), nprod = router_workgroups(T, E, gridDim.x);
-    if ((int)blockIdx.x < nprod) publish_router_rows<kWaves>(xin, a, blockIdx.x, nprod, lt, s_part);
+    const int nprod = router_workgroups(E, gridDim.x);
+    if ((int)blockIdx.x < nprod) publish_router_rows<kWaves>(xin, a, blockIdx.x, nprod, s_part);
     if (tid == 0) s_flag = 1;
     if (tid < MOE_MAX_EXPERTS / 64) s_mask[tid] = 0ull;
     if (tid < 2 * MT) s_hsum[tid / MT][tid % MT] = 0.f;

@@ -63,10 +63,10 @@ __device__ __forceinline__ void draft_one_token(const uint16_t *__restrict__ xin
     // they are running before any other waits for them.  Behind them the shared experts' items, which start at
     // once, then the other routed items, which wait for the routing.
     const int n_sh = SHARED ? a.S * (I / 16) / ITEMS : 0, n_routed = (int)gridDim.x - n_sh;
-    const int nprod = E < n_routed ? E : n_routed;
+    const int nprod = router_workgroups(E, n_routed);
     const int b = blockIdx.x;
     const bool shared = SHARED && b >= nprod && b < nprod + n_sh;
-    if (b < nprod) publish_router_rows<kWaves * ITEMS>(xin, a, b, nprod, 0, s_part);
+    if (b < nprod) publish_router_rows<kWaves * ITEMS>(xin, a, b, nprod, s_part);
     uint32_t ticket = 0xffffffffu, ticket2 = 0xffffffffu;
     auto first_ticket = [&]() { if (lane == 0) ticket = draw_ticket(a.tickets + b % kTicketGroups); };
     auto stage_x = [&]() {

@@ -141,8 +141,8 @@ def test_one_token_with_pairs_of_items(H, I, E, k, g, S):
 
 @pytest.mark.parametrize("H,E,T,g", [(192, 16, 8, 32), (3136, 60, 7, 64), (2176, 100, 5, 128), (1088, 200, 3, 32), (64, 256, 8, 32), (4224, 5, 2, 128)])
 def test_router_rows_shared_out_by_tokens(H, E, T, g):
-    """A router row's tokens in one workgroup (E = 256), in two with a ragged last one (100 and 5 tokens), in four and in one
-    each; x in one round of a workgroup's loads and in several, the last one ragged."""
+    """A workgroup's waves shared out over the tokens of its router row, a power of two of them or fewer; x in one round of a
+    workgroup's loads and in several, the last one ragged."""
     cfg = LayerConfig(80, "rows%d" % E, H, E, 256, min(8, E), g, 0, 1)
     ctx = B.Context(0)
     L = build_layer(cfg)
