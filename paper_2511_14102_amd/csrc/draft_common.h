@@ -131,21 +131,24 @@ struct FusedArgs {
 // of them (T2: T rounded up to a power of two) splitting H, so that a row costs one round of loads and
 // one barrier however many tokens there are (one token after another took 6 us for 8 tokens).  fp64
 // accumulation of exact fp32 products.  Before it publishes, the workgroup clears its share of y.
-template <int NW>
+// ROWS = 2 (one token): it takes two neighbouring rows at a time, half of its waves each.
+template <int NW, int ROWS>
 __device__ inline void publish_router_rows(const uint16_t *__restrict__ xin, const FusedArgs &a, int b, int nprod,
                                            double (&s_part)[NW])
 {
-    constexpr int kTh = NW * 64;
+    constexpr int kTh = NW * 64, kRowWaves = NW / ROWS;
     const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int T = a.T, H = a.H, E = a.E, chunks = H / 8;
     for (int i = b * kTh + tid; i < T * H; i += nprod * kTh)
         __hip_atomic_store(&a.y[i], 0.f, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
     const int lt = T <= 1 ? 0 : (T <= 2 ? 1 : (T <= 4 ? 2 : 3));
-    const int t = wave & ((1 << lt) - 1), part = wave >> lt, step = (NW >> lt) * 64;
+    const int in_row = ROWS > 1 ? wave % kRowWaves : wave, t = in_row & ((1 << lt) - 1), part = in_row >> lt, step = (kRowWaves >> lt) * 64;
     const uint16_t *xt = xin + (size_t)(t < T ? t : T - 1) * H;
-    for (int e = b; e < E; e += nprod) {
-        const uint16_t *row = a.wr + (size_t)e * H;
-        const float bias = a.bias ? a.bias[e] : 0.f;          // (here and not behind the barrier: a round trip to memory)
+    for (int e = b * ROWS; e < E; e += nprod * ROWS) {
+        // of the rows e, e + 1: the one to reduce, the one to publish (behind an odd last row, that one again, not published)
+        const int reduced = ROWS > 1 && e + 1 < E ? wave / kRowWaves : 0, mine = ROWS > 1 ? tid / kReplicas % ROWS : 0;
+        const uint16_t *row = a.wr + (size_t)(e + reduced) * H;
+        const float bias = a.bias ? a.bias[ROWS > 1 && e + mine >= E ? e : e + mine] : 0.f;          // (here and not behind the barrier: a round trip to memory)
         double acc[4] = {0.0, 0.0, 0.0, 0.0};
         auto chunks_at = [&](int c0, auto batch) {           // (a position past the end counts as zeros)
             constexpr int kB = decltype(batch)::value;
@@ -176,19 +179,19 @@ __device__ inline void publish_router_rows(const uint16_t *__restrict__ xin, con
         // of the row were issued after the stores and have returned)
         asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
         __syncthreads();
-        if (tid < T * kReplicas) {                           // thread (token, replica)
-            const int tt = tid / kReplicas, rep = tid % kReplicas;
+        if (tid < T * ROWS * kReplicas && (ROWS == 1 || e + mine < E)) {    // thread (token or row, replica)
+            const int tt = ROWS > 1 ? 0 : tid / kReplicas, rep = tid % kReplicas;
             double l = 0.0;
 #pragma unroll
-            for (int w = 0; w < NW; ++w) l += (w & ((1 << lt) - 1)) == tt ? s_part[w] : 0.0;
+            for (int w = 0; w < kRowWaves; ++w) l += (w & ((1 << lt) - 1)) == tt ? s_part[mine * kRowWaves + w] : 0.0;
             l += (double)bias;
             // {logit, tag} leaves as ONE aligned 16-byte agent-scope store and is read with one
             // 16-byte load: a reader sees the tag only together with the logit
             const unsigned long long lb = (unsigned long long)__double_as_longlong(l);
             const u32x4 rec = {(uint32_t)lb, (uint32_t)(lb >> 32), 1u, 0u};
-            store16_agent(a.slots + (size_t)rep * a.replica_stride + 2 * ((size_t)tt * E + e), rec);
+            store16_agent(a.slots + (size_t)rep * a.replica_stride + 2 * ((size_t)tt * E + e + mine), rec);
         }
-        if (e + nprod < E) __syncthreads();                  // s_part is written again
+        if (e + nprod * ROWS < E) __syncthreads();                  // s_part is written again
     }
 }
 

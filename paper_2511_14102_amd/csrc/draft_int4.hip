@@ -88,8 +88,8 @@ __device__ __forceinline__ void draft_stream(const uint16_t *__restrict__ xin, c
     int32_t *s_rank = reinterpret_cast<int32_t *>(s_dyn + logit_off + (size_t)MT * E * 8);
 
     // ---- 1. router rows owned by this workgroup
-    const int nprod = router_workgroups(E, gridDim.x);
-    if ((int)blockIdx.x < nprod) publish_router_rows<kWaves>(xin, a, blockIdx.x, nprod, s_part);
+    const int nprod = router_workgroups(E, 1, gridDim.x);
+    if ((int)blockIdx.x < nprod) publish_router_rows<kWaves, 1>(xin, a, blockIdx.x, nprod, s_part);
     if (tid == 0) s_flag = 1;
     if (tid < MOE_MAX_EXPERTS / 64) s_mask[tid] = 0ull;
     if (tid < 2 * MT) s_hsum[tid / MT][tid % MT] = 0.f;
@@ -710,9 +710,8 @@ bool one_token_streams(const Shape &s, const DraftFusedArgs &d, int n_cu)
 int draft_resident_slots(const Shape &s, const DraftFusedArgs &d, int n_cu)
 {
     if (s.T == 1 && !one_token_streams(s, d, n_cu)) {
-        long routed = 0;
-        const int slots = draft_one_token_resident(s, d, n_cu, &routed);
-        const long need = s.E < routed ? s.E : routed;
+        int need = 0;
+        const int slots = draft_one_token_resident(s, d, n_cu, &need);
         return need <= slots ? slots : 0;
     }
     int per = 0;

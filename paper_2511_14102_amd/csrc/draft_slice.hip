@@ -63,10 +63,10 @@ __device__ __forceinline__ void draft_one_token(const uint16_t *__restrict__ xin
     // they are running before any other waits for them.  Behind them the shared experts' items, which start at
     // once, then the other routed items, which wait for the routing.
     const int n_sh = SHARED ? a.S * (I / 16) / ITEMS : 0, n_routed = (int)gridDim.x - n_sh;
-    const int nprod = router_workgroups(E, n_routed);
+    const int nprod = router_workgroups(E, ITEMS, n_routed);
     const int b = blockIdx.x;
     const bool shared = SHARED && b >= nprod && b < nprod + n_sh;
-    if (b < nprod) publish_router_rows<kWaves * ITEMS>(xin, a, b, nprod, s_part);
+    if (b < nprod) publish_router_rows<kWaves * ITEMS, ITEMS>(xin, a, b, nprod, s_part);
     uint32_t ticket = 0xffffffffu, ticket2 = 0xffffffffu;
     auto first_ticket = [&]() { if (lane == 0) ticket = draw_ticket(a.tickets + b % kTicketGroups); };
     auto stage_x = [&]() {
@@ -448,7 +448,7 @@ bool slice_pairs(const Shape &s, const DraftFusedArgs &d, int n_cu)
 {
     const int items = s.k * (s.I / 32) + (d.shared_inside ? s.S * (s.I / 16) : 0), routed = s.k * (s.I / 32) / 2;
     // (a unit holds one workgroup of two items: those that reduce the router rows have to be running together)
-    return items >= n_cu && (items <= 2 * n_cu || s.H <= 2048) && (s.E <= n_cu || routed <= n_cu) &&
+    return items >= n_cu && (items <= 2 * n_cu || s.H <= 2048) && router_workgroups(s.E, 2, routed) <= n_cu &&
            slice_dynamic_lds(s.H, s.g, s.E, 2) <= (size_t)(160 - 20) * 1024;
 }
 
@@ -497,13 +497,13 @@ void launch_draft_one_token(const Shape &s, const DraftFusedArgs &d, int n_cu, h
     });
 }
 
-// workgroups the device holds at once, and how many of them the call's routed items make
-int draft_one_token_resident(const Shape &s, const DraftFusedArgs &d, int n_cu, long *routed)
+// workgroups the device holds at once, and how many of them have to be running together
+int draft_one_token_resident(const Shape &s, const DraftFusedArgs &d, int n_cu, int *need)
 {
     int per = 0;
     slice_kernel(s, d, n_cu, [&](auto kernel, int items) {
         per = resident_per_cu(kernel, kThreads * items, slice_dynamic_lds(s.H, s.g, s.E, items));
-        *routed = (long)s.k * (s.I / 32) / items;
+        *need = router_workgroups(s.E, items, s.k * (s.I / 32) / items);
     });
     return per * n_cu;
 }

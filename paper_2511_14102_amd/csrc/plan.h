@@ -127,7 +127,7 @@ int draft_resident_slots(const Shape &s, const DraftFusedArgs &a, int n_cu);
 void launch_draft_one_token(const Shape &s, const DraftFusedArgs &a, int n_cu, hipStream_t st);
 bool draft_one_token_fits(const Shape &s);
 bool draft_shared_inside(const Shape &s, int n_cu);      // whether the call's launch runs the shared experts too
-int draft_one_token_resident(const Shape &s, const DraftFusedArgs &a, int n_cu, long *routed);   // workgroups resident at once; its routed ones
+int draft_one_token_resident(const Shape &s, const DraftFusedArgs &a, int n_cu, int *need);   // workgroups resident at once; those that have to be
 void launch_zero(void *p, size_t bytes, hipStream_t st);
 void launch_stream_read(const void *src, size_t bytes, int workgroups, void *sink, hipStream_t st);
 

@@ -5,6 +5,6 @@ using namespace moespeq;
 
 extern "C" {
 
-int rule_router_workgroups(int experts, int workgroups) { return router_workgroups(experts, workgroups); }
+int rule_router_workgroups(int experts, int rows, int workgroups) { return router_workgroups(experts, rows, workgroups); }
 
 }

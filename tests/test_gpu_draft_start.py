@@ -116,10 +116,12 @@ def test_stream_windows_of_eight(g):
 
 
 @pytest.mark.parametrize("H,I,E,k,g,S", [(64, 4096, 3, 2, 32, 0), (320, 2048, 4, 4, 64, 0), (2112, 2752, 5, 3, 64, 0), (1088, 4160, 6, 4, 32, 0),
-                                         (512, 2048, 4, 1, 64, 2), (2304, 1024, 8, 8, 128, 2), (192, 8192, 3, 2, 64, 2)])
+                                         (512, 2048, 4, 1, 64, 2), (2304, 1024, 8, 8, 128, 2), (192, 8192, 3, 2, 64, 2),
+                                         (192, 1024, 128, 1, 64, 4), (64, 1024, 67, 2, 32, 4), (1088, 2048, 9, 1, 32, 4)])
 def test_one_token_with_pairs_of_items(H, I, E, k, g, S):
     """Calls of one token with 256 work items and more, which run two items per workgroup: fewer row tiles or groups than waves, ragged
-    shares of both, exactly 256 and 512 items, more than two per unit with short rows, and shared experts beside the routed ones."""
+    shares of both, exactly 256 and 512 items, more than two per unit with short rows, and shared experts beside the routed ones; two router rows to a
+    workgroup, an odd last one, and several rounds of them (128 and 67 experts over 16 and 32 routed workgroups)."""
     cfg = LayerConfig(81, "pair%d" % H, H, E, I, k, g, S, 1)
     ctx = B.Context(0)
     for symmetric in (False, True):
