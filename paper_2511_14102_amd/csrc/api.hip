@@ -371,6 +371,7 @@ static int enqueue_draft(moe_ctx *ctx, const moe_layer_desc *desc, const void *x
     a.plan = plan; a.shared = shared; a.shared_stride = moe_bf16_expert_bytes(desc);
     // the workgroups that reduce the router rows (the first ones of the launch, router_workgroups) must be
     // running while the others wait for them
+    a.form = draft_form(s, a, ctx->n_cu);
     const int slots = draft_resident_slots(s, a, ctx->n_cu);
     if (slots == 0) return MOE_ERR_INVALID_ARG;
     const bool own_launches = s.S > 0 && !a.shared_inside;

@@ -12,7 +12,6 @@
 // A operand.  Scale, zero and the 128 offset are applied once per group on the accumulators.
 #pragma once
 #include <type_traits>
-#include "draft_rules.h"
 #include "plan.h"
 #include "stream.h"
 #include "wave.h"
@@ -21,7 +20,7 @@ namespace moespeq {
 
 namespace {
 
-constexpr int kWaves = 8;
+constexpr int kWaves = kDraftWaves;
 constexpr int kThreads = kWaves * 64;
 // The router result is published in kReplicas copies; workgroup b polls copy b % kReplicas, so
 // that the polls of hundreds of workgroups do not all land on one address.

@@ -50,10 +50,7 @@ namespace {
 
 // MT: token capacity of the launch (2, 4 or 8); UPG: 32-code units per
 // group (g / 32); SYM: symmetric format (scale blobs, z = 8); kWin:
-// tiles a wave keeps in flight.
-// SUMS: y is summed in LDS over a workgroup's items of one expert, that many token slots of it
-constexpr int sum_slots(int MT) { return MT == 4 ? 4 : 2; }
-
+// tiles a wave keeps in flight; SUMS: y is summed in LDS over a workgroup's items of one expert, sum_slots(MT) token slots of it.
 template <int MT, int UPG, bool SYM, int kWin, bool SUMS>
 __device__ __forceinline__ void draft_stream(const uint16_t *__restrict__ xin, const FusedArgs &a)
 {
@@ -622,44 +619,6 @@ void stream_read_kernel(const u32x4 *__restrict__ src, size_t tiles, uint32_t *s
 // form without sums of y in LDS).
 constexpr int kMaxPerCu = 1;
 
-// Tiles a wave keeps in flight: eight, or four where padding the two parts of an item to whole windows of eight
-// would add more than a fifth to the stream's positions (an empty position is a load that is not in
-// flight).  8 against 4: phi shape (16 and 8 tiles per part and wave), 4 tokens 43.3 / 50.4 us (without the sums of y, which the
-// window of four does not have, 48.7 / 50.4), 2 tokens 36.7 / 38.4; qwen3 shape (8 and 4), 8 tokens 41.5 / 37.4, 2 tokens 20.8 /
-// 19.1.  Windows of 12 and 16 only add padding (phi, 4 tokens, when 8 took 52.7 us: 58.3 and 59.4).
-int stream_window(const Shape &s, bool sym)
-{
-    const int epl = sym ? 2 : 1;
-    const int nt = (s.H / s.g / epl + kWaves - 1) / kWaves * epl * (s.g / 32);
-    const int nd = (s.H / 64 / epl + kWaves - 1) / kWaves * epl;
-    auto positions = [&](int w) { return (nt + w - 1) / w * w + (nd + w - 1) / w * w; };
-    return positions(8) * 5 > positions(4) * 6 ? 4 : 8;
-}
-
-// dynamic LDS: the bf16 copy of x (padded rows), its per-group sums, the routing scratch (fp64
-// logits and ranks), and per wave the scale / zero entries of its groups and row tiles of one
-// item (whole KiB each)
-size_t draft_dynamic_lds(int MT, int H, int g, int E, bool sym, int entry_copies = 1)
-{
-    const int nw = kWaves;
-    size_t lds = ((size_t)MT * (H + 8) * 2 + (size_t)MT * (H / g) * 4 + 7) & ~(size_t)7;
-    lds += (size_t)MT * E * 12;
-    lds = (lds + 15) & ~(size_t)15;
-    const int epl = sym ? 2 : 1;
-    const int gl_max = (H / g / epl + nw - 1) / nw, dl_max = (H / 64 / epl + nw - 1) / nw;
-    lds += (size_t)entry_copies * nw * ((size_t)((gl_max + 3) / 4) + (size_t)((dl_max + 3) / 4)) * 1024;
-    return lds;
-}
-
-// and behind it the sums of y: from two items per workgroup on, in calls with the window of eight, where they fit (0: no sums)
-size_t sum_lds(const Shape &s, int MT, bool sym, int n_cu)
-{
-    const int maxu = s.E < s.T * s.k ? s.E : s.T * s.k;
-    const size_t sums = (size_t)sum_slots(MT) * s.H * 4;
-    if ((long)maxu * (s.I / 32) < 2L * n_cu || stream_window(s, sym) != 8) return 0;
-    return draft_dynamic_lds(MT, s.H, s.g, s.E, sym) + sums <= (size_t)(160 - 20) * 1024 ? sums : 0;
-}
-
 // go(kernel, bytes of dynamic LDS) with the instantiation for a call
 template <int MT, int UPG, bool SYM, typename F>
 void stream_kernel_m(const Shape &s, int n_cu, F go)
@@ -690,29 +649,22 @@ void stream_kernel(const Shape &s, bool sym, int n_cu, F go)
     else stream_kernel_t<false>(s, n_cu, go);
 }
 
-// One token through the persistent kernel: from two items per compute unit on, where the launch carries no shared
-// experts and the kernel's two copies of x fit LDS, if it sums y in LDS (long rows); without the sums only where pairs of items
-// (draft_slice.hip) make between one and one and a half rounds of long workgroups.  us per call, persistent / pairs (items):
-// H = 4096 (with the sums): 512 27.4 / 27.8, 600 30.9 / 40.9; H = 2304, 576 27.4 / 33.0; H = 2048: 512 23.9 / 20.1, 640 27.7 / 29.5,
-// 768 30.2 / 30.1, 1024 37.2 / 33.4; H = 1024: 512 21.9 / 17.2, 640 25.7 / 25.2, 1024 34.6 / 28.0; H = 320, 1870 56.2 / 39.9.
-bool one_token_streams(const Shape &s, const DraftFusedArgs &d, int n_cu)
-{
-    const int items = s.k * (s.I / 32);
-    if (items < 2 * n_cu || d.shared_inside || !draft_fits(s, 2, d.symmetric != 0)) return false;
-    return s.H > 2048 || sum_lds(s, 2, d.symmetric != 0, n_cu) > 0 || (s.H > 1024 && items > 2 * n_cu && items < 3 * n_cu);
-}
-
 }  // namespace
 
-// The launch shapes: one token, one workgroup per item, dispatched in order, so the first
-// min(E, grid) of them are resident together when that many fit on the device at once; more tokens,
+OneTokenForm draft_form(const Shape &s, const DraftFusedArgs &d, int n_cu)
+{
+    if (s.T > 1) return kPersistent;
+    return one_token_form(s, d.symmetric != 0, d.shared_inside != 0, n_cu, [&] { return draft_one_token_slots(s, d, kSingleItems, n_cu); });
+}
+
+// The launch shapes: one token, one workgroup per item or two, dispatched in order, so the first ones, which
+// reduce the router rows, are resident together when that many fit on the device at once; more tokens,
 // a grid of as many workgroups as the device holds at once.
 int draft_resident_slots(const Shape &s, const DraftFusedArgs &d, int n_cu)
 {
-    if (s.T == 1 && !one_token_streams(s, d, n_cu)) {
-        int need = 0;
-        const int slots = draft_one_token_resident(s, d, n_cu, &need);
-        return need <= slots ? slots : 0;
+    if (d.form != kPersistent) {
+        const int items = d.form == kPairsOfItems ? 2 : 1, slots = draft_one_token_slots(s, d, d.form, n_cu);
+        return router_workgroups(s.E, items, s.k * (s.I / 32) / items) <= slots ? slots : 0;
     }
     int per = 0;
     stream_kernel(s, d.symmetric != 0, n_cu, [&](auto kernel, size_t lds) { per = resident_per_cu(kernel, kThreads, lds); });
@@ -721,7 +673,7 @@ int draft_resident_slots(const Shape &s, const DraftFusedArgs &d, int n_cu)
 
 void launch_draft_fused(const Shape &s, const DraftFusedArgs &d, int n_cu, int slots, hipStream_t st)
 {
-    if (s.T == 1 && !one_token_streams(s, d, n_cu)) { launch_draft_one_token(s, d, n_cu, st); return; }
+    if (d.form != kPersistent) { launch_draft_one_token(s, d, st); return; }
     const FusedArgs a = fused_args(s, d);
     // never more workgroups than there can be items
     const int maxu = s.E < s.T * s.k ? s.E : s.T * s.k;
@@ -730,16 +682,6 @@ void launch_draft_fused(const Shape &s, const DraftFusedArgs &d, int n_cu, int s
     stream_kernel(s, d.symmetric != 0, n_cu, [&](auto kernel, size_t lds) {
         launch_with_lds(kernel, grid, block, lds, st, (const uint16_t *)d.x, a);
     });
-}
-
-bool draft_fits(const Shape &s, int tokens, bool sym)
-{
-    if (tokens <= 1) return draft_one_token_fits(s);
-    const int MT = tokens <= 2 ? 2 : (tokens <= 4 ? 4 : 8);
-    // 160 KiB of LDS per workgroup, 20 KiB of them for the kernel's static arrays.  (The limit callers
-    // know counts the entries twice; one copy is kept.)
-    const size_t entries = draft_dynamic_lds(MT, s.H, s.g, s.E, sym) - draft_dynamic_lds(MT, s.H, s.g, s.E, sym, 0);
-    return draft_dynamic_lds(MT, s.H, s.g, s.E, sym) + entries <= (size_t)(160 - 20) * 1024;
 }
 
 void launch_stream_read(const void *src, size_t bytes, int workgroups, void *sink, hipStream_t st)

@@ -432,26 +432,6 @@ template <int UPG, bool SYM, bool SHARED>
 __global__ __launch_bounds__(2 * kThreads, 4)
 void draft_pair_kernel(const uint16_t *__restrict__ xin, const FusedArgs a) { draft_one_token<UPG, SYM, SHARED, 2>(xin, a); }
 
-// dynamic LDS: x, the fp64 logits and the ranks, the sums of x per group, the outputs of two items
-size_t slice_dynamic_lds(int H, int g, int E, int items) { return (size_t)H * 2 + (size_t)E * 12 + (size_t)(H / g) * 4 + (items > 1 ? (size_t)H * 8 : 0); }
-
-// Items per workgroup.  Every item adds to all of y, and fp32 additions to one address follow each other at 25 ns (400 workgroups
-// adding to the same 4096 floats take 13.8 us, to four copies of them 7.9, without adding 3.8), so that n items cannot
-// end less than n x 25 ns after the first one, and beyond 256 items some units have two, whose second one also starts late: its
-// loads wait until the first one's have returned.  Two items in one workgroup halve the chain and give every unit the same.
-// Not below one item per unit, where pairs leave units empty, and with long items not beyond two per unit, where a second
-// round of workgroups costs more than the chain.  us per call, single / paired (items):
-//   H = 4096: 224 18.5 / 19.6, 256 20.0 / 20.0, 320 23.7 / 21.5, 384 25.7 / 24.7, 576 38.9 / 47.0, 768 44.4 / 49.8
-//   H = 2048: 192 14.6 / 17.1, 224 14.3 / 15.1, 240 15.0 / 15.2, 320 18.8 / 16.4, 504 24.4 / 20.6, 624 30.9 / 28.7, 768 35.6 / 28.9
-//   H = 512: 240 13.0 / 12.6, 504 21.1 / 15.8, 768 26.0 / 17.9
-bool slice_pairs(const Shape &s, const DraftFusedArgs &d, int n_cu)
-{
-    const int items = s.k * (s.I / 32) + (d.shared_inside ? s.S * (s.I / 16) : 0), routed = s.k * (s.I / 32) / 2;
-    // (a unit holds one workgroup of two items: those that reduce the router rows have to be running together)
-    return items >= n_cu && (items <= 2 * n_cu || s.H <= 2048) && router_workgroups(s.E, 2, routed) <= n_cu &&
-           slice_dynamic_lds(s.H, s.g, s.E, 2) <= (size_t)(160 - 20) * 1024;
-}
-
 template <bool SYM, bool SHARED, typename F>
 void slice_kernel(int g, bool pairs, F go)           // go(kernel, items per workgroup)
 {
@@ -460,57 +440,33 @@ void slice_kernel(int g, bool pairs, F go)           // go(kernel, items per wor
     else pairs ? go(draft_pair_kernel<4, SYM, SHARED>, 2) : go(draft_fused_kernel<4, SYM, SHARED>, 1);
 }
 template <typename F>
-void slice_kernel(const Shape &s, const DraftFusedArgs &d, int n_cu, F go)
+void slice_kernel(const Shape &s, const DraftFusedArgs &d, OneTokenForm form, F go)
 {
-    const bool pairs = slice_pairs(s, d, n_cu);
+    const bool pairs = form == kPairsOfItems;
     if (d.symmetric) { if (d.shared_inside) slice_kernel<true, true>(s.g, pairs, go); else slice_kernel<true, false>(s.g, pairs, go); }
     else { if (d.shared_inside) slice_kernel<false, true>(s.g, pairs, go); else slice_kernel<false, false>(s.g, pairs, go); }
 }
 
 }  // namespace
 
-// Whether a one-token call runs its shared experts in its own launch: up to seven 16-row items per compute unit, or
-// one per 128 of H where that is more.  Beyond, items are many and short, a workgroup's start costs more
-// than two launches, and the bf16 kernels take them.  us per call inside / in their own launches (256 units; with pairs of
-// items inside, slice_pairs; with single ones, whose chain of additions is twice as long, the line lay at three per unit, or one per 256):
-//   items per unit   H = 256       H = 512       H = 1024      H = 1536      H = 2048
-//   4   (S = 4)      28.1 / 29.8                 35.1 / 35.1
-//   5.5 (S = 4)      37.7 / 41.5   40.1 / 44.9   48.5 / 53.5
-//   7   (S = 2)      39.8 / 50.7                 49.0 / 58.4
-//   8   (S = 4)      48.8 / 47.7                 50.9 / 54.9
-//   12  (S = 4)                                                99.5 / 106.0
-//   14  (S = 4)                    71.7 / 67.2   78.8 / 77.5                 142.2 / 147.5
-bool draft_shared_inside(const Shape &s, int n_cu)
-{
-    const long items = (long)s.S * (s.I / 16);
-    return s.T == 1 && s.S > 0 && (items <= 7L * n_cu || items * 128 <= (long)n_cu * s.H);
-}
-
 // one token: router inside the launch, a work item per (selected expert, slice) and per 16 rows of
 // every shared expert
-void launch_draft_one_token(const Shape &s, const DraftFusedArgs &d, int n_cu, hipStream_t st)
+void launch_draft_one_token(const Shape &s, const DraftFusedArgs &d, hipStream_t st)
 {
     const FusedArgs a = fused_args(s, d);
-    slice_kernel(s, d, n_cu, [&](auto kernel, int items) {
+    slice_kernel(s, d, d.form, [&](auto kernel, int items) {
         const int grid = (a.k * (a.I / 32) + (d.shared_inside ? a.S * (a.I / 16) : 0)) / items;      // (I is a multiple of 64: even counts)
         launch_with_lds(kernel, dim3(grid), dim3(kThreads * items), slice_dynamic_lds(a.H, a.g, a.E, items), st, (const uint16_t *)d.x, a);
     });
 }
 
-// workgroups the device holds at once, and how many of them have to be running together
-int draft_one_token_resident(const Shape &s, const DraftFusedArgs &d, int n_cu, int *need)
+int draft_one_token_slots(const Shape &s, const DraftFusedArgs &d, OneTokenForm form, int n_cu)
 {
     int per = 0;
-    slice_kernel(s, d, n_cu, [&](auto kernel, int items) {
+    slice_kernel(s, d, form, [&](auto kernel, int items) {
         per = resident_per_cu(kernel, kThreads * items, slice_dynamic_lds(s.H, s.g, s.E, items));
-        *need = router_workgroups(s.E, items, s.k * (s.I / 32) / items);
     });
     return per * n_cu;
-}
-
-bool draft_one_token_fits(const Shape &s)
-{
-    return slice_dynamic_lds(s.H, s.g, s.E, 1) <= (size_t)(160 - 20) * 1024;
 }
 
 }  // namespace moespeq

@@ -5,6 +5,7 @@
 #include <hip/hip_ext.h>
 #include <stdint.h>
 #include "../../include/moespeq.h"
+#include "draft_rules.h"
 
 namespace moespeq {
 
@@ -43,10 +44,6 @@ struct Plan {
     alignas(16) uint8_t act_row[kMaxActive][16];     // row of token t, kNoRow: the token did not choose this expert
     float   row_w[kMaxRows];          // routing weight of a row (1 for shared)
     int32_t row_live[kMaxRows];       // 0: expert absent, the row's output must be skipped
-};
-
-struct Shape {
-    int T, H, E, I, k, S, g, renorm;
 };
 
 // Workspace carve-up (byte offsets from a 256-byte aligned base).  [tickets, plan) must be
@@ -110,6 +107,7 @@ struct DraftFusedArgs {
     const void *q, *sz; size_t stride_q, stride_sz;
     int symmetric;                     // sz holds scale blobs (z = 8)
     int shared_inside;                 // the shared experts run in the call's launch
+    OneTokenForm form;                 // of a call with one token (draft_form); more tokens: the persistent launch
     unsigned long long *slots; size_t replica_stride; uint32_t *tickets;
     uint32_t *status; uint32_t spin_limit;
     float *y; int32_t *ids_out; float *conf_out;
@@ -117,17 +115,15 @@ struct DraftFusedArgs {
 };
 // slots: what draft_resident_slots returned for the call (more than one token: the persistent grid)
 void launch_draft_fused(const Shape &s, const DraftFusedArgs &a, int n_cu, int slots, hipStream_t st);
-// whether the x copy and the entry buffers of a call with `tokens` tokens (1-8) fit into LDS
-bool draft_fits(const Shape &s, int tokens, bool symmetric);
+// The form of the call's launch (a.form), once the rest of `a` is there
+OneTokenForm draft_form(const Shape &s, const DraftFusedArgs &a, int n_cu);
 // How many workgroups of the call's launch the device (n_cu compute units) holds at once; 0 if the ones that
 // reduce the router rows would not all be running while the others wait for them
 int draft_resident_slots(const Shape &s, const DraftFusedArgs &a, int n_cu);
-// draft_slice.hip: the call with ONE token (router inside the launch), one workgroup per
-// (expert, slice) work item
-void launch_draft_one_token(const Shape &s, const DraftFusedArgs &a, int n_cu, hipStream_t st);
-bool draft_one_token_fits(const Shape &s);
-bool draft_shared_inside(const Shape &s, int n_cu);      // whether the call's launch runs the shared experts too
-int draft_one_token_resident(const Shape &s, const DraftFusedArgs &a, int n_cu, int *need);   // workgroups resident at once; those that have to be
+// draft_slice.hip: the call with ONE token (router inside the launch) in a form of one or two (expert, slice) work items per
+// workgroup
+void launch_draft_one_token(const Shape &s, const DraftFusedArgs &a, hipStream_t st);
+int draft_one_token_slots(const Shape &s, const DraftFusedArgs &a, OneTokenForm form, int n_cu);   // workgroups of it the device holds at once
 void launch_zero(void *p, size_t bytes, hipStream_t st);
 void launch_stream_read(const void *src, size_t bytes, int workgroups, void *sink, hipStream_t st);
 

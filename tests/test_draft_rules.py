@@ -27,3 +27,24 @@ def test_pairs_leave_as_much_room_as_single_items(n_cu, E):
     assert single == E
     calls = 2 * n_cu // (E + E % 2)
     assert calls == 0 or pair <= n_cu // calls
+
+
+SHAPES = [(H, E, I, k, g, 0) for H in (256, 1024, 2048, 2304, 4096) for E in (8, 64, 65, 100, 128, 200, 256) for I in (512, 768, 1408, 4096, 14336)
+          for k in (1, 2, 8) for g in (64, 128)]
+
+
+@pytest.mark.parametrize("n_cu", UNITS)
+def test_one_token_calls_with_two_items_per_unit_are_never_refused(n_cu):
+    """The persistent launch takes every such call without shared experts whose two copies of x fit LDS; another form is
+    chosen only where the device holds its router workgroups at once (two of single items to a unit, one of a pair)."""
+    r = rules()
+    seen = set()
+    for H, E, I, k, g, S in SHAPES:
+        if k * (I // 32) < 2 * n_cu or not r.rule_fits(H, E, I, k, g, S, 2):
+            continue
+        form = r.rule_one_token_form(H, E, I, k, g, S, 0, n_cu, 2 * n_cu)
+        seen.add(form)
+        if form < 2:
+            items, room = (1, 2 * n_cu) if form == 0 else (2, n_cu)
+            assert r.rule_router_workgroups(E, items, k * (I // 32) // items) <= room, (H, E, I, k, g, form)
+    assert 2 in seen and 1 in seen
