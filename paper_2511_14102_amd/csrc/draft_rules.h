@@ -97,10 +97,9 @@ inline bool slice_pairs(const Shape &s, bool shared_inside, int n_cu)
            slice_dynamic_lds(s.H, s.g, s.E, 2) <= kDraftLds;
 }
 
-// Whether a one-token call runs its shared experts in its own launch: up to seven 16-row items per compute unit, or
-// one per 128 of H where that is more.  Beyond, items are many and short, a workgroup's start costs more
-// than two launches, and the bf16 kernels take them.  us per call inside / in their own launches (256 units; with pairs of
-// items inside, slice_pairs; with single ones, whose chain of additions is twice as long, the line lay at three per unit, or one per 256):
+// Whether a one-token call runs its shared experts in its own launch: up to three 16-row items per compute unit, or one per 256 of
+// H where that is more; as pairs of items up to seven, or one per 128.  Beyond, items are many and short, a workgroup's start costs
+// more than two launches, and the bf16 kernels take them.  us per call inside as pairs / in their own launches (256 units):
 //   items per unit   H = 256       H = 512       H = 1024      H = 1536      H = 2048
 //   4   (S = 4)      28.1 / 29.8                 35.1 / 35.1
 //   5.5 (S = 4)      37.7 / 41.5   40.1 / 44.9   48.5 / 53.5
@@ -108,10 +107,14 @@ inline bool slice_pairs(const Shape &s, bool shared_inside, int n_cu)
 //   8   (S = 4)      48.8 / 47.7                 50.9 / 54.9
 //   12  (S = 4)                                                99.5 / 106.0
 //   14  (S = 4)                    71.7 / 67.2   78.8 / 77.5                 142.2 / 147.5
+// As single items (their chain of additions is twice as long) beyond the first line, with eight experts chosen, whose routed items
+// leave the persistent launch as well: H = 2304, 10 per unit 180 / 168, 14 per unit 248 / 223; H = 3072, 14 289 / 256; H = 3456, 14 297 / 286.
 inline bool draft_shared_inside(const Shape &s, int n_cu)
 {
     const long items = (long)s.S * (s.I / 16);
-    return s.T == 1 && s.S > 0 && (items <= 7L * n_cu || items * 128 <= (long)n_cu * s.H);
+    if (s.T != 1 || s.S == 0) return false;
+    if (items <= 3L * n_cu || items * 256 <= (long)n_cu * s.H) return true;
+    return (items <= 7L * n_cu || items * 128 <= (long)n_cu * s.H) && slice_pairs(s, true, n_cu);
 }
 
 // One token through the persistent kernel: from two items per compute unit on, where the launch carries no shared

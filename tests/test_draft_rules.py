@@ -48,3 +48,23 @@ def test_one_token_calls_with_two_items_per_unit_are_never_refused(n_cu):
             items, room = (1, 2 * n_cu) if form == 0 else (2, n_cu)
             assert r.rule_router_workgroups(E, items, k * (I // 32) // items) <= room, (H, E, I, k, g, form)
     assert 2 in seen and 1 in seen
+
+
+@pytest.mark.parametrize("n_cu", UNITS)
+def test_many_shared_items_run_inside_only_as_pairs(n_cu):
+    """The line up to which shared experts run in a one-token call's own launch was measured with pairs of items; where the call
+    runs single items (long rows, more than two items per unit), it is three per unit, or one per 256 of H."""
+    r = rules()
+    inside = outside = 0
+    for H in range(256, 4097, 128):
+        for I in (512, 1408, 4096, 7168, 10240, 14336):
+            for S in (1, 2, 4):
+                for k in (1, 2, 8):
+                    items = S * (I // 16)
+                    if not r.rule_shared_inside(H, 64, I, k, 128, S, n_cu):
+                        outside += 1
+                        assert items > 3 * n_cu and items * 256 > n_cu * H
+                    elif items > 3 * n_cu and items * 256 > n_cu * H:
+                        inside += 1
+                        assert r.rule_one_token_form(H, 64, I, k, 128, S, 1, n_cu, 2 * n_cu) == 1, (H, I, S, k)
+    assert inside and outside

@@ -12,6 +12,7 @@ import synth
 from oracle import oracle as orc
 from synth.configs import LayerConfig
 from tests.common import oracle_arrays, oracle_draft, rel_err
+from tests.draft_rules import rules
 from tests.gpu_common import TOL_DRAFT, build_layer, say, to_np, tokens_with_clear_routing
 
 pytestmark = pytest.mark.gpu
@@ -161,18 +162,26 @@ def test_router_rows_shared_out_by_tokens(H, E, T, g):
     ctx.close()
 
 
-def test_shared_experts_on_the_line_run_inside():
-    """As many 16-row items per compute unit as H has 256s (1024 on 256 units): the call's own launch runs the
-    shared experts, no launch of the bf16 kernels is made."""
-    cfg = LayerConfig(74, "line", 1024, 2, 8192, 1, 128, 2, 1)
+@pytest.mark.parametrize("H,I,k,S,g,inside", [(1024, 8192, 1, 2, 128, True),
+                                              (256, 7168, 2, 4, 64, True), (256, 7232, 2, 4, 64, False),
+                                              (1024, 8192, 2, 4, 64, True), (1024, 8256, 2, 4, 64, False),
+                                              (2304, 9216, 2, 4, 64, True), (2304, 9280, 2, 4, 64, False)])
+def test_shared_experts_on_the_line_run_inside(H, I, k, S, g, inside):
+    """On 256 units: as many 16-row items as H has 256s per unit; seven per unit, as pairs, and one step more; as many as H has 128s, and
+    one step more; rows too long for pairs, on the line of single items (9 per unit) and one step beyond.  Up to the line the call's own launch
+    runs the shared experts and no launch of the bf16 kernels is made; beyond, the routed experts run alone (as pairs, or in the persistent
+    launch) and leave the plan for the bf16 kernels."""
+    cfg = LayerConfig(74, "line", H, 2, I, k, g, S, 1)
     if torch.cuda.get_device_properties(0).multi_processor_count != 256:
         pytest.skip("the line is stated for 256 compute units")
+    assert bool(rules().rule_shared_inside(H, 2, I, k, g, S, 256)) == inside
     ctx = B.Context(0)
     L = build_layer(cfg)
     A = oracle_arrays(L)
     D = DeviceLayer(ctx, cfg, L, max_tokens=1, verify=False)
     x = tokens_with_clear_routing(cfg, A, 1, step=2)
     ref = oracle_draft(A, x)
+    say("line of shared experts H", H, "I", I)
     ctx.profile_enable(True)
     r = D.draft(x.cuda())
     torch.cuda.synchronize()
@@ -180,5 +189,5 @@ def test_shared_experts_on_the_line_run_inside():
     ctx.profile_enable(False)
     assert np.array_equal(to_np(r["ids"]), ref["ids"])
     assert rel_err(to_np(r["y"]), ref["y"]) <= TOL_DRAFT
-    assert launches["draft_fused_kernel"] == 1 and launches["bf16_gateup_kernel"] == 0
+    assert launches["draft_fused_kernel"] == 1 and launches["bf16_gateup_kernel"] == (0 if inside else 1)
     ctx.close()
