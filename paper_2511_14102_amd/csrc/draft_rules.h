@@ -107,6 +107,10 @@ inline bool slice_pairs(const Shape &s, bool shared_inside, int n_cu)
 //   8   (S = 4)      48.8 / 47.7                 50.9 / 54.9
 //   12  (S = 4)                                                99.5 / 106.0
 //   14  (S = 4)                    71.7 / 67.2   78.8 / 77.5                 142.2 / 147.5
+// With one routed expert beside four shared ones and short rows the two sides lie close together from five per unit on, and inside
+// is the slower one where its workgroups fill their rounds badly: the line is five.  The same two sides, S = 4, k = 1: H = 256, 5 per unit
+// 26.4 / 26.9, 6 30.9 / 29.9, 7 35.1 / 33.2; H = 768, 6 36.9 / 36.9, 7 40.5 / 41.6; H = 1024, 5 34.0 / 36.9, 6 42.3 / 41.1, 8 51.6 / 50.9; H = 1280, 8
+// 58.2 / 63.3; H = 2048, 14 131 / 136; k = 2, H = 256, 7 36.9 / 39.4; S = 3, k = 1, H = 256, 7 36.0 / 39.7.
 // As single items (their chain of additions is twice as long) beyond the first line, with eight experts chosen, whose routed items
 // leave the persistent launch as well: H = 2304, 10 per unit 180 / 168, 14 per unit 248 / 223; H = 3072, 14 289 / 256; H = 3456, 14 297 / 286.
 inline bool draft_shared_inside(const Shape &s, int n_cu)
@@ -114,7 +118,8 @@ inline bool draft_shared_inside(const Shape &s, int n_cu)
     const long items = (long)s.S * (s.I / 16);
     if (s.T != 1 || s.S == 0) return false;
     if (items <= 3L * n_cu || items * 256 <= (long)n_cu * s.H) return true;
-    return (items <= 7L * n_cu || items * 128 <= (long)n_cu * s.H) && slice_pairs(s, true, n_cu);
+    const bool few_routed = 4 * s.k <= s.S && s.H <= 1024;
+    return (few_routed ? items <= 5L * n_cu : items <= 7L * n_cu || items * 128 <= (long)n_cu * s.H) && slice_pairs(s, true, n_cu);
 }
 
 // One token through the persistent kernel: from two items per compute unit on, where the launch carries no shared

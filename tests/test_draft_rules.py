@@ -68,3 +68,11 @@ def test_many_shared_items_run_inside_only_as_pairs(n_cu):
                         inside += 1
                         assert r.rule_one_token_form(H, 64, I, k, 128, S, 1, n_cu, 2 * n_cu) == 1, (H, I, S, k)
     assert inside and outside
+
+
+@pytest.mark.parametrize("H,I,k,S,inside", [(256, 5120, 1, 4, True), (256, 6144, 1, 4, False), (256, 7168, 1, 4, False), (512, 7168, 1, 4, False),
+                                            (1024, 6144, 1, 4, False), (1024, 8192, 1, 4, False), (1280, 8192, 1, 4, True), (2048, 16384, 1, 4, True),
+                                            (256, 7168, 2, 4, True), (1024, 8192, 2, 4, True), (256, 9536, 1, 3, True), (256, 14336, 1, 2, True)])
+def test_shared_experts_beside_one_routed(H, I, k, S, inside):
+    """Four shared experts beside one routed and short rows: beyond five items per unit (256 units) their own launches are faster."""
+    assert bool(rules().rule_shared_inside(H, 8, I, k, 64, S, 256)) == inside
