@@ -83,17 +83,21 @@ inline bool draft_fits(const Shape &s, int tokens, bool sym)
 // Items per workgroup.  Every item adds to all of y, and fp32 additions to one address follow each other at 25 ns (400 workgroups
 // adding to the same 4096 floats take 13.8 us, to four copies of them 7.9, without adding 3.8), so that n items cannot
 // end less than n x 25 ns after the first one, and beyond 256 items some units have two, whose second one also starts late: its
-// loads wait until the first one's have returned.  Two items in one workgroup halve the chain and give every unit the same.
-// Not below one item per unit, where pairs leave units empty, and with long items not beyond two per unit, where a second
+// loads wait until the first one's have returned.  Two items in one workgroup halve the chain and start together.  Below two
+// items per unit they leave units empty: up to one item per unit that costs more than the shorter chain saves (at exactly one with long
+// rows and no shared experts inside), beyond it less.  With long items not beyond two per unit, where a second
 // round of workgroups costs more than the chain.  us per call, single / paired (items):
 //   H = 4096: 224 18.5 / 19.6, 256 20.0 / 20.0, 320 23.7 / 21.5, 384 25.7 / 24.7, 576 38.9 / 47.0, 768 44.4 / 49.8
 //   H = 2048: 192 14.6 / 17.1, 224 14.3 / 15.1, 240 15.0 / 15.2, 320 18.8 / 16.4, 504 24.4 / 20.6, 624 30.9 / 28.7, 768 35.6 / 28.9
 //   H = 512: 240 13.0 / 12.6, 504 21.1 / 15.8, 768 26.0 / 17.9
+//   256 items, groups of 32: H = 1024 14.6 / 13.8, 2048 16.9 / 17.1, 4096 20.6 / 22.2, 5120 24.1 / 25.4, 7168 28.3 / 30.5; groups of
+//   128: H = 1024 14.5 / 13.6, 2048 16.0 / 15.8, 4096 21.0 / 20.7, 5120 22.8 / 23.6, 7168 28.0 / 28.1; 128 of them
+//   shared ones': H = 2048 15.1 / 13.5, 4096 20.9 / 20.4; 264 items: H = 8192 38.0 / 30.0
 inline bool slice_pairs(const Shape &s, bool shared_inside, int n_cu)
 {
     const int items = s.k * (s.I / 32) + (shared_inside ? s.S * (s.I / 16) : 0), routed = s.k * (s.I / 32) / 2;
     // (a unit holds one workgroup of two items: those that reduce the router rows have to be running together)
-    return items >= n_cu && (items <= 2 * n_cu || s.H <= 2048) && router_workgroups(s.E, 2, routed) <= n_cu &&
+    return (items > n_cu || (items == n_cu && (s.H < 2048 || shared_inside))) && (items <= 2 * n_cu || s.H <= 2048) && router_workgroups(s.E, 2, routed) <= n_cu &&
            slice_dynamic_lds(s.H, s.g, s.E, 2) <= kDraftLds;
 }
 

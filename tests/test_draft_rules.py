@@ -76,3 +76,18 @@ def test_many_shared_items_run_inside_only_as_pairs(n_cu):
 def test_shared_experts_beside_one_routed(H, I, k, S, inside):
     """Four shared experts beside one routed and short rows: beyond five items per unit (256 units) their own launches are faster."""
     assert bool(rules().rule_shared_inside(H, 8, I, k, 64, S, 256)) == inside
+
+
+@pytest.mark.parametrize("n_cu", UNITS)
+def test_one_item_per_unit_runs_single_items(n_cu):
+    """With exactly one item per unit and long rows single items fill the device and pairs half of it; one more item and some unit
+    would have two."""
+    r = rules()
+    k = 4
+    I = n_cu // k * 32
+    for H, form in ((1024, 1), (2048, 0), (4096, 0), (8192, 0)):
+        assert r.rule_one_token_form(H, 8, I, k, 64, 0, 0, n_cu, 2 * n_cu) == form
+        assert r.rule_one_token_form(H, 8, I + 64, k, 64, 0, 0, n_cu, 2 * n_cu) == 1
+        assert r.rule_one_token_form(H, 8, I - 64, k, 64, 0, 0, n_cu, 2 * n_cu) == 0
+        if n_cu >= 64:                                     # half of the items a shared expert's
+            assert r.rule_one_token_form(H, 8, I // 2, k, 64, 2, 1, n_cu, 2 * n_cu) == 1
