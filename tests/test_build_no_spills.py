@@ -39,6 +39,7 @@ def test_draft_kernel_instantiations_do_not_spill():
     for src, kernel, count in (("draft_int4.hip", "draft_stream_kernel", 36),     # 2 windows x 3 token capacities x 3 group sizes x 2 formats
                                ("draft_int4.hip", "draft_stream_sums_kernel", 18),    # 3 token capacities x 3 group sizes x 2 formats
                                ("draft_slice.hip", "draft_fused_kernel", 12),     # with and without shared experts x 3 group sizes x 2 formats
+                               ("draft_slice.hip", "draft_pair_kernel", 12),      # the same, two items per workgroup
                                ("draft_prefill.hip", "prefill_tile_kernel", 12)): # (gate/up, down) x 3 group sizes x 2 formats
         blocks = _kernel_blocks(_assembly(src), kernel)
         assert len(blocks) == count, (src, len(blocks))

@@ -71,11 +71,22 @@ def test_one_token_with_shared_experts(H, I, g, S):
     ctx.close()
 
 
-@pytest.mark.parametrize("H,k,g,S", [(128, 2, 32, 0), (576, 2, 64, 0), (128, 2, 32, 2), (128, 1, 32, 4)])
-def test_one_token_with_many_items(H, k, g, S):
-    """I = 8192: 256 work items per selected expert (two experts: the persistent kernel runs the call), and
-    with two or more shared experts more 16-row items than the call's own launch takes."""
-    cfg = LayerConfig(73, "many%d" % H, H, 4, 8192, k, g, S, 1)
+def one_token_form(cfg):
+    """(whether the shared experts run inside, the form) of a one-token call on 256 units: 0 single items, 1 pairs, 2 persistent."""
+    if torch.cuda.get_device_properties(0).multi_processor_count != 256:
+        pytest.skip("the forms are stated for 256 compute units")
+    shape = (cfg.hidden, cfg.n_experts, cfg.inter, cfg.top_k, cfg.group_size, cfg.n_shared)
+    inside = rules().rule_shared_inside(*shape, 256)
+    return bool(inside), rules().rule_one_token_form(*shape, inside, 256, 512)
+
+
+@pytest.mark.parametrize("H,I,k,g,S,form", [(128, 8192, 2, 32, 0, (False, 1)), (576, 8192, 2, 64, 0, (False, 1)), (128, 8192, 2, 32, 2, (True, 1)),
+                                            (128, 8192, 1, 32, 4, (False, 1)), (1088, 5120, 4, 32, 0, (False, 2)), (2304, 8192, 2, 64, 0, (False, 2))])
+def test_one_token_with_many_items(H, I, k, g, S, form):
+    """256 to 640 work items of routed experts, then three tokens: short rows run as pairs, with two shared experts inside and with
+    four, which are more 16-row items than the call's own launch takes; longer rows run in the persistent kernel, without sums of y in LDS and with."""
+    cfg = LayerConfig(73, "many%d" % H, H, 4, I, k, g, S, 1)
+    assert one_token_form(cfg) == form
     ctx = B.Context(0)
     for symmetric in (False, True):
         if symmetric and B.int4_expert_scale_bytes(B.LayerDesc.from_config(cfg)) == 0:
@@ -92,7 +103,6 @@ def test_one_token_with_many_items(H, k, g, S):
             assert np.array_equal(to_np(r["ids"]), ref["ids"][t0:t1])
             assert rel_err(to_np(r["y"]), ref["y"][t0:t1]) <= TOL_DRAFT
     ctx.close()
-
 
 
 @pytest.mark.parametrize("g", [32, 64, 128])
@@ -116,14 +126,16 @@ def test_stream_windows_of_eight(g):
     ctx.close()
 
 
-@pytest.mark.parametrize("H,I,E,k,g,S", [(64, 4096, 3, 2, 32, 0), (320, 2048, 4, 4, 64, 0), (2112, 2752, 5, 3, 64, 0), (1088, 4160, 6, 4, 32, 0),
+@pytest.mark.parametrize("H,I,E,k,g,S", [(64, 4096, 3, 2, 32, 0), (320, 2048, 4, 4, 64, 0), (2112, 2752, 5, 3, 64, 0), (1024, 4160, 6, 4, 32, 0),
+                                         (320, 2048, 8, 8, 64, 0), (576, 5120, 6, 5, 64, 0),
                                          (512, 2048, 4, 1, 64, 2), (2304, 1024, 8, 8, 128, 2), (192, 8192, 3, 2, 64, 2),
                                          (192, 1024, 128, 1, 64, 4), (64, 1024, 67, 2, 32, 4), (1088, 2048, 9, 1, 32, 4)])
 def test_one_token_with_pairs_of_items(H, I, E, k, g, S):
     """Calls of one token with 256 work items and more, which run two items per workgroup: fewer row tiles or groups than waves, ragged
-    shares of both, exactly 256 and 512 items, more than two per unit with short rows, and shared experts beside the routed ones; two router rows to a
+    shares of both, exactly 256 and 512 items, more than two per unit (520 and 800, short rows), and shared experts beside the routed ones; two router rows to a
     workgroup, an odd last one, and several rounds of them (128 and 67 experts over 16 and 32 routed workgroups)."""
     cfg = LayerConfig(81, "pair%d" % H, H, E, I, k, g, S, 1)
+    assert one_token_form(cfg) == (S > 0, 1)
     ctx = B.Context(0)
     for symmetric in (False, True):
         if symmetric and B.int4_expert_scale_bytes(B.LayerDesc.from_config(cfg)) == 0:
@@ -172,9 +184,7 @@ def test_shared_experts_on_the_line_run_inside(H, I, k, S, g, inside):
     runs the shared experts and no launch of the bf16 kernels is made; beyond, the routed experts run alone (as pairs, or in the persistent
     launch) and leave the plan for the bf16 kernels."""
     cfg = LayerConfig(74, "line", H, 2, I, k, g, S, 1)
-    if torch.cuda.get_device_properties(0).multi_processor_count != 256:
-        pytest.skip("the line is stated for 256 compute units")
-    assert bool(rules().rule_shared_inside(H, 2, I, k, g, S, 256)) == inside
+    assert one_token_form(cfg)[0] == inside
     ctx = B.Context(0)
     L = build_layer(cfg)
     A = oracle_arrays(L)
