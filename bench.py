@@ -269,7 +269,8 @@ def resident_leg(args, cfg, ctx, dev):
         roofline, table = roofline_table(cfg, kern, nbytes, ROOT)
         extra["kernels"] = table
         extra["kernel_us"] = {n: round(v["us_avg"], 2) for n, v in kern.items()}
-        # the same bytes as one draft call, read by a kernel that only reads (practical ceiling)
+        # the same bytes as one draft call, read by a kernel that only reads (practical ceiling): as many workgroups of eight waves as
+        # the call has work items (the draft kernel's own workgroups may hold two)
         grid = k * cfg.inter // 32
         extra["stream_read_ceiling"] = stream_ceiling(ctx, torch, [D.q_blob for D in layers],
                                                       nbytes["draft_fused_kernel"], grid)
@@ -814,8 +815,8 @@ def draft_table_leg(args, cfg, ctx, dev):
 
 def read_probe_leg(args, cfg, ctx, dev):
     """--read-probe: moe_stream_read_probe (a kernel that only reads) over the bytes of one one-token draft call,
-    cold data (the int4 blobs of distinct layers in rotation), for several grids: the draft kernel's own launch
-    shape (k I / 32 workgroups) and grids that fill the compute units evenly.  A side measurement."""
+    cold data (the int4 blobs of distinct layers in rotation), for several grids: as many workgroups as the call has
+    work items (k I / 32) and grids that fill the compute units evenly.  A side measurement."""
     import torch
     import synth
     from paper_2511_14102_amd.harness import DeviceLayer
@@ -833,7 +834,7 @@ def read_probe_leg(args, cfg, ctx, dev):
             rows.setdefault(str(grid), []).append(r["us"])
     print(json.dumps({"metric": "read-only kernel over the bytes of one draft call, 1 GPU", "unit": "us", "data": "synthetic",
                       "config": {"workload": "%s-shaped MoE layer, %d distinct layers rotating" % (cfg.name, n_layers)},
-                      "bytes": nbytes // 1024 * 1024, "compute_units": n_cu, "draft_kernel_workgroups": own,
+                      "bytes": nbytes // 1024 * 1024, "compute_units": n_cu, "draft_work_items": own,
                       "us_by_workgroups": rows}), flush=True)
 
 

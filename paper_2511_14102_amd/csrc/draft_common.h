@@ -130,7 +130,8 @@ struct FusedArgs {
 // of them (T2: T rounded up to a power of two) splitting H, so that a row costs one round of loads and
 // one barrier however many tokens there are (one token after another took 6 us for 8 tokens).  fp64
 // accumulation of exact fp32 products.  Before it publishes, the workgroup clears its share of y.
-// ROWS = 2 (one token): it takes two neighbouring rows at a time, half of its waves each.
+// ROWS = 2 (one token): it takes two neighbouring rows at a time, half of its waves each.  us per pass, one row / two: H = 2048, E = 128, 22
+// routed workgroups 255 / 204; phi shape (E = 16) 191.5 / 193.5, which is what the room for other calls' workgroups costs (router_workgroups).
 template <int NW, int ROWS>
 __device__ inline void publish_router_rows(const uint16_t *__restrict__ xin, const FusedArgs &a, int b, int nprod,
                                            double (&s_part)[NW])

@@ -20,12 +20,12 @@
 // multiplied.  With several tokens a call has many items (every distinct expert of the call,
 // I / 32 slices each) and this wins clearly over one workgroup per item.
 //
-// Bound: the weight stream at one workgroup per compute unit (phi shape, 4 tokens: 202 MB in 46.4 us, of which
+// Bound: the weight stream at one workgroup per compute unit (phi shape, 4 tokens: 202 MB in 45 to 47 us, of which
 // the start takes about 5 us), and with few tokens per expert also the vector work per tile.  What the stream
 // needs is that its loads stay in flight: a window slot is unpacked and refilled at once, addresses are
 // buffer offsets without clamps, and nothing under a branch counts on the vector memory counter (an empty slot's
 // atomics go out of range instead).  us per call before these: phi 4 tokens 57.5, mixtral 3 tokens, symmetric
-// 87 (now 83), qwen3 8 tokens 60.6 (now 40).
+// 87 (now 70 to 78), qwen3 8 tokens 60.6 (now 36 to 37).
 //
 // Cross-workgroup protocol (one bounded wait, no cache flushes):
 //   1. router row e is reduced by workgroup e (mod router_workgroups), which first clears its share of y
@@ -93,9 +93,11 @@ __device__ __forceinline__ void draft_stream(const uint16_t *__restrict__ xin, c
 
     // ---- 1b. (while the router result travels) x goes to LDS, and its sum per group: 4 UPG neighbouring threads hold a group.
     // (Summed from LDS, by threads that found their token and group with divisions, this was 2.4 us of the start of a call with 4 tokens
-    // of the phi shape and 3.5 us with 8 of the qwen3 shape, where the routing's result is there after 3 us.)
+    // of the phi shape and 3.5 us with 8 of the qwen3 shape, where the routing's result is there after 3 us; before / now with the shares of
+    // split_items, us per pass: phi 380 / 373, mixtral, 3 tokens 281 / 277, qwen3 300 / 294; H = 3072, E = 24, 5 tokens 426 / 399.)
     const int nx = T * (H / 8);                  // pieces of eight values
-    // (whole quotients below 2^19: i + 1/2 over a divisor is further from a whole number than the reciprocal's error)
+    // (whole quotients of a dividend below 2^21 by a reciprocal: (i + 1/2) / d is at least 1 / 2d away from a whole number, and the rounding of
+    // reciprocal and product, 1.5 x 2^-23 of it, is less.  i < 2^16 here, as H <= 2^16 and T <= 8; items < 2^19, as T k <= 128 and I / 32 <= 2^12.)
     const float per_token = 8.f * __builtin_amdgcn_rcpf((float)H);
     auto keep = [&](int i, u32x4 v) {
         float s = ((bf16_lo(v.x) + bf16_hi(v.x)) + (bf16_lo(v.y) + bf16_hi(v.y))) +
@@ -249,8 +251,8 @@ __device__ __forceinline__ void draft_stream(const uint16_t *__restrict__ xin, c
     };
 
     // Work split: the items (distinct experts ascending, I / 32 slices each) are dealt evenly, n / G
-    // each, the last n % G workgroups one more (the first ones, which reduce the router rows, begin later: phi, 4 tokens
-    // 45.7 / 45.3 us; H = 384, E = 5, I = 3200, 2 tokens 16.9 / 16.5).
+    // each, the last n % G workgroups one more (the first ones, which reduce the router rows, begin later: us per pass, the
+    // first / the last ones, phi, 4 tokens 367.4 / 363.9, qwen3, 8 tokens 299.9 / 292.3; H = 384, E = 5, I = 3200, 2 tokens 223.0 / 214.0).
     int it_begin = 0, it_end = 0;
     Item cur, nxt;
     auto split_items = [&](int n_items) {
