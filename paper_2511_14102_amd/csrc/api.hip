@@ -432,10 +432,10 @@ int moe_draft_layer_int4_noalloc(moe_ctx *ctx, const moe_layer_desc *desc,
 }
 
 // workspace of a prefill call: routing weights and slots [T k], the experts' counts and lists, the
-// partial logits, the item count (one 256-byte line), the items, the operand tiles of x and of h (two planes) with
-// their group sums, a tile of zeros, and the per-slot outputs.
+// partial logits, the item count (one 256-byte line), the items, the operand tiles of x and of h with
+// their group sums and (g = 128) scales, a tile of zeros, and the per-slot outputs.
 struct PrefillLayout {
-    size_t w_all, count, list, parts, slot_of, n_items, items, xt, x_sums, h_hi, h_lo, h_sums, zeros, obuf, total;
+    size_t w_all, count, list, parts, slot_of, n_items, items, xt, x_sums, h, h_sums, h_scales, zeros, obuf, total;
     int max_items;
 };
 static PrefillLayout prefill_layout(const moe_layer_desc &d, int T)
@@ -456,9 +456,9 @@ static PrefillLayout prefill_layout(const moe_layer_desc &d, int T)
     L.items = o;   o += align256(room * sizeof(PrefillItem));
     L.xt = o;      o += align256(B.xt);
     L.x_sums = o;  o += align256(B.x_sums);
-    L.h_hi = o;    o += align256(B.h_plane);
-    L.h_lo = o;    o += align256(B.h_plane);
+    L.h = o;       o += align256(B.h);
     L.h_sums = o;  o += align256(B.h_sums);
+    L.h_scales = o; o += align256(B.h_scales);
     L.zeros = o;   o += align256(B.zeros);
     L.obuf = o;    o += align256(B.obuf);
     L.total = o;
@@ -511,7 +511,7 @@ int moe_draft_prefill_int4(moe_ctx *ctx, const moe_layer_desc *desc,
     p.count = (const int32_t *)(ws + L.count); p.list = (const int32_t *)(ws + L.list); p.slot_of = (int32_t *)(ws + L.slot_of);
     p.w_all = (const float *)(ws + L.w_all);
     p.xt = ws + L.xt; p.x_sums = ws + L.x_sums;
-    p.h_hi = ws + L.h_hi; p.h_lo = ws + L.h_lo; p.h_sums = ws + L.h_sums; p.zeros = ws + L.zeros;
+    p.h = ws + L.h; p.h_sums = ws + L.h_sums; p.h_scales = ws + L.h_scales; p.zeros = ws + L.zeros;
     p.obuf = (float *)(ws + L.obuf);
     p.y = y;
     p.shared = shared; p.shared_stride = moe_bf16_expert_bytes(desc);

@@ -40,6 +40,15 @@
 // call's kernels, three launches each, they took 410 of the 605 us of a layer of the dsv2lite shape
 // with 333 tokens.)
 //
+// The down part with groups of 128 (run_e4m3) runs on the 16x16x128 e4m3 products, which take a whole group at twice the rate: a
+// code byte is an e4m3 number as it stands (three vector instructions per word of codes instead of eight), h is a sum of four e4m3
+// planes with one power of two per token and group, which are as many operand bytes and as much time on the matrix cores as two bf16
+// numbers, in half as many instructions, and hold more of h.  A product keeps the vector ALU waiting 22 of its 32 clocks (measured alone: clocks = 22 + 4 per
+// vector instruction beside it, 32 at least), a bf16 product 15 of 16.  us of the down launch, two bf16 numbers / this: phi shape, 512 tokens 152 / 138, dsv2lite, 333 57.4 / 53.5;
+// mixtral, 4096 1794 / 1727 (where the clock falls to 1.6 GHz: power); the cut into planes is nothing measurable of the gate/up launch.
+// (x as two planes in the gate/up part, whose cut took 5, 6 and 16 us of the stage launch: 192 / 183, 71 / 70 and 2206 / 2091 us, but two planes do not hold every bf16 x, and
+// with a third one where they do not it was no gain.)
+//
 // Arithmetic.  Codes become the exact bf16 integers 16 + q; a group's products are summed by the
 // matrix cores (16x16x32 bf16, fp32 accumulate), starting at -24 (sum of the group's x), so that the sum
 // is that of (q - 8) x, and enter the totals with one fused multiply-add by the group's scale.  What the
@@ -77,7 +86,8 @@ constexpr int kXcds = 8;
 // four, three, two or one.  n_items: their count, then each segment's.  Where prefill_by_size does not choose this order, all
 // items are in the first segment, expert by expert.
 constexpr int kSegments = 4;
-constexpr float kOffset = -24.f;                  // factor of a stored group sum: takes 16 + q to q - 8
+// Factor of a stored group sum: takes 16 + q (bf16 codes) or q (e4m3 codes) to q - 8
+constexpr float kOffset = -24.f, kOffsetE4m3 = -8.f;
 
 // Items of an expert in the first segment (lg: log2 of an item's tokens), and the segment of its last item (0: it has none elsewhere)
 __device__ inline int head_items(int assignments, int lg, bool by_size) {
@@ -93,10 +103,11 @@ struct TileArgs {
     size_t stride_q, stride_sz;
     const PrefillItem *items;
     const int32_t *n_items;          // [1 + segments]
-    const char *act0, *act1;         // operand tiles [(item nk + u) 4 + tb] of 1 KiB: x, or h and its remainder
-    const char *act_sums;            // -24 x group sums, fp32 [(item 4 nz + group) 64 + token]; nz = ceil(groups / 4)
+    const char *act;                 // operand tiles of x, nk 4 KiB an item, or of h, twice that (layouts: below)
+    const char *act_sums;            // group sums times the offset, fp32 [(item 4 nz + group) 64 + token]; nz = ceil(groups / 4)
+    const char *act_scales;          // h, g = 128: a group's power of two, a byte each [((item nz + group / 4) 64 + token) 4 + group % 4]
     const char *zeros;               // 4 KiB of zeros
-    char *h_hi, *h_lo, *h_sums;      // gate/up: out, the same layouts over I
+    char *h, *h_sums, *h_scales;     // gate/up: out, the same layouts over I
     float *obuf;                     // down: out [item 64 + token][H]
     const char *shared;              // bf16 blobs of the shared experts (experts E, E + 1, ...)
     size_t shared_stride;
@@ -120,6 +131,88 @@ __device__ inline bf16x8 unpack8_16(uint32_t w, UnpackConsts k) {
     r.w = ((w >> 9) & k.mask) | k.magic;
     return __builtin_bit_cast(bf16x8, r);
 }
+
+// ---- g = 128: the codes as e4m3 numbers, x and h as sums of e4m3 numbers
+// A code byte 0 .. 15 IS the e4m3 number q 2^-9 (below 8 a denormal), so the 8 codes of a word become operand bytes with
+// two masks and a shift: codes 0, 4, 1, 5 in the first four bytes, 2, 6, 3, 7 in the others.
+typedef __attribute__((ext_vector_type(8))) int i32x8;
+__device__ inline void unpack8_e4m3(uint32_t w, uint32_t mask, int &lo, int &hi) {
+    lo = (int)(w & mask);
+    hi = (int)((w >> 4) & mask);
+}
+
+// h = 2^(scale - 127) (p0 + p1 / 16 + p2 / 256 + p3 / 4096), p_i e4m3, one scale (a byte that the matrix cores apply) per token and
+// group of 128, which puts the group's largest value in [128, 256).  What the planes leave of h: 4e-7 of the norm; two bf16 numbers left 2.5e-6.
+constexpr int kPlanes = 4, kPlaneShift = 4;
+// the scales of the code bytes (2^9) per plane, the plane's step in them
+constexpr uint32_t kCodeScales = 136u | (136u - kPlaneShift) << 8 | (136u - 2 * kPlaneShift) << 16 | (136u - 3 * kPlaneShift) << 24;
+
+// from the group's largest magnitude: the scale byte, what h is multiplied by, and back.  (The largest of values that are not all finite may be
+// any; the sums of the planes are then NaN, which takes all outputs of the token to NaN.)
+struct GroupScale {
+    uint32_t byte;
+    __device__ explicit GroupScale(float largest) {
+        const uint32_t e = __float_as_uint(largest) >> 23;
+        byte = (e < 32u ? 32u : e < 254u ? e : 254u) - 7u;
+    }
+    __device__ float up() const { return __uint_as_float((254u - byte) << 23); }
+    __device__ float down() const { return __uint_as_float(byte << 23); }
+};
+__device__ inline float largest8(const float (&v)[8])
+{
+    float m = fabsf(v[0]);
+#pragma unroll
+    for (int j = 1; j < 8; ++j) m = fmaxf(m, fabsf(v[j]));
+    return m;
+}
+
+// Eight h of a k-step (v, scaled; m: the largest of them) as planes; returns the sum of what the planes hold (scaled).  The matrix cores add the products of
+// eight neighbouring bytes on one grid, 2^-13 of the largest one's exponent (measured; the sums of eights meet in fp32).  So the
+// first two planes are rounded to a grid of 2^-10 of the eight's largest exponent first: with codes below 16 their products then
+// lie on the cores' grid and their sum is exact, and the next plane takes up what the grid left (what four bits leave, times the step, has no
+// larger exponent than the value, so the grid is the same for both).  Without this: 7.6e-5 of a group's sum, with it 4e-7, the bf16 form 2.5e-6.
+__device__ inline float split_planes(float (&v)[8], float m, uint32_t (&out)[kPlanes][2])
+{
+    // The exponent is that of the largest value as it is rounded, to the grid and then to four bits: the next one from 1.9375 - 2^-11 on (one
+    // exponent too low cost such an eight's sum 1e-3 of it).  2^-8 at least.
+    const uint32_t e = (__float_as_uint(m) + 0x81000u) >> 23;
+    const float grid = __uint_as_float(((e > 119u ? e : 119u) + 13u) << 23 | 0x400000u);      // 1.5 2^23 units of the grid
+    float sum = 0.f;
+#pragma unroll
+    for (int j = 0; j < 8; ++j) sum += v[j];
+#pragma unroll
+    for (int p = 0; p < kPlanes; ++p) {
+        const float up = (float)(1 << (p * kPlaneShift)), down = -1.f / up;
+        float t[8];
+#pragma unroll
+        for (int j = 0; j < 8; ++j) t[j] = p < 2 ? fmaf(v[j], up, grid) - grid : v[j] * up;
+        int lo = __builtin_amdgcn_cvt_pk_fp8_f32(t[0], t[4], 0, false), hi = __builtin_amdgcn_cvt_pk_fp8_f32(t[2], t[6], 0, false);
+        lo = __builtin_amdgcn_cvt_pk_fp8_f32(t[1], t[5], lo, true);
+        hi = __builtin_amdgcn_cvt_pk_fp8_f32(t[3], t[7], hi, true);
+        out[p][0] = (uint32_t)lo;
+        out[p][1] = (uint32_t)hi;
+        const auto a = __builtin_amdgcn_cvt_pk_f32_fp8(lo, false), b = __builtin_amdgcn_cvt_pk_f32_fp8(lo, true);
+        const auto c = __builtin_amdgcn_cvt_pk_f32_fp8(hi, false), d = __builtin_amdgcn_cvt_pk_f32_fp8(hi, true);
+        const float held[8] = {a[0], b[0], c[0], d[0], a[1], b[1], c[1], d[1]};
+#pragma unroll
+        for (int j = 0; j < 8; ++j) v[j] = fmaf(held[j], down, v[j]);       // (exact)
+    }
+#pragma unroll
+    for (int j = 0; j < 8; ++j) sum -= v[j];
+    return sum;
+}
+
+// the bytes of a scale word by which operands A and B are multiplied have to be constants of the instruction
+template <int SA, int SB>
+__device__ inline f32x4 mfma_e4m3(i32x8 a, i32x8 b, f32x4 c, uint32_t scale_a, uint32_t scale_b) {
+    return __builtin_amdgcn_mfma_scale_f32_16x16x128_f8f6f4(a, b, c, 0, 0, SA, (int)scale_a, SB, (int)scale_b);
+}
+
+// f(0), f(1), .. f(N - 1) with constants
+template <typename F, int... I>
+__device__ __forceinline__ void each(F &&f, std::integer_sequence<int, I...>) { (f(std::integral_constant<int, I>{}), ...); }
+template <int N, typename F>
+__device__ __forceinline__ void each(F &&f) { each(f, std::make_integer_sequence<int, N>{}); }
 
 // An fp32 value as three bf16 pieces (upper halves of p[0..2], exact), in the order in which the
 // two factors of the group-sum contraction pair up over eight k positions:
@@ -169,6 +262,7 @@ void prefill_tile_kernel(TileArgs a)
     constexpr int kZeroStages = 4 * KPG / SK;      // stages per four groups
     constexpr int kSums = SK * NP * 4 * 1024;      // one stage of operand tiles, then the sums of the groups that begin in it
     constexpr int kBuf = kSums + 1024;
+    constexpr int kRow = 36;                       // of h in LDS: 32 columns and 16 bytes against bank conflicts
     __shared__ __align__(1024) unsigned char s_x0[kBuf];
     __shared__ __align__(1024) unsigned char s_x1[kBuf];
     __shared__ __align__(1024) unsigned char s_x2[kBuf];
@@ -230,7 +324,8 @@ void prefill_tile_kernel(TileArgs a)
         else return s_x3;
     };
     const int my_k = DOWN ? wave >> 1 : wave;                        // the k-step (and plane) of a stage this wave requests
-    const char *act = ((DOWN && (wave & 1)) ? a.act1 : a.act0) + (size_t)(DOWN ? item : it.src) * nk * 4096;
+    const char *tiles_of_item = a.act + (size_t)(DOWN ? 2 * item : it.src) * nk * 4096;
+    const char *act = tiles_of_item + (DOWN && (wave & 1) ? (size_t)nk * 4096 : 0);       // bf16: [k-step][tb], h and then its remainder
 
     // this wave's operand tiles of stage n into buffer j
     auto request = [&](int n, auto j, auto ntb_c) {
@@ -271,6 +366,61 @@ void prefill_tile_kernel(TileArgs a)
     constexpr std::integral_constant<int, 2> k2{};
     constexpr std::integral_constant<int, 3> k3{};
 
+    // h of a routed item, g = 128: the workgroup's 128 columns are a group, this wave's 32 its k-step `wave`.  s_h: [token][column]
+    auto finish_e4m3 = [&](auto ntb_c, const float *s_h) {
+        constexpr int NTB = decltype(ntb_c)::value;
+        float (*s_max)[kItemTokens] = reinterpret_cast<float (*)[kItemTokens]>(s_x1 + kSums);
+        float (*s_sum)[kItemTokens] = reinterpret_cast<float (*)[kItemTokens]>(s_x0 + kSums);
+        auto load = [&](int tb, float (&h)[8]) {                  // token r of the block, columns 8 c ..
+            const f32x4 h0 = *reinterpret_cast<const f32x4 *>(&s_h[(16 * tb + r) * kRow + 8 * c]);
+            const f32x4 h1 = *reinterpret_cast<const f32x4 *>(&s_h[(16 * tb + r) * kRow + 8 * c + 4]);
+#pragma unroll
+            for (int j = 0; j < 4; ++j) { h[j] = h0[j]; h[j + 4] = h1[j]; }
+        };
+        float m8[NTB];
+#pragma unroll
+        for (int tb = 0; tb < NTB; ++tb) {
+            float h[8];
+            load(tb, h);
+            m8[tb] = largest8(h);
+            float m = fmaxf(m8[tb], __shfl_xor(m8[tb], 16));
+            m = fmaxf(m, __shfl_xor(m, 32));
+            if (c == 0) s_max[wave][16 * tb + r] = m;
+        }
+        __syncthreads();
+        const int GI = I / 128;
+        char *out = a.h + ((size_t)item * GI + col) * 32768 + (wave >> 1) * 1024 + lane * 16 + (wave & 1) * 8;
+#pragma unroll
+        for (int tb = 0; tb < NTB; ++tb) {
+            float h[8];
+            load(tb, h);
+            const int tok = 16 * tb + r;
+            const GroupScale gs(fmaxf(fmaxf(s_max[0][tok], s_max[1][tok]), fmaxf(s_max[2][tok], s_max[3][tok])));
+            const float up = gs.up();
+#pragma unroll
+            for (int j = 0; j < 8; ++j) h[j] *= up;
+            uint32_t planes[4][2];
+            float sum = split_planes(h, m8[tb] * up, planes) * gs.down();
+#pragma unroll
+            for (int p = 0; p < 4; ++p)
+                *reinterpret_cast<uint2 *>(out + tb * 8192 + p * 2048) = make_uint2(planes[p][0], planes[p][1]);
+            sum += __shfl_xor(sum, 16);
+            sum += __shfl_xor(sum, 32);
+            if (c == 0) {
+                s_sum[wave][tok] = sum;
+                if (wave == 0) a.h_scales[(((size_t)item * ((GI + 3) / 4) + col / 4) * kItemTokens + tok) * 4 + col % 4] = (char)gs.byte;
+            }
+        }
+        __syncthreads();
+        // the group's sums; the last column of workgroups also clears what is left of the last tile of four groups
+        const int tok = tid & 63, gi = col + (tid >> 6);
+        const bool pad = gi >= GI && gi / 4 == (GI - 1) / 4;
+        if (tok < 16 * NTB && (gi == col || pad)) {
+            const float v = gi == col ? (s_sum[0][tok] + s_sum[1][tok]) + (s_sum[2][tok] + s_sum[3][tok]) : 0.f;
+            reinterpret_cast<float *>(a.h_sums)[((size_t)item * ((GI + 3) / 4) * 4 + gi) * kItemTokens + tok] = kOffsetE4m3 * v;
+        }
+    };
+
     // The results of an item: lane (r, c) holds, per row block d and token block, row 16 d + r of tokens
     // 4 c + i.
     auto finish = [&](auto ntb_c, auto &tot) {
@@ -295,7 +445,6 @@ void prefill_tile_kernel(TileArgs a)
             __syncthreads();
             float (*s_hsum)[kItemTokens] = reinterpret_cast<float (*)[kItemTokens]>(s_x0 + kSums);
             float *s_h = reinterpret_cast<float *>(wave == 0 ? s_x0 : wave == 1 ? s_x1 : wave == 2 ? s_x2 : s_x3);
-            constexpr int kRow = 36;                                  // 32 columns and 16 bytes against bank conflicts
 #pragma unroll
             for (int tb = 0; tb < NTB; ++tb) {
 #pragma unroll
@@ -307,7 +456,8 @@ void prefill_tile_kernel(TileArgs a)
                     }
             }
             __builtin_amdgcn_wave_barrier();
-            const size_t slice = (size_t)item * (I / 32) + tile;
+            if (KPG == 4 && routed) { finish_e4m3(ntb_c, s_h); return; }
+            char *h_of_item = a.h + (size_t)item * (I / 32) * 8192 + (size_t)tile * 4096;
 #pragma unroll
             for (int tb = 0; tb < NTB; ++tb) {
                 const f32x4 h0 = *reinterpret_cast<const f32x4 *>(&s_h[(16 * tb + r) * kRow + 8 * c]);
@@ -323,10 +473,10 @@ void prefill_tile_kernel(TileArgs a)
                     if (j & 1) { hi[j >> 1] |= hb << 16; lo[j >> 1] |= lb << 16; }
                     else { hi[j >> 1] = hb; lo[j >> 1] = lb; }
                 }
-                const size_t t = (slice * 4 + tb) * 1024 + lane * 16;
                 if (mine) {
-                    *reinterpret_cast<u32x4 *>(a.h_hi + t) = (u32x4){hi[0], hi[1], hi[2], hi[3]};
-                    *reinterpret_cast<u32x4 *>(a.h_lo + t) = (u32x4){lo[0], lo[1], lo[2], lo[3]};
+                    char *t = h_of_item + tb * 1024 + lane * 16;
+                    *reinterpret_cast<u32x4 *>(t) = (u32x4){hi[0], hi[1], hi[2], hi[3]};
+                    *reinterpret_cast<u32x4 *>(t + (size_t)(I / 32) * 4096) = (u32x4){lo[0], lo[1], lo[2], lo[3]};
                 }
                 sum += __shfl_xor(sum, 16);
                 sum += __shfl_xor(sum, 32);
@@ -353,9 +503,6 @@ void prefill_tile_kernel(TileArgs a)
 
     // an item of a routed expert with NTB token blocks (a compile-time count: no branch inside a stage)
     auto run = [&](auto ntb_c) {
-        // exits between the stages of a trip, for few k-steps (H = 256: gate/up 9.1 -> 7.6 us); not where a group spans
-        // two stages: with them those loops spill
-        constexpr bool kExits = SK >= KPG;
         constexpr int NTB = decltype(ntb_c)::value;
         constexpr int EW = KPG == 1 || (KPG == 2 && NTB < 4) ? 4 : 2;     // groups of entries in flight (four more spill)
         f32x4 tot[4][NTB], acc[4][NTB];
@@ -443,8 +590,7 @@ void prefill_tile_kernel(TileArgs a)
             if constexpr ((J + 3) * SK % KPG == 0) request_sums(n + 3, std::integral_constant<int, (J + 3) & 3>{});
             constexpr bool kZeros = !SYM && J % kZeroStages == 0;
             if constexpr (kZeros) {
-                if (kZeroStages <= 4 || n % kZeroStages == 0) add_zeros();
-                else add_scaled(NTB - 1);
+                add_zeros();
                 load_zeros(n / kZeroStages + 1);
             }
 #pragma unroll
@@ -494,27 +640,200 @@ void prefill_tile_kernel(TileArgs a)
 #pragma unroll
         for (int d = 0; d < 4; ++d) wb[0][d] = unpack8_16(win[0][d], uk);
         win[0] = load_codes(kWin);
-        if constexpr (kExits) {
-            for (int n = 0; ; n += 4) {
-                stage(n, k0);
-                if (n + 1 >= ns) break;
-                stage(n + 1, k1);
-                if (n + 2 >= ns) break;
-                stage(n + 2, k2);
-                if (n + 3 >= ns) break;
-                stage(n + 3, k3);
-                if (n + 4 >= ns) break;
-            }
-        } else {
-            for (int n = 0; n < ns; n += 4) {
-                stage(n, k0);
-                stage(n + 1, k1);
-                stage(n + 2, k2);
-                stage(n + 3, k3);
-            }
+        for (int n = 0; ; n += 4) {                // exits between the stages, for few k-steps (H = 256: gate/up 9.1 -> 7.6 us)
+            stage(n, k0);
+            if (n + 1 >= ns) break;
+            stage(n + 1, k1);
+            if (n + 2 >= ns) break;
+            stage(n + 2, k2);
+            if (n + 3 >= ns) break;
+            stage(n + 3, k3);
+            if (n + 4 >= ns) break;
         }
         // every last stage ends a group (k-steps past the end are zeros)
         add_scaled(NTB - 1);
+        finish(ntb_c, tot);
+    };
+
+    // an item of a routed expert, down part, g = 128, on 16x16x128 products of e4m3 operands: one product per plane, row block and token block takes a
+    // whole group.  A stage is NTB x 4 KiB of operand tiles, half of a group of h (in order: token block, plane, halves of a lane's 32 bytes).
+    auto run_e4m3 = [&](auto ntb_c) {
+        constexpr int NTB = decltype(ntb_c)::value, NPL = kPlanes;
+        constexpr int SPG = 2;                     // stages per group
+        constexpr int FS = 2 * NTB;                // operand tiles of 2 KiB per stage
+        constexpr int W = 2;                       // groups of codes in flight
+        f32x4 tot[4][NTB], acc[2][4];              // acc: products of a token block, and of the one before until they are scaled
+        u32x4 win[4 * W];                          // codes: group n's in slots 4 (n % W) ..
+        i32x8 wb[4];                               // operands of the group's row blocks
+        Entry<SYM> ent[2], ze;
+        float sc[4] = {0.f, 0.f, 0.f, 0.f}, zs[NTB];
+        uint32_t ts[NTB], tn[NTB];                 // scales of the tokens' groups, a byte each: this four, the next
+        uint32_t mask = 0x0f0f0f0fu, code_scales = kCodeScales;
+        asm volatile("" : "+s"(mask));
+        asm volatile("" : "+v"(code_scales));
+#pragma unroll
+        for (int d = 0; d < 4; ++d) {
+            acc[0][d] = acc[1][d] = (f32x4){0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+            for (int tb = 0; tb < NTB; ++tb) tot[d][tb] = (f32x4){0.f, 0.f, 0.f, 0.f};
+        }
+        const int stages = G * SPG;
+        const char *scales = a.act_scales + (size_t)item * nz * 256, *s_run = a.act_sums + (size_t)item * nz * 1024;
+        const char *z_run = szb + (size_t)tile * 256;
+        const uint32_t zstep = (uint32_t)(H / 64) * 256;
+        auto request_stage = [&](int n, auto j) {
+            const int in = n < stages ? n : stages - 1;
+            const char *src = tiles_of_item + (size_t)(in / SPG) * (SPG * 16384) + (in % SPG) * (NTB * 4096) + wave * (NTB * 1024);
+            const auto rsrc = __builtin_amdgcn_make_buffer_rsrc((void *)src, 0, NTB * 1024, 0x00027000);
+            unsigned char *dst = buffer(j) + wave * (NTB * 1024);
+#pragma unroll
+            for (int i = 0; i < NTB; ++i)
+                __builtin_amdgcn_raw_ptr_buffer_load_lds(rsrc, (lvoid)(dst + i * 1024), 16, lane * 16, i * 1024, 0, 0);
+            const auto sums = __builtin_amdgcn_make_buffer_rsrc((void *)(s_run + (size_t)(in / SPG) * 256), 0, 256, 0x00027000);
+            __builtin_amdgcn_raw_ptr_buffer_load_lds(sums, (lvoid)(buffer(j) + kSums), 4, lane * 4, 0, 0, 0);
+        };
+        // scales, and entries and sums of the zero points, of the q-th four groups (past the last: of the last again, the sums there are zeros)
+        auto load_four = [&](int q) {
+            const int in = q < nz ? q : nz - 1;
+#pragma unroll
+            for (int tb = 0; tb < NTB; ++tb) tn[tb] = *reinterpret_cast<const uint32_t *>(scales + in * 256 + (uint32_t)(r * 4) + tb * 64);
+            if constexpr (!SYM) {
+                const uint32_t grp = 4 * q + c, off = (grp < (uint32_t)G ? grp : G - 1) * zstep + r * 16;
+                ze.w = *reinterpret_cast<const u32x4 *>(z_run + off);
+#pragma unroll
+                for (int tb = 0; tb < NTB; ++tb)
+                    zs[tb] = *reinterpret_cast<const float *>(s_run + (size_t)in * 1024 + (uint32_t)((c * kItemTokens + r) * 4) + tb * 64);
+            }
+        };
+        auto add_scaled_rows = [&](int d, int tb, const f32x4 &v) {
+#pragma unroll
+            for (int i = 0; i < 4; ++i) tot[d][tb][i] = fmaf(sc[d], v[i], tot[d][tb][i]);
+            asm volatile("" : "+v"(tot[d][tb]));
+        };
+        auto unpack = [&](int slot, int d) {
+#pragma unroll
+            for (int s = 0; s < 4; ++s) {
+                int lo, hi;
+                unpack8_e4m3(win[slot * 4 + s][d], mask, lo, hi);
+                wb[d][2 * s] = lo;
+                wb[d][2 * s + 1] = hi;
+            }
+            asm volatile("" : "+v"(wb[d]));
+        };
+        auto stage = [&](int grp, auto j) {        // j: stage of a trip of four groups
+            constexpr int J = decltype(j)::value, Q = J / SPG, HALF = J % SPG;
+            constexpr int B0 = J & 3;
+            // issued behind the transfers that this stage needs: those of two stages (NTB + 1 each), and four loads of codes at the end
+            // and one of entries at the start of each group
+            constexpr int kLater = 2 * (NTB + 1) + (HALF == 0 ? 9 : 6);
+            static_assert(kLater < 64, "vmcnt");
+            __builtin_amdgcn_sched_barrier(0);
+            __builtin_amdgcn_s_waitcnt((kLater & 15) | ((kLater >> 4) << 14) | 0x0f70);
+            __builtin_amdgcn_s_barrier();
+            __builtin_amdgcn_sched_barrier(0);
+            const unsigned char *buf = buffer(std::integral_constant<int, B0>{});
+            constexpr int kA = 3;
+            u32x4 xa[kA][2];
+            f32x4 from[2];
+            auto read = [&](int fs) {
+                xa[fs % kA][0] = *reinterpret_cast<const u32x4 *>(&buf[fs * 2048 + lane * 16]);
+                xa[fs % kA][1] = *reinterpret_cast<const u32x4 *>(&buf[fs * 2048 + 1024 + lane * 16]);
+            };
+            auto read_sums = [&](int tb) { from[tb & 1] = *reinterpret_cast<const f32x4 *>(&buf[kSums + (16 * tb + 4 * c) * 4]); };
+            constexpr int F0 = HALF * FS;          // tile of the group with which the stage begins
+            read(0);
+            if (F0 % NPL == 0) read_sums(F0 / NPL);
+            read(1);
+            request_stage(grp * SPG + HALF + 3, std::integral_constant<int, (B0 + 3) & 3>{});
+            if constexpr (J == 0) {
+                // the last token block's share of the group before comes in front of the zero points, as the other blocks' did: a token's
+                // sums are the same bits in every block of an item
+                if constexpr (!SYM) {
+                    bf16x8 zx[NTB];
+#pragma unroll
+                    for (int tb = 0; tb < NTB; ++tb) zx[tb] = __builtin_bit_cast(bf16x8, sum_operand(zs[tb]));
+#pragma unroll
+                    for (int d = 0; d < 4; ++d) {
+                        const bf16x8 f = __builtin_bit_cast(bf16x8, factor_operand(ze.scale(d) * ((ze.zero(d) - 8.f) * (-1.f / kOffsetE4m3))));
+                        add_scaled_rows(d, NTB - 1, acc[1][d]);
+#pragma unroll
+                        for (int tb = 0; tb < NTB; ++tb)
+                            tot[d][tb] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(zx[tb], f, tot[d][tb], 0, 0, 0);
+                    }
+                }
+#pragma unroll
+                for (int tb = 0; tb < NTB; ++tb) ts[tb] = tn[tb];
+                load_four(grp / 4 + 1);
+            }
+            each<FS>([&](auto fc) {
+                constexpr int fs = decltype(fc)::value, f = F0 + fs, tb = f / NPL, p = f % NPL;
+                constexpr int A = (Q * NTB + tb) & 1;      // of acc, token blocks in turn (4 NTB of them in a trip)
+                __builtin_amdgcn_sched_barrier(0);
+                if (fs + 2 < FS) read(fs + 2);
+                if (fs + 1 < FS && (f + 1) % NPL == 0) read_sums(tb + 1);
+                const i32x8 x8 = __builtin_bit_cast(i32x8, xa[fs % kA]);
+                const bool before = p == 1 && (tb > 0 || SYM || J != 0);
+#pragma unroll
+                for (int d = 0; d < 4; ++d) {
+                    acc[A][d] = mfma_e4m3<Q, p>(x8, wb[d], p == 0 ? from[tb & 1] : acc[A][d], ts[tb], code_scales);
+                    if (before) add_scaled_rows(d, tb > 0 ? tb - 1 : NTB - 1, acc[A ^ 1][d]);
+                    if (f == NTB * NPL - 1) unpack((Q + 1) % W, d);
+                }
+                if (f == 1) {
+#pragma unroll
+                    for (int d = 0; d < 4; ++d) sc[d] = ent[Q % 2].scale(d);
+                    ent[Q % 2] = entry_at(grp + 2);
+                }
+                if (f == NTB * NPL - 1) {
+                    __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+                    for (int s = 0; s < 4; ++s) win[(Q + 1) % W * 4 + s] = load_codes(4 * (grp + 1 + W) + s);
+                }
+            });
+            __builtin_amdgcn_sched_barrier(0);
+        };
+        request_stage(0, k0);
+        request_stage(1, k1);
+        request_stage(2, k2);
+        __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+        for (int g = 0; g < W; ++g)
+#pragma unroll
+            for (int s = 0; s < 4; ++s) win[g * 4 + s] = load_codes(4 * g + s);
+        ent[0] = entry_at(0);
+        ent[1] = entry_at(1);
+        load_four(0);
+        // the first stages' transfers have fewer operations behind them than the steady state counts on
+        __builtin_amdgcn_sched_barrier(0);
+        __builtin_amdgcn_s_waitcnt(0x0070);
+#pragma unroll
+        for (int d = 0; d < 4; ++d) unpack(0, d);
+#pragma unroll
+        for (int s = 0; s < 4; ++s) win[s] = load_codes(4 * W + s);
+        auto group = [&](int grp, auto q) {
+            constexpr int Q = decltype(q)::value;
+            stage(grp, std::integral_constant<int, Q * SPG>{});
+            stage(grp, std::integral_constant<int, Q * SPG + 1>{});
+        };
+        for (int grp = 0; ; grp += 4) {
+            group(grp, k0);
+            if (grp + 1 >= G) break;
+            group(grp + 1, k1);
+            if (grp + 2 >= G) break;
+            group(grp + 2, k2);
+            if (grp + 3 >= G) break;
+            group(grp + 3, k3);
+            if (grp + 4 >= G) break;
+        }
+        // (the last group's place in a trip says which half of acc holds its last token block)
+        const bool odd = NTB % 2 == 1 && (G & 1);
+#pragma unroll
+        for (int d = 0; d < 4; ++d) {
+            f32x4 v;
+#pragma unroll
+            for (int i = 0; i < 4; ++i) v[i] = odd ? acc[0][d][i] : acc[1][d][i];
+            add_scaled_rows(d, NTB - 1, v);
+        }
         finish(ntb_c, tot);
     };
 
@@ -593,8 +912,9 @@ void prefill_tile_kernel(TileArgs a)
         else if (ntb == 2) go(std::integral_constant<int, 2>{});
         else go(std::integral_constant<int, 1>{});
     };
-    if (routed) by_blocks(run);
-    else by_blocks(run_shared);
+    if (!routed) by_blocks(run_shared);
+    else if constexpr (DOWN && KPG == 4) by_blocks(run_e4m3);
+    else by_blocks(run);
 }
 
 // Gathers the tokens of token block (item, tb) into operand tiles [(item nk + u) 4 + tb]: lane
@@ -871,8 +1191,9 @@ PrefillBuffers prefill_buffers(const moe_layer_desc &d, size_t m)
     PrefillBuffers b;
     b.xt = m * (d.hidden / 32) * 4096;
     b.x_sums = m * ((d.hidden / d.group_size + 3) / 4) * 1024;
-    b.h_plane = m * (d.inter / 32) * 4096;
+    b.h = m * (d.inter / 32) * 8192;
     b.h_sums = m * ((d.inter / d.group_size + 3) / 4) * 1024;
+    b.h_scales = d.group_size == 128 ? b.h_sums / 4 : 0;
     b.zeros = 4096;
     b.obuf = m * kItemTokens * d.hidden * 4;
     return b;
@@ -913,7 +1234,7 @@ static TileArgs tile_args(const Shape &s, const PrefillCall &p)
     TileArgs t;
     t.q = (const char *)p.q; t.sz = (const char *)p.sz; t.stride_q = p.stride_q; t.stride_sz = p.stride_sz;
     t.items = p.items; t.n_items = p.n_items; t.zeros = (const char *)p.zeros;
-    t.h_hi = (char *)p.h_hi; t.h_lo = (char *)p.h_lo; t.h_sums = (char *)p.h_sums; t.obuf = p.obuf;
+    t.h = (char *)p.h; t.h_sums = (char *)p.h_sums; t.h_scales = (char *)p.h_scales; t.obuf = p.obuf;
     t.shared = (const char *)p.shared; t.shared_stride = p.shared_stride;
     t.H = s.H; t.I = s.I; t.E = s.E; t.segments = prefill_by_size(s) ? kSegments : 1;
     return t;
@@ -922,14 +1243,14 @@ static TileArgs tile_args(const Shape &s, const PrefillCall &p)
 void launch_prefill_gateup(const Shape &s, const PrefillCall &p, int max_items, hipStream_t st)
 {
     TileArgs t = tile_args(s, p);
-    t.act0 = (const char *)p.xt; t.act1 = nullptr; t.act_sums = (const char *)p.x_sums;
+    t.act = (const char *)p.xt; t.act_sums = (const char *)p.x_sums; t.act_scales = nullptr;
     launch_tile<false>(t, p.symmetric != 0, s.g, s.I / 32, max_items, st);
 }
 
 void launch_prefill_down(const Shape &s, const PrefillCall &p, int max_items, hipStream_t st)
 {
     TileArgs t = tile_args(s, p);
-    t.act0 = (const char *)p.h_hi; t.act1 = (const char *)p.h_lo; t.act_sums = (const char *)p.h_sums;
+    t.act = (const char *)p.h; t.act_sums = (const char *)p.h_sums; t.act_scales = (const char *)p.h_scales;
     launch_tile<true>(t, p.symmetric != 0, s.g, s.H / 64, max_items, st);
 }
 

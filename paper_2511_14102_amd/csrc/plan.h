@@ -128,8 +128,8 @@ void launch_zero(void *p, size_t bytes, hipStream_t st);
 void launch_stream_read(const void *src, size_t bytes, int workgroups, void *sink, hipStream_t st);
 
 // draft_prefill.hip: a routed run of tokens.  Byte sizes of the buffers a call with at most
-// `items` work items needs (h_plane: each of the two planes of h), then the launches in order.
-struct PrefillBuffers { size_t xt, x_sums, h_plane, h_sums, zeros, obuf; };
+// `items` work items needs, then the launches in order.
+struct PrefillBuffers { size_t xt, x_sums, h, h_sums, h_scales, zeros, obuf; };
 PrefillBuffers prefill_buffers(const moe_layer_desc &d, size_t items);
 struct PrefillCall {
     const void *x;                     // [T,H] bf16
@@ -137,7 +137,7 @@ struct PrefillCall {
     PrefillItem *items; int32_t *n_items;                          // written by the plan or the stage launch
     const int32_t *count, *list; int32_t *slot_of;
     const float *w_all;                // routing weight of every assignment [T k]
-    void *xt, *x_sums, *h_hi, *h_lo, *h_sums, *zeros; float *obuf;
+    void *xt, *x_sums, *h, *h_sums, *h_scales, *zeros; float *obuf;
     float *y;                          // [T,H] fp32, written (not accumulated)
     const void *shared; size_t shared_stride;                          // bf16 blobs of the shared experts
 };

@@ -137,6 +137,42 @@ def test_prefill_sums_of_tokens_with_a_mean(H, I, g, symmetric):
     ctx.close()
 
 
+@pytest.mark.parametrize("g", [32, 64, 128])
+@pytest.mark.parametrize("symmetric", [False, True])
+def test_prefill_magnitudes(g, symmetric):
+    """Tokens far from unit size, with values far from each other in a group, with groups of zeros, and with an infinite value.  Every finite
+    token is as close to the 64-bit sums as one of N(0,1): x is exact, h has at least 16 significant bits (2.5e-6 of its norm), and the fp32 sums
+    of 1280 and 640 products leave less than that: together below 1e-5 of a token's y."""
+    cfg = LayerConfig(94, "mag%d" % g, 1280, 3, 640, 2, g, 0, 1)      # 10 and 5 groups of 128
+    ctx = B.Context(0)
+    L = synth.make_layer(cfg, 0, symmetric=symmetric)
+    A = oracle_arrays(L)
+    D = DeviceLayer(ctx, cfg, L, max_tokens=4, verify=False, symmetric=symmetric)
+    x = tokens_with_clear_routing(cfg, A, 75, step=19, kind="iid").float()
+    gen = torch.Generator().manual_seed(5)
+    for t in range(0, 40):
+        x[t] *= 2.0 ** (t - 20)
+    for t in range(40, 50):                                          # one value far above the rest of its group
+        x[t, 7 + 128 * (t - 40)] *= 300.0
+    x[50:60, 128:256] = 0.0
+    x[60:65] *= 2.0 ** torch.randint(-9, 3, (5, cfg.hidden), generator=gen)
+    x[65:70, ::100] *= 100.0
+    x[70] = 0.0
+    x = x.bfloat16()
+    ref = oracle_draft(A, x)
+    x[74, 300] = float("inf")
+    say("prefill magnitudes", g, "symmetric" if symmetric else "")
+    r = D.prefill(x.cuda())
+    y = to_np(r["y"])
+    same = [t for t in range(74) if t != 70 and np.array_equal(to_np(r["ids"])[t], ref["ids"][t])]
+    assert len(same) == 73 and not np.any(y[70])
+    err = np.linalg.norm(y[same] - ref["y"][same], axis=1) / np.linalg.norm(ref["y"][same], axis=1)
+    say("   worst token %.3e" % err.max())
+    assert err.max() <= 1e-5
+    assert np.isnan(y[74]).all()
+    ctx.close()
+
+
 PLACES = [
     #            idx  name     H    E   I   k  g    S  renorm
     (LayerConfig(86, "q32", 384, 3, 384, 2, 32, 0, 1), 150),       # items of 32 tokens, 12 groups
