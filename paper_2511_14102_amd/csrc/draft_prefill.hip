@@ -111,7 +111,8 @@ struct TileArgs {
     float *obuf;                     // down: out [item 64 + token][H]
     const char *shared;              // bf16 blobs of the shared experts (experts E, E + 1, ...)
     size_t shared_stride;
-    int H, I, E, segments;
+    int H, I, E, segments, block;
+    bool striped;
 };
 
 // The 8 codes of one word as 8 bf16 values 16 + code: 0x4180 is bf16 16.0, and a code in mantissa
@@ -271,13 +272,20 @@ void prefill_tile_kernel(TileArgs a)
     const int H = a.H, I = a.I;
     const int nk = DOWN ? I / 32 : H / 32, G = nk / KPG, nz = (G + 3) / 4;
     const int tiles = DOWN ? H / 64 : I / 32, cols = (tiles + kTileWaves - 1) / kTileWaves;
-    // Workgroups go to the XCDs in turn.  The item list is in segments of falling size; of each segment XCD x takes the
-    // x-th contiguous eighth of the (column, item) pairs, items fastest, so that the items of one expert,
-    // neighbours in the list, read its weight tiles through the same L2, and the smallest workgroups come last.
+    // Workgroups go to the XCDs in turn.  The item list is in segments of falling size (the smallest workgroups come last); a segment's
+    // (item, column) pairs are in blocks of `block` items, column by column in a block, so that the items of one expert, neighbours in the list, read
+    // its weight tiles, and the columns of an item its operand tiles, through one L2 at about the same time.  XCD x takes the x-th contiguous eighth of a segment's
+    // pairs, or (striped) of every block's, where an eighth of the segment would leave an XCD too few experts.  prefill_blocks says which.
     int n[kSegments];                                                    // (all counts by one load)
 #pragma unroll
     for (int seg = 0; seg < kSegments; ++seg) n[seg] = a.n_items[1 + seg];
-    int at = (int)blockIdx.x / kXcds, seg_items = n[0], first_item = 0, per = (cols * seg_items + kXcds - 1) / kXcds;
+    const int xcd = (int)blockIdx.x % kXcds, block = a.block, of_block = (cols * block + kXcds - 1) / kXcds;      // pairs of a whole block that an XCD takes
+    int at = (int)blockIdx.x / kXcds, seg_items = n[0], first_item = 0;
+    auto per_xcd = [&](int items) {
+        const int whole = a.striped ? items / block : 0;
+        return whole * of_block + (cols * (items - whole * block) + kXcds - 1) / kXcds;
+    };
+    int per = per_xcd(seg_items);
     if (a.segments > 1) {                                                // (without: H = 512, 201 tokens 50.7 / 50.0 us)
 #pragma unroll
         for (int seg = 1; seg < kSegments; ++seg) {
@@ -285,12 +293,25 @@ void prefill_tile_kernel(TileArgs a)
             at -= past ? per : 0;
             first_item += past ? seg_items : 0;
             seg_items = past ? n[seg] : seg_items;
-            per = (cols * seg_items + kXcds - 1) / kXcds;
+            per = per_xcd(seg_items);
         }
     }
-    const int pair = ((int)blockIdx.x % kXcds) * per + at;
-    if (at >= per || pair >= cols * seg_items) return;
-    const int col = pair / seg_items, item = first_item + pair - col * seg_items;
+    if (at >= per) return;
+    int blk, in_blk, end = cols * block;                                 // which block of the segment; which pair of it, below `end`
+    if (a.striped) {
+        blk = at / of_block;
+        const int left = seg_items - blk * block, share = left < block ? (cols * left + kXcds - 1) / kXcds : of_block;
+        // (in turn, since the last share of a block is the smallest)
+        const int eighth = (xcd + blk) % kXcds;
+        in_blk = eighth * share + at - blk * of_block;
+        end = (eighth + 1) * share;
+    } else {
+        blk = (xcd * per + at) / (cols * block);
+        in_blk = xcd * per + at - blk * cols * block;
+    }
+    const int left = seg_items - blk * block, wide = left < block ? left : block;
+    if (left <= 0 || in_blk >= end || in_blk >= cols * wide) return;
+    const int col = in_blk / wide, item = first_item + blk * block + in_blk - col * wide;
     const PrefillItem it = a.items[item];
     const int tid = threadIdx.x, lane = tid & 63, r = lane & 15, c = lane >> 4;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
@@ -1122,7 +1143,8 @@ template <bool DOWN, bool SYM>
 void launch_tile_g(const TileArgs &t, int g, int tiles, int max_items, hipStream_t st)
 {
     const size_t pairs = (size_t)((tiles + kTileWaves - 1) / kTileWaves) * max_items;
-    const dim3 grid((unsigned)(((pairs + kXcds - 1) / kXcds + t.segments - 1) * kXcds)), block(kTileThreads);   // (each segment is rounded up)
+    // (each segment is rounded up, and each block where those are striped)
+    const dim3 grid((unsigned)(((pairs + kXcds - 1) / kXcds + t.segments - 1 + (t.striped ? max_items / t.block + t.segments : 0)) * kXcds)), block(kTileThreads);
     if (g == 32) launch(prefill_tile_kernel<DOWN, SYM, 1>, grid, block, 0, st, t);
     else if (g == 64) launch(prefill_tile_kernel<DOWN, SYM, 2>, grid, block, 0, st, t);
     else launch(prefill_tile_kernel<DOWN, SYM, 4>, grid, block, 0, st, t);
@@ -1240,9 +1262,22 @@ static TileArgs tile_args(const Shape &s, const PrefillCall &p)
     return t;
 }
 
+// The order of the (item, column) pairs.  Blocks of two items: an XCD then has a few experts to itself, whose weights and x it alone reads.
+// Where experts are wide and so few, blocks of eight and an eighth of each to every XCD: x is then read by all XCDs, which costs less than
+// leaving some of them with other amounts of work (shared experts, short rests).  us per pass, items of all experts column by column as it was / blocks of two /
+// eight, striped:  dsv2lite, 333 tokens 570 / 556 / 571; 1200 1290 / 1226 / 1280; qwen3, 512 629 / 599 / 625; qwen15, 700 874 / 840 / 878; H = 1024, E = 24, I = 2048, 900
+// 481 / 453 / 474; phi, 512 609 / 610 / 600, 2048 1793 / 1744 / 1732; phi, 150 423 / 425 / 413; mixtral, 512 605 / 613 / 589, 4096 3455 / 3594 / 3331; H = 2048, E = 6, I = 4096, a shared
+// expert, 2500 1312 / 1344 / 1285.  In the down launch the two differ by less than 1 %, and h is as many bytes as the weights: blocks of two.
+static void prefill_blocks(TileArgs &t, bool down)
+{
+    t.striped = !down && t.I >= 4096;
+    t.block = t.striped ? 8 : 2;
+}
+
 void launch_prefill_gateup(const Shape &s, const PrefillCall &p, int max_items, hipStream_t st)
 {
     TileArgs t = tile_args(s, p);
+    prefill_blocks(t, false);
     t.act = (const char *)p.xt; t.act_sums = (const char *)p.x_sums; t.act_scales = nullptr;
     launch_tile<false>(t, p.symmetric != 0, s.g, s.I / 32, max_items, st);
 }
@@ -1250,6 +1285,7 @@ void launch_prefill_gateup(const Shape &s, const PrefillCall &p, int max_items, 
 void launch_prefill_down(const Shape &s, const PrefillCall &p, int max_items, hipStream_t st)
 {
     TileArgs t = tile_args(s, p);
+    prefill_blocks(t, true);
     t.act = (const char *)p.h; t.act_sums = (const char *)p.h_sums; t.act_scales = (const char *)p.h_scales;
     launch_tile<true>(t, p.symmetric != 0, s.g, s.H / 64, max_items, st);
 }

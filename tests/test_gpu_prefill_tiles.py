@@ -209,6 +209,7 @@ ORDERS = [
     (LayerConfig(91, "o4096", 4096, 16, 64, 2, 32, 0, 1), 300, True, False),      # no shared experts
     (LayerConfig(92, "o128", 128, 48, 4096, 8, 32, 0, 1), 300, False, False),     # more than three and a half rounds
     (LayerConfig(93, "o192", 192, 20, 8192, 2, 64, 1, 1), 280, False, True),
+    (LayerConfig(95, "o1280", 1280, 20, 4096, 1, 128, 0, 1), 1500, True, False),  # largest first, in striped blocks
 ]
 
 
