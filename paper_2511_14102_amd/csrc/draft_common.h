@@ -54,6 +54,41 @@ __device__ inline bf16x8 unpack8(uint32_t w, UnpackConsts k) {
     return __builtin_bit_cast(bf16x8, r);
 }
 
+// ---- e4m3: products of codes with an intermediate h
+// A code byte 0 .. 15 IS the e4m3 number q 2^-9 (below 8 a denormal), so the 8 codes of a word become operand bytes with
+// two masks and a shift: codes 0, 4, 1, 5 in the first four bytes, 2, 6, 3, 7 in the others.
+__device__ inline void unpack8_e4m3(uint32_t w, uint32_t mask, uint32_t &lo, uint32_t &hi) {
+    lo = w & mask;
+    hi = (w >> 4) & mask;
+}
+// h = 2^(byte - 127) (p0 + p1 / 16 + p2 / 256 + p3 / 4096), p_i e4m3, with one power of two for up to 128 h, which puts the largest
+// in [128, 256).  What the planes leave of h: 4e-7 of the norm; two bf16 numbers left 2.5e-6.
+//
+// The matrix cores add the products of eight neighbouring bytes of an operand on one grid, 2^-13 of the largest one's exponent
+// (measured, 16x16x32 and 16x16x128; the sums of eights meet in fp32).  So the first two planes of eight neighbouring h are rounded to a grid of 2^-10
+// of the eight's largest exponent first: with codes below 16 their products then lie on the cores' grid and their sum is exact, and the next plane takes
+// up what the grid left (what four bits leave, times 16, has no larger exponent than the value, so the grid is the same for
+// both).  Without this: 7.6e-5 of a group's sum, with it 4e-7.
+constexpr int kPlanes = 4, kPlaneShift = 4;
+// from the largest magnitude: the scale byte, what h is multiplied by, and back.  (The largest of values that are not all finite may be
+// any; the sums of the planes are then NaN, which takes all outputs of the token to NaN.)
+struct PlaneScale {
+    uint32_t byte;
+    __device__ explicit PlaneScale(float largest) {
+        const uint32_t e = __float_as_uint(largest) >> 23;
+        byte = (e < 32u ? 32u : e < 254u ? e : 254u) - 7u;
+    }
+    __device__ float up() const { return __uint_as_float((254u - byte) << 23); }
+    __device__ float down() const { return __uint_as_float(byte << 23); }
+};
+// 1.5 2^23 units of the grid of eight scaled h, the largest magnitude m.  The exponent is that of the largest value as it is
+// rounded, to the grid and then to four bits: the next one from 1.9375 - 2^-11 on (one exponent too low cost such an eight's sum
+// 1e-3 of it).  2^-8 at least.
+__device__ inline float plane_grid(float m) {
+    const uint32_t e = (__float_as_uint(m) + 0x81000u) >> 23;
+    return __uint_as_float(((e > 119u ? e : 119u) + 13u) << 23 | 0x400000u);
+}
+
 // Computes a value here: a window slot may be refilled behind this point (into the same registers) though the
 // value made from its old contents is used further down.  Left alone, the compiler makes the value where it
 // is used, copies the slot's contents for that, and waits for all loads in flight at every such copy.
@@ -63,9 +98,14 @@ __device__ inline void compute_here(bf16x8 &v) {
     v = __builtin_bit_cast(bf16x8, u);
 }
 __device__ inline void compute_here(float &v) { asm volatile("" : "+v"(v)); }
+__device__ inline void compute_here(uint64_t &v) { asm volatile("" : "+v"(v)); }
 
 __device__ inline f32x4 mfma(u32x4 a, bf16x8 b, f32x4 c) {
     return __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8, a), b, c, 0, 0, 0);
+}
+
+__device__ inline f32x4 mfma_e4m3(uint64_t a, uint64_t b, f32x4 c) {
+    return __builtin_amdgcn_mfma_f32_16x16x32_fp8_fp8((long)a, (long)b, c, 0, 0, 0);
 }
 
 // One 16-byte load at agent scope (served by the device's coherence point, not a stale cache line)

@@ -133,32 +133,12 @@ __device__ inline bf16x8 unpack8_16(uint32_t w, UnpackConsts k) {
     return __builtin_bit_cast(bf16x8, r);
 }
 
-// ---- g = 128: the codes as e4m3 numbers, x and h as sums of e4m3 numbers
-// A code byte 0 .. 15 IS the e4m3 number q 2^-9 (below 8 a denormal), so the 8 codes of a word become operand bytes with
-// two masks and a shift: codes 0, 4, 1, 5 in the first four bytes, 2, 6, 3, 7 in the others.
+// ---- g = 128, down part: 16x16x128 products of e4m3 codes with h as e4m3 planes (draft_common.h), whose scale is a byte that
+// the matrix cores apply
 typedef __attribute__((ext_vector_type(8))) int i32x8;
-__device__ inline void unpack8_e4m3(uint32_t w, uint32_t mask, int &lo, int &hi) {
-    lo = (int)(w & mask);
-    hi = (int)((w >> 4) & mask);
-}
-
-// h = 2^(scale - 127) (p0 + p1 / 16 + p2 / 256 + p3 / 4096), p_i e4m3, one scale (a byte that the matrix cores apply) per token and
-// group of 128, which puts the group's largest value in [128, 256).  What the planes leave of h: 4e-7 of the norm; two bf16 numbers left 2.5e-6.
-constexpr int kPlanes = 4, kPlaneShift = 4;
 // the scales of the code bytes (2^9) per plane, the plane's step in them
 constexpr uint32_t kCodeScales = 136u | (136u - kPlaneShift) << 8 | (136u - 2 * kPlaneShift) << 16 | (136u - 3 * kPlaneShift) << 24;
 
-// from the group's largest magnitude: the scale byte, what h is multiplied by, and back.  (The largest of values that are not all finite may be
-// any; the sums of the planes are then NaN, which takes all outputs of the token to NaN.)
-struct GroupScale {
-    uint32_t byte;
-    __device__ explicit GroupScale(float largest) {
-        const uint32_t e = __float_as_uint(largest) >> 23;
-        byte = (e < 32u ? 32u : e < 254u ? e : 254u) - 7u;
-    }
-    __device__ float up() const { return __uint_as_float((254u - byte) << 23); }
-    __device__ float down() const { return __uint_as_float(byte << 23); }
-};
 __device__ inline float largest8(const float (&v)[8])
 {
     float m = fabsf(v[0]);
@@ -167,17 +147,10 @@ __device__ inline float largest8(const float (&v)[8])
     return m;
 }
 
-// Eight h of a k-step (v, scaled; m: the largest of them) as planes; returns the sum of what the planes hold (scaled).  The matrix cores add the products of
-// eight neighbouring bytes on one grid, 2^-13 of the largest one's exponent (measured; the sums of eights meet in fp32).  So the
-// first two planes are rounded to a grid of 2^-10 of the eight's largest exponent first: with codes below 16 their products then
-// lie on the cores' grid and their sum is exact, and the next plane takes up what the grid left (what four bits leave, times the step, has no
-// larger exponent than the value, so the grid is the same for both).  Without this: 7.6e-5 of a group's sum, with it 4e-7, the bf16 form 2.5e-6.
+// Eight h of a k-step (v, scaled; m: the largest of them) as planes; returns the sum of what the planes hold (scaled)
 __device__ inline float split_planes(float (&v)[8], float m, uint32_t (&out)[kPlanes][2])
 {
-    // The exponent is that of the largest value as it is rounded, to the grid and then to four bits: the next one from 1.9375 - 2^-11 on (one
-    // exponent too low cost such an eight's sum 1e-3 of it).  2^-8 at least.
-    const uint32_t e = (__float_as_uint(m) + 0x81000u) >> 23;
-    const float grid = __uint_as_float(((e > 119u ? e : 119u) + 13u) << 23 | 0x400000u);      // 1.5 2^23 units of the grid
+    const float grid = plane_grid(m);
     float sum = 0.f;
 #pragma unroll
     for (int j = 0; j < 8; ++j) sum += v[j];
@@ -416,7 +389,7 @@ void prefill_tile_kernel(TileArgs a)
             float h[8];
             load(tb, h);
             const int tok = 16 * tb + r;
-            const GroupScale gs(fmaxf(fmaxf(s_max[0][tok], s_max[1][tok]), fmaxf(s_max[2][tok], s_max[3][tok])));
+            const PlaneScale gs(fmaxf(fmaxf(s_max[0][tok], s_max[1][tok]), fmaxf(s_max[2][tok], s_max[3][tok])));
             const float up = gs.up();
 #pragma unroll
             for (int j = 0; j < 8; ++j) h[j] *= up;
@@ -734,10 +707,10 @@ void prefill_tile_kernel(TileArgs a)
         auto unpack = [&](int slot, int d) {
 #pragma unroll
             for (int s = 0; s < 4; ++s) {
-                int lo, hi;
+                uint32_t lo, hi;
                 unpack8_e4m3(win[slot * 4 + s][d], mask, lo, hi);
-                wb[d][2 * s] = lo;
-                wb[d][2 * s + 1] = hi;
+                wb[d][2 * s] = (int)lo;
+                wb[d][2 * s + 1] = (int)hi;
             }
             asm volatile("" : "+v"(wb[d]));
         };

@@ -39,7 +39,8 @@ __device__ __forceinline__ void draft_one_token(const uint16_t *__restrict__ xin
     __shared__ float s_w[MOE_MAX_TOPK], s_conf[MOE_MAX_TOPK];
     __shared__ int32_t s_ok;
     __shared__ float s_red[ITEMS][kWaves][64];       // partial gate/up sums
-    __shared__ __attribute__((aligned(16))) uint16_t s_h[ITEMS][kWaves][2][32];    // h and its remainder, each wave's own copy
+    // h, each wave's own copy: its four e4m3 planes of 32 bytes (a shared expert's: 16 bf16 values and their remainders)
+    __shared__ __attribute__((aligned(16))) uint16_t s_h[ITEMS][kWaves][2][32];
     extern __shared__ __attribute__((aligned(16))) unsigned char s_dyn[];   // x, its group sums, logits, ranks, two items' outputs
 
     const int tid = threadIdx.x;
@@ -346,36 +347,60 @@ __device__ __forceinline__ void draft_one_token(const uint16_t *__restrict__ xin
         if (wave0) second_ticket();
         __syncthreads();
 
-        // ---- 7. h of the slice's 32 rows, in every wave: lanes 0-31 hold the gate rows, 32-63 the up rows
-        float hsum;
+        // ---- 7. h of the slice's 32 rows, in every wave: lanes 0-31 hold the gate rows, 32-63 the up rows.  It goes to LDS as four e4m3
+        // planes (draft_common.h), a row's eights in the byte order of a word's codes.
+        uint8_t *planes = reinterpret_cast<uint8_t *>(&s_h[half][wave][0][0]);
+        float hsum, down;
         {
             float v = 0.f;
 #pragma unroll
             for (int w = 0; w < kWaves; ++w) v += s_red[half][w][lane];
             const float up = __shfl_xor(v, 32);
             const float h = v / (1.f + expf(-v)) * up;
-            const uint16_t hi = f32_to_bf16_rne(h);
-            const uint16_t lo = f32_to_bf16_rne(h - __uint_as_float((uint32_t)hi << 16));
-            if (lane < 32) { s_h[half][wave][0][lane] = hi; s_h[half][wave][1][lane] = lo; }
-            const float hs = __uint_as_float((uint32_t)hi << 16) + __uint_as_float((uint32_t)lo << 16);   // the represented h
-            hsum = wave::sum(lane < 32 ? hs : 0.f);
+            float m = fabsf(h);
+            m = fmaxf(m, wave::move<wave::kSwap1>(m));
+            m = fmaxf(m, wave::move<wave::kSwap2>(m));
+            m = fmaxf(m, wave::move<wave::kHalfMirror>(m));                  // of the row's eight
+            const float row = fmaxf(m, wave::move<wave::kMirror>(m));
+            const PlaneScale scale(fmaxf(wave::from_lane<0>(row), wave::from_lane<16>(row)));
+            down = scale.down();
+            const float hu = h * scale.up(), grid = plane_grid(m * scale.up());
+            const int at = (lane & 24) | ((lane & 3) << 1) | ((lane >> 2) & 1);
+            float left = hu;
+#pragma unroll
+            for (int p = 0; p < kPlanes; ++p) {
+                const float step = (float)(1 << (p * kPlaneShift));
+                const float t = p < 2 ? fmaf(left, step, grid) - grid : left * step;
+                const int b = __builtin_amdgcn_cvt_pk_fp8_f32(t, t, 0, false);
+                if (lane < 32) planes[p * 32 + at] = (uint8_t)b;
+                left = fmaf(__builtin_amdgcn_cvt_f32_fp8(b, 0), -1.f / step, left);         // (exact)
+            }
+            hsum = wave::sum(lane < 32 ? hu - left : 0.f) * (1.f / 512.f);              // of what the planes hold; a code byte is q 2^-9
             __builtin_amdgcn_wave_barrier();
         }
-        const float rw = s_w[u];
+        const float rw = s_w[u] * 512.f;
 
-        // ---- 8. down: this wave's row tiles, all H outputs of the slice's 32 columns.  A rows 4 bl, 4 bl + 1
-        // hold h and its remainder for row block bl of the tile (all other rows zero), and the four MFMAs
+        // ---- 8. down: this wave's row tiles, all H outputs of the slice's 32 columns.  A rows 4 bl .. 4 bl + 3
+        // hold the planes of h for row block bl of the tile (all other rows zero), and the four MFMAs
         // of a tile accumulate into ONE D tile whose lane group bl then holds row block bl: the tile's 64 outputs
-        // in one register pair, one 64-lane atomic per tile.
-        u32x4 ha[4];
+        // in four registers, one 64-lane atomic per tile.
+        // Where the weight stream is through before the last barrier, this is all that is left but the additions, and vector work bounds it:
+        // 12 instructions per tile unpack the codes (28 as bf16, for h as two bf16 numbers) and an e4m3 product keeps the vector ALU waiting 10 clocks
+        // (15).  (From h to the issue of the last addition a workgroup of the phi shape took 3.3 us.)  us per pass, h as two bf16 numbers / this: phi shape, 8 layers
+        // 192.5 / 186.9, qwen15, 16 445.3 / 442.3; others, whose end the chain of additions sets, the same within 0.5 %.
+        uint64_t ha[4];
         {
-            const u32x4 hv = *reinterpret_cast<const u32x4 *>(&s_h[half][wave][r & 1][c * 8]);
+            const uint64_t hv = *reinterpret_cast<const uint64_t *>(planes + (r & 3) * 32 + c * 8);
 #pragma unroll
-            for (int bl = 0; bl < 4; ++bl) {
-                const bool on = (r & 3) < 2 && (r >> 2) == bl;
-                ha[bl] = (u32x4){on ? hv.x : 0u, on ? hv.y : 0u, on ? hv.z : 0u, on ? hv.w : 0u};
-            }
+            for (int bl = 0; bl < 4; ++bl) ha[bl] = (r >> 2) == bl ? hv : 0ull;
         }
+        uint32_t mask = 0x0f0f0f0fu;
+        asm volatile("" : "+s"(mask));
+        auto operand = [&](uint32_t w) {
+            uint32_t lo, hi;
+            unpack8_e4m3(w, mask, lo, hi);
+            return (uint64_t)hi << 32 | lo;
+        };
         // one pass over the window; kReload: the slot is refilled with the tile kWin further on; the last pass
         // refills nothing
         auto down_pass = [&](int j0, auto reload) {
@@ -383,8 +408,8 @@ __device__ __forceinline__ void draft_one_token(const uint16_t *__restrict__ xin
 #pragma unroll
             for (int i = 0; i < kWin; ++i) {
                 const int rt = r0 + j0 + i;
-                float sc = scale_of(dpe[i]), zp = zero_of(dpe[i]);
-                bf16x8 b0 = unpack8(win[i].x, uk), b1 = unpack8(win[i].y, uk), b2 = unpack8(win[i].z, uk), b3 = unpack8(win[i].w, uk);
+                float sc = scale_of(dpe[i]), zp = SYM ? 8.f : (float)__builtin_bit_cast(_Float16, (uint16_t)(dpe[i] >> 16));
+                uint64_t b0 = operand(win[i].x), b1 = operand(win[i].y), b2 = operand(win[i].z), b3 = operand(win[i].w);
                 if constexpr (kReload) {
                     compute_here(b0); compute_here(b1); compute_here(b2); compute_here(b3);
                     compute_here(sc); compute_here(zp);
@@ -395,11 +420,13 @@ __device__ __forceinline__ void draft_one_token(const uint16_t *__restrict__ xin
                 }
                 if (rt < r1) {
                     f32x4 o = (f32x4){0.f, 0.f, 0.f, 0.f};
-                    o = mfma(ha[0], b0, o);
-                    o = mfma(ha[1], b1, o);
-                    o = mfma(ha[2], b2, o);
-                    o = mfma(ha[3], b3, o);
-                    const float val = sc * ((o[0] + o[1]) - zp * hsum) * rw;
+                    o = mfma_e4m3(ha[0], b0, o);
+                    o = mfma_e4m3(ha[1], b1, o);
+                    o = mfma_e4m3(ha[2], b2, o);
+                    o = mfma_e4m3(ha[3], b3, o);
+                    constexpr float kStep = 1.f / (1 << kPlaneShift);
+                    const float sum = fmaf(fmaf(fmaf(o[3], kStep, o[2]), kStep, o[1]), kStep, o[0]);
+                    const float val = sc * (sum - zp * hsum) * rw * down;
                     add_output(rt * 64 + lane, val);
                 }
             }
