@@ -22,9 +22,6 @@ namespace {
 
 constexpr int kWaves = kDraftWaves;
 constexpr int kThreads = kWaves * 64;
-// The router result is published in kReplicas copies; workgroup b polls copy b % kReplicas, so
-// that the polls of hundreds of workgroups do not all land on one address.
-constexpr int kReplicas = kDraftSlotReplicas;
 constexpr int kTicketGroups = 16;
 constexpr uint32_t kMagic = 0x43004300u;      // bf16 pair (128, 128)
 
@@ -149,7 +146,7 @@ struct FusedArgs {
     const char *q;              // int4 codes blobs
     const char *sz;             // scale/zero blobs
     size_t stride_q, stride_sz;
-    unsigned long long *slots;  // kReplicas x [T,E] x {logit bits, tag}; idle: tag = 0
+    unsigned long long *slots;  // copies (exchange_copies_lg) x [T,E] x {logit bits, tag}; idle: tag = 0
     size_t replica_stride;      // in 8-byte units
     uint32_t *tickets;          // kTicketGroups + 1 counters; idle: 0
     uint32_t *status;           // set to 1 when a wait for the router result ran out of polls
@@ -178,7 +175,7 @@ __device__ inline void publish_router_rows(const uint16_t *__restrict__ xin, con
 {
     constexpr int kTh = NW * 64, kRowWaves = NW / ROWS;
     const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
-    const int T = a.T, H = a.H, E = a.E, chunks = H / 8;
+    const int T = a.T, H = a.H, E = a.E, chunks = H / 8, lg = exchange_copies_lg(E);
     for (int i = b * kTh + tid; i < T * H; i += nprod * kTh)
         __hip_atomic_store(&a.y[i], 0.f, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
     const int lt = T <= 1 ? 0 : (T <= 2 ? 1 : (T <= 4 ? 2 : 3));
@@ -186,7 +183,7 @@ __device__ inline void publish_router_rows(const uint16_t *__restrict__ xin, con
     const uint16_t *xt = xin + (size_t)(t < T ? t : T - 1) * H;
     for (int e = b * ROWS; e < E; e += nprod * ROWS) {
         // of the rows e, e + 1: the one to reduce, the one to publish (behind an odd last row, that one again, not published)
-        const int reduced = ROWS > 1 && e + 1 < E ? wave / kRowWaves : 0, mine = ROWS > 1 ? tid / kReplicas % ROWS : 0;
+        const int reduced = ROWS > 1 && e + 1 < E ? wave / kRowWaves : 0, mine = ROWS > 1 ? (tid >> lg) % ROWS : 0;
         const uint16_t *row = a.wr + (size_t)(e + reduced) * H;
         const float bias = a.bias ? a.bias[ROWS > 1 && e + mine >= E ? e : e + mine] : 0.f;          // (here and not behind the barrier: a round trip to memory)
         double acc[4] = {0.0, 0.0, 0.0, 0.0};
@@ -219,8 +216,8 @@ __device__ inline void publish_router_rows(const uint16_t *__restrict__ xin, con
         // of the row were issued after the stores and have returned)
         asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
         __syncthreads();
-        if (tid < T * ROWS * kReplicas && (ROWS == 1 || e + mine < E)) {    // thread (token or row, replica)
-            const int tt = ROWS > 1 ? 0 : tid / kReplicas, rep = tid % kReplicas;
+        if (tid < (T * ROWS) << lg && (ROWS == 1 || e + mine < E)) {        // thread (token or row, copy)
+            const int tt = ROWS > 1 ? 0 : tid >> lg, rep = tid & ((1 << lg) - 1);
             double l = 0.0;
 #pragma unroll
             for (int w = 0; w < kRowWaves; ++w) l += (w & ((1 << lt) - 1)) == tt ? s_part[mine * kRowWaves + w] : 0.0;
@@ -248,7 +245,7 @@ __device__ inline bool poll_and_select(const FusedArgs &a, int t, double *logit,
 #pragma unroll
     for (int i = 0; i < NR; ++i) {
         const int e = lane + 64 * i < E ? lane + 64 * i : E - 1;
-        from[i] = a.slots + (size_t)(blockIdx.x % kReplicas) * a.replica_stride + 2 * ((size_t)t * E + e);
+        from[i] = a.slots + (size_t)(blockIdx.x & ((1u << exchange_copies_lg(E)) - 1u)) * a.replica_stride + 2 * ((size_t)t * E + e);
     }
     u32x4 v[NR];
     bool all = false;
@@ -306,7 +303,7 @@ __device__ inline uint32_t ticket_groups(uint32_t grid) { return grid < (uint32_
 // `threads` threads, of which the calling one is number `me`, put slots and tickets back to idle
 __device__ inline void reset_exchange(const FusedArgs &a, int me, int threads) {
     const int n = a.T * a.E;
-    for (int rep = 0; rep < kReplicas; ++rep)
+    for (int rep = 0; rep < 1 << exchange_copies_lg(a.E); ++rep)
         for (int i = me; i < n; i += threads)
             __hip_atomic_store(a.slots + (size_t)rep * a.replica_stride + 2 * (size_t)i + 1, 0ull, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
     if (me <= kTicketGroups) __hip_atomic_store(a.tickets + me, 0u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);

@@ -30,7 +30,7 @@
 // Cross-workgroup protocol (one bounded wait, no cache flushes):
 //   1. router row e is reduced by workgroup e (mod router_workgroups), which first clears its share of y
 //      with agent-scope stores, waits for their completion, and then publishes the 16-byte
-//      slot {logit, tag = 1} of every token as one 16-byte store (in kReplicas copies);
+//      slot {logit, tag = 1} of every token as one 16-byte store (in a few copies);
 //   2. every workgroup polls the slots with single 16-byte agent-scope loads until all are
 //      tagged, then selects the top-k itself (identical in all workgroups) and draws a ticket;
 //   3. y contributions (of an item, or of a workgroup's items of one expert) are agent-scope atomics, which land after the clearing stores because

@@ -22,6 +22,13 @@ constexpr int router_workgroups(int E, int rows, int workgroups) {
     return n < workgroups ? n : workgroups;
 }
 
+// Copies of the router's results that a call publishes, 2 to the power of this; workgroup b polls copy b mod their number, so that the polls of
+// hundreds of workgroups do not all land on one address.  A copy is a 16-byte store per logit, four of them to a line of memory that
+// different workgroups write, which the last reader clears again: with many experts that costs more than the polls.  us per pass, sixteen / four copies (one
+// token; E): 72 210 / 200, 100 190 / 179, 128 (qwen3) 232 / 220, 256 230 / 212; 8 tokens, E = 128 283 / 274 (two copies 275, one 277).  E <= 64, sixteen / eight / four:
+// dsv2lite 271.3 / 272.4 / 272.9, phi 187.7 / 186.5 / 185.4, qwen15 442 / 440 / 437, E = 32 164.5 / 162.5 / 163.2; E = 8, H = 8192 177.2 / 177.5 / 171, mixtral 156.7 / 158.3 / 157.6.
+constexpr int exchange_copies_lg(int E) { return E > 64 ? 2 : E >= 16 ? 3 : 4; }
+
 // ---- calls of two to eight tokens (draft_int4.hip)
 
 // Token slots of y that a workgroup sums in LDS

@@ -49,7 +49,7 @@ struct Plan {
 // Workspace carve-up (byte offsets from a 256-byte aligned base).  [tickets, plan) must be
 // zero between calls ("idle state"): moe_workspace_init establishes it, the draft kernel
 // restores it.  Their sizes do not depend on T, so the idle region is the same for every call.
-constexpr int kDraftSlotReplicas = 16;   // copies of the draft kernel's router-exchange slots
+constexpr int kDraftSlotReplicas = 16;   // copies of the draft kernel's router-exchange slots that the workspace has room for (calls use exchange_copies_lg of them)
 // inside the first block (the `tickets` block, kWsHeadBytes): the verify call's arrival counter and the
 // draft calls' status word (0: fine, 1: a wait for the router result ran out of polls)
 constexpr size_t kWsArrivalsOffset = 128, kWsStatusOffset = 192;
