@@ -25,8 +25,8 @@ namespace {
 
 // UPG: 32-code units per group (g / 32); SYM: symmetric format (scale blobs, z = 8); SHARED: the shared
 // experts run in this launch (without them the kernel is smaller: its start is a chain of code that runs once); ITEMS: one item
-// per workgroup, or two neighbours (of one expert), eight waves each, whose outputs are added up in LDS
-template <int UPG, bool SYM, bool SHARED, int ITEMS>
+// per workgroup, or two neighbours (of one expert), eight waves each, whose outputs are added up in LDS; PLANES: the down part multiplies e4m3 planes of h
+template <int UPG, bool SYM, bool SHARED, int ITEMS, bool PLANES>
 __device__ __forceinline__ void draft_one_token(const uint16_t *__restrict__ xin, const FusedArgs &a)
 {
     // tiles a wave keeps in flight (rolling window): two workgroups per compute unit leave 128 VGPRs per
@@ -347,93 +347,124 @@ __device__ __forceinline__ void draft_one_token(const uint16_t *__restrict__ xin
         if (wave0) second_ticket();
         __syncthreads();
 
-        // ---- 7. h of the slice's 32 rows, in every wave: lanes 0-31 hold the gate rows, 32-63 the up rows.  It goes to LDS as four e4m3
-        // planes (draft_common.h), a row's eights in the byte order of a word's codes.
-        uint8_t *planes = reinterpret_cast<uint8_t *>(&s_h[half][wave][0][0]);
-        float hsum, down;
+        // ---- 7. h of the slice's 32 rows, in every wave: lanes 0-31 hold the gate rows, 32-63 the up rows; then 8. down: this wave's
+        // row tiles, all H outputs of the slice's 32 columns.  A rows 4 bl .. 4 bl + 3 hold the parts of h for row block bl of the
+        // tile (all other rows zero), and the four MFMAs of a tile accumulate into ONE D tile whose lane group bl then holds row block
+        // bl: the tile's 64 outputs, one 64-lane atomic per tile.
+        // Where the weight stream is through before the last barrier, this is all that is left but the additions, and vector work bounds it.  Long
+        // rows: h as four e4m3 planes (draft_common.h), whose products take codes as they stand: 12 instructions per tile
+        // unpack them (28 as bf16, for h as two bf16 numbers), and an e4m3 product keeps the vector ALU waiting 10 clocks (15).  The cut into planes is some 45 instructions
+        // more, in every wave of the unit, so a wave needs three row tiles to gain.  (Both in one kernel spill.)  us per pass, two bf16 numbers / planes: phi shape (eight
+        // tiles a wave), 8 layers 192.5 / 186.9, qwen15 (four), 16 445.3 / 442.3, H = 1728 249.7 / 246.7, H = 1280 324.2 / 325.7, H = 640 219.5 / 222.3; qwen3 as single items (four) 225 / 225, H = 512 152 / 154.
         {
-            float v = 0.f;
+            constexpr bool kAsPlanes = PLANES;
+            uint8_t *h_bytes = reinterpret_cast<uint8_t *>(&s_h[half][wave][0][0]);
+            float hsum, down = 1.f;
+            {
+                float v = 0.f;
 #pragma unroll
-            for (int w = 0; w < kWaves; ++w) v += s_red[half][w][lane];
-            const float up = __shfl_xor(v, 32);
-            const float h = v / (1.f + expf(-v)) * up;
-            float m = fabsf(h);
-            m = fmaxf(m, wave::move<wave::kSwap1>(m));
-            m = fmaxf(m, wave::move<wave::kSwap2>(m));
-            m = fmaxf(m, wave::move<wave::kHalfMirror>(m));                  // of the row's eight
-            const float row = fmaxf(m, wave::move<wave::kMirror>(m));
-            const PlaneScale scale(fmaxf(wave::from_lane<0>(row), wave::from_lane<16>(row)));
-            down = scale.down();
-            const float hu = h * scale.up(), grid = plane_grid(m * scale.up());
-            const int at = (lane & 24) | ((lane & 3) << 1) | ((lane >> 2) & 1);
-            float left = hu;
+                for (int w = 0; w < kWaves; ++w) v += s_red[half][w][lane];
+                const float other = __shfl_xor(v, 32);
+                if constexpr (kAsPlanes) {
+                    const float gate = lane < 32 ? v : other, up = lane < 32 ? other : v;
+                    const float h = gate / (1.f + expf(-gate)) * up;                 // (lanes 32-63 do and write the same once more: no masks)
+                    float m = fabsf(h);
+                    m = fmaxf(m, wave::move<wave::kSwap1>(m));
+                    m = fmaxf(m, wave::move<wave::kSwap2>(m));
+                    m = fmaxf(m, wave::move<wave::kHalfMirror>(m));                  // of the row's eight
+                    const float row = fmaxf(m, wave::move<wave::kMirror>(m));
+                    const PlaneScale scale(fmaxf(wave::from_lane<0>(row), wave::from_lane<16>(row)));
+                    down = scale.down();
+                    const float hu = h * scale.up(), grid = plane_grid(m * scale.up());
+                    uint8_t *at = h_bytes + ((lane & 24) | ((lane & 3) << 1) | ((lane >> 2) & 1));       // the byte order of a word's codes
+                    float left = hu;
 #pragma unroll
-            for (int p = 0; p < kPlanes; ++p) {
-                const float step = (float)(1 << (p * kPlaneShift));
-                const float t = p < 2 ? fmaf(left, step, grid) - grid : left * step;
-                const int b = __builtin_amdgcn_cvt_pk_fp8_f32(t, t, 0, false);
-                if (lane < 32) planes[p * 32 + at] = (uint8_t)b;
-                left = fmaf(__builtin_amdgcn_cvt_f32_fp8(b, 0), -1.f / step, left);         // (exact)
+                    for (int p = 0; p < kPlanes; ++p) {
+                        const float step = (float)(1 << (p * kPlaneShift));
+                        const float t = p < 2 ? fmaf(left, step, grid) - grid : left * step;
+                        const int b = __builtin_amdgcn_cvt_pk_fp8_f32(t, t, 0, false);
+                        at[p * 32] = (uint8_t)b;
+                        left = fmaf(__builtin_amdgcn_cvt_f32_fp8(b, 0), -1.f / step, left);              // (exact)
+                    }
+                    hsum = wave::sum(hu - left) * (0.5f / 512.f);                    // of what the planes hold (twice); a code byte is q 2^-9
+                } else {
+                    const float h = v / (1.f + expf(-v)) * other;
+                    const uint16_t hi = f32_to_bf16_rne(h);
+                    const uint16_t lo = f32_to_bf16_rne(h - __uint_as_float((uint32_t)hi << 16));
+                    if (lane < 32) { s_h[half][wave][0][lane] = hi; s_h[half][wave][1][lane] = lo; }
+                    const float hs = __uint_as_float((uint32_t)hi << 16) + __uint_as_float((uint32_t)lo << 16);   // the represented h
+                    hsum = wave::sum(lane < 32 ? hs : 0.f);
+                }
+                __builtin_amdgcn_wave_barrier();
             }
-            hsum = wave::sum(lane < 32 ? hu - left : 0.f) * (1.f / 512.f);              // of what the planes hold; a code byte is q 2^-9
-            __builtin_amdgcn_wave_barrier();
-        }
-        const float rw = s_w[u] * 512.f;
+            const float rw = s_w[u] * (kAsPlanes ? 512.f : 1.f);
 
-        // ---- 8. down: this wave's row tiles, all H outputs of the slice's 32 columns.  A rows 4 bl .. 4 bl + 3
-        // hold the planes of h for row block bl of the tile (all other rows zero), and the four MFMAs
-        // of a tile accumulate into ONE D tile whose lane group bl then holds row block bl: the tile's 64 outputs
-        // in four registers, one 64-lane atomic per tile.
-        // Where the weight stream is through before the last barrier, this is all that is left but the additions, and vector work bounds it:
-        // 12 instructions per tile unpack the codes (28 as bf16, for h as two bf16 numbers) and an e4m3 product keeps the vector ALU waiting 10 clocks
-        // (15).  (From h to the issue of the last addition a workgroup of the phi shape took 3.3 us.)  us per pass, h as two bf16 numbers / this: phi shape, 8 layers
-        // 192.5 / 186.9, qwen15, 16 445.3 / 442.3; others, whose end the chain of additions sets, the same within 0.5 %.
-        uint64_t ha[4];
-        {
-            const uint64_t hv = *reinterpret_cast<const uint64_t *>(planes + (r & 3) * 32 + c * 8);
+            typedef std::conditional_t<kAsPlanes, uint64_t, u32x4> a_t;
+            typedef std::conditional_t<kAsPlanes, uint64_t, bf16x8> b_t;
+            a_t ha[4];
 #pragma unroll
-            for (int bl = 0; bl < 4; ++bl) ha[bl] = (r >> 2) == bl ? hv : 0ull;
-        }
-        uint32_t mask = 0x0f0f0f0fu;
-        asm volatile("" : "+s"(mask));
-        auto operand = [&](uint32_t w) {
-            uint32_t lo, hi;
-            unpack8_e4m3(w, mask, lo, hi);
-            return (uint64_t)hi << 32 | lo;
-        };
-        // one pass over the window; kReload: the slot is refilled with the tile kWin further on; the last pass
-        // refills nothing
-        auto down_pass = [&](int j0, auto reload) {
-            constexpr bool kReload = decltype(reload)::value;
-#pragma unroll
-            for (int i = 0; i < kWin; ++i) {
-                const int rt = r0 + j0 + i;
-                float sc = scale_of(dpe[i]), zp = SYM ? 8.f : (float)__builtin_bit_cast(_Float16, (uint16_t)(dpe[i] >> 16));
-                uint64_t b0 = operand(win[i].x), b1 = operand(win[i].y), b2 = operand(win[i].z), b3 = operand(win[i].w);
-                if constexpr (kReload) {
-                    compute_here(b0); compute_here(b1); compute_here(b2); compute_here(b3);
-                    compute_here(sc); compute_here(zp);
-                    __builtin_amdgcn_sched_barrier(0);
-                    win[i] = run_load16(dn_run, lane_off + (uint32_t)(j0 + kWin + i) * 1024u);
-                    dpe[i] = entry(dent_run, j0 + kWin + i);
-                    __builtin_amdgcn_sched_barrier(0);
-                }
-                if (rt < r1) {
-                    f32x4 o = (f32x4){0.f, 0.f, 0.f, 0.f};
-                    o = mfma_e4m3(ha[0], b0, o);
-                    o = mfma_e4m3(ha[1], b1, o);
-                    o = mfma_e4m3(ha[2], b2, o);
-                    o = mfma_e4m3(ha[3], b3, o);
-                    constexpr float kStep = 1.f / (1 << kPlaneShift);
-                    const float sum = fmaf(fmaf(fmaf(o[3], kStep, o[2]), kStep, o[1]), kStep, o[0]);
-                    const float val = sc * (sum - zp * hsum) * rw * down;
-                    add_output(rt * 64 + lane, val);
+            for (int bl = 0; bl < 4; ++bl) {
+                if constexpr (kAsPlanes) {
+                    const uint64_t hv = *reinterpret_cast<const uint64_t *>(h_bytes + (r & 3) * 32 + c * 8);
+                    ha[bl] = (r >> 2) == bl ? hv : 0ull;
+                } else {
+                    const u32x4 hv = *reinterpret_cast<const u32x4 *>(&s_h[half][wave][r & 1][c * 8]);
+                    const bool on = (r & 3) < 2 && (r >> 2) == bl;
+                    ha[bl] = (u32x4){on ? hv.x : 0u, on ? hv.y : 0u, on ? hv.z : 0u, on ? hv.w : 0u};
                 }
             }
-        };
-        int j0 = 0;
-        for (; j0 + kWin < ndw; j0 += kWin) down_pass(j0, std::true_type{});
-        down_pass(j0, std::false_type{});
+            uint32_t mask = 0x0f0f0f0fu;
+            asm volatile("" : "+s"(mask));
+            auto operand = [&](uint32_t w) -> b_t {
+                if constexpr (kAsPlanes) {
+                    uint32_t lo, hi;
+                    unpack8_e4m3(w, mask, lo, hi);
+                    return (uint64_t)hi << 32 | lo;
+                } else return unpack8(w, uk);
+            };
+            // one pass over the window; kReload: the slot is refilled with the tile kWin further on; the last pass
+            // refills nothing
+            auto down_pass = [&](int j0, auto reload) {
+                constexpr bool kReload = decltype(reload)::value;
+#pragma unroll
+                for (int i = 0; i < kWin; ++i) {
+                    const int rt = r0 + j0 + i;
+                    float sc = scale_of(dpe[i]), zp = zero_of(dpe[i]) - (kAsPlanes ? 128.f : 0.f);
+                    b_t b0 = operand(win[i].x), b1 = operand(win[i].y), b2 = operand(win[i].z), b3 = operand(win[i].w);
+                    if constexpr (kReload) {
+                        compute_here(b0); compute_here(b1); compute_here(b2); compute_here(b3);
+                        compute_here(sc); compute_here(zp);
+                        __builtin_amdgcn_sched_barrier(0);
+                        win[i] = run_load16(dn_run, lane_off + (uint32_t)(j0 + kWin + i) * 1024u);
+                        dpe[i] = entry(dent_run, j0 + kWin + i);
+                        __builtin_amdgcn_sched_barrier(0);
+                    }
+                    if (rt < r1) {
+                        f32x4 o = (f32x4){0.f, 0.f, 0.f, 0.f};
+                        float val;
+                        if constexpr (kAsPlanes) {
+                            o = mfma_e4m3(ha[0], b0, o);
+                            o = mfma_e4m3(ha[1], b1, o);
+                            o = mfma_e4m3(ha[2], b2, o);
+                            o = mfma_e4m3(ha[3], b3, o);
+                            constexpr float kStep = 1.f / (1 << kPlaneShift);
+                            const float sum = fmaf(fmaf(fmaf(o[3], kStep, o[2]), kStep, o[1]), kStep, o[0]);
+                            val = sc * (sum - zp * hsum) * rw * down;
+                        } else {
+                            o = mfma(ha[0], b0, o);
+                            o = mfma(ha[1], b1, o);
+                            o = mfma(ha[2], b2, o);
+                            o = mfma(ha[3], b3, o);
+                            val = sc * ((o[0] + o[1]) - zp * hsum) * rw;
+                        }
+                        add_output(rt * 64 + lane, val);
+                    }
+                }
+            };
+            int j0 = 0;
+            for (; j0 + kWin < ndw; j0 += kWin) down_pass(j0, std::true_type{});
+            down_pass(j0, std::false_type{});
+        }
         add_both();
     } else if (wave0) {
         first_ticket();
@@ -454,24 +485,36 @@ __device__ __forceinline__ void draft_one_token(const uint16_t *__restrict__ xin
 // 4 waves per SIMD: two workgroups of one item per compute unit, or one of two
 template <int UPG, bool SYM, bool SHARED>
 __global__ __launch_bounds__(kThreads, 4)
-void draft_fused_kernel(const uint16_t *__restrict__ xin, const FusedArgs a) { draft_one_token<UPG, SYM, SHARED, 1>(xin, a); }
+void draft_fused_kernel(const uint16_t *__restrict__ xin, const FusedArgs a) { draft_one_token<UPG, SYM, SHARED, 1, false>(xin, a); }
 template <int UPG, bool SYM, bool SHARED>
 __global__ __launch_bounds__(2 * kThreads, 4)
-void draft_pair_kernel(const uint16_t *__restrict__ xin, const FusedArgs a) { draft_one_token<UPG, SYM, SHARED, 2>(xin, a); }
+void draft_pair_kernel(const uint16_t *__restrict__ xin, const FusedArgs a) { draft_one_token<UPG, SYM, SHARED, 2, false>(xin, a); }
+// pairs with long rows, from which the cut of h into planes gains (three row tiles per wave)
+constexpr int kPlanesFromH = 1536;
+template <int UPG, bool SYM, bool SHARED>
+__global__ __launch_bounds__(2 * kThreads, 4)
+void draft_pair_planes_kernel(const uint16_t *__restrict__ xin, const FusedArgs a) { draft_one_token<UPG, SYM, SHARED, 2, true>(xin, a); }
 
-template <bool SYM, bool SHARED, typename F>
-void slice_kernel(int g, bool pairs, F go)           // go(kernel, items per workgroup)
+template <int UPG, bool SYM, bool SHARED, typename F>
+void slice_kernel(int H, bool pairs, F go)           // go(kernel, items per workgroup)
 {
-    if (g == 32) pairs ? go(draft_pair_kernel<1, SYM, SHARED>, 2) : go(draft_fused_kernel<1, SYM, SHARED>, 1);
-    else if (g == 64) pairs ? go(draft_pair_kernel<2, SYM, SHARED>, 2) : go(draft_fused_kernel<2, SYM, SHARED>, 1);
-    else pairs ? go(draft_pair_kernel<4, SYM, SHARED>, 2) : go(draft_fused_kernel<4, SYM, SHARED>, 1);
+    if (!pairs) go(draft_fused_kernel<UPG, SYM, SHARED>, 1);
+    else if (H < kPlanesFromH) go(draft_pair_kernel<UPG, SYM, SHARED>, 2);
+    else go(draft_pair_planes_kernel<UPG, SYM, SHARED>, 2);
+}
+template <bool SYM, bool SHARED, typename F>
+void slice_kernel(int H, int g, bool pairs, F go)
+{
+    if (g == 32) slice_kernel<1, SYM, SHARED>(H, pairs, go);
+    else if (g == 64) slice_kernel<2, SYM, SHARED>(H, pairs, go);
+    else slice_kernel<4, SYM, SHARED>(H, pairs, go);
 }
 template <typename F>
 void slice_kernel(const Shape &s, const DraftFusedArgs &d, OneTokenForm form, F go)
 {
     const bool pairs = form == kPairsOfItems;
-    if (d.symmetric) { if (d.shared_inside) slice_kernel<true, true>(s.g, pairs, go); else slice_kernel<true, false>(s.g, pairs, go); }
-    else { if (d.shared_inside) slice_kernel<false, true>(s.g, pairs, go); else slice_kernel<false, false>(s.g, pairs, go); }
+    if (d.symmetric) { if (d.shared_inside) slice_kernel<true, true>(s.H, s.g, pairs, go); else slice_kernel<true, false>(s.H, s.g, pairs, go); }
+    else { if (d.shared_inside) slice_kernel<false, true>(s.H, s.g, pairs, go); else slice_kernel<false, false>(s.H, s.g, pairs, go); }
 }
 
 }  // namespace

@@ -67,3 +67,10 @@ def test_loads_to_lds_do_not_follow_the_write_of_m0_directly(src):
     assert loads, "the loads to LDS are gone?"
     for before, load in loads:
         assert not re.search(r"\bm0\b", before), (before, load)
+
+
+def test_kernel_of_pairs_with_long_rows_does_not_spill():
+    blocks = _kernel_blocks(_assembly("draft_slice.hip"), "draft_pair_planes_kernel")
+    assert len(blocks) == 12                           # with and without shared experts x 3 group sizes x 2 formats
+    for blk in blocks:
+        assert int(re.search(r"\.vgpr_spill_count:\s+(\d+)", blk).group(1)) == 0, blk.split("\n", 1)[0].strip()

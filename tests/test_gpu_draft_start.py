@@ -201,3 +201,27 @@ def test_shared_experts_on_the_line_run_inside(H, I, k, S, g, inside):
     assert rel_err(to_np(r["y"]), ref["y"]) <= TOL_DRAFT
     assert launches["draft_fused_kernel"] == 1 and launches["bf16_gateup_kernel"] == (0 if inside else 1)
     ctx.close()
+
+
+@pytest.mark.parametrize("H,g,S", [(1472, 32, 0), (1536, 32, 0), (1600, 64, 0), (1536, 128, 0), (1472, 64, 2), (1536, 64, 2), (1600, 32, 2)])
+def test_pairs_around_the_line_of_long_rows(H, g, S):
+    """Pairs carry h as two bf16 numbers up to H = 1472 and as four e4m3 planes from 1536 on (three row tiles per wave; at 1600 one wave has four): 272 items, and
+    128 with two shared experts of 128 each beside them."""
+    cfg = LayerConfig(83, "line%d" % H, H, 4, 4352 if S == 0 else 2048, 2, g, S, 1)
+    assert one_token_form(cfg) == (S > 0, 1)
+    ctx = B.Context(0)
+    for symmetric in (False, True):
+        if symmetric and B.int4_expert_scale_bytes(B.LayerDesc.from_config(cfg)) == 0:
+            continue
+        L = synth.make_layer(cfg, 0, symmetric=symmetric)
+        A = oracle_arrays(L)
+        D = DeviceLayer(ctx, cfg, L, max_tokens=1, verify=False, symmetric=symmetric)
+        x = tokens_with_clear_routing(cfg, A, 2, step=6)
+        ref = oracle_draft(A, x)
+        for t in (0, 1, 0):
+            say("line H", H, "g", g, "S", S, "symmetric" if symmetric else "", "token", t)
+            r = D.draft(x[t:t + 1].cuda())
+            torch.cuda.synchronize()
+            assert np.array_equal(to_np(r["ids"]), ref["ids"][t:t + 1])
+            assert rel_err(to_np(r["y"]), ref["y"][t:t + 1]) <= TOL_DRAFT
+    ctx.close()
