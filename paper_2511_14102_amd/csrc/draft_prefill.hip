@@ -1240,17 +1240,20 @@ static TileArgs tile_args(const Shape &s, const PrefillCall &p)
 // leaving some of them with other amounts of work (shared experts, short rests).  us per pass, items of all experts column by column as it was / blocks of two /
 // eight, striped:  dsv2lite, 333 tokens 570 / 556 / 571; 1200 1290 / 1226 / 1280; qwen3, 512 629 / 599 / 625; qwen15, 700 874 / 840 / 878; H = 1024, E = 24, I = 2048, 900
 // 481 / 453 / 474; phi, 512 609 / 610 / 600, 2048 1793 / 1744 / 1732; phi, 150 423 / 425 / 413; mixtral, 512 605 / 613 / 589, 4096 3455 / 3594 / 3331; H = 2048, E = 6, I = 4096, a shared
-// expert, 2500 1312 / 1344 / 1285.  In the down launch the two differ by less than 1 %, and h is as many bytes as the weights: blocks of two.
-static void prefill_blocks(TileArgs &t, bool down)
+// expert, 2500 1312 / 1344 / 1285.  In the down launch the two differ by less than 1 %, and h is as many bytes as the weights: blocks of two.  Also striped, in both
+// launches: many rounds of short routed items behind the shared experts' long ones, which one XCD would have to itself (H = 1728, E = 102, I = 1984, k = 8, two
+// shared, 292 tokens 238 / 278 / 234).
+static void prefill_blocks(TileArgs &t, const Shape &s, bool down)
 {
-    t.striped = !down && t.I >= 4096;
+    const bool short_behind_shared = s.S > 0 && s.T * s.k < kItemTokens * s.E && (long)prefill_columns(s) * items_of(s, kItemTokens) >= 7 * 256;
+    t.striped = (!down && t.I >= 4096) || short_behind_shared;
     t.block = t.striped ? 8 : 2;
 }
 
 void launch_prefill_gateup(const Shape &s, const PrefillCall &p, int max_items, hipStream_t st)
 {
     TileArgs t = tile_args(s, p);
-    prefill_blocks(t, false);
+    prefill_blocks(t, s, false);
     t.act = (const char *)p.xt; t.act_sums = (const char *)p.x_sums; t.act_scales = nullptr;
     launch_tile<false>(t, p.symmetric != 0, s.g, s.I / 32, max_items, st);
 }
@@ -1258,7 +1261,7 @@ void launch_prefill_gateup(const Shape &s, const PrefillCall &p, int max_items, 
 void launch_prefill_down(const Shape &s, const PrefillCall &p, int max_items, hipStream_t st)
 {
     TileArgs t = tile_args(s, p);
-    prefill_blocks(t, true);
+    prefill_blocks(t, s, true);
     t.act = (const char *)p.h; t.act_sums = (const char *)p.h_sums; t.act_scales = (const char *)p.h_scales;
     launch_tile<true>(t, p.symmetric != 0, s.g, s.H / 64, max_items, st);
 }
