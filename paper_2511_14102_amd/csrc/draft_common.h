@@ -302,10 +302,11 @@ __device__ inline uint32_t ticket_members(uint32_t b, uint32_t grid) { return (g
 __device__ inline uint32_t ticket_groups(uint32_t grid) { return grid < (uint32_t)kTicketGroups ? grid : (uint32_t)kTicketGroups; }
 // `threads` threads, of which the calling one is number `me`, put slots and tickets back to idle
 __device__ inline void reset_exchange(const FusedArgs &a, int me, int threads) {
-    const int n = a.T * a.E;
-    for (int rep = 0; rep < 1 << exchange_copies_lg(a.E); ++rep)
-        for (int i = me; i < n; i += threads)
-            __hip_atomic_store(a.slots + (size_t)rep * a.replica_stride + 2 * (size_t)i + 1, 0ull, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    // (all copies of a slot by neighbouring threads: copy by copy, few experts' stores were sixteen rounds one after another at the
+    // kernel's end; us per pass, copy by copy / now: H = 640, E = 6 219.5 / 209.7, H = 1280, E = 5 324.2 / 316.9)
+    const int lg = exchange_copies_lg(a.E), n = (a.T * a.E) << lg;
+    for (int i = me; i < n; i += threads)
+        __hip_atomic_store(a.slots + (size_t)(i & ((1 << lg) - 1)) * a.replica_stride + 2 * (size_t)(i >> lg) + 1, 0ull, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
     if (me <= kTicketGroups) __hip_atomic_store(a.tickets + me, 0u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
 }
 
