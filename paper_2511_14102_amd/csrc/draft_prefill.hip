@@ -66,12 +66,12 @@
 //
 // Bound and figures (gate/up and down kernel; first form: two row blocks per wave, operand tiles through
 // registers, offset 128, two multiply-adds per group).  Many tokens per expert: the matrix cores.
-// mixtral shape, 4096 tokens: 2122 and 1672 us, 907 and 1150 TFLOP/s counting both planes of h
-// (first form: 3750 and 2933 us; a large library product reaches 1250 on this part).  phi shape, 512 tokens:
-// 182 and 135 us (406 and 261), the matrix cores busy 29 and 40 % of it and the vector ALU 44 and 34 %: between the two bounds, a
+// mixtral shape, 4096 tokens: 2221 and 1703 us (under the profiler; the whole call 3685, with h as two bf16 numbers, column by column 3741; the clock falls to 1.6 to 1.8 GHz)
+// (first form: 3750 and 2933 us).  phi shape, 512 tokens:
+// 182 and 127 us (406 and 261), the matrix cores busy 29 and 44 % of it and the vector ALU 46 and 28 %: between the two bounds, a
 // wave waits for its turn at an instruction 38 % of its time and for data 19 %.  Few tokens per expert: the weight stream.
-// dsv2lite shape, 333 tokens (31 per expert), with its shared experts in the same launches: 65 and 55 us for 219 and 110 MB (routed
-// experts alone, first form: 99 and 66); matrix cores 23 and 29 %, waiting for data 23 and 28 %.
+// dsv2lite shape, 333 tokens (31 per expert), with its shared experts in the same launches: 66 and 49 us for 219 and 110 MB (routed
+// experts alone, first form: 99 and 66); matrix cores 23 and 31 %, waiting for data 22 and 28 %.
 #include <hip/hip_runtime.h>
 #include "draft_common.h"
 
